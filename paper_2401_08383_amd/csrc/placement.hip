@@ -10,8 +10,7 @@
 //   placement_locality_from_counts : GPU, scores a BATCH of candidate maps against the counts.
 //       One workgroup per (layer pair, slice of candidates) keeps the pair's E x E counts in LDS;
 //       a wavefront takes one candidate at a time: lane p holds the part of expert p at layer l+1,
-//       walks the E source experts (their parts broadcast by shuffle) and adds the counts of the
-//       pairs that share a part; 64-bit integer arithmetic throughout, so the result is exact.
+//       walks the source experts of that part and adds their counts; exact integer arithmetic.
 //   exf_placement_search           : host.  The paper names no solver; this one is
 //       - exact when the number of balanced partitions of a layer is small: the objective is a
 //         chain over layers, so a dynamic programme over (layer, partition) finds the optimum;
@@ -30,48 +29,139 @@
 
 namespace exf {
 
-constexpr int kScoreThreads = 256;
+constexpr int kScoreThreads = 512;
 constexpr int kScoreWaves = kScoreThreads / kWave;
-constexpr int kScoreSlice = 64;  // candidates per workgroup
+constexpr int kScoreBatch = 4;          // candidates of a wavefront whose maps are in flight together
+constexpr int kScoreMaxPerWave = 32;    // candidates a wavefront scores at most
+constexpr int kScoreWorkgroups = 1024;  // four workgroups fill a compute unit's wavefront slots: slices are cut for one round
 
+// Position of the lowest set bit of a word, 0xffffffff for zero (what the instruction gives).
+__device__ __forceinline__ uint32_t lowest_bit(uint32_t v)
+{
+    uint32_t r = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(v));
+#endif
+    return r;
+}
+
+// Walks the set bits of m (source experts that share this lane's part) and adds their counts.  A lane
+// that has run out reads the zero row behind the table, so the loads carry no condition; four
+// are in flight together.
+constexpr int kScoreStride = kWave;  // entries from row to row of the table in LDS (a shift instead of a multiplication)
+template <typename Acc>
+__device__ __forceinline__ Acc add_matching_rows(const Acc* __restrict__ table, unsigned long long m, int lane)
+{
+    Acc acc = 0;
+    while (__ballot(m != 0ull) != 0ull) {
+        Acc v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t in_low = lowest_bit(static_cast<uint32_t>(m)), in_high = lowest_bit(static_cast<uint32_t>(m >> 32)) | 32u;
+            const uint32_t i = min(min(in_low, in_high), static_cast<uint32_t>(kWave));
+            m &= m - 1ull;  // (0 stays 0)
+            v[u] = table[i * kScoreStride + lane];
+        }
+        acc += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    return acc;
+}
+
+// Lane p of a wavefront needs sum_i counts[i][p] over the source experts i whose part equals its own.
+// The set of these i is built with one pair of ballots per bit of the part numbers (three bits for eight
+// parts) and then walked: E/G steps per candidate instead of E conditional ones, each a conflict-free LDS read
+// (the bank is a function of p alone).  When the counts of the pair add up to less than 2^31 - any trace
+// below two billion tokens - table and sums are 32 bits wide.  4096 maps of 24 layers x 64 experts on 8
+// parts: 222 us with the E-step walk, 27 now; the maps (25 MB) are read twice, once from the L2.
 __global__ __launch_bounds__(kScoreThreads) void placement_score_kernel(const int64_t* __restrict__ counts,
                                                                          const int32_t* __restrict__ placements, int B, int L, int E,
-                                                                         int64_t* __restrict__ local)
+                                                                         int slice, int64_t* __restrict__ local)
 {
-    extern __shared__ long long cnt_lds[];  // [E][E] counts of this layer pair
-    const int l = blockIdx.y;  // layer pair on y (at most 255), candidate slices on x (up to 2^18)
+    extern __shared__ unsigned long long cnt_lds[];  // [65][64]: the pair's counts, row = source expert; row 64 is zero (32- or 64-bit entries)
+    __shared__ unsigned long long pair_sum[kScoreWaves];
+    const int l = blockIdx.y;  // layer pair on y (at most 255), candidate slices on x
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int b_begin = static_cast<int>(blockIdx.x) * slice;
+    const int b_end = min(B, b_begin + slice);
+    // parts of a candidate's experts at layers l (lane = source expert) and l+1 (lane = target expert); the rows
+    // of the wavefront's next kScoreBatch candidates are requested before the current ones are scored (one
+    // candidate ahead left the launch waiting for memory: 28.7 us)
+    auto load_batch = [&](int cand, int (&from)[kScoreBatch], int (&to)[kScoreBatch]) {
+        const int e = min(lane, E - 1);
+#pragma unroll
+        for (int u = 0; u < kScoreBatch; ++u) {
+            const int c = min(cand + u * kScoreWaves, B - 1);
+            const int32_t* row = placements + (static_cast<size_t>(c) * L + l) * E;
+            from[u] = row[e];
+            to[u] = row[E + e];
+        }
+    };
+    int cur_from[kScoreBatch], cur_to[kScoreBatch];
+    load_batch(b_begin + wave, cur_from, cur_to);
+
+    // counts of the pair: a wavefront takes every eighth row, all rows requested at once
+    constexpr int PER = EXF_MAX_EXPERTS / kScoreWaves;
     const int64_t* src = counts + static_cast<size_t>(l) * E * E;
-    for (int i = threadIdx.x; i < E * E; i += kScoreThreads) cnt_lds[i] = src[i];
+    int64_t c[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) c[u] = src[min(wave + u * kScoreWaves, E - 1) * E + min(lane, E - 1)];
+    bool small = true;
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (wave + u * kScoreWaves >= E || lane >= E) c[u] = 0;
+        small = small && static_cast<unsigned long long>(c[u]) < (1ull << 32);
+        sum += static_cast<unsigned long long>(c[u]) & 0xffffffffull;  // at most 4096 terms below 2^32: no wrap
+    }
+    sum = wave_sum(sum);
+    if (__ballot(!small) != 0ull) sum = ~0ull >> 8;  // (eight such values do not wrap either)
+    if (lane == 0) pair_sum[wave] = sum;
+    __syncthreads();
+    sum = 0;
+#pragma unroll
+    for (int w = 0; w < kScoreWaves; ++w) sum += pair_sum[w];
+    const bool narrow = __builtin_amdgcn_readfirstlane(sum < (1ull << 31) ? 1 : 0) != 0;
+    uint32_t* cnt32 = reinterpret_cast<uint32_t*>(cnt_lds);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int at = (wave + u * kScoreWaves) * kScoreStride + lane;
+        if (narrow) cnt32[at] = static_cast<uint32_t>(c[u]);
+        else cnt_lds[at] = static_cast<unsigned long long>(c[u]);
+    }
+    if (threadIdx.x < kWave) {
+        if (narrow) cnt32[kWave * kScoreStride + threadIdx.x] = 0u;
+        else cnt_lds[kWave * kScoreStride + threadIdx.x] = 0ull;
+    }
     __syncthreads();
 
-    const int lane = lane_id();
-    const int wave = threadIdx.x / kWave;
-    const int b_end = min(B, (static_cast<int>(blockIdx.x) + 1) * kScoreSlice);
-    int b = static_cast<int>(blockIdx.x) * kScoreSlice + wave;
-    // parts of the candidate's experts at layers l (lane = source expert) and l+1 (lane = target expert);
-    // the next candidate's two rows are requested before the current one is scored
-    auto load_rows = [&](int cand, int& cur_row, int& nxt_row) {
-        const int c = min(cand, B - 1);
-        const int e = min(lane, E - 1);
-        const int32_t* row = placements + (static_cast<size_t>(c) * L + l) * E;
-        cur_row = row[e];
-        nxt_row = row[E + e];
-    };
-    int part_l = 0, part_l1 = 0;
-    if (b < b_end) load_rows(b, part_l, part_l1);
-    while (b < b_end) {
-        int next_l = 0, next_l1 = 0;
-        load_rows(b + kScoreWaves, next_l, next_l1);
-        long long acc = 0;
-        for (int i = 0; i < E; ++i) {
-            const int pi = __shfl(part_l, i, kWave);
-            if (lane < E && pi == part_l1) acc += cnt_lds[i * E + lane];
+    const unsigned long long experts = E == kWave ? ~0ull : (1ull << E) - 1ull;
+    for (int b0 = b_begin + wave; b0 < b_end; b0 += kScoreBatch * kScoreWaves) {
+        int nxt_from[kScoreBatch], nxt_to[kScoreBatch];
+        load_batch(b0 + kScoreBatch * kScoreWaves, nxt_from, nxt_to);
+#pragma unroll
+        for (int u = 0; u < kScoreBatch; ++u) {
+            const int b = b0 + u * kScoreWaves;
+            if (b >= b_end) break;
+            const unsigned from = static_cast<unsigned>(cur_from[u]), to = static_cast<unsigned>(cur_to[u]);
+            unsigned long long m = lane < E ? experts : 0ull;
+            for (int bit = 0; bit < 32 && __ballot(((from | to) >> bit) != 0u) != 0ull; ++bit) {
+                const unsigned long long set = __ballot(((from >> bit) & 1u) != 0u);
+                m &= ((to >> bit) & 1u) != 0u ? set : ~set;
+            }
+            if (narrow) {
+                const int acc = wave_inclusive_scan(static_cast<int>(add_matching_rows<uint32_t>(cnt32, m, lane)));
+                if (lane == kWave - 1) local[static_cast<size_t>(b) * (L - 1) + l] = acc;
+            } else {
+                const unsigned long long acc = wave_sum(add_matching_rows<unsigned long long>(cnt_lds, m, lane));
+                if (lane == 0) local[static_cast<size_t>(b) * (L - 1) + l] = static_cast<int64_t>(acc);
+            }
         }
-        acc = wave_sum(acc);
-        if (lane == 0) local[static_cast<size_t>(b) * (L - 1) + l] = acc;
-        part_l = next_l;
-        part_l1 = next_l1;
-        b += kScoreWaves;
+#pragma unroll
+        for (int u = 0; u < kScoreBatch; ++u) {
+            cur_from[u] = nxt_from[u];
+            cur_to[u] = nxt_to[u];
+        }
     }
 }
 
@@ -301,10 +391,16 @@ extern "C" int placement_locality_from_counts(const int64_t* counts, const int32
     EXF_REQUIRE_PTR(counts);
     EXF_REQUIRE_PTR(placements);
     EXF_REQUIRE_PTR(local);
-    const dim3 grid(static_cast<unsigned>((B + kScoreSlice - 1) / kScoreSlice), static_cast<unsigned>(L - 1));
-    const size_t lds = static_cast<size_t>(E) * E * sizeof(long long);
+    // candidates per workgroup: one round of kScoreWorkgroups workgroups (a small batch is spread over the
+    // chip), at most kScoreMaxPerWave per wavefront
+    const int64_t slots = static_cast<int64_t>(kScoreWorkgroups / (L - 1)) * kScoreWaves;  // (L - 1 <= 255)
+    int64_t per_wave = (B + slots - 1) / slots;
+    if (per_wave > kScoreMaxPerWave) per_wave = kScoreMaxPerWave;
+    const int slice = static_cast<int>(per_wave) * kScoreWaves;
+    const dim3 grid(static_cast<unsigned>((B + slice - 1) / slice), static_cast<unsigned>(L - 1));
+    const size_t lds = static_cast<size_t>(kWave + 1) * kScoreStride * sizeof(long long);
     hipLaunchKernelGGL(placement_score_kernel, grid, dim3(kScoreThreads), lds, static_cast<hipStream_t>(stream), counts, placements, B, L,
-                       E, local);
+                       E, slice, local);
     return check_launch("placement_locality_from_counts");
 }
 

@@ -1,0 +1,47 @@
+"""Edges of the kernels' tiles and of their dispatch rules, against the same oracles and rules as the other GPU tests."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import synth_inputs as syn
+import test_gpu_parity as P
+import test_placement_search as Q
+from paper_2401_08383_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(f"[case] {msg}", flush=True)
+
+
+# ----------------------------------------------------------------------------- trace columns of any length
+@pytest.mark.parametrize("N", [3, 4, 5, 6, 7, 4097, 8190, 61441, 61443])
+def test_trace_columns_that_start_and_end_anywhere(oracle, N):
+    """Columns off the 16-byte grid, last vectors cut by one to three ids, last chunks shorter than a vector."""
+    P.test_affinity_and_locality_parity(oracle, 5, N, 24, 8)
+    Q.test_affinity_multihop_parity(4, N, 24)
+    Q.test_routing_transfers_parity(5, N, 24, 8)
+
+
+# ----------------------------------------------------------------------------- candidate scores
+@pytest.mark.parametrize("E,Bn,total", [(1, 1, 5), (33, 9, (1 << 31) - 1), (33, 9, 1 << 31), (64, 300, (1 << 31) - 1), (64, 300, 1 << 33),
+                                        (63, 4099, 100000)])
+def test_candidate_scores_around_the_32_bit_table(E, Bn, total):
+    """Pair totals on both sides of the limit of the 32-bit table, parts of any sign and size, one part for all experts."""
+    _say(f"placement_locality_from_counts E={E} B={Bn} total={total}")
+    L = 3
+    g = syn.rng(1200 + E + Bn)
+    counts = np.zeros((L - 1, E, E), dtype=np.int64)
+    for l in range(L - 1):
+        cell = total // (E * E)
+        counts[l] = cell
+        counts[l, g.integers(0, E), g.integers(0, E)] += total - cell * E * E
+        assert counts[l].sum() == total
+    maps = g.choice(np.array([0, 1, 5, 1 << 20, -1, -(1 << 31)], dtype=np.int64), size=(Bn, L, E)).astype(np.int32)
+    maps[0] = 7
+    got = B.placement_locality_from_counts(torch.from_numpy(counts).cuda(), torch.from_numpy(maps).cuda()).cpu().numpy()
+    assert got[0].tolist() == [total] * (L - 1)
+    for b in range(0, Bn, max(1, Bn // 100)):
+        np.testing.assert_array_equal(got[b], O.placement_locality_from_counts(counts, maps[b]))
