@@ -36,6 +36,9 @@ constexpr size_t kAffHistBudget = 48 * 1024;    // LDS bytes for the packed pair
 constexpr int64_t kAffMaxChunk = 61440;         // tokens per workgroup: 16-bit counters cannot overflow
 constexpr int kTargetWorkgroups = 256;          // about one per CU
 
+// Ids per load of a trace column: four, except that a column of fewer has no vector to load.
+static int trace_vec(int64_t N) { return N >= 4 ? 4 : 1; }
+
 struct AffinityPlan {
     int g;           // layer pairs per workgroup
     int Q;           // pair groups
@@ -43,11 +46,11 @@ struct AffinityPlan {
     int words;       // 32-bit words of one packed E x E histogram
     int64_t chunk;   // tokens per workgroup
     int C;           // token chunks
-    int vec;         // 4 if 16-byte trace loads are possible, else 1
+    int vec;         // ids per trace load
     size_t off_counts, off_orphan_next, off_orphan_last, off_invalid, off_local, total_bytes;
 };
 
-static AffinityPlan make_affinity_plan(int L, int64_t N, int E, bool aligned)
+static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
 {
     AffinityPlan p;
     const int pairs = L > 1 ? L - 1 : 0;
@@ -61,7 +64,7 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E, bool aligned)
     p.copies = 1;
     while (p.copies < 16 && hist_bytes * g * (p.copies * 2) <= kAffHistBudget) p.copies *= 2;
     p.Q = pairs > 0 ? (pairs + g - 1) / g : 1;
-    p.vec = (aligned && N % 4 == 0) ? 4 : 1;
+    p.vec = trace_vec(N);
     const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;  // tokens one pass of the workgroup covers
     int c_target = kTargetWorkgroups / p.Q;
     if (c_target < 1) c_target = 1;
@@ -95,15 +98,18 @@ struct TokVec {
 // the end of its chunk re-reads the chunk's last vector (the caller masks such lanes through its own
 // range test).  Keeping branches away from the loads matters: with a branch around each of them the
 // compiler can no longer count the loads in flight and waits for all earlier ones before every new
-// one, which leaves a single load in flight per wavefront.  With VEC = 4 the column base, n and end
-// are multiples of four, so a vector is never cut by the end of the chunk.
+// one, which leaves a single load in flight per wavefront.
+// A column starts at any multiple of four bytes (its length is the number of tokens, any number): the
+// 16-byte load of gfx950 needs no more, and it costs one more cache line per wavefront when it straddles.
+// (Odd token counts used to take 4-byte loads: 44 us for the transfers of a 24 x 999983 trace, 22 now.)
+// A lane whose vector is cut by the end of the chunk receives the LAST VEC ids; cut_vector() moves them.
 template <int VEC>
 __device__ __forceinline__ TokVec<VEC> load_tokens(const int32_t* __restrict__ col, int64_t n, int64_t end)
 {
     TokVec<VEC> r;
-    const int64_t n_safe = min(n, end - VEC);  // callers guarantee end - begin >= VEC
+    const int64_t n_safe = min(n, end - VEC);  // callers guarantee end >= VEC; earlier chunks may be touched
     if constexpr (VEC == 4) {
-        typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4_v;
+        typedef int i32x4_v __attribute__((vector_size(4 * sizeof(int)), aligned(4)));
         const i32x4_v q = __builtin_nontemporal_load(reinterpret_cast<const i32x4_v*>(col + n_safe));  // streamed once
         r.v[0] = q[0];
         r.v[1] = q[1];
@@ -113,6 +119,26 @@ __device__ __forceinline__ TokVec<VEC> load_tokens(const int32_t* __restrict__ c
         r.v[0] = __builtin_nontemporal_load(col + n_safe);
     }
     return r;
+}
+
+// The ids of tokens n, n+1, .. in v[0], v[1], .. again, for a lane with n < end < n + VEC (other lanes
+// are not changed; ids past the end are whatever is left, the caller's range test drops them).
+template <int VEC>
+__device__ __forceinline__ void cut_vector(TokVec<VEC>& t, int64_t n, int64_t end)
+{
+    if constexpr (VEC == 4) {
+        const int64_t by = n - (end - VEC);
+        const bool one = by == 1 || by == 3, two = by == 2 || by == 3;
+        if (one) {
+            t.v[0] = t.v[1];
+            t.v[1] = t.v[2];
+            t.v[2] = t.v[3];
+        }
+        if (two) {
+            t.v[0] = t.v[2];
+            t.v[1] = t.v[3];
+        }
+    }
 }
 
 template <int VEC>
@@ -184,7 +210,12 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
             for (int u = 0; u < VEC; ++u) m = max(m, static_cast<unsigned>(col[s].v[u]));
             clean = clean && m < static_cast<unsigned>(E);
         }
-        if (__ballot(!clean) == 0ull && L > 1) {
+        const bool all_clean = __ballot(!clean) == 0ull;
+        if (!all_clean) {
+#pragma unroll
+            for (int s = 0; s <= kAffMaxGroup; ++s) cut_vector(col[s], n0, n_end);
+        }
+        if (all_clean && L > 1) {
 #pragma unroll
             for (int s = 1; s <= kAffMaxGroup; ++s) {
                 if (l0 + s > l1) break;
@@ -339,6 +370,8 @@ __global__ __launch_bounds__(kTraceThreads) void multihop_partial_kernel(const i
                 }
             }
         } else {
+#pragma unroll
+            for (int s = 0; s <= kAffMaxGroup; ++s) cut_vector(col[s], n0, n_end);
 #pragma unroll
             for (int s = 1; s <= kAffMaxGroup; ++s) {
                 if (s > my_pairs) break;
@@ -502,7 +535,11 @@ __global__ __launch_bounds__(kTraceThreads) void locality_partial_kernel(const i
         TokVec<VEC> hm;
         if constexpr (HOME) hm = load_tokens<VEC>(home, n0, n_end);
         {
-            const TokVec<VEC> t = load_tokens<VEC>(trace, n0, n_end);
+            TokVec<VEC> t = load_tokens<VEC>(trace, n0, n_end);
+            if (__ballot(!in_range) != 0ull) {
+                cut_vector(t, n0, n_end);
+                if constexpr (HOME) cut_vector(hm, n0, n_end);
+            }
             prev_clean = in_range;
             int away = 0;
 #pragma unroll
@@ -547,6 +584,7 @@ __global__ __launch_bounds__(kTraceThreads) void locality_partial_kernel(const i
                         dev_prev[u] = dev;
                     }
                 } else {
+                    cut_vector(cur[a], n0, n_end);
 #pragma unroll
                     for (int u = 0; u < VEC; ++u) {
                         const bool ok = (n0 + u < n_end) && static_cast<unsigned>(cur[a].v[u]) < static_cast<unsigned>(E);
@@ -624,10 +662,7 @@ static int allow_large_lds(Kern kern, size_t bytes, const char* what)
 extern "C" size_t affinity_histogram_workspace_bytes(int L, int64_t N, int E)
 {
     if (L < 1 || N < 0 || E < 1 || E > EXF_MAX_EXPERTS) return 0;
-    // the aligned and unaligned plans differ only in chunk granularity; size for the larger one
-    const size_t a = exf::make_affinity_plan(L, N, E, true).total_bytes;
-    const size_t b = exf::make_affinity_plan(L, N, E, false).total_bytes;
-    return a > b ? a : b;
+    return exf::make_affinity_plan(L, N, E).total_bytes;
 }
 
 namespace exf {
@@ -639,7 +674,7 @@ static int run_affinity(const char* fn, const int32_t* trace, const int32_t* pla
                         int64_t* loads, float* cond_prob, int64_t* n_invalid, int64_t* local_per_pair, void* workspace,
                         size_t workspace_bytes, void* stream)
 {
-    const AffinityPlan p = make_affinity_plan(L, N, E, aligned16(trace));
+    const AffinityPlan p = make_affinity_plan(L, N, E);
     if (workspace_bytes < p.total_bytes) return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "%s: workspace %zu < %zu bytes", fn, workspace_bytes, p.total_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
@@ -712,7 +747,7 @@ struct MultihopPlan {
     int64_t chunk;
     size_t total_bytes;
 };
-static MultihopPlan make_multihop_plan(int L, int64_t N, int E, bool aligned)
+static MultihopPlan make_multihop_plan(int L, int64_t N, int E)
 {
     MultihopPlan p;
     p.pairs = L * (L - 1) / 2;
@@ -727,7 +762,7 @@ static MultihopPlan make_multihop_plan(int L, int64_t N, int E, bool aligned)
     p.Q = 0;
     for (int l = 0; l + 1 < L; ++l) p.Q += (L - 1 - l + g - 1) / g;
     if (p.Q < 1) p.Q = 1;
-    p.vec = (aligned && N % 4 == 0) ? 4 : 1;
+    p.vec = trace_vec(N);
     const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;
     int c_target = kTargetWorkgroups / p.Q;
     if (c_target < 1) c_target = 1;
@@ -745,9 +780,7 @@ static MultihopPlan make_multihop_plan(int L, int64_t N, int E, bool aligned)
 extern "C" size_t affinity_multihop_workspace_bytes(int L, int64_t N, int E)
 {
     if (L < 1 || N < 0 || E < 1 || E > EXF_MAX_EXPERTS) return 0;
-    const size_t a = exf::make_multihop_plan(L, N, E, true).total_bytes;
-    const size_t b = exf::make_multihop_plan(L, N, E, false).total_bytes;
-    return a > b ? a : b;
+    return exf::make_multihop_plan(L, N, E).total_bytes;
 }
 
 extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, int64_t* counts, float* cond_prob, void* workspace,
@@ -759,7 +792,7 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
     if (N > 0) EXF_REQUIRE_PTR(trace);
     EXF_REQUIRE_PTR(counts);
     EXF_REQUIRE_PTR(workspace);
-    const MultihopPlan p = make_multihop_plan(L, N, E, aligned16(trace));
+    const MultihopPlan p = make_multihop_plan(L, N, E);
     if (workspace_bytes < p.total_bytes)
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "affinity_multihop: workspace %zu < %zu bytes", workspace_bytes, p.total_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -790,7 +823,7 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
 extern "C" size_t placement_locality_workspace_bytes(int L, int64_t N)
 {
     if (L < 1 || N < 0) return 0;
-    const int64_t chunk = exf::locality_chunk(N, 1);  // the scalar plan has the most chunks
+    const int64_t chunk = exf::locality_chunk(N, exf::trace_vec(N));
     const int64_t C = N > 0 ? (N + chunk - 1) / chunk : 0;
     return exf::align_up(static_cast<size_t>(C > 0 ? C : 1) * static_cast<size_t>(L > 1 ? L - 1 : 1) * sizeof(uint32_t), 256);
 }
@@ -810,7 +843,7 @@ extern "C" int placement_locality(const int32_t* trace, const int32_t* placement
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "placement_locality: workspace %zu < %zu bytes", workspace_bytes,
                     placement_locality_workspace_bytes(L, N));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int vec = (aligned16(trace) && N % 4 == 0) ? 4 : 1;
+    const int vec = trace_vec(N);
     const int64_t chunk = locality_chunk(N, vec);
     const int C = static_cast<int>(N > 0 ? (N + chunk - 1) / chunk : 0);
     uint32_t* part = static_cast<uint32_t*>(workspace);
@@ -833,7 +866,7 @@ extern "C" int placement_locality(const int32_t* trace, const int32_t* placement
 extern "C" size_t routing_transfers_workspace_bytes(int L, int64_t N)
 {
     if (L < 1 || N < 0) return 0;
-    const int64_t chunk = exf::locality_chunk(N, 1);  // the scalar plan has the most chunks
+    const int64_t chunk = exf::locality_chunk(N, exf::trace_vec(N));
     const int64_t C = N > 0 ? (N + chunk - 1) / chunk : 0;
     return exf::align_up(static_cast<size_t>(C > 0 ? C : 1) * static_cast<size_t>(2 * L - 1) * sizeof(uint32_t), 256);
 }
@@ -857,7 +890,7 @@ extern "C" int routing_transfers(const int32_t* trace, const int32_t* placement,
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "routing_transfers: workspace %zu < %zu bytes", workspace_bytes,
                     routing_transfers_workspace_bytes(L, N));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int vec = (aligned16(trace) && aligned16(home) && N % 4 == 0) ? 4 : 1;
+    const int vec = trace_vec(N);
     const int64_t chunk = locality_chunk(N, vec);
     const int C = static_cast<int>(N > 0 ? (N + chunk - 1) / chunk : 0);
     uint32_t* part = static_cast<uint32_t*>(workspace);
