@@ -26,48 +26,10 @@
 //     short launch of tiles of different heights), every kind of tile is split evenly instead.
 //   - remainder ("tail") tiles of the second contraction are cut into K slices when there are few of
 //     them, and a small kernel adds the slices (see TileSchedule).
-// fp32 kernel: LDS-tiled 64x64x16, 4x4 outputs per thread (tiny configuration; latency bound).
-#include <math.h>
-
-#include "common.hpp"
+// fp32 and few rows per expert: ffn_stream.hip.
+#include "ffn_common.hpp"
 
 namespace exf {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-
-constexpr int kXcdCount = 8;
-
-// ---------------------------------------------------------------------------- activations
-__device__ __forceinline__ float gelu_erf_exact(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752440f)); }
-__device__ __forceinline__ float gelu_tanh_exact(float z)
-{
-    return 0.5f * z * (1.0f + tanhf(0.79788456080286535588f * (z + 0.044715f * z * z * z)));
-}
-
-// bf16 path: z * Phi(z) with the normal CDF evaluated as a logistic function of an odd
-// polynomial,  Phi(z) ~ 1 / (1 + exp(-z (c0 + c1 z^2 + c2 z^4))),  coefficients fitted (minimax
-// on [-10,10]) to the exact erf form: max |error| of the GELU value is 2.6e-5, two orders of
-// magnitude below the bf16 rounding the result receives next.  z^2 is clamped where the logistic
-// has long saturated, so that the quartic term cannot turn the polynomial around.
-__device__ __forceinline__ float gelu_erf_fast(float z)
-{
-    const float t = fminf(z * z, 60.0f);
-    // coefficients carry the factor -log2(e): exp(-z p(t)) = 2^(z q(t)), one v_exp_f32
-    float q = fmaf(1.01407394e-3f, t, -1.06774916e-1f);
-    q = fmaf(q, t, -2.30112032f);
-    const float e = __builtin_amdgcn_exp2f(z * q);
-    return z * __builtin_amdgcn_rcpf(1.0f + e);  // v_rcp_f32: 1 ulp
-}
-// z/2 (1 + tanh u) = z / (1 + exp(-2u))
-__device__ __forceinline__ float gelu_tanh_fast(float z)
-{
-    const float u = 0.79788456080286535588f * (z + 0.044715f * z * z * z);
-    return z * __builtin_amdgcn_rcpf(1.0f + __expf(-2.0f * u));
-}
-
-enum Epilogue { kEpiNone = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2 };
-
 
 // ---------------------------------------------------------------------------- tile lookup
 // Rows of expert e are cut into "full" row tiles of MT rows.  A remainder of at most MT/2 rows is
@@ -399,48 +361,6 @@ __device__ __forceinline__ int chunk_swizzle(int row)
 {
     if constexpr (KT == 64) return SWZ == 1 ? ((row >> 1) & 7) : (row & 7);
     return (row >> 1) & 3;
-}
-
-// A pointer that is the same in every lane, moved to scalar registers.
-__device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p)
-{
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
-    return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// One wavefront-wide direct-to-LDS load: lane i fetches 16 bytes at base + voff and they land at
-// LDS byte address lds_addr + 16*i (M0 carries the wavefront-uniform LDS address).  Issued as
-// inline assembly on purpose: the compiler then keeps exact lgkmcnt waits for the ds_read
-// operand fetches, and the landing of these loads is awaited explicitly with wait_vmcnt.
-__device__ __forceinline__ void lds_dma_16B(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
-#else
-    (void)base; (void)voff; (void)lds_addr;
-#endif
-}
-
-// One wavefront-wide direct-to-LDS load of 4 bytes per lane: lane i fetches base + voff and the word
-// lands at LDS byte address lds_addr + 4*i.
-__device__ __forceinline__ void lds_dma_4B(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
-#else
-    (void)base; (void)voff; (void)lds_addr;
-#endif
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-#endif
 }
 
 // One output tile: rows [row_begin,row_end) (at most MT) x columns [n0, n0+NT) of expert weights wexp,
@@ -1012,89 +932,6 @@ __global__ __launch_bounds__(WM* WN * 64) void tail_reduce_bf16_kernel(const int
         *reinterpret_cast<uint2*>(out + static_cast<size_t>(dst) * N + n) = packed;
 }
 
-// ---------------------------------------------------------------------------- fp32 kernel
-template <int EPI>
-__global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __restrict__ act, const int32_t* __restrict__ offsets,
-                                                                const float* __restrict__ weight, const float* __restrict__ bias,
-                                                                int max_rows, int K, int N, int E_local, float* __restrict__ out,
-                                                                const RowMap map)
-{
-    constexpr int MT = 64, NT = 64, KT = 16;
-    __shared__ float As[KT][MT + 4];
-    __shared__ float Bs[KT][NT + 4];
-    if (map.unrouted != nullptr) {  // output rows no sorted row writes: one thread per row clears it
-        const int64_t stride = static_cast<int64_t>(gridDim.x) * gridDim.y * 256;
-        for (int64_t t = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; t < map.n_unrouted; t += stride)
-            if (map.unrouted[t] < 0) {
-                float4* row = reinterpret_cast<float4*>(out + static_cast<size_t>(t) * N);
-                for (int c = 0; c < N / 4; ++c) row[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-    }
-    const TileRef tile = locate_row_tile(offsets, E_local, MT, blockIdx.x, max_rows);
-    if (tile.expert < 0) return;
-    const int n0 = blockIdx.y * NT;
-    const float* wexp = weight + static_cast<size_t>(tile.expert) * N * K;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int lrow = threadIdx.x / 4, lk = (threadIdx.x % 4) * 4;
-    int a_row = min(tile.row_begin + lrow, tile.row_end - 1);
-    if (map.a_row != nullptr) a_row = map.a_row[a_row] / map.a_div;
-    const float* arow = act + static_cast<size_t>(a_row) * K;
-    const float* brow = wexp + static_cast<size_t>(min(n0 + lrow, N - 1)) * K;
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
-    for (int k0 = 0; k0 < K; k0 += KT) {
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-        if (k0 + lk < K) {  // K % 4 == 0
-            a = *reinterpret_cast<const float4*>(arow + k0 + lk);
-            b = *reinterpret_cast<const float4*>(brow + k0 + lk);
-        }
-        __syncthreads();
-        As[lk + 0][lrow] = a.x; As[lk + 1][lrow] = a.y; As[lk + 2][lrow] = a.z; As[lk + 3][lrow] = a.w;
-        Bs[lk + 0][lrow] = b.x; Bs[lk + 1][lrow] = b.y; Bs[lk + 2][lrow] = b.z; Bs[lk + 3][lrow] = b.w;
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < KT; ++kk) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-        }
-    }
-    const float* bexp = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = tile.row_begin + ty * 4 + i;
-        if (m >= tile.row_end) continue;
-        const int n = n0 + tx * 4;
-        if (n >= N) continue;  // N % 4 == 0
-        int dst = m;
-        float scale = 1.0f;
-        if (EPI == kEpiNone && map.out_row != nullptr) {
-            dst = map.out_row[m];
-            scale = map.out_scale[dst];
-        }
-        float v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float z = acc[i][j];
-            if (bexp != nullptr) z += bexp[n + j];
-            if constexpr (EPI == kEpiGeluErf) z = gelu_erf_exact(z);
-            if constexpr (EPI == kEpiGeluTanh) z = gelu_tanh_exact(z);
-            if constexpr (EPI == kEpiNone) z *= scale;
-            v[j] = z;
-        }
-        *reinterpret_cast<float4*>(out + static_cast<size_t>(dst) * N + n) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-}
-
 // ---------------------------------------------------------------------------- host launchers
 template <int MT, int NT, int KT, int STAGES, int WM, int WN, int SWZ, int OCC>
 static int launch_bf16(const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N,
@@ -1138,26 +975,6 @@ static int launch_bf16(const void* act, const int32_t* offsets, const void* weig
         else EXF_LAUNCH_BF16(kEpiGeluTanh, true);
     }
 #undef EXF_LAUNCH_BF16
-    return EXF_OK;
-}
-
-static int launch_f32(const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N,
-                      int E_local, int epi, void* out, hipStream_t stream, const RowMap& map = RowMap{})
-{
-    const int64_t row_tiles = (A + 63) / 64 + E_local;
-    const int64_t n_tiles = (N + 63) / 64;
-    if (row_tiles >= (1ll << 31) || n_tiles > 65535) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: too many tiles");
-    const dim3 grid(static_cast<unsigned>(row_tiles), static_cast<unsigned>(n_tiles));
-    const float* a = static_cast<const float*>(act);
-    const float* w = static_cast<const float*>(weight);
-    const float* b = static_cast<const float*>(bias);
-    float* o = static_cast<float*>(out);
-    if (epi == kEpiNone)
-        hipLaunchKernelGGL(grouped_gemm_f32_kernel<kEpiNone>, grid, dim3(256), 0, stream, a, offsets, w, b, static_cast<int>(A), K, N, E_local, o, map);
-    else if (epi == kEpiGeluErf)
-        hipLaunchKernelGGL(grouped_gemm_f32_kernel<kEpiGeluErf>, grid, dim3(256), 0, stream, a, offsets, w, b, static_cast<int>(A), K, N, E_local, o, map);
-    else
-        hipLaunchKernelGGL(grouped_gemm_f32_kernel<kEpiGeluTanh>, grid, dim3(256), 0, stream, a, offsets, w, b, static_cast<int>(A), K, N, E_local, o, map);
     return EXF_OK;
 }
 
@@ -1248,9 +1065,17 @@ extern "C" int moe_expert_ffn(const void* x_sorted, const int32_t* expert_offset
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int epi = act == EXF_ACT_GELU_ERF ? kEpiGeluErf : kEpiGeluTanh;
     int rc;
-    if (dt == EXF_F32) {
-        rc = launch_f32(x_sorted, expert_offsets, w1, b1, A, d, f, E_local, epi, workspace, s);
-        if (rc == EXF_OK) rc = launch_f32(workspace, expert_offsets, w2, b2, A, f, d, E_local, kEpiNone, y_sorted, s);
+    if (stream_path_fits(A, E_local, dt)) {
+        StreamGemm first{}, second{};
+        first.act = x_sorted, first.weight = w1, first.bias = b1, first.out = workspace;
+        first.K = d, first.N = f, first.epi = epi;
+        second.act = workspace, second.weight = w2, second.bias = b2, second.out = y_sorted;
+        second.K = f, second.N = d, second.epi = kEpiNone;
+        first.offsets = second.offsets = expert_offsets;
+        first.max_rows = second.max_rows = static_cast<int>(A);
+        first.E_local = second.E_local = E_local;
+        rc = launch_stream_gemm(first, dt, s);
+        if (rc == EXF_OK) rc = launch_stream_gemm(second, dt, s);
     } else {
         void* partial = static_cast<unsigned char*>(workspace) + hidden_bytes(A, f, E_local, dt);
         RowMap first{}, second{};
@@ -1323,7 +1148,6 @@ static int ffn_fused_run(const char* fn, const void* x, const int32_t* src_of_so
     if (workspace_bytes < need) return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "moe_expert_ffn_fused: workspace %zu < %zu bytes", workspace_bytes, need);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int epi = act == EXF_ACT_GELU_ERF ? kEpiGeluErf : kEpiGeluTanh;
-    const size_t elem = dt == EXF_BF16 ? 2 : 4;
     unsigned char* hidden = static_cast<unsigned char*>(workspace);
     RowMap gather{};
     gather.a_row = src_of_sorted;
@@ -1346,9 +1170,20 @@ static int ffn_fused_run(const char* fn, const void* x, const int32_t* src_of_so
     }
     void* second_out = k == 1 ? out : static_cast<void*>(y_sorted);
     int rc;
-    if (dt == EXF_F32) {
-        rc = launch_f32(x, expert_offsets, w1, b1, A, d, f, E_local, epi, hidden, s, gather);
-        if (rc == EXF_OK) rc = launch_f32(hidden, expert_offsets, w2, b2, A, f, d, E_local, kEpiNone, second_out, s, scatter);
+    if (timeline == nullptr && stream_path_fits(A, E_local, dt)) {
+        StreamGemm first{}, second{};
+        first.act = x, first.weight = w1, first.bias = b1, first.out = hidden;
+        first.a_row = src_of_sorted, first.a_div = k;
+        first.K = d, first.N = f, first.epi = epi;
+        second.act = hidden, second.weight = w2, second.bias = b2, second.out = second_out;
+        second.out_row = scatter.out_row, second.out_scale = scatter.out_scale;
+        second.unrouted = scatter.unrouted, second.n_unrouted = scatter.n_unrouted;
+        second.K = f, second.N = d, second.epi = kEpiNone;
+        first.offsets = second.offsets = expert_offsets;
+        first.max_rows = second.max_rows = static_cast<int>(A);
+        first.E_local = second.E_local = E_local;
+        rc = launch_stream_gemm(first, dt, s);
+        if (rc == EXF_OK) rc = launch_stream_gemm(second, dt, s);
     } else {
         void* partial = y_sorted + (k > 1 ? align_up(static_cast<size_t>(A) * static_cast<size_t>(d) * 2, 256) : 0);
         rc = launch_wide_tile(x, expert_offsets, w1, b1, A, d, f, E_local, epi, hidden, s, gather,

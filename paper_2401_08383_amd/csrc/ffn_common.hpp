@@ -1,0 +1,121 @@
+// Shared by the grouped expert GEMM kernels: activations and the launch interface of the weight-streaming path.
+#pragma once
+
+#include <math.h>
+
+#include "common.hpp"
+
+namespace exf {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+
+constexpr int kXcdCount = 8;
+
+// ---------------------------------------------------------------------------- activations
+__device__ __forceinline__ float gelu_erf_exact(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752440f)); }
+__device__ __forceinline__ float gelu_tanh_exact(float z)
+{
+    return 0.5f * z * (1.0f + tanhf(0.79788456080286535588f * (z + 0.044715f * z * z * z)));
+}
+
+// bf16 path: z * Phi(z) with the normal CDF evaluated as a logistic function of an odd
+// polynomial,  Phi(z) ~ 1 / (1 + exp(-z (c0 + c1 z^2 + c2 z^4))),  coefficients fitted (minimax
+// on [-10,10]) to the exact erf form: max |error| of the GELU value is 2.6e-5, two orders of
+// magnitude below the bf16 rounding the result receives next.  z^2 is clamped where the logistic
+// has long saturated, so that the quartic term cannot turn the polynomial around.
+__device__ __forceinline__ float gelu_erf_fast(float z)
+{
+    const float t = fminf(z * z, 60.0f);
+    // coefficients carry the factor -log2(e): exp(-z p(t)) = 2^(z q(t)), one v_exp_f32
+    float q = fmaf(1.01407394e-3f, t, -1.06774916e-1f);
+    q = fmaf(q, t, -2.30112032f);
+    const float e = __builtin_amdgcn_exp2f(z * q);
+    return z * __builtin_amdgcn_rcpf(1.0f + e);  // v_rcp_f32: 1 ulp
+}
+// z/2 (1 + tanh u) = z / (1 + exp(-2u))
+__device__ __forceinline__ float gelu_tanh_fast(float z)
+{
+    const float u = 0.79788456080286535588f * (z + 0.044715f * z * z * z);
+    return z * __builtin_amdgcn_rcpf(1.0f + __expf(-2.0f * u));
+}
+
+enum Epilogue { kEpiNone = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2 };
+
+// ---------------------------------------------------------------------------- direct-to-LDS loads
+// A pointer that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+    return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// One wavefront-wide direct-to-LDS load: lane i fetches 16 bytes at base + voff and they land at
+// LDS byte address lds_addr + 16*i (M0 carries the wavefront-uniform LDS address).  Issued as
+// inline assembly on purpose: the compiler then keeps exact lgkmcnt waits for the ds_read
+// operand fetches, and the landing of these loads is awaited explicitly with wait_vmcnt.
+__device__ __forceinline__ void lds_dma_16B(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
+#else
+    (void)base; (void)voff; (void)lds_addr;
+#endif
+}
+
+// The same for data that is read once: streamed past the caches.
+__device__ __forceinline__ void lds_dma_16B_stream(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
+#else
+    (void)base; (void)voff; (void)lds_addr;
+#endif
+}
+
+// One wavefront-wide direct-to-LDS load of 4 bytes per lane: lane i fetches base + voff and the word
+// lands at LDS byte address lds_addr + 4*i.
+__device__ __forceinline__ void lds_dma_4B(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
+#else
+    (void)base; (void)voff; (void)lds_addr;
+#endif
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+#endif
+}
+
+// ---------------------------------------------------------------------------- weight-streaming path
+// One contraction  out[rows of e, N] = epi(act[rows, K] * weight_e[N, K]^T + bias_e)  (see ffn_stream.hip).
+struct StreamGemm {
+    const void* act;          // [*,K]
+    const void* weight;       // [E_local,N,K]
+    const void* bias;         // [E_local,N] or null
+    void* out;                // [*,N]
+    const int32_t* offsets;   // [E_local+1]
+    const int32_t* a_row;     // operand row of sorted row s is a_row[s] / a_div     (null: row s)
+    const int32_t* out_row;   // output row of sorted row s is out_row[s], scaled by out_scale[out_row[s]] (null: row s, no scale)
+    const float* out_scale;
+    const int32_t* unrouted;  // [n_unrouted]: output row t with unrouted[t] < 0 is set to zero (null: none)
+    int n_unrouted;
+    int a_div;
+    int max_rows;             // row capacity A
+    int K, N, E_local;
+    int epi;                  // Epilogue
+};
+// Is the path taken for A rows of `dt` spread over E_local experts?
+bool stream_path_fits(int64_t A, int E_local, int dt);
+int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
+
+}  // namespace exf

@@ -1,0 +1,584 @@
+// Grouped expert GEMM for few rows per expert (bf16), and for any number of rows in fp32.
+//
+// bf16: with a handful of rows per expert the contraction is a stream of weights (r rows: r flop per weight byte;
+// HBM and the matrix cores balance at about 270).  What counts is how many bytes are in flight on every compute
+// unit all the time, not operand reuse:
+//   - 256 persistent workgroups (one per compute unit), each with a contiguous range of the work items (expert, row tile of
+//     at most 64 rows, block of 16 C columns).  The blocks of one row tile are one continuous stream: the loads
+//     of the next block are in flight while the current one is summed and stored.
+//   - the W wavefronts of a workgroup deal the 128-byte pieces ("units") of the reduction among themselves
+//     (wavefront w takes units w, w + W, ..: neighbouring lines of a row are requested at the same time) and add
+//     their sums through LDS once per block.
+//   - every wavefront owns a ring of R slots in LDS and fills it with direct-to-LDS loads, eight rows of 128 bytes
+//     per load.  Nobody else reads its slots, so no barrier is needed between units, only its own count of
+//     outstanding loads.  (Loading the operands straight into registers in the lane layout of the matrix cores makes
+//     every load touch 64 pieces of 16 bytes: 5.3 TB/s where this streams 6.4.)
+//   - the slot of a block's last unit is free until the block is stored: it carries the sums.
+//   - the weights are read once: loaded with the streaming hint they leave the L2 to the activations (64 experts of
+//     4096 x 16384, 256 tokens top-2, both contractions: 3.08 ms without, 2.66 with, 2.89 as 64-row tiles of ffn.hip).
+//   - row ids and gate weights travel through LDS as well, so that no load result is awaited through a register (the
+//     compiler would wait for every load in flight).
+// fp32 (the exact path, small layers): operands straight from global memory into registers, no LDS but for the sums.
+#include "ffn_common.hpp"
+
+namespace exf {
+
+// ---------------------------------------------------------------------------- shared
+// Output rows no sorted row writes: a wavefront looks at 64 rows at a time and clears those it finds.
+template <typename ST>
+__device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int64_t wave_id, int64_t n_waves)
+{
+    if (p.unrouted == nullptr) return;
+    const int lane = lane_id();
+    const int vec_per_row = p.N * static_cast<int>(sizeof(ST)) / 16;
+    for (int64_t first = wave_id * kWave; first < p.n_unrouted; first += n_waves * kWave) {
+        const int64_t t = first + lane;
+        const int pos = t < p.n_unrouted ? p.unrouted[t] : 0;
+        unsigned long long todo = __ballot(pos < 0);
+        while (todo != 0) {
+            const int b = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            uint4* row = reinterpret_cast<uint4*>(p.out) + static_cast<size_t>(first + b) * vec_per_row;
+            for (int c = lane; c < vec_per_row; c += kWave) row[c] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+}
+
+// Row ranges and row tiles of the experts (lane e = expert e), running sum and total of the tiles.
+struct ExpertTiles {
+    int lo, hi, tiles, incl, total;
+};
+__device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, int tile_rows)
+{
+    ExpertTiles t;
+    const int lane = lane_id();
+    t.lo = 0;
+    t.hi = 0;
+    if (lane < p.E_local) {  // clamped so that a corrupt offsets array can never index past the buffers
+        t.lo = min(max(p.offsets[lane], 0), p.max_rows);
+        t.hi = min(max(p.offsets[lane + 1], t.lo), p.max_rows);
+    }
+    t.tiles = (t.hi - t.lo + tile_rows - 1) / tile_rows;
+    t.incl = wave_inclusive_scan(t.tiles);
+    t.total = wave_read_lane(t.incl, kWave - 1);
+    return t;
+}
+
+static int allow_lds(const void* kern, size_t lds)
+{
+    if (lds <= 64 * 1024) return EXF_OK;
+    hipError_t err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    if (err != hipSuccess) return fail(EXF_ERR_HIP, "moe_expert_ffn: LDS attribute: %s", hipGetErrorString(err));
+    return EXF_OK;
+}
+
+// ---------------------------------------------------------------------------- bf16
+constexpr int kStreamGrid = 256;     // workgroups: one per compute unit
+constexpr int kStreamIdBytes = 512;  // per wavefront: row ids of a tile, gate weights of a tile
+// A row tile has at most 8 * stream_max_ar(C) rows (narrow blocks have shorter tiles: the activations would fill the ring).
+__host__ __device__ constexpr int stream_max_ar(int C) { return C == 4 ? 8 : 4; }
+
+// Ring slots of a wavefront for row tiles of 8 AR rows: what fits 144 KiB, at most four.
+__host__ __device__ constexpr int stream_slot_bytes(int C, int AR) { return (16 * C + 8 * AR) * 128; }
+__host__ __device__ constexpr int stream_ring(int C, int AR, int W)
+{
+    const int fit = 144 * 1024 / (W * stream_slot_bytes(C, AR));
+    return fit > 4 ? 4 : fit;
+}
+__host__ __device__ constexpr int stream_ring_bytes(int C, int W)
+{
+    int most = 0;
+    for (int ar = 1; ar <= stream_max_ar(C); ar *= 2) {
+        const int b = W * stream_ring(C, ar, W) * stream_slot_bytes(C, ar);
+        most = b > most ? b : most;
+    }
+    return most;
+}
+
+// Waits until at most `units` units of LPU loads each are outstanding.
+template <int LPU, int R>
+__device__ __forceinline__ void wait_units(int units)
+{
+    static_assert((R - 1) * LPU < 64, "outstanding loads must fit the vmcnt counter");
+    if (R >= 4 && units >= 3) wait_vmcnt<(R >= 4 ? 3 : 0) * LPU>();
+    else if (R >= 3 && units >= 2) wait_vmcnt<(R >= 3 ? 2 : 0) * LPU>();
+    else if (R >= 2 && units >= 1) wait_vmcnt<(R >= 2 ? 1 : 0) * LPU>();
+    else wait_vmcnt<0>();
+}
+
+// Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
+template <int C, int AR, int W>
+__device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int row_begin, int row_end, int block_begin, int block_end,
+                                               int rotate, unsigned char* smem)
+{
+    constexpr int M = (AR + 1) / 2;  // MFMA tiles along the rows
+    constexpr int R = stream_ring(C, AR, W);
+    constexpr int SLOT = stream_slot_bytes(C, AR);
+    constexpr int LW = 2 * C, LA = AR, LPU = LW + LA;  // loads of a unit: eight rows each
+    constexpr int COLS = 16 * C;
+    static_assert(R >= 2, "a ring of one slot cannot overlap anything");
+    static_assert(8 * AR * COLS * 4 <= SLOT, "a block's sums must fit the slot of its last unit");
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t smem_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem));
+    const uint32_t ring_addr = smem_addr + wave * (R * SLOT);
+    unsigned char* ring = smem + wave * (R * SLOT);
+    constexpr int kIds = stream_ring_bytes(C, W);
+    const uint32_t ids_addr = smem_addr + kIds + wave * kStreamIdBytes;
+    const int* ids = reinterpret_cast<const int*>(smem + kIds + wave * kStreamIdBytes);
+    const float* gate = reinterpret_cast<const float*>(ids + kWave);
+    const uint32_t row_bytes = static_cast<uint32_t>(p.K) * 2u;
+
+    const int units = p.K / 64;
+    const int cnt = wave < units ? (units - wave + W - 1) / W : 0;  // units of a block this wavefront sums
+    const int total = (block_end - block_begin) * cnt;
+    const int start = cnt > 0 ? rotate % cnt : 0;  // the unit a block begins with (see stream_gemm_kernel)
+
+    // LDS row r of a slot (16 C weight rows, then 8 AR activation rows) holds 16-byte piece c at position c ^ ((r / 2) % 8)
+    const int r8 = lane >> 3, c8 = lane & 7;
+    const uint32_t off_even = static_cast<uint32_t>(r8) * row_bytes + ((c8 ^ (r8 >> 1)) * 16);      // rows 8 i + r8, i even
+    const uint32_t off_odd = static_cast<uint32_t>(r8) * row_bytes + ((c8 ^ (r8 >> 1) ^ 4) * 16);   //   i odd
+    const unsigned char* w_block = uniform_ptr(static_cast<const unsigned char*>(p.weight) +
+                                               (static_cast<size_t>(e) * p.N + static_cast<size_t>(block_begin) * COLS) * row_bytes);
+    const unsigned char* act = uniform_ptr(static_cast<const unsigned char*>(p.act));
+    const size_t block_bytes = static_cast<size_t>(COLS) * row_bytes;
+
+    auto issue_w = [&](int slot, int u) {
+        const int at = u + start < cnt ? u + start : u + start - cnt;
+        const unsigned char* base = w_block + static_cast<size_t>(wave + at * W) * 128;
+#pragma unroll
+        for (int i = 0; i < LW; ++i)
+            lds_dma_16B_stream(base + static_cast<size_t>(i * 8) * row_bytes, (i & 1) ? off_odd : off_even, ring_addr + slot * SLOT + i * 1024);
+    };
+    uint32_t off_a[LA];
+    auto issue_a = [&](int slot, int u) {
+        const int at = u + start < cnt ? u + start : u + start - cnt;
+        const unsigned char* base = act + static_cast<size_t>(wave + at * W) * 128;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) lds_dma_16B(base, off_a[i], ring_addr + slot * SLOT + (LW + i) * 1024);
+    };
+
+    // ---- start: row ids, the weights of the first units, then (ids known) their activations -------------------
+    const int first = min(total, R);
+    const int32_t* id_list = p.a_row != nullptr ? p.a_row : p.out_row;
+    if (id_list != nullptr)
+        lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(id_list)), static_cast<uint32_t>(min(row_begin + lane, row_end - 1)) * 4u, ids_addr);
+    int next_u = 0, next_slot = 0;  // the unit of the block at w_block, and the slot, the next load goes to
+    int q_issued = 0;
+    int u_of[R];
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+        u_of[s] = 0;
+        if (s < first) {
+            issue_w(s, next_u);
+            u_of[s] = next_u;
+            next_u += 1;
+            q_issued += 1;
+            if (next_u == cnt) {
+                next_u = 0;
+                w_block += block_bytes;
+            }
+        }
+    }
+    next_slot = first == R ? 0 : first;
+    if (id_list != nullptr) {  // loads land in order: the ids are there once only the weights are outstanding
+        if (first >= 4) wait_vmcnt<(R >= 4 ? 4 : 0) * LW>();
+        else if (first == 3) wait_vmcnt<(R >= 3 ? 3 : 0) * LW>();
+        else if (first == 2) wait_vmcnt<2 * LW>();
+        else if (first == 1) wait_vmcnt<LW>();
+        else wait_vmcnt<0>();
+    }
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int r = i * 8 + r8;
+        int row = min(row_begin + r, row_end - 1);  // rows past the end repeat the last one
+        if (p.a_row != nullptr) row = p.a_div == 1 ? ids[r] : ids[r] / p.a_div;
+        off_a[i] = static_cast<uint32_t>(row) * row_bytes + ((c8 ^ ((r >> 1) & 7)) * 16);
+    }
+    if (p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
+#pragma unroll
+    for (int s = 0; s < R; ++s)
+        if (s < first) issue_a(s, u_of[s]);
+    wait_vmcnt<0>();
+
+    // ---- stream -----------------------------------------------------------------------------------------------
+    const int r16 = lane & 15, g = lane >> 4;
+    const int ra = AR == 1 ? r16 & 7 : r16;  // a tile of eight rows has no second half: read it twice
+    int frag[2], frag_a[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        frag[h] = r16 * 128 + (((4 * h + g) ^ (r16 >> 1)) * 16);
+        frag_a[h] = ra * 128 + (((4 * h + g) ^ (ra >> 1)) * 16);
+    }
+    auto refill = [&]() {
+        if (q_issued < total) {
+            issue_w(next_slot, next_u);
+            issue_a(next_slot, next_u);
+            q_issued += 1;
+            next_u += 1;
+            if (next_u == cnt) {
+                next_u = 0;
+                w_block += block_bytes;
+            }
+            next_slot = next_slot + 1 == R ? 0 : next_slot + 1;
+        }
+    };
+    const int cnt_hi = (units + W - 1) / W, w_hi = units - (cnt_hi - 1) * W;  // wavefronts below w_hi sum cnt_hi units, the others one less
+    int last_hi = R - 1, last_lo = R - 1;  // ring position of the last unit of a block, for either kind of wavefront
+    int slot = 0, q = 0;
+    for (int block = block_begin; block < block_end; ++block) {
+        f32x4_t acc[C][M];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int m = 0; m < M; ++m) acc[c][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < cnt; ++u) {
+            wait_units<LPU, R>(q_issued - q - 1);
+            const unsigned char* s = ring + slot * SLOT;
+            bf16x8_t fw[C][2], fa[M][2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) fw[c][h] = *reinterpret_cast<const bf16x8_t*>(s + c * 2048 + frag[h]);
+#pragma unroll
+                for (int m = 0; m < M; ++m) fa[m][h] = *reinterpret_cast<const bf16x8_t*>(s + (C + m) * 2048 + frag_a[h]);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read: it may be filled again
+            if (u + 1 < cnt) refill();
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int m = 0; m < M; ++m)
+                        acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[c][h], fa[m][h], acc[c][m], 0, 0, 0);
+            q += 1;
+            slot = slot + 1 == R ? 0 : slot + 1;
+        }
+        // sums -> the slot of this block's last unit; float4 of row r, columns 4 j .. at position j ^ (r % 4C)
+        last_hi = (last_hi + cnt_hi) % R;
+        last_lo = (last_lo + cnt_hi - 1) % R;
+        {
+            unsigned char* red = ring + (wave < w_hi ? last_hi : last_lo) * SLOT;
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int r = m * 16 + r16, j = c * 4 + g;
+                    if (AR == 1 && r16 >= 8) continue;
+                    *reinterpret_cast<f32x4_t*>(red + (r * (4 * C) + (j ^ (r & (4 * C - 1)))) * 16) = acc[c][m];
+                }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int n0 = block * COLS;
+        for (int i = threadIdx.x; i < (row_end - row_begin) * (4 * C); i += W * kWave) {
+            const int r = i / (4 * C), j = i % (4 * C);
+            const int at = (r * (4 * C) + (j ^ (r & (4 * C - 1)))) * 16;
+            f32x4_t z = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                z += *reinterpret_cast<const f32x4_t*>(smem + w * (R * SLOT) + (w < w_hi ? last_hi : last_lo) * SLOT + at);
+            int dst = row_begin + r;
+            float scale = 1.0f;
+            if (p.out_row != nullptr) {
+                dst = ids[r];
+                scale = gate[r];
+            }
+            const int n = n0 + j * 4;
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = z[k];
+            if (p.bias != nullptr) {
+                const bf16_t* bias = static_cast<const bf16_t*>(p.bias) + static_cast<size_t>(e) * p.N + n;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] += bf16_to_f32(bias[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (p.epi == kEpiGeluErf) v[k] = gelu_erf_fast(v[k]);
+                else if (p.epi == kEpiGeluTanh) v[k] = gelu_tanh_fast(v[k]);
+                v[k] *= scale;
+            }
+            *reinterpret_cast<uint2*>(static_cast<bf16_t*>(p.out) + static_cast<size_t>(dst) * p.N + n) =
+                make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();  // everybody has read the sums: the slots may be filled again
+        asm volatile("" ::: "memory");
+        if (cnt > 0) refill();
+    }
+}
+
+template <int C, int W>
+__global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    clear_unrouted<bf16_t>(p, static_cast<int64_t>(blockIdx.x) * W + wave, static_cast<int64_t>(gridDim.x) * W);
+    constexpr int TILE_ROWS = 8 * stream_max_ar(C), COLS = 16 * C;
+    const int n_blocks = p.N / COLS;
+    const ExpertTiles et = scan_row_tiles(p, TILE_ROWS);
+    // Every workgroup begins its blocks at another place of the reduction: rows a power of two bytes apart put the same
+    // columns of all rows on few memory channels, and workgroups that walk the reduction in step all ask these
+    // (rows of 8 and 32 KiB, 256 workgroups: 5.3 and 4.8 TB/s in step, 6.1 rotated; rows of 4.5 KiB 6.0 either way).
+    // items (expert, row tile, column block); consecutive workgroup ids are on different XCDs: an XCD's workgroups
+    // take neighbouring ranges, so an expert's rows meet in one L2
+    const int64_t total = static_cast<int64_t>(et.total) * n_blocks;
+    const int per_xcd = static_cast<int>(gridDim.x) / kXcdCount;
+    const int lin = static_cast<int>(blockIdx.x % kXcdCount) * per_xcd + static_cast<int>(blockIdx.x / kXcdCount);
+    int item = static_cast<int>(total * lin / gridDim.x);
+    const int end = static_cast<int>(total * (lin + 1) / gridDim.x);
+    while (item < end) {
+        const int t = item / n_blocks, block = item - t * n_blocks;
+        const int e = __builtin_ctzll(__ballot(t < et.incl));
+        const int in_expert = t - (wave_read_lane(et.incl, e) - wave_read_lane(et.tiles, e));
+        const int row_begin = __builtin_amdgcn_readfirstlane(wave_read_lane(et.lo, e) + in_expert * TILE_ROWS);
+        const int row_end = __builtin_amdgcn_readfirstlane(min(row_begin + TILE_ROWS, wave_read_lane(et.hi, e)));
+        const int block_end = min(n_blocks, block + end - item);
+        const int rows = row_end - row_begin;
+        constexpr int MAX_AR = stream_max_ar(C);
+        if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
+        else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
+        else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
+        else stream_segment<C, MAX_AR, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
+        item += block_end - block;
+    }
+}
+
+template <int C, int W>
+static int launch_stream(const StreamGemm& p, hipStream_t stream)
+{
+    constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C, W)) + W * kStreamIdBytes;
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    auto kern = stream_gemm_kernel<C, W>;
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds)) return rc;
+    hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(W * kWave), lds, stream, p);
+    return EXF_OK;
+}
+
+// Columns per block, by a model of the launch: with q blocks per workgroup it runs ceil(q)/q times as long as its
+// bytes take (the workgroups' shares differ by a block), and the activations, which every block reads
+// again, weigh about 0.6 of their share of the weights (fitted to 9 shapes of 1 to 617 tokens: it picks the fastest
+// of the three or one within 5 %).
+static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
+{
+    const double A = p.max_rows, E = p.E_local;
+    const double touched = E * (1.0 - exp(A * log1p(-1.0 / E)));  // experts with rows, if A rows fall on E experts at random
+    const double act_rows = 8.0 * ceil(1.3 * A / touched / 8.0);
+    int best = 4;
+    double best_cost = 1e300;
+    for (int c = 4; c >= 1; c /= 2) {
+        const double q = touched * (p.N / (16 * c)) / kStreamGrid;
+        const double cost = ceil(q) / q * (1.0 + 0.6 * act_rows / (16 * c));
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = c;
+        }
+    }
+    if (best == 4) return launch_stream<4, 4>(p, stream);
+    if (best == 2) return launch_stream<2, 4>(p, stream);
+    return launch_stream<1, 8>(p, stream);
+}
+
+// ---------------------------------------------------------------------------- fp32
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t reg128_t;
+constexpr int kExactUnit = 32;  // reduction elements per step: 128 bytes of every row
+
+// Sums of this wavefront's units [u_begin, u_end) for 16 C columns x 16 M rows, written to red[row][column] (row
+// stride RS floats).  A lane loads two 16-byte pieces of one weight row and the same pieces of one activation row per
+// unit; they are the operands of eight 16x16x4 MFMAs as they lie (the order in which the reduction index is dealt
+// to the lanes is free as long as both operands agree).  Loads run D units ahead; units past the end are clamped.
+template <int C, int M, int D, int RS>
+__device__ __forceinline__ void exact_units(const float* __restrict__ wexp, const float* __restrict__ act, const int32_t* __restrict__ a_row,
+                                            int a_div, int row_begin, int row_end, int n0, int K, int N, int u_begin, int u_end,
+                                            float* __restrict__ red)
+{
+    const int lane = lane_id();
+    const int r16 = lane & 15, g = lane >> 4;
+    const float *row_w[C], *row_a[M];
+#pragma unroll
+    for (int c = 0; c < C; ++c) row_w[c] = wexp + static_cast<size_t>(min(n0 + c * 16 + r16, N - 1)) * K;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        int r = min(row_begin + m * 16 + r16, row_end - 1);  // rows past the end repeat the last one
+        if (a_row != nullptr) r = a_row[r] / a_div;
+        row_a[m] = act + static_cast<size_t>(r) * K;
+    }
+    f32x4_t acc[C][M];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int m = 0; m < M; ++m) acc[c][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    f32x4_t w[D][C][2], a[D][M][2];
+    auto load = [&](int u, int s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = u * kExactUnit + h * 16 + g * 4;  // K % 4 == 0: a piece is inside or outside as a whole
+            const bool in = k < K;
+            const int at = in ? k : 0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) w[s][c][h] = *reinterpret_cast<const f32x4_t*>(row_w[c] + at);
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(row_a[m] + at);
+                a[s][m][h] = in ? v : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
+    auto compute = [&](int s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int m = 0; m < M; ++m)
+                        acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][c][h][j], a[s][m][h][j], acc[c][m], 0, 0, 0);
+    };
+    if (u_begin < u_end) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) load(min(u_begin + s, u_end - 1), s);
+        int u = u_begin;
+        for (; u + D < u_end; u += D) {
+#pragma unroll
+            for (int s = 0; s < D; ++s) {
+                compute(s);
+                __builtin_amdgcn_sched_barrier(0);
+                load(min(u + D + s, u_end - 1), s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (u + s < u_end) compute(s);
+    }
+    // a lane holds four consecutive columns of one row
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int m = 0; m < M; ++m) *reinterpret_cast<f32x4_t*>(red + (m * 16 + r16) * RS + c * 16 + g * 4) = acc[c][m];
+}
+
+// WI items per workgroup, WK wavefronts per item (they cut the reduction into parts).
+template <int C, int M, int WK, int WI, int D>
+__global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGemm p)
+{
+    constexpr int COLS = 16 * C, RS = COLS + 4;  // (padded: the 16 rows of a float4 column store hit distinct banks)
+    constexpr int TILE_ROWS = 16 * M;
+    extern __shared__ float red[];  // [WI][WK][TILE_ROWS][RS]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    clear_unrouted<float>(p, blockIdx.x * (WK * WI) + wave, static_cast<int64_t>(gridDim.x) * (WK * WI));
+
+    // work items are numbered (expert, column block, row tile); every XCD takes a contiguous share, so the row
+    // tiles of a weight block and the column blocks of an expert's rows meet in one L2
+    const int n_blocks = (p.N + COLS - 1) / COLS;
+    const ExpertTiles et = scan_row_tiles(p, TILE_ROWS);
+    const int total = et.total * n_blocks;
+    const int xcd = static_cast<int>(blockIdx.x % kXcdCount), pos = static_cast<int>(blockIdx.x / kXcdCount);
+    const int first_item = static_cast<int>(static_cast<int64_t>(total) * xcd / kXcdCount);
+    const int last_item = static_cast<int>(static_cast<int64_t>(total) * (xcd + 1) / kXcdCount);
+    const int item = first_item + pos * WI + wave / WK;
+    const bool valid = item < last_item;  // (the same for the wavefronts of an item)
+    const unsigned long long owner = __ballot(item < et.incl * n_blocks);
+    const int e = valid ? __builtin_ctzll(owner) : 0;  // (item < total: some lane owns it)
+    const int e_tiles = max(wave_read_lane(et.tiles, e), 1);
+    const int in_expert = item - (wave_read_lane(et.incl, e) - e_tiles) * n_blocks;
+    const int block = in_expert / e_tiles, tile = in_expert - block * e_tiles;
+    const int row_begin = __builtin_amdgcn_readfirstlane(wave_read_lane(et.lo, e) + tile * TILE_ROWS);
+    const int row_end = __builtin_amdgcn_readfirstlane(min(row_begin + TILE_ROWS, wave_read_lane(et.hi, e)));
+    const int n0 = __builtin_amdgcn_readfirstlane(block * COLS);
+
+    float* item_red = red + static_cast<size_t>(wave / WK) * (WK * TILE_ROWS * RS);
+    if (valid) {
+        const float* wexp = static_cast<const float*>(p.weight) + static_cast<size_t>(e) * p.N * p.K;
+        const float* act = static_cast<const float*>(p.act);
+        const int units = (p.K + kExactUnit - 1) / kExactUnit;
+        const int part = wave % WK;
+        const int u_begin = part * units / WK, u_end = (part + 1) * units / WK;
+        float* mine = item_red + part * (TILE_ROWS * RS);
+        const int m_used = (row_end - row_begin + 15) / 16;
+#define EXF_EXACT_UNITS(MU) exact_units<C, MU, D, RS>(wexp, act, p.a_row, p.a_div, row_begin, row_end, n0, p.K, p.N, u_begin, u_end, mine)
+        if constexpr (M == 1) {
+            EXF_EXACT_UNITS(1);
+        } else {
+            if (m_used == 1) EXF_EXACT_UNITS(1);
+            else if (m_used == 2) EXF_EXACT_UNITS(2);
+            else EXF_EXACT_UNITS(4);
+        }
+#undef EXF_EXACT_UNITS
+    }
+    __syncthreads();
+    if (!valid) return;
+
+    // four columns of one row per thread: the wavefronts' sums in a fixed order, bias, activation, scale
+    constexpr int GROUPS = COLS / 4;
+    const float* bias = p.bias != nullptr ? static_cast<const float*>(p.bias) + static_cast<size_t>(e) * p.N : nullptr;
+    for (int i = threadIdx.x % (WK * kWave); i < (row_end - row_begin) * GROUPS; i += WK * kWave) {
+        const int r = i / GROUPS, q = i % GROUPS;
+        const int n = n0 + q * 4;
+        f32x4_t z = *reinterpret_cast<const f32x4_t*>(item_red + r * RS + q * 4);
+#pragma unroll
+        for (int wv = 1; wv < WK; ++wv) z += *reinterpret_cast<const f32x4_t*>(item_red + (wv * TILE_ROWS + r) * RS + q * 4);
+        if (n >= p.N) continue;  // N % 4 == 0: the four columns are inside or outside together
+        int dst = row_begin + r;
+        float scale = 1.0f;
+        if (p.out_row != nullptr) {
+            dst = p.out_row[dst];
+            scale = p.out_scale[dst];
+        }
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v[j] = z[j];
+            if (bias != nullptr) v[j] += bias[n + j];
+            if (p.epi == kEpiGeluErf) v[j] = gelu_erf_exact(v[j]);
+            else if (p.epi == kEpiGeluTanh) v[j] = gelu_tanh_exact(v[j]);
+            v[j] *= scale;
+        }
+        *reinterpret_cast<float4*>(static_cast<float*>(p.out) + static_cast<size_t>(dst) * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+template <int C, int M, int WK, int WI, int D>
+static int launch_exact(const StreamGemm& p, hipStream_t stream)
+{
+    constexpr int TILE_ROWS = 16 * M;
+    constexpr size_t lds = static_cast<size_t>(WK * WI) * TILE_ROWS * (16 * C + 4) * sizeof(float);
+    auto kern = exact_gemm_kernel<C, M, WK, WI, D>;
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds)) return rc;
+    // row tiles: whole ones and at most one partial tile per expert with rows
+    const int64_t A = p.max_rows;
+    const int64_t row_tiles = A / TILE_ROWS + (A < p.E_local ? A : p.E_local);
+    const int64_t share = row_tiles * ((p.N + 16 * C - 1) / (16 * C)) / kXcdCount + 1;  // items of an XCD at most
+    const int64_t grid = (share + WI - 1) / WI * kXcdCount;
+    if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: too many tiles");
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(WK * WI * kWave), lds, stream, p);
+    return EXF_OK;
+}
+
+// Many tiles and a short reduction: 64 x 64 tiles, one wavefront each, nothing to add up.  Otherwise the reduction
+// is cut over the wavefronts of a workgroup, and narrow blocks spread a small problem over the chip.
+template <int M>
+static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
+{
+    const int64_t tiles = (p.max_rows < p.E_local ? p.max_rows : p.E_local) + p.max_rows / (16 * M);
+    if (p.K <= 1024 && tiles * ((p.N + 63) / 64) >= 512) return launch_exact<4, M, 1, 4, 2>(p, stream);
+    if (tiles * ((p.N + 63) / 64) >= 384) return launch_exact<4, M, 4, 1, 2>(p, stream);
+    return launch_exact<1, M, 8, 1, 2>(p, stream);
+}
+
+// ---------------------------------------------------------------------------- host
+constexpr int kStreamRowsPerExpert = 40;  // bf16: mean rows per expert up to which the weights are streamed
+bool stream_path_fits(int64_t A, int E_local, int dt) { return dt == EXF_F32 || A <= static_cast<int64_t>(kStreamRowsPerExpert) * E_local; }
+
+int launch_stream_gemm(const StreamGemm& p, int dt, hipStream_t stream)
+{
+    if (dt == EXF_BF16) return launch_stream_bf16(p, stream);
+    return p.max_rows <= 16ll * p.E_local ? launch_exact_rows<1>(p, stream) : launch_exact_rows<4>(p, stream);
+}
+
+}  // namespace exf

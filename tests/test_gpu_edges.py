@@ -45,3 +45,25 @@ def test_candidate_scores_around_the_32_bit_table(E, Bn, total):
     assert got[0].tolist() == [total] * (L - 1)
     for b in range(0, Bn, max(1, Bn // 100)):
         np.testing.assert_array_equal(got[b], O.placement_locality_from_counts(counts, maps[b]))
+
+
+# ----------------------------------------------------------------------------- streamed weights (few rows per expert, fp32)
+@pytest.mark.parametrize("d,f", [(64, 64), (128, 576), (832, 320), (64, 4096)])
+@pytest.mark.parametrize("counts", [[0, 1, 8, 9, 16, 17, 0, 31], [32, 33, 0, 64, 65, 7, 1, 3], [0, 0, 0, 1], [1], [100, 0, 0, 2, 0, 5]])
+def test_streamed_ffn_row_tiles(oracle, counts, d, f):
+    """Row tiles of every height, reductions shorter than the wavefronts share, blocks of every width."""
+    P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1300 + d + f)
+
+
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 256, 1024, 8, 1), (3, 64, 64, 2, 2), (40, 192, 448, 1, 1), (41, 192, 448, 1, 1), (90, 128, 704, 64, 2)])
+def test_streamed_ffn_fused(oracle, T, d, f, E, k):
+    """Gathered rows, scattered and scaled results, tokens without a resident expert; 40 and 41 rows per expert are the two
+    sides of the rule that selects the path."""
+    P._fused_case(oracle, T, d, f, E, E, k, 1, True, seed=1400 + T)
+    P._fused_case(oracle, T, d, f, E, max(1, E // 3), k, 0, False, seed=1401 + T)
+
+
+@pytest.mark.parametrize("d,f", [(4, 4), (36, 20), (132, 260), (1028, 64)])
+@pytest.mark.parametrize("counts", [[0, 1, 15, 16, 17, 64, 65], [300, 0, 5], [1]])
+def test_exact_ffn_ragged(oracle, counts, d, f):
+    P._ffn_case(oracle, "f32", counts, d, f, 0, True, seed=1500 + d + f)
