@@ -198,6 +198,40 @@ int moe_combine(const void* y_sorted, const int32_t* sorted_of_src, const float*
                 int d, int k, int dt, void* out, void* stream);
 
 /* ---------------------------------------------------------------------------------------
+ * moe_layer_forward — one pass of the whole expert layer (the calls above in sequence) for callers that
+ * keep their buffers: a serving loop pays for one call instead of four.
+ *   fused != 0 : moe_gate_topk, moe_dispatch (index maps only), moe_expert_ffn_fused
+ *   fused == 0 : moe_gate_topk, moe_dispatch (rows moved), moe_expert_ffn, moe_combine
+ * forced_idx [T,k] int32 or NULL: global expert ids supplied by the caller; the gate still writes topk_idx and topk_w,
+ * but these ids are dispatched.  All other fields are the arguments of the same name of those calls;
+ * x_sorted and y_sorted are used with fused == 0 only.  Results and errors are those of the calls.
+ * ------------------------------------------------------------------------------------- */
+typedef struct exf_moe_layer {
+    const void* x;
+    const void* w_gate;
+    const void* w1;
+    const void* w2;
+    const int32_t* forced_idx;
+    const int32_t* expert_map;
+    int64_t T;
+    int d, f, E, E_local, k, renormalize, act, dt, fused, reserved;
+    int32_t* topk_idx;
+    float* topk_w;
+    void* x_sorted;
+    int32_t* src_of_sorted;
+    int32_t* sorted_of_src;
+    int32_t* expert_counts;
+    int32_t* expert_offsets;
+    void* y_sorted;
+    void* out;
+    void* dispatch_workspace;
+    size_t dispatch_workspace_bytes;
+    void* ffn_workspace;
+    size_t ffn_workspace_bytes;
+} exf_moe_layer;
+int moe_layer_forward(const exf_moe_layer* layer, void* stream);
+
+/* ---------------------------------------------------------------------------------------
  * affinity_histogram — inter-layer expert affinity from a routing trace (Design, "Modeling
  * Inter-layer Expert Affinity", the conditional-probability equation; the heat-map figure).
  *

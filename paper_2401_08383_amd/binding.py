@@ -46,6 +46,7 @@ SIGNATURES = {
     "moe_expert_ffn_fused_workspace_bytes": (_sz, [_i64, _i, _i, _i, _i, _i]),
     "moe_expert_ffn_fused": (_i, [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _i, _i, _i, _i, _i, _i, _vp, _vp, _sz, _vp]),
     "moe_combine": (_i, [_vp, _vp, _vp, _i64, _i, _i, _i, _vp, _vp]),
+    "moe_layer_forward": (_i, [_vp, _vp]),
     "affinity_histogram_workspace_bytes": (_sz, [_i, _i64, _i]),
     "affinity_histogram": (_i, [_vp, _i, _i64, _i, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "affinity_statistics_workspace_bytes": (_sz, [_i, _i64, _i]),
@@ -64,6 +65,15 @@ SIGNATURES = {
     "exf_probe_gemm_loop": (_i, [_vp, _sz, _i, _vp, _vp]),
     "exf_probe_ffn_timeline": (_i, [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _i, _i, _i, _i, _vp, _vp, _sz, _vp, _i, _vp]),
 }
+
+class MoELayerDesc(ctypes.Structure):
+    """exf_moe_layer of include/exflow_moe.h."""
+    _fields_ = ([(n, _vp) for n in ("x", "w_gate", "w1", "w2", "forced_idx", "expert_map")] + [("T", _i64)]
+                + [(n, _i) for n in ("d", "f", "E", "E_local", "k", "renormalize", "act", "dt", "fused", "reserved")]
+                + [(n, _vp) for n in ("topk_idx", "topk_w", "x_sorted", "src_of_sorted", "sorted_of_src", "expert_counts", "expert_offsets",
+                                      "y_sorted", "out", "dispatch_workspace")]
+                + [("dispatch_workspace_bytes", _sz), ("ffn_workspace", _vp), ("ffn_workspace_bytes", _sz)])
+
 
 _lib = None
 
@@ -104,7 +114,8 @@ def _ptr(t):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # (the raw handle; a Stream object costs a microsecond more)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def dtype_code(t: torch.Tensor) -> int:

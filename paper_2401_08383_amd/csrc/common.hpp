@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "exflow_moe.h"
 
 namespace exf {
@@ -14,6 +16,19 @@ namespace exf {
 int fail(int code, const char* fmt, ...);
 // Maps the pending HIP launch error (if any) to EXF_ERR_HIP.
 int check_launch(const char* what);
+
+// Lets a kernel use more than 64 KiB of LDS; asks the runtime once per device (`allowed`: a bit per device).
+inline int allow_lds(const void* kern, size_t lds, std::atomic<uint64_t>& allowed, const char* what)
+{
+    if (lds <= 64 * 1024) return EXF_OK;
+    int dev = -1;
+    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
+    if (known && (allowed.load(std::memory_order_relaxed) >> dev & 1u) != 0) return EXF_OK;
+    hipError_t err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    if (err != hipSuccess) return fail(EXF_ERR_HIP, "%s: LDS attribute: %s", what, hipGetErrorString(err));
+    if (known) allowed.fetch_or(1ull << dev, std::memory_order_relaxed);
+    return EXF_OK;
+}
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -124,48 +139,16 @@ __device__ __forceinline__ int wave_read_lane(int v, int src)
     return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(src));
 }
 
-// Which expert owns row-tile `tile` when every expert's rows [off[e], off[e+1]) are cut into
-// tiles of `mt` rows (tiles never straddle experts)?  Every lane of the calling wavefront
-// returns the same answer.  e = -1 if `tile` is beyond the last tile.  E_local <= 64;
-// max_rows is the row capacity of the activation buffers.
-struct TileRef {
-    int expert;     // local expert id or -1
-    int row_begin;  // first sorted row of the tile
-    int row_end;    // one past the last valid sorted row of the tile
-    int total;      // total number of row tiles over all experts
-};
-
-__device__ __forceinline__ TileRef locate_row_tile(const int32_t* __restrict__ offsets, int E_local, int mt, int tile,
-                                                   int max_rows)
+// Lanes of the wavefront that hold the same local expert as this lane (meaningful where e >= 0): the
+// ids are compared bit by bit, log2(E_local) ballots instead of one ballot per expert.
+__device__ __forceinline__ unsigned long long same_expert_lanes(int e, int E_local)
 {
-    const int lane = lane_id();
-    int lo = 0, hi = 0;
-    if (lane < E_local) {  // clamped so that a corrupt offsets array can never index past the buffers
-        lo = min(max(offsets[lane], 0), max_rows);
-        hi = min(max(offsets[lane + 1], lo), max_rows);
+    unsigned long long m = __ballot(e >= 0);
+    for (int bit = 1; bit < E_local; bit <<= 1) {
+        const unsigned long long b = __ballot((e & bit) != 0);
+        m &= (e & bit) != 0 ? b : ~b;
     }
-    const int cnt = hi - lo;
-    const int tiles = cnt > 0 ? (cnt + mt - 1) / mt : 0;
-    const int incl = wave_inclusive_scan(tiles);
-    const int excl = incl - tiles;
-    const bool mine = (lane < E_local) && (tile >= excl) && (tile < incl);
-    const unsigned long long m = __ballot(mine);
-    TileRef r;
-    r.total = wave_read_lane(incl, kWave - 1);
-    if (m == 0ull) {
-        r.expert = -1;
-        r.row_begin = 0;
-        r.row_end = 0;
-        return r;
-    }
-    const int src = __ffsll(static_cast<long long>(m)) - 1;
-    const int e_lo = wave_read_lane(lo, src);
-    const int e_hi = wave_read_lane(hi, src);
-    const int e_excl = wave_read_lane(excl, src);
-    r.expert = src;
-    r.row_begin = e_lo + (tile - e_excl) * mt;
-    r.row_end = min(r.row_begin + mt, e_hi);
-    return r;
+    return m;
 }
 
 }  // namespace exf

@@ -57,18 +57,6 @@ __device__ __forceinline__ void load_local_experts(const int32_t* __restrict__ t
     }
 }
 
-// Lanes of the wavefront that hold the same local expert as this lane (meaningful where e >= 0): the
-// ids are compared bit by bit, log2(E_local) ballots instead of one ballot per expert.
-__device__ __forceinline__ unsigned long long same_expert_lanes(int e, int E_local)
-{
-    unsigned long long m = __ballot(e >= 0);
-    for (int bit = 1; bit < E_local; bit <<= 1) {
-        const unsigned long long b = __ballot((e & bit) != 0);
-        m &= (e & bit) != 0 ? b : ~b;
-    }
-    return m;
-}
-
 __global__ __launch_bounds__(kDispThreads) void dispatch_count_kernel(const int32_t* __restrict__ topk_idx,
                                                                        const int32_t* __restrict__ expert_map, int64_t A,
                                                                        int E, int E_local,

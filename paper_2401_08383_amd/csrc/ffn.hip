@@ -950,11 +950,8 @@ static int launch_bf16(const void* act, const int32_t* offsets, const void* weig
 #define EXF_LAUNCH_BF16(EPI, BIAS)                                                                                              \
     do {                                                                                                                        \
         auto kern = grouped_gemm_bf16_kernel<MT, NT, KT, STAGES, WM, WN, SWZ, OCC, EPI, BIAS>;                                  \
-        if (lds > 64 * 1024) {                                                                                                  \
-            hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                                 static_cast<int>(lds));                                                       \
-            if (err != hipSuccess) return fail(EXF_ERR_HIP, "moe_expert_ffn: LDS attribute: %s", hipGetErrorString(err));       \
-        }                                                                                                                       \
+        static std::atomic<uint64_t> allowed{0};                                                                                \
+        if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;                 \
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(WM* WN * 64), lds, stream,                              \
                            static_cast<const bf16_t*>(act), offsets, static_cast<const bf16_t*>(weight),                        \
                            static_cast<const bf16_t*>(bias), static_cast<int>(A), K, N, E_local, static_cast<bf16_t*>(out),     \
@@ -1106,7 +1103,7 @@ extern "C" size_t moe_expert_ffn_fused_workspace_bytes(int64_t T, int k, int d, 
 static int ffn_fused_run(const char* fn, const void* x, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
                          const int32_t* expert_offsets, const void* w1, const void* b1, const void* w2, const void* b2, int64_t T, int k,
                          int d, int f, int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream,
-                         unsigned long long* timeline, int timeline_cap)
+                         unsigned long long* timeline, int timeline_cap, const exf::FfnRouting* routing = nullptr)
 {
     using namespace exf;
     (void)fn;
@@ -1174,6 +1171,11 @@ static int ffn_fused_run(const char* fn, const void* x, const int32_t* src_of_so
         StreamGemm first{}, second{};
         first.act = x, first.weight = w1, first.bias = b1, first.out = hidden;
         first.a_row = src_of_sorted, first.a_div = k;
+        if (routing != nullptr) {
+            first.topk_idx = routing->topk_idx, first.expert_map = routing->expert_map, first.E = routing->E;
+            first.src_of_sorted = routing->src_of_sorted, first.sorted_of_src = routing->sorted_of_src;
+            first.expert_counts = routing->expert_counts, first.expert_offsets = routing->expert_offsets;
+        }
         first.K = d, first.N = f, first.epi = epi;
         second.act = hidden, second.weight = w2, second.bias = b2, second.out = second_out;
         second.out_row = scatter.out_row, second.out_scale = scatter.out_scale;
@@ -1204,6 +1206,13 @@ extern "C" int moe_expert_ffn_fused(const void* x, const int32_t* src_of_sorted,
 {
     return ffn_fused_run("moe_expert_ffn_fused", x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, b1, w2, b2, T, k, d, f,
                          E_local, act, dt, out, workspace, workspace_bytes, stream, nullptr, 0);
+}
+
+int exf::ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
+                          int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream)
+{
+    return ffn_fused_run("moe_layer_forward", x, r.src_of_sorted, r.sorted_of_src, topk_w, r.expert_offsets, w1, nullptr, w2, nullptr, T, k, d,
+                         f, E_local, act, dt, out, workspace, workspace_bytes, stream, nullptr, 0, &r);
 }
 
 // moe_expert_ffn_fused (bf16) with a per-workgroup timeline of both contractions (see RowMap::timeline).

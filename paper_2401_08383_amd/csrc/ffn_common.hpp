@@ -113,9 +113,27 @@ struct StreamGemm {
     int max_rows;             // row capacity A
     int K, N, E_local;
     int epi;                  // Epilogue
+    // Routing instead of sorted rows (first contraction of a short batch; null: `offsets` and `a_row` above): every
+    // workgroup sorts the assignments for itself, workgroup 0 writes the maps.
+    const int32_t* topk_idx;    // [max_rows]
+    const int32_t* expert_map;  // [E] or null
+    int E;
+    int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
 };
+constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for itself
 // Is the path taken for A rows of `dt` spread over E_local experts?
 bool stream_path_fits(int64_t A, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
+
+// moe_dispatch (index maps) and moe_expert_ffn_fused as one: the first contraction sorts the assignments itself.  Only
+// where routed_path_fits() says so; the maps are written as moe_dispatch writes them.
+struct FfnRouting {
+    const int32_t *topk_idx, *expert_map;
+    int E;
+    int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
+};
+inline bool routed_path_fits(int64_t A, int E_local, int dt) { return A > 0 && A <= kInlineDispatchMax && stream_path_fits(A, E_local, dt); }
+int ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
+                     int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream);
 
 }  // namespace exf

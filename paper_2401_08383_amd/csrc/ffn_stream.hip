@@ -44,32 +44,96 @@ __device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int64_t wave
     }
 }
 
+// The stable counting sort of moe_dispatch for at most kInlineDispatchMax assignments, by one workgroup into LDS.  Loading
+// the ids costs the same memory round trip as loading finished offsets would, and the sort itself about a third of
+// the launch it replaces.  Segments (round, wavefront) are ascending assignment order, as in dispatch_small_kernel.
+// offs[e]: first sorted position of expert e, offs[E_local] = number kept; list[s]: assignment at position s.
+constexpr int kInlineSegments = kInlineDispatchMax / kWave;
+struct InlineDispatch {
+    int list[kInlineDispatchMax];
+    int offs[EXF_MAX_EXPERTS + 1];
+    unsigned short seg[kInlineSegments][EXF_MAX_EXPERTS];  // count, then start inside its expert's bucket
+};
+template <int THREADS>
+__device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDispatch& d, bool publish)
+{
+    constexpr int WAVES = THREADS / kWave, R = kInlineDispatchMax / THREADS;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int A = p.max_rows, rounds = (A + THREADS - 1) / THREADS;
+    int e[R], rank[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) e[r] = p.topk_idx[min(r * THREADS + static_cast<int>(threadIdx.x), A - 1)];
+    for (int i = threadIdx.x; i < rounds * WAVES * (EXF_MAX_EXPERTS / 2); i += THREADS) reinterpret_cast<uint32_t*>(d.seg)[i] = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool ok = r * THREADS + static_cast<int>(threadIdx.x) < A && e[r] >= 0 && e[r] < p.E;
+        int local = e[r];
+        if (p.expert_map != nullptr) local = p.expert_map[ok ? e[r] : 0];
+        e[r] = (ok && local >= 0 && local < p.E_local) ? local : -1;
+    }
+    __syncthreads();
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r >= rounds) break;
+        const unsigned long long m = same_expert_lanes(e[r], p.E_local);
+        rank[r] = __popcll(m & below);
+        if (e[r] >= 0 && (m & below) == 0ull) d.seg[r * WAVES + wave][e[r]] = static_cast<unsigned short>(__popcll(m));
+    }
+    __syncthreads();
+    if (wave == 0) {  // lane = expert
+        int run = 0;
+        for (int s = 0; s < rounds * WAVES; ++s) {
+            const int c = d.seg[s][lane];
+            d.seg[s][lane] = static_cast<unsigned short>(run);
+            run += c;
+        }
+        const int incl = wave_inclusive_scan(run);
+        d.offs[lane] = incl - run;
+        if (lane == kWave - 1) d.offs[kWave] = incl;
+        if (publish) {
+            if (lane < p.E_local) {
+                p.expert_counts[lane] = run;
+                p.expert_offsets[lane] = incl - run;
+            }
+            if (lane == p.E_local - 1) p.expert_offsets[p.E_local] = incl;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r >= rounds) break;
+        const int a = r * THREADS + static_cast<int>(threadIdx.x);
+        int pos = -1;
+        if (e[r] >= 0) {
+            pos = d.offs[e[r]] + d.seg[r * WAVES + wave][e[r]] + rank[r];
+            d.list[pos] = a;
+            if (publish) p.src_of_sorted[pos] = a;
+        }
+        if (publish && a < A) p.sorted_of_src[a] = pos;
+    }
+    __syncthreads();
+}
+
 // Row ranges and row tiles of the experts (lane e = expert e), running sum and total of the tiles.
 struct ExpertTiles {
     int lo, hi, tiles, incl, total;
 };
-__device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, int tile_rows)
+__device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, const int32_t* offsets, int tile_rows)
 {
     ExpertTiles t;
     const int lane = lane_id();
     t.lo = 0;
     t.hi = 0;
     if (lane < p.E_local) {  // clamped so that a corrupt offsets array can never index past the buffers
-        t.lo = min(max(p.offsets[lane], 0), p.max_rows);
-        t.hi = min(max(p.offsets[lane + 1], t.lo), p.max_rows);
+        t.lo = min(max(offsets[lane], 0), p.max_rows);
+        t.hi = min(max(offsets[lane + 1], t.lo), p.max_rows);
     }
     t.tiles = (t.hi - t.lo + tile_rows - 1) / tile_rows;
     t.incl = wave_inclusive_scan(t.tiles);
     t.total = wave_read_lane(t.incl, kWave - 1);
     return t;
-}
-
-static int allow_lds(const void* kern, size_t lds)
-{
-    if (lds <= 64 * 1024) return EXF_OK;
-    hipError_t err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (err != hipSuccess) return fail(EXF_ERR_HIP, "moe_expert_ffn: LDS attribute: %s", hipGetErrorString(err));
-    return EXF_OK;
 }
 
 // ---------------------------------------------------------------------------- bf16
@@ -109,7 +173,7 @@ __device__ __forceinline__ void wait_units(int units)
 // Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
 template <int C, int AR, int W>
 __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int row_begin, int row_end, int block_begin, int block_end,
-                                               int rotate, unsigned char* smem)
+                                               int rotate, const int* list, unsigned char* smem)
 {
     constexpr int M = (AR + 1) / 2;  // MFMA tiles along the rows
     constexpr int R = stream_ring(C, AR, W);
@@ -160,7 +224,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
 
     // ---- start: row ids, the weights of the first units, then (ids known) their activations -------------------
     const int first = min(total, R);
-    const int32_t* id_list = p.a_row != nullptr ? p.a_row : p.out_row;
+    const int32_t* id_list = list != nullptr ? nullptr : (p.a_row != nullptr ? p.a_row : p.out_row);
     if (id_list != nullptr)
         lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(id_list)), static_cast<uint32_t>(min(row_begin + lane, row_end - 1)) * 4u, ids_addr);
     int next_u = 0, next_slot = 0;  // the unit of the block at w_block, and the slot, the next load goes to
@@ -192,7 +256,9 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     for (int i = 0; i < LA; ++i) {
         const int r = i * 8 + r8;
         int row = min(row_begin + r, row_end - 1);  // rows past the end repeat the last one
-        if (p.a_row != nullptr) row = p.a_div == 1 ? ids[r] : ids[r] / p.a_div;
+        if (list != nullptr) row = list[row];
+        else if (p.a_row != nullptr) row = ids[r];
+        if (p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
         off_a[i] = static_cast<uint32_t>(row) * row_bytes + ((c8 ^ ((r >> 1) & 7)) * 16);
     }
     if (p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
@@ -311,15 +377,23 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     }
 }
 
-template <int C, int W>
+template <int C, int W, bool INLINE>
 __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int* list = nullptr;
+    const int32_t* offsets = p.offsets;
+    if constexpr (INLINE) {
+        InlineDispatch* d = reinterpret_cast<InlineDispatch*>(smem + stream_ring_bytes(C, W) + W * kStreamIdBytes);
+        sort_assignments<W * kWave>(p, *d, blockIdx.x == 0);
+        list = d->list;
+        offsets = d->offs;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     clear_unrouted<bf16_t>(p, static_cast<int64_t>(blockIdx.x) * W + wave, static_cast<int64_t>(gridDim.x) * W);
     constexpr int TILE_ROWS = 8 * stream_max_ar(C), COLS = 16 * C;
     const int n_blocks = p.N / COLS;
-    const ExpertTiles et = scan_row_tiles(p, TILE_ROWS);
+    const ExpertTiles et = scan_row_tiles(p, offsets, TILE_ROWS);
     // Every workgroup begins its blocks at another place of the reduction: rows a power of two bytes apart put the same
     // columns of all rows on few memory channels, and workgroups that walk the reduction in step all ask these
     // (rows of 8 and 32 KiB, 256 workgroups: 5.3 and 4.8 TB/s in step, 6.1 rotated; rows of 4.5 KiB 6.0 either way).
@@ -339,23 +413,30 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         const int block_end = min(n_blocks, block + end - item);
         const int rows = row_end - row_begin;
         constexpr int MAX_AR = stream_max_ar(C);
-        if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
-        else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
-        else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
-        else stream_segment<C, MAX_AR, W>(p, e, row_begin, row_end, block, block_end, lin, smem);
+        if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
+        else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
+        else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
+        else stream_segment<C, MAX_AR, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
         item += block_end - block;
     }
+}
+
+template <int C, int W, bool INLINE>
+static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
+{
+    constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C, W)) + W * kStreamIdBytes + (INLINE ? sizeof(InlineDispatch) : 0);
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    auto kern = stream_gemm_kernel<C, W, INLINE>;
+    static std::atomic<uint64_t> allowed{0};
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
+    hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(W * kWave), lds, stream, p);
+    return EXF_OK;
 }
 
 template <int C, int W>
 static int launch_stream(const StreamGemm& p, hipStream_t stream)
 {
-    constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C, W)) + W * kStreamIdBytes;
-    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    auto kern = stream_gemm_kernel<C, W>;
-    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds)) return rc;
-    hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(W * kWave), lds, stream, p);
-    return EXF_OK;
+    return p.topk_idx != nullptr ? launch_stream_as<C, W, true>(p, stream) : launch_stream_as<C, W, false>(p, stream);
 }
 
 // Columns per block, by a model of the launch: with q blocks per workgroup it runs ceil(q)/q times as long as its
@@ -464,7 +545,7 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
 }
 
 // WI items per workgroup, WK wavefronts per item (they cut the reduction into parts).
-template <int C, int M, int WK, int WI, int D>
+template <int C, int M, int WK, int WI, int D, bool INLINE>
 __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGemm p)
 {
     constexpr int COLS = 16 * C, RS = COLS + 4;  // (padded: the 16 rows of a float4 column store hit distinct banks)
@@ -472,11 +553,18 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     extern __shared__ float red[];  // [WI][WK][TILE_ROWS][RS]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     clear_unrouted<float>(p, blockIdx.x * (WK * WI) + wave, static_cast<int64_t>(gridDim.x) * (WK * WI));
+    const int32_t *a_row = p.a_row, *offsets = p.offsets;
+    if constexpr (INLINE) {
+        InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * WK * TILE_ROWS * RS);
+        sort_assignments<WK * WI * kWave>(p, *d, blockIdx.x == 0);
+        a_row = d->list;
+        offsets = d->offs;
+    }
 
     // work items are numbered (expert, column block, row tile); every XCD takes a contiguous share, so the row
     // tiles of a weight block and the column blocks of an expert's rows meet in one L2
     const int n_blocks = (p.N + COLS - 1) / COLS;
-    const ExpertTiles et = scan_row_tiles(p, TILE_ROWS);
+    const ExpertTiles et = scan_row_tiles(p, offsets, TILE_ROWS);
     const int total = et.total * n_blocks;
     const int xcd = static_cast<int>(blockIdx.x % kXcdCount), pos = static_cast<int>(blockIdx.x / kXcdCount);
     const int first_item = static_cast<int>(static_cast<int64_t>(total) * xcd / kXcdCount);
@@ -501,7 +589,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
         const int u_begin = part * units / WK, u_end = (part + 1) * units / WK;
         float* mine = item_red + part * (TILE_ROWS * RS);
         const int m_used = (row_end - row_begin + 15) / 16;
-#define EXF_EXACT_UNITS(MU) exact_units<C, MU, D, RS>(wexp, act, p.a_row, p.a_div, row_begin, row_end, n0, p.K, p.N, u_begin, u_end, mine)
+#define EXF_EXACT_UNITS(MU) exact_units<C, MU, D, RS>(wexp, act, a_row, p.a_div, row_begin, row_end, n0, p.K, p.N, u_begin, u_end, mine)
         if constexpr (M == 1) {
             EXF_EXACT_UNITS(1);
         } else {
@@ -543,13 +631,14 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     }
 }
 
-template <int C, int M, int WK, int WI, int D>
-static int launch_exact(const StreamGemm& p, hipStream_t stream)
+template <int C, int M, int WK, int WI, int D, bool INLINE>
+static int launch_exact_as(const StreamGemm& p, hipStream_t stream)
 {
     constexpr int TILE_ROWS = 16 * M;
-    constexpr size_t lds = static_cast<size_t>(WK * WI) * TILE_ROWS * (16 * C + 4) * sizeof(float);
-    auto kern = exact_gemm_kernel<C, M, WK, WI, D>;
-    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds)) return rc;
+    constexpr size_t lds = static_cast<size_t>(WK * WI) * TILE_ROWS * (16 * C + 4) * sizeof(float) + (INLINE ? sizeof(InlineDispatch) : 0);
+    auto kern = exact_gemm_kernel<C, M, WK, WI, D, INLINE>;
+    static std::atomic<uint64_t> allowed{0};
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     // row tiles: whole ones and at most one partial tile per expert with rows
     const int64_t A = p.max_rows;
     const int64_t row_tiles = A / TILE_ROWS + (A < p.E_local ? A : p.E_local);
@@ -558,6 +647,12 @@ static int launch_exact(const StreamGemm& p, hipStream_t stream)
     if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: too many tiles");
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(WK * WI * kWave), lds, stream, p);
     return EXF_OK;
+}
+
+template <int C, int M, int WK, int WI, int D>
+static int launch_exact(const StreamGemm& p, hipStream_t stream)
+{
+    return p.topk_idx != nullptr ? launch_exact_as<C, M, WK, WI, D, true>(p, stream) : launch_exact_as<C, M, WK, WI, D, false>(p, stream);
 }
 
 // Many tiles and a short reduction: 64 x 64 tiles, one wavefront each, nothing to add up.  Otherwise the reduction

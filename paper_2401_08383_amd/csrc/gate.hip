@@ -508,11 +508,8 @@ static int launch_gate_bf16_lds(const void* x, const void* wg, int64_t T, int d,
 #define EXF_LAUNCH_GATE_LDS(W)                                                                                                   \
     do {                                                                                                                        \
         auto kern = gate_bf16_lds_kernel<NT, W>;                                                                                \
-        if (lds > 64 * 1024) {                                                                                                  \
-            hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                                 static_cast<int>(lds));                                                       \
-            if (err != hipSuccess) return fail(EXF_ERR_HIP, "moe_gate_topk: LDS attribute: %s", hipGetErrorString(err));         \
-        }                                                                                                                       \
+        static std::atomic<uint64_t> allowed{0};                                                                                \
+        if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_gate_topk")) return rc;                  \
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(W * 64), lds, stream, static_cast<const bf16_t*>(x),  \
                            static_cast<const bf16_t*>(wg), T, d, E, k, renormalize, logits_out, topk_idx, topk_w);              \
     } while (0)

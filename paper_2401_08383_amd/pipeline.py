@@ -9,12 +9,24 @@ moe_expert_ffn_fused reads and writes the unsorted token rows, so no combine cal
 """
 from __future__ import annotations
 
+import ctypes
+
 import torch
 
 from . import binding as B
 
 
-class MoELayerRun:
+class _Prepared:
+    """A run whose arguments are put in order once: ``_args`` is dropped whenever an attribute is assigned."""
+    _args = None
+
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        if name != "_args":
+            object.__setattr__(self, "_args", None)
+
+
+class MoELayerRun(_Prepared):
     def __init__(self, x, w_gate, w1, w2, k, renormalize=False, expert_map=None, E_local=None, topk_idx=None,
                  act=B.EXF_ACT_GELU_ERF, fused=False):
         self.lib = B.lib()
@@ -81,14 +93,28 @@ class MoELayerRun:
         B._check(self.lib.moe_combine(self.y_sorted.data_ptr(), self.sorted_of_src.data_ptr(), self.topk_w.data_ptr(), self.T,
                                       self.d, self.k, self.dt, self.out.data_ptr(), B._stream()))
 
+    def _describe(self):
+        p = B._ptr
+        d = B.MoELayerDesc(
+            forced_idx=p(self.forced_idx), expert_map=p(self.expert_map), T=self.T, d=self.d, f=self.f, E=self.E, E_local=self.E_local,
+            k=self.k, renormalize=self.renorm, act=self.act, dt=self.dt, fused=int(self.fused), topk_idx=p(self.topk_idx),
+            topk_w=p(self.topk_w), x_sorted=p(self.x_sorted), src_of_sorted=p(self.src_of_sorted), sorted_of_src=p(self.sorted_of_src),
+            expert_counts=p(self.expert_counts), expert_offsets=p(self.expert_offsets), y_sorted=p(self.y_sorted), out=p(self.out),
+            dispatch_workspace=p(self.ws_dispatch), dispatch_workspace_bytes=self.ws_dispatch.numel(), ffn_workspace=p(self.ws_ffn),
+            ffn_workspace_bytes=self.ws_ffn.numel())
+        self._args = (d, ctypes.addressof(d), self.lib.moe_layer_forward)
+        return self._args
+
     def step(self):
-        self.gate()
-        self.dispatch()
-        self.ffn()
-        self.combine()
+        """The whole pass in one native call (gate, dispatch, expert FFN, combine)."""
+        d, address, forward = self._args or self._describe()
+        d.x, d.w_gate, d.w1, d.w2 = self.x.data_ptr(), self.w_gate.data_ptr(), self.w1.data_ptr(), self.w2.data_ptr()
+        rc = forward(address, B._stream())
+        if rc:
+            B._check(rc)
 
 
-class AffinityRun:
+class AffinityRun(_Prepared):
     def __init__(self, trace, placement, E, G, one_pass=True):
         self.lib = B.lib()
         self.one_pass = bool(one_pass)  # step() = affinity_statistics, else affinity_histogram + placement_locality
@@ -122,10 +148,12 @@ class AffinityRun:
     def statistics(self, trace=None):
         """Both results from one pass over the trace (affinity_statistics)."""
         t = self.trace if trace is None else trace
-        B._check(self.lib.affinity_statistics(t.data_ptr(), self.placement.data_ptr(), self.L, self.N, self.E, self.G,
-                                              self.counts.data_ptr(), self.loads.data_ptr(), self.cond_prob.data_ptr(),
-                                              self.n_invalid.data_ptr(), self.local_per_pair.data_ptr(), self.ws_hist.data_ptr(),
-                                              self.ws_hist.numel(), B._stream()))
+        if self._args is None:
+            self._args = (self.L, self.N, self.E, self.G, self.counts.data_ptr(), self.loads.data_ptr(), self.cond_prob.data_ptr(),
+                          self.n_invalid.data_ptr(), self.local_per_pair.data_ptr(), self.ws_hist.data_ptr(), self.ws_hist.numel())
+        rc = self.lib.affinity_statistics(t.data_ptr(), self.placement.data_ptr(), *self._args, B._stream())
+        if rc:
+            B._check(rc)
 
     def step(self):
         if self.one_pass:

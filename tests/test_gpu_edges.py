@@ -67,3 +67,54 @@ def test_streamed_ffn_fused(oracle, T, d, f, E, k):
 @pytest.mark.parametrize("counts", [[0, 1, 15, 16, 17, 64, 65], [300, 0, 5], [1]])
 def test_exact_ffn_ragged(oracle, counts, d, f):
     P._ffn_case(oracle, "f32", counts, d, f, 0, True, seed=1500 + d + f)
+
+
+# ----------------------------------------------------------------------------- one native call per layer
+@pytest.mark.parametrize("T,k,E,E_local,dtype,fused,routing", [
+    (1, 1, 8, 8, "bf16", True, "gate"), (16, 2, 64, 64, "bf16", True, "gate"), (300, 2, 33, 11, "bf16", True, "gate"),
+    (1024, 1, 64, 64, "bf16", True, "ids"), (1025, 1, 64, 64, "bf16", True, "ids"), (512, 2, 64, 8, "bf16", True, "ids"),
+    (77, 1, 8, 1, "bf16", True, "dropped"), (513, 1, 9, 9, "f32", True, "ids"), (200, 2, 5, 5, "f32", False, "gate"), (90, 2, 7, 7, "bf16", False, "ids")])
+def test_layer_forward_is_its_calls(T, k, E, E_local, dtype, fused, routing):
+    """moe_layer_forward writes what the separate calls write, maps included, also where it sorts without a dispatch launch."""
+    _say(f"layer forward T={T} k={k} E={E} E_local={E_local} {dtype} fused={fused} {routing}")
+    from paper_2401_08383_amd.pipeline import MoELayerRun
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1600 + T)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    d, f = 128, 192
+
+    def rnd(*shape):
+        return torch.randn(shape, device="cuda", generator=g).to(dt)
+
+    expert_map = None
+    if E_local < E:
+        expert_map = torch.full((E,), -1, dtype=torch.int32, device="cuda")
+        expert_map[torch.randperm(E, device="cuda", generator=g)[:E_local]] = torch.arange(E_local, dtype=torch.int32, device="cuda")
+    idx = None
+    if routing == "ids":
+        idx = torch.randint(-1, E + 2, (T, k), device="cuda", generator=g, dtype=torch.int32)  # invalid ids among them
+    elif routing == "dropped":
+        idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+    run = MoELayerRun(rnd(T, d), rnd(E, d), rnd(E_local, f, d), rnd(E_local, d, f), k, k > 1, expert_map=expert_map, topk_idx=idx, fused=fused)
+    names = ["topk_idx", "topk_w", "src_of_sorted", "sorted_of_src", "expert_counts", "expert_offsets", "out"]
+
+    def results(how):
+        for n in names:
+            getattr(run, n).fill_(-7)
+        how()
+        return [getattr(run, n).clone() for n in names]
+
+    def calls():
+        run.gate()
+        run.dispatch()
+        run.ffn()
+        run.combine()
+
+    ref = results(calls)
+    got = results(run.step)
+    for n, a, b in zip(names, got, ref):
+        assert torch.equal(a, b), n
+    run.x = rnd(T, d)  # an attribute that is assigned is used
+    for n, a, b in zip(names, results(run.step), results(calls)):
+        assert torch.equal(a, b), n
