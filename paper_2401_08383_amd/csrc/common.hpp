@@ -47,6 +47,8 @@ constexpr int kWave = 64;  // CDNA wavefront width
 
 // ---- device side -------------------------------------------------------------------------
 typedef uint16_t bf16_t;  // storage only; arithmetic is fp32
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 
@@ -150,5 +152,59 @@ __device__ __forceinline__ unsigned long long same_expert_lanes(int e, int E_loc
     }
     return m;
 }
+
+// ---------------------------------------------------------------------------- direct-to-LDS loads
+// A pointer that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+    return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// One wavefront-wide direct-to-LDS load: lane i fetches 16 bytes at base + voff and they land at
+// LDS byte address lds_addr + 16*i (M0 carries the wavefront-uniform LDS address).  Issued as
+// inline assembly on purpose: the compiler then keeps exact lgkmcnt waits for the ds_read
+// operand fetches, and the landing of these loads is awaited explicitly with wait_vmcnt.
+__device__ __forceinline__ void lds_dma_16B(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
+#else
+    (void)base; (void)voff; (void)lds_addr;
+#endif
+}
+
+// The same for data that is read once: streamed past the caches.
+__device__ __forceinline__ void lds_dma_16B_stream(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
+#else
+    (void)base; (void)voff; (void)lds_addr;
+#endif
+}
+
+// One wavefront-wide direct-to-LDS load of 4 bytes per lane: lane i fetches base + voff and the word
+// lands at LDS byte address lds_addr + 4*i.
+__device__ __forceinline__ void lds_dma_4B(const unsigned char* base, uint32_t voff, uint32_t lds_addr)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1\n" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory");
+#else
+    (void)base; (void)voff; (void)lds_addr;
+#endif
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+#endif
+}
+
 
 }  // namespace exf

@@ -655,15 +655,16 @@ static int launch_exact(const StreamGemm& p, hipStream_t stream)
     return p.topk_idx != nullptr ? launch_exact_as<C, M, WK, WI, D, true>(p, stream) : launch_exact_as<C, M, WK, WI, D, false>(p, stream);
 }
 
-// Many tiles and a short reduction: 64 x 64 tiles, one wavefront each, nothing to add up.  Otherwise the reduction
-// is cut over the wavefronts of a workgroup, and narrow blocks spread a small problem over the chip.
+// Enough tiles of 64 columns x 16 M rows for the chip: one wavefront per tile where the reduction is short (nothing to
+// add up), four otherwise.  A smaller problem is cut into 16 x 16 tiles with four wavefronts along the reduction
+// (512 tokens x 8 experts x 64 x 256: 36 workgroups of 64 rows took 8.3 us in the second
+// contraction, 4 now).
 template <int M>
 static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 {
     const int64_t tiles = (p.max_rows < p.E_local ? p.max_rows : p.E_local) + p.max_rows / (16 * M);
-    if (p.K <= 1024 && tiles * ((p.N + 63) / 64) >= 512) return launch_exact<4, M, 1, 4, 2>(p, stream);
-    if (tiles * ((p.N + 63) / 64) >= 384) return launch_exact<4, M, 4, 1, 2>(p, stream);
-    return launch_exact<1, M, 8, 1, 2>(p, stream);
+    if (tiles * ((p.N + 63) / 64) < 384) return launch_exact<1, 1, 4, 1, 2>(p, stream);
+    return p.K <= 1024 ? launch_exact<4, M, 1, 4, 2>(p, stream) : launch_exact<4, M, 4, 1, 2>(p, stream);
 }
 
 // ---------------------------------------------------------------------------- host

@@ -118,3 +118,10 @@ def test_layer_forward_is_its_calls(T, k, E, E_local, dtype, fused, routing):
     run.x = rnd(T, d)  # an attribute that is assigned is used
     for n, a, b in zip(names, results(run.step), results(calls)):
         assert torch.equal(a, b), n
+
+
+# ----------------------------------------------------------------------------- gate: ragged reductions, both tile heights
+@pytest.mark.parametrize("T,d,E,k", [(1, 8, 1, 1), (17, 56, 16, 2), (16, 72, 17, 2), (33, 2056, 33, 1), (8191, 64, 64, 2), (8192, 200, 64, 2),
+                                     (8200, 136, 17, 1), (40, 4096, 32, 2), (64 * 128 + 65, 1088, 48, 1)])
+def test_gate_units_and_token_tiles(oracle, T, d, E, k):
+    P.test_gate_topk_parity(oracle, "bf16", T, d, E, k, 1)
