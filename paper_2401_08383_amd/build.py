@@ -21,6 +21,7 @@ FLAGS = [
     # packed fp32 VALU forms are kept off (device pass only; the host pass ignores the feature)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function", "-Wno-pass-failed",
+    "-mllvm", "-pragma-unroll-threshold=1000000",  # the K loops are unrolled by hand-placed slots: completely or not at all
 ]
 
 

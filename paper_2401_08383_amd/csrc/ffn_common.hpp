@@ -67,7 +67,7 @@ struct StreamGemm {
 };
 constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for itself
 // Is the path taken for A rows of `dt` spread over E_local experts?
-bool stream_path_fits(int64_t A, int E_local, int dt);
+bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
 
 // moe_dispatch (index maps) and moe_expert_ffn_fused as one: the first contraction sorts the assignments itself.  Only
@@ -77,7 +77,10 @@ struct FfnRouting {
     int E;
     int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
 };
-inline bool routed_path_fits(int64_t A, int E_local, int dt) { return A > 0 && A <= kInlineDispatchMax && stream_path_fits(A, E_local, dt); }
+inline bool routed_path_fits(int64_t A, int d, int f, int E_local, int dt)
+{
+    return A > 0 && A <= kInlineDispatchMax && stream_path_fits(A, d, f, E_local, dt);
+}
 int ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
                      int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream);
 

@@ -10,7 +10,7 @@ extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
     if (rc != EXF_OK) return rc;
     const int32_t* idx = l.forced_idx != nullptr ? l.forced_idx : l.topk_idx;
     if (l.fused != 0 && l.k >= 1 && l.k <= EXF_MAX_TOPK && l.E >= 1 && l.E_local >= 1 && l.E_local <= EXF_MAX_EXPERTS &&
-        exf::routed_path_fits(l.T * l.k, l.E_local, l.dt)) {
+        exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt)) {
         EXF_REQUIRE_PTR(idx);
         EXF_REQUIRE_PTR(l.expert_counts);
         exf::FfnRouting r{idx, l.expert_map, l.E, l.src_of_sorted, l.sorted_of_src, l.expert_counts, l.expert_offsets};

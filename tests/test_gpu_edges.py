@@ -55,12 +55,26 @@ def test_streamed_ffn_row_tiles(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1300 + d + f)
 
 
-@pytest.mark.parametrize("T,d,f,E,k", [(1, 256, 1024, 8, 1), (3, 64, 64, 2, 2), (40, 192, 448, 1, 1), (41, 192, 448, 1, 1), (90, 128, 704, 64, 2)])
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 256, 1024, 8, 1), (3, 64, 64, 2, 2), (256, 192, 448, 1, 1), (257, 192, 448, 1, 1), (84, 128, 704, 3, 1), (90, 128, 704, 64, 2)])
 def test_streamed_ffn_fused(oracle, T, d, f, E, k):
-    """Gathered rows, scattered and scaled results, tokens without a resident expert; 40 and 41 rows per expert are the two
-    sides of the rule that selects the path."""
+    """Gathered rows, scattered and scaled results, tokens without a resident expert; 256 and 257 rows are the two sides
+    of the rule that selects the path."""
     P._fused_case(oracle, T, d, f, E, E, k, 1, True, seed=1400 + T)
     P._fused_case(oracle, T, d, f, E, max(1, E // 3), k, 0, False, seed=1401 + T)
+
+
+# ----------------------------------------------------------------------------- grouped contraction (many rows per expert)
+@pytest.mark.parametrize("d,f", [(64, 64), (128, 320), (192, 448), (320, 256), (576, 832)])
+@pytest.mark.parametrize("counts", [[128, 129, 0, 192, 193], [64, 65, 1, 255, 256, 257], [287, 288, 289, 320, 321], [511, 544, 545, 576, 577], [0, 2049]])
+def test_grouped_ffn_row_tiles(oracle, counts, d, f):
+    """Tiles of every height and both widths, whole and cut ones, reductions from one K tile on."""
+    P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1700 + d + f)
+
+
+@pytest.mark.parametrize("T,d,f,E,k", [(700, 64, 192, 3, 1), (1500, 192, 320, 5, 2), (900, 320, 1088, 2, 2)])
+def test_grouped_ffn_fused(oracle, T, d, f, E, k):
+    P._fused_case(oracle, T, d, f, E, E, k, 1, True, seed=1800 + T)
+    P._fused_case(oracle, T, d, f, E, max(1, E // 2), k, 0, False, seed=1801 + T)
 
 
 @pytest.mark.parametrize("d,f", [(4, 4), (36, 20), (132, 260), (1028, 64)])
