@@ -26,6 +26,8 @@
 //   are summed by a second kernel.
 #include "common.hpp"
 
+#include <type_traits>
+
 namespace exf {
 
 constexpr int kXcds = 8;
@@ -103,14 +105,16 @@ struct TokVec {
 // 16-byte load of gfx950 needs no more, and it costs one more cache line per wavefront when it straddles.
 // (Odd token counts used to take 4-byte loads: 44 us for the transfers of a 24 x 999983 trace, 22 now.)
 // A lane whose vector is cut by the end of the chunk receives the LAST VEC ids; cut_vector() moves them.
-template <int VEC>
+// STREAM: the column is read once.
+template <int VEC, bool STREAM = true>
 __device__ __forceinline__ TokVec<VEC> load_tokens(const int32_t* __restrict__ col, int64_t n, int64_t end)
 {
     TokVec<VEC> r;
     const int64_t n_safe = min(n, end - VEC);  // callers guarantee end >= VEC; earlier chunks may be touched
     if constexpr (VEC == 4) {
         typedef int i32x4_v __attribute__((vector_size(4 * sizeof(int)), aligned(4)));
-        const i32x4_v q = __builtin_nontemporal_load(reinterpret_cast<const i32x4_v*>(col + n_safe));  // streamed once
+        const i32x4_v* at = reinterpret_cast<const i32x4_v*>(col + n_safe);
+        const i32x4_v q = STREAM ? __builtin_nontemporal_load(at) : *at;
         r.v[0] = q[0];
         r.v[1] = q[1];
         r.v[2] = q[2];
@@ -302,99 +306,229 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
 }
 
 // Counts for EVERY ordered layer pair l < m (the appendix statistic), pairs numbered source layer
-// first.  A workgroup owns a chunk of tokens and a group (l; m0 .. m0+g-1): it loads column l and
-// the g target columns and bins (col l, col m) - the same four-columns-for-three-pairs economy as
-// the one-hop kernel.  Groups are numbered q = 0 .. Q-1 in pair order; transitions with an invalid
-// end are skipped; the packed per-chunk partials go to part_counts[chunk][pair][words].
-template <int VEC>
-__global__ __launch_bounds__(kTraceThreads) void multihop_partial_kernel(const int32_t* __restrict__ trace, int L, int64_t N, int E,
-                                                                          int g, int Q, int copies, int words, int64_t chunk, int C,
-                                                                          uint32_t* __restrict__ part_counts)
+// first.  What bounds it is the LDS: one atomic per token and pair (24 layers x 1M tokens: 290 million, 64 of them in 8 to
+// 12 cycles), so everything else is kept below that.
+//   - A workgroup owns a chunk of tokens and a block pair (I, J) of four layers each: eight columns in registers give 16
+//     pairs, half a column read per pair (with one source and three targets it was 1.33, and the reads took 200 us).
+//   - The six pairs inside a block are handed out to the block pairs it is part of (19 histograms at 24 layers: 152 KB); with
+//     fewer than four blocks they have workgroups of their own.  All workgroups then have nearly the same work, and their
+//     number is made a whole number of rounds (see make_multihop_plan).
+//   - A histogram row starts at an even counter, so the word of a transition is row(a) + b/2 and its half is b%2: both
+//     are formed once per token and column, a transition costs one addition and one atomic.
+// Transitions with an invalid end are skipped; the packed per-chunk partials go to part_counts[chunk][pair][words].
+// 24 x 1M tokens, 64 experts: 207 us before, 89 now (7 LDS cycles an atomic, 55 us of the compute units' LDS).
+constexpr int kHopBlock = 4;       // layers per block
+constexpr int kHopThreads = 1024;
+constexpr int kHopInside = 6;      // pairs inside a block
+constexpr int kHopShareBlocks = 4; // from so many blocks on the inside pairs are handed out
+__host__ __device__ constexpr int hop_inside_source(int k) { return k < 3 ? 0 : (k < 5 ? 1 : 2); }
+__host__ __device__ constexpr int hop_inside_target(int k) { return k < 3 ? k + 1 : (k < 5 ? k - 1 : 3); }
+// Inside pairs of block b that the block pair (b, other) takes; b == other: all (no handing out).
+__host__ __device__ inline unsigned hop_inside_mask(int b, int other, int blocks, int L)
 {
-    extern __shared__ uint32_t lds[];
-    uint32_t* hist = lds;  // [copies][g][words], two 16-bit counters per word
-    const int xcd = blockIdx.x % kXcds;
-    const int j = blockIdx.x / kXcds;
-    const int c = (j / Q) * kXcds + xcd;
-    const int q = j % Q;
-    if (c >= C) return;
-    for (int i = threadIdx.x; i < copies * g * words; i += kTraceThreads) lds[i] = 0u;
-    __syncthreads();
-
-    // group q -> source layer l, first target m0, number of pairs
-    int l = 0, before = 0, pair_base = 0;
-    for (;; ++l) {
-        const int targets = L - 1 - l;
-        const int groups = (targets + g - 1) / g;
-        if (q < before + groups) break;
-        before += groups;
-        pair_base += targets;
+    unsigned mask = 0;
+    for (int k = 0; k < kHopInside; ++k) {
+        const int turn = k < blocks - 1 ? k : k - (blocks - 1);  // (no divisions; blocks - 1 >= 3 where it is used)
+        const int partner = b + 1 + turn < blocks ? b + 1 + turn : b + 1 + turn - blocks;
+        const bool mine = b == other || (blocks >= kHopShareBlocks && partner == other);
+        if (mine && b * kHopBlock + hop_inside_target(k) < L) mask |= 1u << k;
     }
-    const int m0 = l + 1 + (q - before) * g;
-    const int my_pairs = min(g, L - m0);
-    pair_base += m0 - (l + 1);
-    const int total_pairs = L * (L - 1) / 2;
+    return mask;
+}
+// Block pair q: first those with I < J, then (few blocks) the blocks themselves.
+__host__ __device__ inline void hop_blocks(int q, int blocks, int& I, int& J)
+{
+    const int cross = blocks * (blocks - 1) / 2;
+    if (q >= cross) {
+        I = J = q - cross;
+        return;
+    }
+    for (I = 0; q >= blocks - 1 - I; ++I) q -= blocks - 1 - I;
+    J = I + 1 + q;
+}
 
+template <int VEC>
+__global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int32_t* __restrict__ trace, int L, int64_t N, int E,
+                                                                          int blocks, int Q, int copies, int copy_words, int words,
+                                                                          int64_t chunk, int C, uint32_t* __restrict__ part_counts)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];  // [copies][copy_words >= slots * words], two 16-bit counters per word
+    // every XCD takes an eighth of the workgroups, chunk by chunk: the block pairs of a chunk share its columns in one L2
+    const int64_t items = static_cast<int64_t>(C) * Q, item = (blockIdx.x % kXcds) * ((items + kXcds - 1) / kXcds) + blockIdx.x / kXcds;
+    if (item >= items) return;
+    const int c = static_cast<int>(item / Q);
+    int I, J;
+    hop_blocks(static_cast<int>(item % Q), blocks, I, J);
+    const int i0 = I * kHopBlock, j0 = J * kHopBlock;
+    const int targets = I == J ? 0 : min(kHopBlock, L - j0);  // (block I is whole where there is a later one)
+    const unsigned inside_i = hop_inside_mask(I, J, blocks, L), inside_j = I == J ? 0u : hop_inside_mask(J, I, blocks, L);
     const int64_t n_begin = static_cast<int64_t>(c) * chunk;
     const int64_t n_end = min(N, n_begin + chunk);
-    uint32_t* my_hist = hist + (threadIdx.x & (copies - 1)) * g * words;
-    const int64_t sweep = static_cast<int64_t>(kTraceThreads) * VEC;
-    auto load_cols = [&](int64_t n0, TokVec<VEC>(&col)[kAffMaxGroup + 1]) {  // clamped, never skipped
-        col[0] = load_tokens<VEC>(trace + static_cast<int64_t>(l) * N, n0, n_end);
+    const uint32_t hist_bytes = static_cast<uint32_t>(words) * 4u;
+    const uint32_t row_bytes = static_cast<uint32_t>((E + 1) / 2) * 4u;
+    const uint32_t my_copy = static_cast<uint32_t>(threadIdx.x & (copies - 1)) * static_cast<uint32_t>(copy_words) * 4u;
+    // The transitions of one sweep, in loops over the targets and over the two blocks: unrolled, the code of one sweep is 17 KB, and
+    // short traces wait for nothing else (18 layers x 9787 tokens: 19.5 us, 9787 tokens are one sweep or two).  As the source of a pair a token is the byte offset of its row, as the target that of its
+    // word and the addend: one addition and one atomic a transition.  CHECK: an invalid id adds 0 (to a word of row 0 or
+    // column 0); this costs as many vector instructions as the LDS has cycles, so clean wavefronts (nearly all) do without.
+    auto count_all = [&](auto check, const TokVec<VEC>(&col)[2 * kHopBlock], int left) {
+        constexpr bool CHECK = decltype(check)::value;
+        auto valid = [&](const TokVec<VEC>& t, int u) { return !CHECK || (static_cast<uint32_t>(t.v[u]) < static_cast<uint32_t>(E) && u < left); };
+        auto row_of = [&](const TokVec<VEC>& t, int u) { return valid(t, u) ? my_copy + __umul24(static_cast<uint32_t>(t.v[u]), row_bytes) : 0u; };
+        auto word_of = [&](const TokVec<VEC>& t, int u) { return valid(t, u) ? static_cast<uint32_t>(t.v[u]) / 2u * 4u : 0u; };
+        auto one_of = [&](const TokVec<VEC>& t, int u) { return valid(t, u) ? 1u << (static_cast<uint32_t>(t.v[u]) % 2u * 16u) : 0u; };
+        auto add = [&](uint32_t at, uint32_t one) { atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(lds) + at), one); };
+        uint32_t slot = 0;
+        {
+            uint32_t row[kHopBlock][VEC];
+            TokVec<VEC> target[kHopBlock];
 #pragma unroll
-        for (int s = 1; s <= kAffMaxGroup; ++s)
-            col[s] = load_tokens<VEC>(trace + static_cast<int64_t>(min(m0 + s - 1, L - 1)) * N, n0, n_end);
-    };
-    TokVec<VEC> col[kAffMaxGroup + 1], nxt[kAffMaxGroup + 1];
-    load_cols(n_begin + static_cast<int64_t>(threadIdx.x) * VEC, col);
-    for (int64_t base = n_begin; base < n_end; base += sweep) {
-        const int64_t n0 = base + static_cast<int64_t>(threadIdx.x) * VEC;
-        load_cols(n0 + sweep, nxt);
-        bool clean = n0 + VEC <= n_end;
+            for (int s = 0; s < kHopBlock; ++s) {
+                target[s] = col[kHopBlock + s];
 #pragma unroll
-        for (int s = 0; s <= kAffMaxGroup; ++s) {
-            unsigned m = 0;
-#pragma unroll
-            for (int u = 0; u < VEC; ++u) m = max(m, static_cast<unsigned>(col[s].v[u]));
-            clean = clean && m < static_cast<unsigned>(E);  // (clamped duplicate columns repeat a checked one)
-        }
-        if (__ballot(!clean) == 0ull) {
-#pragma unroll
-            for (int s = 1; s <= kAffMaxGroup; ++s) {
-                if (s > my_pairs) break;
-                uint32_t* h = my_hist + (s - 1) * words;
+                for (int u = 0; u < VEC; ++u) row[s][u] = row_of(col[s], u);
+            }
+#pragma unroll 1
+            for (int t = 0; t < targets; ++t) {
+                uint32_t word[VEC], one[VEC];
 #pragma unroll
                 for (int u = 0; u < VEC; ++u) {
-                    const int bin = col[0].v[u] * E + col[s].v[u];
-                    atomicAdd(&h[bin >> 1], 1u << ((bin & 1) * 16));
+                    word[u] = slot + word_of(target[0], u);
+                    one[u] = one_of(target[0], u);
                 }
+#pragma unroll
+                for (int s = 0; s < kHopBlock; ++s)
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) add(s * hist_bytes + row[s][u] + word[u], valid(col[s], u) ? one[u] : 0u);
+                slot += kHopBlock * hist_bytes;
+#pragma unroll
+                for (int s = 0; s + 1 < kHopBlock; ++s) target[s] = target[s + 1];
             }
+        }
+        slot = targets > 0 ? kHopBlock * kHopBlock * hist_bytes : 0u;
+        TokVec<VEC> x[kHopBlock];
+#pragma unroll
+        for (int s = 0; s < kHopBlock; ++s) x[s] = col[s];
+#pragma unroll 1
+        for (unsigned mask = inside_i, h = 0; h < 2; ++h, mask = inside_j) {
+#pragma unroll
+            for (int k = 0; k < kHopInside; ++k)
+                if ((mask >> k & 1u) != 0u) {
+                    const TokVec<VEC>&from = x[hop_inside_source(k)], &to = x[hop_inside_target(k)];
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) add(slot + row_of(from, u) + word_of(to, u), valid(from, u) ? one_of(to, u) : 0u);
+                    slot += hist_bytes;
+                }
+#pragma unroll
+            for (int s = 0; s < kHopBlock; ++s) x[s] = col[kHopBlock + s];
+        }
+    };
+    const int64_t sweep = static_cast<int64_t>(kHopThreads) * VEC;
+    auto load_cols = [&](int64_t n0, TokVec<VEC>(&col)[2 * kHopBlock]) {  // clamped, never skipped
+#pragma unroll
+        for (int s = 0; s < 2 * kHopBlock; ++s)
+            col[s] = load_tokens<VEC, false>(trace + static_cast<int64_t>(min(s < kHopBlock ? i0 + s : j0 + s - kHopBlock, L - 1)) * N, n0, n_end);
+    };
+    TokVec<VEC> col[2 * kHopBlock], nxt[2 * kHopBlock];
+    const int64_t wave_first = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)) * (kWave * VEC);
+    load_cols(n_begin + static_cast<int64_t>(threadIdx.x) * VEC, col);
+    for (int i = threadIdx.x; i < copies * (copy_words / 2); i += kHopThreads) reinterpret_cast<uint2*>(lds)[i] = make_uint2(0u, 0u);
+    __syncthreads();
+    for (int64_t base = n_begin; base + wave_first < n_end; base += sweep) {
+        const int64_t n0 = base + static_cast<int64_t>(threadIdx.x) * VEC;
+        if (base + sweep + wave_first < n_end) load_cols(n0 + sweep, nxt);
+        unsigned m = 0;
+#pragma unroll
+        for (int s = 0; s < 2 * kHopBlock; ++s)
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) m = max(m, static_cast<unsigned>(col[s].v[u]));  // (clamped duplicate columns repeat a checked one)
+        const int left = static_cast<int>(min(n_end - n0, static_cast<int64_t>(VEC)));  // tokens of this lane
+        if (__ballot(left < VEC || m >= static_cast<unsigned>(E)) == 0ull) {
+            count_all(std::false_type{}, col, left);
         } else {
 #pragma unroll
-            for (int s = 0; s <= kAffMaxGroup; ++s) cut_vector(col[s], n0, n_end);
-#pragma unroll
-            for (int s = 1; s <= kAffMaxGroup; ++s) {
-                if (s > my_pairs) break;
-                uint32_t* h = my_hist + (s - 1) * words;
-#pragma unroll
-                for (int u = 0; u < VEC; ++u) {
-                    const int a = col[0].v[u], b = col[s].v[u];
-                    if (n0 + u < n_end && static_cast<unsigned>(a) < static_cast<unsigned>(E) &&
-                        static_cast<unsigned>(b) < static_cast<unsigned>(E)) {
-                        const int bin = a * E + b;
-                        atomicAdd(&h[bin >> 1], (bin & 1) ? 0x10000u : 1u);
-                    }
-                }
-            }
+            for (int s = 0; s < 2 * kHopBlock; ++s) cut_vector(col[s], n0, n_end);
+            count_all(std::true_type{}, col, left);
         }
 #pragma unroll
-        for (int s = 0; s <= kAffMaxGroup; ++s) col[s] = nxt[s];
+        for (int s = 0; s < 2 * kHopBlock; ++s) col[s] = nxt[s];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < my_pairs * words; i += kTraceThreads) {
-        uint32_t sum = 0;
-        for (int r = 0; r < copies; ++r) sum += hist[r * g * words + i];
-        part_counts[(static_cast<size_t>(c) * total_pairs + pair_base) * words + i] = sum;
+
+    // flush, replicas summed (packed halves cannot carry: a bin holds at most `chunk` < 65536)
+    const size_t total_pairs = static_cast<size_t>(L) * (L - 1) / 2;
+    const int cross = targets > 0 ? kHopBlock * kHopBlock : 0;
+    const int used = cross + __builtin_popcount(inside_i) + __builtin_popcount(inside_j);
+    const unsigned per_slot = static_cast<unsigned>(words / 2), inverse = ((1u << 26) + per_slot - 1u) / per_slot;  // exact below 20 x 1024
+    for (int i = threadIdx.x; i < used * (words / 2); i += kHopThreads) {
+        const int slot = static_cast<int>(static_cast<unsigned>(i) * inverse >> 26), w = i - slot * (words / 2);
+        int l, to;  // layers of the slot's pair
+        if (slot < cross) {
+            l = i0 + slot % kHopBlock;
+            to = j0 + slot / kHopBlock;
+            if (slot / kHopBlock >= targets) continue;
+        } else {
+            unsigned left = inside_i | inside_j << kHopInside;
+            for (int r = slot - cross; r > 0; --r) left &= left - 1u;
+            const int k = __builtin_ctz(left), first = k < kHopInside ? i0 : j0, kk = k < kHopInside ? k : k - kHopInside;
+            l = first + hop_inside_source(kk);
+            to = first + hop_inside_target(kk);
+        }
+        const uint2* from = reinterpret_cast<const uint2*>(lds + static_cast<size_t>(slot) * words) + w;
+        uint2 sum = make_uint2(0u, 0u);
+#pragma unroll 4
+        for (int r = 0; r < copies; ++r) {
+            const uint2 v = from[r * (copy_words / 2)];
+            sum.x += v.x;
+            sum.y += v.y;
+        }
+        const size_t pair = static_cast<size_t>(l) * (2 * L - l - 1) / 2 + (to - l - 1);
+        reinterpret_cast<uint2*>(part_counts + (static_cast<size_t>(c) * total_pairs + pair) * words)[w] = sum;
+    }
+}
+
+// Half a wavefront per (pair, source expert) row, lane w of it the counters 2w and 2w+1: sums the chunks (16 independent loads
+// in flight), the row sum by lane exchanges, the conditional probabilities.  Bound by the read of the partials: a lane per
+// counter fetched every word twice (24 layers, 64 experts, 17 chunks: 18 us, now 12).
+__global__ __launch_bounds__(256) void multihop_finalize_kernel(const uint32_t* __restrict__ part_counts, int C, int pairs, int E, int words,
+                                                                int64_t* __restrict__ counts, float* __restrict__ cond_prob)
+{
+    const int row = static_cast<int>(blockIdx.x) * (256 / 32) + static_cast<int>(threadIdx.x) / 32;
+    const bool live = row < pairs * E;
+    const int w = threadIdx.x % 32, row_words = (E + 1) / 2;
+    const int r = live ? row : 0;
+    const int pair = r / E, i = r % E;
+    const uint32_t* src = part_counts + static_cast<size_t>(pair) * words + i * row_words + min(w, row_words - 1);
+    const size_t step = static_cast<size_t>(pairs) * words;
+    long long even = 0, odd = 0;
+    for (int c0 = 0; c0 < C; c0 += 16) {
+        uint32_t v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = src[min(c0 + u, C - 1) * step];  // clamped, never branched around
+        uint32_t lo = 0, hi = 0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            lo += c0 + u < C ? v[u] & 0xffffu : 0u;
+            hi += c0 + u < C ? v[u] >> 16 : 0u;
+        }
+        even += lo;
+        odd += hi;
+    }
+    if (w >= row_words) even = odd = 0;
+    long long sum = even + odd;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 32);
+    if (!live || w >= row_words) return;
+    const size_t o = static_cast<size_t>(row) * E + 2 * w;
+    auto share = [&](long long cnt) { return sum > 0 ? static_cast<float>(static_cast<double>(cnt) / static_cast<double>(sum)) : 0.0f; };
+    if (2 * w + 1 < E) {
+        typedef long long i64x2_v __attribute__((vector_size(2 * sizeof(long long)), aligned(8)));
+        typedef float f32x2_v __attribute__((vector_size(2 * sizeof(float)), aligned(4)));
+        *reinterpret_cast<i64x2_v*>(counts + o) = i64x2_v{even, odd};
+        if (cond_prob != nullptr) *reinterpret_cast<f32x2_v*>(cond_prob + o) = f32x2_v{share(even), share(odd)};
+    } else {
+        counts[o] = even;
+        if (cond_prob != nullptr) cond_prob[o] = share(even);
     }
 }
 
@@ -443,8 +577,7 @@ __global__ __launch_bounds__(256) void affinity_finalize_kernel(const uint32_t* 
             }
         }
         long long orphan = 0;
-        if (loads != nullptr)  // (the multi-hop statistic has no orphan tallies)
-            for (int c = p; c < C; c += kWave) orphan += part_orphan_next[(static_cast<size_t>(c) * pairs + l) * E + i];
+        for (int c = p; c < C; c += kWave) orphan += part_orphan_next[(static_cast<size_t>(c) * pairs + l) * E + i];
         orphan = wave_sum(orphan);
         const long long row_sum = wave_sum(cnt);
         if (p < E) {
@@ -743,35 +876,53 @@ extern "C" int affinity_statistics(const int32_t* trace, const int32_t* placemen
 
 namespace exf {
 struct MultihopPlan {
-    int g, Q, copies, words, C, vec, pairs;
+    int blocks, Q, copies, copy_words, words, C, vec, pairs;
     int64_t chunk;
-    size_t total_bytes;
+    size_t lds_bytes, total_bytes;
 };
+constexpr int kHopLdsBytes = 160 * 1024;
+constexpr int kHopBanks = 64;
+constexpr int64_t kHopMaxChunk = 65280;  // 16-bit counters cannot overflow; whole wavefronts of four tokens a lane
+constexpr int64_t kHopMinChunk = 1024;
+constexpr int64_t kHopPartialWords = 4 << 20;  // partials that are written and added up within a few microseconds
 static MultihopPlan make_multihop_plan(int L, int64_t N, int E)
 {
     MultihopPlan p;
     p.pairs = L * (L - 1) / 2;
-    p.words = (E * E + 1) / 2;
-    const size_t hist_bytes = static_cast<size_t>(p.words) * sizeof(uint32_t);
-    int g = static_cast<int>(kAffHistBudget / hist_bytes);
-    if (g > kAffMaxGroup) g = kAffMaxGroup;
-    if (g < 1) g = 1;
-    p.g = g;
+    p.words = (E * ((E + 1) / 2) + 1) / 2 * 2;
+    p.blocks = (L + kHopBlock - 1) / kHopBlock;
+    const int cross = p.blocks * (p.blocks - 1) / 2;
+    p.Q = cross + (p.blocks < kHopShareBlocks ? p.blocks : 0);
+    int slots = p.blocks >= 8 ? kHopBlock * kHopBlock + 2 : 1;  // (at least seven partners: one inside pair of each block)
+    for (int q = 0; q < p.Q && p.blocks < 8; ++q) {
+        int I, J;
+        hop_blocks(q, p.blocks, I, J);
+        const int inside = __builtin_popcount(hop_inside_mask(I, J, p.blocks, L)) + (I == J ? 0 : __builtin_popcount(hop_inside_mask(J, I, p.blocks, L)));
+        const int need = inside + (I == J ? 0 : kHopBlock * kHopBlock);
+        if (need > slots) slots = need;
+    }
+    // replicas of small histograms, so that hot bins do not serialise, each beginning on the LDS banks after the previous one's
+    p.copy_words = slots * p.words;
+    if (p.words < kHopBanks) p.copy_words += ((p.words - p.copy_words) % kHopBanks + kHopBanks) % kHopBanks;
     p.copies = 1;
-    while (p.copies < 16 && hist_bytes * g * (p.copies * 2) <= kAffHistBudget) p.copies *= 2;
-    p.Q = 0;
-    for (int l = 0; l + 1 < L; ++l) p.Q += (L - 1 - l + g - 1) / g;
-    if (p.Q < 1) p.Q = 1;
+    while (p.copies < 32 && p.copy_words * 4 * (p.copies * 2) <= kHopLdsBytes / 2) p.copies *= 2;
+    p.lds_bytes = static_cast<size_t>(p.copy_words) * p.copies * sizeof(uint32_t);
     p.vec = trace_vec(N);
-    const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;
-    int c_target = kTargetWorkgroups / p.Q;
-    if (c_target < 1) c_target = 1;
-    int64_t chunk = (N + c_target - 1) / c_target;
-    chunk = (chunk + sweep - 1) / sweep * sweep;
-    if (chunk < sweep) chunk = sweep;
-    if (chunk > kAffMaxChunk) chunk = kAffMaxChunk / sweep * sweep;
-    p.chunk = chunk;
-    p.C = static_cast<int>(N > 0 ? (N + chunk - 1) / chunk : 0);
+    // As few chunks as the counters allow (each costs a pass over its histograms), but a whole number of rounds of one workgroup
+    // per compute unit
+    int64_t c_least = (N + kHopMaxChunk - 1) / kHopMaxChunk;
+    if (c_least < 1) c_least = 1;
+    const int64_t rounds = (c_least * p.Q + kTargetWorkgroups - 1) / kTargetWorkgroups;
+    int64_t c_target = rounds * kTargetWorkgroups / p.Q;
+    // (two tokens a counter word at least, or clearing and writing the histograms takes longer than filling them - unless these are few)
+    const int64_t few = kHopPartialWords / (static_cast<int64_t>(p.pairs > 0 ? p.pairs : 1) * p.words);
+    int64_t c_most = N / (2 * p.words) > few ? N / (2 * p.words) : few;
+    if (c_most > N / kHopMinChunk) c_most = N / kHopMinChunk;
+    if (c_target > c_most) c_target = c_most;
+    if (c_target < c_least) c_target = c_least;
+    p.chunk = ((N + c_target - 1) / c_target + 255) / 256 * 256;  // (a wavefront cut by the end of its chunk takes the checked path)
+    if (p.chunk < 256) p.chunk = 256;
+    p.C = static_cast<int>(N > 0 ? (N + p.chunk - 1) / p.chunk : 0);
     p.total_bytes = align_up(static_cast<size_t>(p.C > 0 ? p.C : 1) * (p.pairs > 0 ? p.pairs : 1) * p.words * sizeof(uint32_t), 256);
     return p;
 }
@@ -798,25 +949,17 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* part_counts = static_cast<uint32_t*>(workspace);
     if (p.C > 0) {
-        const int c_pad = (p.C + kXcds - 1) / kXcds * kXcds;
-        const int64_t grid = static_cast<int64_t>(c_pad) * p.Q;
+        const int64_t grid = (static_cast<int64_t>(p.C) * p.Q + kXcds - 1) / kXcds * kXcds;
         if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "affinity_multihop: too many workgroups");
-        const size_t lds = static_cast<size_t>(p.copies) * p.g * p.words * sizeof(uint32_t);
-        if (p.vec == 4) {
-            if (int rc = allow_large_lds(multihop_partial_kernel<4>, lds, "affinity_multihop")) return rc;
-            hipLaunchKernelGGL(multihop_partial_kernel<4>, dim3(static_cast<unsigned>(grid)), dim3(kTraceThreads), lds, s, trace, L, N, E,
-                               p.g, p.Q, p.copies, p.words, p.chunk, p.C, part_counts);
-        } else {
-            if (int rc = allow_large_lds(multihop_partial_kernel<1>, lds, "affinity_multihop")) return rc;
-            hipLaunchKernelGGL(multihop_partial_kernel<1>, dim3(static_cast<unsigned>(grid)), dim3(kTraceThreads), lds, s, trace, L, N, E,
-                               p.g, p.Q, p.copies, p.words, p.chunk, p.C, part_counts);
-        }
+        auto kern = p.vec == 4 ? multihop_partial_kernel<4> : multihop_partial_kernel<1>;
+        static std::atomic<uint64_t> allowed4{0}, allowed1{0};
+        if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kHopLdsBytes, p.vec == 4 ? allowed4 : allowed1, "affinity_multihop")) return rc;
+        hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kHopThreads), p.lds_bytes, s, trace, L, N, E, p.blocks, p.Q,
+                           p.copies, p.copy_words, p.words, p.chunk, p.C, part_counts);
     }
-    // one wavefront per (pair, source expert) row: sums the chunks, forms the conditional probabilities
-    // (the finalize kernel of the one-hop statistic, told that there are pairs+1 "layers" and no loads)
-    const unsigned fin_grid = static_cast<unsigned>((p.pairs * E + kFinRowsPerWorkgroup - 1) / kFinRowsPerWorkgroup);
-    hipLaunchKernelGGL(affinity_finalize_kernel, dim3(fin_grid), dim3(256), 0, s, part_counts, nullptr, nullptr, nullptr, p.C, 1,
-                       p.pairs + 1, E, p.words, counts, nullptr, cond_prob, nullptr, nullptr, nullptr);
+    const int64_t fin_grid = (static_cast<int64_t>(p.pairs) * E + 256 / 32 - 1) / (256 / 32);
+    hipLaunchKernelGGL(multihop_finalize_kernel, dim3(static_cast<unsigned>(fin_grid)), dim3(256), 0, s, part_counts, p.C, p.pairs, E, p.words,
+                       counts, cond_prob);
     return check_launch("affinity_multihop");
 }
 

@@ -26,6 +26,13 @@ def test_trace_columns_that_start_and_end_anywhere(oracle, N):
 
 
 # ----------------------------------------------------------------------------- candidate scores
+@pytest.mark.parametrize("L,N,E", [(2, 65281, 64), (4, 5, 1), (5, 4100, 63), (8, 8193, 2), (9, 65280, 33), (12, 130561, 5), (13, 20000, 64), (16, 16385, 64),
+                                   (17, 9000, 31), (29, 24577, 7), (31, 3, 64), (33, 12289, 64)])
+def test_multihop_blocks(L, N, E):
+    """Whole and cut blocks of layers, few and many of them, rows of odd length, chunks at the counters' limit."""
+    Q.test_affinity_multihop_parity(L, N, E)
+
+
 @pytest.mark.parametrize("E,Bn,total", [(1, 1, 5), (33, 9, (1 << 31) - 1), (33, 9, 1 << 31), (64, 300, (1 << 31) - 1), (64, 300, 1 << 33),
                                         (63, 4099, 100000)])
 def test_candidate_scores_around_the_32_bit_table(E, Bn, total):
