@@ -17,7 +17,7 @@ def _say(msg):
 
 
 # ----------------------------------------------------------------------------- trace columns of any length
-@pytest.mark.parametrize("N", [3, 4, 5, 6, 7, 4097, 8190, 61441, 61443])
+@pytest.mark.parametrize("N", [3, 4, 5, 6, 7, 4097, 8190, 61441, 61443, 65537, 262145, 262147])
 def test_trace_columns_that_start_and_end_anywhere(oracle, N):
     """Columns off the 16-byte grid, last vectors cut by one to three ids, last chunks shorter than a vector."""
     P.test_affinity_and_locality_parity(oracle, 5, N, 24, 8)
