@@ -16,17 +16,14 @@ import torch
 from . import binding as B
 
 
-class _Prepared:
-    """A run whose arguments are put in order once: ``_args`` is dropped whenever an attribute is assigned."""
-    _args = None
+class MoELayerRun:
+    _args = None  # what step() passes, put in order once; dropped whenever an attribute is assigned
 
     def __setattr__(self, name, value):
         object.__setattr__(self, name, value)
         if name != "_args":
             object.__setattr__(self, "_args", None)
 
-
-class MoELayerRun(_Prepared):
     def __init__(self, x, w_gate, w1, w2, k, renormalize=False, expert_map=None, E_local=None, topk_idx=None,
                  act=B.EXF_ACT_GELU_ERF, fused=False):
         self.lib = B.lib()
@@ -96,25 +93,35 @@ class MoELayerRun(_Prepared):
     def _describe(self):
         p = B._ptr
         d = B.MoELayerDesc(
-            forced_idx=p(self.forced_idx), expert_map=p(self.expert_map), T=self.T, d=self.d, f=self.f, E=self.E, E_local=self.E_local,
-            k=self.k, renormalize=self.renorm, act=self.act, dt=self.dt, fused=int(self.fused), topk_idx=p(self.topk_idx),
-            topk_w=p(self.topk_w), x_sorted=p(self.x_sorted), src_of_sorted=p(self.src_of_sorted), sorted_of_src=p(self.sorted_of_src),
-            expert_counts=p(self.expert_counts), expert_offsets=p(self.expert_offsets), y_sorted=p(self.y_sorted), out=p(self.out),
-            dispatch_workspace=p(self.ws_dispatch), dispatch_workspace_bytes=self.ws_dispatch.numel(), ffn_workspace=p(self.ws_ffn),
-            ffn_workspace_bytes=self.ws_ffn.numel())
-        self._args = (d, ctypes.addressof(d), self.lib.moe_layer_forward)
+            x=p(self.x), w_gate=p(self.w_gate), w1=p(self.w1), w2=p(self.w2), forced_idx=p(self.forced_idx), expert_map=p(self.expert_map),
+            T=self.T, d=self.d, f=self.f, E=self.E, E_local=self.E_local, k=self.k, renormalize=self.renorm, act=self.act, dt=self.dt,
+            fused=int(self.fused), topk_idx=p(self.topk_idx), topk_w=p(self.topk_w), x_sorted=p(self.x_sorted),
+            src_of_sorted=p(self.src_of_sorted), sorted_of_src=p(self.sorted_of_src), expert_counts=p(self.expert_counts),
+            expert_offsets=p(self.expert_offsets), y_sorted=p(self.y_sorted), out=p(self.out), dispatch_workspace=p(self.ws_dispatch),
+            dispatch_workspace_bytes=self.ws_dispatch.numel(), ffn_workspace=p(self.ws_ffn), ffn_workspace_bytes=self.ws_ffn.numel())
+        tensors = [t for t in (self.x, self.w_gate, self.w1, self.w2, self.forced_idx, self.expert_map, self.topk_idx, self.topk_w,
+                               self.x_sorted, self.src_of_sorted, self.sorted_of_src, self.expert_counts, self.expert_offsets,
+                               self.y_sorted, self.out, self.ws_dispatch, self.ws_ffn) if t is not None]
+        self._args = (tensors, self._storage(tensors), d, ctypes.addressof(d), self.lib.moe_layer_forward)
         return self._args
+
+    @staticmethod
+    def _storage(tensors):
+        """Where the tensors' elements lie now, and how many the two workspaces (the last ones) have."""
+        return (*map(torch.Tensor.data_ptr, tensors), tensors[-2].numel(), tensors[-1].numel())
 
     def step(self):
         """The whole pass in one native call (gate, dispatch, expert FFN, combine)."""
-        d, address, forward = self._args or self._describe()
-        d.x, d.w_gate, d.w1, d.w2 = self.x.data_ptr(), self.w_gate.data_ptr(), self.w1.data_ptr(), self.w2.data_ptr()
+        tensors, storage, _, address, forward = self._args or self._describe()
+        # (a tensor's storage can be replaced without an assignment: set_, resize_, .data = ..)
+        if self._storage(tensors) != storage:
+            _, _, _, address, forward = self._describe()
         rc = forward(address, B._stream())
         if rc:
             B._check(rc)
 
 
-class AffinityRun(_Prepared):
+class AffinityRun:
     def __init__(self, trace, placement, E, G, one_pass=True):
         self.lib = B.lib()
         self.one_pass = bool(one_pass)  # step() = affinity_statistics, else affinity_histogram + placement_locality
@@ -148,10 +155,9 @@ class AffinityRun(_Prepared):
     def statistics(self, trace=None):
         """Both results from one pass over the trace (affinity_statistics)."""
         t = self.trace if trace is None else trace
-        if self._args is None:
-            self._args = (self.L, self.N, self.E, self.G, self.counts.data_ptr(), self.loads.data_ptr(), self.cond_prob.data_ptr(),
-                          self.n_invalid.data_ptr(), self.local_per_pair.data_ptr(), self.ws_hist.data_ptr(), self.ws_hist.numel())
-        rc = self.lib.affinity_statistics(t.data_ptr(), self.placement.data_ptr(), *self._args, B._stream())
+        rc = self.lib.affinity_statistics(t.data_ptr(), self.placement.data_ptr(), self.L, self.N, self.E, self.G, self.counts.data_ptr(),
+                                          self.loads.data_ptr(), self.cond_prob.data_ptr(), self.n_invalid.data_ptr(),
+                                          self.local_per_pair.data_ptr(), self.ws_hist.data_ptr(), self.ws_hist.numel(), B._stream())
         if rc:
             B._check(rc)
 
