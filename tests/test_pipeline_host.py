@@ -105,3 +105,51 @@ def test_the_statistic_uses_the_storage_its_tensors_have_now():
         assert t.data_ptr() != old.data_ptr()
         names = ("trace", "placement", None, None, None, None, "counts", "loads", "cond_prob", "n_invalid", "local_per_pair", "ws_hist")
         assert [calls[-1][i] for i, n in enumerate(names) if n] == [getattr(run, n).data_ptr() for n in names if n], attr
+
+
+class CallsStub(LayerStub):
+    """Records the entry points called, moe_layer_forward and the single ones."""
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.seen.append(name)
+            return 0
+
+        if name.startswith("__"):
+            raise AttributeError(name)
+        return call
+
+
+@pytest.mark.parametrize("name", ["gate", "dispatch", "ffn", "combine"])
+@pytest.mark.parametrize("where", ["subclass", "instance", "class"])
+def test_a_step_goes_through_methods_that_were_replaced(monkeypatch, name, where):
+    """A subclass's method or a hook around one of the four calls is part of the step, as long as it is there."""
+    hooked = []
+    original = getattr(MoELayerRun, name)
+
+    def hook(self):
+        hooked.append(name)
+        original(self)
+
+    run = _layer_run(False)
+    run.lib = CallsStub()
+    run.step()
+    assert len(run.lib.seen) == 1 and isinstance(run.lib.seen[0], dict)  # one native call
+    if where == "subclass":
+        run.__class__ = type("Timed", (MoELayerRun,), {name: hook})
+    elif where == "instance":
+        setattr(run, name, lambda: hook(run))
+    else:
+        monkeypatch.setattr(MoELayerRun, name, hook)
+    run.step()
+    assert hooked == [name]
+    assert run.lib.seen[1:] == ["moe_gate_topk", "moe_dispatch", "moe_expert_ffn", "moe_combine"]
+    if where == "subclass":
+        run.__class__ = MoELayerRun
+    elif where == "instance":
+        delattr(run, name)
+    else:
+        monkeypatch.undo()
+        monkeypatch.setattr(B, "_stream", lambda: 0)
+    run.step()
+    assert hooked == [name] and isinstance(run.lib.seen[-1], dict) and len(run.lib.seen) == 6
