@@ -204,7 +204,8 @@ int moe_combine(const void* y_sorted, const int32_t* sorted_of_src, const float*
  *   fused == 0 : moe_gate_topk, moe_dispatch (rows moved), moe_expert_ffn, moe_combine
  * forced_idx [T,k] int32 or NULL: global expert ids supplied by the caller; the gate still writes topk_idx and topk_w,
  * but these ids are dispatched.  All other fields are the arguments of the same name of those calls;
- * x_sorted and y_sorted are used with fused == 0 only.  Results and errors are those of the calls.
+ * x_sorted and y_sorted are used with fused == 0 only.  Results and errors are those of the calls; every argument of every
+ * call is checked before the first launch, and all of them are required also where a short batch needs fewer launches.
  * ------------------------------------------------------------------------------------- */
 typedef struct exf_moe_layer {
     const void* x;

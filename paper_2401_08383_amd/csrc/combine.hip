@@ -134,12 +134,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     }
 }
 
-}  // namespace exf
-
-extern "C" int moe_combine(const void* y_sorted, const int32_t* sorted_of_src, const float* topk_w, int64_t T, int d, int k,
-                           int dt, void* out, void* stream)
+int check_combine(const void* y_sorted, const int32_t* sorted_of_src, const float* topk_w, int64_t T, int d, int k, int dt, const void* out)
 {
-    using namespace exf;
     if (dt != EXF_F32 && dt != EXF_BF16) return fail(EXF_ERR_BAD_DTYPE, "moe_combine: dt = %d", dt);
     if (T < 0) return fail(EXF_ERR_BAD_SHAPE, "moe_combine: T = %lld < 0", static_cast<long long>(T));
     if (k < 1 || k > EXF_MAX_TOPK) return fail(EXF_ERR_BAD_SHAPE, "moe_combine: k = %d outside [1,%d]", k, EXF_MAX_TOPK);
@@ -148,13 +144,24 @@ extern "C" int moe_combine(const void* y_sorted, const int32_t* sorted_of_src, c
     if (d < gran || d % gran != 0)
         return fail(EXF_ERR_BAD_SHAPE, "moe_combine: d = %d must be a positive multiple of %d", d, gran);
     if (T == 0) return EXF_OK;
-    EXF_REQUIRE_PTR(y_sorted);
-    EXF_REQUIRE_PTR(sorted_of_src);
-    EXF_REQUIRE_PTR(topk_w);
-    EXF_REQUIRE_PTR(out);
-    EXF_REQUIRE_ALIGNED(y_sorted);
-    EXF_REQUIRE_ALIGNED(out);
-    const int vec_per_row = d / gran;
+    EXF_CHECK_PTR("moe_combine", y_sorted);
+    EXF_CHECK_PTR("moe_combine", sorted_of_src);
+    EXF_CHECK_PTR("moe_combine", topk_w);
+    EXF_CHECK_PTR("moe_combine", out);
+    EXF_CHECK_ALIGNED("moe_combine", y_sorted);
+    EXF_CHECK_ALIGNED("moe_combine", out);
+    return EXF_OK;
+}
+
+}  // namespace exf
+
+extern "C" int moe_combine(const void* y_sorted, const int32_t* sorted_of_src, const float* topk_w, int64_t T, int d, int k,
+                           int dt, void* out, void* stream)
+{
+    using namespace exf;
+    if (int rc = check_combine(y_sorted, sorted_of_src, topk_w, T, d, k, dt, out)) return rc;
+    if (T == 0) return EXF_OK;
+    const int vec_per_row = d / (dt == EXF_BF16 ? 8 : 4);
     const int64_t A = T * k;
     const int row_batch = row_batch_for(T);
     int64_t blocks = ((T + row_batch - 1) / row_batch + 3) / 4;  // four wavefronts (row batches) per workgroup

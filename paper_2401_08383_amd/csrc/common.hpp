@@ -33,15 +33,30 @@ inline int allow_lds(const void* kern, size_t lds, std::atomic<uint64_t>& allowe
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-#define EXF_REQUIRE_PTR(p)                                                        \
+// Refuse a null or misaligned pointer argument of the call `fn`.
+#define EXF_CHECK_PTR(fn, p)                                                      \
     do {                                                                          \
-        if ((p) == nullptr) return ::exf::fail(EXF_ERR_NULL_PTR, "%s: %s is NULL", __func__, #p); \
+        if ((p) == nullptr) return ::exf::fail(EXF_ERR_NULL_PTR, "%s: %s is NULL", fn, #p); \
     } while (0)
-#define EXF_REQUIRE_ALIGNED(p)                                                    \
+#define EXF_CHECK_ALIGNED(fn, p)                                                  \
     do {                                                                          \
         if (!::exf::aligned16(p))                                                 \
-            return ::exf::fail(EXF_ERR_MISALIGNED, "%s: %s is not 16-byte aligned", __func__, #p); \
+            return ::exf::fail(EXF_ERR_MISALIGNED, "%s: %s is not 16-byte aligned", fn, #p); \
     } while (0)
+#define EXF_REQUIRE_PTR(p) EXF_CHECK_PTR(__func__, p)
+#define EXF_REQUIRE_ALIGNED(p) EXF_CHECK_ALIGNED(__func__, p)
+
+// What the calls of a layer refuse, without launching anything: moe_layer_forward asks all of them before its first launch.
+int check_gate(const void* x, const void* w_gate, int64_t T, int d, int E, int k, int dt, const int32_t* topk_idx, const float* topk_w);
+int check_dispatch(const void* x, const int32_t* topk_idx, int64_t T, int d, int k, int E, int E_local, int dt, const void* x_sorted,
+                   const int32_t* src_of_sorted, const int32_t* sorted_of_src, const int32_t* expert_counts, const int32_t* expert_offsets,
+                   const void* workspace, size_t workspace_bytes);
+int check_ffn(const void* x_sorted, const int32_t* expert_offsets, const void* w1, const void* w2, int64_t A, int d, int f, int E_local,
+              int act, int dt, const void* y_sorted, const void* workspace, size_t workspace_bytes);
+int check_ffn_fused(const void* x, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
+                    const int32_t* expert_offsets, const void* w1, const void* w2, int64_t T, int k, int d, int f, int E_local, int act,
+                    int dt, const void* out, const void* workspace, size_t workspace_bytes);
+int check_combine(const void* y_sorted, const int32_t* sorted_of_src, const float* topk_w, int64_t T, int d, int k, int dt, const void* out);
 
 constexpr int kWave = 64;  // CDNA wavefront width
 

@@ -474,11 +474,9 @@ extern "C" size_t moe_dispatch_workspace_bytes(int64_t T, int k, int E_local)
 
 namespace exf {
 
-// Validation and launches shared by moe_dispatch (chunk counts in the caller's workspace) and
-// moe_dispatch_static (chunk counts in this library's own device array).
-static int dispatch_run(const void* x, const int32_t* topk_idx, const int32_t* expert_map, int64_t T, int d, int k, int E, int E_local,
-                        int dt, void* x_sorted, int32_t* src_of_sorted, int32_t* sorted_of_src, int32_t* expert_counts,
-                        int32_t* expert_offsets, void* workspace, size_t workspace_bytes, void* stream)
+int check_dispatch(const void* x, const int32_t* topk_idx, int64_t T, int d, int k, int E, int E_local, int dt, const void* x_sorted,
+                   const int32_t* src_of_sorted, const int32_t* sorted_of_src, const int32_t* expert_counts, const int32_t* expert_offsets,
+                   const void* workspace, size_t workspace_bytes)
 {
     if (dt != EXF_F32 && dt != EXF_BF16) return fail(EXF_ERR_BAD_DTYPE, "moe_dispatch: dt = %d", dt);
     if (T < 0) return fail(EXF_ERR_BAD_SHAPE, "moe_dispatch: T = %lld < 0", static_cast<long long>(T));
@@ -491,22 +489,35 @@ static int dispatch_run(const void* x, const int32_t* topk_idx, const int32_t* e
     const int gran = dt == EXF_BF16 ? 8 : 4;
     if (x_sorted != nullptr && (d < gran || d % gran != 0))
         return fail(EXF_ERR_BAD_SHAPE, "moe_dispatch: d = %d must be a positive multiple of %d", d, gran);
-    EXF_REQUIRE_PTR(expert_counts);
-    EXF_REQUIRE_PTR(expert_offsets);
-    EXF_REQUIRE_PTR(workspace);
+    EXF_CHECK_PTR("moe_dispatch", expert_counts);
+    EXF_CHECK_PTR("moe_dispatch", expert_offsets);
+    EXF_CHECK_PTR("moe_dispatch", workspace);
     if (workspace_bytes < moe_dispatch_workspace_bytes(T, k, E_local))
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "moe_dispatch: workspace %zu < %zu bytes", workspace_bytes,
                     moe_dispatch_workspace_bytes(T, k, E_local));
     if (A > 0) {
-        EXF_REQUIRE_PTR(topk_idx);
-        EXF_REQUIRE_PTR(src_of_sorted);
-        EXF_REQUIRE_PTR(sorted_of_src);
+        EXF_CHECK_PTR("moe_dispatch", topk_idx);
+        EXF_CHECK_PTR("moe_dispatch", src_of_sorted);
+        EXF_CHECK_PTR("moe_dispatch", sorted_of_src);
         if (x_sorted != nullptr) {
-            EXF_REQUIRE_PTR(x);
-            EXF_REQUIRE_ALIGNED(x);
-            EXF_REQUIRE_ALIGNED(x_sorted);
+            EXF_CHECK_PTR("moe_dispatch", x);
+            EXF_CHECK_ALIGNED("moe_dispatch", x);
+            EXF_CHECK_ALIGNED("moe_dispatch", x_sorted);
         }
     }
+    return EXF_OK;
+}
+
+// Validation and launches shared by moe_dispatch (chunk counts in the caller's workspace) and
+// moe_dispatch_static (chunk counts in this library's own device array).
+static int dispatch_run(const void* x, const int32_t* topk_idx, const int32_t* expert_map, int64_t T, int d, int k, int E, int E_local,
+                        int dt, void* x_sorted, int32_t* src_of_sorted, int32_t* sorted_of_src, int32_t* expert_counts,
+                        int32_t* expert_offsets, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (int rc = check_dispatch(x, topk_idx, T, d, k, E, E_local, dt, x_sorted, src_of_sorted, sorted_of_src, expert_counts, expert_offsets,
+                                workspace, workspace_bytes))
+        return rc;
+    const int64_t A = T * k;
     hipStream_t s = static_cast<hipStream_t>(stream);
     int32_t* block_counts = static_cast<int32_t*>(workspace);
     const int n_blocks = static_cast<int>(dispatch_blocks(A));

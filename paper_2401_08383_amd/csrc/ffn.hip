@@ -825,11 +825,9 @@ extern "C" size_t moe_expert_ffn_workspace_bytes(int64_t A, int d, int f, int E_
     return exf::hidden_bytes(A, f, E_local, dt) + (dt == EXF_BF16 ? exf::kReservedBytes : 0);
 }
 
-extern "C" int moe_expert_ffn(const void* x_sorted, const int32_t* expert_offsets, const void* w1, const void* b1, const void* w2,
-                              const void* b2, int64_t A, int d, int f, int E_local, int act, int dt, void* y_sorted,
-                              void* workspace, size_t workspace_bytes, void* stream)
+int exf::check_ffn(const void* x_sorted, const int32_t* expert_offsets, const void* w1, const void* w2, int64_t A, int d, int f, int E_local,
+                   int act, int dt, const void* y_sorted, const void* workspace, size_t workspace_bytes)
 {
-    using namespace exf;
     if (dt != EXF_F32 && dt != EXF_BF16) return fail(EXF_ERR_BAD_DTYPE, "moe_expert_ffn: dt = %d", dt);
     if (act != EXF_ACT_GELU_ERF && act != EXF_ACT_GELU_TANH) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: act = %d", act);
     if (A < 0 || A >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: A = %lld outside [0,2^31)", static_cast<long long>(A));
@@ -846,20 +844,30 @@ extern "C" int moe_expert_ffn(const void* x_sorted, const int32_t* expert_offset
             return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: (A + 32 (E_local + 1))*max(d,f) and d*f must stay below 2^31 elements (bf16)");
     }
     if (A == 0) return EXF_OK;
-    EXF_REQUIRE_PTR(x_sorted);
-    EXF_REQUIRE_PTR(expert_offsets);
-    EXF_REQUIRE_PTR(w1);
-    EXF_REQUIRE_PTR(w2);
-    EXF_REQUIRE_PTR(y_sorted);
-    EXF_REQUIRE_PTR(workspace);
-    EXF_REQUIRE_ALIGNED(x_sorted);
-    EXF_REQUIRE_ALIGNED(w1);
-    EXF_REQUIRE_ALIGNED(w2);
-    EXF_REQUIRE_ALIGNED(y_sorted);
-    EXF_REQUIRE_ALIGNED(workspace);
+    EXF_CHECK_PTR("moe_expert_ffn", x_sorted);
+    EXF_CHECK_PTR("moe_expert_ffn", expert_offsets);
+    EXF_CHECK_PTR("moe_expert_ffn", w1);
+    EXF_CHECK_PTR("moe_expert_ffn", w2);
+    EXF_CHECK_PTR("moe_expert_ffn", y_sorted);
+    EXF_CHECK_PTR("moe_expert_ffn", workspace);
+    EXF_CHECK_ALIGNED("moe_expert_ffn", x_sorted);
+    EXF_CHECK_ALIGNED("moe_expert_ffn", w1);
+    EXF_CHECK_ALIGNED("moe_expert_ffn", w2);
+    EXF_CHECK_ALIGNED("moe_expert_ffn", y_sorted);
+    EXF_CHECK_ALIGNED("moe_expert_ffn", workspace);
     if (workspace_bytes < moe_expert_ffn_workspace_bytes(A, d, f, E_local, dt))
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "moe_expert_ffn: workspace %zu < %zu bytes", workspace_bytes,
                     moe_expert_ffn_workspace_bytes(A, d, f, E_local, dt));
+    return EXF_OK;
+}
+
+extern "C" int moe_expert_ffn(const void* x_sorted, const int32_t* expert_offsets, const void* w1, const void* b1, const void* w2,
+                              const void* b2, int64_t A, int d, int f, int E_local, int act, int dt, void* y_sorted,
+                              void* workspace, size_t workspace_bytes, void* stream)
+{
+    using namespace exf;
+    if (int rc = check_ffn(x_sorted, expert_offsets, w1, w2, A, d, f, E_local, act, dt, y_sorted, workspace, workspace_bytes)) return rc;
+    if (A == 0) return EXF_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int epi = act == EXF_ACT_GELU_ERF ? kEpiGeluErf : kEpiGeluTanh;
     int rc;
@@ -895,13 +903,10 @@ extern "C" size_t moe_expert_ffn_fused_workspace_bytes(int64_t T, int k, int d, 
     return bytes + (dt == EXF_BF16 ? exf::kReservedBytes : 0);
 }
 
-static int ffn_fused_run(const char* fn, const void* x, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
-                         const int32_t* expert_offsets, const void* w1, const void* b1, const void* w2, const void* b2, int64_t T, int k,
-                         int d, int f, int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream,
-                         unsigned long long* timeline, int timeline_cap, const exf::FfnRouting* routing = nullptr)
+int exf::check_ffn_fused(const void* x, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
+                         const int32_t* expert_offsets, const void* w1, const void* w2, int64_t T, int k, int d, int f, int E_local, int act,
+                         int dt, const void* out, const void* workspace, size_t workspace_bytes)
 {
-    using namespace exf;
-    (void)fn;
     if (dt != EXF_F32 && dt != EXF_BF16) return fail(EXF_ERR_BAD_DTYPE, "moe_expert_ffn_fused: dt = %d", dt);
     if (act != EXF_ACT_GELU_ERF && act != EXF_ACT_GELU_TANH) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn_fused: act = %d", act);
     if (k < 1 || k > EXF_MAX_TOPK) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn_fused: k = %d outside [1,%d]", k, EXF_MAX_TOPK);
@@ -921,23 +926,37 @@ static int ffn_fused_run(const char* fn, const void* x, const int32_t* src_of_so
             return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn_fused: (T*k + 32 (E_local + 1))*max(d,f) and d*f must stay below 2^31 elements");
     }
     if (T == 0) return EXF_OK;
-    EXF_REQUIRE_PTR(x);
-    EXF_REQUIRE_PTR(src_of_sorted);
-    EXF_REQUIRE_PTR(sorted_of_src);
-    EXF_REQUIRE_PTR(topk_w);
-    EXF_REQUIRE_PTR(expert_offsets);
-    EXF_REQUIRE_PTR(w1);
-    EXF_REQUIRE_PTR(w2);
-    EXF_REQUIRE_PTR(out);
-    EXF_REQUIRE_PTR(workspace);
-    EXF_REQUIRE_ALIGNED(x);
-    EXF_REQUIRE_ALIGNED(w1);
-    EXF_REQUIRE_ALIGNED(w2);
-    EXF_REQUIRE_ALIGNED(out);
-    EXF_REQUIRE_ALIGNED(workspace);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", x);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", src_of_sorted);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", sorted_of_src);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", topk_w);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", expert_offsets);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", w1);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", w2);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", out);
+    EXF_CHECK_PTR("moe_expert_ffn_fused", workspace);
+    EXF_CHECK_ALIGNED("moe_expert_ffn_fused", x);
+    EXF_CHECK_ALIGNED("moe_expert_ffn_fused", w1);
+    EXF_CHECK_ALIGNED("moe_expert_ffn_fused", w2);
+    EXF_CHECK_ALIGNED("moe_expert_ffn_fused", out);
+    EXF_CHECK_ALIGNED("moe_expert_ffn_fused", workspace);
     if (x == out) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn_fused: out must not alias x");
     const size_t need = moe_expert_ffn_fused_workspace_bytes(T, k, d, f, E_local, dt);
     if (workspace_bytes < need) return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "moe_expert_ffn_fused: workspace %zu < %zu bytes", workspace_bytes, need);
+    return EXF_OK;
+}
+
+static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
+                         const int32_t* expert_offsets, const void* w1, const void* b1, const void* w2, const void* b2, int64_t T, int k,
+                         int d, int f, int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream,
+                         unsigned long long* timeline, int timeline_cap, const exf::FfnRouting* routing = nullptr)
+{
+    using namespace exf;
+    if (int rc = check_ffn_fused(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, w2, T, k, d, f, E_local, act, dt, out, workspace,
+                                 workspace_bytes))
+        return rc;
+    if (T == 0) return EXF_OK;
+    const int64_t A = T * k;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int epi = act == EXF_ACT_GELU_ERF ? kEpiGeluErf : kEpiGeluTanh;
     unsigned char* hidden = static_cast<unsigned char*>(workspace);
@@ -993,15 +1012,15 @@ extern "C" int moe_expert_ffn_fused(const void* x, const int32_t* src_of_sorted,
                                     int64_t T, int k, int d, int f, int E_local, int act, int dt, void* out, void* workspace,
                                     size_t workspace_bytes, void* stream)
 {
-    return ffn_fused_run("moe_expert_ffn_fused", x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, b1, w2, b2, T, k, d, f,
-                         E_local, act, dt, out, workspace, workspace_bytes, stream, nullptr, 0);
+    return ffn_fused_run(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, b1, w2, b2, T, k, d, f, E_local, act, dt, out,
+                         workspace, workspace_bytes, stream, nullptr, 0);
 }
 
 int exf::ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
                           int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream)
 {
-    return ffn_fused_run("moe_layer_forward", x, r.src_of_sorted, r.sorted_of_src, topk_w, r.expert_offsets, w1, nullptr, w2, nullptr, T, k, d,
-                         f, E_local, act, dt, out, workspace, workspace_bytes, stream, nullptr, 0, &r);
+    return ffn_fused_run(x, r.src_of_sorted, r.sorted_of_src, topk_w, r.expert_offsets, w1, nullptr, w2, nullptr, T, k, d, f,
+                         E_local, act, dt, out, workspace, workspace_bytes, stream, nullptr, 0, &r);
 }
 
 // moe_expert_ffn_fused (bf16) with a per-workgroup timeline of both contractions (see RowMap::timeline).
@@ -1012,7 +1031,7 @@ extern "C" int exf_probe_ffn_timeline(const void* x, const int32_t* src_of_sorte
 {
     EXF_REQUIRE_PTR(timeline);
     if (capacity < 1) return exf::fail(EXF_ERR_BAD_SHAPE, "exf_probe_ffn_timeline: capacity = %d < 1", capacity);
-    return ffn_fused_run("exf_probe_ffn_timeline", x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, nullptr, w2, nullptr, T, k,
-                         d, f, E_local, EXF_ACT_GELU_ERF, EXF_BF16, out, workspace, workspace_bytes, stream,
+    return ffn_fused_run(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, nullptr, w2, nullptr, T, k, d, f,
+                         E_local, EXF_ACT_GELU_ERF, EXF_BF16, out, workspace, workspace_bytes, stream,
                          reinterpret_cast<unsigned long long*>(timeline), capacity);
 }

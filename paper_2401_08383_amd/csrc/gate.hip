@@ -372,24 +372,31 @@ static int validate_topk_args(const char* fn, int64_t T, int E, int k)
     return EXF_OK;
 }
 
-}  // namespace exf
-
-extern "C" int moe_gate_topk(const void* x, const void* w_gate, int64_t T, int d, int E, int k, int renormalize, int dt,
-                             float* logits_out, int32_t* topk_idx, float* topk_w, void* stream)
+int check_gate(const void* x, const void* w_gate, int64_t T, int d, int E, int k, int dt, const int32_t* topk_idx, const float* topk_w)
 {
-    using namespace exf;
     if (dt != EXF_F32 && dt != EXF_BF16) return fail(EXF_ERR_BAD_DTYPE, "moe_gate_topk: dt = %d", dt);
     if (int rc = validate_topk_args("moe_gate_topk", T, E, k)) return rc;
     const int gran = dt == EXF_BF16 ? 8 : 4;
     if (d < gran || d % gran != 0)
         return fail(EXF_ERR_BAD_SHAPE, "moe_gate_topk: d = %d must be a positive multiple of %d", d, gran);
     if (T == 0) return EXF_OK;
-    EXF_REQUIRE_PTR(x);
-    EXF_REQUIRE_PTR(w_gate);
-    EXF_REQUIRE_PTR(topk_idx);
-    EXF_REQUIRE_PTR(topk_w);
-    EXF_REQUIRE_ALIGNED(x);
-    EXF_REQUIRE_ALIGNED(w_gate);
+    EXF_CHECK_PTR("moe_gate_topk", x);
+    EXF_CHECK_PTR("moe_gate_topk", w_gate);
+    EXF_CHECK_PTR("moe_gate_topk", topk_idx);
+    EXF_CHECK_PTR("moe_gate_topk", topk_w);
+    EXF_CHECK_ALIGNED("moe_gate_topk", x);
+    EXF_CHECK_ALIGNED("moe_gate_topk", w_gate);
+    return EXF_OK;
+}
+
+}  // namespace exf
+
+extern "C" int moe_gate_topk(const void* x, const void* w_gate, int64_t T, int d, int E, int k, int renormalize, int dt,
+                             float* logits_out, int32_t* topk_idx, float* topk_w, void* stream)
+{
+    using namespace exf;
+    if (int rc = check_gate(x, w_gate, T, d, E, k, dt, topk_idx, topk_w)) return rc;
+    if (T == 0) return EXF_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dt == EXF_F32) {
         const int64_t blocks = (T + 3) / 4;

@@ -6,21 +6,35 @@ extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
 {
     EXF_REQUIRE_PTR(layer);
     const exf_moe_layer& l = *layer;
+    const bool fused = l.fused != 0;
+    void* x_sorted = fused ? nullptr : l.x_sorted;
+    const int32_t* idx = l.forced_idx != nullptr ? l.forced_idx : l.topk_idx;
+    // everything the calls refuse, before anything is launched
+    if (int bad = exf::check_gate(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.dt, l.topk_idx, l.topk_w)) return bad;
+    if (int bad = exf::check_dispatch(l.x, idx, l.T, l.d, l.k, l.E, l.E_local, l.dt, x_sorted, l.src_of_sorted, l.sorted_of_src, l.expert_counts,
+                                      l.expert_offsets, l.dispatch_workspace, l.dispatch_workspace_bytes))
+        return bad;
+    if (fused) {
+        if (int bad = exf::check_ffn_fused(l.x, l.src_of_sorted, l.sorted_of_src, l.topk_w, l.expert_offsets, l.w1, l.w2, l.T, l.k, l.d, l.f,
+                                           l.E_local, l.act, l.dt, l.out, l.ffn_workspace, l.ffn_workspace_bytes))
+            return bad;
+    } else {
+        if (int bad = exf::check_ffn(l.x_sorted, l.expert_offsets, l.w1, l.w2, l.T * l.k, l.d, l.f, l.E_local, l.act, l.dt, l.y_sorted,
+                                     l.ffn_workspace, l.ffn_workspace_bytes))
+            return bad;
+        if (int bad = exf::check_combine(l.y_sorted, l.sorted_of_src, l.topk_w, l.T, l.d, l.k, l.dt, l.out)) return bad;
+    }
     int rc = moe_gate_topk(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.renormalize, l.dt, nullptr, l.topk_idx, l.topk_w, stream);
     if (rc != EXF_OK) return rc;
-    const int32_t* idx = l.forced_idx != nullptr ? l.forced_idx : l.topk_idx;
-    if (l.fused != 0 && l.k >= 1 && l.k <= EXF_MAX_TOPK && l.E >= 1 && l.E_local >= 1 && l.E_local <= EXF_MAX_EXPERTS &&
-        exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt)) {
-        EXF_REQUIRE_PTR(idx);
-        EXF_REQUIRE_PTR(l.expert_counts);
+    if (fused && exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt)) {
         exf::FfnRouting r{idx, l.expert_map, l.E, l.src_of_sorted, l.sorted_of_src, l.expert_counts, l.expert_offsets};
         return exf::ffn_fused_routed(r, l.x, l.topk_w, l.w1, l.w2, l.T, l.k, l.d, l.f, l.E_local, l.act, l.dt, l.out, l.ffn_workspace,
                                      l.ffn_workspace_bytes, stream);
     }
-    rc = moe_dispatch(l.x, idx, l.expert_map, l.T, l.d, l.k, l.E, l.E_local, l.dt, l.fused != 0 ? nullptr : l.x_sorted, l.src_of_sorted,
+    rc = moe_dispatch(l.x, idx, l.expert_map, l.T, l.d, l.k, l.E, l.E_local, l.dt, x_sorted, l.src_of_sorted,
                       l.sorted_of_src, l.expert_counts, l.expert_offsets, l.dispatch_workspace, l.dispatch_workspace_bytes, stream);
     if (rc != EXF_OK) return rc;
-    if (l.fused != 0)
+    if (fused)
         return moe_expert_ffn_fused(l.x, l.src_of_sorted, l.sorted_of_src, l.topk_w, l.expert_offsets, l.w1, nullptr, l.w2, nullptr, l.T,
                                     l.k, l.d, l.f, l.E_local, l.act, l.dt, l.out, l.ffn_workspace, l.ffn_workspace_bytes, stream);
     rc = moe_expert_ffn(l.x_sorted, l.expert_offsets, l.w1, nullptr, l.w2, nullptr, l.T * l.k, l.d, l.f, l.E_local, l.act, l.dt,

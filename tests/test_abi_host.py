@@ -207,3 +207,43 @@ def test_candidate_batch_bound_of_the_scoring_call():
     assert lib.placement_locality_from_counts(one, one, -1, 4, 8, one, None) == B.EXF_ERR_BAD_SHAPE
     assert lib.placement_locality_from_counts(one, one, 0, 4, 8, one, None) == B.EXF_OK
     assert lib.placement_locality_from_counts(None, one, 1 << 24, 4, 8, one, None) == B.EXF_ERR_NULL_PTR
+
+
+def _layer_desc(T, fused, dt, k, changed):
+    """A valid description at dummy addresses (never dereferenced on the host)."""
+    lib = exf.lib()
+    d, f, E = 64, 128, 8
+    at = iter(range(4096, 4096 + 64 * 256, 256))
+    pointers = {n: next(at) for n in ("x", "w_gate", "w1", "w2", "topk_idx", "topk_w", "x_sorted", "src_of_sorted", "sorted_of_src",
+                                      "expert_counts", "expert_offsets", "y_sorted", "out", "dispatch_workspace", "ffn_workspace")}
+    ffn = lib.moe_expert_ffn_fused_workspace_bytes(T, k, d, f, E, dt) if fused else lib.moe_expert_ffn_workspace_bytes(T * k, d, f, E, dt)
+    desc = B.MoELayerDesc(T=T, d=d, f=f, E=E, E_local=E, k=k, renormalize=0, act=0, dt=dt, fused=int(fused),
+                          dispatch_workspace_bytes=lib.moe_dispatch_workspace_bytes(T, k, E), ffn_workspace_bytes=ffn, **pointers)
+    for n, v in changed.items():
+        setattr(desc, n, v)
+    return desc
+
+
+@pytest.mark.parametrize("T,fused,dt,k", [(4, True, B.EXF_BF16, 1), (4, True, B.EXF_F32, 2), (4000, True, B.EXF_BF16, 2), (4, False, B.EXF_BF16, 2),
+                                          (4000, False, B.EXF_F32, 1)])
+def test_layer_forward_refuses_what_its_calls_refuse(T, fused, dt, k):
+    """Every argument of every call, also of the last one, is looked at before the first launch (without a GPU a launch
+    would be EXF_ERR_HIP), however the layer is put together: short batches without a dispatch launch as well."""
+    lib = exf.lib()
+    null, small, bad = B.EXF_ERR_NULL_PTR, B.EXF_ERR_WORKSPACE_TOO_SMALL, B.EXF_ERR_BAD_SHAPE
+    cases = [(n, None, null) for n in ("x", "w_gate", "w1", "w2", "topk_idx", "topk_w", "src_of_sorted", "sorted_of_src", "expert_counts",
+                                       "expert_offsets", "out", "dispatch_workspace", "ffn_workspace")]
+    cases += [(n, 4100, B.EXF_ERR_MISALIGNED) for n in ("x", "w_gate", "w1", "w2", "out", "ffn_workspace")]
+    cases += [("dispatch_workspace_bytes", 0, small), ("ffn_workspace_bytes", 16, small), ("T", -1, bad), ("k", 3, bad), ("k", 0, bad),
+              ("E", 0, bad), ("E", 65, bad), ("E_local", 0, bad), ("E_local", 65, bad), ("d", 0, bad), ("f", 30, bad), ("act", 5, bad),
+              ("dt", 7, B.EXF_ERR_BAD_DTYPE)]
+    if fused:
+        cases.append(("out", 4096, bad))  # aliases x
+    else:
+        cases += [("y_sorted", None, null), ("y_sorted", 4100, B.EXF_ERR_MISALIGNED), ("x_sorted", 4100, B.EXF_ERR_MISALIGNED), ("x_sorted", None, null)]
+    for name, value, expect in cases:
+        desc = _layer_desc(T, fused, dt, k, {name: value})
+        rc = lib.moe_layer_forward(ctypes.addressof(desc), None)
+        assert rc == expect, (name, value, rc, exf.last_error())
+        assert exf.last_error().startswith("moe_"), exf.last_error()  # names the call that refuses it
+    assert lib.moe_layer_forward(None, None) == null
