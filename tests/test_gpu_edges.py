@@ -146,3 +146,23 @@ def test_layer_forward_is_its_calls(T, k, E, E_local, dtype, fused, routing):
                                      (8200, 136, 17, 1), (40, 4096, 32, 2), (64 * 128 + 65, 1088, 48, 1)])
 def test_gate_units_and_token_tiles(oracle, T, d, E, k):
     P.test_gate_topk_parity(oracle, "bf16", T, d, E, k, 1)
+
+
+@pytest.mark.parametrize("T,d,E,k", [(16384, 8, 1, 1), (16385, 64, 64, 2), (16447, 200, 17, 2), (16448, 256, 33, 1), (16400, 320, 16, 2),
+                                     (16384 + 63, 384, 48, 2), (16390, 2056, 9, 1), (20001, 136, 64, 1)])
+def test_gate_of_a_long_batch(oracle, T, d, E, k):
+    """From 64 * 256 tokens on: workgroups cut by the last token, reductions shorter than the ring, ragged ones, both sets of sums."""
+    P.test_gate_topk_parity(oracle, "bf16", T, d, E, k, 1)
+
+
+@pytest.mark.parametrize("d,E", [(64, 64), (1088, 40), (192, 8), (2112, 16), (2048, 17)])
+def test_gate_of_a_long_batch_adds_as_the_shorter_one(d, E):
+    """The same tokens in a shorter batch, through the other kernel: the same bits."""
+    _say(f"gate long / shorter batch d={d} E={E}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1900 + d)
+    x = torch.randn((16384 + 31, d), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((E, d), device="cuda", generator=g).to(torch.bfloat16)
+    first = 9000  # (between 8192 and 16384: four sums from 17 experts on, as in the long batch)
+    for a, b in zip(B.moe_gate_topk(x, w, 2, True, True), B.moe_gate_topk(x[:first].contiguous(), w, 2, True, True)):
+        assert torch.equal(a[:first], b)
