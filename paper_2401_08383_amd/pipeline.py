@@ -119,11 +119,10 @@ class MoELayerRun:
             self.ffn()
             self.combine()
             return
-        tensors, storage, _, address, forward = self._args or self._describe()
-        # (a tensor's storage can be replaced without an assignment: set_, resize_, .data = ..)
-        if self._storage(tensors) != storage:
-            _, _, _, address, forward = self._describe()
-        rc = forward(address, B._stream())
+        args = self._args
+        if args is None or self._storage(args[0]) != args[1]:  # (a storage can be replaced without an assignment: set_, resize_, .data = ..)
+            args = self._describe()
+        rc = args[4](args[3], B._stream())
         if rc:
             B._check(rc)
 
