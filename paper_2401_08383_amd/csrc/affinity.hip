@@ -799,13 +799,18 @@ static int validate_trace_args(const char* fn, int L, int64_t N, int E)
     return EXF_OK;
 }
 
-template <typename Kern>
-static int allow_large_lds(Kern kern, size_t bytes, const char* what)
+// LDS of locality_partial_kernel at most: the placement of all layers and the counts
+constexpr size_t kLocMaxLdsBytes = (EXF_MAX_TRACE_LAYERS * EXF_MAX_EXPERTS + 2 * EXF_MAX_TRACE_LAYERS) * sizeof(int32_t);
+template <int VEC, bool HOME>
+static int launch_locality(const char* fn, const LocalityPlan& p, const int32_t* trace, const int32_t* placement, const int32_t* home, int L,
+                           int64_t N, int E, uint32_t* part, hipStream_t stream)
 {
-    if (bytes <= 64 * 1024) return EXF_OK;
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(bytes));
-    if (err != hipSuccess) return fail(EXF_ERR_HIP, "%s: LDS attribute: %s", what, hipGetErrorString(err));
+    auto kern = locality_partial_kernel<VEC, HOME>;
+    const size_t lds = (static_cast<size_t>(L) * E + (L - 1) + (HOME ? L : 0)) * sizeof(int32_t);
+    static std::atomic<uint64_t> allowed{0};
+    if (lds > 64 * 1024)
+        if (int rc = allow_lds(reinterpret_cast<const void*>(kern), kLocMaxLdsBytes, allowed, fn)) return rc;
+    hipLaunchKernelGGL(kern, dim3(p.C), dim3(p.threads), lds, stream, trace, placement, home, L, N, E, p.chunk, part);
     return EXF_OK;
 }
 
@@ -840,15 +845,11 @@ static int run_affinity(const char* fn, const int32_t* trace, const int32_t* pla
         const unsigned grid = static_cast<unsigned>(c_pad) * p.Q;
         const size_t lds = (static_cast<size_t>(p.copies) * p.g * p.words + static_cast<size_t>(p.g) * E + E + 1 + p.g +
                             static_cast<size_t>(p.g + 1) * E) * sizeof(uint32_t);
-        if (p.vec == 4) {
-            if (int rc = allow_large_lds(affinity_partial_kernel<4>, lds, fn)) return rc;
-            hipLaunchKernelGGL(affinity_partial_kernel<4>, dim3(grid), dim3(kTraceThreads), lds, s, trace, L, N, E, p.g, p.Q, p.copies,
-                               p.words, p.chunk, p.C, part_counts, part_orphan_next, part_orphan_last, part_invalid, placement, part_local);
-        } else {
-            if (int rc = allow_large_lds(affinity_partial_kernel<1>, lds, fn)) return rc;
-            hipLaunchKernelGGL(affinity_partial_kernel<1>, dim3(grid), dim3(kTraceThreads), lds, s, trace, L, N, E, p.g, p.Q, p.copies,
-                               p.words, p.chunk, p.C, part_counts, part_orphan_next, part_orphan_last, part_invalid, placement, part_local);
-        }
+        static_assert(kAffHistBudget + ((2 * kAffMaxGroup + 2) * EXF_MAX_EXPERTS + 1 + kAffMaxGroup) * sizeof(uint32_t) <= 64 * 1024,
+                      "within the LDS that a launch may use without asking");
+        auto kern = p.vec == 4 ? affinity_partial_kernel<4> : affinity_partial_kernel<1>;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kTraceThreads), lds, s, trace, L, N, E, p.g, p.Q, p.copies, p.words, p.chunk, p.C, part_counts,
+                           part_orphan_next, part_orphan_last, part_invalid, placement, part_local);
     }
     // rows of all pairs, then the loads of the final layer, the invalid tally and (with a placement) the
     // locality numerators of all pairs
@@ -1008,16 +1009,9 @@ extern "C" int placement_locality(const int32_t* trace, const int32_t* placement
     const int C = p.C;
     uint32_t* part = static_cast<uint32_t*>(workspace);
     if (C > 0) {
-        const size_t lds = (static_cast<size_t>(L) * E + (L - 1)) * sizeof(int32_t);
-        if (p.vec == 4) {
-            if (int rc = allow_large_lds(locality_partial_kernel<4, false>, lds, "placement_locality")) return rc;
-            hipLaunchKernelGGL((locality_partial_kernel<4, false>), dim3(C), dim3(p.threads), lds, s, trace, placement, nullptr, L, N,
-                               E, p.chunk, part);
-        } else {
-            if (int rc = allow_large_lds(locality_partial_kernel<1, false>, lds, "placement_locality")) return rc;
-            hipLaunchKernelGGL((locality_partial_kernel<1, false>), dim3(C), dim3(p.threads), lds, s, trace, placement, nullptr, L, N,
-                               E, p.chunk, part);
-        }
+        const int rc = p.vec == 4 ? launch_locality<4, false>("placement_locality", p, trace, placement, nullptr, L, N, E, part, s)
+                                  : launch_locality<1, false>("placement_locality", p, trace, placement, nullptr, L, N, E, part, s);
+        if (rc != EXF_OK) return rc;
     }
     hipLaunchKernelGGL(locality_finalize_kernel, dim3(L - 1), dim3(kWave), 0, s, part, C, L - 1, L - 1, local_per_pair, nullptr);
     return check_launch("placement_locality");
@@ -1054,16 +1048,9 @@ extern "C" int routing_transfers(const int32_t* trace, const int32_t* placement,
     uint32_t* part = static_cast<uint32_t*>(workspace);
     const int n_out = 2 * L - 1;
     if (C > 0) {
-        const size_t lds = (static_cast<size_t>(L) * E + n_out) * sizeof(int32_t);
-        if (p.vec == 4) {
-            if (int rc = allow_large_lds(locality_partial_kernel<4, true>, lds, "routing_transfers")) return rc;
-            hipLaunchKernelGGL((locality_partial_kernel<4, true>), dim3(C), dim3(p.threads), lds, s, trace, placement, home, L, N, E,
-                               p.chunk, part);
-        } else {
-            if (int rc = allow_large_lds(locality_partial_kernel<1, true>, lds, "routing_transfers")) return rc;
-            hipLaunchKernelGGL((locality_partial_kernel<1, true>), dim3(C), dim3(p.threads), lds, s, trace, placement, home, L, N, E,
-                               p.chunk, part);
-        }
+        const int rc = p.vec == 4 ? launch_locality<4, true>("routing_transfers", p, trace, placement, home, L, N, E, part, s)
+                                  : launch_locality<1, true>("routing_transfers", p, trace, placement, home, L, N, E, part, s);
+        if (rc != EXF_OK) return rc;
     }
     hipLaunchKernelGGL(locality_finalize_kernel, dim3(n_out), dim3(kWave), 0, s, part, C, L - 1, n_out, local_per_pair, away_per_layer);
     return check_launch("routing_transfers");

@@ -7,8 +7,6 @@
 
 namespace exf {
 
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-
 constexpr int kXcdCount = 8;
 
 // ---------------------------------------------------------------------------- activations

@@ -25,6 +25,21 @@ def test_trace_columns_that_start_and_end_anywhere(oracle, N):
     Q.test_routing_transfers_parity(5, N, 24, 8)
 
 
+@pytest.mark.parametrize("N", [300, 262147])
+def test_placement_of_all_layers_beyond_64_KiB(oracle, N):
+    """The most layers and experts: the placement and the counts take more LDS than a launch may use unasked.  Both calls
+    twice: the second one relies on what the first has asked for."""
+    for _ in range(2):
+        Q.test_routing_transfers_parity(256, N, 64, 8)
+    _say(f"placement_locality L=256 N={N}")
+    g = syn.rng(1150)
+    trace = g.integers(0, 64, size=(256, N)).astype(np.int32)
+    pl = syn.balanced_random_placement(256, 64, 8, 1151)
+    for _ in range(2):
+        got = B.placement_locality(torch.from_numpy(trace).cuda(), torch.from_numpy(pl).cuda(), 8).cpu().numpy()
+        np.testing.assert_array_equal(got, oracle.placement_locality(trace, pl))
+
+
 # ----------------------------------------------------------------------------- candidate scores
 @pytest.mark.parametrize("L,N,E", [(2, 65281, 64), (4, 5, 1), (5, 4100, 63), (8, 8193, 2), (9, 65280, 33), (12, 130561, 5), (13, 20000, 64), (16, 16385, 64),
                                    (17, 9000, 31), (29, 24577, 7), (31, 3, 64), (33, 12289, 64)])
