@@ -40,7 +40,7 @@ def test_placement_of_all_layers_beyond_64_KiB(oracle, N):
         np.testing.assert_array_equal(got, oracle.placement_locality(trace, pl))
 
 
-# ----------------------------------------------------------------------------- candidate scores
+# ----------------------------------------------------------------------------- counts of all layer pairs
 @pytest.mark.parametrize("L,N,E", [(2, 65281, 64), (4, 5, 1), (5, 4100, 63), (8, 8193, 2), (9, 65280, 33), (12, 130561, 5), (13, 20000, 64), (16, 16385, 64),
                                    (17, 9000, 31), (29, 24577, 7), (31, 3, 64), (33, 12289, 64)])
 def test_multihop_blocks(L, N, E):
@@ -48,6 +48,7 @@ def test_multihop_blocks(L, N, E):
     Q.test_affinity_multihop_parity(L, N, E)
 
 
+# ----------------------------------------------------------------------------- candidate scores
 @pytest.mark.parametrize("E,Bn,total", [(1, 1, 5), (33, 9, (1 << 31) - 1), (33, 9, 1 << 31), (64, 300, (1 << 31) - 1), (64, 300, 1 << 33),
                                         (63, 4099, 100000)])
 def test_candidate_scores_around_the_32_bit_table(E, Bn, total):
