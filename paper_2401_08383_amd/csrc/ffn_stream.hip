@@ -4,7 +4,7 @@
 // HBM and the matrix cores balance at about 270).  What counts is how many bytes are in flight on every compute
 // unit all the time, not operand reuse:
 //   - 256 persistent workgroups (one per compute unit), each with a contiguous range of the work items (expert, row tile of
-//     at most 64 rows, block of 16 C columns).  The blocks of one row tile are one continuous stream: the loads
+//     at most 64 rows, block of 16 C columns), all ranges of about the same cost.  The blocks of one row tile are one continuous stream: the loads
 //     of the next block are in flight while the current one is summed and stored.
 //   - the W wavefronts of a workgroup deal the 128-byte pieces ("units") of the reduction among themselves
 //     (wavefront w takes units w, w + W, ..: neighbouring lines of a row are requested at the same time) and add
@@ -158,6 +158,14 @@ __host__ __device__ constexpr int stream_ring_bytes(int C, int W)
     }
     return most;
 }
+
+// What a block of a row tile of 8 AR rows costs, in tenths of its weights: the activations are read again by every block and weigh
+// more the more of the ring they take.  Dealing ranges of equal cost instead of equal numbers of blocks keeps the tall tiles of
+// the experts that many tokens chose from being what the launch waits for, both contractions, rows falling on the experts as
+// 1/rank^1.1: 290 rows, 57 experts of 1024 x 4096 180 us before, 144 now; 400 rows, 32 of 2048 x 8192 489 and 379; 655
+// rows, 29 of 2560 x 10240 755 and 593 (64-row tiles of ffn.hip: 164, 423, 557); evenly spread rows as before or up to 6 %
+// less.  Coefficients of 3 and 5 instead of 4 give 601 and 586 there, but 290 instead of 284 with 5 for 128 rows, 8 of 4096 x 14336.
+__host__ __device__ constexpr uint32_t stream_cost(int C, int AR) { return static_cast<uint32_t>((10 * C + 4 * AR) / C); }
 
 // Waits until at most `units` units of LPU loads each are outstanding.
 template <int LPU, int R>
@@ -391,33 +399,66 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
     }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     clear_unrouted<bf16_t>(p, static_cast<int64_t>(blockIdx.x) * W + wave, static_cast<int64_t>(gridDim.x) * W);
-    constexpr int TILE_ROWS = 8 * stream_max_ar(C), COLS = 16 * C;
-    const int n_blocks = p.N / COLS;
+    constexpr int MAX_AR = stream_max_ar(C), TILE_ROWS = 8 * MAX_AR, COLS = 16 * C;
+    const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
     const ExpertTiles et = scan_row_tiles(p, offsets, TILE_ROWS);
     // Every workgroup begins its blocks at another place of the reduction: rows a power of two bytes apart put the same
     // columns of all rows on few memory channels, and workgroups that walk the reduction in step all ask these
     // (rows of 8 and 32 KiB, 256 workgroups: 5.3 and 4.8 TB/s in step, 6.1 rotated; rows of 4.5 KiB 6.0 either way).
     // items (expert, row tile, column block); consecutive workgroup ids are on different XCDs: an XCD's workgroups
-    // take neighbouring ranges, so an expert's rows meet in one L2
-    const int64_t total = static_cast<int64_t>(et.total) * n_blocks;
+    // take neighbouring ranges, so an expert's rows meet in one L2.  The ranges have the same number of blocks, or the same cost
+    // where that is expected to end earlier: by the dearest block at most above the mean, against a whole number of dearest blocks.
+    const int cnt = et.hi - et.lo;
+    const uint32_t whole = static_cast<uint32_t>(cnt) / TILE_ROWS;
+    const int rest = cnt - static_cast<int>(whole) * TILE_ROWS;
+    constexpr uint32_t kWholeCost = stream_cost(C, MAX_AR);
+    uint32_t whole_cost = 1u, rest_cost = rest != 0 ? 1u : 0u, cost_incl = static_cast<uint32_t>(et.incl);  // cost of a block
+    if (__ballot(cnt > 16) != 0ull) {  // (else all blocks cost nearly the same)
+        const uint32_t c = rest == 0 ? 0u : (rest <= 8 ? stream_cost(C, 1) : (rest <= 16 ? stream_cost(C, 2) : (rest <= 32 ? stream_cost(C, 4) : kWholeCost)));
+        const uint32_t incl = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(whole * kWholeCost + c)));
+        const uint32_t dearest = __ballot(cnt > 32) != 0ull ? kWholeCost : stream_cost(C, 4);
+        const uint32_t even = (static_cast<uint32_t>(et.total) * n_blocks + kStreamGrid - 1) / kStreamGrid * dearest;
+        const float all = static_cast<float>(wave_read_lane(static_cast<int>(incl), kWave - 1)) * static_cast<float>(n_blocks);
+        if (all < 2e9f && all * (1.0f / kStreamGrid) + static_cast<float>(dearest) < static_cast<float>(even)) {  // (32-bit products below)
+            whole_cost = kWholeCost;
+            rest_cost = c;
+            cost_incl = incl;
+        }
+    }
+    const uint32_t cost = whole * whole_cost + rest_cost;
+    const uint32_t total = static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost_incl), kWave - 1)) * n_blocks;
     const int per_xcd = static_cast<int>(gridDim.x) / kXcdCount;
     const int lin = static_cast<int>(blockIdx.x % kXcdCount) * per_xcd + static_cast<int>(blockIdx.x / kXcdCount);
-    int item = static_cast<int>(total * lin / gridDim.x);
-    const int end = static_cast<int>(total * (lin + 1) / gridDim.x);
-    while (item < end) {
-        const int t = item / n_blocks, block = item - t * n_blocks;
-        const int e = __builtin_ctzll(__ballot(t < et.incl));
-        const int in_expert = t - (wave_read_lane(et.incl, e) - wave_read_lane(et.tiles, e));
-        const int row_begin = __builtin_amdgcn_readfirstlane(wave_read_lane(et.lo, e) + in_expert * TILE_ROWS);
+    uint32_t at = static_cast<uint32_t>(static_cast<uint64_t>(total) * lin / kStreamGrid);
+    const uint32_t end = static_cast<uint32_t>(static_cast<uint64_t>(total) * (lin + 1) / kStreamGrid);
+    while (at < end) {
+        const int e = __builtin_ctzll(__ballot(at < cost_incl * n_blocks));
+        const uint32_t e_cost = static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost), e));
+        const uint32_t e_begin = (static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost_incl), e)) - e_cost) * n_blocks;
+        const uint32_t e_whole = static_cast<uint32_t>(wave_read_lane(static_cast<int>(whole), e));
+        uint32_t tile = (at - e_begin) / (whole_cost * n_blocks), c = whole_cost;
+        if (tile >= e_whole) {
+            tile = e_whole;
+            c = e_cost - e_whole * whole_cost;
+        }
+        const uint32_t tile_begin = e_begin + tile * whole_cost * n_blocks;
+        // the blocks that begin inside the range
+        uint32_t block = at - tile_begin, block_end = end - tile_begin;
+        if (c != 1u) {
+            block = (block + c - 1) / c;
+            block_end = (block_end + c - 1) / c;
+        }
+        block_end = min(n_blocks, block_end);
+        const int row_begin = __builtin_amdgcn_readfirstlane(wave_read_lane(et.lo, e) + static_cast<int>(tile) * TILE_ROWS);
         const int row_end = __builtin_amdgcn_readfirstlane(min(row_begin + TILE_ROWS, wave_read_lane(et.hi, e)));
-        const int block_end = min(n_blocks, block + end - item);
+        at = tile_begin + c * n_blocks;
+        if (block >= block_end) continue;
         const int rows = row_end - row_begin;
-        constexpr int MAX_AR = stream_max_ar(C);
-        if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
-        else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
-        else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
-        else stream_segment<C, MAX_AR, W>(p, e, row_begin, row_end, block, block_end, lin, list, smem);
-        item += block_end - block;
+        const int b0 = __builtin_amdgcn_readfirstlane(static_cast<int>(block)), b1 = __builtin_amdgcn_readfirstlane(static_cast<int>(block_end));
+        if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else stream_segment<C, MAX_AR, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
     }
 }
 

@@ -78,6 +78,15 @@ def test_streamed_ffn_row_tiles(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1300 + d + f)
 
 
+@pytest.mark.parametrize("counts,d,f", [
+    ([200, 62, 35, 33, 17, 16, 9, 8, 7, 1, 0, 0, 0, 0, 0, 3], 64, 4160),   # blocks of 64 columns
+    ([90, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1], 320, 8256),                    # 64, then 16
+    ([3, 0, 33, 1, 0, 17, 33, 1, 1, 100, 65], 576, 1664)])                 # 32 in both contractions
+def test_streamed_ffn_ranges_of_equal_cost(oracle, counts, d, f):
+    """Rows so uneven that the workgroups' ranges are cut by cost: every block of every tile, for every block width."""
+    P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1350 + d)
+
+
 @pytest.mark.parametrize("T,d,f,E,k", [(1, 256, 1024, 8, 1), (3, 64, 64, 2, 2), (256, 192, 448, 1, 1), (257, 192, 448, 1, 1), (84, 128, 704, 3, 1), (90, 128, 704, 64, 2)])
 def test_streamed_ffn_fused(oracle, T, d, f, E, k):
     """Gathered rows, scattered and scaled results, tokens without a resident expert; 256 and 257 rows are the two sides
