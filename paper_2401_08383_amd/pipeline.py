@@ -91,18 +91,15 @@ class MoELayerRun:
                                       self.d, self.k, self.dt, self.out.data_ptr(), B._stream()))
 
     def _describe(self):
-        p = B._ptr
-        d = B.MoELayerDesc(
-            x=p(self.x), w_gate=p(self.w_gate), w1=p(self.w1), w2=p(self.w2), forced_idx=p(self.forced_idx), expert_map=p(self.expert_map),
-            T=self.T, d=self.d, f=self.f, E=self.E, E_local=self.E_local, k=self.k, renormalize=self.renorm, act=self.act, dt=self.dt,
-            fused=int(self.fused), topk_idx=p(self.topk_idx), topk_w=p(self.topk_w), x_sorted=p(self.x_sorted),
-            src_of_sorted=p(self.src_of_sorted), sorted_of_src=p(self.sorted_of_src), expert_counts=p(self.expert_counts),
-            expert_offsets=p(self.expert_offsets), y_sorted=p(self.y_sorted), out=p(self.out), dispatch_workspace=p(self.ws_dispatch),
-            dispatch_workspace_bytes=self.ws_dispatch.numel(), ffn_workspace=p(self.ws_ffn), ffn_workspace_bytes=self.ws_ffn.numel())
-        tensors = [t for t in (self.x, self.w_gate, self.w1, self.w2, self.forced_idx, self.expert_map, self.topk_idx, self.topk_w,
-                               self.x_sorted, self.src_of_sorted, self.sorted_of_src, self.expert_counts, self.expert_offsets,
-                               self.y_sorted, self.out, self.ws_dispatch, self.ws_ffn) if t is not None]
-        self._args = (tensors, self._storage(tensors), d, ctypes.addressof(d), self.lib.moe_layer_forward)
+        tensors = (self.x, self.w_gate, self.w1, self.w2, self.forced_idx, self.expert_map, self.topk_idx, self.topk_w, self.x_sorted,
+                   self.src_of_sorted, self.sorted_of_src, self.expert_counts, self.expert_offsets, self.y_sorted, self.out,
+                   self.ws_dispatch, self.ws_ffn)
+        at = [None if t is None else t.data_ptr() for t in tensors]
+        n_dispatch, n_ffn = self.ws_dispatch.numel(), self.ws_ffn.numel()
+        d = B.MoELayerDesc(*at[:6], self.T, self.d, self.f, self.E, self.E_local, self.k, self.renorm, self.act, self.dt, self.fused, 0,
+                           *at[6:16], n_dispatch, at[16], n_ffn)
+        given = [t for t in tensors if t is not None]
+        self._args = (given, (*[p for p in at if p is not None], n_dispatch, n_ffn), d, ctypes.addressof(d), self.lib.moe_layer_forward)
         return self._args
 
     @staticmethod
