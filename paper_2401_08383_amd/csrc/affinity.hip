@@ -372,8 +372,8 @@ __global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int
     const uint32_t row_bytes = static_cast<uint32_t>((E + 1) / 2) * 4u;
     const uint32_t my_copy = static_cast<uint32_t>(threadIdx.x & (copies - 1)) * static_cast<uint32_t>(copy_words) * 4u;
     // The transitions of one sweep, in loops over the targets and over the two blocks: unrolled, the code of one sweep is 17 KB, and
-    // short traces wait for nothing else (18 layers x 9787 tokens: 19.5 us, 9787 tokens are one sweep or two).  As the source of a pair a token is the byte offset of its row, as the target that of its
-    // word and the addend: one addition and one atomic a transition.  CHECK: an invalid id adds 0 (to a word of row 0 or
+    // short traces (one sweep or two) wait for nothing else.  As the source of a pair a token is the byte offset of its row, as
+    // the target that of its word and the addend: one addition and one atomic a transition.  CHECK: an invalid id adds 0 (to a word of row 0 or
     // column 0); this costs as many vector instructions as the LDS has cycles, so clean wavefronts (nearly all) do without.
     auto count_all = [&](auto check, const TokVec<VEC>(&col)[2 * kHopBlock], int left) {
         constexpr bool CHECK = decltype(check)::value;
@@ -488,6 +488,80 @@ __global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int
         }
         const size_t pair = static_cast<size_t>(l) * (2 * L - l - 1) / 2 + (to - l - 1);
         reinterpret_cast<uint2*>(part_counts + (static_cast<size_t>(c) * total_pairs + pair) * words)[w] = sum;
+    }
+}
+
+// The same counts by groups of one source layer and up to three targets: four columns in registers for three pairs, 24 KB of
+// histograms (two replicas of them) to clear and to write instead of 152, a sixth of the code.  It reads more than twice as many
+// columns per pair as the blocks, but starts and ends sooner: short traces and few layers (see multihop_in_groups; 8 layers x
+// 100000 tokens, 64 experts: 25.5 us by blocks, 11.4).  Groups are numbered in pair order; histogram rows and partials as above.
+template <int VEC>
+__global__ __launch_bounds__(kTraceThreads) void multihop_group_kernel(const int32_t* __restrict__ trace, int L, int64_t N, int E, int Q,
+                                                                       int copies, int words, int64_t chunk, int C,
+                                                                       uint32_t* __restrict__ part_counts)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];  // [copies][kAffMaxGroup][words], two 16-bit counters per word
+    // all groups of a token chunk on one XCD: the columns they share are served by its L2
+    const int j = static_cast<int>(blockIdx.x) / kXcds;
+    const int c = j / Q * kXcds + static_cast<int>(blockIdx.x) % kXcds;
+    if (c >= C) return;
+    int q = j % Q, l = 0, pair = 0;  // source layer and number of its first pair
+    for (; q >= (L - 2 - l) / kAffMaxGroup + 1; ++l) {
+        q -= (L - 2 - l) / kAffMaxGroup + 1;
+        pair += L - 1 - l;
+    }
+    const int m0 = l + 1 + q * kAffMaxGroup;  // first target
+    const int my_pairs = min(kAffMaxGroup, L - m0);
+    pair += q * kAffMaxGroup;
+
+    const int64_t n_begin = static_cast<int64_t>(c) * chunk;
+    const int64_t n_end = min(N, n_begin + chunk);
+    const int64_t sweep = static_cast<int64_t>(kTraceThreads) * VEC;
+    auto load_cols = [&](int64_t n0, TokVec<VEC>(&col)[kAffMaxGroup + 1]) {  // clamped, never skipped
+        col[0] = load_tokens<VEC, false>(trace + static_cast<int64_t>(l) * N, n0, n_end);
+#pragma unroll
+        for (int s = 1; s <= kAffMaxGroup; ++s) col[s] = load_tokens<VEC, false>(trace + static_cast<int64_t>(min(m0 + s - 1, L - 1)) * N, n0, n_end);
+    };
+    TokVec<VEC> col[kAffMaxGroup + 1], nxt[kAffMaxGroup + 1];
+    load_cols(n_begin + static_cast<int64_t>(threadIdx.x) * VEC, col);
+    for (int i = threadIdx.x; i < copies * kAffMaxGroup * words / 2; i += kTraceThreads) reinterpret_cast<uint2*>(lds)[i] = make_uint2(0u, 0u);
+    __syncthreads();
+    const int row_words = (E + 1) / 2;
+    uint32_t* mine = lds + (threadIdx.x & (copies - 1)) * kAffMaxGroup * words;
+    for (int64_t base = n_begin; base < n_end; base += sweep) {
+        const int64_t n0 = base + static_cast<int64_t>(threadIdx.x) * VEC;
+        load_cols(n0 + sweep, nxt);
+        unsigned m = 0;
+#pragma unroll
+        for (int s = 0; s <= kAffMaxGroup; ++s)
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) m = max(m, static_cast<unsigned>(col[s].v[u]));  // (clamped duplicate columns repeat a checked one)
+        const bool clean = __ballot(n0 + VEC > n_end || m >= static_cast<unsigned>(E)) == 0ull;
+        if (!clean) {
+#pragma unroll
+            for (int s = 0; s <= kAffMaxGroup; ++s) cut_vector(col[s], n0, n_end);
+        }
+#pragma unroll
+        for (int s = 1; s <= kAffMaxGroup; ++s) {
+            if (s > my_pairs) break;
+            uint32_t* h = mine + (s - 1) * words;
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) {
+                const int a = col[0].v[u], b = col[s].v[u];
+                if (clean || (n0 + u < n_end && static_cast<unsigned>(a) < static_cast<unsigned>(E) && static_cast<unsigned>(b) < static_cast<unsigned>(E)))
+                    atomicAdd(&h[a * row_words + (b >> 1)], 1u << ((b & 1) * 16));
+            }
+        }
+#pragma unroll
+        for (int s = 0; s <= kAffMaxGroup; ++s) col[s] = nxt[s];
+    }
+    __syncthreads();
+    // flush, replicas summed (packed halves cannot carry: a bin holds at most `chunk` < 65536)
+    uint32_t* to = part_counts + (static_cast<size_t>(c) * (static_cast<size_t>(L) * (L - 1) / 2) + pair) * words;
+    for (int i = threadIdx.x; i < my_pairs * words; i += kTraceThreads) {
+        uint32_t sum = 0;
+        for (int r = 0; r < copies; ++r) sum += lds[r * kAffMaxGroup * words + i];
+        to[i] = sum;
     }
 }
 
@@ -896,6 +970,7 @@ extern "C" int affinity_statistics(const int32_t* trace, const int32_t* placemen
 
 namespace exf {
 struct MultihopPlan {
+    bool groups;  // multihop_group_kernel instead of blocks of four by four layers
     int blocks, Q, copies, copy_words, words, C, vec, pairs;
     int64_t chunk;
     size_t lds_bytes, total_bytes;
@@ -905,11 +980,47 @@ constexpr int kHopBanks = 64;
 constexpr int64_t kHopMaxChunk = 65280;  // 16-bit counters cannot overflow; whole wavefronts of four tokens a lane
 constexpr int64_t kHopMinChunk = 1024;
 constexpr int64_t kHopPartialWords = 4 << 20;  // partials that are written and added up within a few microseconds
+static size_t multihop_partial_bytes(const MultihopPlan& p)
+{
+    return align_up(static_cast<size_t>(p.C > 0 ? p.C : 1) * (p.pairs > 0 ? p.pairs : 1) * p.words * sizeof(uint32_t), 256);
+}
+// Groups of three pairs or blocks of sixteen: the blocks read fewer columns per pair and their workgroups clear and write far larger
+// histograms, so they pay for long traces of many layers.  Where both take the same time, in millions of transitions (pairs times
+// tokens), by layers and experts, measured at 4 to 24 layers x 8, 24, 40 and 64 experts x 2000 to 800000 tokens.  Groups and blocks, us:
+// 4 x 300000, 64 experts 13.0 and 26.7; 8 x 100000, 64 experts 11.4 and 25.5; 12 x 150000, 8 experts 12.2 and 13.9; 12 x 250001, 8
+// experts 19.3 and 15.8; 18 x 9787, 64 experts 17 and 24; 16 x 450000, 64 experts 40.8 and 38.3; 24 x 1000000, 64 experts 126 and 90.
+static bool multihop_in_groups(int L, int64_t N, int E)
+{
+    const double most = L <= 17 ? 8.0 + 0.32 * E : (L <= 19 ? 4.0 + 0.3 * E : (L <= 22 ? 0.6 * (E - 40) : 0.0));
+    return 1e-6 * (0.5 * L * (L - 1)) * static_cast<double>(N) <= most;
+}
+static void plan_multihop_groups(MultihopPlan& p, int L, int64_t N)
+{
+    p.Q = 0;
+    for (int l = 0; l + 1 < L; ++l) p.Q += (L - 2 - l) / kAffMaxGroup + 1;
+    if (p.Q < 1) p.Q = 1;
+    p.copies = 1;
+    while (p.copies < 16 && sizeof(uint32_t) * p.words * kAffMaxGroup * (p.copies * 2) <= kAffHistBudget) p.copies *= 2;
+    p.lds_bytes = sizeof(uint32_t) * p.words * kAffMaxGroup * p.copies;
+    const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;
+    const int64_t c_target = kTargetWorkgroups / p.Q > 1 ? kTargetWorkgroups / p.Q : 1;
+    p.chunk = ((N + c_target - 1) / c_target + sweep - 1) / sweep * sweep;
+    if (p.chunk < sweep) p.chunk = sweep;
+    if (p.chunk > kAffMaxChunk) p.chunk = kAffMaxChunk / sweep * sweep;
+    p.C = static_cast<int>(N > 0 ? (N + p.chunk - 1) / p.chunk : 0);
+    p.total_bytes = multihop_partial_bytes(p);
+}
 static MultihopPlan make_multihop_plan(int L, int64_t N, int E)
 {
-    MultihopPlan p;
+    MultihopPlan p{};
     p.pairs = L * (L - 1) / 2;
     p.words = (E * ((E + 1) / 2) + 1) / 2 * 2;
+    p.vec = trace_vec(N);
+    p.groups = multihop_in_groups(L, N, E);
+    if (p.groups) {
+        plan_multihop_groups(p, L, N);
+        return p;
+    }
     p.blocks = (L + kHopBlock - 1) / kHopBlock;
     const int cross = p.blocks * (p.blocks - 1) / 2;
     p.Q = cross + (p.blocks < kHopShareBlocks ? p.blocks : 0);
@@ -927,7 +1038,6 @@ static MultihopPlan make_multihop_plan(int L, int64_t N, int E)
     p.copies = 1;
     while (p.copies < 32 && p.copy_words * 4 * (p.copies * 2) <= kHopLdsBytes / 2) p.copies *= 2;
     p.lds_bytes = static_cast<size_t>(p.copy_words) * p.copies * sizeof(uint32_t);
-    p.vec = trace_vec(N);
     // As few chunks as the counters allow (each costs a pass over its histograms), but a whole number of rounds of one workgroup
     // per compute unit
     int64_t c_least = (N + kHopMaxChunk - 1) / kHopMaxChunk;
@@ -943,7 +1053,7 @@ static MultihopPlan make_multihop_plan(int L, int64_t N, int E)
     p.chunk = ((N + c_target - 1) / c_target + 255) / 256 * 256;  // (a wavefront cut by the end of its chunk takes the checked path)
     if (p.chunk < 256) p.chunk = 256;
     p.C = static_cast<int>(N > 0 ? (N + p.chunk - 1) / p.chunk : 0);
-    p.total_bytes = align_up(static_cast<size_t>(p.C > 0 ? p.C : 1) * (p.pairs > 0 ? p.pairs : 1) * p.words * sizeof(uint32_t), 256);
+    p.total_bytes = multihop_partial_bytes(p);
     return p;
 }
 }  // namespace exf
@@ -968,7 +1078,13 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "affinity_multihop: workspace %zu < %zu bytes", workspace_bytes, p.total_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* part_counts = static_cast<uint32_t*>(workspace);
-    if (p.C > 0) {
+    if (p.C > 0 && p.groups) {
+        const int64_t grid = static_cast<int64_t>((p.C + kXcds - 1) / kXcds * kXcds) * p.Q;
+        if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "affinity_multihop: too many workgroups");
+        auto kern = p.vec == 4 ? multihop_group_kernel<4> : multihop_group_kernel<1>;
+        hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kTraceThreads), p.lds_bytes, s, trace, L, N, E, p.Q, p.copies, p.words,
+                           p.chunk, p.C, part_counts);
+    } else if (p.C > 0) {
         const int64_t grid = (static_cast<int64_t>(p.C) * p.Q + kXcds - 1) / kXcds * kXcds;
         if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "affinity_multihop: too many workgroups");
         auto kern = p.vec == 4 ? multihop_partial_kernel<4> : multihop_partial_kernel<1>;

@@ -48,6 +48,28 @@ def test_multihop_blocks(L, N, E):
     Q.test_affinity_multihop_parity(L, N, E)
 
 
+@pytest.mark.parametrize("L,N,E", [(5, 1100003, 3), (8, 430001, 5), (12, 250000, 2), (13, 200003, 9), (16, 250001, 64)])
+def test_multihop_blocks_of_few_layers(L, N, E):
+    """Traces of few layers that are long enough for the blocks."""
+    Q.test_affinity_multihop_parity(L, N, E)
+
+
+@pytest.mark.parametrize("L,N,E", [(2, 1, 64), (2, 3, 1), (3, 4099, 63), (4, 61441, 33), (5, 7, 64), (7, 8195, 2), (11, 40001, 17), (17, 60003, 40),
+                                   (18, 4096, 64), (19, 30001, 5), (22, 4097, 64)])
+def test_multihop_groups(L, N, E):
+    """One to three targets in the last group of a layer, columns that start anywhere, every number of replicas."""
+    Q.test_affinity_multihop_parity(L, N, E)
+
+
+def test_multihop_groups_fill_a_counter():
+    """Every transition of the longest chunk in one 16-bit counter."""
+    N = 61440 * 256 + 5
+    _say(f"multihop L=2 N={N}, one transition only")
+    trace = torch.full((2, N), 63, dtype=torch.int32, device="cuda")
+    counts = B.affinity_multihop(trace, 64)["counts"]
+    assert counts[0, 63, 63].item() == N and counts.sum().item() == N
+
+
 # ----------------------------------------------------------------------------- candidate scores
 @pytest.mark.parametrize("E,Bn,total", [(1, 1, 5), (33, 9, (1 << 31) - 1), (33, 9, 1 << 31), (64, 300, (1 << 31) - 1), (64, 300, 1 << 33),
                                         (63, 4099, 100000)])
