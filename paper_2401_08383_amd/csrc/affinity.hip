@@ -824,15 +824,21 @@ __global__ __launch_bounds__(kTraceThreads) void locality_partial_kernel(const i
 }
 
 // One wavefront per output element j: the first `pairs` elements go to local_per_pair, the rest
-// (present with home devices only) to away_per_layer.
+// (present with home devices only) to away_per_layer.  The sums of up to 256 chunks are asked for at once; in a loop that leaves
+// one lane after the other they were awaited one by one (transfers of 6 x 1000000 tokens, 245 chunks: 12.3 us, now 10.7).
 __global__ __launch_bounds__(kWave) void locality_finalize_kernel(const uint32_t* __restrict__ part, int C, int pairs, int n_out,
                                                                    int64_t* __restrict__ local_per_pair,
                                                                    int64_t* __restrict__ away_per_layer)
 {
     const int j = blockIdx.x;
     long long s = 0;
-#pragma unroll 4
-    for (int c = threadIdx.x; c < C; c += kWave) s += part[static_cast<size_t>(c) * n_out + j];
+    for (int c0 = threadIdx.x; c0 - static_cast<int>(threadIdx.x) < C; c0 += 4 * kWave) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = part[static_cast<size_t>(min(c0 + u * kWave, C - 1)) * n_out + j];  // clamped, never branched around
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += c0 + u * kWave < C ? v[u] : 0u;
+    }
     s = wave_sum(s);
     if (threadIdx.x == 0) {
         if (j < pairs) local_per_pair[j] = s;
