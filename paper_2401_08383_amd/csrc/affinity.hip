@@ -21,9 +21,9 @@
 //
 // placement_locality
 //   a workgroup owns a chunk of tokens for ALL layers (each trace entry is read exactly once),
-//   maps expert -> device through an LDS copy of the placement, keeps the loads of four layers in
-//   flight, and counts per pair the tokens whose device does not change; per-chunk partial counts
-//   are summed by a second kernel.
+//   maps expert -> device through an LDS copy of the placement, asks for the next two layers while
+//   it counts the last two, and counts per pair the tokens whose device does not change; per-chunk
+//   partial counts are summed by a second kernel.
 #include "common.hpp"
 
 #include <type_traits>
@@ -103,7 +103,7 @@ struct TokVec {
 // one, which leaves a single load in flight per wavefront.
 // A column starts at any multiple of four bytes (its length is the number of tokens, any number): the
 // 16-byte load of gfx950 needs no more, and it costs one more cache line per wavefront when it straddles.
-// (Odd token counts used to take 4-byte loads: 44 us for the transfers of a 24 x 999983 trace, 22 now.)
+// (Odd token counts used to take 4-byte loads: 46.5 us for the transfers of a 24 x 999983 trace, 24.9 now.)
 // A lane whose vector is cut by the end of the chunk receives the LAST VEC ids; cut_vector() moves them.
 // STREAM: the column is read once.
 template <int VEC, bool STREAM = true>
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
     auto load_cols = [&](int64_t n0, TokVec<VEC>(&col)[kAffMaxGroup + 1]) {
 #pragma unroll
         for (int s = 0; s <= kAffMaxGroup; ++s)
-            if (s == 0 || s == kAffMaxGroup) {  // read by the neighbouring groups too: not past the L2 (24 x 1M tokens: 25.3 -> 23.3 us)
+            if (s == 0 || s == kAffMaxGroup) {  // read by the neighbouring groups too: not past the L2 (this launch, 24 x 1M tokens: 25.6 us, so 23.1)
                 col[s] = load_tokens<VEC, false>(trace + static_cast<int64_t>(min(l0 + s, l1)) * N, n0, n_end);
             } else {
                 col[s] = load_tokens<VEC>(trace + static_cast<int64_t>(min(l0 + s, l1)) * N, n0, n_end);
@@ -848,8 +848,8 @@ __global__ __launch_bounds__(kWave) void locality_finalize_kernel(const uint32_t
 
 // A thread walks all layers of its tokens, one after the other: a short trace is spread as thin as possible, one token a thread up
 // to a token for every thread of the chip, and in workgroups of four wavefronts as long as these give at most one set of
-// partial counts per compute unit (1000 sets cost the second launch 4 us).  22 layers x 1813 tokens with home devices:
-// four tokens a thread 21.6 us, one 13.4; 24 x 250000: 23.7, now 16.4.
+// partial counts per compute unit (1000 sets cost the second launch 4 us).  Transfers of 24 layers x 250000
+// tokens: four tokens a thread in workgroups of 1024 23.8 us, one token a thread 15.7.
 struct LocalityPlan {
     int vec, threads, C;
     int64_t chunk;
