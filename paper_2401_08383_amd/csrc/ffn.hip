@@ -77,7 +77,7 @@ __device__ __forceinline__ void timeline_stamp(const RowMap& map, int slot)
 // The rows of an expert become q = rows / 256 tiles, and what is left over is spread over them in quanta of 32 rows: a tile
 // of 288 rows costs an eighth more, one more tile a whole one.  A tile takes at most `most` quanta; where the
 // remainder is larger there is one tile more, all of one height.  most = 1, or 2 where the launch then has fewer rounds of
-// tiles (see plan_tiles).  An expert of at most 128 rows has one small tile.
+// tiles (see plan_tiles).  An expert of at most 128 rows has one small tile, or two of 64 rows where the launch has few tiles.
 // Heights a tile is instantiated for: 64 and 128 (small), 192, 256, 288, 320.
 constexpr int kTileRows = 256;
 constexpr int kQuantum = 32;
@@ -86,7 +86,7 @@ constexpr int kSmallRows = 128;
 struct TileRows {
     int tiles, height, extra;  // row tiles, their base height, quanta spread over them
 };
-__device__ __forceinline__ TileRows cut_rows(int cnt, int most)
+__device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool halves)
 {
     TileRows t;
     const int q = cnt / kTileRows, r = cnt - q * kTileRows;
@@ -99,6 +99,10 @@ __device__ __forceinline__ TileRows cut_rows(int cnt, int most)
         // (q is at most 7 here)
         const int even = q == 0 ? cnt : (q == 1 ? (cnt + 1) / 2 : (q == 2 ? (cnt + 2) / 3 : kTileRows));
         t.height = even <= 64 && q == 0 ? 64 : (even <= kSmallRows && q == 0 ? kSmallRows : (even <= 192 ? 192 : kTileRows));
+        if (halves && t.height == kSmallRows) {
+            t.tiles = 2;
+            t.height = kSmallRows / 2;
+        }
     }
     return t;
 }
@@ -109,6 +113,7 @@ struct TilePlan {  // lane e = expert e; the same in every workgroup
     int big_incl, small_incl;   // running sums of row tiles times column tiles
     int total_big, total_small;
     int most;                   // quanta a tile takes at most
+    bool halves;                // experts of 65 to 128 rows: two tiles of 64
 };
 struct Tile2D {
     int expert;
@@ -135,7 +140,7 @@ __device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offse
     }
     // one quantum per tile, unless two make the launch a round of tiles shorter
     const bool small = cnt <= kSmallRows;
-    const int lean = cnt > 0 ? cut_rows(cnt, 1).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2).tiles : 0;
+    const int lean = cnt > 0 ? cut_rows(cnt, 1, false).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2, false).tiles : 0;
     const int lean_incl = wave_inclusive_scan(small ? 0 : lean * n_tiles), tall_incl = wave_inclusive_scan(small ? 0 : tall * n_tiles);
     p.small_incl = wave_inclusive_scan(small ? lean * n_tiles : 0);
     const int lean_total = wave_read_lane(lean_incl, kWave - 1), tall_total = wave_read_lane(tall_incl, kWave - 1);
@@ -145,6 +150,20 @@ __device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offse
     p.big_incl = use_tall ? tall_incl : lean_incl;
     p.total_big = use_tall ? tall_total : lean_total;
     p.total_small = wave_read_lane(p.small_incl, kWave - 1);
+    // Tiles of 128 rows in halves while all tiles then still have their columns cut into four, side by side: a compute unit has
+    // half the work (both contractions, one expert of 2048 x 8192, 100 rows: 53.5 us and 45.4; of 4096 x 14336, 128 rows: 107 and
+    // 85; four of 1024 x 4096, 100 rows each: 34.7 and 30.4.  Twice as many, cut into two: 40.0 and 41.1 for eight, 66 rows each).
+    p.halves = false;
+    if (p.total_big + p.total_small < kComputeUnits / 4) {
+        const unsigned long long mid = __ballot(cnt > kSmallRows / 2 && cnt <= kSmallRows);
+        const int more = __popcll(mid) * n_tiles;
+        if (mid != 0ull && p.total_big + p.total_small + more <= kComputeUnits / 4) {
+            p.halves = true;
+            if ((mid >> lane & 1ull) != 0ull) p.tiles = 2;
+            p.small_incl += __popcll(mid & (~0ull >> (kWave - 1 - lane))) * n_tiles;
+            p.total_small += more;
+        }
+    }
     return p;
 }
 
@@ -223,7 +242,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
         col_tile = static_cast<int>(c);
         row_tile = blocked_rows + static_cast<int>(rr - c * rows_left);
     }
-    const TileRows t = cut_rows(e_hi - e_lo, p.most);
+    const TileRows t = cut_rows(e_hi - e_lo, p.most, p.halves);
     // quanta: every tile takes extra / tiles, the first extra % tiles one more
     const int each = t.extra >= 2 * t.tiles ? 2 : (t.extra >= t.tiles ? 1 : 0), more = t.extra - each * t.tiles;
     const int begin_row = e_lo + row_tile * t.height + (row_tile * each + min(row_tile, more)) * kQuantum;
@@ -764,8 +783,8 @@ static int launch_bf16_as(const void* act, const int32_t* offsets, const void* w
                           void* out, hipStream_t stream, const RowMap& map)
 {
     constexpr size_t lds = gemm_lds_bytes<NT>();
-    // worst case: every expert has one tile more than whole ones; two kinds of tiles are shared out over the XCDs, and the last
-    // round may be cut
+    // worst case: every expert has one tile more than whole ones (or two halves, but then the grid of a cut round is enough); two
+    // kinds of tiles are shared out over the XCDs, and the last round may be cut
     const int64_t n_tiles = (N + NT - 1) / NT;
     const int64_t items = (A / kTileRows + (A < E_local ? A : E_local)) * n_tiles;
     const int64_t grid = (items / kXcdCount + 2 + kUnitsPerXcd) * kXcdCount;

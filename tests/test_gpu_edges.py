@@ -125,6 +125,13 @@ def test_grouped_ffn_row_tiles(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1700 + d + f)
 
 
+@pytest.mark.parametrize("counts,d,f", [([65, 128, 0, 64, 127], 320, 1088), ([100], 128, 4160), ([66, 129, 300, 96], 64, 576),
+                                        ([100] * 13, 192, 1088), ([128, 65] * 9 + [1, 260], 128, 1024)])
+def test_grouped_ffn_small_tiles_in_halves(oracle, counts, d, f):
+    """Experts of 65 to 128 rows: two tiles of 64 rows in launches of few tiles, one of 128 in larger ones (the last two)."""
+    P._ffn_case(oracle, "bf16", counts, d, f, 1, True, seed=1750 + d)
+
+
 @pytest.mark.parametrize("T,d,f,E,k", [(700, 64, 192, 3, 1), (1500, 192, 320, 5, 2), (900, 320, 1088, 2, 2)])
 def test_grouped_ffn_fused(oracle, T, d, f, E, k):
     P._fused_case(oracle, T, d, f, E, E, k, 1, True, seed=1800 + T)
