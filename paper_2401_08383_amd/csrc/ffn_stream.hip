@@ -413,7 +413,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
     const int rest = cnt - static_cast<int>(whole) * TILE_ROWS;
     constexpr uint32_t kWholeCost = stream_cost(C, MAX_AR);
     uint32_t whole_cost = 1u, rest_cost = rest != 0 ? 1u : 0u, cost_incl = static_cast<uint32_t>(et.incl);  // cost of a block
-    if (__ballot(cnt > 16) != 0ull) {  // (else all blocks cost nearly the same)
+    if (et.total > 1 && __ballot(cnt > 16) != 0ull) {  // (else all blocks cost nearly the same)
         const uint32_t c = rest == 0 ? 0u : (rest <= 8 ? stream_cost(C, 1) : (rest <= 16 ? stream_cost(C, 2) : (rest <= 32 ? stream_cost(C, 4) : kWholeCost)));
         const uint32_t incl = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(whole * kWholeCost + c)));
         const uint32_t dearest = __ballot(cnt > 32) != 0ull ? kWholeCost : stream_cost(C, 4);
@@ -429,8 +429,10 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
     const uint32_t total = static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost_incl), kWave - 1)) * n_blocks;
     const int per_xcd = static_cast<int>(gridDim.x) / kXcdCount;
     const int lin = static_cast<int>(blockIdx.x % kXcdCount) * per_xcd + static_cast<int>(blockIdx.x / kXcdCount);
-    uint32_t at = static_cast<uint32_t>(static_cast<uint64_t>(total) * lin / kStreamGrid);
-    const uint32_t end = static_cast<uint32_t>(static_cast<uint64_t>(total) * (lin + 1) / kStreamGrid);
+    // total * lin / kStreamGrid and the next one's begin, in 32 bits and scalar registers
+    const uint32_t t_hi = __builtin_amdgcn_readfirstlane(total / kStreamGrid), t_lo = __builtin_amdgcn_readfirstlane(total % kStreamGrid);
+    uint32_t at = __builtin_amdgcn_readfirstlane(t_hi * lin + t_lo * lin / kStreamGrid);
+    const uint32_t end = __builtin_amdgcn_readfirstlane(t_hi * (lin + 1) + t_lo * (lin + 1) / kStreamGrid);
     while (at < end) {
         const int e = __builtin_ctzll(__ballot(at < cost_incl * n_blocks));
         const uint32_t e_cost = static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost), e));
@@ -451,10 +453,10 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         block_end = min(n_blocks, block_end);
         const int row_begin = __builtin_amdgcn_readfirstlane(wave_read_lane(et.lo, e) + static_cast<int>(tile) * TILE_ROWS);
         const int row_end = __builtin_amdgcn_readfirstlane(min(row_begin + TILE_ROWS, wave_read_lane(et.hi, e)));
-        at = tile_begin + c * n_blocks;
-        if (block >= block_end) continue;
-        const int rows = row_end - row_begin;
         const int b0 = __builtin_amdgcn_readfirstlane(static_cast<int>(block)), b1 = __builtin_amdgcn_readfirstlane(static_cast<int>(block_end));
+        at = __builtin_amdgcn_readfirstlane(tile_begin + c * n_blocks);
+        if (b0 >= b1) continue;
+        const int rows = row_end - row_begin;
         if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
         else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
         else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
@@ -712,12 +714,16 @@ static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 // bf16: the weights are streamed where few rows use them, on the mean at most 28 an expert: 24 rows of 64 experts of 1024 x 4096 take
 // 222 us against 219 with the tiles of ffn.hip, 32 rows of 8 experts of 2048 x 8192 both 114.  With few experts the
 // tiles also wait for their K loops, a quarter of a microsecond for 64 elements of d + f, while streaming costs 35 ns per row and
-// million weights: up to 256 rows in all the lower of the two (one expert of 1024 x 4096: 24.8 us against 37 with 96
-// rows, 40 against 41 with 180; of 4096 x 14336: 60 against 83 with 32, 171 against 114 with 100).
+// million weights: up to 256 rows in all the lower of the two (three experts of 1024 x 4096: 21.2 us against 27.2 with 87 rows, 27.6
+// against 27.3 with 117).  Up to 128 rows of a single expert are known to fill 32, 64 or 128 of a row tile's, which is what they
+// cost (1024 x 4096: 24.8 against 27.4 with 117 rows; 2048 x 8192: 37.1 against 44.9 with 58, 53.2 against 45.6 with 65; 4096 x
+// 14336: 52.7 against 74.0 with 30, 83.4 against 74.2 with 33).
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
     if (dt == EXF_F32 || A <= 28ll * E_local) return true;
-    return A <= 256 && A * d * f <= 120000ll * (static_cast<int64_t>(d) + f);
+    if (A > 256) return false;
+    const int64_t rows = E_local > 1 || A > 128 ? A : (A <= 32 ? 32 : (A + 63) / 64 * 64);
+    return rows * d * f <= 120000ll * (static_cast<int64_t>(d) + f);
 }
 
 int launch_stream_gemm(const StreamGemm& p, int dt, hipStream_t stream)

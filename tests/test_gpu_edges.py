@@ -117,6 +117,13 @@ def test_streamed_ffn_fused(oracle, T, d, f, E, k):
     P._fused_case(oracle, T, d, f, E, max(1, E // 3), k, 0, False, seed=1401 + T)
 
 
+@pytest.mark.parametrize("A", [32, 33, 64, 65, 128, 129])
+def test_single_expert_on_both_sides_of_the_streaming_rule(oracle, A):
+    """One expert whose rows fill 32, 64 or 128 of a row tile: 512 x 2112 streams all of them, 1536 x 3072 up to 64 rows."""
+    P._ffn_case(oracle, "bf16", [A], 512, 2112, 0, True, seed=1360 + A)
+    P._ffn_case(oracle, "bf16", [A], 1536, 3072, 0, False, seed=1361 + A)
+
+
 # ----------------------------------------------------------------------------- grouped contraction (many rows per expert)
 @pytest.mark.parametrize("d,f", [(64, 64), (128, 320), (192, 448), (320, 256), (576, 832)])
 @pytest.mark.parametrize("counts", [[128, 129, 0, 192, 193], [64, 65, 1, 255, 256, 257], [287, 288, 289, 320, 321], [511, 544, 545, 576, 577], [0, 2049]])
