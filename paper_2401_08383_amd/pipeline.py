@@ -58,6 +58,7 @@ class MoELayerRun:
         else:
             ffn_bytes = self.lib.moe_expert_ffn_workspace_bytes(A, self.d, self.f, self.E_local, self.dt)
         self.ws_ffn = torch.empty(max(ffn_bytes, 256), dtype=torch.uint8, device=dev)
+        self._describe()
 
     # each method enqueues one entry point on the current stream
     def gate(self):
