@@ -303,7 +303,7 @@ def timeline_report(syn, torch, B, index, dev):
         spans.append((t0, t1))
         print(f"{name}: {int(ran.sum())} workgroups ran a tile, first start to last end {(t1 - t0) * us:.1f} us")
         kind = r[:, 6] & 3
-        for kd, kn in ((2, "tall"), (0, "full"), (1, "remainder")):
+        for kd, kn in ((2, "taller"), (0, "256-row"), (1, "shorter")):
             m = ran & (kind == kd)
             if not m.any():
                 continue

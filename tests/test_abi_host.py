@@ -124,7 +124,7 @@ def test_workspace_sizes():
     lib = exf.lib()
     assert lib.moe_dispatch_workspace_bytes(0, 1, 8) >= 32
     assert lib.moe_dispatch_workspace_bytes(32768, 1, 8) % 256 == 0
-    split = 256 * 64 * 256 * 4  # bf16: room for the partial sums of K-sliced remainder tiles
+    split = 256 * 64 * 256 * 4  # bf16: 16 MiB in reserve (part of the interface; no kernel uses them at present)
     # bf16 hidden rows: every expert starts on a 32-row boundary (A + 32 E_local rows, rounded up to 32)
     assert lib.moe_expert_ffn_workspace_bytes(8192, 1024, 4096, 8, B.EXF_BF16) == (8192 + 32 * 8) * 4096 * 2 + split
     assert lib.moe_expert_ffn_workspace_bytes(8191, 1024, 4096, 8, B.EXF_BF16) == (8192 + 32 * 8) * 4096 * 2 + split

@@ -206,15 +206,15 @@ def test_ffn_bf16_long_reduction(oracle):
 
 @pytest.mark.parametrize("bias", [False, True])
 def test_ffn_bf16_remainder_tiles_in_k_slices(oracle, bias):
-    """Few remainder tiles and a long second reduction: they run as K slices added by a second kernel."""
-    _say(f"ffn bf16 K-sliced remainder tiles bias={bias}")
-    _ffn_case(oracle, "bf16", [70, 300, 5], 128, 1024, 0, bias, seed=440)          # 4 tail tiles x 4 slices
-    _ffn_case(oracle, "bf16", [257, 0, 129, 64, 1], 256, 2048, 1, bias, seed=441)  # 8 slices, two column tiles
+    """Few small tiles and a long second reduction (such tiles were once cut along the reduction; now their columns are)."""
+    _say(f"ffn bf16 small tiles, long reduction bias={bias}")
+    _ffn_case(oracle, "bf16", [70, 300, 5], 128, 1024, 0, bias, seed=440)
+    _ffn_case(oracle, "bf16", [257, 0, 129, 64, 1], 256, 2048, 1, bias, seed=441)
 
 
 def test_ffn_bf16_wide_second_contraction(oracle):
-    """Enough rows and output columns that the second contraction takes its 256x256 tile (with K-sliced
-    remainder tiles); sampled rows of every expert against the oracle."""
+    """Enough rows and output columns that the second contraction takes its 256x256 tile (beside a small
+    one); sampled rows of every expert against the oracle."""
     _say("ffn bf16 wide second contraction")
     counts = [9000, 70, 7430]
     off = np.concatenate([[0], np.cumsum(counts)])
@@ -230,10 +230,9 @@ def test_ffn_bf16_wide_second_contraction(oracle):
 
 @pytest.mark.parametrize("bias", [False, True])
 def test_ffn_bf16_tall_tiles(oracle, bias):
-    """Launches with two or more rounds of 256-row tiles fold small remainders into taller last tiles
-    of the expert (320 rows): remainders of 1, 64, 65 and 128 rows (one and two tall tiles), 129 rows (a
-    masked full tile instead), a remainder larger than the expert's full tiles can take (tail tiles),
-    experts without a full tile.  Every element against the oracle; first contraction (wide hidden
+    """Remainders of an expert's 256-row tiles are spread over them in quanta of 32 rows: remainders of 1,
+    64, 65 and 128 rows, 129 rows, remainders larger than the expert's tiles take (one tile more),
+    experts without a whole tile.  Every element against the oracle; first contraction (wide hidden
     layer), then second contraction (wide output)."""
     counts = [6 * 256 + 1, 3 * 256 + 65, 2 * 256 + 128, 5 * 256 + 129, 256 + 44, 256 + 100, 200, 100, 0, 2 * 256 + 64]
     _say(f"ffn bf16 tall tiles bias={bias}: first contraction")
@@ -368,7 +367,7 @@ def test_ffn_fused_top1_parity(oracle, act, bias):
 
 def test_ffn_fused_top1_skewed_and_tiny(oracle):
     _say("ffn fused top-1 skewed / tiny")
-    _fused_case(oracle, 900, 128, 1024, 6, 6, 1, 0, True, seed=713)  # remainder tiles in K slices, scattered by the adding kernel
+    _fused_case(oracle, 900, 128, 1024, 6, 6, 1, 0, True, seed=713)  # small tiles, scattered
     _fused_case(oracle, 3000, 256, 512, 32, 32, 1, 0, False, seed=710, skew=True)
     _fused_case(oracle, 1, 64, 64, 4, 4, 1, 0, False, seed=711)
     _fused_case(oracle, 67, 64, 64, 8, 1, 1, 0, True, seed=712)  # one resident expert, seven of eight tokens unrouted
@@ -508,8 +507,7 @@ def test_repeat_calls_are_deterministic():
     r1 = exf.moe_dispatch(x, idx, 64)
     r2 = exf.moe_dispatch(x, idx, 64)
     assert torch.equal(r1.src_of_sorted, r2.src_of_sorted) and torch.equal(r1.x_sorted, r2.x_sorted)
-    # expert FFN with remainder tiles in K slices (the slices are added in a fixed order), through both
-    # entry points, with the workspace overwritten between the calls
+    # expert FFN through both entry points, with the workspace overwritten between the calls
     g = syn.rng(721)
     T, d, f, E = 2100, 128, 1024, 6
     xs = to_dev(g.standard_normal((T, d), dtype=np.float32), "bf16")
