@@ -997,6 +997,7 @@ static size_t multihop_partial_bytes(const MultihopPlan& p)
 // experts 19.3 and 15.8; 18 x 9787, 64 experts 17 and 24; 16 x 450000, 64 experts 40.8 and 38.3; 24 x 1000000, 64 experts 126 and 90.
 static bool multihop_in_groups(int L, int64_t N, int E)
 {
+    if (N > kAffMaxChunk * kTargetWorkgroups) return false;  // (more chunks than the blocks cut, each with partials of its own)
     const double most = L <= 17 ? 8.0 + 0.32 * E : (L <= 19 ? 4.0 + 0.3 * E : (L <= 22 ? 0.6 * (E - 40) : 0.0));
     return 1e-6 * (0.5 * L * (L - 1)) * static_cast<double>(N) <= most;
 }

@@ -63,7 +63,7 @@ def test_multihop_groups(L, N, E):
 
 def test_multihop_groups_fill_a_counter():
     """Every transition of the longest chunk in one 16-bit counter."""
-    N = 61440 * 256 + 5
+    N = 61440 * 256 - 5
     _say(f"multihop L=2 N={N}, one transition only")
     trace = torch.full((2, N), 63, dtype=torch.int32, device="cuda")
     counts = B.affinity_multihop(trace, 64)["counts"]
