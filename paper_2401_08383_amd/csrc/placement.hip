@@ -7,10 +7,8 @@
 //     total - sum_l sum_{i,p} counts[l][i][p] * [part_l(i) == part_{l+1}(p)],
 // so it is evaluated from 754 KB of counts instead of the trace.
 //
-//   placement_locality_from_counts : GPU, scores a BATCH of candidate maps against the counts.
-//       One workgroup per (layer pair, slice of candidates) keeps the pair's E x E counts in LDS;
-//       a wavefront takes one candidate at a time: lane p holds the part of expert p at layer l+1,
-//       walks the source experts of that part and adds their counts; exact integer arithmetic.
+//   placement_locality_from_counts : GPU, scores a BATCH of candidate maps against the counts, as a contraction of
+//       the counts' digits with the maps' "same part" matrices on the matrix cores; exact integer arithmetic.
 //   exf_placement_search           : host.  The paper names no solver; this one is
 //       - exact when the number of balanced partitions of a layer is small: the objective is a
 //         chain over layers, so a dynamic programme over (layer, partition) finds the optimum;
@@ -23,146 +21,313 @@
 
 #include <algorithm>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
 
 namespace exf {
 
-constexpr int kScoreThreads = 512;
-constexpr int kScoreWaves = kScoreThreads / kWave;
-constexpr int kScoreBatch = 4;          // candidates of a wavefront whose maps are in flight together
-constexpr int kScoreMaxPerWave = 32;    // candidates a wavefront scores at most
-constexpr int kScoreWorkgroups = 1024;  // four workgroups fill a compute unit's wavefront slots: slices are cut for one round
+constexpr int kScoreWaves = 4;
+constexpr int kScoreThreads = kScoreWaves * kWave;
+constexpr int kScoreWorkgroups = 768;      // three workgroups fill a compute unit's registers
+constexpr int kDigits = 4, kDigitBits = 7; // of a count, 28 bits of it at a time
+constexpr int kCountBits = kDigits * kDigitBits;
+constexpr int kSourceRow = kDigits * EXF_MAX_EXPERTS;  // bytes of a source expert in LDS: [digit][target expert]
+constexpr int kSetMaps = 16;               // candidates of a set: columns of a matrix operand
+constexpr int kMapBytes = EXF_MAX_EXPERTS; // a map's row in LDS: a byte per expert
 
-// Position of the lowest set bit of a word, 0xffffffff for zero (what the instruction gives).
-__device__ __forceinline__ uint32_t lowest_bit(uint32_t v)
-{
-    uint32_t r = 0;
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(v));
-#endif
-    return r;
-}
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4_t;
 
-// Walks the set bits of m (source experts that share this lane's part) and adds their counts.  A lane
-// that has run out reads the zero row behind the table, so the loads carry no condition; four
-// are in flight together.
-constexpr int kScoreStride = kWave;  // entries from row to row of the table in LDS (a shift instead of a multiplication)
-template <typename Acc>
-__device__ __forceinline__ Acc add_matching_rows(const Acc* __restrict__ table, unsigned long long m, int lane)
-{
-    Acc acc = 0;
-    while (__ballot(m != 0ull) != 0ull) {
-        Acc v[4];
+// LOADS x (WIDE ? 4 : 1) rows of candidates' maps, four part numbers a lane and load (WIDE) or one, on their way to LDS as
+// bytes [map][expert].  Columns past the last expert get whatever is there: their counts are zero.
+template <int ROWS, bool WIDE>
+struct MapRows {
+    static constexpr int PER = WIDE ? 4 : 1, LOADS = ROWS / PER;  // rows a load, loads
+    typedef typename std::conditional<WIDE, int4, int>::type Piece;
+    Piece v[LOADS];
+    template <typename Row>  // row(n): the n-th row
+    __device__ __forceinline__ void load(Row row, int E, int lane)
+    {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t in_low = lowest_bit(static_cast<uint32_t>(m)), in_high = lowest_bit(static_cast<uint32_t>(m >> 32)) | 32u;
-            const uint32_t i = min(min(in_low, in_high), static_cast<uint32_t>(kWave));
-            m &= m - 1ull;  // (0 stays 0)
-            v[u] = table[i * kScoreStride + lane];
+        for (int i = 0; i < LOADS; ++i) {
+            if constexpr (WIDE) v[i] = *reinterpret_cast<const int4*>(row(4 * i + (lane >> 4)) + min(4 * (lane & 15), E - 4));
+            else v[i] = row(i)[min(lane, E - 1)];
         }
-        acc += (v[0] + v[1]) + (v[2] + v[3]);
     }
-    return acc;
+    // returns the bits of all parts seen
+    __device__ __forceinline__ uint32_t store(unsigned char* to, int lane) const
+    {
+        uint32_t any = 0;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            if constexpr (WIDE) {
+                any |= static_cast<uint32_t>((v[i].x | v[i].y) | (v[i].z | v[i].w));
+                const uint32_t lo = __builtin_amdgcn_perm(v[i].y, v[i].x, 0x0c0c0400u), hi = __builtin_amdgcn_perm(v[i].w, v[i].z, 0x04000c0cu);
+                *reinterpret_cast<uint32_t*>(to + (4 * i + (lane >> 4)) * kMapBytes + 4 * (lane & 15)) = lo | hi;
+            } else {
+                any |= static_cast<uint32_t>(v[i]);
+                to[i * kMapBytes + lane] = static_cast<unsigned char>(v[i]);
+            }
+        }
+        return any;
+    }
+};
+
+// Part numbers that do not fit seven bits: what counts is which source experts share a target's part, so the lowest of them
+// stands for the part (64 for a target whose part no source expert has).  One map, a lane an expert.
+__device__ __forceinline__ void relabel(const int32_t* __restrict__ row, int E, int lane, unsigned char* source, unsigned char* target)
+{
+    const unsigned from = static_cast<unsigned>(row[min(lane, E - 1)]), to = static_cast<unsigned>(row[E + min(lane, E - 1)]);
+    unsigned long long like_from = E == kWave ? ~0ull : (1ull << E) - 1ull, like_to = like_from;
+    for (int bit = 0; bit < 32 && __ballot(((from | to) >> bit) != 0u) != 0ull; ++bit) {
+        const unsigned long long set = __ballot(((from >> bit) & 1u) != 0u);
+        like_from &= ((from >> bit) & 1u) != 0u ? set : ~set;
+        like_to &= ((to >> bit) & 1u) != 0u ? set : ~set;
+    }
+    source[lane] = static_cast<unsigned char>(like_from != 0ull ? __builtin_ctzll(like_from) : kWave + 1);
+    target[lane] = static_cast<unsigned char>(like_to != 0ull ? __builtin_ctzll(like_to) : kWave);
 }
 
-// Lane p of a wavefront needs sum_i counts[i][p] over the source experts i whose part equals its own.
-// The set of these i is built with one pair of ballots per bit of the part numbers (three bits for eight
-// parts) and then walked: E/G steps per candidate instead of E conditional ones, each a conflict-free LDS read
-// (the bank is a function of p alone).  When the counts of the pair add up to less than 2^31 - any trace
-// below two billion tokens - table and sums are 32 bits wide.  4096 maps of 24 layers x 64 experts on 8
-// parts: 222 us with the E-step walk, 27 now; the maps (25 MB) are read twice, once from the L2.
-__global__ __launch_bounds__(kScoreThreads) void placement_score_kernel(const int64_t* __restrict__ counts,
-                                                                         const int32_t* __restrict__ placements, int B, int L, int E,
-                                                                         int slice, int64_t* __restrict__ local)
+// Bytes that say where a target's part is the source's.  FEW (all parts below eight): ones; the source's part picks one of eight
+// bytes, and the targets' parts select from them, one byte permutation for four targets.  Otherwise (parts below 128): 128
+// minus the difference of the parts has bit 7 set only for equal parts - as a signed byte -128 instead of one.
+template <bool FEW>
+struct SamePart {
+    uint32_t lo, hi;
+    __device__ __forceinline__ SamePart(uint32_t word, int byte)
+    {
+        if constexpr (FEW) {  // (`word` holds eight times the parts)
+            const uint64_t lut = 1ull << ((word >> (8 * byte)) & 63u);
+            lo = static_cast<uint32_t>(lut), hi = static_cast<uint32_t>(lut >> 32);
+        } else {
+            lo = __builtin_amdgcn_perm(0u, word, 0x01010101u * static_cast<uint32_t>(byte));
+            hi = 0u;
+        }
+    }
+    __device__ __forceinline__ int operator()(uint32_t targets) const
+    {
+        if constexpr (FEW) return static_cast<int>(__builtin_amdgcn_perm(hi, lo, targets));
+        else return static_cast<int>((0x80808080u - (targets ^ lo)) & 0x80808080u);
+    }
+};
+
+// Digits of the scores of SETS x 16 candidates: sum over source and target experts of digit * [same part].  Lanes of a quarter
+// hold the source experts 16 * quarter + j, four of them in a word: the words [word, words).
+template <bool FEW, int SETS>
+__device__ __forceinline__ void contract(const unsigned char* digits, const unsigned char* from, const unsigned char* to, int word, int words, int chunks,
+                                         int lane, i32x4_t (&acc)[SETS])
 {
-    extern __shared__ unsigned long long cnt_lds[];  // [65][64]: the pair's counts, row = source expert; row 64 is zero (32- or 64-bit entries)
-    __shared__ unsigned long long pair_sum[kScoreWaves];
-    const int l = blockIdx.y;  // layer pair on y (at most 255), candidate slices on x
+    const int map_at = (lane & 15) * kMapBytes;
+    uint32_t target[SETS][16];
+#pragma unroll
+    for (int s = 0; s < SETS; ++s)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint4 x = *reinterpret_cast<const uint4*>(to + s * kSetMaps * kMapBytes + map_at + t * 16);
+            target[s][4 * t] = x.x, target[s][4 * t + 1] = x.y, target[s][4 * t + 2] = x.z, target[s][4 * t + 3] = x.w;
+        }
+    const unsigned char* row = digits + ((lane >> 4) * 16 + word * 4) * kSourceRow + (lane & (kDigits - 1)) * EXF_MAX_EXPERTS;
+#pragma unroll 1  // (each instruction is fetched once a pass otherwise)
+    for (; word < words; ++word, row += 4 * kSourceRow) {
+        uint32_t source[SETS];
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            source[s] = *reinterpret_cast<const uint32_t*>(from + s * kSetMaps * kMapBytes + map_at + (lane >> 4) * 16 + word * 4);
+            if (FEW) source[s] <<= 3;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (t >= chunks) break;
+                const i32x4_t a = *reinterpret_cast<const i32x4_t*>(row + j * kSourceRow + t * 16);
+#pragma unroll
+                for (int s = 0; s < SETS; ++s) {
+                    const SamePart<FEW> same(source[s], j);
+                    const i32x4_t b = {same(target[s][4 * t]), same(target[s][4 * t + 1]), same(target[s][4 * t + 2]), same(target[s][4 * t + 3])};
+                    acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, acc[s], 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+// score[map] = sum over (i, p) of counts[i][p] * [part_l(i) == part_{l+1}(p)]: a product of the pair's counts, cut into four
+// digits of seven bits (four rows of a matrix operand, the other twelve repeat them), with a zero-one matrix of 4096 rows
+// (i, p) and a column per map.  The counts' digits lie in LDS in operand order; a lane builds its part of the other operand in
+// registers: it holds the parts of 16 source experts (its quarter of the wavefront's) and of all target experts of one map.
+// Sums are exact in 32 bits (4096 * 127 * 128 < 2^31).  Counts of 2^28 and more take further rounds over their higher bits.
+// SPLIT wavefronts share SETS x 16 candidates and take a part of the source experts each (a small batch), or every wavefront
+// has its own.
+// 4096 maps of 24 layers x 64 experts: 13.3 us for 2, 4 or 8 parts (walking the matching source experts of every target: 58.6,
+// 36.8 and 26.7), 17.4 for 64, 6.8 with 8 experts: about half is the loads of the maps and the start of a workgroup.  The rest is
+// issue: per 16 candidates and pair 64 matrix instructions and 330 vector ones that build the operand.
+template <int SPLIT, int SETS, bool WIDE>
+__global__ __launch_bounds__(kScoreThreads, 3) void placement_score_kernel(const int64_t* __restrict__ counts,
+                                                                           const int32_t* __restrict__ placements, int B, int L, int E,
+                                                                           int passes, int64_t* __restrict__ local)
+{
+    constexpr int GROUPS = kScoreWaves / SPLIT, GROUP_MAPS = SETS * kSetMaps, MAPS = GROUPS * GROUP_MAPS;  // candidates of a pass
+    constexpr int OWN = GROUP_MAPS / SPLIT;  // rows a wavefront loads
+    __shared__ __attribute__((aligned(16))) unsigned char digits[EXF_MAX_EXPERTS * kSourceRow];
+    __shared__ __attribute__((aligned(16))) unsigned char maps[GROUPS][2][GROUP_MAPS * kMapBytes];  // parts at layers l and l + 1
+    __shared__ i32x4_t sums[SPLIT > 1 ? kScoreWaves : 1][SETS * 16];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int b_begin = static_cast<int>(blockIdx.x) * slice;
-    const int b_end = min(B, b_begin + slice);
-    // parts of a candidate's experts at layers l (lane = source expert) and l+1 (lane = target expert); the rows
-    // of the wavefront's next kScoreBatch candidates are requested before the current ones are scored (one
-    // candidate ahead left the launch waiting for memory: 28.7 us)
-    auto load_batch = [&](int cand, int (&from)[kScoreBatch], int (&to)[kScoreBatch]) {
-        const int e = min(lane, E - 1);
+    const int group = wave / SPLIT, piece = wave % SPLIT;
+    // the layer pairs of the same candidates run on one XCD, one after the other: a row two pairs share comes from its L2
+    const int xcd = static_cast<int>(blockIdx.x % 8u), rest = static_cast<int>(blockIdx.x / 8u);
+    const int l = rest % (L - 1);
+    const int64_t first = static_cast<int64_t>(rest / (L - 1) * 8 + xcd) * passes * MAPS;
+    if (first >= B) return;
+    const int64_t last = min(static_cast<int64_t>(B), first + static_cast<int64_t>(passes) * MAPS);
+    auto row_of = [&](int64_t b) { return placements + (static_cast<size_t>(min(b, static_cast<int64_t>(B) - 1)) * L + l) * E; };
+
+    MapRows<OWN, WIDE> rows[2];
+    auto load_maps = [&](int64_t pass) {
 #pragma unroll
-        for (int u = 0; u < kScoreBatch; ++u) {
-            const int c = min(cand + u * kScoreWaves, B - 1);
-            const int32_t* row = placements + (static_cast<size_t>(c) * L + l) * E;
-            from[u] = row[e];
-            to[u] = row[E + e];
+        for (int h = 0; h < 2; ++h) rows[h].load([&](int n) { return row_of(pass + group * GROUP_MAPS + piece * OWN + n) + h * E; }, E, lane);
+    };
+    load_maps(first);
+
+    // 28 bits of the pair's counts, from bit `shift`: four targets of a source expert at a time, a byte each in a word per
+    // digit.  Returns the bits above.
+    const int64_t* src = counts + static_cast<size_t>(l) * E * E;
+    constexpr int ITEMS = EXF_MAX_EXPERTS * EXF_MAX_EXPERTS / 4 / kScoreThreads;
+    auto load_counts = [&](uint64_t (&c)[ITEMS][4]) {
+#pragma unroll
+        for (int n = 0; n < ITEMS; ++n) {
+            const int item = static_cast<int>(threadIdx.x) + n * kScoreThreads, i = item / (EXF_MAX_EXPERTS / 4), p = item % (EXF_MAX_EXPERTS / 4) * 4;
+            if constexpr (WIDE) {
+                typedef __attribute__((__vector_size__(4 * sizeof(uint64_t)), __aligned__(16))) uint64_t u64x4_t;
+                const u64x4_t x = *reinterpret_cast<const u64x4_t*>(src + min(i, E - 1) * E + min(p, E - 4));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[n][q] = x[q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[n][q] = static_cast<uint64_t>(src[min(i, E - 1) * E + min(p + q, E - 1)]);
+            }
         }
     };
-    int cur_from[kScoreBatch], cur_to[kScoreBatch];
-    load_batch(b_begin + wave, cur_from, cur_to);
-
-    // counts of the pair: a wavefront takes every eighth row, all rows requested at once
-    constexpr int PER = EXF_MAX_EXPERTS / kScoreWaves;
-    const int64_t* src = counts + static_cast<size_t>(l) * E * E;
-    int64_t c[PER];
+    auto cut_counts = [&](const uint64_t (&c)[ITEMS][4], int shift) {
+        uint64_t above = 0;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) c[u] = src[min(wave + u * kScoreWaves, E - 1) * E + min(lane, E - 1)];
-    bool small = true;
-    unsigned long long sum = 0;
+        for (int n = 0; n < ITEMS; ++n) {
+            const int item = static_cast<int>(threadIdx.x) + n * kScoreThreads, i = item / (EXF_MAX_EXPERTS / 4), p = item % (EXF_MAX_EXPERTS / 4) * 4;
+            uint32_t v[4];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        if (wave + u * kScoreWaves >= E || lane >= E) c[u] = 0;
-        small = small && static_cast<unsigned long long>(c[u]) < (1ull << 32);
-        sum += static_cast<unsigned long long>(c[u]) & 0xffffffffull;  // at most 4096 terms below 2^32: no wrap
-    }
-    sum = wave_sum(sum);
-    if (__ballot(!small) != 0ull) sum = ~0ull >> 8;  // (eight such values do not wrap either)
-    if (lane == 0) pair_sum[wave] = sum;
-    __syncthreads();
-    sum = 0;
-#pragma unroll
-    for (int w = 0; w < kScoreWaves; ++w) sum += pair_sum[w];
-    const bool narrow = __builtin_amdgcn_readfirstlane(sum < (1ull << 31) ? 1 : 0) != 0;
-    uint32_t* cnt32 = reinterpret_cast<uint32_t*>(cnt_lds);
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int at = (wave + u * kScoreWaves) * kScoreStride + lane;
-        if (narrow) cnt32[at] = static_cast<uint32_t>(c[u]);
-        else cnt_lds[at] = static_cast<unsigned long long>(c[u]);
-    }
-    if (threadIdx.x < kWave) {
-        if (narrow) cnt32[kWave * kScoreStride + threadIdx.x] = 0u;
-        else cnt_lds[kWave * kScoreStride + threadIdx.x] = 0ull;
-    }
-    __syncthreads();
-
-    const unsigned long long experts = E == kWave ? ~0ull : (1ull << E) - 1ull;
-    for (int b0 = b_begin + wave; b0 < b_end; b0 += kScoreBatch * kScoreWaves) {
-        int nxt_from[kScoreBatch], nxt_to[kScoreBatch];
-        load_batch(b0 + kScoreBatch * kScoreWaves, nxt_from, nxt_to);
-#pragma unroll
-        for (int u = 0; u < kScoreBatch; ++u) {
-            const int b = b0 + u * kScoreWaves;
-            if (b >= b_end) break;
-            const unsigned from = static_cast<unsigned>(cur_from[u]), to = static_cast<unsigned>(cur_to[u]);
-            unsigned long long m = lane < E ? experts : 0ull;
-            for (int bit = 0; bit < 32 && __ballot(((from | to) >> bit) != 0u) != 0ull; ++bit) {
-                const unsigned long long set = __ballot(((from >> bit) & 1u) != 0u);
-                m &= ((to >> bit) & 1u) != 0u ? set : ~set;
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t x = i < E && p + q < E ? c[n][q] >> shift : 0ull;
+                above |= x >> kCountBits;
+                v[q] = static_cast<uint32_t>(x);
             }
-            if (narrow) {
-                const int acc = wave_inclusive_scan(static_cast<int>(add_matching_rows<uint32_t>(cnt32, m, lane)));
-                if (lane == kWave - 1) local[static_cast<size_t>(b) * (L - 1) + l] = acc;
-            } else {
-                const unsigned long long acc = wave_sum(add_matching_rows<unsigned long long>(cnt_lds, m, lane));
-                if (lane == 0) local[static_cast<size_t>(b) * (L - 1) + l] = static_cast<int64_t>(acc);
+#pragma unroll
+            for (int d = 0; d < kDigits; ++d) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) word |= ((v[q] >> (kDigitBits * d)) & ((1u << kDigitBits) - 1u)) << (8 * q);
+                *reinterpret_cast<uint32_t*>(digits + i * kSourceRow + d * EXF_MAX_EXPERTS + p) = word;
             }
         }
+        return __syncthreads_or(above != 0ull ? 1 : 0) != 0;
+    };
+    const int chunks = (E + 15) / 16, words = min(4, (E + 3) / 4);
+    uint64_t first_counts[ITEMS][4];
+    load_counts(first_counts);
+    unsigned char *from = maps[group][0], *to = maps[group][1];
+    auto store_maps = [&](int64_t pass) {
+        const uint32_t any = rows[0].store(from + piece * OWN * kMapBytes, lane) | rows[1].store(to + piece * OWN * kMapBytes, lane);
+        if (__ballot(any >= 128u) != 0ull) {
+            __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses are done in order)
+            for (int n = piece * OWN; n < piece * OWN + OWN; ++n) relabel(row_of(pass + group * GROUP_MAPS + n), E, lane, from + n * kMapBytes, to + n * kMapBytes);
+        }
+        return any;
+    };
+    uint32_t any = store_maps(first);
+    const bool more = cut_counts(first_counts, 0);  // counts of 2^28 or more
+
+    for (int64_t pass = first; pass < last; pass += MAPS) {
+        const int64_t b0 = pass + group * GROUP_MAPS;
+        const int here = static_cast<int>(max(static_cast<int64_t>(0), min(last - b0, static_cast<int64_t>(GROUP_MAPS))));
+        uint64_t score[SETS];
 #pragma unroll
-        for (int u = 0; u < kScoreBatch; ++u) {
-            cur_from[u] = nxt_from[u];
-            cur_to[u] = nxt_to[u];
+        for (int s = 0; s < SETS; ++s) score[s] = 0;
+        bool few = true;
+        for (int shift = 0; shift == 0 || (more && shift < 64); shift += kCountBits) {
+            if (more && (shift > 0 || pass > first)) {  // (the same in all wavefronts)
+                uint64_t c[ITEMS][4];
+                load_counts(c);
+                __syncthreads();  // (others may still read the digits)
+                cut_counts(c, shift);
+            } else if (SPLIT > 1) {
+                __syncthreads();
+            }
+            if (shift == 0) {
+                __builtin_amdgcn_wave_barrier();
+                if constexpr (SPLIT == 1) {
+                    few = __ballot(any >= 8u) == 0ull;
+                } else {  // all parts of the group's maps, not only of the rows loaded here
+                    uint32_t seen = 0;
+                    for (int n = lane; n < 2 * GROUP_MAPS * kMapBytes / 16; n += kWave) {
+                        const uint4 x = *reinterpret_cast<const uint4*>(from + n * 16);
+                        seen |= (x.x | x.y) | (x.z | x.w);
+                    }
+                    few = __ballot((seen & 0xf8f8f8f8u) != 0u) == 0ull;
+                }
+            }
+            i32x4_t acc[SETS];
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) acc[s] = i32x4_t{0, 0, 0, 0};
+            if (here > 0) {
+                const int w0 = SPLIT == 1 ? 0 : piece * (4 / SPLIT), w1 = SPLIT == 1 ? words : min(words, w0 + 4 / SPLIT);
+                if (few) contract<true, SETS>(digits, from, to, w0, w1, chunks, lane, acc);
+                else contract<false, SETS>(digits, from, to, w0, w1, chunks, lane, acc);
+            }
+            if constexpr (SPLIT > 1) {
+                if (lane < 16)
+#pragma unroll
+                    for (int s = 0; s < SETS; ++s) sums[wave][s * 16 + lane] = acc[s];
+                __syncthreads();
+                if (piece == 0 && lane < 16)
+#pragma unroll
+                    for (int w = 1; w < SPLIT; ++w)
+#pragma unroll
+                        for (int s = 0; s < SETS; ++s) acc[s] += sums[wave + w][s * 16 + lane];
+            }
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                int64_t sum = 0;
+#pragma unroll
+                for (int d = 0; d < kDigits; ++d) sum += static_cast<int64_t>(acc[s][d]) << (kDigitBits * d);
+                score[s] += static_cast<uint64_t>(few ? sum : -sum >> 7) << shift;
+            }
+        }
+        if (lane < 16 && piece == 0) {
+#pragma unroll
+            for (int s = 0; s < SETS; ++s)
+                if (s * 16 + lane < here) local[static_cast<size_t>(b0 + s * 16 + lane) * (L - 1) + l] = static_cast<int64_t>(score[s]);
+        }
+        if (SPLIT > 1 && pass + MAPS < last) __syncthreads();
+        if (pass + MAPS < last) {
+            load_maps(pass + MAPS);
+            any = store_maps(pass + MAPS);
         }
     }
+}
+
+template <int SPLIT, int SETS>
+static void launch_scores(const int64_t* counts, const int32_t* placements, int B, int L, int E, int64_t* local, hipStream_t stream)
+{
+    constexpr int MAPS = kScoreWaves / SPLIT * SETS * kSetMaps;
+    const int64_t all = (static_cast<int64_t>(B) + MAPS - 1) / MAPS;
+    const int passes = static_cast<int>((all * (L - 1) + kScoreWorkgroups - 1) / kScoreWorkgroups);  // of a workgroup
+    const int64_t groups = (all + passes - 1) / passes;
+    const dim3 grid(static_cast<unsigned>((groups + 7) / 8 * 8 * (L - 1)));
+    if (E % 4 == 0 && aligned16(placements) && aligned16(counts))
+        hipLaunchKernelGGL((placement_score_kernel<SPLIT, SETS, true>), grid, dim3(kScoreThreads), 0, stream, counts, placements, B, L, E, passes, local);
+    else
+        hipLaunchKernelGGL((placement_score_kernel<SPLIT, SETS, false>), grid, dim3(kScoreThreads), 0, stream, counts, placements, B, L, E, passes, local);
 }
 
 // ------------------------------------------------------------------------------------ host solver
@@ -391,16 +556,11 @@ extern "C" int placement_locality_from_counts(const int64_t* counts, const int32
     EXF_REQUIRE_PTR(counts);
     EXF_REQUIRE_PTR(placements);
     EXF_REQUIRE_PTR(local);
-    // candidates per workgroup: one round of kScoreWorkgroups workgroups (a small batch is spread over the
-    // chip), at most kScoreMaxPerWave per wavefront
-    const int64_t slots = static_cast<int64_t>(kScoreWorkgroups / (L - 1)) * kScoreWaves;  // (L - 1 <= 255)
-    int64_t per_wave = (B + slots - 1) / slots;
-    if (per_wave > kScoreMaxPerWave) per_wave = kScoreMaxPerWave;
-    const int slice = static_cast<int>(per_wave) * kScoreWaves;
-    const dim3 grid(static_cast<unsigned>((B + slice - 1) / slice), static_cast<unsigned>(L - 1));
-    const size_t lds = static_cast<size_t>(kWave + 1) * kScoreStride * sizeof(long long);
-    hipLaunchKernelGGL(placement_score_kernel, grid, dim3(kScoreThreads), lds, static_cast<hipStream_t>(stream), counts, placements, B, L,
-                       E, slice, local);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // A batch that one round of workgroups of 16 candidates covers is split over the wavefronts, otherwise every wavefront takes 32
+    // (64 candidates of 24 x 64: 3.9 us split, 6.2 not; 1024: 8.1 and 7.3)
+    if ((static_cast<int64_t>(B) + kSetMaps - 1) / kSetMaps * (L - 1) <= kScoreWorkgroups) launch_scores<4, 1>(counts, placements, B, L, E, local, s);
+    else launch_scores<1, 2>(counts, placements, B, L, E, local, s);
     return check_launch("placement_locality_from_counts");
 }
 

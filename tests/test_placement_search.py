@@ -111,6 +111,30 @@ def test_gpu_scores_candidate_batches_exactly(L, E, G, Bn):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("L,E,Bn,low,high,bits", [
+    (3, 1, 17, 0, 1, 20), (2, 3, 16, 0, 8, 28), (4, 4, 15, 0, 9, 20), (3, 16, 33, 0, 8, 29), (3, 17, 31, 0, 128, 28), (2, 63, 129, 0, 64, 20),
+    (3, 64, 40, -2, 129, 20),               # parts that do not fit seven bits
+    (2, 64, 20, 1 << 20, (1 << 20) + 9, 30),
+    (24, 64, 561, 0, 8, 20), (24, 20, 561, 0, 4, 62),   # one wavefront for 32 candidates; counts of more than 28 bits
+    (256, 4, 900, 0, 4, 29), (256, 5, 900, 0, 4, 20),   # several passes of a workgroup
+])
+def test_gpu_scores_at_the_edges_of_the_operand(L, E, Bn, low, high, bits):
+    print(f"[case] placement scores L={L} E={E} B={Bn} parts {low}..{high - 1} counts {bits} bits", flush=True)
+    g = syn.rng(730 + L + E + Bn)
+    counts = g.integers(0, 1 << bits, size=(L - 1, E, E)).astype(np.int64)
+    counts[0, 0, E - 1] = (1 << bits) - 1
+    pls = g.integers(low, high, size=(Bn, L, E)).astype(np.int32)
+    got = B.placement_locality_from_counts(torch.from_numpy(counts).to("cuda:0"), torch.from_numpy(pls).to("cuda:0")).cpu().numpy()
+    same = pls[:, :-1, :, None] == pls[:, 1:, None, :]                       # [B,L-1,source,target]
+    step = max(1, Bn // 40)
+    for b in sorted(set(range(0, Bn, step)) | {15, 16, 31, 32, 127, 128, Bn - 1}):
+        if b < Bn:
+            np.testing.assert_array_equal(got[b], oracle.placement_locality_from_counts(counts, pls[b]))
+    all_maps = np.stack([(counts[l] * same[:, l]).sum(axis=(1, 2)) for l in range(L - 1)], axis=1)
+    np.testing.assert_array_equal(got, all_maps)
+
+
+@pytest.mark.gpu
 def test_gpu_search_pipeline_on_a_trace():
     """trace -> affinity_histogram (GPU) -> host solver -> scores of {found, default, random} from
     the counts (GPU batch) agree with placement_locality on the trace (GPU) and with the oracle."""
