@@ -150,6 +150,23 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     return v;
 }
 
+// Asks for all 64-byte lines of a kernel's arguments (BYTES of them) at once.  They lie in host memory, and the first access to a
+// line takes half a microsecond: left to the compiler, which loads an argument where it is used first, a kernel of a few
+// microseconds pays that once per line.
+template <int BYTES>
+__device__ __forceinline__ void touch_arguments()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto* a = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int LINES = (BYTES + 63) / 64;
+    uint32_t v[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) v[i] = a[i * 16];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(v[i]));
+#endif
+}
+
 // Value of `v` in lane `src`, where src is the same in every lane (read on the scalar path).
 __device__ __forceinline__ int wave_read_lane(int v, int src)
 {

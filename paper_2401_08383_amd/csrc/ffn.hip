@@ -167,14 +167,6 @@ __device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offse
     return p;
 }
 
-// Quotient of two wavefront-uniform non-negative numbers; the divisors are powers of two in the common shapes
-// (column tiles per row), and a division by a run-time value costs some twenty dependent instructions.
-__device__ __forceinline__ unsigned uniform_udiv(unsigned a, unsigned d)
-{
-    if ((d & (d - 1u)) == 0u) return a >> (31 - __builtin_clz(d | 1u));  // d = 2^k (d = 0 never occurs)
-    return a / d;
-}
-
 // Size of XCD `xcd`'s share of n items of one kind; `begin` receives its first item.  An XCD runs the workgroups whose
 // id is its own modulo 8, so the map workgroup -> item decides how much work it gets: of the n items of a kind (big,
 // small) every XCD takes a contiguous share of n/8, and the n%8 left over go one each to consecutive XCDs, continuing
@@ -1004,6 +996,13 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
             first.topk_idx = routing->topk_idx, first.expert_map = routing->expert_map, first.E = routing->E;
             first.src_of_sorted = routing->src_of_sorted, first.sorted_of_src = routing->sorted_of_src;
             first.expert_counts = routing->expert_counts, first.expert_offsets = routing->expert_offsets;
+            first.w_gate = routing->w_gate, first.renormalize = routing->renormalize;
+            first.k = second.k = k;
+            first.gate_idx = routing->gate_idx, first.gate_w = routing->gate_w;
+            if (dt == EXF_BF16 && A <= kFewAssignments) {
+                second.topk_idx = routing->topk_idx, second.expert_map = routing->expert_map, second.E = routing->E;
+                second.second = true;
+            }
         }
         first.K = d, first.N = f, first.epi = epi;
         second.act = hidden, second.weight = w2, second.bias = b2, second.out = second_out;

@@ -9,6 +9,14 @@ namespace exf {
 
 constexpr int kXcdCount = 8;
 
+// Quotient of two wavefront-uniform non-negative numbers; the divisors are powers of two in the common shapes
+// (column tiles per row), and a division by a run-time value costs some twenty dependent instructions.
+__device__ __forceinline__ unsigned uniform_udiv(unsigned a, unsigned d)
+{
+    if ((d & (d - 1u)) == 0u) return a >> (31 - __builtin_clz(d | 1u));  // d = 2^k (d = 0 never occurs)
+    return a / d;
+}
+
 // ---------------------------------------------------------------------------- activations
 __device__ __forceinline__ float gelu_erf_exact(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752440f)); }
 __device__ __forceinline__ float gelu_tanh_exact(float z)
@@ -62,7 +70,17 @@ struct StreamGemm {
     const int32_t* expert_map;  // [E] or null
     int E;
     int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
+    // At most kFewAssignments: both contractions sort, every wavefront for itself, `second` the one that
+    // reads rows in sorted order.  With `w_gate` the first one is the gate of act [T,K] as well (workgroup 0 stores gate_idx and gate_w,
+    // and the others compute it, too, where topk_idx is gate_idx).
+    bool second;
+    int k;
+    const void* w_gate;
+    int renormalize;
+    int32_t* gate_idx;
+    float* gate_w;
 };
+constexpr int kFewAssignments = 64;
 constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for itself
 // Is the path taken for A rows of `dt` spread over E_local experts?
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
@@ -74,11 +92,17 @@ struct FfnRouting {
     const int32_t *topk_idx, *expert_map;
     int E;
     int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
+    const void* w_gate;  // the first contraction is the gate as well (null: it has run); only where gate_joins_layer() says so
+    int renormalize;
+    int32_t* gate_idx;
+    float* gate_w;
 };
 inline bool routed_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
     return A > 0 && A <= kInlineDispatchMax && stream_path_fits(A, d, f, E_local, dt);
 }
+// Is a layer on the routed path gated by its first contraction?
+bool gate_joins_layer(int64_t T, int k, int d, int E, int dt);
 int ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
                      int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream);
 

@@ -4,7 +4,7 @@
 // HBM and the matrix cores balance at about 270).  What counts is how many bytes are in flight on every compute
 // unit all the time, not operand reuse:
 //   - 256 persistent workgroups (one per compute unit), each with a contiguous range of the work items (expert, row tile of
-//     at most 64 rows, block of 16 C columns), all ranges of about the same cost.  The blocks of one row tile are one continuous stream: the loads
+//     at most 64 rows, block of 8 to 64 columns), all ranges of about the same cost.  The blocks of one row tile are one continuous stream: the loads
 //     of the next block are in flight while the current one is summed and stored.
 //   - the W wavefronts of a workgroup deal the 128-byte pieces ("units") of the reduction among themselves
 //     (wavefront w takes units w, w + W, ..: neighbouring lines of a row are requested at the same time) and add
@@ -13,13 +13,17 @@
 //     per load.  Nobody else reads its slots, so no barrier is needed between units, only its own count of
 //     outstanding loads.  (Loading the operands straight into registers in the lane layout of the matrix cores makes
 //     every load touch 64 pieces of 16 bytes: 5.3 TB/s where this streams 6.4.)
-//   - the slot of a block's last unit is free until the block is stored: it carries the sums.
+//   - the slot of a block's last unit is free until the block is stored: it carries the sums (at most eight rows have a place of
+//     their own for them).
 //   - the weights are read once: loaded with the streaming hint they leave the L2 to the activations (64 experts of
 //     4096 x 16384, 256 tokens top-2, both contractions: 3.08 ms without, 2.66 with, 2.89 as 64-row tiles of ffn.hip).
 //   - row ids and gate weights travel through LDS as well, so that no load result is awaited through a register (the
 //     compiler would wait for every load in flight).
 // fp32 (the exact path, small layers): operands straight from global memory into registers, no LDS but for the sums.
 #include "ffn_common.hpp"
+#include "gate_tile.hpp"
+
+#include <type_traits>
 
 namespace exf {
 
@@ -120,6 +124,12 @@ __device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDisp
 struct ExpertTiles {
     int lo, hi, tiles, incl, total;
 };
+__device__ __forceinline__ void count_tiles(ExpertTiles& t, int tile_rows)
+{
+    t.tiles = (t.hi - t.lo + tile_rows - 1) / tile_rows;
+    t.incl = wave_inclusive_scan(t.tiles);
+    t.total = wave_read_lane(t.incl, kWave - 1);
+}
 __device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, const int32_t* offsets, int tile_rows)
 {
     ExpertTiles t;
@@ -130,34 +140,142 @@ __device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, const
         t.lo = min(max(offsets[lane], 0), p.max_rows);
         t.hi = min(max(offsets[lane + 1], t.lo), p.max_rows);
     }
-    t.tiles = (t.hi - t.lo + tile_rows - 1) / tile_rows;
-    t.incl = wave_inclusive_scan(t.tiles);
-    t.total = wave_read_lane(t.incl, kWave - 1);
+    count_tiles(t, tile_rows);
+    return t;
+}
+
+// Sorting at most kFewAssignments: lane = assignment, every wavefront for itself, no barrier and no memory but the ids and the
+// expert map, which are asked for together (with the output rows' gate weights in the second contraction).  sorted[s]: token at
+// position s; in the second contraction of a top-1 layer the gate weight of position s at sorted[64 + s].  Neither contraction then
+// waits for maps in memory, which themselves wait for offsets.
+// The gate of at most 16 tokens joins in (first contraction, p.w_gate): each workgroup needs its result anyway, and computing it in all
+// of them takes 1.9 us where its own launch, of one workgroup, took 3.1 and the gap behind it.  These kernels are chains of
+// instructions and memory round trips (a wavefront issues one instruction in about five cycles), so what a launch of at most
+// eight rows does not need is compiled out (EIGHT).  One token, 8 experts of 1024 x 4096: 15.2 us in three launches, 12.2 in
+// two; one GPU's 2 of 8 experts with the routing given 15.6 and 12.1; 16 tokens, 8 experts 32.1 and 29.7.
+template <int W, int LDS, bool EIGHT>
+__device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned char* smem, int* sorted, int tile_rows)
+{
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int A = p.max_rows;
+    const int at = min(lane, A - 1);
+    const bool gated = p.w_gate != nullptr && (blockIdx.x == 0 || p.topk_idx == p.gate_idx);  // (the same in all wavefronts)
+    const int local_of = p.expert_map != nullptr ? p.expert_map[min(lane, p.E - 1)] : lane;  // lane = expert
+    int id = 0;
+    if (p.w_gate == nullptr || p.topk_idx != p.gate_idx) id = p.topk_idx[at];
+    float scale = 1.0f;
+    if (p.second && p.out_row != nullptr) scale = p.out_scale[at];  // (k = 1: the assignment is the token)
+    if (gated) {
+        const int T = A / p.k;
+        Route r;
+        auto gate = [&](auto nt, auto sums) {
+            constexpr int NT = decltype(nt)::value, P = decltype(sums)::value;
+            r = gate_few<NT, P, W, LDS>(p.act, p.w_gate, T, p.K, p.E, p.k, p.renormalize, smem);
+        };
+        const int nt = (p.E + 15) / 16;
+        const bool eight = gate_sums(nt, p.K) == 8;
+        typedef std::integral_constant<int, 4> Four;
+        typedef std::integral_constant<int, 8> Eight;
+        if (nt == 1 && eight) gate(std::integral_constant<int, 1>(), Eight());
+        else if (nt == 1) gate(std::integral_constant<int, 1>(), Four());
+        else if (nt == 2 && eight) gate(std::integral_constant<int, 2>(), Eight());
+        else if (nt == 2) gate(std::integral_constant<int, 2>(), Four());
+        else if (nt == 3) gate(std::integral_constant<int, 3>(), Four());
+        else gate(std::integral_constant<int, 4>(), Four());
+        const int first = __shfl(r.i0, p.k == 1 ? lane : lane >> 1, kWave), second = __shfl(r.i1, lane >> 1, kWave);
+        const int mine = p.k == 1 || (lane & 1) == 0 ? first : second;
+        if (p.topk_idx == p.gate_idx) id = mine;
+        if (blockIdx.x == 0 && wave == 0 && lane < T) store_route(r, lane, p.k, p.gate_idx, p.gate_w);
+    }
+    const bool ok = lane < A && id >= 0 && id < p.E;
+    int e = __shfl(local_of, ok ? id : 0, kWave);
+    e = ok && e >= 0 && e < p.E_local ? e : -1;
+    int pos = 0, below = 0, count = 0;  // (the last two: lane = expert)
+    if (A <= 4) {
+        for (int b = 0; b < A; ++b) {
+            const int other = wave_read_lane(e, b);
+            if (other < 0) continue;
+            pos += other < e || (other == e && b < lane) ? 1 : 0;
+            below += other < lane ? 1 : 0;
+            count += other == lane ? 1 : 0;
+        }
+    } else {
+        // assignments of this one's expert; its first one tells the expert's lane how many (`sorted` is scratch so far)
+        const unsigned long long like = same_expert_lanes(e, p.E_local);
+        sorted[lane] = 0;
+        __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses are done in order)
+        const int rank = static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(like >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(like), 0u)));
+        if (e >= 0 && rank == 0) sorted[e] = __popcll(like);
+        __builtin_amdgcn_wave_barrier();
+        count = sorted[lane];
+        below = wave_inclusive_scan(count) - count;
+        pos = __shfl(below, max(e, 0), kWave) + rank;
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (e >= 0) {
+        sorted[pos] = p.k == 2 ? lane >> 1 : lane;
+        reinterpret_cast<float*>(sorted)[kWave + pos] = scale;
+    }
+    if (!p.second && blockIdx.x == 0 && wave == 0) {
+        if (lane < p.E_local) {
+            p.expert_counts[lane] = count;
+            p.expert_offsets[lane] = below;
+        }
+        if (lane == p.E_local - 1) p.expert_offsets[p.E_local] = below + count;
+        if (lane < A) p.sorted_of_src[lane] = e >= 0 ? pos : -1;
+        if (e >= 0) p.src_of_sorted[pos] = lane;
+    }
+    if (p.unrouted != nullptr) {  // output rows nobody writes, dealt to the workgroups
+        unsigned long long todo = __ballot(lane < A && e < 0);
+        for (int n = 0; todo != 0ull; ++n, todo &= todo - 1ull) {
+            if (n != static_cast<int>(blockIdx.x)) continue;
+            uint4* row = reinterpret_cast<uint4*>(p.out) + static_cast<size_t>(__builtin_ctzll(todo)) * (p.N / 8);
+            for (int c = threadIdx.x; c < p.N / 8; c += W * kWave) row[c] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+    ExpertTiles t;
+    t.lo = below;
+    t.hi = below + count;
+    if constexpr (EIGHT) {  // one tile an expert
+        const unsigned long long some = __ballot(count > 0);
+        t.tiles = count > 0 ? 1 : 0;
+        t.incl = t.tiles + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(some >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(some), 0u)));
+        t.total = __popcll(some);
+    } else {
+        count_tiles(t, tile_rows);
+    }
     return t;
 }
 
 // ---------------------------------------------------------------------------- bf16
 constexpr int kStreamGrid = 256;     // workgroups: one per compute unit
 constexpr int kStreamIdBytes = 512;  // per wavefront: row ids of a tile, gate weights of a tile
-// A row tile has at most 8 * stream_max_ar(C) rows (narrow blocks have shorter tiles: the activations would fill the ring).
-__host__ __device__ constexpr int stream_max_ar(int C) { return C == 4 ? 8 : 4; }
+// C8: columns of a block / 8.  A row tile has at most 8 * stream_max_ar(C8) rows (narrow blocks have shorter tiles: the
+// activations would fill the ring).
+__host__ __device__ constexpr int stream_max_ar(int C8) { return C8 == 8 ? 8 : 4; }
 
-// Ring slots of a wavefront for row tiles of 8 AR rows: what fits 144 KiB, at most four.
-__host__ __device__ constexpr int stream_slot_bytes(int C, int AR) { return (16 * C + 8 * AR) * 128; }
-__host__ __device__ constexpr int stream_ring(int C, int AR, int W)
+// Ring slots of a wavefront for row tiles of 8 AR rows: what fits 144 KiB, at most eight (with four the second contraction of a single
+// row, 8 units a wavefront, was two round trips to memory).
+__host__ __device__ constexpr int stream_slot_bytes(int C8, int AR) { return (8 * C8 + 8 * AR) * 128; }
+__host__ __device__ constexpr int stream_ring(int C8, int AR, int W)
 {
-    const int fit = 144 * 1024 / (W * stream_slot_bytes(C, AR));
-    return fit > 4 ? 4 : fit;
+    const int fit = 144 * 1024 / (W * stream_slot_bytes(C8, AR));
+    return fit > 8 ? 8 : fit;
 }
-__host__ __device__ constexpr int stream_ring_bytes(int C, int W)
+__host__ __device__ constexpr int stream_ring_bytes(int C8, int W)
 {
     int most = 0;
-    for (int ar = 1; ar <= stream_max_ar(C); ar *= 2) {
-        const int b = W * stream_ring(C, ar, W) * stream_slot_bytes(C, ar);
+    for (int ar = 1; ar <= stream_max_ar(C8); ar *= 2) {
+        const int b = W * stream_ring(C8, ar, W) * stream_slot_bytes(C8, ar);
         most = b > most ? b : most;
     }
     return most;
 }
+
+// Sums of a block of eight rows of kRowsEight: behind the row ids.
+__host__ __device__ constexpr int stream_sums_at(int C8, int W) { return stream_ring_bytes(C8, W) + W * kStreamIdBytes; }
+__host__ __device__ constexpr int stream_sums_bytes(int C8) { return 8 * 8 * C8 * 4; }
 
 // What a block of a row tile of 8 AR rows costs, in tenths of its weights: the activations are read again by every block and weigh
 // more the more of the ring they take.  Dealing ranges of equal cost instead of equal numbers of blocks keeps the tall tiles of
@@ -165,29 +283,33 @@ __host__ __device__ constexpr int stream_ring_bytes(int C, int W)
 // 1/rank^1.1: 290 rows, 57 experts of 1024 x 4096 180 us before, 144 now; 400 rows, 32 of 2048 x 8192 489 and 379; 655
 // rows, 29 of 2560 x 10240 755 and 593 (64-row tiles of ffn.hip: 164, 423, 557); evenly spread rows as before or up to 6 %
 // less.  Coefficients of 3 and 5 instead of 4 give 601 and 586 there, but 290 instead of 284 with 5 for 128 rows, 8 of 4096 x 14336.
-__host__ __device__ constexpr uint32_t stream_cost(int C, int AR) { return static_cast<uint32_t>((10 * C + 4 * AR) / C); }
+__host__ __device__ constexpr uint32_t stream_cost(int C8, int AR) { return static_cast<uint32_t>((10 * C8 + 8 * AR) / C8); }
 
 // Waits until at most `units` units of LPU loads each are outstanding.
 template <int LPU, int R>
 __device__ __forceinline__ void wait_units(int units)
 {
     static_assert((R - 1) * LPU < 64, "outstanding loads must fit the vmcnt counter");
-    if (R >= 4 && units >= 3) wait_vmcnt<(R >= 4 ? 3 : 0) * LPU>();
-    else if (R >= 3 && units >= 2) wait_vmcnt<(R >= 3 ? 2 : 0) * LPU>();
-    else if (R >= 2 && units >= 1) wait_vmcnt<(R >= 2 ? 1 : 0) * LPU>();
-    else wait_vmcnt<0>();
+    if constexpr (R <= 1) {
+        wait_vmcnt<0>();
+    } else {
+        if (units >= R - 1) wait_vmcnt<(R - 1) * LPU>();
+        else wait_units<LPU, R - 1>(units);
+    }
 }
 
 // Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
-template <int C, int AR, int W>
+template <int C8, int AR, int W, bool FEW_ROWS = false>
 __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int row_begin, int row_end, int block_begin, int block_end,
-                                               int rotate, const int* list, unsigned char* smem)
+                                               int rotate, const int* list, bool tokens, bool listed_out, unsigned char* smem)
 {
-    constexpr int M = (AR + 1) / 2;  // MFMA tiles along the rows
-    constexpr int R = stream_ring(C, AR, W);
-    constexpr int SLOT = stream_slot_bytes(C, AR);
-    constexpr int LW = 2 * C, LA = AR, LPU = LW + LA;  // loads of a unit: eight rows each
-    constexpr int COLS = 16 * C;
+    constexpr int C = (C8 + 1) / 2, M = (AR + 1) / 2;  // MFMA tiles along the columns and the rows (eight of either are read twice)
+    constexpr int R = stream_ring(C8, AR, W);
+    constexpr int SLOT = stream_slot_bytes(C8, AR);
+    constexpr int LW = C8, LA = AR, LPU = LW + LA;  // loads of a unit: eight rows each
+    constexpr int COLS = 8 * C8, QUADS = 2 * C8;     // columns of a block, and fours of them
+    constexpr int STEP = AR == 1 && C8 == 1 ? 4 : (AR == 1 && C8 == 2 ? 2 : 1);  // units read at once: a few rows wait for the LDS, unit by unit
+    static_assert(STEP < R, "loads go on while a step is read");
     static_assert(R >= 2, "a ring of one slot cannot overlap anything");
     static_assert(8 * AR * COLS * 4 <= SLOT, "a block's sums must fit the slot of its last unit");
     const int lane = lane_id();
@@ -195,18 +317,19 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     const uint32_t smem_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem));
     const uint32_t ring_addr = smem_addr + wave * (R * SLOT);
     unsigned char* ring = smem + wave * (R * SLOT);
-    constexpr int kIds = stream_ring_bytes(C, W);
+    constexpr int kIds = stream_ring_bytes(C8, W);
     const uint32_t ids_addr = smem_addr + kIds + wave * kStreamIdBytes;
-    const int* ids = reinterpret_cast<const int*>(smem + kIds + wave * kStreamIdBytes);
+    // output rows and their gate weights: of the tile, or of all sorted rows (listed_out)
+    const int* ids = reinterpret_cast<const int*>(smem + kIds + wave * kStreamIdBytes) + (listed_out ? row_begin : 0);
     const float* gate = reinterpret_cast<const float*>(ids + kWave);
     const uint32_t row_bytes = static_cast<uint32_t>(p.K) * 2u;
 
-    const int units = p.K / 64;
-    const int cnt = wave < units ? (units - wave + W - 1) / W : 0;  // units of a block this wavefront sums
+    const int units = static_cast<int>(static_cast<unsigned>(p.K) / 64u);
+    const int cnt = static_cast<int>(static_cast<unsigned>(max(units - wave + W - 1, 0)) / W);  // units of a block this wavefront sums
     const int total = (block_end - block_begin) * cnt;
-    const int start = cnt > 0 ? rotate % cnt : 0;  // the unit a block begins with (see stream_gemm_kernel)
+    const int start = cnt == 0 ? 0 : ((cnt & (cnt - 1)) == 0 ? rotate & (cnt - 1) : rotate % cnt);  // the unit a block begins with (see stream_gemm_kernel)
 
-    // LDS row r of a slot (16 C weight rows, then 8 AR activation rows) holds 16-byte piece c at position c ^ ((r / 2) % 8)
+    // LDS row r of a slot (8 C8 weight rows, then 8 AR activation rows) holds 16-byte piece c at position c ^ ((r / 2) % 8)
     const int r8 = lane >> 3, c8 = lane & 7;
     const uint32_t off_even = static_cast<uint32_t>(r8) * row_bytes + ((c8 ^ (r8 >> 1)) * 16);      // rows 8 i + r8, i even
     const uint32_t off_odd = static_cast<uint32_t>(r8) * row_bytes + ((c8 ^ (r8 >> 1) ^ 4) * 16);   //   i odd
@@ -231,9 +354,22 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     };
 
     // ---- start: row ids, the weights of the first units, then (ids known) their activations -------------------
+    const int32_t* id_list = list != nullptr || listed_out ? nullptr : (p.a_row != nullptr ? p.a_row : p.out_row);
+    const bool known = id_list == nullptr;  // no row ids to wait for: units are asked for whole, as later on
+    auto place_rows = [&]() {
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const int r = i * 8 + r8;
+            int row = min(row_begin + r, row_end - 1);  // rows past the end repeat the last one
+            if (list != nullptr) row = list[row];
+            else if (p.a_row != nullptr) row = ids[r];
+            if (!tokens && p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
+            off_a[i] = static_cast<uint32_t>(row) * row_bytes + ((c8 ^ ((r >> 1) & 7)) * 16);
+        }
+    };
+    if (known) place_rows();
     const int first = min(total, R);
-    const int32_t* id_list = list != nullptr ? nullptr : (p.a_row != nullptr ? p.a_row : p.out_row);
-    if (id_list != nullptr)
+    if (!known)
         lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(id_list)), static_cast<uint32_t>(min(row_begin + lane, row_end - 1)) * 4u, ids_addr);
     int next_u = 0, next_slot = 0;  // the unit of the block at w_block, and the slot, the next load goes to
     int q_issued = 0;
@@ -243,6 +379,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
         u_of[s] = 0;
         if (s < first) {
             issue_w(s, next_u);
+            if (known) issue_a(s, next_u);
             u_of[s] = next_u;
             next_u += 1;
             q_issued += 1;
@@ -253,36 +390,26 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
         }
     }
     next_slot = first == R ? 0 : first;
-    if (id_list != nullptr) {  // loads land in order: the ids are there once only the weights are outstanding
-        if (first >= 4) wait_vmcnt<(R >= 4 ? 4 : 0) * LW>();
-        else if (first == 3) wait_vmcnt<(R >= 3 ? 3 : 0) * LW>();
-        else if (first == 2) wait_vmcnt<2 * LW>();
-        else if (first == 1) wait_vmcnt<LW>();
-        else wait_vmcnt<0>();
+    if (!known) {  // loads land in order: the ids are there once only the weights are outstanding
+        wait_units<LW, R + 1>(first);
     }
+    if (!known) place_rows();
+    if (p.out_row != nullptr && !listed_out) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
+    if (!known) {
 #pragma unroll
-    for (int i = 0; i < LA; ++i) {
-        const int r = i * 8 + r8;
-        int row = min(row_begin + r, row_end - 1);  // rows past the end repeat the last one
-        if (list != nullptr) row = list[row];
-        else if (p.a_row != nullptr) row = ids[r];
-        if (p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
-        off_a[i] = static_cast<uint32_t>(row) * row_bytes + ((c8 ^ ((r >> 1) & 7)) * 16);
+        for (int s = 0; s < R; ++s)
+            if (s < first) issue_a(s, u_of[s]);
+        wait_vmcnt<0>();
     }
-    if (p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
-#pragma unroll
-    for (int s = 0; s < R; ++s)
-        if (s < first) issue_a(s, u_of[s]);
-    wait_vmcnt<0>();
 
     // ---- stream -----------------------------------------------------------------------------------------------
     const int r16 = lane & 15, g = lane >> 4;
-    const int ra = AR == 1 ? r16 & 7 : r16;  // a tile of eight rows has no second half: read it twice
+    const int rw = C8 == 1 ? r16 & 7 : r16, ra = AR == 1 ? r16 & 7 : r16;  // eight rows have no second half: read it twice
     int frag[2], frag_a[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        frag[h] = r16 * 128 + (((4 * h + g) ^ (r16 >> 1)) * 16);
-        frag_a[h] = ra * 128 + (((4 * h + g) ^ (ra >> 1)) * 16);
+        frag[h] = rw * 128 + (((4 * h + g) ^ (rw >> 1)) * 16);
+        frag_a[h] = LW * 1024 + ra * 128 + (((4 * h + g) ^ (ra >> 1)) * 16);
     }
     auto refill = [&]() {
         if (q_issued < total) {
@@ -306,54 +433,69 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
         for (int c = 0; c < C; ++c)
 #pragma unroll
             for (int m = 0; m < M; ++m) acc[c][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        for (int u = 0; u < cnt; ++u) {
-            wait_units<LPU, R>(q_issued - q - 1);
-            const unsigned char* s = ring + slot * SLOT;
-            bf16x8_t fw[C][2], fa[M][2];
+        for (int u = 0; u < cnt; u += STEP) {
+            const int n = min(STEP, cnt - u);
+            wait_units<LPU, R>(q_issued - q - n);
+            bf16x8_t fw[STEP][C][2], fa[STEP][M][2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int i = 0; i < STEP; ++i) {
+                if (i > 0 && i >= n) break;
+                const unsigned char* s = ring + slot * SLOT;
 #pragma unroll
-                for (int c = 0; c < C; ++c) fw[c][h] = *reinterpret_cast<const bf16x8_t*>(s + c * 2048 + frag[h]);
+                for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                for (int m = 0; m < M; ++m) fa[m][h] = *reinterpret_cast<const bf16x8_t*>(s + (C + m) * 2048 + frag_a[h]);
+                    for (int c = 0; c < C; ++c) fw[i][c][h] = *reinterpret_cast<const bf16x8_t*>(s + c * 2048 + frag[h]);
+#pragma unroll
+                    for (int m = 0; m < M; ++m) fa[i][m][h] = *reinterpret_cast<const bf16x8_t*>(s + m * 2048 + frag_a[h]);
+                }
+                slot = slot + 1 == R ? 0 : slot + 1;
             }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read: it may be filled again
-            if (u + 1 < cnt) refill();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slots have been read: they may be filled again
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int i = 0; i < STEP; ++i)
+                if (FEW_ROWS ? i < n : u + i + 1 < cnt) refill();
 #pragma unroll
-                for (int c = 0; c < C; ++c)
+            for (int i = 0; i < STEP; ++i) {
+                if (i > 0 && i >= n) break;
 #pragma unroll
-                    for (int m = 0; m < M; ++m)
-                        acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[c][h], fa[m][h], acc[c][m], 0, 0, 0);
-            q += 1;
-            slot = slot + 1 == R ? 0 : slot + 1;
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+#pragma unroll
+                        for (int m = 0; m < M; ++m)
+                            acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i][c][h], fa[i][m][h], acc[c][m], 0, 0, 0);
+            }
+            q += n;
         }
-        // sums -> the slot of this block's last unit; float4 of row r, columns 4 j .. at position j ^ (r % 4C)
-        last_hi = (last_hi + cnt_hi) % R;
-        last_lo = (last_lo + cnt_hi - 1) % R;
+        // sums -> the slot of this block's last unit; float4 of row r, columns 4 j .. at position j ^ (r % QUADS)
+        if constexpr (!FEW_ROWS) {
+            last_hi = (last_hi + cnt_hi) % R;
+            last_lo = (last_lo + cnt_hi - 1) % R;
+        }
         {
-            unsigned char* red = ring + (wave < w_hi ? last_hi : last_lo) * SLOT;
+            unsigned char* red = FEW_ROWS ? smem + stream_sums_at(C8, W) + wave * stream_sums_bytes(C8) : ring + (wave < w_hi ? last_hi : last_lo) * SLOT;
 #pragma unroll
             for (int c = 0; c < C; ++c)
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
                     const int r = m * 16 + r16, j = c * 4 + g;
-                    if (AR == 1 && r16 >= 8) continue;
-                    *reinterpret_cast<f32x4_t*>(red + (r * (4 * C) + (j ^ (r & (4 * C - 1)))) * 16) = acc[c][m];
+                    if ((AR == 1 && r16 >= 8) || (C8 == 1 && g >= 2)) continue;
+                    *reinterpret_cast<f32x4_t*>(red + (r * QUADS + (j ^ (r & (QUADS - 1)))) * 16) = acc[c][m];
                 }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const int n0 = block * COLS;
-        for (int i = threadIdx.x; i < (row_end - row_begin) * (4 * C); i += W * kWave) {
-            const int r = i / (4 * C), j = i % (4 * C);
-            const int at = (r * (4 * C) + (j ^ (r & (4 * C - 1)))) * 16;
+        for (int i = threadIdx.x; i < (row_end - row_begin) * QUADS; i += W * kWave) {
+            const int r = i / QUADS, j = i % QUADS;
+            const int at = (r * QUADS + (j ^ (r & (QUADS - 1)))) * 16;
             f32x4_t z = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < W; ++w)
-                z += *reinterpret_cast<const f32x4_t*>(smem + w * (R * SLOT) + (w < w_hi ? last_hi : last_lo) * SLOT + at);
+                z += *reinterpret_cast<const f32x4_t*>((FEW_ROWS ? smem + stream_sums_at(C8, W) + w * stream_sums_bytes(C8)
+                                                                 : smem + w * (R * SLOT) + (w < w_hi ? last_hi : last_lo) * SLOT) +
+                                                       at);
             int dst = row_begin + r;
             float scale = 1.0f;
             if (p.out_row != nullptr) {
@@ -381,27 +523,41 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();  // everybody has read the sums: the slots may be filled again
         asm volatile("" ::: "memory");
-        if (cnt > 0) refill();
+        if (!FEW_ROWS && cnt > 0) refill();
     }
 }
 
-template <int C, int W, bool INLINE>
+// Where the rows of a contraction come from: sorted (maps in memory), sorted by the workgroup, sorted by every wavefront.
+enum StreamRows { kRowsSorted, kRowsInline, kRowsFew, kRowsEight };  // (the last: as kRowsFew, at most eight)
+
+template <int C8, int W, StreamRows ROWS>
 __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const int* list = nullptr;
-    const int32_t* offsets = p.offsets;
-    if constexpr (INLINE) {
-        InlineDispatch* d = reinterpret_cast<InlineDispatch*>(smem + stream_ring_bytes(C, W) + W * kStreamIdBytes);
-        sort_assignments<W * kWave>(p, *d, blockIdx.x == 0);
-        list = d->list;
-        offsets = d->offs;
-    }
+    touch_arguments<sizeof(StreamGemm)>();
+    constexpr int MAX_AR = stream_max_ar(C8), TILE_ROWS = 8 * MAX_AR, COLS = 8 * C8;
+    constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;  // `list` holds tokens, not assignments
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    clear_unrouted<bf16_t>(p, static_cast<int64_t>(blockIdx.x) * W + wave, static_cast<int64_t>(gridDim.x) * W);
-    constexpr int MAX_AR = stream_max_ar(C), TILE_ROWS = 8 * MAX_AR, COLS = 16 * C;
+    const int* list = nullptr;
+    bool listed_out = false;
+    ExpertTiles et;
+    if constexpr (FEW) {
+        int* sorted = reinterpret_cast<int*>(smem + stream_ring_bytes(C8, W) + wave * kStreamIdBytes);
+        et = route_few<W, stream_ring_bytes(C8, W), ROWS == kRowsEight>(p, smem, sorted, TILE_ROWS);
+        if (p.second) listed_out = p.out_row != nullptr;
+        else list = sorted;
+    } else {
+        const int32_t* offsets = p.offsets;
+        if constexpr (ROWS == kRowsInline) {
+            InlineDispatch* d = reinterpret_cast<InlineDispatch*>(smem + stream_ring_bytes(C8, W) + W * kStreamIdBytes);
+            sort_assignments<W * kWave>(p, *d, blockIdx.x == 0);
+            list = d->list;
+            offsets = d->offs;
+        }
+        clear_unrouted<bf16_t>(p, static_cast<int64_t>(blockIdx.x) * W + wave, static_cast<int64_t>(gridDim.x) * W);
+        et = scan_row_tiles(p, offsets, TILE_ROWS);
+    }
     const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
-    const ExpertTiles et = scan_row_tiles(p, offsets, TILE_ROWS);
     // Every workgroup begins its blocks at another place of the reduction: rows a power of two bytes apart put the same
     // columns of all rows on few memory channels, and workgroups that walk the reduction in step all ask these
     // (rows of 8 and 32 KiB, 256 workgroups: 5.3 and 4.8 TB/s in step, 6.1 rotated; rows of 4.5 KiB 6.0 either way).
@@ -411,12 +567,12 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
     const int cnt = et.hi - et.lo;
     const uint32_t whole = static_cast<uint32_t>(cnt) / TILE_ROWS;
     const int rest = cnt - static_cast<int>(whole) * TILE_ROWS;
-    constexpr uint32_t kWholeCost = stream_cost(C, MAX_AR);
+    constexpr uint32_t kWholeCost = stream_cost(C8, MAX_AR);
     uint32_t whole_cost = 1u, rest_cost = rest != 0 ? 1u : 0u, cost_incl = static_cast<uint32_t>(et.incl);  // cost of a block
-    if (et.total > 1 && __ballot(cnt > 16) != 0ull) {  // (else all blocks cost nearly the same)
-        const uint32_t c = rest == 0 ? 0u : (rest <= 8 ? stream_cost(C, 1) : (rest <= 16 ? stream_cost(C, 2) : (rest <= 32 ? stream_cost(C, 4) : kWholeCost)));
+    if (ROWS != kRowsEight && et.total > 1 && __ballot(cnt > 16) != 0ull) {  // (else all blocks cost nearly the same)
+        const uint32_t c = rest == 0 ? 0u : (rest <= 8 ? stream_cost(C8, 1) : (rest <= 16 ? stream_cost(C8, 2) : (rest <= 32 ? stream_cost(C8, 4) : kWholeCost)));
         const uint32_t incl = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(whole * kWholeCost + c)));
-        const uint32_t dearest = __ballot(cnt > 32) != 0ull ? kWholeCost : stream_cost(C, 4);
+        const uint32_t dearest = __ballot(cnt > 32) != 0ull ? kWholeCost : stream_cost(C8, 4);
         const uint32_t even = (static_cast<uint32_t>(et.total) * n_blocks + kStreamGrid - 1) / kStreamGrid * dearest;
         const float all = static_cast<float>(wave_read_lane(static_cast<int>(incl), kWave - 1)) * static_cast<float>(n_blocks);
         if (all < 2e9f && all * (1.0f / kStreamGrid) + static_cast<float>(dearest) < static_cast<float>(even)) {  // (32-bit products below)
@@ -426,19 +582,29 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         }
     }
     const uint32_t cost = whole * whole_cost + rest_cost;
-    const uint32_t total = static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost_incl), kWave - 1)) * n_blocks;
-    const int per_xcd = static_cast<int>(gridDim.x) / kXcdCount;
+    const uint32_t total = static_cast<uint32_t>(ROWS == kRowsEight ? et.total : wave_read_lane(static_cast<int>(cost_incl), kWave - 1)) * n_blocks;
+    constexpr int per_xcd = kStreamGrid / kXcdCount;
     const int lin = static_cast<int>(blockIdx.x % kXcdCount) * per_xcd + static_cast<int>(blockIdx.x / kXcdCount);
     // total * lin / kStreamGrid and the next one's begin, in 32 bits and scalar registers
     const uint32_t t_hi = __builtin_amdgcn_readfirstlane(total / kStreamGrid), t_lo = __builtin_amdgcn_readfirstlane(total % kStreamGrid);
     uint32_t at = __builtin_amdgcn_readfirstlane(t_hi * lin + t_lo * lin / kStreamGrid);
     const uint32_t end = __builtin_amdgcn_readfirstlane(t_hi * (lin + 1) + t_lo * (lin + 1) / kStreamGrid);
     while (at < end) {
+        if constexpr (ROWS == kRowsEight) {  // an expert with rows has one tile
+            const uint32_t t = uniform_udiv(at, n_blocks);
+            const int e = __builtin_ctzll(__ballot(cnt > 0 && et.incl == static_cast<int>(t) + 1));
+            const int row_begin = wave_read_lane(et.lo, e), row_end = wave_read_lane(et.hi, e);
+            const int b0 = static_cast<int>(at - t * n_blocks);
+            at = min(end, (t + 1) * n_blocks);
+            stream_segment<C8, 1, W, true>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, FEW, listed_out, smem);
+            continue;
+        }
         const int e = __builtin_ctzll(__ballot(at < cost_incl * n_blocks));
         const uint32_t e_cost = static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost), e));
         const uint32_t e_begin = (static_cast<uint32_t>(wave_read_lane(static_cast<int>(cost_incl), e)) - e_cost) * n_blocks;
         const uint32_t e_whole = static_cast<uint32_t>(wave_read_lane(static_cast<int>(whole), e));
-        uint32_t tile = (at - e_begin) / (whole_cost * n_blocks), c = whole_cost;
+        uint32_t tile = 0, c = whole_cost;
+        if (e_whole != 0) tile = (at - e_begin) / (whole_cost * n_blocks);  // (a division by a run-time value takes a quarter of a microsecond)
         if (tile >= e_whole) {
             tile = e_whole;
             c = e_cost - e_whole * whole_cost;
@@ -457,32 +623,35 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         at = __builtin_amdgcn_readfirstlane(tile_begin + c * n_blocks);
         if (b0 >= b1) continue;
         const int rows = row_end - row_begin;
-        if (rows <= 8) stream_segment<C, 1, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
-        else if (rows <= 16) stream_segment<C, 2, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
-        else if (rows <= 32) stream_segment<C, 4, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
-        else stream_segment<C, MAX_AR, W>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        if (rows <= 8) stream_segment<C8, 1, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        else if (rows <= 16) stream_segment<C8, 2, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        else if (rows <= 32) stream_segment<C8, 4, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        else stream_segment<C8, MAX_AR, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
     }
 }
 
-template <int C, int W, bool INLINE>
+template <int C8, int W, StreamRows ROWS>
 static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
 {
-    constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C, W)) + W * kStreamIdBytes + (INLINE ? sizeof(InlineDispatch) : 0);
+    constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C8, W)) + W * kStreamIdBytes + (ROWS == kRowsInline ? sizeof(InlineDispatch) : (ROWS == kRowsEight ? W * stream_sums_bytes(C8) : 0));
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    auto kern = stream_gemm_kernel<C, W, INLINE>;
+    auto kern = stream_gemm_kernel<C8, W, ROWS>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(W * kWave), lds, stream, p);
     return EXF_OK;
 }
 
-template <int C, int W>
+template <int C8, int W>
 static int launch_stream(const StreamGemm& p, hipStream_t stream)
 {
-    return p.topk_idx != nullptr ? launch_stream_as<C, W, true>(p, stream) : launch_stream_as<C, W, false>(p, stream);
+    if (p.topk_idx == nullptr) return launch_stream_as<C8, W, kRowsSorted>(p, stream);
+    if (p.max_rows <= 8) return launch_stream_as<C8, W, kRowsEight>(p, stream);
+    return p.max_rows <= kFewAssignments ? launch_stream_as<C8, W, kRowsFew>(p, stream) : launch_stream_as<C8, W, kRowsInline>(p, stream);
 }
 
-// Columns per block, by a model of the launch: with q blocks per workgroup it runs ceil(q)/q times as long as its
+// Columns per block, by a model of the launch (blocks of 8 columns: one row of 4096 x 1024 has 128 of them for 256 workgroups
+// instead of 64 of 16, the layer of one token 14.2 us and 13.6): with q blocks per workgroup it runs ceil(q)/q times as long as its
 // bytes take (the workgroups' shares differ by a block), and the activations, which every block reads
 // again, weigh about 0.6 of their share of the weights (fitted to 9 shapes of 1 to 617 tokens: it picks the fastest
 // of the three or one within 5 %).
@@ -491,18 +660,19 @@ static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
     const double A = p.max_rows, E = p.E_local;
     const double touched = E * (1.0 - exp(A * log1p(-1.0 / E)));  // experts with rows, if A rows fall on E experts at random
     const double act_rows = 8.0 * ceil(1.3 * A / touched / 8.0);
-    int best = 4;
+    int best = 8;
     double best_cost = 1e300;
-    for (int c = 4; c >= 1; c /= 2) {
-        const double q = touched * (p.N / (16 * c)) / kStreamGrid;
-        const double cost = ceil(q) / q * (1.0 + 0.6 * act_rows / (16 * c));
+    for (int c = 8; c >= 1; c /= 2) {  // (in eights)
+        const double q = touched * (p.N / (8 * c)) / kStreamGrid;
+        const double cost = ceil(q) / q * (1.0 + 0.6 * act_rows / (8 * c));
         if (cost < best_cost) {
             best_cost = cost;
             best = c;
         }
     }
+    if (best == 8) return launch_stream<8, 4>(p, stream);
     if (best == 4) return launch_stream<4, 4>(p, stream);
-    if (best == 2) return launch_stream<2, 4>(p, stream);
+    if (best == 2) return launch_stream<2, 8>(p, stream);
     return launch_stream<1, 8>(p, stream);
 }
 
@@ -718,6 +888,12 @@ static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 // against 27.3 with 117).  Up to 128 rows of a single expert are known to fill 32, 64 or 128 of a row tile's, which is what they
 // cost (1024 x 4096: 24.8 against 27.4 with 117 rows; 2048 x 8192: 37.1 against 44.9 with 58, 53.2 against 45.6 with 65; 4096 x
 // 14336: 52.7 against 74.0 with 30, 83.4 against 74.2 with 33).
+bool gate_joins_layer(int64_t T, int k, int d, int E, int dt)
+{
+    (void)k, (void)d, (void)E;
+    return dt == EXF_BF16 && T <= kGateFewTokens;
+}
+
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
     if (dt == EXF_F32 || A <= 28ll * E_local) return true;

@@ -4,36 +4,9 @@
 // weights of all experts passing through every compute unit for short ones.  bf16 runs on the matrix cores (experts
 // on the MFMA row axis, tokens on the column axis, so that a token's logits sit in 4 lanes); softmax and selection are
 // fp32.  fp32 inputs (small layers) use one wavefront per token with wavefront reductions.
-#include <math.h>
-
-#include "common.hpp"
+#include "gate_tile.hpp"
 
 namespace exf {
-
-
-struct Route {
-    int i0, i1;
-    float w0, w1;
-};
-
-// Softmax weights of the selected experts from the two best logits and sum exp(l - l0).
-__device__ __forceinline__ void route_weights(Route& r, float l0, float l1, float sum_exp, int k, int renormalize)
-{
-    if (k == 1) {
-        r.w0 = 1.0f / sum_exp;
-        r.w1 = 0.0f;
-    } else {
-        const float t = expf(l1 - l0);
-        if (renormalize) {
-            const float z = 1.0f + t;
-            r.w0 = 1.0f / z;
-            r.w1 = t / z;
-        } else {
-            r.w0 = 1.0f / sum_exp;
-            r.w1 = t / sum_exp;
-        }
-    }
-}
 
 // Wavefront routing: lane e holds logit e (lanes >= E hold -inf).  Every lane returns the result.
 __device__ __forceinline__ void wave_argmax(float& v, int& i)
@@ -71,17 +44,6 @@ __device__ __forceinline__ Route route_wave(float my_logit, int E, int k, int re
     const float s = wave_sum(live ? expf(my_logit - l0) : 0.0f);
     route_weights(r, l0, l1, s, k, renormalize);
     return r;
-}
-
-__device__ __forceinline__ void store_route(const Route& r, int64_t t, int k, int32_t* __restrict__ topk_idx,
-                                            float* __restrict__ topk_w)
-{
-    topk_idx[t * k] = r.i0;
-    topk_w[t * k] = r.w0;
-    if (k > 1) {
-        topk_idx[t * k + 1] = r.i1;
-        topk_w[t * k + 1] = r.w1;
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -143,72 +105,6 @@ __global__ __launch_bounds__(256) void gate_f32_kernel(const float* __restrict__
         if (logits_out != nullptr && lane < E) logits_out[t * E + lane] = mine;
         const Route r = route_wave(mine, E, k, renormalize);
         if (lane == 0) store_route(r, t, k, topk_idx, topk_w);
-    }
-}
-
-__device__ __forceinline__ void pick_better(float& v, int& i, float ov, int oi)
-{
-    if (ov > v || (ov == v && oi < i)) {
-        v = ov;
-        i = oi;
-    }
-}
-
-// Routing from the accumulator layout: lane (r16, g) holds the logits of token `tok` (its r16-th of the tile) for the experts
-// nt*16 + 4g + v (ascending in (nt, v)), so the four lanes of a token need two shuffle steps.
-template <int NT>
-__device__ __forceinline__ void route_quads(const f32x4_t (&acc)[NT], int64_t tok, int64_t T, int E, int k, int renormalize,
-                                            float* __restrict__ logits_out, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w)
-{
-    const int g = lane_id() >> 4;
-    float l0 = -INFINITY;
-    int i0 = 2 * kWave;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int e = nt * 16 + 4 * g + v;
-            if (e < E) pick_better(l0, i0, acc[nt][v], e);
-        }
-    pick_better(l0, i0, __shfl_xor(l0, 16, kWave), __shfl_xor(i0, 16, kWave));
-    pick_better(l0, i0, __shfl_xor(l0, 32, kWave), __shfl_xor(i0, 32, kWave));
-    float l1 = -INFINITY;
-    int i1 = 2 * kWave;
-    if (k > 1) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int e = nt * 16 + 4 * g + v;
-                if (e < E && e != i0) pick_better(l1, i1, acc[nt][v], e);
-            }
-        pick_better(l1, i1, __shfl_xor(l1, 16, kWave), __shfl_xor(i1, 16, kWave));
-        pick_better(l1, i1, __shfl_xor(l1, 32, kWave), __shfl_xor(i1, 32, kWave));
-    }
-    float se = 0.0f;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (nt * 16 + 4 * g + v < E) se += expf(acc[nt][v] - l0);
-    se += __shfl_xor(se, 16, kWave);
-    se += __shfl_xor(se, 32, kWave);
-    if (tok >= T) return;
-    if (logits_out != nullptr) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int e = nt * 16 + 4 * g + v;
-                if (e < E) logits_out[tok * E + e] = acc[nt][v];
-            }
-    }
-    if (g == 0) {
-        Route r;
-        r.i0 = i0;
-        r.i1 = i1;
-        route_weights(r, l0, l1, se, k, renormalize);
-        store_route(r, tok, k, topk_idx, topk_w);
     }
 }
 
@@ -515,8 +411,7 @@ static int dispatch_gate_bf16(const void* x, const void* wg, int64_t T, int d, i
         return launch_gate_long<NT, 4>(x, wg, T, d, E, k, renormalize, logits_out, topk_idx, topk_w, stream);
     }
     if (NT > 1 && T >= 64 * 128) return launch_gate_stream<NT, 4, 4>(x, wg, T, d, E, k, renormalize, logits_out, topk_idx, topk_w, stream);
-    if (d >= 2048 && NT <= 2)  // a long reduction over more wavefronts while their rings fit
-        return launch_gate_stream<NT, 1, NT <= 2 ? 8 : 4>(x, wg, T, d, E, k, renormalize, logits_out, topk_idx, topk_w, stream);
+    if (gate_sums(NT, d) == 8) return launch_gate_stream<NT, 1, NT <= 2 ? 8 : 4>(x, wg, T, d, E, k, renormalize, logits_out, topk_idx, topk_w, stream);
     return launch_gate_stream<NT, 1, 4>(x, wg, T, d, E, k, renormalize, logits_out, topk_idx, topk_w, stream);
 }
 

@@ -24,10 +24,14 @@ extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
             return bad;
         if (int bad = exf::check_combine(l.y_sorted, l.sorted_of_src, l.topk_w, l.T, l.d, l.k, l.dt, l.out)) return bad;
     }
-    int rc = moe_gate_topk(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.renormalize, l.dt, nullptr, l.topk_idx, l.topk_w, stream);
+    const bool routed = fused && exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt);
+    const bool gated = routed && exf::gate_joins_layer(l.T, l.k, l.d, l.E, l.dt);
+    int rc = EXF_OK;
+    if (!gated) rc = moe_gate_topk(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.renormalize, l.dt, nullptr, l.topk_idx, l.topk_w, stream);
     if (rc != EXF_OK) return rc;
-    if (fused && exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt)) {
-        exf::FfnRouting r{idx, l.expert_map, l.E, l.src_of_sorted, l.sorted_of_src, l.expert_counts, l.expert_offsets};
+    if (routed) {
+        exf::FfnRouting r{idx,          l.expert_map, l.E, l.src_of_sorted, l.sorted_of_src, l.expert_counts, l.expert_offsets, gated ? l.w_gate : nullptr,
+                          l.renormalize, l.topk_idx,   l.topk_w};
         return exf::ffn_fused_routed(r, l.x, l.topk_w, l.w1, l.w2, l.T, l.k, l.d, l.f, l.E_local, l.act, l.dt, l.out, l.ffn_workspace,
                                      l.ffn_workspace_bytes, stream);
     }

@@ -159,12 +159,27 @@ def test_exact_ffn_ragged(oracle, counts, d, f):
 def test_layer_forward_is_its_calls(T, k, E, E_local, dtype, fused, routing):
     """moe_layer_forward writes what the separate calls write, maps included, also where it sorts without a dispatch launch."""
     _say(f"layer forward T={T} k={k} E={E} E_local={E_local} {dtype} fused={fused} {routing}")
+    _layer_against_calls(T, k, E, E_local, dtype, fused, routing, 128, 192)
+
+
+# a handful of rows: one to eight, up to sixteen tokens (gated by the first contraction) and past them, up to 64 assignments and past
+# them; one to four tiles of experts; four and eight sums of the gate; blocks of 8 to 64 columns, one and several an expert
+@pytest.mark.parametrize("T,k,E,E_local,d,f,routing", [
+    (1, 1, 1, 1, 64, 64, "gate"), (1, 2, 2, 2, 1024, 4096, "gate"), (8, 1, 8, 8, 192, 64, "gate"), (4, 2, 17, 17, 2048, 320, "gate"), (9, 1, 16, 4, 2112, 128, "gate"),
+    (16, 2, 33, 33, 64, 256, "gate"), (16, 1, 64, 64, 2048, 64, "gate"), (17, 1, 40, 40, 128, 448, "gate"), (5, 1, 32, 32, 4096, 64, "gate"),
+    (3, 1, 8, 2, 1024, 2048, "ids"), (8, 1, 8, 8, 64, 8192, "ids"), (32, 2, 8, 8, 256, 512, "ids"), (64, 1, 3, 3, 128, 256, "ids"), (65, 1, 3, 3, 128, 256, "ids"),
+    (7, 1, 64, 9, 128, 64, "dropped"), (2, 2, 64, 9, 128, 64, "dropped"), (16, 1, 1, 1, 512, 1024, "gate")])
+def test_layer_forward_of_a_few_rows(T, k, E, E_local, d, f, routing):
+    _say(f"layer forward T={T} k={k} E={E} E_local={E_local} {d} x {f} {routing}")
+    _layer_against_calls(T, k, E, E_local, "bf16", True, routing, d, f)
+
+
+def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f):
     from paper_2401_08383_amd.pipeline import MoELayerRun
 
     g = torch.Generator(device="cuda")
     g.manual_seed(1600 + T)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    d, f = 128, 192
 
     def rnd(*shape):
         return torch.randn(shape, device="cuda", generator=g).to(dt)
