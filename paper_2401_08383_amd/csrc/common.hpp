@@ -134,6 +134,43 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
+// The values of the two lanes that differ in bit OFF of their number, the same two in both of them (or the same pair of values: OFF 8,
+// 4, 2, 1 expect that the lanes whose numbers differ in the higher bits below 16 already agree, as they do on the way
+// through a butterfly).  Rows of 16 lanes trade places, lanes of a row rotate: no trip through the LDS pipeline.
+template <int OFF>
+__device__ __forceinline__ void butterfly(uint32_t v, uint32_t& a, uint32_t& b)
+{
+    if constexpr (OFF == 32) {
+        const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = s[0], b = s[1];
+    } else if constexpr (OFF == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = s[0], b = s[1];
+    } else {
+        a = v;
+        b = __builtin_amdgcn_update_dpp(0, v, 0x120 + OFF, 0xf, 0xf, true);  // row_ror
+    }
+}
+template <int OFF>
+__device__ __forceinline__ void butterfly(float v, float& a, float& b)
+{
+    uint32_t x, y;
+    butterfly<OFF>(__float_as_uint(v), x, y);
+    a = __uint_as_float(x), b = __uint_as_float(y);
+}
+template <int OFF>
+__device__ __forceinline__ float butterfly_add(float v)
+{
+    float a, b;
+    butterfly<OFF>(v, a, b);
+    return a + b;
+}
+// wave_sum of floats, added in the same order: the same bits.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    return butterfly_add<1>(butterfly_add<2>(butterfly_add<4>(butterfly_add<8>(butterfly_add<16>(butterfly_add<32>(v))))));
+}
+
 // Inclusive prefix sum across the 64 lanes of a wavefront, on the cross-lane data path of the vector
 // ALU (a shuffle goes through the LDS pipeline and costs a round trip of its own per step; a tile
 // lookup runs several scans in a row before a workgroup can request its first operand).  Steps 1-4 add

@@ -88,10 +88,17 @@ __device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDisp
     __syncthreads();
     if (wave == 0) {  // lane = expert
         int run = 0;
-        for (int s = 0; s < rounds * WAVES; ++s) {
-            const int c = d.seg[s][lane];
-            d.seg[s][lane] = static_cast<unsigned short>(run);
-            run += c;
+        constexpr int AHEAD = kInlineSegments < 8 ? kInlineSegments : 8;  // segments read together: they do not wait for one another's store
+        for (int s0 = 0; s0 < rounds * WAVES; s0 += AHEAD) {
+            int c[AHEAD];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) c[i] = d.seg[min(s0 + i, kInlineSegments - 1)][lane];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (s0 + i >= rounds * WAVES) break;
+                d.seg[s0 + i][lane] = static_cast<unsigned short>(run);
+                run += c[i];
+            }
         }
         const int incl = wave_inclusive_scan(run);
         d.offs[lane] = incl - run;
@@ -697,7 +704,8 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         int r = min(row_begin + m * 16 + r16, row_end - 1);  // rows past the end repeat the last one
-        if (a_row != nullptr) r = a_row[r] / a_div;
+        if (a_row != nullptr) r = a_row[r];
+        if (a_row != nullptr && a_div > 1) r = static_cast<int>(static_cast<unsigned>(r) / static_cast<unsigned>(a_div));
         row_a[m] = act + static_cast<size_t>(r) * K;
     }
     f32x4_t acc[C][M];
@@ -793,6 +801,18 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     const int row_end = __builtin_amdgcn_readfirstlane(min(row_begin + TILE_ROWS, wave_read_lane(et.hi, e)));
     const int n0 = __builtin_amdgcn_readfirstlane(block * COLS);
 
+    // the output row and its weight, where this thread stores four columns of one row below: two dependent loads, begun in front
+    // of the sums (behind them they were 0.9 us of a small layer's 14.2)
+    constexpr int GROUPS = COLS / 4;
+    constexpr bool ONE = TILE_ROWS * GROUPS <= WK * kWave;
+    const int thread = threadIdx.x % (WK * kWave);
+    int one_dst = 0;
+    float one_scale = 1.0f;
+    if (ONE && valid && p.out_row != nullptr) {
+        one_dst = p.out_row[min(row_begin + thread / GROUPS, row_end - 1)];
+        one_scale = p.out_scale[one_dst];
+    }
+
     float* item_red = red + static_cast<size_t>(wave / WK) * (WK * TILE_ROWS * RS);
     if (valid) {
         const float* wexp = static_cast<const float*>(p.weight) + static_cast<size_t>(e) * p.N * p.K;
@@ -816,9 +836,8 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     if (!valid) return;
 
     // four columns of one row per thread: the wavefronts' sums in a fixed order, bias, activation, scale
-    constexpr int GROUPS = COLS / 4;
     const float* bias = p.bias != nullptr ? static_cast<const float*>(p.bias) + static_cast<size_t>(e) * p.N : nullptr;
-    for (int i = threadIdx.x % (WK * kWave); i < (row_end - row_begin) * GROUPS; i += WK * kWave) {
+    for (int i = thread; i < (row_end - row_begin) * GROUPS; i += WK * kWave) {
         const int r = i / GROUPS, q = i % GROUPS;
         const int n = n0 + q * 4;
         f32x4_t z = *reinterpret_cast<const f32x4_t*>(item_red + r * RS + q * 4);
@@ -828,8 +847,8 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
         int dst = row_begin + r;
         float scale = 1.0f;
         if (p.out_row != nullptr) {
-            dst = p.out_row[dst];
-            scale = p.out_scale[dst];
+            dst = ONE ? one_dst : p.out_row[dst];
+            scale = ONE ? one_scale : p.out_scale[dst];
         }
         float v[4];
 #pragma unroll

@@ -11,15 +11,12 @@ namespace exf {
 // Wavefront routing: lane e holds logit e (lanes >= E hold -inf).  Every lane returns the result.
 __device__ __forceinline__ void wave_argmax(float& v, int& i)
 {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(v, off, kWave);
-        const int oi = __shfl_xor(i, off, kWave);
-        if (ov > v || (ov == v && oi < i)) {
-            v = ov;
-            i = oi;
-        }
-    }
+    best_of_pair<32>(v, i);
+    best_of_pair<16>(v, i);
+    best_of_pair<8>(v, i);
+    best_of_pair<4>(v, i);
+    best_of_pair<2>(v, i);
+    best_of_pair<1>(v, i);
 }
 
 __device__ __forceinline__ Route route_wave(float my_logit, int E, int k, int renormalize)
@@ -75,7 +72,7 @@ __global__ __launch_bounds__(256) void gate_f32_kernel(const float* __restrict__
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave; t < T; t += waves) {
         const float* xr = x + t * d;
         float mine = 0.0f;
-        // eight experts at a time: their loads and their wavefront sums (six dependent shuffles each) overlap
+        // eight experts at a time: their loads and their wavefront sums (six dependent steps each) overlap
         constexpr int EB = 8;
         for (int e0 = 0; e0 < E; e0 += EB) {
             float acc[EB];
@@ -95,9 +92,7 @@ __global__ __launch_bounds__(256) void gate_f32_kernel(const float* __restrict__
                 }
             }
 #pragma unroll
-            for (int off = kWave / 2; off > 0; off >>= 1)
-#pragma unroll
-                for (int j = 0; j < EB; ++j) acc[j] += __shfl_xor(acc[j], off, kWave);
+            for (int j = 0; j < EB; ++j) acc[j] = wave_sum(acc[j]);
 #pragma unroll
             for (int j = 0; j < EB; ++j)
                 if (lane == e0 + j) mine = acc[j];

@@ -52,33 +52,13 @@ __device__ __forceinline__ void pick_later(float& v, int& i, float ov, int oi, b
     i = better ? oi : i;
 }
 
-// The values of the two lanes that differ in bit OFF (16 or 32) of their number, in both of them, in the same order (a swap
-// of rows instead of a trip through the LDS pipeline).
-template <int OFF>
-__device__ __forceinline__ void row_pairs(uint32_t v, uint32_t& low, uint32_t& high)
-{
-    if constexpr (OFF == 16) {
-        const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        low = s[0], high = s[1];
-    } else {
-        const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        low = s[0], high = s[1];
-    }
-}
-template <int OFF>
-__device__ __forceinline__ void row_pairs(float v, float& low, float& high)
-{
-    uint32_t a, b;
-    row_pairs<OFF>(__float_as_uint(v), a, b);
-    low = __uint_as_float(a), high = __uint_as_float(b);
-}
 template <int OFF>
 __device__ __forceinline__ void best_of_pair(float& v, int& i)
 {
     float v0, v1;
     uint32_t i0, i1;
-    row_pairs<OFF>(v, v0, v1);
-    row_pairs<OFF>(static_cast<uint32_t>(i), i0, i1);
+    butterfly<OFF>(v, v0, v1);
+    butterfly<OFF>(static_cast<uint32_t>(i), i0, i1);
     const bool second = v1 > v0 || (v1 == v0 && static_cast<int>(i1) < static_cast<int>(i0));
     v = second ? v1 : v0;
     i = static_cast<int>(second ? i1 : i0);
@@ -123,10 +103,7 @@ __device__ __forceinline__ Route route_of_quads(const f32x4_t (&acc)[NT], int E,
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             se += nt * 16 + 4 * g + v < E ? expf(acc[nt][v] - l0) : 0.0f;
-    float a, b;
-    row_pairs<16>(se, a, b);
-    row_pairs<32>(a + b, a, b);
-    se = a + b;
+    se = butterfly_add<32>(butterfly_add<16>(se));
     Route r;
     r.i0 = i0;
     r.i1 = i1;
