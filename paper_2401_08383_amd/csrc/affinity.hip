@@ -320,7 +320,9 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
 //   - A histogram row starts at an even counter, so the word of a transition is row(a) + b/2 and its half is b%2: both
 //     are formed once per token and column, a transition costs one addition and one atomic.
 // Transitions with an invalid end are skipped; the packed per-chunk partials go to part_counts[chunk][pair][words].
-// 24 x 1M tokens, 64 experts: 207 us before, 89 now (7 LDS cycles an atomic, 55 us of the compute units' LDS).
+// 24 x 1M tokens, 64 experts, both launches: 99.0 us with loops over the targets and a second set of registers for the next sweep, 96.6
+// now.  Atomics are 59 us of it (7.6 cycles each; 43 without bank conflicts), the second launch 11.5, start, clearing and
+// writing of the histograms 15.
 constexpr int kHopBlock = 4;       // layers per block
 constexpr int kHopThreads = 1024;
 constexpr int kHopInside = 6;      // pairs inside a block
@@ -371,13 +373,52 @@ __global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int
     const uint32_t hist_bytes = static_cast<uint32_t>(words) * 4u;
     const uint32_t row_bytes = static_cast<uint32_t>((E + 1) / 2) * 4u;
     const uint32_t my_copy = static_cast<uint32_t>(threadIdx.x & (copies - 1)) * static_cast<uint32_t>(copy_words) * 4u;
-    // The transitions of one sweep, in loops over the targets and over the two blocks: unrolled, the code of one sweep is 17 KB, and
-    // short traces (one sweep or two) wait for nothing else.  As the source of a pair a token is the byte offset of its row, as
-    // the target that of its word and the addend: one addition and one atomic a transition.  CHECK: an invalid id adds 0 (to a word of row 0 or
-    // column 0); this costs as many vector instructions as the LDS has cycles, so clean wavefronts (nearly all) do without.
-    auto count_all = [&](auto check, const TokVec<VEC>(&col)[2 * kHopBlock], int left) {
-        constexpr bool CHECK = decltype(check)::value;
-        auto valid = [&](const TokVec<VEC>& t, int u) { return !CHECK || (static_cast<uint32_t>(t.v[u]) < static_cast<uint32_t>(E) && u < left); };
+    // The transitions of one sweep.  As the source of a pair a token is the byte offset of its row, as the target that of its word and
+    // the addend: one addition and one atomic a transition.
+    // Clean wavefronts (nearly all): the pairs inside the blocks first, then the tokens of the others as offsets and addends, formed once
+    // and indexed statically; the next sweep's loads then go where this one's tokens were.
+    auto add_at = [&](uint32_t at, uint32_t one) { atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(lds) + at), one); };
+    auto clean_row = [&](int32_t t) { return my_copy + __umul24(static_cast<uint32_t>(t), row_bytes); };
+    auto clean_word = [&](int32_t t) { return (static_cast<uint32_t>(t) << 1) & ~3u; };
+    auto clean_one = [&](int32_t t) { return 1u << ((static_cast<uint32_t>(t) << 4) & 31u); };
+    auto count_clean = [&](TokVec<VEC>(&col)[2 * kHopBlock], auto load_next) {
+        uint32_t slot = targets > 0 ? kHopBlock * kHopBlock * hist_bytes : 0u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int k = 0; k < kHopInside; ++k)
+                if (((h == 0 ? inside_i : inside_j) >> k & 1u) != 0u) {
+                    const TokVec<VEC>&from = col[h * kHopBlock + hop_inside_source(k)], &to = col[h * kHopBlock + hop_inside_target(k)];
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) add_at(slot + clean_row(from.v[u]) + clean_word(to.v[u]), clean_one(to.v[u]));
+                    slot += hist_bytes;
+                }
+        uint32_t row[kHopBlock][VEC], word[kHopBlock][VEC], one[kHopBlock][VEC];
+#pragma unroll
+        for (int s = 0; s < kHopBlock; ++s)
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) {
+                row[s][u] = clean_row(col[s].v[u]);
+                word[s][u] = clean_word(col[kHopBlock + s].v[u]);
+                one[s][u] = clean_one(col[kHopBlock + s].v[u]);
+            }
+        load_next();
+        slot = 0;
+#pragma unroll
+        for (int t = 0; t < kHopBlock; ++t) {
+            if (t >= targets) break;
+#pragma unroll
+            for (int s = 0; s < kHopBlock; ++s) {
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) add_at(row[s][u] + word[t][u] + slot, one[t][u]);
+                slot += hist_bytes;
+            }
+        }
+    };
+    // The others, in loops over the targets and over the two blocks (little code): an invalid id adds 0 (to a word of row 0 or
+    // column 0); this costs as many vector instructions as the LDS has cycles.
+    auto count_checked = [&](const TokVec<VEC>(&col)[2 * kHopBlock], int left) {
+        auto valid = [&](const TokVec<VEC>& t, int u) { return static_cast<uint32_t>(t.v[u]) < static_cast<uint32_t>(E) && u < left; };
         auto row_of = [&](const TokVec<VEC>& t, int u) { return valid(t, u) ? my_copy + __umul24(static_cast<uint32_t>(t.v[u]), row_bytes) : 0u; };
         auto word_of = [&](const TokVec<VEC>& t, int u) { return valid(t, u) ? static_cast<uint32_t>(t.v[u]) / 2u * 4u : 0u; };
         auto one_of = [&](const TokVec<VEC>& t, int u) { return valid(t, u) ? 1u << (static_cast<uint32_t>(t.v[u]) % 2u * 16u) : 0u; };
@@ -433,14 +474,16 @@ __global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int
         for (int s = 0; s < 2 * kHopBlock; ++s)
             col[s] = load_tokens<VEC, false>(trace + static_cast<int64_t>(min(s < kHopBlock ? i0 + s : j0 + s - kHopBlock, L - 1)) * N, n0, n_end);
     };
-    TokVec<VEC> col[2 * kHopBlock], nxt[2 * kHopBlock];
+    TokVec<VEC> col[2 * kHopBlock];
     const int64_t wave_first = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)) * (kWave * VEC);
     load_cols(n_begin + static_cast<int64_t>(threadIdx.x) * VEC, col);
     for (int i = threadIdx.x; i < copies * (copy_words / 2); i += kHopThreads) reinterpret_cast<uint2*>(lds)[i] = make_uint2(0u, 0u);
     __syncthreads();
     for (int64_t base = n_begin; base + wave_first < n_end; base += sweep) {
         const int64_t n0 = base + static_cast<int64_t>(threadIdx.x) * VEC;
-        if (base + sweep + wave_first < n_end) load_cols(n0 + sweep, nxt);
+        auto load_next = [&]() {
+            if (base + sweep + wave_first < n_end) load_cols(n0 + sweep, col);
+        };
         unsigned m = 0;
 #pragma unroll
         for (int s = 0; s < 2 * kHopBlock; ++s)
@@ -448,14 +491,13 @@ __global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int
             for (int u = 0; u < VEC; ++u) m = max(m, static_cast<unsigned>(col[s].v[u]));  // (clamped duplicate columns repeat a checked one)
         const int left = static_cast<int>(min(n_end - n0, static_cast<int64_t>(VEC)));  // tokens of this lane
         if (__ballot(left < VEC || m >= static_cast<unsigned>(E)) == 0ull) {
-            count_all(std::false_type{}, col, left);
+            count_clean(col, load_next);
         } else {
 #pragma unroll
             for (int s = 0; s < 2 * kHopBlock; ++s) cut_vector(col[s], n0, n_end);
-            count_all(std::true_type{}, col, left);
+            count_checked(col, left);
+            load_next();
         }
-#pragma unroll
-        for (int s = 0; s < 2 * kHopBlock; ++s) col[s] = nxt[s];
     }
     __syncthreads();
 
