@@ -215,19 +215,19 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
     const int e = __builtin_ctzll(owner);  // (j is below the total: some lane owns it)
     const int e_lo = wave_read_lane(p.lo, e), e_hi = wave_read_lane(p.hi, e), e_rt = wave_read_lane(p.tiles, e);
     const int r = j - (wave_read_lane(small ? p.small_incl : p.big_incl, e) - e_rt * n_tiles);
-    // Order of the expert's tiles.  With many row tiles, consecutive tiles form blocks of kBlockRows row tiles x
-    // kBlockCols column tiles: the 32 workgroups of an XCD that run side by side share 4 activation and 8 weight
-    // panels in their L2, against 16 and 2 when the rows of a column simply follow each other.  Remaining row
-    // tiles (and small experts) run row tile fastest.
-    constexpr int kBlockRows = 4, kBlockCols = 8;
+    // Order of the expert's tiles.  With many row tiles, consecutive tiles form blocks of 32, up to eight columns wide: the 32
+    // workgroups of an XCD that run side by side share 4 activation and 8 weight panels in their L2, against 16 and 2 when the
+    // rows of a column simply follow each other.  Four column tiles: blocks of 8 x 4 (32768 tokens, 8 experts of 1024 x 4096:
+    // 521 us with rows simply following each other, 511).  Remaining row tiles (and small experts) run row tile fastest.
+    const unsigned block_cols = min(static_cast<unsigned>(n_tiles & -n_tiles), 8u), block_rows = 32u / block_cols;  // powers of two
     int row_tile, col_tile;
-    const int blocked_rows = (n_tiles & (kBlockCols - 1)) == 0 ? (e_rt & ~(kBlockRows - 1)) : 0;
+    const int blocked_rows = block_cols > 1u ? (e_rt & -static_cast<int>(block_rows)) : 0;
     if (r < blocked_rows * n_tiles) {
-        const unsigned per_row_block = static_cast<unsigned>(kBlockRows * n_tiles);
-        const unsigned rbk = uniform_udiv(static_cast<unsigned>(r), per_row_block), in_rb = static_cast<unsigned>(r) - rbk * per_row_block;
-        const unsigned cb = in_rb / (kBlockRows * kBlockCols), in_b = in_rb % (kBlockRows * kBlockCols);
-        col_tile = static_cast<int>(cb * kBlockCols + in_b / kBlockRows);
-        row_tile = static_cast<int>(rbk * kBlockRows + in_b % kBlockRows);
+        const unsigned rbk = uniform_udiv(static_cast<unsigned>(r), block_rows * static_cast<unsigned>(n_tiles));
+        const unsigned in_rb = static_cast<unsigned>(r) - rbk * (block_rows * static_cast<unsigned>(n_tiles));
+        const unsigned in_b = in_rb % 32u, in_col = uniform_udiv(in_b, block_rows);
+        col_tile = static_cast<int>(in_rb / 32u * block_cols + in_col);
+        row_tile = static_cast<int>(rbk * block_rows + (in_b - in_col * block_rows));
     } else {
         const unsigned rr = static_cast<unsigned>(r - blocked_rows * n_tiles), rows_left = static_cast<unsigned>(e_rt - blocked_rows);
         const unsigned c = uniform_udiv(rr, rows_left);
