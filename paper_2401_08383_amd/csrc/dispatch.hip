@@ -14,8 +14,7 @@
 //                a unique permutation), writes both index maps and copies the slice's rows
 //                x_sorted[position] = x[assignment / k] as 16-byte vector copies.
 //                (Without rows to move, dispatch_scatter_kernel ranks whole chunks instead.)
-//   Index maps only and at most 16384 assignments: ONE workgroup of 1024 threads does all three steps
-//   in a single launch (dispatch_small_kernel) - at that size the launches, not the work, are the cost.
+//   Shorter lists (kDirectMaps, kDirectRows): one launch, every workgroup counts the whole list for itself.
 // No step needs the host to know a data-dependent size.
 #include <mutex>
 
@@ -190,106 +189,193 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_scatter_kernel(
     }
 }
 
-// Count, scan and scatter of a short assignment list in one workgroup of 16 wavefronts (index maps
-// only).  Thread t takes the assignments a = r*1024 + t, r < R.  A "segment" is what one wavefront
-// holds in one round; segments in (round, wavefront) order are ascending assignment order.  Every
-// segment counts its experts with the ballots of same_expert_lanes, a wavefront per expert scans the
-// R*16 segment counts into segment starts and the expert's total, one wavefront scans the totals into
-// the bucket starts: position = bucket start + segment start + lower lanes with the same expert - the
-// same stable permutation as the chunked kernels.
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallMaxRounds = 16;
-template <int R>
-__global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(const int32_t* __restrict__ topk_idx,
-                                                                        const int32_t* __restrict__ expert_map, int64_t A, int E,
-                                                                        int E_local, int32_t* __restrict__ expert_counts,
-                                                                        int32_t* __restrict__ expert_offsets,
-                                                                        int32_t* __restrict__ src_of_sorted,
-                                                                        int32_t* __restrict__ sorted_of_src)
+// Copies the rows of a slice of MOVE assignments from `first` on to their sorted positions pos_s (-1: not kept): every wavefront
+// takes MOVE / 4 of them and streams them as a flat sequence of 16-byte chunks (`vec_per_row` = row bytes / 16) with
+// non-temporal loads and stores, four chunks per lane in flight and the next four requested before these are stored
+// (branch-free when every row of the wavefront is kept and the chunks divide evenly).
+template <int MOVE>
+__device__ __forceinline__ void move_rows(const uint4* __restrict__ x, uint4* __restrict__ x_sorted, const int* pos_s, int64_t first, int64_t A, int k,
+                                          int vec_per_row)
 {
-    constexpr int SEG = R * kSmallWaves;       // segments
-    constexpr int PER = SEG / kWave;           // consecutive segments a lane scans
-    static_assert(SEG % kWave == 0 && R <= kSmallMaxRounds, "segment scan layout");
-    __shared__ unsigned short seg[EXF_MAX_EXPERTS][SEG];  // count, then start, of a segment inside its expert's bucket (<= 16384)
-    __shared__ int total[EXF_MAX_EXPERTS];
+    constexpr int ROWS = MOVE / kDispWaves;  // rows a wavefront moves
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
-
-    int g[R], e[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {  // all ids first, all map entries next: two memory round trips in total
-        const int64_t a = static_cast<int64_t>(r) * kSmallThreads + threadIdx.x;
-        g[r] = topk_idx[min(a, A - 1)];
+    constexpr int U = 4;
+    int tok = 0, dst = -1;
+    if (lane < ROWS) {
+        const int j = wave * ROWS + lane;
+        tok = static_cast<int>(min(first + j, A - 1) / k);
+        dst = pos_s[j];
     }
-    {   // (cleared while the ids are on their way)
-        uint32_t* words = reinterpret_cast<uint32_t*>(&seg[0][0]);
-        for (int i = threadIdx.x; i < EXF_MAX_EXPERTS * SEG / 2; i += kSmallThreads) words[i] = 0u;
+    const float rcp = 1.0f / static_cast<float>(vec_per_row);
+    const int total = ROWS * vec_per_row;
+    constexpr int kPass = kWave * U;  // chunks the wavefront moves per pass
+    const bool all_kept = __ballot(lane < ROWS && dst < 0) == 0ull;
+    if (all_kept && total % kPass == 0) {
+        const int n_pass = total / kPass;
+        auto load_pass = [&](int pass, uint4(&v)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = pass * kPass + u * kWave + lane;
+                const int r = row_of_chunk(c, vec_per_row, rcp);
+                const int col = c - r * vec_per_row;
+                const int t = __shfl(tok, r, kWave);
+                v[u] = load_stream16(x + static_cast<int64_t>(t) * vec_per_row + col);
+            }
+        };
+        auto store_pass = [&](int pass, const uint4(&v)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = pass * kPass + u * kWave + lane;
+                const int r = row_of_chunk(c, vec_per_row, rcp);
+                const int col = c - r * vec_per_row;
+                const int p = __shfl(dst, r, kWave);
+                store_stream16(x_sorted + static_cast<int64_t>(p) * vec_per_row + col, v[u]);
+            }
+        };
+        uint4 cur[U], nxt[U];
+        load_pass(0, cur);
+        for (int pass = 0; pass + 1 < n_pass; ++pass) {
+            load_pass(pass + 1, nxt);
+            store_pass(pass, cur);
+#pragma unroll
+            for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+        }
+        store_pass(n_pass - 1, cur);
+        return;
+    }
+    for (int c0 = lane; c0 < total; c0 += kWave * U) {  // some row not kept, or a ragged chunk count: every chunk checked
+        uint4 v[U];
+        int p[U], col[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * kWave;
+            const bool live = c < total;
+            const int r = live ? row_of_chunk(c, vec_per_row, rcp) : 0;
+            col[u] = c - r * vec_per_row;
+            const int t = __shfl(tok, r, kWave);
+            p[u] = live ? __shfl(dst, r, kWave) : -1;
+            v[u] = p[u] >= 0 ? load_stream16(x + static_cast<int64_t>(t) * vec_per_row + col[u]) : uint4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (p[u] >= 0) store_stream16(x_sorted + static_cast<int64_t>(p[u]) * vec_per_row + col[u], v[u]);
+    }
+}
+
+// Count, scan and placement of a list of at most kDirectMax assignments in one launch: every workgroup counts the WHOLE list
+// for itself - ids from the L2, one LDS atomic an id, into eight copies a counter so that few experts do not meet at one
+// address; the low half of a counter is the total, the high half the assignments in front of the workgroup's own slice -
+// and ranks its slice by the lanes below that hold the same expert and the wavefronts below: the same stable permutation as
+// the chunked kernels.  Reading the list in every workgroup takes less than a launch of its own for the counts.  Index maps, one
+// workgroup of 1024 threads before: 8192 assignments 6.9 us with 8 experts, 9.5 with 64, now 4.7 either way; 16384 14.9 and 5.7;
+// 24000 (two launches) 7.9 and 6.5, but 32768 of 64 experts with 8 local ones 7.1 and 9.3.  With rows (two launches, slices of 32 before):
+// 3062 x 1024 9.6 and 6.4, 512 x 4096 16.0 and 7.7; slices of 8 rows also spread few rows over the chip; from 4096 assignments on
+// the list costs more than that (10000 x 512: 12.7 with 8, 10.1 with 16, 10.0 in two launches; 8192 x 512 with 8 of 64 experts
+// local 10.4, 7.8 and 7.5).
+constexpr int64_t kDirectMaps = 20480, kDirectRows = 7168, kDirectRows8 = 4096;  // (half a counter holds 65535)
+constexpr int kDirectCopies = 8;
+template <int THREADS>
+struct DirectCounts {
+    uint32_t count[EXF_MAX_EXPERTS][kDirectCopies];
+    unsigned short seg[THREADS / kWave][EXF_MAX_EXPERTS];  // the slice's assignments, per wavefront and expert
+};
+// Sorted position of assignment begin + thread (-1: not kept, or not below min(end, A)).
+template <int THREADS>
+__device__ __forceinline__ int place_direct(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ expert_map, int A, int E, int E_local, int begin,
+                                            int end, DirectCounts<THREADS>& d, int32_t* __restrict__ expert_counts, int32_t* __restrict__ expert_offsets)
+{
+    constexpr int WAVES = THREADS / kWave, U = 8;  // ids of a thread in flight
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    auto local = [&](int id, bool there) {
+        const bool ok = there && id >= 0 && id < E;
+        int m = id;
+        if (expert_map != nullptr) m = expert_map[ok ? id : 0];
+        return ok && m >= 0 && m < E_local ? m : -1;
+    };
+    const int mine = begin + static_cast<int>(threadIdx.x);
+    const bool in_slice = mine < min(end, A);
+    const int id_mine = topk_idx[min(mine, A - 1)];
+    int id[U];
+    auto load = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) id[u] = topk_idx[min(i0 + u * THREADS + static_cast<int>(threadIdx.x), A - 1)];
+    };
+    load(0);
+    for (int i = threadIdx.x; i < static_cast<int>(sizeof(d) / 4); i += THREADS) reinterpret_cast<uint32_t*>(&d)[i] = 0u;
+    __syncthreads();
+    const int e = local(id_mine, in_slice);
+    const unsigned long long like = same_expert_lanes(e, E_local), below = (1ull << lane) - 1ull;
+    const int rank = __popcll(like & below);
+    if (e >= 0 && rank == 0) d.seg[wave][e] = static_cast<unsigned short>(__popcll(like));
+    for (int i0 = 0; i0 < A; i0 += U * THREADS) {
+        int q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = local(id[u], i0 + u * THREADS + static_cast<int>(threadIdx.x) < A);
+        if (i0 + U * THREADS < A) load(i0 + U * THREADS);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (q[u] >= 0) atomicAdd(&d.count[q[u]][lane & (kDirectCopies - 1)], i0 + u * THREADS + static_cast<int>(threadIdx.x) < begin ? 0x10001u : 1u);
     }
     __syncthreads();
+    // every wavefront for itself, lane = expert
+    uint32_t sum = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t a = static_cast<int64_t>(r) * kSmallThreads + threadIdx.x;
-        const bool ok = a < A && g[r] >= 0 && g[r] < E;
-        if (expert_map != nullptr) {
-            const int m = expert_map[ok ? g[r] : 0];
-            e[r] = (ok && m >= 0 && m < E_local) ? m : -1;
-        } else {
-            e[r] = (ok && g[r] < E_local) ? g[r] : -1;
-        }
-    }
-
-    const unsigned long long below = (1ull << lane) - 1ull;
-    int rank[R];
+    for (int c = 0; c < kDirectCopies; ++c) sum += d.count[lane][c];
+    int before = static_cast<int>(sum >> 16);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const unsigned long long m = same_expert_lanes(e[r], E_local);
-        rank[r] = __popcll(m & below);
-        if (e[r] >= 0 && (m & below) == 0ull) seg[e[r]][r * kSmallWaves + wave] = static_cast<unsigned short>(__popcll(m));
-    }
-    __syncthreads();
-
-    for (int q = wave; q < E_local; q += kSmallWaves) {
-        int c[PER], sum = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            c[j] = seg[q][lane * PER + j];
-            sum += c[j];
-        }
-        const int incl = wave_inclusive_scan(sum);
-        int run = incl - sum;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            seg[q][lane * PER + j] = static_cast<unsigned short>(run);
-            run += c[j];
-        }
-        if (lane == kWave - 1) total[q] = incl;
-    }
-    __syncthreads();
-    // every wavefront scans the totals for itself: lane q then holds the start of expert q's bucket
-    const int t = lane < E_local ? total[lane] : 0;
-    const int incl = wave_inclusive_scan(t);
-    const int bucket = incl - t;
-    if (wave == 0) {
+    for (int w = 0; w < WAVES - 1; ++w) before += w < wave ? d.seg[w][lane] : 0;
+    const int total = static_cast<int>(sum & 0xffffu), incl = wave_inclusive_scan(total);
+    if (blockIdx.x == 0 && wave == 0) {
         if (lane < E_local) {
-            expert_counts[lane] = t;
-            expert_offsets[lane] = bucket;
+            expert_counts[lane] = total;
+            expert_offsets[lane] = incl - total;
         }
         if (lane == E_local - 1) expert_offsets[E_local] = incl;
     }
+    const int start = __shfl(incl - total + before, max(e, 0), kWave);  // (all lanes take part: a shuffle reads active lanes only)
+    return e >= 0 ? start + rank : -1;
+}
 
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t a = static_cast<int64_t>(r) * kSmallThreads + threadIdx.x;
-        const int start = __shfl(bucket, max(e[r], 0));  // (all lanes take part: a shuffle reads active lanes only)
-        if (e[r] >= 0) {
-            const int pos = start + seg[e[r]][r * kSmallWaves + wave] + rank[r];
-            src_of_sorted[pos] = static_cast<int32_t>(a);
-            sorted_of_src[a] = pos;
-        } else if (a < A) {
-            sorted_of_src[a] = -1;
-        }
+// Index maps: a slice of one assignment a thread.
+constexpr int kDirectThreads = 1024;
+__global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ expert_map,
+                                                                         int A, int E, int E_local, int slice, int32_t* __restrict__ expert_counts,
+                                                                         int32_t* __restrict__ expert_offsets, int32_t* __restrict__ src_of_sorted,
+                                                                         int32_t* __restrict__ sorted_of_src)
+{
+    __shared__ DirectCounts<kDirectThreads> d;
+    const int begin = static_cast<int>(blockIdx.x) * slice;
+    const int pos = place_direct<kDirectThreads>(topk_idx, expert_map, A, E, E_local, begin, begin + slice, d, expert_counts, expert_offsets);
+    const int a = begin + static_cast<int>(threadIdx.x);
+    if (static_cast<int>(threadIdx.x) < slice && a < A) {
+        if (pos >= 0) src_of_sorted[pos] = a;
+        sorted_of_src[a] = pos;
     }
+}
+
+// Index maps and rows: a slice of MOVE assignments.
+template <int MOVE>
+__global__ __launch_bounds__(kDispThreads) void dispatch_direct_rows_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ expert_map,
+                                                                            int A, int E, int E_local, int32_t* __restrict__ expert_counts,
+                                                                            int32_t* __restrict__ expert_offsets, int32_t* __restrict__ src_of_sorted,
+                                                                            int32_t* __restrict__ sorted_of_src, const uint4* __restrict__ x, int k,
+                                                                            int vec_per_row, uint4* __restrict__ x_sorted)
+{
+    __shared__ DirectCounts<kDispThreads> d;
+    __shared__ int pos_s[MOVE];
+    touch_arguments<88>();
+    const int begin = static_cast<int>(blockIdx.x) * MOVE;
+    const int pos = place_direct<kDispThreads>(topk_idx, expert_map, A, E, E_local, begin, begin + MOVE, d, expert_counts, expert_offsets);
+    if (threadIdx.x < MOVE) {
+        const int a = begin + static_cast<int>(threadIdx.x);
+        if (pos >= 0) src_of_sorted[pos] = a;
+        if (a < A) sorted_of_src[a] = pos;
+        pos_s[threadIdx.x] = pos;
+    }
+    __syncthreads();
+    move_rows<MOVE>(x, x_sorted, pos_s, begin, A, k, vec_per_row);
 }
 
 // Scatter and row move in one launch (used whenever rows are moved).  A workgroup owns MOVE
@@ -298,10 +384,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(const int
 //     matrix), adds the assignments of its chunk that precede its slice (recounted from the ids,
 //     LDS atomics), and ranks its own slice by the lanes below that hold the same expert: stable, same permutation;
 //   - writes both index maps for its slice;
-//   - copies its rows x[a / k] -> x_sorted[position]: every wavefront takes MOVE/4 rows and streams
-//     them as a flat sequence of 16-byte chunks (`vec_per_row` = row bytes / 16) with non-temporal
-//     loads and stores, four chunks per lane in flight and the next four requested before these
-//     are stored (branch-free when every row of the wavefront is kept and the chunks divide evenly).
+//   - copies its rows x[a / k] -> x_sorted[position].
 template <bool FUSED_SCAN, int MOVE>
 __global__ __launch_bounds__(kDispThreads) void dispatch_place_kernel(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ expert_map, int64_t A, int E, int E_local, int n_coarse,
@@ -311,7 +394,6 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_place_kernel(
 {
     static_assert(MOVE == 32 || MOVE == 64, "a slice is ranked by one wavefront and split over four");
     constexpr int SUBS = kDispChunk / MOVE;  // slices per chunk
-    constexpr int ROWS = MOVE / kDispWaves;  // rows a wavefront moves
     __shared__ int cursor[EXF_MAX_EXPERTS];  // start of the chunk inside every expert's bucket
     __shared__ int pre[EXF_MAX_EXPERTS];     // assignments of the chunk in front of the slice, per expert
     __shared__ int pos_s[MOVE];              // sorted position of every assignment of the slice (-1: not kept)
@@ -397,68 +479,7 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_place_kernel(
     }
     __syncthreads();
 
-    // ---- rows: wavefront w moves rows w*ROWS .. w*ROWS+ROWS-1 of the slice -----------------------
-    constexpr int U = 4;
-    int tok = 0, dst = -1;
-    if (lane < ROWS) {
-        const int j = wave * ROWS + lane;
-        tok = static_cast<int>(min(base + first + j, A - 1) / k);
-        dst = pos_s[j];
-    }
-    const float rcp = 1.0f / static_cast<float>(vec_per_row);
-    const int total = ROWS * vec_per_row;
-    constexpr int kPass = kWave * U;  // chunks the wavefront moves per pass
-    const bool all_kept = __ballot(lane < ROWS && dst < 0) == 0ull;
-    if (all_kept && total % kPass == 0) {
-        const int n_pass = total / kPass;
-        auto load_pass = [&](int pass, uint4(&v)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int c = pass * kPass + u * kWave + lane;
-                const int r = row_of_chunk(c, vec_per_row, rcp);
-                const int col = c - r * vec_per_row;
-                const int t = __shfl(tok, r, kWave);
-                v[u] = load_stream16(x + static_cast<int64_t>(t) * vec_per_row + col);
-            }
-        };
-        auto store_pass = [&](int pass, const uint4(&v)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int c = pass * kPass + u * kWave + lane;
-                const int r = row_of_chunk(c, vec_per_row, rcp);
-                const int col = c - r * vec_per_row;
-                const int p = __shfl(dst, r, kWave);
-                store_stream16(x_sorted + static_cast<int64_t>(p) * vec_per_row + col, v[u]);
-            }
-        };
-        uint4 cur[U], nxt[U];
-        load_pass(0, cur);
-        for (int pass = 0; pass + 1 < n_pass; ++pass) {
-            load_pass(pass + 1, nxt);
-            store_pass(pass, cur);
-#pragma unroll
-            for (int u = 0; u < U; ++u) cur[u] = nxt[u];
-        }
-        store_pass(n_pass - 1, cur);
-        return;
-    }
-    for (int c0 = lane; c0 < total; c0 += kWave * U) {  // some row not kept, or a ragged chunk count: every chunk checked
-        uint4 v[U];
-        int p[U], col[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c = c0 + u * kWave;
-            const bool live = c < total;
-            const int r = live ? row_of_chunk(c, vec_per_row, rcp) : 0;
-            col[u] = c - r * vec_per_row;
-            const int t = __shfl(tok, r, kWave);
-            p[u] = live ? __shfl(dst, r, kWave) : -1;
-            v[u] = p[u] >= 0 ? load_stream16(x + static_cast<int64_t>(t) * vec_per_row + col[u]) : uint4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (p[u] >= 0) store_stream16(x_sorted + static_cast<int64_t>(p[u]) * vec_per_row + col[u], v[u]);
-    }
+    move_rows<MOVE>(x, x_sorted, pos_s, base + first, A, k, vec_per_row);
 }
 
 static int64_t dispatch_blocks(int64_t A) { return (A + kDispChunk - 1) / kDispChunk; }
@@ -521,15 +542,21 @@ static int dispatch_run(const void* x, const int32_t* topk_idx, const int32_t* e
     hipStream_t s = static_cast<hipStream_t>(stream);
     int32_t* block_counts = static_cast<int32_t*>(workspace);
     const int n_blocks = static_cast<int>(dispatch_blocks(A));
-    if (A > 0 && x_sorted == nullptr && A <= static_cast<int64_t>(kSmallMaxRounds) * kSmallThreads) {
-        // index maps of a short list: one launch, the workspace stays untouched
-#define EXF_LAUNCH_SMALL(R)                                                                                                  \
-    hipLaunchKernelGGL(dispatch_small_kernel<R>, dim3(1), dim3(kSmallThreads), 0, s, topk_idx, expert_map, A, E, E_local, \
-                       expert_counts, expert_offsets, src_of_sorted, sorted_of_src)
-        if (A <= 4 * kSmallThreads) EXF_LAUNCH_SMALL(4);
-        else if (A <= 8 * kSmallThreads) EXF_LAUNCH_SMALL(8);
-        else EXF_LAUNCH_SMALL(16);
-#undef EXF_LAUNCH_SMALL
+    const int vec_per_row = d * (dt == EXF_BF16 ? 2 : 4) / 16;
+    if (A > 0 && A <= kDirectMaps && x_sorted == nullptr) {  // one launch, the workspace stays untouched
+        constexpr int slice = 256;
+        hipLaunchKernelGGL(dispatch_direct_kernel, dim3(static_cast<unsigned>((A + slice - 1) / slice)), dim3(kDirectThreads), 0, s, topk_idx, expert_map,
+                           static_cast<int>(A), E, E_local, slice, expert_counts, expert_offsets, src_of_sorted, sorted_of_src);
+        return check_launch("moe_dispatch");
+    }
+    if (A > 0 && A <= kDirectRows && x_sorted != nullptr) {
+#define EXF_LAUNCH_DIRECT(MOVE)                                                                                                                        \
+    hipLaunchKernelGGL(dispatch_direct_rows_kernel<MOVE>, dim3(static_cast<unsigned>((A + MOVE - 1) / MOVE)), dim3(kDispThreads), 0, s, topk_idx,     \
+                       expert_map, static_cast<int>(A), E, E_local, expert_counts, expert_offsets, src_of_sorted, sorted_of_src,                     \
+                       static_cast<const uint4*>(x), k, vec_per_row, static_cast<uint4*>(x_sorted))
+        if (A <= kDirectRows8) EXF_LAUNCH_DIRECT(8);
+        else EXF_LAUNCH_DIRECT(16);
+#undef EXF_LAUNCH_DIRECT
         return check_launch("moe_dispatch");
     }
     if (n_blocks > 0)
@@ -549,7 +576,6 @@ static int dispatch_run(const void* x, const int32_t* topk_idx, const int32_t* e
                                    E, E_local, block_counts, expert_counts, expert_offsets, src_of_sorted, sorted_of_src);
         } else {
             // index maps and rows in one launch; slices of 32 assignments while that still leaves few workgroups
-            const int vec_per_row = d * (dt == EXF_BF16 ? 2 : 4) / 16;
             const bool small = (A + 63) / 64 < 512;
             const int move = small ? 32 : 64;
             const unsigned grid = static_cast<unsigned>((A + move - 1) / move);

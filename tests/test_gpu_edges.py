@@ -151,6 +151,27 @@ def test_exact_ffn_ragged(oracle, counts, d, f):
     P._ffn_case(oracle, "f32", counts, d, f, 0, True, seed=1500 + d + f)
 
 
+# ----------------------------------------------------------------------------- dispatch: every workgroup counts the whole list
+@pytest.mark.parametrize("T,k,d,E,E_local", [
+    (1, 1, 8, 1, 1), (7, 1, 72, 3, 3), (9, 2, 1032, 64, 64), (2048, 2, 64, 8, 8), (4097, 1, 136, 40, 7), (3584, 2, 16, 64, 64), (7169, 1, 16, 64, 64)])
+def test_dispatch_rows_in_one_launch(oracle, T, k, d, E, E_local):
+    """Slices of 8 and of 16 assignments, cut by the end of the list, ragged rows, dropped assignments; the first size past them."""
+    _say(f"dispatch rows T={T} k={k} d={d} E={E} E_local={E_local}")
+    g = syn.rng(2000 + T)
+    x = syn.quantize(g.standard_normal((T, d), dtype=np.float32), "bf16")
+    idx = g.integers(-1, E + 1, size=(T, k)).astype(np.int32)
+    expert_map = None
+    if E_local < E:
+        expert_map = np.full(E, -1, dtype=np.int32)
+        expert_map[g.permutation(E)[:E_local]] = np.arange(E_local, dtype=np.int32)
+    P._run_dispatch(oracle, x, idx, E, E_local, expert_map, "bf16")
+
+
+@pytest.mark.parametrize("A,E,E_local", [(1, 1, 1), (255, 64, 64), (257, 2, 2), (20480, 64, 9), (20481, 64, 64), (20479, 1, 1)])
+def test_dispatch_maps_in_one_launch(oracle, A, E, E_local):
+    P.test_dispatch_index_only_short_lists(oracle, A, E, E_local)
+
+
 # ----------------------------------------------------------------------------- one native call per layer
 @pytest.mark.parametrize("T,k,E,E_local,dtype,fused,routing", [
     (1, 1, 8, 8, "bf16", True, "gate"), (16, 2, 64, 64, "bf16", True, "gate"), (300, 2, 33, 11, "bf16", True, "gate"),
