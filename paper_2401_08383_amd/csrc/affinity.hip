@@ -24,7 +24,7 @@
 //   maps expert -> device through an LDS copy of the placement, asks for the next two layers while
 //   it counts the last two, and counts per pair the tokens whose device does not change; per-chunk
 //   partial counts are summed by a second kernel.
-#include "common.hpp"
+#include "trace_tile.hpp"
 
 #include <type_traits>
 
@@ -89,60 +89,6 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
     off += align_up(static_cast<size_t>(p.C) * (pairs > 0 ? pairs : 1) * sizeof(uint32_t), 256);
     p.total_bytes = off > 0 ? off : 256;
     return p;
-}
-
-template <int VEC>
-struct TokVec {
-    int v[VEC];
-};
-
-// Loads the ids of tokens n .. n+VEC-1 of one trace column.  The load is UNCONDITIONAL: a lane past
-// the end of its chunk re-reads the chunk's last vector (the caller masks such lanes through its own
-// range test).  Keeping branches away from the loads matters: with a branch around each of them the
-// compiler can no longer count the loads in flight and waits for all earlier ones before every new
-// one, which leaves a single load in flight per wavefront.
-// A column starts at any multiple of four bytes (its length is the number of tokens, any number): the
-// 16-byte load of gfx950 needs no more, and it costs one more cache line per wavefront when it straddles.
-// (Odd token counts used to take 4-byte loads: 46.5 us for the transfers of a 24 x 999983 trace, 24.9 now.)
-// A lane whose vector is cut by the end of the chunk receives the LAST VEC ids; cut_vector() moves them.
-// STREAM: the column is read once.
-template <int VEC, bool STREAM = true>
-__device__ __forceinline__ TokVec<VEC> load_tokens(const int32_t* __restrict__ col, int64_t n, int64_t end)
-{
-    TokVec<VEC> r;
-    const int64_t n_safe = min(n, end - VEC);  // callers guarantee end >= VEC; earlier chunks may be touched
-    if constexpr (VEC == 4) {
-        typedef int i32x4_v __attribute__((vector_size(4 * sizeof(int)), aligned(4)));
-        const i32x4_v* at = reinterpret_cast<const i32x4_v*>(col + n_safe);
-        const i32x4_v q = STREAM ? __builtin_nontemporal_load(at) : *at;
-        r.v[0] = q[0];
-        r.v[1] = q[1];
-        r.v[2] = q[2];
-        r.v[3] = q[3];
-    } else {
-        r.v[0] = __builtin_nontemporal_load(col + n_safe);
-    }
-    return r;
-}
-
-// The ids of tokens n, n+1, .. in v[0], v[1], .. again, for a lane with n < end < n + VEC (other lanes
-// are not changed; ids past the end are whatever is left, the caller's range test drops them).
-template <int VEC>
-__device__ __forceinline__ void cut_vector(TokVec<VEC>& t, int64_t n, int64_t end)
-{
-    if constexpr (VEC == 4) {
-        const int64_t by = n - (end - VEC);
-        const bool one = by == 1 || by == 3, two = by == 2 || by == 3;
-        if (one) {
-            t.v[0] = t.v[1];
-            t.v[1] = t.v[2];
-            t.v[2] = t.v[3];
-        }
-        if (two) {
-            t.v[0] = t.v[2];
-            t.v[1] = t.v[3];
-        }
-    }
 }
 
 template <int VEC>
@@ -956,6 +902,7 @@ static int run_affinity(const char* fn, const int32_t* trace, const int32_t* pla
     const AffinityPlan p = make_affinity_plan(L, N, E);
     if (workspace_bytes < p.total_bytes) return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "%s: workspace %zu < %zu bytes", fn, workspace_bytes, p.total_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (statistics_direct(trace, placement, L, N, E, counts, loads, cond_prob, n_invalid, local_per_pair, s)) return check_launch(fn);
     char* ws = static_cast<char*>(workspace);
     uint32_t* part_counts = reinterpret_cast<uint32_t*>(ws + p.off_counts);
     uint32_t* part_orphan_next = reinterpret_cast<uint32_t*>(ws + p.off_orphan_next);
@@ -1126,6 +1073,7 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
     if (workspace_bytes < p.total_bytes)
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "affinity_multihop: workspace %zu < %zu bytes", workspace_bytes, p.total_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (multihop_direct(trace, L, N, E, counts, cond_prob, s)) return check_launch("affinity_multihop");
     uint32_t* part_counts = static_cast<uint32_t*>(workspace);
     if (p.C > 0 && p.groups) {
         const int64_t grid = static_cast<int64_t>((p.C + kXcds - 1) / kXcds * kXcds) * p.Q;
@@ -1170,6 +1118,7 @@ extern "C" int placement_locality(const int32_t* trace, const int32_t* placement
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "placement_locality: workspace %zu < %zu bytes", workspace_bytes,
                     placement_locality_workspace_bytes(L, N));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (locality_direct(trace, placement, nullptr, L, N, E, local_per_pair, nullptr, s)) return check_launch("placement_locality");
     const LocalityPlan p = locality_plan(N);
     const int C = p.C;
     uint32_t* part = static_cast<uint32_t*>(workspace);
@@ -1208,6 +1157,7 @@ extern "C" int routing_transfers(const int32_t* trace, const int32_t* placement,
         return fail(EXF_ERR_WORKSPACE_TOO_SMALL, "routing_transfers: workspace %zu < %zu bytes", workspace_bytes,
                     routing_transfers_workspace_bytes(L, N));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (locality_direct(trace, placement, home, L, N, E, local_per_pair, away_per_layer, s)) return check_launch("routing_transfers");
     const LocalityPlan p = locality_plan(N);
     const int C = p.C;
     uint32_t* part = static_cast<uint32_t*>(workspace);

@@ -25,6 +25,23 @@ def test_trace_columns_that_start_and_end_anywhere(oracle, N):
     Q.test_routing_transfers_parity(5, N, 24, 8)
 
 
+@pytest.mark.parametrize("L,N,E,G", [
+    (2, 4, 1, 1), (3, 5, 64, 8), (2, 4095, 63, 7), (24, 4097, 64, 8), (2, 8191, 64, 8), (2, 8193, 8, 4), (5, 24575, 40, 5), (5, 24576, 2, 2), (5, 24577, 8, 4),
+    (4, 11392, 8, 4), (4, 11393, 8, 4), (12, 10240, 8, 4), (12, 10241, 16, 4), (33, 16385, 3, 3), (33, 2000, 24, 4)])
+def test_short_traces(oracle, L, N, E, G):
+    """One launch a call up to a number of tokens that depends on the call, two beyond: both sides of it, tokens cut by the end of a sweep,
+    invalid ids, few bins and as many as there are."""
+    P.test_affinity_and_locality_parity(oracle, L, N, E, G)
+    trace, _ = syn.planted_trace(L, N, E, 0.5, seed=2100 + N)
+    g = syn.rng(2101 + L)
+    bad = g.random((L, N)) < 0.02
+    bad[L - 1, N - 1] = bad[0, 0] = True
+    trace[bad] = g.choice(np.array([-1, E, 1 << 20, -(1 << 31)]), size=int(bad.sum())).astype(np.int32)
+    P._affinity_case(oracle, trace, E, syn.balanced_random_placement(L, E, G, seed=2102), G)
+    Q.test_affinity_multihop_parity(L, N, E)
+    Q.test_routing_transfers_parity(L, N, E, G)
+
+
 @pytest.mark.parametrize("N", [300, 262147])
 def test_placement_of_all_layers_beyond_64_KiB(oracle, N):
     """The most layers and experts: the placement and the counts take more LDS than a launch may use unasked.  Both calls
