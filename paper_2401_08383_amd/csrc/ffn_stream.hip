@@ -661,7 +661,8 @@ static int launch_stream(const StreamGemm& p, hipStream_t stream)
 // instead of 64 of 16, the layer of one token 14.2 us and 13.6): with q blocks per workgroup it runs ceil(q)/q times as long as its
 // bytes take (the workgroups' shares differ by a block), and the activations, which every block reads
 // again, weigh about 0.6 of their share of the weights (fitted to 9 shapes of 1 to 617 tokens: it picks the fastest
-// of the three or one within 5 %).
+// or one within 5 %).  Blocks of 8 columns up to kFewAssignments only: one expert of 1024 x 4096, 60 rows 22.9 us with
+// blocks of 16 and 21.8, but 70 rows 24.9 and 29.3; four of 512 x 2048, 120 rows 18.5 and 20.7.
 static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
 {
     const double A = p.max_rows, E = p.E_local;
@@ -669,7 +670,7 @@ static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
     const double act_rows = 8.0 * ceil(1.3 * A / touched / 8.0);
     int best = 8;
     double best_cost = 1e300;
-    for (int c = 8; c >= 1; c /= 2) {  // (in eights)
+    for (int c = 8; c >= (p.max_rows > kFewAssignments ? 2 : 1); c /= 2) {  // (in eights)
         const double q = touched * (p.N / (8 * c)) / kStreamGrid;
         const double cost = ceil(q) / q * (1.0 + 0.6 * act_rows / (8 * c));
         if (cost < best_cost) {
