@@ -77,8 +77,8 @@ __device__ __forceinline__ void timeline_stamp(const RowMap& map, int slot)
 // The rows of an expert become q = rows / 256 tiles, and what is left over is spread over them in quanta of 32 rows: a tile
 // of 288 rows costs an eighth more, one more tile a whole one.  A tile takes at most `most` quanta; where the
 // remainder is larger there is one tile more, all of one height.  most = 1, or 2 where the launch then has fewer rounds of
-// tiles (see plan_tiles).  An expert of at most 128 rows has one small tile, or two of 64 rows where the launch has few tiles.
-// Heights a tile is instantiated for: 64 and 128 (small), 192, 256, 288, 320.
+// tiles (see plan_tiles).  An expert of at most 128 rows has one small tile.  Heights of a tile: 64 and 128 (small), 192,
+// 256, 288, 320; of a piece of one (see locate_tile) 64, 96, 128 and 160 besides.
 constexpr int kTileRows = 256;
 constexpr int kQuantum = 32;
 constexpr int kSmallRows = 128;
@@ -86,7 +86,7 @@ constexpr int kSmallRows = 128;
 struct TileRows {
     int tiles, height, extra;  // row tiles, their base height, quanta spread over them
 };
-__device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool halves)
+__device__ __forceinline__ TileRows cut_rows(int cnt, int most)
 {
     TileRows t;
     const int q = cnt / kTileRows, r = cnt - q * kTileRows;
@@ -99,10 +99,6 @@ __device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool halves)
         // (q is at most 7 here)
         const int even = q == 0 ? cnt : (q == 1 ? (cnt + 1) / 2 : (q == 2 ? (cnt + 2) / 3 : kTileRows));
         t.height = even <= 64 && q == 0 ? 64 : (even <= kSmallRows && q == 0 ? kSmallRows : (even <= 192 ? 192 : kTileRows));
-        if (halves && t.height == kSmallRows) {
-            t.tiles = 2;
-            t.height = kSmallRows / 2;
-        }
     }
     return t;
 }
@@ -113,14 +109,13 @@ struct TilePlan {  // lane e = expert e; the same in every workgroup
     int big_incl, small_incl;   // running sums of row tiles times column tiles
     int total_big, total_small;
     int most;                   // quanta a tile takes at most
-    bool halves;                // experts of 65 to 128 rows: two tiles of 64
 };
 struct Tile2D {
     int expert;
     int row_begin, row_end;
     int n0;      // first output column
     int height;
-    int cut;     // log2 of the pieces its columns are cut into
+    int cut;     // log2 of the pieces its columns are cut into (height and rows are those of the piece)
     int hid_shift;  // hidden row of sorted row m of this expert: m + hid_shift
 };
 
@@ -140,7 +135,7 @@ __device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offse
     }
     // one quantum per tile, unless two make the launch a round of tiles shorter
     const bool small = cnt <= kSmallRows;
-    const int lean = cnt > 0 ? cut_rows(cnt, 1, false).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2, false).tiles : 0;
+    const int lean = cnt > 0 ? cut_rows(cnt, 1).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2).tiles : 0;
     const int lean_incl = wave_inclusive_scan(small ? 0 : lean * n_tiles), tall_incl = wave_inclusive_scan(small ? 0 : tall * n_tiles);
     p.small_incl = wave_inclusive_scan(small ? lean * n_tiles : 0);
     const int lean_total = wave_read_lane(lean_incl, kWave - 1), tall_total = wave_read_lane(tall_incl, kWave - 1);
@@ -150,20 +145,6 @@ __device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offse
     p.big_incl = use_tall ? tall_incl : lean_incl;
     p.total_big = use_tall ? tall_total : lean_total;
     p.total_small = wave_read_lane(p.small_incl, kWave - 1);
-    // Tiles of 128 rows in halves while all tiles then still have their columns cut into four, side by side: a compute unit has
-    // half the work (both contractions, one expert of 2048 x 8192, 100 rows: 53.5 us and 45.4; of 4096 x 14336, 128 rows: 107 and
-    // 85; four of 1024 x 4096, 100 rows each: 34.7 and 30.4.  Twice as many, cut into two: 40.0 and 41.1 for eight, 66 rows each).
-    p.halves = false;
-    if (p.total_big + p.total_small < kComputeUnits / 4) {
-        const unsigned long long mid = __ballot(cnt > kSmallRows / 2 && cnt <= kSmallRows);
-        const int more = __popcll(mid) * n_tiles;
-        if (mid != 0ull && p.total_big + p.total_small + more <= kComputeUnits / 4) {
-            p.halves = true;
-            if ((mid >> lane & 1ull) != 0ull) p.tiles = 2;
-            p.small_incl += __popcll(mid & (~0ull >> (kWave - 1 - lane))) * n_tiles;
-            p.total_small += more;
-        }
-    }
     return p;
 }
 
@@ -181,10 +162,14 @@ __device__ __forceinline__ int xcd_share(int n, int xcd, int& rot, int& begin)
 }
 
 // Work item of workgroup `wg`: the big tiles of its XCD first, then the small ones, which fill the ragged end.  The tiles of an
-// XCD's last (or only) round are cut into two or four narrower ones where its compute units have room for that: a tile
+// XCD's last (or only) round are cut into two, four or eight pieces where its compute units have room for that: a tile
 // runs on one compute unit for as long as its K loop takes, however idle the others are.  (32 skewed experts of
-// 2048 x 8192, 16384 tokens, second contraction: 584 tiles of 200 us in 2.3 rounds, 645 -> 545 us with the K loop below;
-// one expert of 1024 x 4096, 200 tokens: 70 -> 40 us.)
+// 2048 x 8192, 16384 tokens, second contraction: 584 tiles of 200 us in 2.3 rounds, 645 -> 545 us with the K loop below.)
+//   A compute unit takes in about 25 bytes a cycle of what its XCD's L2 holds, and that bounds a piece, not its MFMAs: every cut
+// goes where it leaves the fewer rows of operands, across the rows of the tile as long as these are more than its columns.
+// Both contractions, columns only in up to four pieces -> either way in up to eight: four experts of 1024 x 4096, 800 rows
+// 63.7 -> 47.5 us; one of 2048 x 8192, 130 rows 75.4 -> 56.8; eight of 1024 x 4096, 2000 rows 92.3 -> 80.9; 16 of them, 3062
+// rows (the second contraction alone is cut: 256 x 64 -> 128 x 128) 101.9 -> 98.2.
 constexpr int kUnitsPerXcd = kComputeUnits / kXcdCount;
 __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E_local, int NT, int N, int max_rows, int wg,
                                             const RowMap& probe, Tile2D& out)
@@ -196,7 +181,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
     int rot = 0, begin = 0, begin_small = 0;
     const int share = xcd_share(p.total_big, xcd, rot, begin), share_small = xcd_share(p.total_small, xcd, rot, begin_small);
     const int last_round = (share + share_small) % kUnitsPerXcd, whole = share + share_small - last_round;
-    out.cut = last_round > kUnitsPerXcd / 2 ? 0 : (last_round > kUnitsPerXcd / 4 ? 1 : 2);
+    out.cut = last_round > kUnitsPerXcd / 2 ? 0 : (last_round > kUnitsPerXcd / 4 ? 1 : (last_round > kUnitsPerXcd / 8 ? 2 : 3));
     int piece = 0;
     if (pos < whole) {
         out.cut = 0;
@@ -234,19 +219,49 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
         col_tile = static_cast<int>(c);
         row_tile = blocked_rows + static_cast<int>(rr - c * rows_left);
     }
-    const TileRows t = cut_rows(e_hi - e_lo, p.most, p.halves);
+    const TileRows t = cut_rows(e_hi - e_lo, p.most);
     // quanta: every tile takes extra / tiles, the first extra % tiles one more
     const int each = t.extra >= 2 * t.tiles ? 2 : (t.extra >= t.tiles ? 1 : 0), more = t.extra - each * t.tiles;
     const int begin_row = e_lo + row_tile * t.height + (row_tile * each + min(row_tile, more)) * kQuantum;
-    const int height = t.height + (each + (row_tile < more ? 1 : 0)) * kQuantum;
+    int height = t.height + (each + (row_tile < more ? 1 : 0)) * kQuantum;
+    int row_begin = begin_row, row_end = min(begin_row + height, e_hi);
+    if (out.cut > 0) {
+        const int rows = __builtin_amdgcn_readfirstlane(row_end - row_begin);
+        int cut = out.cut;
+        if (cut == 3 && rows <= 64) {  // no instance of an eighth: four pieces
+            if (piece >= 4) return false;
+            cut = 2;
+        }
+        int row_cut = 0;
+#pragma unroll
+        for (int i = 1; i <= 2; ++i) {
+            const int part = ((rows + (kQuantum << i) - 1) >> (i + 5)) * kQuantum;
+            const bool too_tall = cut == 2 && height > NT / 2;  // no instance of that height
+            if (row_cut == i - 1 && cut > 0 && (height - part > NT >> cut || too_tall)) {
+                row_cut = i;
+                cut -= 1;
+                height = part;
+            }
+        }
+        out.cut = cut;
+        if (row_cut > 0) {
+            row_begin += (piece & ((1 << row_cut) - 1)) * height;
+            row_end = min(row_end, row_begin + height);
+            piece >>= row_cut;
+        }
+    }
     const int n0 = col_tile * NT + piece * (NT >> out.cut);
-    if (n0 >= N) return false;  // a piece of a ragged last column tile
+    if (n0 >= N || row_begin >= row_end) return false;  // a piece of a ragged last column tile, or of a tile of few rows
     // every lane holds the same values; readfirstlane tells the compiler so (scalar registers)
     out.expert = __builtin_amdgcn_readfirstlane(e);
     out.n0 = __builtin_amdgcn_readfirstlane(n0);
     out.cut = __builtin_amdgcn_readfirstlane(out.cut);
-    out.row_begin = __builtin_amdgcn_readfirstlane(begin_row);
-    out.row_end = __builtin_amdgcn_readfirstlane(min(begin_row + height, e_hi));
+    out.row_begin = __builtin_amdgcn_readfirstlane(row_begin);
+    out.row_end = __builtin_amdgcn_readfirstlane(row_end);
+    // to the next height there is an instance of (every height that comes out here has a case in the kernel below)
+    height = max(height, 64);
+    if (NT == 256 && height == 96 && out.cut != 1) height = 128;
+    if (height == 288 && out.cut == 1) height = 320;
     out.height = __builtin_amdgcn_readfirstlane(height);
     out.hid_shift = __builtin_amdgcn_readfirstlane(kHiddenRowBlock * e - (e_lo & (kHiddenRowBlock - 1)));
     return true;
@@ -733,27 +748,35 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     const bf16_t* bias_e = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
 #define EXF_TILE(H, CUT) \
     gemm_tile<H, (NT >> CUT), WAVES, EPI>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.n0, K, N, out, smem, map)
-#define EXF_CUT_TILE(CUT)                                                   \
-    do {                                                                    \
-        if (tile.height == kTileRows) EXF_TILE(kTileRows, CUT);             \
-        else if (tile.height > kTileRows) EXF_TILE(kTileRows + 2 * kQuantum, CUT); \
-        else if (tile.height == 192) EXF_TILE(192, CUT);                    \
-        else if (tile.height == 128) EXF_TILE(128, CUT);                    \
-        else EXF_TILE(64, CUT);                                             \
-    } while (0)
-    if (tile.cut == 0) {
-        if (tile.height == kTileRows) EXF_TILE(kTileRows, 0);
-        else if (tile.height == kTileRows + kQuantum) EXF_TILE(kTileRows + kQuantum, 0);
-        else if (tile.height == kTileRows + 2 * kQuantum) EXF_TILE(kTileRows + 2 * kQuantum, 0);
-        else if (tile.height == 192) EXF_TILE(192, 0);
-        else if (tile.height == 128) EXF_TILE(128, 0);
-        else EXF_TILE(64, 0);
-    } else if (tile.cut == 1) {
-        EXF_CUT_TILE(1);
-    } else {
-        EXF_CUT_TILE(2);
+#define EXF_CASE(H, CUT) \
+    case (CUT) * 16 + (H) / kQuantum: EXF_TILE(H, CUT); break
+#define EXF_WIDE_CASE(H, CUT)                      \
+    case (CUT) * 16 + (H) / kQuantum:              \
+        if constexpr (NT == 256) EXF_TILE(H, CUT); \
+        break
+    switch (tile.cut * 16 + tile.height / kQuantum) {
+        EXF_CASE(64, 0);
+        EXF_CASE(128, 0);
+        EXF_CASE(160, 0);
+        EXF_CASE(192, 0);
+        EXF_CASE(256, 0);
+        EXF_CASE(288, 0);
+        EXF_CASE(320, 0);
+        EXF_CASE(64, 1);
+        EXF_CASE(96, 1);
+        EXF_CASE(128, 1);
+        EXF_CASE(160, 1);
+        EXF_WIDE_CASE(192, 1);
+        EXF_WIDE_CASE(256, 1);
+        EXF_WIDE_CASE(320, 1);
+        EXF_CASE(64, 2);
+        EXF_WIDE_CASE(128, 2);
+        case 96 / kQuantum:
+            if constexpr (NT == 128) EXF_TILE(96, 0);
+            break;
     }
-#undef EXF_CUT_TILE
+#undef EXF_CASE
+#undef EXF_WIDE_CASE
 #undef EXF_TILE
     timeline_stamp(map, 4);
 }
@@ -763,7 +786,7 @@ template <int NT>
 constexpr int gemm_lds_bytes()
 {
     int most = 0;
-    const int heights[] = {64, 128, 192, kTileRows, kTileRows + kQuantum, kTileRows + 2 * kQuantum};
+    const int heights[] = {64, 96, 128, 160, 192, kTileRows, kTileRows + kQuantum, kTileRows + 2 * kQuantum};
     for (int h : heights) most = tile_ring_bytes(h, NT) > most ? tile_ring_bytes(h, NT) : most;
     for (int h : heights) most = tile_ring_bytes(h, NT / 2) > most ? tile_ring_bytes(h, NT / 2) : most;
     for (int h : heights) most = tile_ring_bytes(h, NT / 4) > most ? tile_ring_bytes(h, NT / 4) : most;
@@ -775,7 +798,7 @@ static int launch_bf16_as(const void* act, const int32_t* offsets, const void* w
                           void* out, hipStream_t stream, const RowMap& map)
 {
     constexpr size_t lds = gemm_lds_bytes<NT>();
-    // worst case: every expert has one tile more than whole ones (or two halves, but then the grid of a cut round is enough); two
+    // worst case: every expert has one tile more than whole ones (a cut round has at most one workgroup per compute unit); two
     // kinds of tiles are shared out over the XCDs, and the last round may be cut
     const int64_t n_tiles = (N + NT - 1) / NT;
     const int64_t items = (A / kTileRows + (A < E_local ? A : E_local)) * n_tiles;

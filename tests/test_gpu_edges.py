@@ -156,6 +156,13 @@ def test_grouped_ffn_small_tiles_in_halves(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 1, True, seed=1750 + d)
 
 
+@pytest.mark.parametrize("d,f", [(64, 192), (128, 320), (576, 1024), (1088, 1984)])
+@pytest.mark.parametrize("counts", [[129, 160, 192, 193, 256, 257, 288], [289, 320, 385, 65, 66], [128, 96, 97, 64, 33, 1, 260, 130, 577]])
+def test_grouped_ffn_cut_tiles(oracle, counts, d, f):
+    """Tiles of every height in eight, four and two pieces (64 x 192 to 1088 x 1984), across rows, columns and both."""
+    P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1770 + d)
+
+
 @pytest.mark.parametrize("T,d,f,E,k", [(700, 64, 192, 3, 1), (1500, 192, 320, 5, 2), (900, 320, 1088, 2, 2)])
 def test_grouped_ffn_fused(oracle, T, d, f, E, k):
     P._fused_case(oracle, T, d, f, E, E, k, 1, True, seed=1800 + T)
