@@ -100,6 +100,17 @@ __device__ __forceinline__ void store_stream16(uint4* p, uint4 x)
     const u32x4_v v = {x.x, x.y, x.z, x.w};
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_v*>(p));
 }
+// Written through to memory by the L2 (a wide store's data registers may be overwritten two wait states after it at the earliest).
+__device__ __forceinline__ void store_through16(uint4* p, uint4 x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const u32x4_v v = {x.x, x.y, x.z, x.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+#else
+    (void)p;
+    (void)x;
+#endif
+}
 
 // Launch width of the pure streaming kernels: a grid-stride loop over about two workgroups per
 // CU sustained the highest HBM rate when measured (many more workgroups were slower).

@@ -27,6 +27,8 @@
 //     ends up with 4 consecutive output columns of one row; one swap between rows of 16 lanes makes that 8,
 //     and a 16-byte store needs no transposition through LDS.
 // fp32 and few rows per expert: ffn_stream.hip.
+#include <type_traits>
+
 #include "ffn_common.hpp"
 
 namespace exf {
@@ -117,6 +119,7 @@ struct Tile2D {
     int height;
     int cut;     // log2 of the pieces its columns are cut into (height and rows are those of the piece)
     int hid_shift;  // hidden row of sorted row m of this expert: m + hid_shift
+    bool through;   // its hidden rows are written through to memory
 };
 
 __device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offsets, int E_local, int n_tiles, int max_rows, const RowMap& probe)
@@ -263,6 +266,12 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
     if (NT == 256 && height == 96 && out.cut != 1) height = 128;
     if (height == 288 && out.cut == 1) height = 320;
     out.height = __builtin_amdgcn_readfirstlane(height);
+    // Hidden rows of experts with several row tiles in a launch of at most two rounds: nothing overlaps the last stores there, and
+    // what they leave in the L2s has to be written back when the kernel ends.  Written through, both contractions: 8192 tokens, 8
+    // experts of 1024 x 4096 152.2 -> 147.0 us (two rounds), 4 experts, 2048 tokens 65.9 -> 63.0, one, 6000 tokens 124.3 -> 118.3.  Not in
+    // longer launches (32768 tokens, 8 experts: 520 -> 535 us) and not where the weights of experts of one row tile bound the
+    // launch (16 experts, 2500 tokens: 87.0 -> 89.7): non-temporal stores.
+    out.through = __builtin_amdgcn_readfirstlane(e_rt >= 2 && p.total_big + p.total_small <= 2 * kComputeUnits ? 1 : 0) != 0;
     out.hid_shift = __builtin_amdgcn_readfirstlane(kHiddenRowBlock * e - (e_lo & (kHiddenRowBlock - 1)));
     return true;
 }
@@ -469,7 +478,7 @@ struct GemmTile {
 
 template <int H, int NT, int WAVES, int EPI>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const bf16_t* __restrict__ wexp, const bf16_t* __restrict__ bias_e,
-                                          int row_begin, int row_end, int hid_shift, int n0, int K, int N, bf16_t* __restrict__ out,
+                                          int row_begin, int row_end, int hid_shift, bool through, int n0, int K, int N, bf16_t* __restrict__ out,
                                           unsigned char* smem, const RowMap& map)
 {
     typedef GemmTile<H, NT, WAVES> G;
@@ -651,51 +660,57 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
             for (int b = 0; b < TM; ++b) scale[b] = map.out_scale[dst[b]];
         }
     }
+    auto finish = [&](auto written_through) {
 #pragma unroll
-    for (int a = 0; a < TN; a += 2) {
-        const int n = n_lane + a * 16;
-        float bias_v[2][4];
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) bias_v[q][v] = 0.0f;
-        if (bias_e != nullptr) {
+        for (int a = 0; a < TN; a += 2) {
+            const int n = n_lane + a * 16;
+            float bias_v[2][4];
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    bias_v[q][v] = bf16_to_f32(bias_e[min(n0 + wn * G::WTN + (a + q) * 16 + quad * 4 + v, N - 1)]);
-        }
+                for (int v = 0; v < 4; ++v) bias_v[q][v] = 0.0f;
+            if (bias_e != nullptr) {
 #pragma unroll
-        for (int b = 0; b < TM; ++b) {
-            uint32_t w[2][2];
+                for (int q = 0; q < 2; ++q)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                float v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float z = g.acc[b][a + q][r] + bias_v[q][r];
-                    if constexpr (EPI == kEpiGeluErf) z = gelu_erf_fast(z);
-                    else if constexpr (EPI == kEpiGeluTanh) z = gelu_tanh_fast(z);
-                    else z *= scale[b];
-                    v[r] = z;
-                }
-                w[q][0] = pack_bf16x2(v[0], v[1]);
-                w[q][1] = pack_bf16x2(v[2], v[3]);
+                    for (int v = 0; v < 4; ++v)
+                        bias_v[q][v] = bf16_to_f32(bias_e[min(n0 + wn * G::WTN + (a + q) * 16 + quad * 4 + v, N - 1)]);
             }
-            const auto s0 = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
-            const auto s1 = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
-            const int m = row_begin + wm * G::WTM + b * 16 + (lane & 15);
-            uint4* to;
-            if constexpr (HIDDEN_OUT)
-                to = reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(out) +
-                                              hidden_offset(static_cast<uint32_t>(m + hid_shift), static_cast<uint32_t>(n) / 8u, static_cast<uint32_t>(N) / 8u));
-            else
-                to = reinterpret_cast<uint4*>(out + static_cast<size_t>(dst[b]) * N + n);
-            if (m < row_end && n < N)  // N % 64 == 0: eight columns are inside or outside together
-                store_stream16(to, make_uint4(s0[0], s1[0], s0[1], s1[1]));
+#pragma unroll
+            for (int b = 0; b < TM; ++b) {
+                uint32_t w[2][2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    float v[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float z = g.acc[b][a + q][r] + bias_v[q][r];
+                        if constexpr (EPI == kEpiGeluErf) z = gelu_erf_fast(z);
+                        else if constexpr (EPI == kEpiGeluTanh) z = gelu_tanh_fast(z);
+                        else z *= scale[b];
+                        v[r] = z;
+                    }
+                    w[q][0] = pack_bf16x2(v[0], v[1]);
+                    w[q][1] = pack_bf16x2(v[2], v[3]);
+                }
+                const auto s0 = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+                const int m = row_begin + wm * G::WTM + b * 16 + (lane & 15);
+                uint4* to;
+                if constexpr (HIDDEN_OUT)
+                    to = reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(out) +
+                                                  hidden_offset(static_cast<uint32_t>(m + hid_shift), static_cast<uint32_t>(n) / 8u, static_cast<uint32_t>(N) / 8u));
+                else
+                    to = reinterpret_cast<uint4*>(out + static_cast<size_t>(dst[b]) * N + n);
+                if (m < row_end && n < N) {  // N % 64 == 0: eight columns are inside or outside together
+                    if constexpr (decltype(written_through)::value) store_through16(to, make_uint4(s0[0], s1[0], s0[1], s1[1]));
+                    else store_stream16(to, make_uint4(s0[0], s1[0], s0[1], s1[1]));
+                }
+            }
         }
-    }
+    };
+    if (HIDDEN_OUT && through) finish(std::integral_constant<bool, HIDDEN_OUT>());
+    else finish(std::false_type());
 }
 
 template <int NT, int WAVES, int EPI>
@@ -747,7 +762,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     const bf16_t* wexp = weight + static_cast<size_t>(tile.expert) * N * K;
     const bf16_t* bias_e = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
 #define EXF_TILE(H, CUT) \
-    gemm_tile<H, (NT >> CUT), WAVES, EPI>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.n0, K, N, out, smem, map)
+    gemm_tile<H, (NT >> CUT), WAVES, EPI>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.through, tile.n0, K, N, out, smem, map)
 #define EXF_CASE(H, CUT) \
     case (CUT) * 16 + (H) / kQuantum: EXF_TILE(H, CUT); break
 #define EXF_WIDE_CASE(H, CUT)                      \

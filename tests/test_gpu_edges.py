@@ -163,6 +163,12 @@ def test_grouped_ffn_cut_tiles(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1770 + d)
 
 
+@pytest.mark.parametrize("counts", [[4096, 4096], [4095, 0, 200, 4097], [4096, 4100, 300]])
+def test_grouped_ffn_around_two_rounds(oracle, counts):
+    """512 tiles of the first contraction and a few more: hidden rows written through, by some experts only, by none."""
+    P._ffn_case(oracle, "bf16", counts, 64, 4096, 0, True, seed=1790)
+
+
 @pytest.mark.parametrize("T,d,f,E,k", [(700, 64, 192, 3, 1), (1500, 192, 320, 5, 2), (900, 320, 1088, 2, 2)])
 def test_grouped_ffn_fused(oracle, T, d, f, E, k):
     P._fused_case(oracle, T, d, f, E, E, k, 1, True, seed=1800 + T)
