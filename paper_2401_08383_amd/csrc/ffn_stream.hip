@@ -50,7 +50,7 @@ __device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int64_t wave
 
 // The stable counting sort of moe_dispatch for at most kInlineDispatchMax assignments, by one workgroup into LDS.  Loading
 // the ids costs the same memory round trip as loading finished offsets would, and the sort itself about a third of
-// the launch it replaces.  Segments (round, wavefront) are ascending assignment order, as in dispatch_small_kernel.
+// the launch it replaces.  Segments (round, wavefront) are ascending assignment order.
 // offs[e]: first sorted position of expert e, offs[E_local] = number kept; list[s]: assignment at position s.
 constexpr int kInlineSegments = kInlineDispatchMax / kWave;
 struct InlineDispatch {

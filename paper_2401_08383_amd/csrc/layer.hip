@@ -1,5 +1,5 @@
 // moe_layer_forward: the calls of one expert layer in sequence; a short batch is sorted by the first contraction's
-// workgroups instead of a launch of its own.
+// workgroups instead of a launch of its own, and a handful of tokens is routed by them as well.
 #include "ffn_common.hpp"
 
 extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
