@@ -347,8 +347,8 @@ struct GemmTile {
     uint32_t off_a[LA], off_w[LW];
     uint32_t frag_w[2], frag_a[2];  // LDS byte offsets of the operand fetches of the two K steps
     const unsigned char *act_b, *wgt_b;
-    uint32_t a_step;                // bytes of the activation operand from K tile to K tile
-    int ka_next, kw_next, nk;       // K tiles the pointers are at, K tiles of the reduction
+    int64_t a_step, a_back, w_back; // bytes of the activation operand from K tile to K tile, of both from the last one to the first
+    int a_left, w_left, nk;         // K tiles behind those the pointers are at, K tiles of the reduction
     unsigned char* smem;            // activation stages, then weight stages
     uint32_t smem_addr;
     int wave;
@@ -361,17 +361,26 @@ struct GemmTile {
     __device__ __forceinline__ void issue_w(uint32_t st, int i) { lds_dma_16B(wgt_b, off_w[i], smem_addr + SA * A_BYTES + st + group_w(i) * 1024); }
 
     // On to the next K tile of the reduction; behind the last one follows the first (see gemm_tile).
+    // (A loop of few MFMAs is bound by the issue of its other instructions, so the way back is kept and rings of equal depth share a
+    // counter: the 64 x 32 tile's K tile had 75 instructions, 58 of them scalar.)
     __device__ __forceinline__ void step_a()
     {
-        const bool wrap = ka_next + 1 == nk;
-        ka_next = wrap ? 0 : ka_next + 1;
-        act_b += wrap ? -static_cast<int64_t>(a_step) * (nk - 1) : static_cast<int64_t>(a_step);
+        const bool wrap = a_left == 0;
+        a_left = wrap ? nk - 1 : a_left - 1;
+        act_b += wrap ? a_back : a_step;
     }
     __device__ __forceinline__ void step_w()
     {
-        const bool wrap = kw_next + 1 == nk;
-        kw_next = wrap ? 0 : kw_next + 1;
-        wgt_b += wrap ? -static_cast<int64_t>(RB) * (nk - 1) : static_cast<int64_t>(RB);
+        const bool wrap = w_left == 0;
+        w_left = wrap ? nk - 1 : w_left - 1;
+        wgt_b += wrap ? w_back : static_cast<int64_t>(RB);
+    }
+    __device__ __forceinline__ void step_both()  // SA == SB: behind the first loads both operands are at one K tile
+    {
+        const bool wrap = a_left == 0;
+        a_left = wrap ? nk - 1 : a_left - 1;
+        act_b += wrap ? a_back : a_step;
+        wgt_b += wrap ? w_back : static_cast<int64_t>(RB);
     }
 
     // Stages of one operand's ring around a K tile: the one read now, the next one, the one whose refill is being completed.
@@ -421,8 +430,12 @@ struct GemmTile {
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // my operand fetches from this tile are complete
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
-                    if (STEADY || (flags & kThisA) != 0u) step_a();
-                    if (STEADY || (flags & kThisW) != 0u) step_w();
+                    if constexpr (SA == SB) {
+                        if (STEADY || (flags & kThisA) != 0u) step_both();
+                    } else {
+                        if (STEADY || (flags & kThisA) != 0u) step_a();
+                        if (STEADY || (flags & kThisW) != 0u) step_w();
+                    }
                 }
                 if (b * TN + a < ACC_HALF) mfma_16x16x32<true>(fw[ks][a], fa[b], acc[b][a]);
                 else mfma_16x16x32<false>(fw[ks][a], fa[b], acc[b][a]);
@@ -498,9 +511,11 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     // share panels in their L2, stay in step.)
     const int k0 = static_cast<int>(static_cast<unsigned>(blockIdx.x % kXcdCount) * static_cast<unsigned>(nk) / kXcdCount);
     g.nk = nk;
-    g.ka_next = k0;
-    g.kw_next = k0;
+    g.a_left = nk - 1 - k0;
+    g.w_left = nk - 1 - k0;
     g.a_step = HIDDEN_ACT ? kKTile / 8 * kHiddenRowBlock * 16 : RB;
+    g.a_back = -g.a_step * (nk - 1);
+    g.w_back = -static_cast<int64_t>(RB) * (nk - 1);
     g.act_b = uniform_ptr(reinterpret_cast<const unsigned char*>(act) + static_cast<size_t>(k0) * g.a_step);
     g.wgt_b = uniform_ptr(reinterpret_cast<const unsigned char*>(wexp) + static_cast<size_t>(k0) * RB);
 
