@@ -171,8 +171,8 @@ __device__ __forceinline__ int xcd_share(int n, int xcd, int& rot, int& begin)
 //   A compute unit takes in about 25 bytes a cycle of what its XCD's L2 holds, and that bounds a piece, not its MFMAs: every cut
 // goes where it leaves the fewer rows of operands, across the rows of the tile as long as these are more than its columns.
 // Both contractions, columns only in up to four pieces -> either way in up to eight: four experts of 1024 x 4096, 800 rows
-// 63.7 -> 47.5 us; one of 2048 x 8192, 130 rows 75.4 -> 56.8; eight of 1024 x 4096, 2000 rows 92.3 -> 80.9; 16 of them, 3062
-// rows (the second contraction alone is cut: 256 x 64 -> 128 x 128) 101.9 -> 98.2.
+// 63.7 -> 47.8 us; one of 2048 x 8192, 130 rows 75.4 -> 60.0; eight of 1024 x 4096, 2000 rows 92.3 -> 81.5; 16 of them, 3062
+// rows (the second contraction alone is cut: 256 x 64 -> 128 x 128) 101.9 -> 96.4.
 constexpr int kUnitsPerXcd = kComputeUnits / kXcdCount;
 __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E_local, int NT, int N, int max_rows, int wg,
                                             const RowMap& probe, Tile2D& out)
@@ -362,7 +362,8 @@ struct GemmTile {
 
     // On to the next K tile of the reduction; behind the last one follows the first (see gemm_tile).
     // (A loop of few MFMAs is bound by the issue of its other instructions, so the way back is kept and rings of equal depth share a
-    // counter: the 64 x 32 tile's K tile had 75 instructions, 58 of them scalar.)
+    // counter: the 64 x 32 tile's K tile had 75 instructions, 58 of them scalar, and has 58.  One expert of 2048 x 8192, 130 rows 61.0 ->
+    // 55.4 us; the large tiles gain as well, 32 of them, 16384 rows 1042 -> 1028.)
     __device__ __forceinline__ void step_a()
     {
         const bool wrap = a_left == 0;
