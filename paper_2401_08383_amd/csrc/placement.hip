@@ -55,7 +55,7 @@ struct MapRows {
             else v[i] = row(i)[min(lane, E - 1)];
         }
     }
-    // returns the bits of all parts seen
+    // returns all bits of the numbers
     __device__ __forceinline__ uint32_t store(unsigned char* to, int lane) const
     {
         uint32_t any = 0;
@@ -72,21 +72,99 @@ struct MapRows {
         }
         return any;
     }
+    // change(part, the other rows' part at its place)
+    template <typename Change>
+    __device__ __forceinline__ void each(const MapRows& other, Change change)
+    {
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            if constexpr (WIDE) {
+                change(v[i].x, other.v[i].x), change(v[i].y, other.v[i].y);
+                change(v[i].z, other.v[i].z), change(v[i].w, other.v[i].w);
+            } else {
+                change(v[i], other.v[i]);
+            }
+        }
+    }
+    // row n, a lane an expert (lanes past the last one get whatever is there)
+    __device__ __forceinline__ int row(int n, int lane) const
+    {
+        if constexpr (WIDE) {
+            const int4& x = v[n / 4];
+            const int at = 16 * (n % 4) + (lane >> 2);
+            const int a = __shfl(x.x, at, kWave), b = __shfl(x.y, at, kWave), c = __shfl(x.z, at, kWave), d = __shfl(x.w, at, kWave);
+            return (lane & 2) != 0 ? ((lane & 1) != 0 ? d : c) : ((lane & 1) != 0 ? b : a);
+        } else {
+            return v[n];
+        }
+    }
 };
 
-// Part numbers that do not fit seven bits: what counts is which source experts share a target's part, so the lowest of them
-// stands for the part (64 for a target whose part no source expert has).  One map, a lane an expert.
-__device__ __forceinline__ void relabel(const int32_t* __restrict__ row, int E, int lane, unsigned char* source, unsigned char* target)
+// Part numbers that do not fit seven bits (-1 for an expert without a place, the device ids of a large cluster).  Only which parts are
+// equal counts, so a wavefront renumbers those of a few maps at a time.  Where their codes differ in at most seven bits, these
+// bits are the numbers.  Otherwise the lowest source expert with the same part stands for it (64 for a target whose part no
+// source expert has), by the lanes that agree in each differing bit, a lane an expert.  Returns all bits of the numbers, or 128.
+// 50 maps of 3 x 64, us (parts below 128: 3.8): parts 128 to 135 4.3, -1 to 63 4.6, 0 to 7 and 256 to 263 4.5, -3 to 100 5.6, any
+// 8.7, where rows loaded once more, map by map, and looked at bit by bit in the order of memory took 6.8, 13.0, 7.1, 12.9 and 12.8;
+// 4096 of 24 x 64, parts -1 to 7, 27 and 117.
+constexpr int kRenumbered = 4;  // maps at a time
+template <bool WIDE>
+__device__ __forceinline__ uint32_t renumber(MapRows<kRenumbered, WIDE> (&rows)[2], int E, int lane, unsigned char* from, unsigned char* to)
 {
-    const unsigned from = static_cast<unsigned>(row[min(lane, E - 1)]), to = static_cast<unsigned>(row[E + min(lane, E - 1)]);
-    unsigned long long like_from = E == kWave ? ~0ull : (1ull << E) - 1ull, like_to = like_from;
-    for (int bit = 0; bit < 32 && __ballot(((from | to) >> bit) != 0u) != 0ull; ++bit) {
-        const unsigned long long set = __ballot(((from >> bit) & 1u) != 0u);
-        like_from &= ((from >> bit) & 1u) != 0u ? set : ~set;
-        like_to &= ((to >> bit) & 1u) != 0u ? set : ~set;
+    // Gray codes, their top bit moved to the bottom: parts near each other differ in few bits, on either side of zero as well
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        rows[h].each(rows[h], [](int& part, int) {
+            const uint32_t gray = static_cast<uint32_t>(part) ^ (static_cast<uint32_t>(part) >> 1);
+            part = static_cast<int>(gray << 1 | gray >> 31);
+        });
+    int first;
+    if constexpr (WIDE) first = __builtin_amdgcn_readfirstlane(rows[0].v[0].x);
+    else first = __builtin_amdgcn_readfirstlane(rows[0].v[0]);
+    uint32_t bits = 0;  // in which codes differ
+#pragma unroll
+    for (int h = 0; h < 2; ++h) rows[h].each(rows[h], [&](int& code, int) { bits |= static_cast<uint32_t>(code ^ first); });
+#pragma unroll
+    for (int off = 1; off < kWave; off *= 2) bits |= __shfl_xor(bits, off, kWave);
+    bits = __builtin_amdgcn_readfirstlane(bits);
+    if (__builtin_popcount(bits) <= 7) {
+        const MapRows<kRenumbered, WIDE> codes[2] = {rows[0], rows[1]};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) rows[h].each(codes[h], [](int& number, int) { number = 0; });
+#pragma unroll 1
+        for (uint32_t left = bits; left != 0u; left &= left - 1u) {
+            const int bit = __builtin_ctz(left);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) rows[h].each(codes[h], [&](int& number, int code) { number = number << 1 | (code >> bit & 1); });
+        }
+        return rows[0].store(from, lane) | rows[1].store(to, lane);
     }
-    source[lane] = static_cast<unsigned char>(like_from != 0ull ? __builtin_ctzll(like_from) : kWave + 1);
-    target[lane] = static_cast<unsigned char>(like_to != 0ull ? __builtin_ctzll(like_to) : kWave);
+    int a[kRenumbered], b[kRenumbered];
+    uint64_t like_a[kRenumbered], like_b[kRenumbered];  // source experts with the same part
+#pragma unroll
+    for (int n = 0; n < kRenumbered; ++n) {
+        a[n] = rows[0].row(n, lane);
+        b[n] = rows[1].row(n, lane);
+        like_a[n] = like_b[n] = E == kWave ? ~0ull : (1ull << E) - 1ull;
+    }
+#pragma unroll 1
+    for (uint32_t left = bits; left != 0u; left &= left - 1u) {
+        const int bit = __builtin_ctz(left);
+#pragma unroll
+        for (int n = 0; n < kRenumbered; ++n) {
+            const int64_t all_a = static_cast<int>(__builtin_amdgcn_sbfe(a[n], bit, 1));  // the bit in all places
+            const int64_t all_b = static_cast<int>(__builtin_amdgcn_sbfe(b[n], bit, 1));
+            const uint64_t set = __ballot(all_a != 0);
+            like_a[n] &= ~(set ^ static_cast<uint64_t>(all_a));
+            like_b[n] &= ~(set ^ static_cast<uint64_t>(all_b));
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < kRenumbered; ++n) {
+        from[n * kMapBytes + lane] = static_cast<unsigned char>(like_a[n] != 0ull ? __builtin_ctzll(like_a[n]) : kWave + 1);
+        to[n * kMapBytes + lane] = static_cast<unsigned char>(like_b[n] != 0ull ? __builtin_ctzll(like_b[n]) : kWave);
+    }
+    return 128u;
 }
 
 // Bytes that say where a target's part is the source's.  FEW (all parts below eight): ones; the source's part picks one of eight
@@ -237,10 +315,20 @@ __global__ __launch_bounds__(kScoreThreads, 3) void placement_score_kernel(const
     load_counts(first_counts);
     unsigned char *from = maps[group][0], *to = maps[group][1];
     auto store_maps = [&](int64_t pass) {
-        const uint32_t any = rows[0].store(from + piece * OWN * kMapBytes, lane) | rows[1].store(to + piece * OWN * kMapBytes, lane);
-        if (__ballot(any >= 128u) != 0ull) {
-            __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses are done in order)
-            for (int n = piece * OWN; n < piece * OWN + OWN; ++n) relabel(row_of(pass + group * GROUP_MAPS + n), E, lane, from + n * kMapBytes, to + n * kMapBytes);
+        unsigned char *own_from = from + piece * OWN * kMapBytes, *own_to = to + piece * OWN * kMapBytes;
+        uint32_t any = rows[0].store(own_from, lane) | rows[1].store(own_to, lane);
+        if (__builtin_expect(__ballot(any >= 128u) == 0ull, 1)) return any;
+        any = 0;  // (a wavefront's LDS accesses are done in order)
+        if constexpr (OWN == kRenumbered) {
+            any = renumber<WIDE>(rows, E, lane, own_from, own_to);
+        } else {  // loaded again, from the L2: holding all rows until here would spill registers of every launch
+#pragma unroll 1
+            for (int n0 = 0; n0 < OWN; n0 += kRenumbered) {
+                MapRows<kRenumbered, WIDE> some[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) some[h].load([&](int n) { return row_of(pass + group * GROUP_MAPS + piece * OWN + n0 + n) + h * E; }, E, lane);
+                any |= renumber<WIDE>(some, E, lane, own_from + n0 * kMapBytes, own_to + n0 * kMapBytes);
+            }
         }
         return any;
     };

@@ -115,6 +115,9 @@ def test_gpu_scores_candidate_batches_exactly(L, E, G, Bn):
     (3, 1, 17, 0, 1, 20), (2, 3, 16, 0, 8, 28), (4, 4, 15, 0, 9, 20), (3, 16, 33, 0, 8, 29), (3, 17, 31, 0, 128, 28), (2, 63, 129, 0, 64, 20),
     (3, 64, 40, -2, 129, 20),               # parts that do not fit seven bits
     (2, 64, 20, 1 << 20, (1 << 20) + 9, 30),
+    # their codes differ in no bit, in three, in seven, in eight, in all; whole and cut rows of maps; few maps and many
+    (3, 64, 17, 500, 501, 20), (4, 63, 33, 128, 136, 20), (3, 64, 50, -1, 64, 20), (3, 63, 50, -1, 65, 20), (2, 61, 19, -(1 << 31), 1 << 31, 20),
+    (24, 64, 577, -1, 8, 20), (24, 63, 577, -64, 64, 20), (24, 64, 577, -3, 101, 29), (24, 7, 577, -(1 << 31), 1 << 31, 20),
     (24, 64, 561, 0, 8, 20), (24, 20, 561, 0, 4, 62),   # one wavefront for 32 candidates; counts of more than 28 bits
     (256, 4, 900, 0, 4, 29), (256, 5, 900, 0, 4, 20),   # several passes of a workgroup
 ])
