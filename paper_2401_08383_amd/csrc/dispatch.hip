@@ -263,39 +263,42 @@ __device__ __forceinline__ void move_rows(const uint4* __restrict__ x, uint4* __
     }
 }
 
-// Count, scan and placement of a list of at most kDirectMax assignments in one launch: every workgroup counts the WHOLE list
-// for itself - ids from the L2, one LDS atomic an id, into eight copies a counter so that few experts do not meet at one
-// address; the low half of a counter is the total, the high half the assignments in front of the workgroup's own slice -
-// and ranks its slice by the lanes below that hold the same expert and the wavefronts below: the same stable permutation as
-// the chunked kernels.  Reading the list in every workgroup takes less than a launch of its own for the counts.  Index maps, one
-// workgroup of 1024 threads before: 8192 assignments 6.9 us with 8 experts, 9.5 with 64, now 4.7 either way; 16384 14.9 and 5.7;
-// 24000 (two launches) 7.9 and 6.5, but 32768 of 64 experts with 8 local ones 7.1 and 9.3.  With rows (two launches, slices of 32 before):
-// 3062 x 1024 9.6 and 6.4, 512 x 4096 16.0 and 7.7; slices of 8 rows also spread few rows over the chip; from 4096 assignments on
-// the list costs more than that (10000 x 512: 12.7 with 8, 10.1 with 16, 10.0 in two launches; 8192 x 512 with 8 of 64 experts
-// local 10.4, 7.8 and 7.5).
-constexpr int64_t kDirectMaps = 20480, kDirectRows = 7168, kDirectRows8 = 4096;  // (half a counter holds 65535)
+// Count, scan and placement of a short list (at most kDirectMaps assignments, kDirectRows with rows) in one launch: every
+// workgroup counts the WHOLE list for itself - ids from the L2, one LDS atomic an id, into eight copies a counter so that few
+// experts do not meet at one address; the low half of a counter is the total, the high half the assignments in front of the
+// workgroup's own slice - and ranks its slice by the lanes below that hold the same expert and the wavefronts below: the same
+// stable permutation as the chunked kernels.  Reading the list in every workgroup takes less than a launch of its own for the counts.
+// What a launch this short waits for is instructions and memory round trips, so only the wavefronts that hold assignments of the
+// slice add the copies up, the expert map is asked for with the ids and looked up across lanes, and a thread asks for as many
+// ids as it needs (with all 16 wavefronts adding, the map looked up in memory and eight ids a thread always: 1024 assignments 4.4
+// to 4.8 us).
+//   Index maps, us, in one workgroup of 1024 threads (up to 16384; beyond, two launches) and now, with 1, 8 and 64 experts: 64
+// assignments 3.0, 3.7, 4.7 and 2.4, 2.4, 2.5; 1024 3.1, 3.8, 5.0 and 2.6, 2.8, 2.9; 4096 3.3, 4.6, 6.1 and 3.1, 3.1, 3.3; 16384 7.8,
+// 13.0, 17.7 and 5.0, 4.6, 4.7; 20480 7.2, 6.9, 7.9 and 5.8, 5.6, 5.7, with 8 of 64 experts local 7.2 and 6.2.
+//   With rows, two launches with slices of 32 and now, 8 experts: 64 x 1024 7.1 and 4.1; 1024 x 4096 18.2 and 7.7; 3062 x 1024 10.2 and
+// 6.2; 5000 x 1024 10.7 and 8.9; 7168 x 1024 11.4 and 10.8.  Slices of 8 rows spread few rows over the chip; from 4096 assignments on the list
+// costs more than that.  Where the rows are short the list is most of it, and two launches read it once: 7168 x 64 6.2 and 6.5, with
+// 8 of 64 experts local 6.4 and 6.8, 6144 x 64 6.2 and 6.0; 7168 x 256 6.5 and 6.8, 7168 x 504 9.2 and 8.4.
+constexpr int64_t kDirectMaps = 20480, kDirectRows = 7168, kDirectShortRows = 6144, kDirectRows8 = 4096;  // (half a counter holds 65535)
+constexpr int kDirectRowVecs = 48;  // 16-byte pieces of a row that is not short
 constexpr int kDirectCopies = 8;
-template <int THREADS>
+template <int SLICE>
 struct DirectCounts {
+    static constexpr int WAVES = SLICE > kWave ? SLICE / kWave : 1;  // that hold assignments of the slice
     uint32_t count[EXF_MAX_EXPERTS][kDirectCopies];
-    unsigned short seg[THREADS / kWave][EXF_MAX_EXPERTS];  // the slice's assignments, per wavefront and expert
+    unsigned short seg[WAVES][EXF_MAX_EXPERTS];  // the slice's assignments, per wavefront and expert
 };
-// Sorted position of assignment begin + thread (-1: not kept, or not below min(end, A)).
-template <int THREADS>
+// Sorted position of assignment begin + thread, thread < SLICE (-1: not kept, or past the list).  U: ids of a thread in flight.
+template <int THREADS, int SLICE, int U>
 __device__ __forceinline__ int place_direct(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ expert_map, int A, int E, int E_local, int begin,
-                                            int end, DirectCounts<THREADS>& d, int32_t* __restrict__ expert_counts, int32_t* __restrict__ expert_offsets)
+                                            DirectCounts<SLICE>& d, int32_t* __restrict__ expert_counts, int32_t* __restrict__ expert_offsets)
 {
-    constexpr int WAVES = THREADS / kWave, U = 8;  // ids of a thread in flight
+    constexpr int WAVES = DirectCounts<SLICE>::WAVES;
+    static_assert(SLICE <= THREADS, "a thread places one assignment at most");
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    auto local = [&](int id, bool there) {
-        const bool ok = there && id >= 0 && id < E;
-        int m = id;
-        if (expert_map != nullptr) m = expert_map[ok ? id : 0];
-        return ok && m >= 0 && m < E_local ? m : -1;
-    };
+    const int map = expert_map != nullptr ? expert_map[min(lane, E - 1)] : lane;  // lane = expert
     const int mine = begin + static_cast<int>(threadIdx.x);
-    const bool in_slice = mine < min(end, A);
     const int id_mine = topk_idx[min(mine, A - 1)];
     int id[U];
     auto load = [&](int i0) {
@@ -304,11 +307,20 @@ __device__ __forceinline__ int place_direct(const int32_t* __restrict__ topk_idx
     };
     load(0);
     for (int i = threadIdx.x; i < static_cast<int>(sizeof(d) / 4); i += THREADS) reinterpret_cast<uint32_t*>(&d)[i] = 0u;
+    auto local = [&](int id, bool there) {
+        const bool ok = there && id >= 0 && id < E;
+        int m = id;
+        if (expert_map != nullptr) m = __shfl(map, ok ? id : 0, kWave);
+        return ok && m >= 0 && m < E_local ? m : -1;
+    };
     __syncthreads();
-    const int e = local(id_mine, in_slice);
-    const unsigned long long like = same_expert_lanes(e, E_local), below = (1ull << lane) - 1ull;
-    const int rank = __popcll(like & below);
-    if (e >= 0 && rank == 0) d.seg[wave][e] = static_cast<unsigned short>(__popcll(like));
+    int e = -1, rank = 0;
+    if (wave < WAVES) {
+        e = local(id_mine, static_cast<int>(threadIdx.x) < SLICE && mine < A);
+        const unsigned long long like = same_expert_lanes(e, E_local), below = (1ull << lane) - 1ull;
+        rank = __popcll(like & below);
+        if (e >= 0 && rank == 0) d.seg[wave][e] = static_cast<unsigned short>(__popcll(like));
+    }
     for (int i0 = 0; i0 < A; i0 += U * THREADS) {
         int q[U];
 #pragma unroll
@@ -319,6 +331,7 @@ __device__ __forceinline__ int place_direct(const int32_t* __restrict__ topk_idx
             if (q[u] >= 0) atomicAdd(&d.count[q[u]][lane & (kDirectCopies - 1)], i0 + u * THREADS + static_cast<int>(threadIdx.x) < begin ? 0x10001u : 1u);
     }
     __syncthreads();
+    if (wave >= WAVES) return -1;
     // every wavefront for itself, lane = expert
     uint32_t sum = 0;
 #pragma unroll
@@ -338,18 +351,19 @@ __device__ __forceinline__ int place_direct(const int32_t* __restrict__ topk_idx
     return e >= 0 ? start + rank : -1;
 }
 
-// Index maps: a slice of one assignment a thread.
-constexpr int kDirectThreads = 1024;
+// Index maps: a slice of 256 assignments.
+constexpr int kDirectThreads = 1024, kDirectSlice = 256;
+template <int U>
 __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ expert_map,
-                                                                         int A, int E, int E_local, int slice, int32_t* __restrict__ expert_counts,
+                                                                         int A, int E, int E_local, int32_t* __restrict__ expert_counts,
                                                                          int32_t* __restrict__ expert_offsets, int32_t* __restrict__ src_of_sorted,
                                                                          int32_t* __restrict__ sorted_of_src)
 {
-    __shared__ DirectCounts<kDirectThreads> d;
-    const int begin = static_cast<int>(blockIdx.x) * slice;
-    const int pos = place_direct<kDirectThreads>(topk_idx, expert_map, A, E, E_local, begin, begin + slice, d, expert_counts, expert_offsets);
+    __shared__ DirectCounts<kDirectSlice> d;
+    const int begin = static_cast<int>(blockIdx.x) * kDirectSlice;
+    const int pos = place_direct<kDirectThreads, kDirectSlice, U>(topk_idx, expert_map, A, E, E_local, begin, d, expert_counts, expert_offsets);
     const int a = begin + static_cast<int>(threadIdx.x);
-    if (static_cast<int>(threadIdx.x) < slice && a < A) {
+    if (threadIdx.x < kDirectSlice && a < A) {
         if (pos >= 0) src_of_sorted[pos] = a;
         sorted_of_src[a] = pos;
     }
@@ -363,11 +377,11 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_direct_rows_kernel(cons
                                                                             int32_t* __restrict__ sorted_of_src, const uint4* __restrict__ x, int k,
                                                                             int vec_per_row, uint4* __restrict__ x_sorted)
 {
-    __shared__ DirectCounts<kDispThreads> d;
+    __shared__ DirectCounts<MOVE> d;
     __shared__ int pos_s[MOVE];
     touch_arguments<88>();
     const int begin = static_cast<int>(blockIdx.x) * MOVE;
-    const int pos = place_direct<kDispThreads>(topk_idx, expert_map, A, E, E_local, begin, begin + MOVE, d, expert_counts, expert_offsets);
+    const int pos = place_direct<kDispThreads, MOVE, 8>(topk_idx, expert_map, A, E, E_local, begin, d, expert_counts, expert_offsets);
     if (threadIdx.x < MOVE) {
         const int a = begin + static_cast<int>(threadIdx.x);
         if (pos >= 0) src_of_sorted[pos] = a;
@@ -544,12 +558,16 @@ static int dispatch_run(const void* x, const int32_t* topk_idx, const int32_t* e
     const int n_blocks = static_cast<int>(dispatch_blocks(A));
     const int vec_per_row = d * (dt == EXF_BF16 ? 2 : 4) / 16;
     if (A > 0 && A <= kDirectMaps && x_sorted == nullptr) {  // one launch, the workspace stays untouched
-        constexpr int slice = 256;
-        hipLaunchKernelGGL(dispatch_direct_kernel, dim3(static_cast<unsigned>((A + slice - 1) / slice)), dim3(kDirectThreads), 0, s, topk_idx, expert_map,
-                           static_cast<int>(A), E, E_local, slice, expert_counts, expert_offsets, src_of_sorted, sorted_of_src);
+#define EXF_LAUNCH_DIRECT(U)                                                                                                                           \
+    hipLaunchKernelGGL(dispatch_direct_kernel<U>, dim3(static_cast<unsigned>((A + kDirectSlice - 1) / kDirectSlice)), dim3(kDirectThreads), 0, s,        \
+                       topk_idx, expert_map, static_cast<int>(A), E, E_local, expert_counts, expert_offsets, src_of_sorted, sorted_of_src)
+        if (A <= kDirectThreads) EXF_LAUNCH_DIRECT(1);
+        else if (A <= 4 * kDirectThreads) EXF_LAUNCH_DIRECT(4);
+        else EXF_LAUNCH_DIRECT(8);
+#undef EXF_LAUNCH_DIRECT
         return check_launch("moe_dispatch");
     }
-    if (A > 0 && A <= kDirectRows && x_sorted != nullptr) {
+    if (A > 0 && x_sorted != nullptr && A <= (vec_per_row < kDirectRowVecs ? kDirectShortRows : kDirectRows)) {
 #define EXF_LAUNCH_DIRECT(MOVE)                                                                                                                        \
     hipLaunchKernelGGL(dispatch_direct_rows_kernel<MOVE>, dim3(static_cast<unsigned>((A + MOVE - 1) / MOVE)), dim3(kDispThreads), 0, s, topk_idx,     \
                        expert_map, static_cast<int>(A), E, E_local, expert_counts, expert_offsets, src_of_sorted, sorted_of_src,                     \

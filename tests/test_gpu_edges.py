@@ -183,9 +183,11 @@ def test_exact_ffn_ragged(oracle, counts, d, f):
 
 # ----------------------------------------------------------------------------- dispatch: every workgroup counts the whole list
 @pytest.mark.parametrize("T,k,d,E,E_local", [
-    (1, 1, 8, 1, 1), (7, 1, 72, 3, 3), (9, 2, 1032, 64, 64), (2048, 2, 64, 8, 8), (4097, 1, 136, 40, 7), (3584, 2, 16, 64, 64), (7169, 1, 16, 64, 64)])
+    (1, 1, 8, 1, 1), (7, 1, 72, 3, 3), (9, 2, 1032, 64, 64), (2048, 2, 64, 8, 8), (4097, 1, 136, 40, 7), (3584, 2, 16, 64, 64), (7169, 1, 16, 64, 64),
+    (6144, 1, 376, 9, 9), (6145, 1, 376, 9, 9), (7168, 1, 384, 2, 2), (7169, 1, 384, 2, 2)])
 def test_dispatch_rows_in_one_launch(oracle, T, k, d, E, E_local):
-    """Slices of 8 and of 16 assignments, cut by the end of the list, ragged rows, dropped assignments; the first size past them."""
+    """Slices of 8 and of 16 assignments, cut by the end of the list, ragged rows, dropped assignments; the first size past them, for
+    short rows and for others."""
     _say(f"dispatch rows T={T} k={k} d={d} E={E} E_local={E_local}")
     g = syn.rng(2000 + T)
     x = syn.quantize(g.standard_normal((T, d), dtype=np.float32), "bf16")
@@ -197,7 +199,8 @@ def test_dispatch_rows_in_one_launch(oracle, T, k, d, E, E_local):
     P._run_dispatch(oracle, x, idx, E, E_local, expert_map, "bf16")
 
 
-@pytest.mark.parametrize("A,E,E_local", [(1, 1, 1), (255, 64, 64), (257, 2, 2), (20480, 64, 9), (20481, 64, 64), (20479, 1, 1)])
+@pytest.mark.parametrize("A,E,E_local", [(1, 1, 1), (255, 64, 64), (257, 2, 2), (20480, 64, 9), (20481, 64, 64), (20479, 1, 1),
+                                         (1023, 7, 7), (1024, 64, 1), (1025, 2, 2), (4096, 33, 33), (4097, 64, 8), (8193, 5, 5)])
 def test_dispatch_maps_in_one_launch(oracle, A, E, E_local):
     P.test_dispatch_index_only_short_lists(oracle, A, E, E_local)
 
