@@ -31,6 +31,7 @@ namespace exf {
 constexpr int kScoreWaves = 4;
 constexpr int kScoreThreads = kScoreWaves * kWave;
 constexpr int kScoreWorkgroups = 768;      // three workgroups fill a compute unit's registers
+constexpr int kScoreShare = 32;            // of an XCD at least: one per compute unit
 constexpr int kDigits = 4, kDigitBits = 7; // of a count, 28 bits of it at a time
 constexpr int kCountBits = kDigits * kDigitBits;
 constexpr int kSourceRow = kDigits * EXF_MAX_EXPERTS;  // bytes of a source expert in LDS: [digit][target expert]
@@ -256,10 +257,14 @@ __global__ __launch_bounds__(kScoreThreads, 3) void placement_score_kernel(const
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int group = wave / SPLIT, piece = wave % SPLIT;
-    // the layer pairs of the same candidates run on one XCD, one after the other: a row two pairs share comes from its L2
+    // Workgroups are numbered candidates first, pairs second, and an XCD takes consecutive ones: a row that two pairs share mostly comes
+    // from its L2.  Equal shares however few candidates there are, but one per compute unit at least: spread thinner, pairs of the same
+    // maps read these from memory once per XCD (16 maps of 12 x 64: 3.9 us, 3.7 now).  (A whole XCD for each group of candidates: one map of
+    // 100 x 64 6.1 us, now 4.1; 200 maps of them, parts 0 to 63, 19.8 and 8.7.)
     const int xcd = static_cast<int>(blockIdx.x % 8u), rest = static_cast<int>(blockIdx.x / 8u);
-    const int l = rest % (L - 1);
-    const int64_t first = static_cast<int64_t>(rest / (L - 1) * 8 + xcd) * passes * MAPS;
+    const int item = xcd * static_cast<int>(gridDim.x / 8u) + rest;
+    const int l = item % (L - 1);
+    const int64_t first = static_cast<int64_t>(item / (L - 1)) * passes * MAPS;
     if (first >= B) return;
     const int64_t last = min(static_cast<int64_t>(B), first + static_cast<int64_t>(passes) * MAPS);
     // rows of both layers of the maps from the b-th on
@@ -416,7 +421,8 @@ static void launch_scores(const int64_t* counts, const int32_t* placements, int 
     const int64_t all = (static_cast<int64_t>(B) + MAPS - 1) / MAPS;
     const int passes = static_cast<int>((all * (L - 1) + kScoreWorkgroups - 1) / kScoreWorkgroups);  // of a workgroup
     const int64_t groups = (all + passes - 1) / passes;
-    const dim3 grid(static_cast<unsigned>((groups + 7) / 8 * 8 * (L - 1)));
+    const int64_t share = std::max<int64_t>((groups * (L - 1) + 7) / 8, kScoreShare);  // workgroups of an XCD
+    const dim3 grid(static_cast<unsigned>(share * 8));
     if (E % 4 == 0 && aligned16(placements) && aligned16(counts))
         hipLaunchKernelGGL((placement_score_kernel<SPLIT, SETS, true>), grid, dim3(kScoreThreads), 0, stream, counts, placements, B, L, E, passes, local);
     else
