@@ -238,7 +238,7 @@ __device__ __forceinline__ void contract(const unsigned char* digits, const unsi
 // (i, p) and a column per map.  The counts' digits lie in LDS in operand order; a lane builds its part of the other operand in
 // registers: it holds the parts of 16 source experts (its quarter of the wavefront's) and of all target experts of one map.
 // Sums are exact in 32 bits (4096 * 127 * 128 < 2^31).  Counts of 2^28 and more take further rounds over their higher bits, as many as
-// they have (333 maps of 6 x 33, counts of up to 28 bits 4.1 us, of up to 56 5.9; always three rounds 8.0).
+// they have (333 maps of 6 x 33, counts of up to 28 bits 4.5 us, of up to 56 6.0; 6.3 with the counts loaded again, always three rounds 8.0).
 // SPLIT wavefronts share SETS x 16 candidates and take a part of the source experts each (a small batch), or every wavefront
 // has its own.
 // 4096 maps of 24 layers x 64 experts: 13.3 us for 2, 4 or 8 parts (walking the matching source experts of every target: 58.6,
@@ -354,10 +354,15 @@ __global__ __launch_bounds__(kScoreThreads, 3) void placement_score_kernel(const
         bool few = true, above = more;  // counts have bits above these
         for (int shift = 0; shift == 0 || (above && shift < 64); shift += kCountBits) {
             if (more && (shift > 0 || pass > first)) {  // (the same in all wavefronts)
-                uint64_t c[ITEMS][4];
-                load_counts(c);
-                __syncthreads();  // (others may still read the digits)
-                above = cut_counts(c, shift);
+                if constexpr (SPLIT > 1) {  // (one pass: the counts are still in registers)
+                    __syncthreads();
+                    above = cut_counts(first_counts, shift);
+                } else {
+                    uint64_t c[ITEMS][4];
+                    load_counts(c);
+                    __syncthreads();  // (others may still read the digits)
+                    above = cut_counts(c, shift);
+                }
             } else if (SPLIT > 1) {
                 __syncthreads();
             }

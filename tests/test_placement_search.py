@@ -120,6 +120,7 @@ def test_gpu_scores_candidate_batches_exactly(L, E, G, Bn):
     (24, 64, 577, -1, 8, 20), (24, 63, 577, -64, 64, 20), (24, 64, 577, -3, 101, 29), (24, 7, 577, -(1 << 31), 1 << 31, 20),
     (24, 64, 561, 0, 8, 20), (24, 20, 561, 0, 4, 62),   # one wavefront for 32 candidates; counts of more than 28 bits
     (256, 4, 900, 0, 4, 29), (256, 5, 900, 0, 4, 20),   # several passes of a workgroup
+    (2, 33, 1, 0, 8, 57), (6, 64, 33, -1, 64, 62),   # three rounds over the counts of four wavefronts with the same candidates
     (33, 8, 16, 0, 8, 20), (34, 9, 16, 0, 8, 20), (100, 64, 1, 0, 8, 20), (101, 63, 200, 0, 64, 20),  # shares of the XCDs: one, part of a second, several
 ])
 def test_gpu_scores_at_the_edges_of_the_operand(L, E, Bn, low, high, bits):
