@@ -658,21 +658,25 @@ static int launch_stream(const StreamGemm& p, hipStream_t stream)
 }
 
 // Columns per block, by a model of the launch (blocks of 8 columns: one row of 4096 x 1024 has 128 of them for 256 workgroups
-// instead of 64 of 16, the layer of one token 14.2 us and 13.6): with q blocks per workgroup it runs ceil(q)/q times as long as its
-// bytes take (the workgroups' shares differ by a block), and the activations, which every block reads
-// again, weigh about 0.6 of their share of the weights (fitted to 9 shapes of 1 to 617 tokens: it picks the fastest
-// or one within 5 %).  Blocks of 8 columns up to kFewAssignments only: one expert of 1024 x 4096, 60 rows 22.9 us with
-// blocks of 16 and 21.8, but 70 rows 24.9 and 29.3; four of 512 x 2048, 120 rows 18.5 and 20.7.
+// instead of 64 of 16, the layer of one token 14.2 us and 13.6): a workgroup has ceil(q) blocks, and the activations, which every block
+// reads again, weigh about 0.6 of as many bytes of weights (fitted to 9 shapes of 1 to 617 tokens: it picks the fastest or one within
+// 5 %).  A single expert's row tiles are known and counted: blocks of up to 32 columns have tiles of 32 rows, so more rows are twice the
+// blocks (one expert of 2048 x 8192, 40 to 64 rows 45.5 us without them - its second contraction in 512 blocks of 8 columns - and
+// 40.3; of 512 x 2048 15.3 and 14.3).  Among several, blocks of 8 columns only where an expert's rows hardly exceed a tile: up to
+// kFewAssignments in all (four experts of 512 x 2048, 120 rows 20.7 us with them and 18.5) and 28 an expert (two of 768 x 3072, 60
+// rows 23.0 and 20.4; 48 rows 16.4 and 16.9).
 static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
 {
     const double A = p.max_rows, E = p.E_local;
     const double touched = E * (1.0 - exp(A * log1p(-1.0 / E)));  // experts with rows, if A rows fall on E experts at random
-    const double act_rows = 8.0 * ceil(1.3 * A / touched / 8.0);
+    const bool one = p.E_local == 1 && p.max_rows <= kFewAssignments;
     int best = 8;
     double best_cost = 1e300;
-    for (int c = 8; c >= (p.max_rows > kFewAssignments ? 2 : 1); c /= 2) {  // (in eights)
-        const double q = touched * (p.N / (8 * c)) / kStreamGrid;
-        const double cost = ceil(q) / q * (1.0 + 0.6 * act_rows / (8 * c));
+    for (int c = 8; c >= (one || (p.max_rows <= kFewAssignments && 1.125 * A / touched <= 8 * stream_max_ar(1)) ? 1 : 2); c /= 2) {  // (in eights)
+        const double tiles = one ? ceil(A / (8 * stream_max_ar(c))) : 1.0;
+        const double act_rows = 8.0 * ceil((one ? A / tiles : 1.3 * A / touched) / 8.0);
+        const double q = touched * tiles * (p.N / (8 * c)) / kStreamGrid;
+        const double cost = ceil(q) * (8 * c + 0.6 * act_rows);
         if (cost < best_cost) {
             best_cost = cost;
             best = c;
