@@ -189,21 +189,27 @@ bool statistics_direct(const int32_t* trace, const int32_t* placement, int L, in
     return true;
 }
 
-// The chunked kernels take longer the more layers and experts there are, this one nearly only by tokens, until the pairs are more than
-// the compute units.  Chunked and direct, us: 4 x 20000, 32 experts 7.3 and 5.0; 9 x 50000, 8 experts 7.7 and 9.1; 13 x 50000, 24
-// experts 9.4 and 8.6, 13 x 100000, 64 experts 15.8 and 14.4; 16 x 100000, 8 experts 14.3 and 13.6, 20 x 100000, 64 experts
-// 33.5 and 15.8; 24 x 8192, 64 experts 29.3 and 8.6, 24 x 100000 37.4 and 25.8, 24 x 50000, 8 experts 15.3 and 14.2.
-static int64_t most_hop_tokens(int L, int E)
+// A pair's workgroup takes 3 to 4 us and 0.1 us for 1000 tokens, and again that for every further set of pairs that the compute units
+// hold (253 pairs of 23 layers at once, 276 of 24 two to a unit).  The chunked kernels take longer the more layers and experts there
+// are and hardly by tokens, so each range of layers has its line.  Chunked and direct at it, us: 4 x 20000, 32 experts 7.3 and 5.0, 9 x
+// 50000, 8 experts 7.7 and 9.1; 13 x 50000, 24 experts 9.4 and 8.6, 13 x 100000, 64 experts 15.8 and 14.4; with 4, 16 and 64 experts 16 x
+// 106496 14.8, 19.6, 24.6 and 14.0, 14.4, 16.0, 19 x 106496 15.3, 17.7, 28.2 and 14.1, 14.5, 16.5, 23 x 106496 17.9, 20.6, 38.7 and 14.9,
+// 15.3, 17.4; 24 x 49152, 8 experts 14.7 and 12.3, 24 x 90112, 24 experts 23.5 and 21.0, 24 x 131072, 48 experts 34.7 and 30.2; 32 layers
+// of these 17.0 and 14.4, 27.2 and 25.4, 38.0 and 37.5.
+//   Beyond, every pair costs a workgroup's start while the chunked kernels' cost per pair shrinks with the experts: 64 x 16384, 4, 12
+// and 64 experts 20.5, 26.1, 61.8 and 22.8, 24.9, 39.1; 100 x 8192, 4, 24 and 64 experts 35.0, 65.2, 123.3 and 48.0, 59.3, 74.4; shorter
+// traces need more of them (80 x 1000, 24 experts a tenth longer, 80 x 4000 a twentieth shorter).  255 x 4000, 32 experts 349 and 591.
+static bool few_hop_tokens(int L, int64_t N, int E)
 {
-    if (L < 12) return 32768;
-    if (L < 16) return E >= 40 ? 81920 : 49152;
-    if (L < 24) return 106496;
-    if (L > 32) return L <= 100 ? 16384 : 0;  // (100 x 10000, 64 experts 131 and 84; 255 x 4000, 32 experts 349 and 591)
-    return E >= 40 ? 131072 : (E >= 24 ? 90112 : 49152);
+    if (L < 12) return N <= 32768;
+    if (L < 16) return N <= (E >= 40 ? 81920 : 49152);
+    if (L < 24) return N <= 106496;
+    if (L > 32) return L <= 100 && N <= 16384 && E >= (N < 2048 ? 1.0 : 0.7) * (L - 48);
+    return N <= (E >= 40 ? 131072 : (E >= 24 ? 90112 : 49152));
 }
 bool multihop_direct(const int32_t* trace, int L, int64_t N, int E, int64_t* counts, float* cond_prob, hipStream_t stream)
 {
-    if (!pair_trace_fits(L, N) || N > most_hop_tokens(L, E)) return false;
+    if (!pair_trace_fits(L, N) || !few_hop_tokens(L, N, E)) return false;
     launch_pairs<true>(L * (L - 1) / 2, trace, nullptr, L, N, E, counts, nullptr, cond_prob, nullptr, nullptr, stream);
     return true;
 }

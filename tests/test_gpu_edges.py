@@ -65,6 +65,14 @@ def test_multihop_blocks(L, N, E):
     Q.test_affinity_multihop_parity(L, N, E)
 
 
+# the last trace in one launch and the first in chunks, for each range of layers and experts
+@pytest.mark.parametrize("L,N,E", [(2, 32768, 63), (11, 32769, 5), (12, 81920, 40), (15, 81921, 41), (13, 49152, 39), (14, 49153, 8), (16, 106496, 16), (23, 106497, 7),
+                                   (24, 49152, 23), (26, 49153, 2), (25, 90112, 24), (32, 90113, 39), (24, 131072, 40), (27, 131073, 64), (33, 16384, 1), (34, 16385, 9),
+                                   (58, 2047, 10), (58, 2047, 9), (58, 2048, 7), (58, 2048, 6), (100, 2048, 37), (101, 2048, 64)])
+def test_multihop_either_side_of_one_launch(L, N, E):
+    Q.test_affinity_multihop_parity(L, N, E)
+
+
 @pytest.mark.parametrize("L,N,E", [(5, 1100003, 3), (8, 430001, 5), (12, 250000, 2), (13, 200003, 9), (16, 250001, 64)])
 def test_multihop_blocks_of_few_layers(L, N, E):
     """Traces of few layers that are long enough for the blocks."""
