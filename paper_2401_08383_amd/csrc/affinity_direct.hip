@@ -2,6 +2,8 @@
 // counts up in a second launch; where a trace is short, that launch (its start, its gap and its round trip to memory: 4 to 5 us) and
 // the clearing and writing of the partials are most of the time.  Here a workgroup takes a whole layer pair (counts) or a
 // whole layer (locality, transfers), however little of the chip that fills, and writes final results.
+#include <algorithm>
+
 #include "trace_tile.hpp"
 
 namespace exf {
@@ -286,12 +288,14 @@ __global__ __launch_bounds__(kPairThreads) void locality_direct_kernel(const int
     }
 }
 
-// (Two launches and one, us: 2 x 8192 4.7 and 3.7, 2 x 11000 4.6 and 5.0; 12 x 8192 7.5 and 3.9, 12 x 28000 7.7 and 7.7; 24 x 8192 10.4
-// and 3.9, 24 x 50000 11.5 and 11.6.)
+// A layer's workgroup takes 3 us and 1.1 for every 8192 tokens after the first ones, with home devices 3.7 and 1.3; the chunked kernels longer
+// the more layers there are.  Two launches and one at the line, us: locality 2 x 8192 4.3 and 3.1, 3 x 9792 4.9 and 4.3, 24 x 43392 8.8
+// and 8.1, 96 x 158592 36.1 and 22.8, 256 x 414592 167 and 119; transfers 2 x 8192 5.0 and 3.8, 4 x 9792 5.4 and 5.3, 24 x 41792 10.2 and 10.4, 96
+// x 156992 44.4 and 28.7 (3 x 9792 5.0 and 5.2, 24 x 43392 9.9 and 10.3: one layer less in the line).
 bool locality_direct(const int32_t* trace, const int32_t* placement, const int32_t* home, int L, int64_t N, int E, int64_t* local_per_pair,
                      int64_t* away_per_layer, hipStream_t stream)
 {
-    if (N < 4 || N > 8192 + 1600ll * (L - 2)) return false;
+    if (N < 4 || N > 8192 + 1600ll * (home != nullptr ? std::max(L - 3, 0) : L - 2)) return false;
     if (home != nullptr)
         hipLaunchKernelGGL(locality_direct_kernel<true>, dim3(static_cast<unsigned>(L)), dim3(kPairThreads), 0, stream, trace, placement, home, L, N, E,
                            local_per_pair, away_per_layer);

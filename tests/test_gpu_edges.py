@@ -65,6 +65,12 @@ def test_multihop_blocks(L, N, E):
     Q.test_affinity_multihop_parity(L, N, E)
 
 
+@pytest.mark.parametrize("L,N", [(1, 8192), (1, 8193), (2, 8193), (3, 8192), (3, 8193), (3, 9792), (3, 9793), (4, 9792), (4, 9793), (24, 41792), (24, 41793), (24, 43392), (24, 43393)])
+def test_transfers_either_side_of_one_launch(oracle, L, N):
+    Q.test_routing_transfers_parity(L, N, 8, 4)
+    P.test_affinity_and_locality_parity(oracle, L, N, 8, 4)
+
+
 # the last trace in one launch and the first in chunks, for each range of layers and experts
 @pytest.mark.parametrize("L,N,E", [(2, 32768, 63), (11, 32769, 5), (12, 81920, 40), (15, 81921, 41), (13, 49152, 39), (14, 49153, 8), (16, 106496, 16), (23, 106497, 7),
                                    (24, 49152, 23), (26, 49153, 2), (25, 90112, 24), (32, 90113, 39), (24, 131072, 40), (27, 131073, 64), (33, 16384, 1), (34, 16385, 9),
