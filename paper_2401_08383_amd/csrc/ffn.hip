@@ -105,6 +105,56 @@ __device__ __forceinline__ TileRows cut_rows(int cnt, int most)
     return t;
 }
 
+// A tile of `height` rows (`rows` of them there are) in 2^pieces pieces: its columns in 2^cut parts, its rows in 2^row_cut of `height`
+// rows.  Every cut goes where it leaves the fewer rows of operands (see locate_tile) and where there is an instance.
+struct TileCut {
+    int cut, row_cut, height;
+};
+__host__ __device__ constexpr TileCut cut_tile(int NT, int height, int rows, int pieces)
+{
+    TileCut t{pieces, 0, height};
+    if (t.cut == 3 && rows <= 64) t.cut = 2;  // no instance of an eighth: four pieces
+    for (int i = 1; i <= 2; ++i) {
+        const int part = ((rows + (kQuantum << i) - 1) >> (i + 5)) * kQuantum;
+        const bool too_tall = t.cut == 2 && t.height > NT / 2;  // no instance of that height
+        if (t.row_cut == i - 1 && t.cut > 0 && (t.height - part > NT >> t.cut || too_tall)) {
+            t.row_cut = i;
+            t.cut -= 1;
+            t.height = part;
+        }
+    }
+    return t;
+}
+// The kernel's instances, and the next height there is one of.
+__host__ __device__ constexpr bool has_instance(int NT, int height, int cut)
+{
+    const bool wide = NT == 256;
+    if (cut == 0) return height == 64 || (height == 96 && !wide) || height == 128 || height == 160 || height == 192 || height == 256 || height == 288 || height == 320;
+    if (cut == 1) return height == 64 || height == 96 || height == 128 || height == 160 || (wide && (height == 192 || height == 256 || height == 320));
+    return cut == 2 && (height == 64 || (wide && height == 128));
+}
+__host__ __device__ constexpr int instance_height(int NT, int height, int cut)
+{
+    if (height < 64) height = 64;
+    if (NT == 256 && height == 96 && cut != 1) height = 128;
+    if (height == 288 && cut == 1) height = 320;
+    return height;
+}
+// Every tile, whole or in pieces, has all its rows in pieces that the kernel has an instance for (it writes nothing otherwise).
+constexpr bool tiles_are_covered(int NT)
+{
+    const int heights[] = {64, 128, 192, 256, 288, 320};
+    for (int height : heights)
+        for (int rows = 1; rows <= height; rows += rows % kQuantum == 1 ? kQuantum - 2 : 1)  // 1, 31, 32, 33, 63, ..
+            for (int pieces = 0; pieces <= 3; ++pieces) {
+                const TileCut t = pieces > 0 ? cut_tile(NT, height, rows, pieces) : TileCut{0, 0, height};
+                const int taken = instance_height(NT, t.height, t.cut);
+                if (!has_instance(NT, taken, t.cut) || taken < t.height || t.height << t.row_cut < rows || t.cut < 0 || t.cut + t.row_cut > pieces) return false;
+            }
+    return true;
+}
+static_assert(tiles_are_covered(128) && tiles_are_covered(256), "a tile without an instance");
+
 struct TilePlan {  // lane e = expert e; the same in every workgroup
     int lo, hi;
     int tiles;                  // row tiles (0: no rows)
@@ -229,28 +279,14 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
     int height = t.height + (each + (row_tile < more ? 1 : 0)) * kQuantum;
     int row_begin = begin_row, row_end = min(begin_row + height, e_hi);
     if (out.cut > 0) {
-        const int rows = __builtin_amdgcn_readfirstlane(row_end - row_begin);
-        int cut = out.cut;
-        if (cut == 3 && rows <= 64) {  // no instance of an eighth: four pieces
-            if (piece >= 4) return false;
-            cut = 2;
-        }
-        int row_cut = 0;
-#pragma unroll
-        for (int i = 1; i <= 2; ++i) {
-            const int part = ((rows + (kQuantum << i) - 1) >> (i + 5)) * kQuantum;
-            const bool too_tall = cut == 2 && height > NT / 2;  // no instance of that height
-            if (row_cut == i - 1 && cut > 0 && (height - part > NT >> cut || too_tall)) {
-                row_cut = i;
-                cut -= 1;
-                height = part;
-            }
-        }
-        out.cut = cut;
-        if (row_cut > 0) {
-            row_begin += (piece & ((1 << row_cut) - 1)) * height;
+        const TileCut t = cut_tile(NT, height, __builtin_amdgcn_readfirstlane(row_end - row_begin), out.cut);
+        if (piece >= 1 << (t.cut + t.row_cut)) return false;
+        out.cut = t.cut;
+        height = t.height;
+        if (t.row_cut > 0) {
+            row_begin += (piece & ((1 << t.row_cut) - 1)) * height;
             row_end = min(row_end, row_begin + height);
-            piece >>= row_cut;
+            piece >>= t.row_cut;
         }
     }
     const int n0 = col_tile * NT + piece * (NT >> out.cut);
@@ -261,11 +297,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
     out.cut = __builtin_amdgcn_readfirstlane(out.cut);
     out.row_begin = __builtin_amdgcn_readfirstlane(row_begin);
     out.row_end = __builtin_amdgcn_readfirstlane(row_end);
-    // to the next height there is an instance of (every height that comes out here has a case in the kernel below)
-    height = max(height, 64);
-    if (NT == 256 && height == 96 && out.cut != 1) height = 128;
-    if (height == 288 && out.cut == 1) height = 320;
-    out.height = __builtin_amdgcn_readfirstlane(height);
+    out.height = __builtin_amdgcn_readfirstlane(instance_height(NT, height, out.cut));
     // Hidden rows of experts with several row tiles in a launch of at most two rounds: nothing overlaps the last stores there, and
     // what they leave in the L2s has to be written back when the kernel ends.  Written through, both contractions: 8192 tokens, 8
     // experts of 1024 x 4096 152.2 -> 147.0 us (two rounds), 4 experts, 2048 tokens 65.9 -> 63.0, one, 6000 tokens 124.3 -> 118.3.  Not in
@@ -779,35 +811,26 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     const bf16_t* bias_e = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
 #define EXF_TILE(H, CUT) \
     gemm_tile<H, (NT >> CUT), WAVES, EPI>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.through, tile.n0, K, N, out, smem, map)
-#define EXF_CASE(H, CUT) \
-    case (CUT) * 16 + (H) / kQuantum: EXF_TILE(H, CUT); break
-#define EXF_WIDE_CASE(H, CUT)                      \
-    case (CUT) * 16 + (H) / kQuantum:              \
-        if constexpr (NT == 256) EXF_TILE(H, CUT); \
+#define EXF_CASE(H, CUT)                                         \
+    case (CUT) * 16 + (H) / kQuantum:                            \
+        if constexpr (has_instance(NT, H, CUT)) EXF_TILE(H, CUT); \
         break
+#define EXF_CASES(CUT)  \
+    EXF_CASE(64, CUT);  \
+    EXF_CASE(96, CUT);  \
+    EXF_CASE(128, CUT); \
+    EXF_CASE(160, CUT); \
+    EXF_CASE(192, CUT); \
+    EXF_CASE(256, CUT); \
+    EXF_CASE(288, CUT); \
+    EXF_CASE(320, CUT)
     switch (tile.cut * 16 + tile.height / kQuantum) {
-        EXF_CASE(64, 0);
-        EXF_CASE(128, 0);
-        EXF_CASE(160, 0);
-        EXF_CASE(192, 0);
-        EXF_CASE(256, 0);
-        EXF_CASE(288, 0);
-        EXF_CASE(320, 0);
-        EXF_CASE(64, 1);
-        EXF_CASE(96, 1);
-        EXF_CASE(128, 1);
-        EXF_CASE(160, 1);
-        EXF_WIDE_CASE(192, 1);
-        EXF_WIDE_CASE(256, 1);
-        EXF_WIDE_CASE(320, 1);
-        EXF_CASE(64, 2);
-        EXF_WIDE_CASE(128, 2);
-        case 96 / kQuantum:
-            if constexpr (NT == 128) EXF_TILE(96, 0);
-            break;
+        EXF_CASES(0);
+        EXF_CASES(1);
+        EXF_CASES(2);
     }
+#undef EXF_CASES
 #undef EXF_CASE
-#undef EXF_WIDE_CASE
 #undef EXF_TILE
     timeline_stamp(map, 4);
 }
