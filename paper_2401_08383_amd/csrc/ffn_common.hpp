@@ -101,8 +101,8 @@ inline bool routed_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
     return A > 0 && A <= kInlineDispatchMax && stream_path_fits(A, d, f, E_local, dt);
 }
-// Is a layer on the routed path gated by its first contraction?
-bool gate_joins_layer(int64_t T, int k, int d, int E, int dt);
+// Is a layer on the routed path gated by its first contraction?  routed: its experts are given, the gate's ids are only stored.
+bool gate_joins_layer(int64_t T, int d, int E, int dt, bool routed);
 int ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
                      int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream);
 

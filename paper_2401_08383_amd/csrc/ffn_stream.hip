@@ -905,6 +905,15 @@ static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 }
 
 // ---------------------------------------------------------------------------- host
+// With the routing given only the first workgroup is the gate, and its launch is saved whatever it takes (8 of 8 x 4096 to 64 x 16384
+// 3 to 14 us less).  Otherwise every workgroup reads the gate's weights before its own, which costs more than the launch where
+// they are many: separate minus joined, mean over 1 to 16 tokens and f from 64 to 2048, us: 8 x 1024 1.1, 8 x 4096 0.7, 32 x 2048 0.4, 64 x
+// 1024 0.4; 32 x 4096 0.25, 64 x 2048 -0.3, 8 x 16384 -0.8; 64 x 4096 -0.6, 64 x 16384 -2.2.
+bool gate_joins_layer(int64_t T, int d, int E, int dt, bool routed)
+{
+    return dt == EXF_BF16 && T <= kGateFewTokens && (routed || static_cast<int64_t>(E) * d <= 98304);
+}
+
 // bf16: the weights are streamed where few rows use them, on the mean at most 28 an expert: 24 rows of 64 experts of 1024 x 4096 take
 // 222 us against 219 with the tiles of ffn.hip, 32 rows of 8 experts of 2048 x 8192 both 114.  With few experts the
 // tiles also wait for their K loops, a quarter of a microsecond for 64 elements of d + f, while streaming costs 35 ns per row and
@@ -912,12 +921,6 @@ static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 // against 27.3 with 117).  Up to 128 rows of a single expert are known to fill 32, 64 or 128 of a row tile's, which is what they
 // cost (1024 x 4096: 24.8 against 27.4 with 117 rows; 2048 x 8192: 37.1 against 44.9 with 58, 53.2 against 45.6 with 65; 4096 x
 // 14336: 52.7 against 74.0 with 30, 83.4 against 74.2 with 33).
-bool gate_joins_layer(int64_t T, int k, int d, int E, int dt)
-{
-    (void)k, (void)d, (void)E;
-    return dt == EXF_BF16 && T <= kGateFewTokens;
-}
-
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
     if (dt == EXF_F32 || A <= 28ll * E_local) return true;

@@ -25,7 +25,7 @@ extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
         if (int bad = exf::check_combine(l.y_sorted, l.sorted_of_src, l.topk_w, l.T, l.d, l.k, l.dt, l.out)) return bad;
     }
     const bool routed = fused && exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt);
-    const bool gated = routed && exf::gate_joins_layer(l.T, l.k, l.d, l.E, l.dt);
+    const bool gated = routed && exf::gate_joins_layer(l.T, l.d, l.E, l.dt, idx != l.topk_idx);
     int rc = EXF_OK;
     if (!gated) rc = moe_gate_topk(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.renormalize, l.dt, nullptr, l.topk_idx, l.topk_w, stream);
     if (rc != EXF_OK) return rc;
