@@ -906,12 +906,14 @@ static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 
 // ---------------------------------------------------------------------------- host
 // With the routing given only the first workgroup is the gate, and its launch is saved whatever it takes (8 of 8 x 4096 to 64 x 16384
-// 3 to 14 us less).  Otherwise every workgroup reads the gate's weights before its own, which costs more than the launch where
-// they are many: separate minus joined, mean over 1 to 16 tokens and f from 64 to 2048, us: 8 x 1024 1.1, 8 x 4096 0.7, 32 x 2048 0.4, 64 x
-// 1024 0.4; 32 x 4096 0.25, 64 x 2048 -0.3, 8 x 16384 -0.8; 64 x 4096 -0.6, 64 x 16384 -2.2.
+// 3 to 14 us less).  Otherwise every workgroup is, in front of its own weights, which costs more than the launch where a wavefront
+// has many units of the reduction to walk, each with 16 rows of tokens and those of the experts: separate minus joined, mean over 1 to 16
+// tokens and f from 64 to 2048, us, by these rows in sixteens: 32 x 2048 (12) 0.4, 64 x 1024 (20) 0.4, 32 x 4096 (24) 0.25, 64 x 1536 (30)
+// 0.1, 8 x 8192 (32) 0.2, 48 x 2048 (32) 0.0, 64 x 2048 (40) -0.3, 32 x 8192 (48) -0.8, 8 x 16384 (64) -0.8, 64 x 4096 (80) -0.6, 64 x 16384 -2.2.
 bool gate_joins_layer(int64_t T, int d, int E, int dt, bool routed)
 {
-    return dt == EXF_BF16 && T <= kGateFewTokens && (routed || static_cast<int64_t>(E) * d <= 98304);
+    const int nt = (E + 15) / 16;
+    return dt == EXF_BF16 && T <= kGateFewTokens && (routed || d / 64 * (nt + 1) <= 32 * gate_sums(nt, d));
 }
 
 // bf16: the weights are streamed where few rows use them, on the mean at most 28 an expert: 24 rows of 64 experts of 1024 x 4096 take

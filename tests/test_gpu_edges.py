@@ -238,7 +238,8 @@ def test_layer_forward_is_its_calls(T, k, E, E_local, dtype, fused, routing):
     (3, 1, 8, 2, 1024, 2048, "ids"), (8, 1, 8, 8, 64, 8192, "ids"), (32, 2, 8, 8, 256, 512, "ids"), (64, 1, 3, 3, 128, 256, "ids"), (65, 1, 3, 3, 128, 256, "ids"),
     (7, 1, 64, 9, 128, 64, "dropped"), (2, 2, 64, 9, 128, 64, "dropped"), (16, 1, 1, 1, 512, 1024, "gate"),
     # the most gate weights that join the first contraction and the first that do not, either with the experts given
-    (2, 1, 64, 64, 1536, 64, "gate"), (16, 2, 64, 64, 1600, 64, "gate"), (16, 1, 64, 8, 1600, 64, "ids"), (16, 2, 33, 33, 3008, 64, "ids"),
+    (2, 1, 64, 64, 1600, 64, "gate"), (16, 2, 64, 64, 1664, 64, "gate"), (3, 1, 20, 20, 5440, 64, "gate"), (3, 1, 20, 20, 5504, 64, "gate"),
+    (16, 1, 64, 8, 1664, 64, "ids"), (16, 2, 33, 33, 3008, 64, "ids"),
     # one row tile of a single expert and two, two experts past one tile
     (32, 1, 1, 1, 2048, 512, "gate"), (33, 1, 1, 1, 2048, 512, "gate"), (64, 1, 1, 1, 512, 2048, "gate"), (57, 1, 2, 2, 320, 2048, "gate")])
 def test_layer_forward_of_a_few_rows(T, k, E, E_local, d, f, routing):
