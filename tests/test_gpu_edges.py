@@ -27,7 +27,8 @@ def test_trace_columns_that_start_and_end_anywhere(oracle, N):
 
 @pytest.mark.parametrize("L,N,E,G", [
     (2, 4, 1, 1), (3, 5, 64, 8), (2, 4095, 63, 7), (24, 4097, 64, 8), (2, 8191, 64, 8), (2, 8193, 8, 4), (5, 24575, 40, 5), (5, 24576, 2, 2), (5, 24577, 8, 4),
-    (4, 11392, 8, 4), (4, 11393, 8, 4), (12, 10240, 8, 4), (12, 10241, 16, 4), (33, 16385, 3, 3), (33, 2000, 24, 4)])
+    (4, 11392, 8, 4), (4, 11393, 8, 4), (12, 10240, 8, 4), (12, 10241, 16, 4), (33, 16385, 3, 3), (33, 2000, 24, 4),
+    (5, 24577, 64, 8), (24, 5120, 64, 8), (24, 5121, 64, 8), (24, 61443, 64, 8)])
 def test_short_traces(oracle, L, N, E, G):
     """One launch a call up to a number of tokens that depends on the call, two beyond: both sides of it, tokens cut by the end of a sweep,
     invalid ids, few bins and as many as there are."""
@@ -42,10 +43,11 @@ def test_short_traces(oracle, L, N, E, G):
     Q.test_routing_transfers_parity(L, N, E, G)
 
 
-@pytest.mark.parametrize("N", [300, 262147])
+@pytest.mark.parametrize("N", [300, 262147, 414593])
 def test_placement_of_all_layers_beyond_64_KiB(oracle, N):
-    """The most layers and experts: the placement and the counts take more LDS than a launch may use unasked.  Both calls
-    twice: the second one relies on what the first has asked for."""
+    """The most layers and experts.  Up to 412992 tokens (locality 414592) a workgroup takes a layer and two rows of the placement; beyond,
+    the placement of all layers and the counts take more LDS than a launch may use unasked.  Both calls twice: the second one relies
+    on what the first has asked for."""
     for _ in range(2):
         Q.test_routing_transfers_parity(256, N, 64, 8)
     _say(f"placement_locality L=256 N={N}")
@@ -59,7 +61,8 @@ def test_placement_of_all_layers_beyond_64_KiB(oracle, N):
 
 # ----------------------------------------------------------------------------- counts of all layer pairs
 @pytest.mark.parametrize("L,N,E", [(2, 65281, 64), (4, 5, 1), (5, 4100, 63), (8, 8193, 2), (9, 65280, 33), (12, 130561, 5), (13, 20000, 64), (16, 16385, 64),
-                                   (17, 9000, 31), (29, 24577, 7), (31, 3, 64), (33, 12289, 64)])
+                                   (17, 9000, 31), (29, 24577, 7), (31, 3, 64), (33, 12289, 64),
+                                   (29, 49153, 7), (30, 90115, 33), (33, 16385, 64), (47, 20001, 16)])
 def test_multihop_blocks(L, N, E):
     """Whole and cut blocks of layers, few and many of them, rows of odd length, chunks at the counters' limit."""
     Q.test_affinity_multihop_parity(L, N, E)
@@ -165,8 +168,8 @@ def test_grouped_ffn_row_tiles(oracle, counts, d, f):
 
 @pytest.mark.parametrize("counts,d,f", [([65, 128, 0, 64, 127], 320, 1088), ([100], 128, 4160), ([66, 129, 300, 96], 64, 576),
                                         ([100] * 13, 192, 1088), ([128, 65] * 9 + [1, 260], 128, 1024)])
-def test_grouped_ffn_small_tiles_in_halves(oracle, counts, d, f):
-    """Experts of 65 to 128 rows: two tiles of 64 rows in launches of few tiles, one of 128 in larger ones (the last two)."""
+def test_grouped_ffn_tiles_of_128_rows(oracle, counts, d, f):
+    """Experts of 65 to 128 rows: a tile in pieces of 64 rows in launches of few tiles, whole in larger ones (the last two)."""
     P._ffn_case(oracle, "bf16", counts, d, f, 1, True, seed=1750 + d)
 
 
