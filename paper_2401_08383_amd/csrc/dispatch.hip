@@ -272,7 +272,7 @@ __device__ __forceinline__ void move_rows(const uint4* __restrict__ x, uint4* __
 // slice add the copies up, the expert map is asked for with the ids and looked up across lanes, and a thread asks for as many
 // ids as it needs (with all 16 wavefronts adding, the map looked up in memory and eight ids a thread always: 1024 assignments 4.4
 // to 4.8 us).
-//   Index maps, us, in one workgroup of 1024 threads (up to 16384; beyond, two launches) and now, with 1, 8 and 64 experts: 64
+//   Index maps, us, captured and back to back, in one workgroup of 1024 threads (up to 16384; beyond, two launches) and now, with 1, 8 and 64 experts: 64
 // assignments 3.0, 3.7, 4.7 and 2.4, 2.4, 2.5; 1024 3.1, 3.8, 5.0 and 2.6, 2.8, 2.9; 4096 3.3, 4.6, 6.1 and 3.1, 3.1, 3.3; 16384 7.8,
 // 13.0, 17.7 and 5.0, 4.6, 4.7; 20480 7.2, 6.9, 7.9 and 5.8, 5.6, 5.7, with 8 of 64 experts local 7.2 and 6.2.
 //   With rows, two launches with slices of 32 and now, 8 experts: 64 x 1024 7.1 and 4.1; 1024 x 4096 18.2 and 7.7; 3062 x 1024 10.2 and
