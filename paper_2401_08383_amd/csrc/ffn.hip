@@ -55,6 +55,8 @@ struct RowMap {
     // rows / K tiles, [7] the experts' row ranges have arrived (between [0] and [1]).
     unsigned long long* timeline;
     int timeline_cap;
+    // With out_row and kEpiKeepSorted: sorted row s is the result in bf16, and what is scaled and rounded again is that, as the combine does it.
+    bf16_t* sorted_out;
 };
 
 // The hidden activations between the two contractions live in a layout of their own (nobody else reads them): the
@@ -536,7 +538,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     g.wave = wave;
     g.smem = smem;
     g.smem_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem));
-    constexpr bool HIDDEN_OUT = EPI != kEpiNone, HIDDEN_ACT = EPI == kEpiNone;  // the first contraction writes what the second reads
+    constexpr bool HIDDEN_ACT = EPI == kEpiNone || EPI == kEpiKeepSorted, HIDDEN_OUT = !HIDDEN_ACT;  // the first contraction writes what the second reads
     const int r8 = lane >> 3, c8 = lane & 7;
     const int nk = K / kKTile;
     // The XCDs begin at different places of the reduction: rows a power of two bytes apart put the same columns of all rows
@@ -700,7 +702,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
         dst[b] = row_begin + wm * G::WTM + b * 16 + (lane & 15);
         scale[b] = 1.0f;
     }
-    if constexpr (EPI == kEpiNone) {
+    if constexpr (HIDDEN_ACT) {
         if (map.out_row != nullptr) {
 #pragma unroll
             for (int b = 0; b < TM; ++b) dst[b] = map.out_row[min(dst[b], row_end - 1)];
@@ -735,7 +737,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
                         float z = g.acc[b][a + q][r] + bias_v[q][r];
                         if constexpr (EPI == kEpiGeluErf) z = gelu_erf_fast(z);
                         else if constexpr (EPI == kEpiGeluTanh) z = gelu_tanh_fast(z);
-                        else z *= scale[b];
+                        else if constexpr (EPI == kEpiNone) z *= scale[b];
                         v[r] = z;
                     }
                     w[q][0] = pack_bf16x2(v[0], v[1]);
@@ -751,7 +753,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
                 else
                     to = reinterpret_cast<uint4*>(out + static_cast<size_t>(dst[b]) * N + n);
                 if (m < row_end && n < N) {  // N % 64 == 0: eight columns are inside or outside together
-                    if constexpr (decltype(written_through)::value) store_through16(to, make_uint4(s0[0], s1[0], s0[1], s1[1]));
+                    if constexpr (EPI == kEpiKeepSorted) {
+                        const uint4 y = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+                        store_stream16(reinterpret_cast<uint4*>(map.sorted_out + static_cast<size_t>(m) * N + n), y);
+                        const uint32_t p[4] = {y.x, y.y, y.z, y.w};
+                        uint32_t o[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) o[c] = pack_bf16x2(fmaf(scale[b], __uint_as_float(p[c] << 16), 0.0f), fmaf(scale[b], __uint_as_float(p[c] & 0xffff0000u), 0.0f));
+                        store_stream16(to, make_uint4(o[0], o[1], o[2], o[3]));
+                    } else if constexpr (decltype(written_through)::value) store_through16(to, make_uint4(s0[0], s1[0], s0[1], s1[1]));
                     else store_stream16(to, make_uint4(s0[0], s1[0], s0[1], s1[1]));
                 }
             }
@@ -883,9 +893,13 @@ static int launch_second_contraction(const void* act, const int32_t* offsets, co
                                      int K, int N, int E_local, void* out, hipStream_t stream, const RowMap& map)
 {
     const int64_t wide_tiles = (A / 256) * ((N + 255) / 256);
-    if (wide_tiles >= static_cast<int64_t>(kWideRounds) * kComputeUnits)
-        return launch_bf16_as<256, 4, kEpiNone>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
-    return launch_bf16_as<128, 4, kEpiNone>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
+    const bool wide = wide_tiles >= static_cast<int64_t>(kWideRounds) * kComputeUnits;
+    if (map.sorted_out == nullptr) {
+        if (wide) return launch_bf16_as<256, 4, kEpiNone>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
+        return launch_bf16_as<128, 4, kEpiNone>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
+    }
+    if (wide) return launch_bf16_as<256, 4, kEpiKeepSorted>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
+    return launch_bf16_as<128, 4, kEpiKeepSorted>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
 }
 
 }  // namespace exf
@@ -1040,9 +1054,11 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
                          unsigned long long* timeline, int timeline_cap, const exf::FfnRouting* routing = nullptr)
 {
     using namespace exf;
-    if (int rc = check_ffn_fused(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, w2, T, k, d, f, E_local, act, dt, out, workspace,
-                                 workspace_bytes))
-        return rc;
+    if (routing == nullptr) {  // (a layer's arguments have been checked)
+        if (int rc = check_ffn_fused(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, w2, T, k, d, f, E_local, act, dt, out, workspace,
+                                     workspace_bytes))
+            return rc;
+    }
     if (T == 0) return EXF_OK;
     const int64_t A = T * k;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1062,8 +1078,8 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
         scatter.unrouted = sorted_of_src;
         scatter.n_unrouted = static_cast<int>(T);
     }
-    unsigned char* y_sorted = hidden + hidden_bytes(A, f, E_local, dt);
-    void* second_out = k == 1 ? out : static_cast<void*>(y_sorted);
+    void* y_sorted = routing != nullptr && routing->y_sorted != nullptr ? routing->y_sorted : hidden + hidden_bytes(A, f, E_local, dt);
+    void* second_out = k == 1 ? out : y_sorted;
     int rc;
     if (timeline == nullptr && stream_path_fits(A, d, f, E_local, dt)) {
         StreamGemm first{}, second{};
@@ -1076,6 +1092,8 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
             first.w_gate = routing->w_gate, first.renormalize = routing->renormalize;
             first.k = second.k = k;
             first.gate_idx = routing->gate_idx, first.gate_w = routing->gate_w;
+            first.sorted_act = routing->x_sorted;
+            if (k == 1) second.sorted_out = routing->y_sorted;
             if (dt == EXF_BF16 && A <= kFewAssignments) {
                 second.topk_idx = routing->topk_idx, second.expert_map = routing->expert_map, second.E = routing->E;
                 second.second = true;
@@ -1109,6 +1127,38 @@ extern "C" int moe_expert_ffn_fused(const void* x, const int32_t* src_of_sorted,
 {
     return ffn_fused_run(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets, w1, b1, w2, b2, T, k, d, f, E_local, act, dt, out,
                          workspace, workspace_bytes, stream, nullptr, 0);
+}
+
+int exf::ffn_combined(const void* x_sorted, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
+                      const int32_t* expert_offsets, const void* w1, const void* w2, int64_t T, int d, int f, int E_local, int act, int dt,
+                      void* y_sorted, void* out, void* workspace, void* stream)
+{
+    if (T == 0) return EXF_OK;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int epi = act == EXF_ACT_GELU_ERF ? kEpiGeluErf : kEpiGeluTanh;
+    int rc;
+    if (stream_path_fits(T, d, f, E_local, dt)) {
+        StreamGemm first{}, second{};
+        first.act = x_sorted, first.weight = w1, first.out = workspace;
+        first.K = d, first.N = f, first.epi = epi;
+        second.act = workspace, second.weight = w2, second.out = out, second.sorted_out = y_sorted;
+        second.out_row = src_of_sorted, second.out_scale = topk_w;
+        second.unrouted = sorted_of_src, second.n_unrouted = static_cast<int>(T);
+        second.K = f, second.N = d, second.epi = kEpiNone;
+        first.offsets = second.offsets = expert_offsets;
+        first.max_rows = second.max_rows = static_cast<int>(T);
+        first.E_local = second.E_local = E_local;
+        rc = launch_stream_gemm(first, dt, s);
+        if (rc == EXF_OK) rc = launch_stream_gemm(second, dt, s);
+    } else {
+        RowMap scatter{};
+        scatter.out_row = src_of_sorted, scatter.out_scale = topk_w;
+        scatter.unrouted = sorted_of_src, scatter.n_unrouted = static_cast<int>(T);
+        scatter.sorted_out = static_cast<bf16_t*>(y_sorted);
+        rc = launch_first_contraction(x_sorted, expert_offsets, w1, nullptr, T, d, f, E_local, epi, workspace, s, RowMap{});
+        if (rc == EXF_OK) rc = launch_second_contraction(workspace, expert_offsets, w2, nullptr, T, f, d, E_local, out, s, scatter);
+    }
+    return rc == EXF_OK ? check_launch("moe_layer_forward") : rc;
 }
 
 int exf::ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,

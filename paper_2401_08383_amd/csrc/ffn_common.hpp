@@ -45,7 +45,7 @@ __device__ __forceinline__ float gelu_tanh_fast(float z)
     return z * __builtin_amdgcn_rcpf(1.0f + __expf(-2.0f * u));
 }
 
-enum Epilogue { kEpiNone = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2 };
+enum Epilogue { kEpiNone = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2, kEpiKeepSorted = 3 };  // (the last: tiles of ffn.hip, RowMap::sorted_out)
 
 // ---------------------------------------------------------------------------- weight-streaming path
 // One contraction  out[rows of e, N] = epi(act[rows, K] * weight_e[N, K]^T + bias_e)  (see ffn_stream.hip).
@@ -79,6 +79,10 @@ struct StreamGemm {
     int renormalize;
     int32_t* gate_idx;
     float* gate_w;
+    // The sorted rows besides the result (null: not wanted).  With topk_idx: [*,K], the operand rows in sorted order.
+    void* sorted_act;
+    // With out_row: [*,N], sorted row s before it is scaled, in the storage type; the scaled one is formed from that, as the combine would.
+    void* sorted_out;
 };
 constexpr int kFewAssignments = 64;
 constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for itself
@@ -86,8 +90,8 @@ constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for i
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
 
-// moe_dispatch (index maps) and moe_expert_ffn_fused as one: the first contraction sorts the assignments itself.  Only
-// where routed_path_fits() says so; the maps are written as moe_dispatch writes them.
+// moe_dispatch and the expert FFN as one: the first contraction sorts the assignments itself.  Only where routed_path_fits() says so;
+// the maps, and the sorted rows where they are wanted, are written as moe_dispatch and moe_expert_ffn write them.
 struct FfnRouting {
     const int32_t *topk_idx, *expert_map;
     int E;
@@ -96,6 +100,7 @@ struct FfnRouting {
     int renormalize;
     int32_t* gate_idx;
     float* gate_w;
+    void *x_sorted, *y_sorted;  // null: not wanted
 };
 inline bool routed_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
@@ -103,6 +108,10 @@ inline bool routed_path_fits(int64_t A, int d, int f, int E_local, int dt)
 }
 // Is a layer on the routed path gated by its first contraction?  routed: its experts are given, the gate's ids are only stored.
 bool gate_joins_layer(int64_t T, int d, int E, int dt, bool routed);
+// The expert FFN of a top-1 layer and its combine, moe_expert_ffn and moe_combine in two launches: the same results.
+int ffn_combined(const void* x_sorted, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w, const int32_t* expert_offsets,
+                 const void* w1, const void* w2, int64_t T, int d, int f, int E_local, int act, int dt, void* y_sorted, void* out, void* workspace,
+                 void* stream);
 int ffn_fused_routed(const FfnRouting& r, const void* x, const float* topk_w, const void* w1, const void* w2, int64_t T, int k, int d, int f,
                      int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream);
 

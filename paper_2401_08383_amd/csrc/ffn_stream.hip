@@ -48,6 +48,21 @@ __device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int64_t wave
     }
 }
 
+// The sorted copy of the operand rows, sorted row s by workgroup s % gridDim.x (list[s] / a_div: its row): behind everything else, where
+// the loads of nothing wait for it.
+template <int THREADS, typename ST>
+__device__ __forceinline__ void copy_sorted_rows(const StreamGemm& p, const int* list, int kept, int a_div)
+{
+    const int vec_per_row = p.K * static_cast<int>(sizeof(ST)) / 16;
+    for (int s = static_cast<int>(blockIdx.x); s < kept; s += static_cast<int>(gridDim.x)) {
+        int row = list[s];
+        if (a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(a_div));
+        const uint4* from = reinterpret_cast<const uint4*>(p.act) + static_cast<size_t>(row) * vec_per_row;
+        uint4* to = reinterpret_cast<uint4*>(p.sorted_act) + static_cast<size_t>(s) * vec_per_row;
+        for (int c = threadIdx.x; c < vec_per_row; c += THREADS) to[c] = from[c];
+    }
+}
+
 // The stable counting sort of moe_dispatch for at most kInlineDispatchMax assignments, by one workgroup into LDS.  Loading
 // the ids costs the same memory round trip as loading finished offsets would, and the sort itself about a third of
 // the launch it replaces.  Segments (round, wavefront) are ascending assignment order.
@@ -306,7 +321,8 @@ __device__ __forceinline__ void wait_units(int units)
 }
 
 // Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
-template <int C8, int AR, int W, bool FEW_ROWS = false>
+// KEEP_OUT: p.sorted_out is given.
+template <int C8, int AR, int W, bool KEEP_OUT, bool FEW_ROWS = false>
 __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int row_begin, int row_end, int block_begin, int block_end,
                                                int rotate, const int* list, bool tokens, bool listed_out, unsigned char* smem)
 {
@@ -522,7 +538,14 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
             for (int k = 0; k < 4; ++k) {
                 if (p.epi == kEpiGeluErf) v[k] = gelu_erf_fast(v[k]);
                 else if (p.epi == kEpiGeluTanh) v[k] = gelu_tanh_fast(v[k]);
-                v[k] *= scale;
+                if constexpr (!KEEP_OUT) v[k] *= scale;
+            }
+            if constexpr (KEEP_OUT) {
+                const uint2 y = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+                *reinterpret_cast<uint2*>(static_cast<bf16_t*>(p.sorted_out) + static_cast<size_t>(row_begin + r) * p.N + n) = y;
+                const uint32_t w[4] = {y.x << 16, y.x & 0xffff0000u, y.y << 16, y.y & 0xffff0000u};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = fmaf(scale, __uint_as_float(w[k]), 0.0f);  // (the combine's bits)
             }
             *reinterpret_cast<uint2*>(static_cast<bf16_t*>(p.out) + static_cast<size_t>(dst) * p.N + n) =
                 make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
@@ -537,13 +560,18 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
 // Where the rows of a contraction come from: sorted (maps in memory), sorted by the workgroup, sorted by every wavefront.
 enum StreamRows { kRowsSorted, kRowsInline, kRowsFew, kRowsEight };  // (the last: as kRowsFew, at most eight)
 
-template <int C8, int W, StreamRows ROWS>
+// The sorted rows that are wanted besides the result: none, p.sorted_act (a contraction that sorts), p.sorted_out (one that scales).  Instances
+// of their own: what a handful of rows does not need costs them 0.6 us of 12.
+enum StreamKeep { kKeepNone, kKeepAct, kKeepOut };
+
+template <int C8, int W, StreamRows ROWS, StreamKeep KEEP>
 __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     touch_arguments<sizeof(StreamGemm)>();
     constexpr int MAX_AR = stream_max_ar(C8), TILE_ROWS = 8 * MAX_AR, COLS = 8 * C8;
     constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;  // `list` holds tokens, not assignments
+    constexpr bool KEEP_OUT = KEEP == kKeepOut;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int* list = nullptr;
     bool listed_out = false;
@@ -603,7 +631,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             const int row_begin = wave_read_lane(et.lo, e), row_end = wave_read_lane(et.hi, e);
             const int b0 = static_cast<int>(at - t * n_blocks);
             at = min(end, (t + 1) * n_blocks);
-            stream_segment<C8, 1, W, true>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, FEW, listed_out, smem);
+            stream_segment<C8, 1, W, KEEP_OUT, true>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, FEW, listed_out, smem);
             continue;
         }
         const int e = __builtin_ctzll(__ballot(at < cost_incl * n_blocks));
@@ -630,31 +658,47 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         at = __builtin_amdgcn_readfirstlane(tile_begin + c * n_blocks);
         if (b0 >= b1) continue;
         const int rows = row_end - row_begin;
-        if (rows <= 8) stream_segment<C8, 1, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
-        else if (rows <= 16) stream_segment<C8, 2, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
-        else if (rows <= 32) stream_segment<C8, 4, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
-        else stream_segment<C8, MAX_AR, W>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        if (rows <= 8) stream_segment<C8, 1, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        else if (rows <= 16) stream_segment<C8, 2, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        else if (rows <= 32) stream_segment<C8, 4, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        else stream_segment<C8, MAX_AR, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
     }
+    if constexpr (KEEP == kKeepAct) copy_sorted_rows<W * kWave, bf16_t>(p, list, wave_read_lane(et.hi, p.E_local - 1), FEW ? 1 : p.a_div);
 }
 
-template <int C8, int W, StreamRows ROWS>
+template <int C8, int W, StreamRows ROWS, StreamKeep KEEP>
 static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
 {
     constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C8, W)) + W * kStreamIdBytes + (ROWS == kRowsInline ? sizeof(InlineDispatch) : (ROWS == kRowsEight ? W * stream_sums_bytes(C8) : 0));
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    auto kern = stream_gemm_kernel<C8, W, ROWS>;
+    auto kern = stream_gemm_kernel<C8, W, ROWS, KEEP>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(W * kWave), lds, stream, p);
     return EXF_OK;
 }
 
-template <int C8, int W>
+template <int C8, int W, StreamRows ROWS, bool KEPT>
+static int launch_stream_rows(const StreamGemm& p, hipStream_t stream)
+{
+    if constexpr (KEPT) {
+        if constexpr (ROWS != kRowsSorted) {  // (rows that are there in sorted order are not wanted again)
+            if (p.sorted_act != nullptr) return launch_stream_as<C8, W, ROWS, kKeepAct>(p, stream);
+        }
+        if constexpr (ROWS != kRowsInline) {  // (a first contraction)
+            if (p.sorted_act == nullptr) return launch_stream_as<C8, W, ROWS, kKeepOut>(p, stream);
+        }
+        return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: sorted rows of a contraction that has none");
+    } else {
+        return launch_stream_as<C8, W, ROWS, kKeepNone>(p, stream);
+    }
+}
+template <int C8, int W, bool KEPT>
 static int launch_stream(const StreamGemm& p, hipStream_t stream)
 {
-    if (p.topk_idx == nullptr) return launch_stream_as<C8, W, kRowsSorted>(p, stream);
-    if (p.max_rows <= 8) return launch_stream_as<C8, W, kRowsEight>(p, stream);
-    return p.max_rows <= kFewAssignments ? launch_stream_as<C8, W, kRowsFew>(p, stream) : launch_stream_as<C8, W, kRowsInline>(p, stream);
+    if (p.topk_idx == nullptr) return launch_stream_rows<C8, W, kRowsSorted, KEPT>(p, stream);
+    if (p.max_rows <= 8) return launch_stream_rows<C8, W, kRowsEight, KEPT>(p, stream);
+    return p.max_rows <= kFewAssignments ? launch_stream_rows<C8, W, kRowsFew, KEPT>(p, stream) : launch_stream_rows<C8, W, kRowsInline, KEPT>(p, stream);
 }
 
 // Columns per block, by a model of the launch (blocks of 8 columns: one row of 4096 x 1024 has 128 of them for 256 workgroups
@@ -665,6 +709,7 @@ static int launch_stream(const StreamGemm& p, hipStream_t stream)
 // 40.3; of 512 x 2048 15.3 and 14.3).  Among several, blocks of 8 columns only where an expert's rows hardly exceed a tile: up to
 // kFewAssignments in all (four experts of 512 x 2048, 120 rows 20.7 us with them and 18.5) and 28 an expert (two of 768 x 3072, 60
 // rows 23.0 and 20.4; 48 rows 16.4 and 16.9).
+template <bool KEPT>
 static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
 {
     const double A = p.max_rows, E = p.E_local;
@@ -682,10 +727,10 @@ static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
             best = c;
         }
     }
-    if (best == 8) return launch_stream<8, 4>(p, stream);
-    if (best == 4) return launch_stream<4, 4>(p, stream);
-    if (best == 2) return launch_stream<2, 8>(p, stream);
-    return launch_stream<1, 8>(p, stream);
+    if (best == 8) return launch_stream<8, 4, KEPT>(p, stream);
+    if (best == 4) return launch_stream<4, 4, KEPT>(p, stream);
+    if (best == 2) return launch_stream<2, 8, KEPT>(p, stream);
+    return launch_stream<1, 8, KEPT>(p, stream);
 }
 
 // ---------------------------------------------------------------------------- fp32
@@ -771,7 +816,7 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
 }
 
 // WI items per workgroup, WK wavefronts per item (they cut the reduction into parts).
-template <int C, int M, int WK, int WI, int D, bool INLINE>
+template <int C, int M, int WK, int WI, int D, bool INLINE, StreamKeep KEEP>
 __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGemm p)
 {
     constexpr int COLS = 16 * C, RS = COLS + 4;  // (padded: the 16 rows of a float4 column store hit distinct banks)
@@ -838,6 +883,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
 #undef EXF_EXACT_UNITS
     }
     __syncthreads();
+    if constexpr (INLINE && KEEP == kKeepAct) copy_sorted_rows<WK * WI * kWave, float>(p, a_row, offsets[p.E_local], p.a_div);
     if (!valid) return;
 
     // four columns of one row per thread: the wavefronts' sums in a fixed order, bias, activation, scale
@@ -862,18 +908,23 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
             if (bias != nullptr) v[j] += bias[n + j];
             if (p.epi == kEpiGeluErf) v[j] = gelu_erf_exact(v[j]);
             else if (p.epi == kEpiGeluTanh) v[j] = gelu_tanh_exact(v[j]);
-            v[j] *= scale;
+            if constexpr (KEEP != kKeepOut) v[j] *= scale;
+        }
+        if constexpr (KEEP == kKeepOut) {
+            *reinterpret_cast<float4*>(static_cast<float*>(p.sorted_out) + static_cast<size_t>(row_begin + r) * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = fmaf(scale, v[j], 0.0f);  // (the combine's bits)
         }
         *reinterpret_cast<float4*>(static_cast<float*>(p.out) + static_cast<size_t>(dst) * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
     }
 }
 
-template <int C, int M, int WK, int WI, int D, bool INLINE>
+template <int C, int M, int WK, int WI, int D, bool INLINE, StreamKeep KEEP>
 static int launch_exact_as(const StreamGemm& p, hipStream_t stream)
 {
     constexpr int TILE_ROWS = 16 * M;
     constexpr size_t lds = static_cast<size_t>(WK * WI) * TILE_ROWS * (16 * C + 4) * sizeof(float) + (INLINE ? sizeof(InlineDispatch) : 0);
-    auto kern = exact_gemm_kernel<C, M, WK, WI, D, INLINE>;
+    auto kern = exact_gemm_kernel<C, M, WK, WI, D, INLINE, KEEP>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     // row tiles: whole ones and at most one partial tile per expert with rows
@@ -889,7 +940,12 @@ static int launch_exact_as(const StreamGemm& p, hipStream_t stream)
 template <int C, int M, int WK, int WI, int D>
 static int launch_exact(const StreamGemm& p, hipStream_t stream)
 {
-    return p.topk_idx != nullptr ? launch_exact_as<C, M, WK, WI, D, true>(p, stream) : launch_exact_as<C, M, WK, WI, D, false>(p, stream);
+    if (p.topk_idx != nullptr) {
+        if (p.sorted_act != nullptr) return launch_exact_as<C, M, WK, WI, D, true, kKeepAct>(p, stream);
+        return launch_exact_as<C, M, WK, WI, D, true, kKeepNone>(p, stream);
+    }
+    if (p.sorted_out != nullptr) return launch_exact_as<C, M, WK, WI, D, false, kKeepOut>(p, stream);
+    return launch_exact_as<C, M, WK, WI, D, false, kKeepNone>(p, stream);
 }
 
 // Enough tiles of 64 columns x 16 M rows for the chip: one wavefront per tile where the reduction is short (nothing to
@@ -933,7 +989,10 @@ bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt)
 
 int launch_stream_gemm(const StreamGemm& p, int dt, hipStream_t stream)
 {
-    if (dt == EXF_BF16) return launch_stream_bf16(p, stream);
+    if (dt == EXF_BF16) {
+        if (p.sorted_act == nullptr && p.sorted_out == nullptr) return launch_stream_bf16<false>(p, stream);
+        return launch_stream_bf16<true>(p, stream);
+    }
     return p.max_rows <= 16ll * p.E_local ? launch_exact_rows<1>(p, stream) : launch_exact_rows<4>(p, stream);
 }
 

@@ -250,7 +250,20 @@ def test_layer_forward_of_a_few_rows(T, k, E, E_local, d, f, routing):
     _layer_against_calls(T, k, E, E_local, "bf16", True, routing, d, f)
 
 
-def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f):
+# the four calls in one: sorted by the first contraction (one to eight rows, up to 64, up to 1024; several row tiles a workgroup copies) and
+# by a dispatch of its own, weighted by the second contraction (streamed, tiles of all kinds, fp32 in tiles of 16 and 64 rows) and by a combine
+@pytest.mark.parametrize("T,k,E,E_local,dtype,routing,d,f", [
+    (1, 1, 8, 8, "bf16", "gate", 64, 128), (8, 1, 8, 3, "bf16", "gate", 1024, 256), (16, 2, 33, 33, "bf16", "gate", 128, 64), (64, 1, 5, 5, "bf16", "ids", 192, 320),
+    (7, 1, 64, 9, "bf16", "dropped", 128, 64), (65, 1, 20, 20, "bf16", "ids", 64, 192), (1024, 1, 64, 64, "bf16", "ids", 128, 64), (512, 2, 64, 48, "bf16", "gate", 64, 64),
+    (1025, 1, 64, 64, "bf16", "ids", 64, 64), (300, 1, 3, 2, "bf16", "ids", 320, 576), (2000, 1, 7, 7, "bf16", "gate", 192, 128), (700, 1, 1, 1, "bf16", "gate", 1088, 256),
+    (1100, 1, 9, 4, "bf16", "dropped", 64, 64), (40, 1, 6, 6, "f32", "ids", 36, 132), (1024, 1, 8, 4, "f32", "ids", 44, 812), (1025, 1, 4, 4, "f32", "ids", 64, 196),
+    (512, 2, 5, 5, "f32", "gate", 64, 128)])
+def test_unfused_layer_is_its_calls(T, k, E, E_local, dtype, routing, d, f):
+    _say(f"unfused layer T={T} k={k} E={E} E_local={E_local} {dtype} {routing} {d} x {f}")
+    _layer_against_calls(T, k, E, E_local, dtype, False, routing, d, f, ("x_sorted", "y_sorted"))
+
+
+def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f, more=()):
     from paper_2401_08383_amd.pipeline import MoELayerRun
 
     g = torch.Generator(device="cuda")
@@ -270,7 +283,7 @@ def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f):
     elif routing == "dropped":
         idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
     run = MoELayerRun(rnd(T, d), rnd(E, d), rnd(E_local, f, d), rnd(E_local, d, f), k, k > 1, expert_map=expert_map, topk_idx=idx, fused=fused)
-    names = ["topk_idx", "topk_w", "src_of_sorted", "sorted_of_src", "expert_counts", "expert_offsets", "out"]
+    names = ["topk_idx", "topk_w", "src_of_sorted", "sorted_of_src", "expert_counts", "expert_offsets", "out", *more]
 
     def results(how):
         for n in names:
