@@ -784,24 +784,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     timeline_stamp(map, 0);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap)
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + 4] = 0ull;  // stays zero if this workgroup has no tile
-    if (map.unrouted != nullptr) {
-        // output rows no sorted row writes (dropped or remote assignments): one wavefront looks at 64
-        // rows at a time and clears those it finds, all lanes together
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-        const int lane = lane_id();
-        const int64_t stride = static_cast<int64_t>(gridDim.x) * (WAVES * kWave);
-        for (int64_t first = static_cast<int64_t>(blockIdx.x) * (WAVES * kWave) + wave * kWave; first < map.n_unrouted; first += stride) {
-            const int64_t t = first + lane;
-            const int pos = t < map.n_unrouted ? map.unrouted[t] : 0;
-            unsigned long long todo = __ballot(pos < 0);
-            while (todo != 0) {
-                const int b = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                uint4* row = reinterpret_cast<uint4*>(out + static_cast<size_t>(first + b) * N);
-                for (int c = lane; c < N / 8; c += kWave) row[c] = make_uint4(0u, 0u, 0u, 0u);
-            }
-        }
-    }
+    if (map.unrouted != nullptr) clear_unrouted_rows(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
     Tile2D tile;
     if (!locate_tile(offsets, E_local, NT, N, max_rows, static_cast<int>(blockIdx.x), map, tile)) return;
     timeline_stamp(map, 1);

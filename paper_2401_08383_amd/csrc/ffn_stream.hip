@@ -28,24 +28,10 @@
 namespace exf {
 
 // ---------------------------------------------------------------------------- shared
-// Output rows no sorted row writes: a wavefront looks at 64 rows at a time and clears those it finds.
 template <typename ST>
-__device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int64_t wave_id, int64_t n_waves)
+__device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int waves)
 {
-    if (p.unrouted == nullptr) return;
-    const int lane = lane_id();
-    const int vec_per_row = p.N * static_cast<int>(sizeof(ST)) / 16;
-    for (int64_t first = wave_id * kWave; first < p.n_unrouted; first += n_waves * kWave) {
-        const int64_t t = first + lane;
-        const int pos = t < p.n_unrouted ? p.unrouted[t] : 0;
-        unsigned long long todo = __ballot(pos < 0);
-        while (todo != 0) {
-            const int b = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            uint4* row = reinterpret_cast<uint4*>(p.out) + static_cast<size_t>(first + b) * vec_per_row;
-            for (int c = lane; c < vec_per_row; c += kWave) row[c] = make_uint4(0u, 0u, 0u, 0u);
-        }
-    }
+    if (p.unrouted != nullptr) clear_unrouted_rows(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N * static_cast<int>(sizeof(ST)) / 16, waves);
 }
 
 // The sorted copy of the operand rows, sorted row s by workgroup s % gridDim.x (list[s] / a_div: its row): behind everything else, where
@@ -589,7 +575,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             list = d->list;
             offsets = d->offs;
         }
-        clear_unrouted<bf16_t>(p, static_cast<int64_t>(blockIdx.x) * W + wave, static_cast<int64_t>(gridDim.x) * W);
+        clear_unrouted<bf16_t>(p, W);
         et = scan_row_tiles(p, offsets, TILE_ROWS);
     }
     const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
@@ -823,7 +809,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     constexpr int TILE_ROWS = 16 * M;
     extern __shared__ float red[];  // [WI][WK][TILE_ROWS][RS]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    clear_unrouted<float>(p, blockIdx.x * (WK * WI) + wave, static_cast<int64_t>(gridDim.x) * (WK * WI));
+    clear_unrouted<float>(p, WK * WI);
     const int32_t *a_row = p.a_row, *offsets = p.offsets;
     if constexpr (INLINE) {
         InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * WK * TILE_ROWS * RS);

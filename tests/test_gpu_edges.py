@@ -306,6 +306,25 @@ def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f, more=())
         assert torch.equal(a, b), n
 
 
+# one row a wavefront, several, 64 at a time and more than once round; the streamed contraction, tiles, fp32
+@pytest.mark.parametrize("T,dtype", [(98, "bf16"), (1500, "bf16"), (7001, "bf16"), (250003, "bf16"), (700, "f32"), (40000, "f32")])
+def test_rows_that_nobody_writes_are_cleared(T, dtype):
+    _say(f"cleared rows T={T} {dtype}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1700 + T)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn((T, 64), device="cuda", generator=g).to(dt)
+    w1, w2 = (torch.randn(shape, device="cuda", generator=g).to(dt) for shape in ((2, 64, 64), (2, 64, 64)))
+    idx = torch.randint(-1, 12, (T, 1), device="cuda", generator=g, dtype=torch.int32)
+    maps = B.moe_dispatch(x, idx, 2, gather=False)
+    out = torch.full_like(x, -7)
+    B.moe_expert_ffn_fused(x, maps.src_of_sorted, maps.sorted_of_src, torch.ones((T, 1), device="cuda"), maps.expert_offsets, w1, w2, out=out)
+    kept = maps.sorted_of_src.flatten()[:T] >= 0
+    assert 0 < int(kept.sum()) < T // 4
+    assert torch.equal(out[~kept], torch.zeros_like(out[~kept]))
+    assert bool((out[kept] != -7).any(dim=1).all())
+
+
 # ----------------------------------------------------------------------------- gate: ragged reductions, both tile heights
 @pytest.mark.parametrize("T,d,E,k", [(1, 8, 1, 1), (17, 56, 16, 2), (16, 72, 17, 2), (33, 2056, 33, 1), (8191, 64, 64, 2), (8192, 200, 64, 2),
                                      (8200, 136, 17, 1), (40, 4096, 32, 2), (64 * 128 + 65, 1088, 48, 1)])
