@@ -784,7 +784,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     timeline_stamp(map, 0);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap)
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + 4] = 0ull;  // stays zero if this workgroup has no tile
-    if (map.unrouted != nullptr) clear_unrouted_rows(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
+    if (map.unrouted != nullptr) clear_unrouted_rows<false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
     Tile2D tile;
     if (!locate_tile(offsets, E_local, NT, N, max_rows, static_cast<int>(blockIdx.x), map, tile)) return;
     timeline_stamp(map, 1);
@@ -965,8 +965,7 @@ extern "C" int moe_expert_ffn(const void* x_sorted, const int32_t* expert_offset
         first.offsets = second.offsets = expert_offsets;
         first.max_rows = second.max_rows = static_cast<int>(A);
         first.E_local = second.E_local = E_local;
-        rc = launch_stream_gemm(first, dt, s);
-        if (rc == EXF_OK) rc = launch_stream_gemm(second, dt, s);
+        rc = launch_stream_pair(first, second, dt, s);
     } else {
         rc = launch_first_contraction(x_sorted, expert_offsets, w1, b1, A, d, f, E_local, epi, workspace, s, RowMap{});
         if (rc == EXF_OK) rc = launch_second_contraction(workspace, expert_offsets, w2, b2, A, f, d, E_local, y_sorted, s, RowMap{});
@@ -1090,8 +1089,7 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
         first.offsets = second.offsets = expert_offsets;
         first.max_rows = second.max_rows = static_cast<int>(A);
         first.E_local = second.E_local = E_local;
-        rc = launch_stream_gemm(first, dt, s);
-        if (rc == EXF_OK) rc = launch_stream_gemm(second, dt, s);
+        rc = launch_stream_pair(first, second, dt, s);
     } else {
         rc = launch_first_contraction(x, expert_offsets, w1, b1, A, d, f, E_local, epi, hidden, s, gather);
         if (rc == EXF_OK) rc = launch_second_contraction(hidden, expert_offsets, w2, b2, A, f, d, E_local, second_out, s, scatter);
@@ -1131,8 +1129,7 @@ int exf::ffn_combined(const void* x_sorted, const int32_t* src_of_sorted, const 
         first.offsets = second.offsets = expert_offsets;
         first.max_rows = second.max_rows = static_cast<int>(T);
         first.E_local = second.E_local = E_local;
-        rc = launch_stream_gemm(first, dt, s);
-        if (rc == EXF_OK) rc = launch_stream_gemm(second, dt, s);
+        rc = launch_stream_pair(first, second, dt, s);
     } else {
         RowMap scatter{};
         scatter.out_row = src_of_sorted, scatter.out_scale = topk_w;

@@ -47,13 +47,17 @@ __device__ __forceinline__ float gelu_tanh_fast(float z)
 
 // Output rows that no sorted row writes (unrouted[t] < 0), dealt evenly to all wavefronts of the launch, at most 64 at a time.  (64 to each of
 // the first ones, these cleared them one after the other in front of their share of the product: 98 tokens of which a tenth is kept, one
-// expert of 1600 x 6400, 49.1 us, now 41.9; 1759 of which a fifth, 1216 x 4864, 42.7 and 36.6.)
+// expert of 1600 x 6400, 49.1 us, now 41.9; 1759 of which a fifth, 1216 x 4864, 42.7 and 36.6.)  ALL_AT_ONCE: 64 to each of the first ones all
+// the same, for launches of a few microseconds that wait for every instruction in front of their loads (fp32, 394 tokens, 4 experts of
+// 76 x 492 15.0 us dealt out and 14.7).
+template <bool ALL_AT_ONCE>
 __device__ __forceinline__ void clear_unrouted_rows(const int32_t* __restrict__ unrouted, int n_unrouted, uint4* __restrict__ out, int vec_per_row, int waves)
 {
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t all = gridDim.x * static_cast<uint32_t>(waves);
-    const uint32_t mine = min((static_cast<uint32_t>(n_unrouted) + all - 1u) / all, static_cast<uint32_t>(kWave));
+    uint32_t mine = ALL_AT_ONCE ? kWave : 1;
+    while (mine < static_cast<uint32_t>(kWave) && static_cast<uint64_t>(mine) * all < static_cast<uint64_t>(n_unrouted)) mine *= 2;  // (a division takes a quarter of a microsecond)
     for (int64_t first = static_cast<int64_t>(blockIdx.x * static_cast<uint32_t>(waves) + wave) * mine; first < n_unrouted; first += static_cast<int64_t>(all) * mine) {
         const int64_t t = first + lane;
         const int pos = lane < static_cast<int>(mine) && t < n_unrouted ? unrouted[t] : 0;
@@ -111,6 +115,20 @@ constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for i
 // Is the path taken for A rows of `dt` spread over E_local experts?
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
+// fp32: are both contractions one launch, and that launch (out of the first one is not written).
+bool exact_pair_fits(int64_t A, int d, int f, int E_local);
+int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream);
+inline int launch_stream_pair(const StreamGemm& first, const StreamGemm& second, int dt, hipStream_t stream)
+{
+    if (dt == EXF_F32 && exact_pair_fits(first.max_rows, first.K, first.N, first.E_local)) {
+        // (two launches may write where the first one has read)
+        const uintptr_t bytes = static_cast<uintptr_t>(first.max_rows) * first.K * 4, act = reinterpret_cast<uintptr_t>(first.act);
+        auto apart = [&](const void* to) { return reinterpret_cast<uintptr_t>(to) >= act + bytes || reinterpret_cast<uintptr_t>(to) + bytes <= act; };
+        if (apart(second.out) && (second.sorted_out == nullptr || apart(second.sorted_out))) return launch_exact_pair(first, second, stream);
+    }
+    const int rc = launch_stream_gemm(first, dt, stream);
+    return rc == EXF_OK ? launch_stream_gemm(second, dt, stream) : rc;
+}
 
 // moe_dispatch and the expert FFN as one: the first contraction sorts the assignments itself.  Only where routed_path_fits() says so;
 // the maps, and the sorted rows where they are wanted, are written as moe_dispatch and moe_expert_ffn write them.

@@ -28,12 +28,6 @@
 namespace exf {
 
 // ---------------------------------------------------------------------------- shared
-template <typename ST>
-__device__ __forceinline__ void clear_unrouted(const StreamGemm& p, int waves)
-{
-    if (p.unrouted != nullptr) clear_unrouted_rows(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N * static_cast<int>(sizeof(ST)) / 16, waves);
-}
-
 // The sorted copy of the operand rows, sorted row s by workgroup s % gridDim.x (list[s] / a_div: its row): behind everything else, where
 // the loads of nothing wait for it.
 template <int THREADS, typename ST>
@@ -575,7 +569,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             list = d->list;
             offsets = d->offs;
         }
-        clear_unrouted<bf16_t>(p, W);
+        if (p.unrouted != nullptr) clear_unrouted_rows<false>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
         et = scan_row_tiles(p, offsets, TILE_ROWS);
     }
     const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
@@ -809,7 +803,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     constexpr int TILE_ROWS = 16 * M;
     extern __shared__ float red[];  // [WI][WK][TILE_ROWS][RS]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    clear_unrouted<float>(p, WK * WI);
+    if (p.unrouted != nullptr) clear_unrouted_rows<true>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 4, WK * WI);
     const int32_t *a_row = p.a_row, *offsets = p.offsets;
     if constexpr (INLINE) {
         InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * WK * TILE_ROWS * RS);
@@ -934,16 +928,208 @@ static int launch_exact(const StreamGemm& p, hipStream_t stream)
     return launch_exact_as<C, M, WK, WI, D, false, kKeepNone>(p, stream);
 }
 
-// Enough tiles of 64 columns x 16 M rows for the chip: one wavefront per tile where the reduction is short (nothing to
-// add up), four otherwise.  A smaller problem is cut into 16 x 16 tiles with four wavefronts along the reduction
-// (512 tokens x 8 experts x 64 x 256: 36 workgroups of 64 rows took 8.3 us in the second
-// contraction, 4 now).
+// Enough tiles of 64 columns x 16 M rows for the chip: one wavefront per tile of 64 rows where the reduction is short (nothing to
+// add up), two per 32 columns of 16 rows (7688 rows, 5 experts of 132 x 396, both contractions 54.3 us, with one per 64 columns 62.7; 3017, 6 of 96 x 284
+// 19.1 and 22.5), four for long reductions.  A smaller problem is cut into 16 x 16 tiles with four wavefronts along the reduction
+// (512 tokens x 8 experts x 64 x 256: 36 workgroups of 64 rows took 8.3 us in the second contraction, 4 now).
 template <int M>
 static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 {
     const int64_t tiles = (p.max_rows < p.E_local ? p.max_rows : p.E_local) + p.max_rows / (16 * M);
     if (tiles * ((p.N + 63) / 64) < 384) return launch_exact<1, 1, 4, 1, 2>(p, stream);
-    return p.K <= 1024 ? launch_exact<4, M, 1, 4, 2>(p, stream) : launch_exact<4, M, 4, 1, 2>(p, stream);
+    if (p.K > 1024) return launch_exact<4, M, 4, 1, 2>(p, stream);
+    if constexpr (M == 1) return launch_exact<2, 1, 2, 2, 2>(p, stream);
+    else return launch_exact<4, M, 1, 4, 2>(p, stream);
+}
+
+// ---------------------------------------------------------------------------- fp32, both contractions at once
+// A workgroup takes a tile of 16 sorted rows through both contractions: the hidden activations stay in LDS, and the second launch goes with
+// what it waits for (the first one's last workgroup, row ranges, row ids, a round trip for the weights; those of the second contraction
+// are asked for behind the first one's products).  What it cannot do is spread a tile over compute units: one takes the expert's weights
+// in at some 40 bytes a cycle, 0.2 us for 1000 d f, so it is for layers whose tiles fill the chip (see exact_pair_fits).
+// Every sum is that of exact_gemm_kernel<1, 1, 4, 1>: the reduction in four parts, added in order.  Two launches and one, us: 3724 rows, 10 experts
+// of 120 x 444 26.0 and 17.6; 3333, 9 of 92 x 192 16.0 and 10.1; 2692, 2 of 56 x 256 14.8 and 9.1; 7688, 5 of 132 x 396 54.3 and 37.6.
+constexpr int kPairRows = 16, kPairWaves = 16, kPairParts = 4;
+constexpr int kPairAhead = 2;  // units of 32 asked for ahead (two workgroups share a compute unit: 64 registers)
+struct PairWeights {
+    f32x4_t w[kPairAhead][2];
+    const float* row;
+    int K;
+    __device__ __forceinline__ void load(int u, int s)
+    {
+        const int g = lane_id() >> 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = u * kExactUnit + h * 16 + g * 4;
+            w[s][h] = *reinterpret_cast<const f32x4_t*>(row + (k < K ? k : 0));
+        }
+    }
+    __device__ __forceinline__ void begin(const float* weight, int n0, int N, int K_, int u_begin, int u_end)
+    {
+        row = weight + static_cast<size_t>(min(n0 + (lane_id() & 15), N - 1)) * K_;
+        K = K_;
+        if (u_begin >= u_end) return;
+#pragma unroll
+        for (int s = 0; s < kPairAhead; ++s) load(min(u_begin + s, u_end - 1), s);
+    }
+    // Units [u_begin, u_end) (behind begin()); act: 16 rows of `stride` floats in LDS.  `after(u)`: unit u is in acc.
+    template <typename After>
+    __device__ __forceinline__ void sum(const float* act, int stride, int u_begin, int u_end, f32x4_t& acc, After after)
+    {
+        const int g = lane_id() >> 4;
+        const float* row_a = act + (lane_id() & 15) * stride;
+        auto compute = [&](int u, int s) {
+            f32x4_t a[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = u * kExactUnit + h * 16 + g * 4;  // K % 4 == 0: a piece is inside or outside as a whole
+                a[h] = *reinterpret_cast<const f32x4_t*>(row_a + (k < K ? k : 0));
+                if (k >= K) a[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][h][j], a[h][j], acc, 0, 0, 0);
+            after(u);
+        };
+        int u = u_begin;
+        for (; u + kPairAhead < u_end; u += kPairAhead) {
+#pragma unroll
+            for (int s = 0; s < kPairAhead; ++s) {
+                compute(u + s, s);
+                __builtin_amdgcn_sched_barrier(0);
+                load(min(u + kPairAhead + s, u_end - 1), s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kPairAhead; ++s)
+            if (u + s < u_end) compute(u + s, s);
+    }
+};
+__host__ __device__ constexpr size_t pair_floats(int d, int f) { return static_cast<size_t>(kPairRows) * (f + 4) + static_cast<size_t>(kPairParts) * kPairRows * (d + 4); }
+
+__global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const StreamGemm p, const StreamGemm q)
+{
+    extern __shared__ __attribute__((aligned(16))) float pair_smem[];
+    touch_arguments<2 * sizeof(StreamGemm)>();
+    const int lane = lane_id(), r16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int d = p.K, f = p.N;
+    const int act_stride = d + 4, hid_stride = f + 4;  // (padded: 16 rows lie in distinct banks)
+    float* hid = pair_smem;                     // [16][f + 4]
+    float* act = hid + kPairRows * hid_stride;  // [16][d + 4], later the sums of the parts: [4][16][d + 4]
+    if (q.unrouted != nullptr) clear_unrouted_rows<false>(q.unrouted, q.n_unrouted, static_cast<uint4*>(q.out), d / 4, kPairWaves);
+    // every XCD takes a contiguous share of the tiles: those of an expert meet in one L2
+    const ExpertTiles et = scan_row_tiles(p, p.offsets, kPairRows);
+    const int xcd = static_cast<int>(blockIdx.x % kXcdCount);
+    const int item = static_cast<int>(static_cast<int64_t>(et.total) * xcd / kXcdCount) + static_cast<int>(blockIdx.x / kXcdCount);
+    if (item >= static_cast<int>(static_cast<int64_t>(et.total) * (xcd + 1) / kXcdCount)) return;
+    const int e = __builtin_ctzll(__ballot(item < et.incl));  // (item < total: some lane owns it)
+    const int tile = item - (wave_read_lane(et.incl, e) - wave_read_lane(et.tiles, e));
+    const int row_begin = wave_read_lane(et.lo, e) + tile * kPairRows, rows = min(kPairRows, wave_read_lane(et.hi, e) - row_begin);
+
+    // a wavefront brings one row and stores it; the first weights travel with the rows
+    const float* w1 = static_cast<const float*>(p.weight) + static_cast<size_t>(e) * f * d;
+    const float* w2 = static_cast<const float*>(q.weight) + static_cast<size_t>(e) * d * f;
+    const int units1 = (d + kExactUnit - 1) / kExactUnit, units2 = (f + kExactUnit - 1) / kExactUnit;
+    const int sorted = row_begin + min(wave, rows - 1);  // (rows past the end repeat the last one)
+    int from = sorted;
+    if (p.a_row != nullptr) from = p.a_div > 1 ? static_cast<int>(static_cast<unsigned>(p.a_row[sorted]) / static_cast<unsigned>(p.a_div)) : p.a_row[sorted];
+    int dst = sorted;
+    float scale = 1.0f;
+    if (q.out_row != nullptr) {
+        dst = q.out_row[sorted];
+        scale = q.out_scale[dst];
+    }
+    PairWeights pw;
+    pw.begin(w1, wave * 16, f, d, 0, units1);
+    for (int c = lane; c < d / 4; c += kWave) {
+        reinterpret_cast<float4*>(act + wave * act_stride)[c] = reinterpret_cast<const float4*>(static_cast<const float*>(p.act) + static_cast<size_t>(from) * d)[c];
+    }
+    __syncthreads();
+
+    // ---- hidden activations: 16 columns by a wavefront, all four parts
+    const int part_end[3] = {units1 / kPairParts, 2 * units1 / kPairParts, 3 * units1 / kPairParts};
+    for (int n0 = wave * 16; n0 < f; n0 += kPairWaves * 16) {
+        f32x4_t z = f32x4_t{0.f, 0.f, 0.f, 0.f}, acc = z;
+        pw.sum(act, act_stride, 0, units1, acc, [&](int u) {
+            if (u + 1 == part_end[0] || u + 1 == part_end[1] || u + 1 == part_end[2]) {
+                z += acc;
+                acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        });
+        z += acc;
+        if (n0 + kPairWaves * 16 < f) pw.begin(w1, n0 + kPairWaves * 16, f, d, 0, units1);
+        const int n = n0 + g * 4;
+        if (n < f) {  // f % 4 == 0: the four columns are inside or outside together
+            float v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j] = z[j];
+                if (p.bias != nullptr) v[j] += static_cast<const float*>(p.bias)[static_cast<size_t>(e) * f + n + j];
+                v[j] = p.epi == kEpiGeluErf ? gelu_erf_exact(v[j]) : gelu_tanh_exact(v[j]);
+            }
+            *reinterpret_cast<float4*>(hid + r16 * hid_stride + n) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    }
+
+    // ---- outputs: (16 columns, part) by a wavefront
+    const int items2 = (d + 15) / 16 * kPairParts;
+    auto begin2 = [&](int i) {
+        const int part = i % kPairParts;
+        pw.begin(w2, i / kPairParts * 16, d, f, part * units2 / kPairParts, (part + 1) * units2 / kPairParts);
+    };
+    if (wave < items2) begin2(wave);
+    __syncthreads();
+    float* red = act;
+    for (int i = wave; i < items2; i += kPairWaves) {
+        const int part = i % kPairParts, n = i / kPairParts * 16 + g * 4;
+        f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        pw.sum(hid, hid_stride, part * units2 / kPairParts, (part + 1) * units2 / kPairParts, acc, [](int) {});
+        if (i + kPairWaves < items2) begin2(i + kPairWaves);
+        if (n < d) *reinterpret_cast<f32x4_t*>(red + (part * kPairRows + r16) * act_stride + n) = acc;
+    }
+    __syncthreads();
+    if (wave >= rows) return;
+    const float* bias = q.bias != nullptr ? static_cast<const float*>(q.bias) + static_cast<size_t>(e) * d : nullptr;
+    for (int c = lane; c < d / 4; c += kWave) {
+        f32x4_t z = *reinterpret_cast<const f32x4_t*>(red + wave * act_stride + c * 4);
+#pragma unroll
+        for (int part = 1; part < kPairParts; ++part) z += *reinterpret_cast<const f32x4_t*>(red + (part * kPairRows + wave) * act_stride + c * 4);
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = bias != nullptr ? z[j] + bias[c * 4 + j] : z[j];
+        if (q.sorted_out != nullptr) {
+            reinterpret_cast<float4*>(static_cast<float*>(q.sorted_out) + static_cast<size_t>(sorted) * d)[c] = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = fmaf(scale, v[j], 0.0f);  // (the combine's bits)
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] *= scale;
+        }
+        reinterpret_cast<float4*>(static_cast<float*>(q.out) + static_cast<size_t>(dst) * d)[c] = make_float4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+// The line: 6.5 us and 0.2 for 1000 d f at one tile a compute unit, against 11 us and 1.4 for a million tiles d f in two launches; both within a
+// few microseconds of 50 layers of 600 to 8000 rows (79 tiles of 232 x 232 20.6 and 16.7, 98 of 52 x 576 16.3 and 18.5, 117 of
+// 188 x 796 39.6 and 41.5, 227 of 220 x 968 49.8 and 74.2).  Lists that a first contraction sorts have at most 80 tiles: two launches.
+bool exact_pair_fits(int64_t A, int d, int f, int E_local)
+{
+    const int64_t tiles = A / kPairRows + (A < E_local ? A : E_local);
+    return A > kInlineDispatchMax && pair_floats(d, f) * sizeof(float) <= 160 * 1024 && static_cast<int64_t>(d) * f * (143 - tiles) <= 3200000;
+}
+
+int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream)
+{
+    static std::atomic<uint64_t> allowed{0};
+    if (int rc = allow_lds(reinterpret_cast<const void*>(exact_pair_kernel), 160 * 1024, allowed, "moe_expert_ffn")) return rc;
+    const int64_t A = first.max_rows;
+    const int64_t share = (A / kPairRows + (A < first.E_local ? A : first.E_local)) / kXcdCount + 1;  // tiles of an XCD at most
+    hipLaunchKernelGGL(exact_pair_kernel, dim3(static_cast<unsigned>(share * kXcdCount)), dim3(kPairWaves * kWave), pair_floats(first.K, first.N) * sizeof(float),
+                       stream, first, second);
+    return EXF_OK;
 }
 
 // ---------------------------------------------------------------------------- host
@@ -979,7 +1165,8 @@ int launch_stream_gemm(const StreamGemm& p, int dt, hipStream_t stream)
         if (p.sorted_act == nullptr && p.sorted_out == nullptr) return launch_stream_bf16<false>(p, stream);
         return launch_stream_bf16<true>(p, stream);
     }
-    return p.max_rows <= 16ll * p.E_local ? launch_exact_rows<1>(p, stream) : launch_exact_rows<4>(p, stream);
+    // tiles of 64 rows for the reuse of weights that do not lie in the L2s (3544 rows, 4 experts of 232 x 524, both contractions 61.1 us with them, 47.6)
+    return p.max_rows <= 16ll * p.E_local || static_cast<int64_t>(p.K) * p.N <= (1 << 18) ? launch_exact_rows<1>(p, stream) : launch_exact_rows<4>(p, stream);
 }
 
 }  // namespace exf

@@ -198,6 +198,37 @@ def test_exact_ffn_ragged(oracle, counts, d, f):
     P._ffn_case(oracle, "f32", counts, d, f, 0, True, seed=1500 + d + f)
 
 
+# both contractions by one workgroup a row tile: last columns and reductions of any length, tiles of one row, experts without rows, either side
+# of the line (a long list of few tiles, weights that do not fit, the last list that a first contraction sorts)
+@pytest.mark.parametrize("d,f", [(4, 4), (36, 20), (132, 260), (256, 1024), (68, 2052)])
+@pytest.mark.parametrize("counts", [[0, 1, 1500, 16, 17, 64, 65], [3001, 0, 5], [1025], [1024], [160] * 16])
+@pytest.mark.parametrize("act", [0, 1])
+def test_exact_ffn_in_one_launch(oracle, counts, d, f, act):
+    P._ffn_case(oracle, "f32", counts, d, f, act, act == 0, seed=1540 + d + f)
+
+
+@pytest.mark.parametrize("T,k,E,E_local,fused,routing,d,f", [
+    (3001, 1, 9, 9, True, "gate", 44, 212), (3001, 1, 9, 4, True, "ids", 256, 92), (2000, 2, 5, 5, True, "gate", 96, 132), (5000, 1, 3, 1, True, "dropped", 32, 128),
+    (3001, 1, 9, 4, False, "ids", 100, 60), (1100, 2, 16, 16, False, "gate", 64, 128), (4096, 1, 16, 16, False, "gate", 256, 1024)])
+def test_exact_layer_in_one_launch(T, k, E, E_local, fused, routing, d, f):
+    _say(f"fp32 layer T={T} k={k} E={E} E_local={E_local} fused={fused} {routing} {d} x {f}")
+    _layer_against_calls(T, k, E, E_local, "f32", fused, routing, d, f, () if fused else ("x_sorted", "y_sorted"))
+
+
+def test_exact_ffn_in_place():
+    """Rows that are written where they were read: the same results in two launches."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1590)
+    x = torch.randn((3000, 64), device="cuda", generator=g)
+    w1, w2 = torch.randn((5, 128, 64), device="cuda", generator=g), torch.randn((5, 64, 128), device="cuda", generator=g)
+    off = torch.tensor([0, 700, 700, 1500, 2999, 3000], dtype=torch.int32, device="cuda")
+    y = B.moe_expert_ffn(x, off, w1, w2)
+    ws = torch.empty(B.lib().moe_expert_ffn_workspace_bytes(3000, 64, 128, 5, B.EXF_F32), dtype=torch.uint8, device="cuda")
+    B._check(B.lib().moe_expert_ffn(x.data_ptr(), off.data_ptr(), w1.data_ptr(), None, w2.data_ptr(), None, 3000, 64, 128, 5, 0, B.EXF_F32, x.data_ptr(),
+                                    ws.data_ptr(), ws.numel(), B._stream()))
+    assert float((x - y).abs().max()) <= 1e-5 * float(y.abs().max())
+
+
 # ----------------------------------------------------------------------------- dispatch: every workgroup counts the whole list
 @pytest.mark.parametrize("T,k,d,E,E_local", [
     (1, 1, 8, 1, 1), (7, 1, 72, 3, 3), (9, 2, 1032, 64, 64), (2048, 2, 64, 8, 8), (4097, 1, 136, 40, 7), (3584, 2, 16, 64, 64), (7169, 1, 16, 64, 64),
