@@ -67,13 +67,17 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
     while (p.copies < 16 && hist_bytes * g * (p.copies * 2) <= kAffHistBudget) p.copies *= 2;
     p.Q = pairs > 0 ? (pairs + g - 1) / g : 1;
     p.vec = trace_vec(N);
-    const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;  // tokens one pass of the workgroup covers
     int c_target = kTargetWorkgroups / p.Q;
     if (c_target < 1) c_target = 1;
+    // at least a sweep (the second launch reads all chunks: 3 x 79098 tokens in chunks of 512 17.0 us, of 4096 9.2), past that whole wavefronts (one
+    // cut by the end of its chunk takes the checked path), not sweeps: 24 x 135000 tokens were 17 chunks for 32
+    // (16.3 us, now 14.4; 24 x 500000 of 52 experts 20.0 and 17.9)
+    const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;  // tokens one pass of the workgroup covers
+    const int64_t unit = static_cast<int64_t>(kWave) * p.vec;
     int64_t chunk = (N + c_target - 1) / c_target;
-    chunk = (chunk + sweep - 1) / sweep * sweep;
+    chunk = (chunk + unit - 1) / unit * unit;
     if (chunk < sweep) chunk = sweep;
-    if (chunk > kAffMaxChunk) chunk = kAffMaxChunk / sweep * sweep;
+    if (chunk > kAffMaxChunk) chunk = kAffMaxChunk / unit * unit;
     p.chunk = chunk;
     p.C = static_cast<int>(N > 0 ? (N + chunk - 1) / chunk : 0);
     size_t off = 0;
@@ -117,15 +121,9 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
     const int q = j % Q;
     if (c >= C) return;
 
-    const int lds_words = copies * g * words + g * E + E + 1 + g;
-    for (int i = threadIdx.x; i < lds_words; i += kTraceThreads) lds[i] = 0u;
     const int pairs = L - 1;
     const int l0 = q * g;                                  // first column of this group
     const int l1 = pairs > 0 ? min(l0 + g, pairs) : 0;     // last column (pairs l0 .. l1-1)
-    if (placement != nullptr)
-        for (int i = threadIdx.x; i < (l1 - l0 + 1) * E; i += kTraceThreads) device[i] = placement[l0 * E + i];
-    __syncthreads();
-
     const bool owns_last = (l1 == L - 1);
     const int64_t n_begin = static_cast<int64_t>(c) * chunk;
     const int64_t n_end = min(N, n_begin + chunk);
@@ -148,8 +146,16 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
             }
     };
     TokVec<VEC> col[kAffMaxGroup + 1], nxt[kAffMaxGroup + 1];
-    load_cols(n_begin + static_cast<int64_t>(threadIdx.x) * VEC, col);
-    for (int64_t base = n_begin; base < n_end; base += sweep) {
+    const int devices = placement != nullptr ? (l1 - l0 + 1) * E : 0;  // (at most 4 x 64)
+    int32_t my_device = 0;
+    if (placement != nullptr) my_device = placement[l0 * E + min(static_cast<int>(threadIdx.x), devices - 1)];
+    load_cols(n_begin + static_cast<int64_t>(threadIdx.x) * VEC, col);  // (they travel while the counters are cleared)
+    const int lds_words = copies * g * words + g * E + E + 1 + g;
+    for (int i = threadIdx.x; i < lds_words; i += kTraceThreads) lds[i] = 0u;
+    if (static_cast<int>(threadIdx.x) < devices) device[threadIdx.x] = my_device;
+    barrier_for_lds();
+    const int64_t wave_first = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)) * (kWave * VEC);
+    for (int64_t base = n_begin; base + wave_first < n_end; base += sweep) {
         const int64_t n0 = base + static_cast<int64_t>(threadIdx.x) * VEC;
         load_cols(n0 + sweep, nxt);
         // Fast path (the normal case): every id this wavefront holds in the sweep is inside [0,E) and
@@ -224,24 +230,50 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
     if (invalid_local) atomicAdd(invalid_cnt, invalid_local);
     __syncthreads();
 
-    // flush: sum the replicas (packed halves cannot carry: a bin holds at most `chunk` < 65536); with a
-    // placement, also count per pair the transitions of the bins whose two experts share a device
+    // flush: sum the replicas (packed halves cannot carry: a bin holds at most `chunk` < 65536); with a placement, also count per pair the
+    // transitions of the bins whose two experts share a device.  A power of two of lanes takes a row, each of them two of its bins (found
+    // for every word by itself, with divisions, the devices were 3.6 us of the 22.7 of this launch at 24 x 1M tokens: the call 28.0 us, now
+    // 26.0; fewer words than two a thread gain nothing, 23 x 7452 of 38 experts 10.6 us and 11.2).  An odd number of experts has words of two rows.
     const int my_pairs = l1 - l0;
-    for (int i = threadIdx.x; i < my_pairs * words; i += kTraceThreads) {
-        uint32_t s = 0;
-        for (int r = 0; r < copies; ++r) s += hist[r * g * words + i];
-        part_counts[(static_cast<size_t>(c) * pairs + l0) * words + i] = s;
-        if (placement != nullptr) {
-            const int pr = i / words, wd = i - pr * words;
-            const int32_t* here = device + pr * E;
-            const int32_t* there = here + E;
-            uint32_t stay = 0;
+    if (placement != nullptr && E % 2 == 0 && my_pairs * words > 11 * kTraceThreads / 4) {
+        const int row_words = E / 2, log_lanes = row_words > 1 ? 32 - __builtin_clz(row_words - 1) : 0;
+        const int w = static_cast<int>(threadIdx.x) & ((1 << log_lanes) - 1);
+        uint32_t stay[kAffMaxGroup] = {};
+        for (int row = static_cast<int>(threadIdx.x) >> log_lanes; row < my_pairs * E; row += kTraceThreads >> log_lanes) {
+            const int pr = row < E ? 0 : (row < 2 * E ? 1 : 2), i = row - pr * E;
+            static_assert(kAffMaxGroup == 3, "pairs of a group");
+            if (w >= row_words) continue;
+            const int at = pr * words + i * row_words + w;
+            uint32_t s = 0;
+            for (int r = 0; r < copies; ++r) s += hist[r * g * words + at];
+            part_counts[(static_cast<size_t>(c) * pairs + l0) * words + at] = s;
+            const int32_t here = device[row], even = device[(pr + 1) * E + 2 * w], odd = device[(pr + 1) * E + 2 * w + 1];
+            const uint32_t mine = (here == even ? s & 0xffffu : 0u) + (here == odd ? s >> 16 : 0u);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int bin = 2 * wd + h;
-                if (bin < E * E && here[bin / E] == there[bin % E]) stay += (s >> (16 * h)) & 0xffffu;
+            for (int k = 0; k < kAffMaxGroup; ++k) stay[k] += pr == k ? mine : 0u;
+        }
+#pragma unroll
+        for (int pr = 0; pr < kAffMaxGroup; ++pr) {
+            const uint32_t sum = wave_sum(stay[pr]);
+            if (lane_id() == 0 && sum != 0) atomicAdd(&stay_cnt[min(pr, g - 1)], sum);
+        }
+    } else {
+        for (int i = threadIdx.x; i < my_pairs * words; i += kTraceThreads) {
+            uint32_t s = 0;
+            for (int r = 0; r < copies; ++r) s += hist[r * g * words + i];
+            part_counts[(static_cast<size_t>(c) * pairs + l0) * words + i] = s;
+            if (placement != nullptr) {
+                const int pr = i / words, wd = i - pr * words;
+                const int32_t* here = device + pr * E;
+                const int32_t* there = here + E;
+                uint32_t stay = 0;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int bin = 2 * wd + h;
+                    if (bin < E * E && here[bin / E] == there[bin % E]) stay += (s >> (16 * h)) & 0xffffu;
+                }
+                if (stay != 0) atomicAdd(&stay_cnt[pr], stay);
             }
-            if (stay != 0) atomicAdd(&stay_cnt[pr], stay);
         }
     }
     if (placement != nullptr) {

@@ -137,6 +137,16 @@ __device__ __forceinline__ int row_of_chunk(int c, int vec_per_row, float rcp)
 
 __device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x) & (kWave - 1); }
 
+// A workgroup barrier behind which everybody's LDS accesses are done; loads from memory stay in flight across it.
+__device__ __forceinline__ void barrier_for_lds()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#endif
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v)
 {

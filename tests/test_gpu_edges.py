@@ -43,6 +43,19 @@ def test_short_traces(oracle, L, N, E, G):
     Q.test_routing_transfers_parity(L, N, E, G)
 
 
+# chunks of whole wavefronts past one sweep, the last one cut; rows of 23, 31 and 32 words and an odd number of experts (words of two rows),
+# groups of three pairs and of fewer
+@pytest.mark.parametrize("L,N,E,G", [(24, 135001, 64, 8), (4, 40000, 62, 2), (23, 200003, 46, 2), (5, 300002, 64, 4), (24, 140001, 63, 7), (24, 131072, 44, 4)])
+def test_locality_from_the_histograms_of_a_chunk(oracle, L, N, E, G):
+    _say(f"statistics L={L} N={N} E={E} G={G}")
+    trace, _ = syn.planted_trace(L, N, E, 0.5, seed=2150 + N)
+    g = syn.rng(2151 + L)
+    bad = g.random((L, N)) < 0.001
+    bad[L - 1, N - 1] = bad[0, 0] = True
+    trace[bad] = g.choice(np.array([-1, E, 1 << 20, -(1 << 31)]), size=int(bad.sum())).astype(np.int32)
+    P._affinity_case(oracle, trace, E, syn.balanced_random_placement(L, E, G, seed=2152), G)
+
+
 @pytest.mark.parametrize("N", [300, 262147, 414593])
 def test_placement_of_all_layers_beyond_64_KiB(oracle, N):
     """The most layers and experts.  Up to 412992 tokens (locality 414592) a workgroup takes a layer and two rows of the placement; beyond,
