@@ -80,17 +80,20 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
     if (chunk > kAffMaxChunk) chunk = kAffMaxChunk / unit * unit;
     p.chunk = chunk;
     p.C = static_cast<int>(N > 0 ? (N + chunk - 1) / chunk : 0);
+    // room for as many chunks as any shorter trace has: a workspace for the longest one does for all
+    const int64_t sweeps = N > 0 ? (N + sweep - 1) / sweep : 0;
+    const size_t room = p.C > c_target ? p.C : static_cast<size_t>(sweeps < c_target ? sweeps : c_target);
     size_t off = 0;
     p.off_counts = off;
-    off += align_up(static_cast<size_t>(p.C) * pairs * p.words * sizeof(uint32_t), 256);
+    off += align_up(room * pairs * p.words * sizeof(uint32_t), 256);
     p.off_orphan_next = off;
-    off += align_up(static_cast<size_t>(p.C) * (pairs > 0 ? pairs : 1) * E * sizeof(uint32_t), 256);
+    off += align_up(room * (pairs > 0 ? pairs : 1) * E * sizeof(uint32_t), 256);
     p.off_orphan_last = off;
-    off += align_up(static_cast<size_t>(p.C) * E * sizeof(uint32_t), 256);
+    off += align_up(room * E * sizeof(uint32_t), 256);
     p.off_invalid = off;
-    off += align_up(static_cast<size_t>(p.C) * p.Q * sizeof(uint32_t), 256);
+    off += align_up(room * p.Q * sizeof(uint32_t), 256);
     p.off_local = off;  // per chunk and pair: transitions that stay on their device (affinity_statistics)
-    off += align_up(static_cast<size_t>(p.C) * (pairs > 0 ? pairs : 1) * sizeof(uint32_t), 256);
+    off += align_up(room * (pairs > 0 ? pairs : 1) * sizeof(uint32_t), 256);
     p.total_bytes = off > 0 ? off : 256;
     return p;
 }

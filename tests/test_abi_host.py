@@ -209,6 +209,16 @@ def test_candidate_batch_bound_of_the_scoring_call():
     assert lib.placement_locality_from_counts(None, one, 1 << 24, 4, 8, one, None) == B.EXF_ERR_NULL_PTR
 
 
+@pytest.mark.parametrize("L,E", [(2, 8), (3, 24), (10, 40), (24, 64), (33, 63), (128, 64)])
+def test_statistics_workspace_of_a_longer_trace_does_for_a_shorter_one(L, E):
+    lib = exf.lib()
+    least = 0
+    for N in sorted({0, 1, 3, *range(1000, 1 << 21, 9973), *(c * 4096 + o for c in range(1, 300) for o in (-1, 0, 1)), 61440 * 300, 61440 * 300 + 1}):
+        nbytes = lib.affinity_statistics_workspace_bytes(L, N, E)
+        assert nbytes >= least and nbytes == lib.affinity_histogram_workspace_bytes(L, N, E), (N, nbytes, least)
+        least = nbytes
+
+
 def _layer_desc(T, fused, dt, k, changed):
     """A valid description at dummy addresses (never dereferenced on the host)."""
     lib = exf.lib()
