@@ -753,23 +753,44 @@ __global__ __launch_bounds__(kTraceThreads) void locality_partial_kernel(const i
     uint32_t* pair_cnt = reinterpret_cast<uint32_t*>(lds_i + L * E);  // [L-1] pairs, then (HOME) [L] away counts
     uint32_t* away_cnt = pair_cnt + (L - 1);
     const int n_out = (L - 1) + (HOME ? L : 0);
-    for (int i = threadIdx.x; i < L * E; i += blockDim.x) pl[i] = placement[i];
-    for (int i = threadIdx.x; i < n_out; i += blockDim.x) pair_cnt[i] = 0u;
-    __syncthreads();
-
-    const int lane = lane_id();
     const int64_t n_begin = static_cast<int64_t>(blockIdx.x) * chunk;
     const int64_t n_end = min(N, n_begin + chunk);
-    for (int64_t base = n_begin; base < n_end; base += static_cast<int64_t>(blockDim.x) * VEC) {
+    const int64_t sweep = static_cast<int64_t>(blockDim.x) * VEC;
+    const int lane = lane_id();
+    auto load_layers = [&](int lb, int64_t n0, TokVec<VEC>(&dst)[kLocAhead]) {
+#pragma unroll
+        for (int a = 0; a < kLocAhead; ++a)  // layers past the last one are clamped, not skipped: no branch at the loads
+            dst[a] = load_tokens<VEC>(trace + static_cast<int64_t>(min(lb + a, L - 1)) * N, n0, n_end);
+    };
+    TokVec<VEC> hm, first, cur[kLocAhead], nxt[kLocAhead];
+    auto begin_sweep = [&](int64_t n0) {
+        if constexpr (HOME) hm = load_tokens<VEC>(home, n0, n_end);
+        first = load_tokens<VEC>(trace, n0, n_end);
+        load_layers(1, n0, cur);
+    };
+    // the placement, and behind it the first tokens: they travel together (24 x 999983 tokens with home devices 25.05 us one after
+    // the other, 24.3 now; 6 x 2000001 15.2 and 14.7)
+    constexpr int kPlacementAhead = 2;
+    const int entries = L * E;
+    int32_t entry[kPlacementAhead];
+#pragma unroll
+    for (int k = 0; k < kPlacementAhead; ++k) entry[k] = placement[min(static_cast<int>(threadIdx.x + k * blockDim.x), entries - 1)];
+    begin_sweep(n_begin + static_cast<int64_t>(threadIdx.x) * VEC);
+    for (int i = threadIdx.x; i < n_out; i += blockDim.x) pair_cnt[i] = 0u;
+#pragma unroll
+    for (int k = 0; k < kPlacementAhead; ++k)
+        if (static_cast<int>(threadIdx.x + k * blockDim.x) < entries) pl[threadIdx.x + k * blockDim.x] = entry[k];
+    for (int i = threadIdx.x + kPlacementAhead * blockDim.x; i < entries; i += blockDim.x) pl[i] = placement[i];
+    barrier_for_lds();
+
+    for (int64_t base = n_begin; base < n_end; base += sweep) {
         const int64_t n0 = base + static_cast<int64_t>(threadIdx.x) * VEC;
         int dev_prev[VEC];
         bool ok_prev[VEC];
         const bool in_range = n0 + VEC <= n_end;  // all tokens of this lane exist
         bool prev_clean;                           // all ids of the previous layer valid (and in range)
-        TokVec<VEC> hm;
-        if constexpr (HOME) hm = load_tokens<VEC>(home, n0, n_end);
         {
-            TokVec<VEC> t = load_tokens<VEC>(trace, n0, n_end);
+            TokVec<VEC> t = first;
             if (__ballot(!in_range) != 0ull) {
                 cut_vector(t, n0, n_end);
                 if constexpr (HOME) cut_vector(hm, n0, n_end);
@@ -786,17 +807,10 @@ __global__ __launch_bounds__(kTraceThreads) void locality_partial_kernel(const i
             if constexpr (HOME)
                 if (lane == 0 && away != 0) atomicAdd(&away_cnt[0], static_cast<uint32_t>(away));
         }
-        auto load_layers = [&](int lb, TokVec<VEC>(&dst)[kLocAhead]) {
-#pragma unroll
-            for (int a = 0; a < kLocAhead; ++a)  // layers past the last one are clamped, not skipped: no branch at the loads
-                dst[a] = load_tokens<VEC>(trace + static_cast<int64_t>(min(lb + a, L - 1)) * N, n0, n_end);
-        };
         // software pipeline over batches of kLocAhead layers: the next batch is requested before the
         // current one is counted
-        TokVec<VEC> cur[kLocAhead], nxt[kLocAhead];
-        load_layers(1, cur);
         for (int lb = 1; lb < L; lb += kLocAhead) {
-            load_layers(lb + kLocAhead, nxt);
+            load_layers(lb + kLocAhead, n0, nxt);
 #pragma unroll
             for (int a = 0; a < kLocAhead; ++a) {
                 const int l = lb + a;
@@ -841,6 +855,7 @@ __global__ __launch_bounds__(kTraceThreads) void locality_partial_kernel(const i
 #pragma unroll
             for (int a = 0; a < kLocAhead; ++a) cur[a] = nxt[a];
         }
+        if (base + sweep < n_end) begin_sweep(n0 + sweep);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < n_out; i += blockDim.x) part[static_cast<size_t>(blockIdx.x) * n_out + i] = pair_cnt[i];
