@@ -184,9 +184,8 @@ def moe_dispatch(x, topk_idx, E, E_local=None, expert_map=None, out=None, worksp
             torch.empty(E_local, dtype=torch.int32, device=dev),
             torch.empty(E_local + 1, dtype=torch.int32, device=dev),
         )
-    nbytes = lib().moe_dispatch_workspace_bytes(T, k, E_local)
     if workspace is None:
-        workspace = _workspace(nbytes, dev)
+        workspace = _workspace(lib().moe_dispatch_workspace_bytes(T, k, E_local), dev)
     _check(lib().moe_dispatch(_ptr(x), _ptr(topk_idx), _ptr(expert_map), T, d, k, E, E_local, dtype_code(x),
                               _ptr(out.x_sorted), _ptr(out.src_of_sorted), _ptr(out.sorted_of_src),
                               _ptr(out.expert_counts), _ptr(out.expert_offsets), _ptr(workspace), workspace.numel(), _stream()))
@@ -215,9 +214,8 @@ def moe_expert_ffn(x_sorted, expert_offsets, w1, w2, b1=None, b2=None, act=EXF_A
     dt = dtype_code(x_sorted)
     if out is None:
         out = torch.empty((A, d), dtype=x_sorted.dtype, device=x_sorted.device)
-    nbytes = lib().moe_expert_ffn_workspace_bytes(A, d, f, E_local, dt)
     if workspace is None:
-        workspace = _workspace(nbytes, x_sorted.device)
+        workspace = _workspace(lib().moe_expert_ffn_workspace_bytes(A, d, f, E_local, dt), x_sorted.device)
     _check(lib().moe_expert_ffn(_ptr(x_sorted), _ptr(expert_offsets), _ptr(w1), _ptr(b1), _ptr(w2), _ptr(b2), A, d, f,
                                 E_local, act, dt, _ptr(out), _ptr(workspace), workspace.numel(), _stream()))
     return out
@@ -237,9 +235,8 @@ def moe_expert_ffn_fused(x, src_of_sorted, sorted_of_src, topk_w, expert_offsets
     dt = dtype_code(x)
     if out is None:
         out = torch.empty((T, d), dtype=x.dtype, device=x.device)
-    nbytes = lib().moe_expert_ffn_fused_workspace_bytes(T, k, d, f, E_local, dt)
     if workspace is None:
-        workspace = _workspace(nbytes, x.device)
+        workspace = _workspace(lib().moe_expert_ffn_fused_workspace_bytes(T, k, d, f, E_local, dt), x.device)
     _check(lib().moe_expert_ffn_fused(_ptr(x), _ptr(src_of_sorted), _ptr(sorted_of_src), _ptr(topk_w), _ptr(expert_offsets),
                                       _ptr(w1), _ptr(b1), _ptr(w2), _ptr(b2), T, k, d, f, E_local, act, dt, _ptr(out),
                                       _ptr(workspace), workspace.numel(), _stream()))
@@ -269,9 +266,8 @@ def affinity_histogram(trace, E, want_loads=True, want_prob=True, want_invalid=T
             cond_prob=torch.empty((max(L - 1, 0), E, E), dtype=torch.float32, device=dev) if want_prob else None,
             n_invalid=torch.empty(1, dtype=torch.int64, device=dev) if want_invalid else None,
         )
-    nbytes = lib().affinity_histogram_workspace_bytes(L, N, E)
     if workspace is None:
-        workspace = _workspace(nbytes, dev)
+        workspace = _workspace(lib().affinity_histogram_workspace_bytes(L, N, E), dev)
     _check(lib().affinity_histogram(_ptr(trace), L, N, E, _ptr(out["counts"]), _ptr(out["loads"]), _ptr(out["cond_prob"]),
                                     _ptr(out["n_invalid"]), _ptr(workspace), workspace.numel(), _stream()))
     return out
@@ -292,9 +288,8 @@ def affinity_statistics(trace, placement, G, want_loads=True, want_prob=True, wa
             n_invalid=torch.empty(1, dtype=torch.int64, device=dev) if want_invalid else None,
             local_per_pair=torch.empty(max(L - 1, 0), dtype=torch.int64, device=dev),
         )
-    nbytes = lib().affinity_statistics_workspace_bytes(L, N, E)
     if workspace is None:
-        workspace = _workspace(nbytes, dev)
+        workspace = _workspace(lib().affinity_statistics_workspace_bytes(L, N, E), dev)
     _check(lib().affinity_statistics(_ptr(trace), _ptr(placement), L, N, E, G, _ptr(out["counts"]), _ptr(out["loads"]),
                                      _ptr(out["cond_prob"]), _ptr(out["n_invalid"]), _ptr(out["local_per_pair"]), _ptr(workspace),
                                      workspace.numel(), _stream()))
@@ -309,9 +304,8 @@ def placement_locality(trace, placement, G, workspace=None, out=None):
     assert trace.is_contiguous() and placement.is_contiguous()
     if out is None:
         out = torch.empty(max(L - 1, 0), dtype=torch.int64, device=trace.device)
-    nbytes = lib().placement_locality_workspace_bytes(L, N)
     if workspace is None:
-        workspace = _workspace(nbytes, trace.device)
+        workspace = _workspace(lib().placement_locality_workspace_bytes(L, N), trace.device)
     _check(lib().placement_locality(_ptr(trace), _ptr(placement), L, N, E, G, _ptr(out), _ptr(workspace), workspace.numel(),
                                     _stream()))
     return out
@@ -324,9 +318,8 @@ def affinity_multihop(trace, E, want_prob=True, workspace=None):
     P = L * (L - 1) // 2
     counts = torch.empty((P, E, E), dtype=torch.int64, device=trace.device)
     prob = torch.empty((P, E, E), dtype=torch.float32, device=trace.device) if want_prob else None
-    nbytes = lib().affinity_multihop_workspace_bytes(L, N, E)
     if workspace is None:
-        workspace = _workspace(nbytes, trace.device)
+        workspace = _workspace(lib().affinity_multihop_workspace_bytes(L, N, E), trace.device)
     _check(lib().affinity_multihop(_ptr(trace), L, N, E, _ptr(counts), _ptr(prob), _ptr(workspace), workspace.numel(), _stream()))
     return {"counts": counts, "cond_prob": prob}
 
@@ -334,17 +327,19 @@ def affinity_multihop(trace, E, want_prob=True, workspace=None):
 def routing_transfers(trace, placement, home, G, workspace=None):
     """-> (local_per_pair int64 [L-1], away_per_layer int64 [L]) on the device."""
     L, N = trace.shape
-    E = placement.shape[1]
-    assert placement.shape[0] == L and home.shape == (N,)
+    rows, E = placement.shape
+    assert rows == L and home.shape == (N,)
     assert trace.dtype == placement.dtype == home.dtype == torch.int32
     assert trace.is_contiguous() and placement.is_contiguous() and home.is_contiguous()
-    local = torch.empty(max(L - 1, 0), dtype=torch.int64, device=trace.device)
-    away = torch.empty(L, dtype=torch.int64, device=trace.device)
-    nbytes = lib().routing_transfers_workspace_bytes(L, N)
+    dev = trace.device
+    local = torch.empty(max(L - 1, 0), dtype=torch.int64, device=dev)
+    away = torch.empty(L, dtype=torch.int64, device=dev)
     if workspace is None:
-        workspace = _workspace(nbytes, trace.device)
-    _check(lib().routing_transfers(_ptr(trace), _ptr(placement), _ptr(home), L, N, E, G, _ptr(local), _ptr(away), _ptr(workspace),
-                                   workspace.numel(), _stream()))
+        workspace = _workspace(lib().routing_transfers_workspace_bytes(L, N), dev)
+    rc = lib().routing_transfers(trace.data_ptr(), placement.data_ptr(), home.data_ptr(), L, N, E, G, local.data_ptr(), away.data_ptr(),
+                                 workspace.data_ptr(), workspace.numel(), _stream())
+    if rc:
+        _check(rc)
     return local, away
 
 
