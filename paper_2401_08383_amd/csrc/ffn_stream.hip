@@ -155,19 +155,19 @@ __device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, const
 // instructions and memory round trips (a wavefront issues one instruction in about five cycles), so what a launch of at most
 // eight rows does not need is compiled out (EIGHT).  One token, 8 experts of 1024 x 4096: 15.2 us in three launches, 12.2 in
 // two; one GPU's 2 of 8 experts with the routing given 15.6 and 12.1; 16 tokens, 8 experts 32.1 and 29.7.
-template <int W, int LDS, bool EIGHT>
+template <int W, int LDS, bool EIGHT, bool SECOND>
 __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned char* smem, int* sorted, int tile_rows)
 {
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int A = p.max_rows;
     const int at = min(lane, A - 1);
-    const bool gated = p.w_gate != nullptr && (blockIdx.x == 0 || p.topk_idx == p.gate_idx);  // (the same in all wavefronts)
+    const bool gated = !SECOND && p.w_gate != nullptr && (blockIdx.x == 0 || p.topk_idx == p.gate_idx);  // (the same in all wavefronts)
     const int local_of = p.expert_map != nullptr ? p.expert_map[min(lane, p.E - 1)] : lane;  // lane = expert
     int id = 0;
-    if (p.w_gate == nullptr || p.topk_idx != p.gate_idx) id = p.topk_idx[at];
+    if (SECOND || p.w_gate == nullptr || p.topk_idx != p.gate_idx) id = p.topk_idx[at];
     float scale = 1.0f;
-    if (p.second && p.out_row != nullptr) scale = p.out_scale[at];  // (k = 1: the assignment is the token)
+    if (SECOND && p.out_row != nullptr) scale = p.out_scale[at];  // (k = 1: the assignment is the token)
     if (gated) {
         const int T = A / p.k;
         Route r;
@@ -217,9 +217,9 @@ __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned c
     }
     if (e >= 0) {
         sorted[pos] = p.k == 2 ? lane >> 1 : lane;
-        reinterpret_cast<float*>(sorted)[kWave + pos] = scale;
+        if (SECOND) reinterpret_cast<float*>(sorted)[kWave + pos] = scale;
     }
-    if (!p.second && blockIdx.x == 0 && wave == 0) {
+    if (!SECOND && blockIdx.x == 0 && wave == 0) {
         if (lane < p.E_local) {
             p.expert_counts[lane] = count;
             p.expert_offsets[lane] = below;
@@ -228,7 +228,7 @@ __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned c
         if (lane < A) p.sorted_of_src[lane] = e >= 0 ? pos : -1;
         if (e >= 0) p.src_of_sorted[pos] = lane;
     }
-    if (p.unrouted != nullptr) {  // output rows nobody writes, dealt to the workgroups
+    if (SECOND && p.unrouted != nullptr) {  // output rows nobody writes, dealt to the workgroups
         unsigned long long todo = __ballot(lane < A && e < 0);
         for (int n = 0; todo != 0ull; ++n, todo &= todo - 1ull) {
             if (n != static_cast<int>(blockIdx.x)) continue;
@@ -300,12 +300,17 @@ __device__ __forceinline__ void wait_units(int units)
     }
 }
 
+// Where the rows of a contraction come from: sorted (maps in memory), sorted by the workgroup, sorted by every wavefront.
+enum StreamRows { kRowsSorted, kRowsInline, kRowsFew, kRowsEight };  // (the last: as kRowsFew, at most eight)
+
 // Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
 // KEEP_OUT: p.sorted_out is given.
-template <int C8, int AR, int W, bool KEEP_OUT, bool FEW_ROWS = false>
+template <int C8, int AR, int W, bool KEEP_OUT, StreamRows ROWS, bool SECOND>
 __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int row_begin, int row_end, int block_begin, int block_end,
-                                               int rotate, const int* list, bool tokens, bool listed_out, unsigned char* smem)
+                                               int rotate, const int* list, unsigned char* smem)
 {
+    constexpr bool FEW_ROWS = ROWS == kRowsEight, FEW = FEW_ROWS || ROWS == kRowsFew;  // FEW: `list` holds tokens, not assignments
+    const bool listed_out = FEW && SECOND && p.out_row != nullptr;
     constexpr int C = (C8 + 1) / 2, M = (AR + 1) / 2;  // MFMA tiles along the columns and the rows (eight of either are read twice)
     constexpr int R = stream_ring(C8, AR, W);
     constexpr int SLOT = stream_slot_bytes(C8, AR);
@@ -357,16 +362,16 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     };
 
     // ---- start: row ids, the weights of the first units, then (ids known) their activations -------------------
-    const int32_t* id_list = list != nullptr || listed_out ? nullptr : (p.a_row != nullptr ? p.a_row : p.out_row);
+    const int32_t* id_list = FEW || ROWS == kRowsInline ? nullptr : (p.a_row != nullptr ? p.a_row : p.out_row);
     const bool known = id_list == nullptr;  // no row ids to wait for: units are asked for whole, as later on
     auto place_rows = [&]() {
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int r = i * 8 + r8;
             int row = min(row_begin + r, row_end - 1);  // rows past the end repeat the last one
-            if (list != nullptr) row = list[row];
-            else if (p.a_row != nullptr) row = ids[r];
-            if (!tokens && p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
+            if (ROWS == kRowsInline || (FEW && !SECOND)) row = list[row];
+            else if (ROWS == kRowsSorted && p.a_row != nullptr) row = ids[r];
+            if (!FEW && p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
             off_a[i] = static_cast<uint32_t>(row) * row_bytes + ((c8 ^ ((r >> 1) & 7)) * 16);
         }
     };
@@ -397,7 +402,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
         wait_units<LW, R + 1>(first);
     }
     if (!known) place_rows();
-    if (p.out_row != nullptr && !listed_out) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
+    if (!FEW && p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
     if (!known) {
 #pragma unroll
         for (int s = 0; s < R; ++s)
@@ -537,30 +542,26 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     }
 }
 
-// Where the rows of a contraction come from: sorted (maps in memory), sorted by the workgroup, sorted by every wavefront.
-enum StreamRows { kRowsSorted, kRowsInline, kRowsFew, kRowsEight };  // (the last: as kRowsFew, at most eight)
-
 // The sorted rows that are wanted besides the result: none, p.sorted_act (a contraction that sorts), p.sorted_out (one that scales).  Instances
 // of their own: what a handful of rows does not need costs them 0.6 us of 12.
 enum StreamKeep { kKeepNone, kKeepAct, kKeepOut };
 
-template <int C8, int W, StreamRows ROWS, StreamKeep KEEP>
+// SECOND: a second contraction of a handful of rows (p.second; otherwise the arguments say).
+template <int C8, int W, StreamRows ROWS, StreamKeep KEEP, bool SECOND>
 __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     touch_arguments<sizeof(StreamGemm)>();
     constexpr int MAX_AR = stream_max_ar(C8), TILE_ROWS = 8 * MAX_AR, COLS = 8 * C8;
-    constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;  // `list` holds tokens, not assignments
+    constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;
     constexpr bool KEEP_OUT = KEEP == kKeepOut;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int* list = nullptr;
-    bool listed_out = false;
     ExpertTiles et;
     if constexpr (FEW) {
         int* sorted = reinterpret_cast<int*>(smem + stream_ring_bytes(C8, W) + wave * kStreamIdBytes);
-        et = route_few<W, stream_ring_bytes(C8, W), ROWS == kRowsEight>(p, smem, sorted, TILE_ROWS);
-        if (p.second) listed_out = p.out_row != nullptr;
-        else list = sorted;
+        et = route_few<W, stream_ring_bytes(C8, W), ROWS == kRowsEight, SECOND>(p, smem, sorted, TILE_ROWS);
+        list = sorted;
     } else {
         const int32_t* offsets = p.offsets;
         if constexpr (ROWS == kRowsInline) {
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             const int row_begin = wave_read_lane(et.lo, e), row_end = wave_read_lane(et.hi, e);
             const int b0 = static_cast<int>(at - t * n_blocks);
             at = min(end, (t + 1) * n_blocks);
-            stream_segment<C8, 1, W, KEEP_OUT, true>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, FEW, listed_out, smem);
+            stream_segment<C8, 1, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, smem);
             continue;
         }
         const int e = __builtin_ctzll(__ballot(at < cost_incl * n_blocks));
@@ -638,20 +639,20 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         at = __builtin_amdgcn_readfirstlane(tile_begin + c * n_blocks);
         if (b0 >= b1) continue;
         const int rows = row_end - row_begin;
-        if (rows <= 8) stream_segment<C8, 1, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
-        else if (rows <= 16) stream_segment<C8, 2, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
-        else if (rows <= 32) stream_segment<C8, 4, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
-        else stream_segment<C8, MAX_AR, W, KEEP_OUT>(p, e, row_begin, row_end, b0, b1, lin, list, FEW, listed_out, smem);
+        if (rows <= 8) stream_segment<C8, 1, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else if (rows <= 16) stream_segment<C8, 2, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else if (rows <= 32) stream_segment<C8, 4, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else stream_segment<C8, MAX_AR, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
     }
     if constexpr (KEEP == kKeepAct) copy_sorted_rows<W * kWave, bf16_t>(p, list, wave_read_lane(et.hi, p.E_local - 1), FEW ? 1 : p.a_div);
 }
 
-template <int C8, int W, StreamRows ROWS, StreamKeep KEEP>
+template <int C8, int W, StreamRows ROWS, StreamKeep KEEP, bool SECOND>
 static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
 {
     constexpr size_t lds = static_cast<size_t>(stream_ring_bytes(C8, W)) + W * kStreamIdBytes + (ROWS == kRowsInline ? sizeof(InlineDispatch) : (ROWS == kRowsEight ? W * stream_sums_bytes(C8) : 0));
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    auto kern = stream_gemm_kernel<C8, W, ROWS, KEEP>;
+    auto kern = stream_gemm_kernel<C8, W, ROWS, KEEP, SECOND>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(W * kWave), lds, stream, p);
@@ -661,16 +662,20 @@ static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
 template <int C8, int W, StreamRows ROWS, bool KEPT>
 static int launch_stream_rows(const StreamGemm& p, hipStream_t stream)
 {
+    constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;
     if constexpr (KEPT) {
         if constexpr (ROWS != kRowsSorted) {  // (rows that are there in sorted order are not wanted again)
-            if (p.sorted_act != nullptr) return launch_stream_as<C8, W, ROWS, kKeepAct>(p, stream);
+            if (p.sorted_act != nullptr && !p.second) return launch_stream_as<C8, W, ROWS, kKeepAct, false>(p, stream);
         }
         if constexpr (ROWS != kRowsInline) {  // (a first contraction)
-            if (p.sorted_act == nullptr) return launch_stream_as<C8, W, ROWS, kKeepOut>(p, stream);
+            if (p.sorted_act == nullptr && p.second == FEW) return launch_stream_as<C8, W, ROWS, kKeepOut, FEW>(p, stream);
         }
         return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: sorted rows of a contraction that has none");
+    } else if constexpr (FEW) {
+        if (p.second) return launch_stream_as<C8, W, ROWS, kKeepNone, true>(p, stream);
+        return launch_stream_as<C8, W, ROWS, kKeepNone, false>(p, stream);
     } else {
-        return launch_stream_as<C8, W, ROWS, kKeepNone>(p, stream);
+        return launch_stream_as<C8, W, ROWS, kKeepNone, false>(p, stream);
     }
 }
 template <int C8, int W, bool KEPT>
