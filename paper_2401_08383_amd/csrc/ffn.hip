@@ -1078,7 +1078,6 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
             if (k == 1) second.sorted_out = routing->y_sorted;
             if (dt == EXF_BF16 && A <= kFewAssignments) {
                 second.topk_idx = routing->topk_idx, second.expert_map = routing->expert_map, second.E = routing->E;
-                second.second = true;
             }
         }
         first.K = d, first.N = f, first.epi = epi;

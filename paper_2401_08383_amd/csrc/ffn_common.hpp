@@ -96,10 +96,9 @@ struct StreamGemm {
     const int32_t* expert_map;  // [E] or null
     int E;
     int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
-    // At most kFewAssignments: both contractions sort, every wavefront for itself, `second` the one that
-    // reads rows in sorted order.  With `w_gate` the first one is the gate of act [T,K] as well (workgroup 0 stores gate_idx and gate_w,
-    // and the others compute it, too, where topk_idx is gate_idx).
-    bool second;
+    // At most kFewAssignments: both contractions sort, every wavefront for itself; the second one reads rows in sorted order.  With
+    // `w_gate` the first one is the gate of act [T,K] as well (workgroup 0 stores gate_idx and gate_w, and the others compute it, too,
+    // where topk_idx is gate_idx).
     int k;
     const void* w_gate;
     int renormalize;

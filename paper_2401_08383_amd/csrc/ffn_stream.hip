@@ -362,7 +362,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     };
 
     // ---- start: row ids, the weights of the first units, then (ids known) their activations -------------------
-    const int32_t* id_list = FEW || ROWS == kRowsInline ? nullptr : (p.a_row != nullptr ? p.a_row : p.out_row);
+    const int32_t* id_list = FEW || ROWS == kRowsInline ? nullptr : (SECOND ? p.out_row : p.a_row);
     const bool known = id_list == nullptr;  // no row ids to wait for: units are asked for whole, as later on
     auto place_rows = [&]() {
 #pragma unroll
@@ -370,8 +370,8 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
             const int r = i * 8 + r8;
             int row = min(row_begin + r, row_end - 1);  // rows past the end repeat the last one
             if (ROWS == kRowsInline || (FEW && !SECOND)) row = list[row];
-            else if (ROWS == kRowsSorted && p.a_row != nullptr) row = ids[r];
-            if (!FEW && p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
+            else if (ROWS == kRowsSorted && !SECOND && p.a_row != nullptr) row = ids[r];
+            if (!FEW && !SECOND && p.a_div > 1) row = static_cast<int>(static_cast<unsigned>(row) / static_cast<unsigned>(p.a_div));
             off_a[i] = static_cast<uint32_t>(row) * row_bytes + ((c8 ^ ((r >> 1) & 7)) * 16);
         }
     };
@@ -402,7 +402,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
         wait_units<LW, R + 1>(first);
     }
     if (!known) place_rows();
-    if (!FEW && p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
+    if (!FEW && SECOND && p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
     if (!known) {
 #pragma unroll
         for (int s = 0; s < R; ++s)
@@ -506,7 +506,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
                                                        at);
             int dst = row_begin + r;
             float scale = 1.0f;
-            if (p.out_row != nullptr) {
+            if (SECOND && p.out_row != nullptr) {
                 dst = ids[r];
                 scale = gate[r];
             }
@@ -521,9 +521,8 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (p.epi == kEpiGeluErf) v[k] = gelu_erf_fast(v[k]);
-                else if (p.epi == kEpiGeluTanh) v[k] = gelu_tanh_fast(v[k]);
-                if constexpr (!KEEP_OUT) v[k] *= scale;
+                if constexpr (!SECOND) v[k] = p.epi == kEpiGeluErf ? gelu_erf_fast(v[k]) : gelu_tanh_fast(v[k]);
+                else if constexpr (!KEEP_OUT) v[k] *= scale;
             }
             if constexpr (KEEP_OUT) {
                 const uint2 y = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
@@ -546,7 +545,7 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
 // of their own: what a handful of rows does not need costs them 0.6 us of 12.
 enum StreamKeep { kKeepNone, kKeepAct, kKeepOut };
 
-// SECOND: a second contraction of a handful of rows (p.second; otherwise the arguments say).
+// SECOND: a second contraction, which has no activation but may scale and scatter its rows.
 template <int C8, int W, StreamRows ROWS, StreamKeep KEEP, bool SECOND>
 __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
 {
@@ -570,7 +569,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             list = d->list;
             offsets = d->offs;
         }
-        if (p.unrouted != nullptr) clear_unrouted_rows<false>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
+        if (SECOND && p.unrouted != nullptr) clear_unrouted_rows<false>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
         et = scan_row_tiles(p, offsets, TILE_ROWS);
     }
     const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
@@ -662,19 +661,19 @@ static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
 template <int C8, int W, StreamRows ROWS, bool KEPT>
 static int launch_stream_rows(const StreamGemm& p, hipStream_t stream)
 {
-    constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;
+    const bool second = p.epi == kEpiNone;
     if constexpr (KEPT) {
         if constexpr (ROWS != kRowsSorted) {  // (rows that are there in sorted order are not wanted again)
-            if (p.sorted_act != nullptr && !p.second) return launch_stream_as<C8, W, ROWS, kKeepAct, false>(p, stream);
+            if (!second && p.sorted_act != nullptr) return launch_stream_as<C8, W, ROWS, kKeepAct, false>(p, stream);
         }
-        if constexpr (ROWS != kRowsInline) {  // (a first contraction)
-            if (p.sorted_act == nullptr && p.second == FEW) return launch_stream_as<C8, W, ROWS, kKeepOut, FEW>(p, stream);
+        if constexpr (ROWS != kRowsInline) {
+            if (second && p.sorted_out != nullptr) return launch_stream_as<C8, W, ROWS, kKeepOut, true>(p, stream);
         }
         return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: sorted rows of a contraction that has none");
-    } else if constexpr (FEW) {
-        if (p.second) return launch_stream_as<C8, W, ROWS, kKeepNone, true>(p, stream);
-        return launch_stream_as<C8, W, ROWS, kKeepNone, false>(p, stream);
     } else {
+        if constexpr (ROWS != kRowsInline) {  // (a first contraction)
+            if (second) return launch_stream_as<C8, W, ROWS, kKeepNone, true>(p, stream);
+        }
         return launch_stream_as<C8, W, ROWS, kKeepNone, false>(p, stream);
     }
 }
