@@ -154,7 +154,7 @@ int moe_dispatch_static(const void* x, const int32_t* topk_idx, const int32_t* e
  * Shapes: d, f multiples of 64 (bf16) / 4 (fp32); 1 <= E_local <= EXF_MAX_EXPERTS.
  * workspace: moe_expert_ffn_workspace_bytes(A, d, f, E_local, dt) bytes (the hidden activations of
  * A rows of f values; bf16: in a layout of the library's own in which every expert starts on a 32-row
- * boundary - A + 32 E_local rows -, plus 16 MiB in reserve that no kernel uses at present).
+ * boundary - A + 32 E_local rows -, plus 16 MiB in reserve, which moe_layer_forward writes to).
  * ------------------------------------------------------------------------------------- */
 size_t moe_expert_ffn_workspace_bytes(int64_t A, int d, int f, int E_local, int dt);
 int moe_expert_ffn(const void* x_sorted, const int32_t* expert_offsets, const void* w1, const void* b1,

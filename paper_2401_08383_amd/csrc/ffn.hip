@@ -784,7 +784,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     timeline_stamp(map, 0);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap)
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + 4] = 0ull;  // stays zero if this workgroup has no tile
-    if (map.unrouted != nullptr) clear_unrouted_rows<false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
+    if (map.unrouted != nullptr) clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
     Tile2D tile;
     if (!locate_tile(offsets, E_local, NT, N, max_rows, static_cast<int>(blockIdx.x), map, tile)) return;
     timeline_stamp(map, 1);
@@ -890,7 +890,7 @@ static int launch_second_contraction(const void* act, const int32_t* offsets, co
 
 namespace exf {
 // The workspace the entry points ask for, bf16: hidden activations of A rows, of up to 32 more per expert (see
-// hidden_offset), and 16 MiB in reserve (the sizes are part of the interface).
+// hidden_offset), and 16 MiB in reserve (the sizes are part of the interface; a top-2 layer of separate calls uses them, see pairs_meet).
 constexpr int kReservedRowsPerExpert = kHiddenRowBlock;
 constexpr size_t kReservedBytes = 16u << 20;
 static size_t hidden_bytes(int64_t A, int f, int E_local, int dt)
@@ -1030,6 +1030,18 @@ int exf::check_ffn_fused(const void* x, const int32_t* src_of_sorted, const int3
     return EXF_OK;
 }
 
+// Do the two rows of a token of a top-2 layer meet in the second contraction (meet() in ffn_stream.hip) instead of in a combine?  Where the first
+// one sorts, so that the maps are this call's and the words have been cleared; of the separate calls, whose workspace has no room of its own for
+// these, those in bf16 that get by with the reserve.  Past a gigabyte of weights of the second contraction the launch saved is
+// less than a hundredth, and the wait for the exchange at the end of every block has cost more (8 tokens, 16 experts of 4096 x 16384 426 and 433 us).
+constexpr int64_t kMeetingWeights = 1ll << 29;
+static bool pairs_meet(int64_t T, int k, int d, int f, int E_local, int dt, bool fused)
+{
+    const int64_t A = T * k;
+    return k == 2 && exf::routed_path_fits(A, d, f, E_local, dt) && (A < E_local ? A : E_local) * d * f <= kMeetingWeights &&
+           (fused || (dt == EXF_BF16 && static_cast<size_t>(T) * d * 2 <= exf::kReservedBytes));
+}
+
 static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int32_t* sorted_of_src, const float* topk_w,
                          const int32_t* expert_offsets, const void* w1, const void* b1, const void* w2, const void* b2, int64_t T, int k,
                          int d, int f, int E_local, int act, int dt, void* out, void* workspace, size_t workspace_bytes, void* stream,
@@ -1054,14 +1066,15 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
     RowMap scatter{};
     scatter.timeline = timeline != nullptr ? timeline + static_cast<size_t>(timeline_cap) * 8 : nullptr;
     scatter.timeline_cap = timeline_cap;
-    if (k == 1) {
-        scatter.out_row = src_of_sorted;  // k = 1: the flat assignment index is the token
+    const bool pairs = routing != nullptr && timeline == nullptr && pairs_meet(T, k, d, f, E_local, dt, routing->y_sorted == nullptr);
+    if (k == 1 || pairs) {
+        scatter.out_row = src_of_sorted;  // (k = 1: the flat assignment index is the token)
         scatter.out_scale = topk_w;
         scatter.unrouted = sorted_of_src;
         scatter.n_unrouted = static_cast<int>(T);
     }
     void* y_sorted = routing != nullptr && routing->y_sorted != nullptr ? routing->y_sorted : hidden + hidden_bytes(A, f, E_local, dt);
-    void* second_out = k == 1 ? out : y_sorted;
+    void* second_out = k == 1 || pairs ? out : y_sorted;
     int rc;
     if (timeline == nullptr && stream_path_fits(A, d, f, E_local, dt)) {
         StreamGemm first{}, second{};
@@ -1075,7 +1088,8 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
             first.k = second.k = k;
             first.gate_idx = routing->gate_idx, first.gate_w = routing->gate_w;
             first.sorted_act = routing->x_sorted;
-            if (k == 1) second.sorted_out = routing->y_sorted;
+            if (k == 1 || pairs) second.sorted_out = routing->y_sorted;
+            if (pairs) first.exchange = second.exchange = reinterpret_cast<unsigned long long*>(hidden + hidden_bytes(A, f, E_local, dt));
             if (dt == EXF_BF16 && A <= kFewAssignments) {
                 second.topk_idx = routing->topk_idx, second.expert_map = routing->expert_map, second.E = routing->E;
             }
@@ -1094,7 +1108,7 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
         if (rc == EXF_OK) rc = launch_second_contraction(hidden, expert_offsets, w2, b2, A, f, d, E_local, second_out, s, scatter);
     }
     if (rc != EXF_OK) return rc;
-    if (k == 1) return check_launch("moe_expert_ffn_fused");
+    if (k == 1 || pairs) return check_launch("moe_expert_ffn_fused");
     rc = check_launch("moe_expert_ffn_fused");
     if (rc != EXF_OK) return rc;
     return moe_combine(y_sorted, sorted_of_src, topk_w, T, d, k, dt, out, stream);

@@ -50,7 +50,7 @@ __device__ __forceinline__ float gelu_tanh_fast(float z)
 // expert of 1600 x 6400, 49.1 us, now 41.9; 1759 of which a fifth, 1216 x 4864, 42.7 and 36.6.)  ALL_AT_ONCE: 64 to each of the first ones all
 // the same, for launches of a few microseconds that wait for every instruction in front of their loads (fp32, 394 tokens, 4 experts of
 // 76 x 492 15.0 us dealt out and 14.7).
-template <bool ALL_AT_ONCE>
+template <bool ALL_AT_ONCE, bool PAIRS>
 __device__ __forceinline__ void clear_unrouted_rows(const int32_t* __restrict__ unrouted, int n_unrouted, uint4* __restrict__ out, int vec_per_row, int waves)
 {
     const int lane = lane_id();
@@ -60,7 +60,8 @@ __device__ __forceinline__ void clear_unrouted_rows(const int32_t* __restrict__ 
     while (mine < static_cast<uint32_t>(kWave) && static_cast<uint64_t>(mine) * all < static_cast<uint64_t>(n_unrouted)) mine *= 2;  // (a division takes a quarter of a microsecond)
     for (int64_t first = static_cast<int64_t>(blockIdx.x * static_cast<uint32_t>(waves) + wave) * mine; first < n_unrouted; first += static_cast<int64_t>(all) * mine) {
         const int64_t t = first + lane;
-        const int pos = lane < static_cast<int>(mine) && t < n_unrouted ? unrouted[t] : 0;
+        int pos = 0;
+        if (lane < static_cast<int>(mine) && t < n_unrouted) pos = PAIRS ? max(unrouted[2 * t], unrouted[2 * t + 1]) : unrouted[t];
         unsigned long long todo = __ballot(pos < 0);
         while (todo != 0) {
             const int b = __builtin_ctzll(todo);
@@ -90,25 +91,27 @@ struct StreamGemm {
     int max_rows;             // row capacity A
     int K, N, E_local;
     int epi;                  // Epilogue
+    int E, k, renormalize;    // of the routing below (up here no padding is sent along: another line of arguments is 0.2 us of a launch)
     // Routing instead of sorted rows (first contraction of a short batch; null: `offsets` and `a_row` above): every
     // workgroup sorts the assignments for itself, workgroup 0 writes the maps.
     const int32_t* topk_idx;    // [max_rows]
     const int32_t* expert_map;  // [E] or null
-    int E;
     int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
     // At most kFewAssignments: both contractions sort, every wavefront for itself; the second one reads rows in sorted order.  With
     // `w_gate` the first one is the gate of act [T,K] as well (workgroup 0 stores gate_idx and gate_w, and the others compute it, too,
     // where topk_idx is gate_idx).
-    int k;
     const void* w_gate;
-    int renormalize;
     int32_t* gate_idx;
     float* gate_w;
     // The sorted rows besides the result (null: not wanted).  With topk_idx: [*,K], the operand rows in sorted order.
     void* sorted_act;
     // With out_row: [*,N], sorted row s before it is scaled, in the storage type; the scaled one is formed from that, as the combine would.
     void* sorted_out;
+    // A top-2 layer whose token rows are added up by the second contraction: [T,N] of the storage type in words of eight bytes, see meet() in
+    // ffn_stream.hip.  The first contraction fills them with kNoRow.  (Then out_row: assignments, unrouted: of both.)
+    unsigned long long* exchange;
 };
+constexpr unsigned long long kNoRow = ~0ull;
 constexpr int kFewAssignments = 64;
 constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for itself
 // Is the path taken for A rows of `dt` spread over E_local experts?

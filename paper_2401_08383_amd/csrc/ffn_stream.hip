@@ -43,6 +43,25 @@ __device__ __forceinline__ void copy_sorted_rows(const StreamGemm& p, const int*
     }
 }
 
+// The two rows of a token of a top-2 layer come from different workgroups of the second contraction.  Eight bytes of either (four bf16, two
+// floats) meet in a word of p.exchange: an atomic exchange puts a row's there and returns what was; who gets kNoRow came first and leaves,
+// who gets the other row's bytes adds both up, in the order of the combine.  Nobody waits and the data travel inside the atomics, so no
+// store has to be made visible to another XCD's L2.  The launch of the combine is gone.
+__device__ __forceinline__ unsigned long long meet(unsigned long long* word, unsigned long long mine)
+{
+    if (mine == kNoRow) mine = 0x7fff7fff7fff7fffull;  // (NaNs as well, in either type)
+    return __hip_atomic_exchange(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// By the first contraction, behind everything else.
+template <int THREADS, typename ST>
+__device__ __forceinline__ void clear_exchange(const StreamGemm& p)
+{
+    const uint32_t none = static_cast<uint32_t>(kNoRow);
+    const int64_t vecs = static_cast<int64_t>(p.max_rows / 2) * (p.K * static_cast<int>(sizeof(ST)) / 16);
+    for (int64_t i = blockIdx.x * THREADS + threadIdx.x; i < vecs; i += gridDim.x * THREADS)
+        reinterpret_cast<uint4*>(p.exchange)[i] = make_uint4(none, none, none, none);
+}
+
 // The stable counting sort of moe_dispatch for at most kInlineDispatchMax assignments, by one workgroup into LDS.  Loading
 // the ids costs the same memory round trip as loading finished offsets would, and the sort itself about a third of
 // the launch it replaces.  Segments (round, wavefront) are ascending assignment order.
@@ -155,7 +174,7 @@ __device__ __forceinline__ ExpertTiles scan_row_tiles(const StreamGemm& p, const
 // instructions and memory round trips (a wavefront issues one instruction in about five cycles), so what a launch of at most
 // eight rows does not need is compiled out (EIGHT).  One token, 8 experts of 1024 x 4096: 15.2 us in three launches, 12.2 in
 // two; one GPU's 2 of 8 experts with the routing given 15.6 and 12.1; 16 tokens, 8 experts 32.1 and 29.7.
-template <int W, int LDS, bool EIGHT, bool SECOND>
+template <int W, int LDS, bool EIGHT, bool SECOND, bool PAIRS>
 __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned char* smem, int* sorted, int tile_rows)
 {
     const int lane = lane_id();
@@ -167,7 +186,9 @@ __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned c
     int id = 0;
     if (SECOND || p.w_gate == nullptr || p.topk_idx != p.gate_idx) id = p.topk_idx[at];
     float scale = 1.0f;
-    if (SECOND && p.out_row != nullptr) scale = p.out_scale[at];  // (k = 1: the assignment is the token)
+    if (SECOND && p.out_row != nullptr) scale = p.out_scale[at];
+    float mate_scale = 0.0f;
+    if constexpr (PAIRS) mate_scale = p.out_scale[at ^ 1];
     if (gated) {
         const int T = A / p.k;
         Route r;
@@ -216,8 +237,13 @@ __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned c
         __builtin_amdgcn_wave_barrier();
     }
     if (e >= 0) {
-        sorted[pos] = p.k == 2 ? lane >> 1 : lane;
+        sorted[pos] = p.k == 2 && !PAIRS ? lane >> 1 : lane;
         if (SECOND) reinterpret_cast<float*>(sorted)[kWave + pos] = scale;
+    }
+    const int mate = PAIRS ? __shfl_xor(e, 1, kWave) : -1;  // local expert of the token's other assignment
+    if (PAIRS && e >= 0) {
+        reinterpret_cast<float*>(sorted)[2 * kWave + pos] = mate_scale;
+        sorted[3 * kWave + pos] = mate;
     }
     if (!SECOND && blockIdx.x == 0 && wave == 0) {
         if (lane < p.E_local) {
@@ -229,10 +255,10 @@ __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned c
         if (e >= 0) p.src_of_sorted[pos] = lane;
     }
     if (SECOND && p.unrouted != nullptr) {  // output rows nobody writes, dealt to the workgroups
-        unsigned long long todo = __ballot(lane < A && e < 0);
+        unsigned long long todo = __ballot(lane < A && e < 0 && mate < 0 && !(PAIRS && (lane & 1) != 0));
         for (int n = 0; todo != 0ull; ++n, todo &= todo - 1ull) {
             if (n != static_cast<int>(blockIdx.x)) continue;
-            uint4* row = reinterpret_cast<uint4*>(p.out) + static_cast<size_t>(__builtin_ctzll(todo)) * (p.N / 8);
+            uint4* row = reinterpret_cast<uint4*>(p.out) + static_cast<size_t>(__builtin_ctzll(todo) >> (PAIRS ? 1 : 0)) * (p.N / 8);
             for (int c = threadIdx.x; c < p.N / 8; c += W * kWave) row[c] = make_uint4(0u, 0u, 0u, 0u);
         }
     }
@@ -252,7 +278,7 @@ __device__ __forceinline__ ExpertTiles route_few(const StreamGemm& p, unsigned c
 
 // ---------------------------------------------------------------------------- bf16
 constexpr int kStreamGrid = 256;     // workgroups: one per compute unit
-constexpr int kStreamIdBytes = 512;  // per wavefront: row ids of a tile, gate weights of a tile
+constexpr int kStreamIdBytes = 1024;  // per wavefront and row of a tile: its id, its gate weight, that of its token's other row, whether there is one
 // C8: columns of a block / 8.  A row tile has at most 8 * stream_max_ar(C8) rows (narrow blocks have shorter tiles: the
 // activations would fill the ring).
 __host__ __device__ constexpr int stream_max_ar(int C8) { return C8 == 8 ? 8 : 4; }
@@ -303,12 +329,17 @@ __device__ __forceinline__ void wait_units(int units)
 // Where the rows of a contraction come from: sorted (maps in memory), sorted by the workgroup, sorted by every wavefront.
 enum StreamRows { kRowsSorted, kRowsInline, kRowsFew, kRowsEight };  // (the last: as kRowsFew, at most eight)
 
+// The sorted rows that are wanted besides the result: none, p.sorted_act (a contraction that sorts), p.sorted_out (one that scales).  Instances
+// of their own: what a handful of rows does not need costs them 0.6 us of 12.
+// The last: the two rows of a token meet in p.exchange (p.sorted_out as well if it is given).
+enum StreamKeep { kKeepNone, kKeepAct, kKeepOut, kKeepPairs };
+
 // Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
-// KEEP_OUT: p.sorted_out is given.
-template <int C8, int AR, int W, bool KEEP_OUT, StreamRows ROWS, bool SECOND>
+template <int C8, int AR, int W, StreamKeep KEEP, StreamRows ROWS, bool SECOND>
 __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int row_begin, int row_end, int block_begin, int block_end,
                                                int rotate, const int* list, unsigned char* smem)
 {
+    constexpr bool KEEP_OUT = KEEP == kKeepOut, PAIRS = KEEP == kKeepPairs;
     constexpr bool FEW_ROWS = ROWS == kRowsEight, FEW = FEW_ROWS || ROWS == kRowsFew;  // FEW: `list` holds tokens, not assignments
     const bool listed_out = FEW && SECOND && p.out_row != nullptr;
     constexpr int C = (C8 + 1) / 2, M = (AR + 1) / 2;  // MFMA tiles along the columns and the rows (eight of either are read twice)
@@ -403,6 +434,10 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     }
     if (!known) place_rows();
     if (!FEW && SECOND && p.out_row != nullptr) lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane]) * 4u, ids_addr + 256);
+    if constexpr (!FEW && PAIRS) {
+        lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.out_scale)), static_cast<uint32_t>(ids[lane] ^ 1) * 4u, ids_addr + 512);
+        lds_dma_4B(uniform_ptr(reinterpret_cast<const unsigned char*>(p.unrouted)), static_cast<uint32_t>(ids[lane] ^ 1) * 4u, ids_addr + 768);
+    }
     if (!known) {
 #pragma unroll
         for (int s = 0; s < R; ++s)
@@ -522,7 +557,27 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 if constexpr (!SECOND) v[k] = p.epi == kEpiGeluErf ? gelu_erf_fast(v[k]) : gelu_tanh_fast(v[k]);
-                else if constexpr (!KEEP_OUT) v[k] *= scale;
+                else if constexpr (!KEEP_OUT && !PAIRS) v[k] *= scale;
+            }
+            if constexpr (PAIRS) {
+                const uint2 y = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+                if (p.sorted_out != nullptr) *reinterpret_cast<uint2*>(static_cast<bf16_t*>(p.sorted_out) + static_cast<size_t>(row_begin + r) * p.N + n) = y;
+                const bool second = (dst & 1) != 0, mated = ids[3 * kWave + r] >= 0;
+                dst >>= 1;
+                uint2 other = make_uint2(0u, 0u);
+                if (mated) {
+                    const unsigned long long got = meet(p.exchange + (static_cast<size_t>(dst) * p.N + n) / 4, static_cast<unsigned long long>(y.y) << 32 | y.x);
+                    if (got == kNoRow) continue;  // the other row's thread finds this one
+                    other = make_uint2(static_cast<uint32_t>(got), static_cast<uint32_t>(got >> 32));
+                }
+                const uint2 y0 = second ? other : y, y1 = second ? y : other;
+                const float mate_scale = mated ? gate[kWave + r] : 0.0f, w0 = second ? mate_scale : scale, w1 = second ? scale : mate_scale;
+                const uint32_t b0[2] = {y0.x, y0.y}, b1[2] = {y1.x, y1.y};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {  // (the combine's bits)
+                    const uint32_t f0 = (k & 1) != 0 ? b0[k / 2] & 0xffff0000u : b0[k / 2] << 16, f1 = (k & 1) != 0 ? b1[k / 2] & 0xffff0000u : b1[k / 2] << 16;
+                    v[k] = fmaf(w1, __uint_as_float(f1), fmaf(w0, __uint_as_float(f0), 0.0f));
+                }
             }
             if constexpr (KEEP_OUT) {
                 const uint2 y = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
@@ -541,10 +596,6 @@ __device__ __forceinline__ void stream_segment(const StreamGemm& p, int e, int r
     }
 }
 
-// The sorted rows that are wanted besides the result: none, p.sorted_act (a contraction that sorts), p.sorted_out (one that scales).  Instances
-// of their own: what a handful of rows does not need costs them 0.6 us of 12.
-enum StreamKeep { kKeepNone, kKeepAct, kKeepOut };
-
 // SECOND: a second contraction, which has no activation but may scale and scatter its rows.
 template <int C8, int W, StreamRows ROWS, StreamKeep KEEP, bool SECOND>
 __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
@@ -553,13 +604,13 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
     touch_arguments<sizeof(StreamGemm)>();
     constexpr int MAX_AR = stream_max_ar(C8), TILE_ROWS = 8 * MAX_AR, COLS = 8 * C8;
     constexpr bool FEW = ROWS == kRowsFew || ROWS == kRowsEight;
-    constexpr bool KEEP_OUT = KEEP == kKeepOut;
+    constexpr bool PAIRS = KEEP == kKeepPairs;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int* list = nullptr;
     ExpertTiles et;
     if constexpr (FEW) {
         int* sorted = reinterpret_cast<int*>(smem + stream_ring_bytes(C8, W) + wave * kStreamIdBytes);
-        et = route_few<W, stream_ring_bytes(C8, W), ROWS == kRowsEight, SECOND>(p, smem, sorted, TILE_ROWS);
+        et = route_few<W, stream_ring_bytes(C8, W), ROWS == kRowsEight, SECOND, PAIRS>(p, smem, sorted, TILE_ROWS);
         list = sorted;
     } else {
         const int32_t* offsets = p.offsets;
@@ -569,7 +620,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             list = d->list;
             offsets = d->offs;
         }
-        if (SECOND && p.unrouted != nullptr) clear_unrouted_rows<false>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
+        if (SECOND && p.unrouted != nullptr) clear_unrouted_rows<false, PAIRS>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
         et = scan_row_tiles(p, offsets, TILE_ROWS);
     }
     const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
@@ -611,7 +662,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             const int row_begin = wave_read_lane(et.lo, e), row_end = wave_read_lane(et.hi, e);
             const int b0 = static_cast<int>(at - t * n_blocks);
             at = min(end, (t + 1) * n_blocks);
-            stream_segment<C8, 1, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, smem);
+            stream_segment<C8, 1, W, KEEP, ROWS, SECOND>(p, e, row_begin, row_end, b0, static_cast<int>(at - t * n_blocks), lin, list, smem);
             continue;
         }
         const int e = __builtin_ctzll(__ballot(at < cost_incl * n_blocks));
@@ -638,12 +689,13 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         at = __builtin_amdgcn_readfirstlane(tile_begin + c * n_blocks);
         if (b0 >= b1) continue;
         const int rows = row_end - row_begin;
-        if (rows <= 8) stream_segment<C8, 1, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
-        else if (rows <= 16) stream_segment<C8, 2, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
-        else if (rows <= 32) stream_segment<C8, 4, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
-        else stream_segment<C8, MAX_AR, W, KEEP_OUT, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        if (rows <= 8) stream_segment<C8, 1, W, KEEP, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else if (rows <= 16) stream_segment<C8, 2, W, KEEP, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else if (rows <= 32) stream_segment<C8, 4, W, KEEP, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
+        else stream_segment<C8, MAX_AR, W, KEEP, ROWS, SECOND>(p, e, row_begin, row_end, b0, b1, lin, list, smem);
     }
     if constexpr (KEEP == kKeepAct) copy_sorted_rows<W * kWave, bf16_t>(p, list, wave_read_lane(et.hi, p.E_local - 1), FEW ? 1 : p.a_div);
+    if (!SECOND && ROWS != kRowsSorted && p.exchange != nullptr) clear_exchange<W * kWave, bf16_t>(p);
 }
 
 template <int C8, int W, StreamRows ROWS, StreamKeep KEEP, bool SECOND>
@@ -658,31 +710,33 @@ static int launch_stream_as(const StreamGemm& p, hipStream_t stream)
     return EXF_OK;
 }
 
-template <int C8, int W, StreamRows ROWS, bool KEPT>
+enum StreamWant { kWantResult, kWantSorted, kWantPairs };  // the last: rows that meet in p.exchange
+template <int C8, int W, StreamRows ROWS, StreamWant WANT>
 static int launch_stream_rows(const StreamGemm& p, hipStream_t stream)
 {
     const bool second = p.epi == kEpiNone;
-    if constexpr (KEPT) {
-        if constexpr (ROWS != kRowsSorted) {  // (rows that are there in sorted order are not wanted again)
-            if (!second && p.sorted_act != nullptr) return launch_stream_as<C8, W, ROWS, kKeepAct, false>(p, stream);
-        }
-        if constexpr (ROWS != kRowsInline) {
-            if (second && p.sorted_out != nullptr) return launch_stream_as<C8, W, ROWS, kKeepOut, true>(p, stream);
-        }
-        return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: sorted rows of a contraction that has none");
-    } else {
+    if constexpr (WANT == kWantResult) {
         if constexpr (ROWS != kRowsInline) {  // (a first contraction)
             if (second) return launch_stream_as<C8, W, ROWS, kKeepNone, true>(p, stream);
         }
         return launch_stream_as<C8, W, ROWS, kKeepNone, false>(p, stream);
+    } else {
+        if constexpr (WANT == kWantSorted && ROWS != kRowsSorted) {  // (rows that are there in sorted order are not wanted again)
+            if (!second && p.sorted_act != nullptr) return launch_stream_as<C8, W, ROWS, kKeepAct, false>(p, stream);
+        }
+        if constexpr (WANT == kWantSorted && ROWS != kRowsInline) {
+            if (second && p.sorted_out != nullptr) return launch_stream_as<C8, W, ROWS, kKeepOut, true>(p, stream);
+        }
+        if constexpr (WANT == kWantPairs && ROWS != kRowsInline) return launch_stream_as<C8, W, ROWS, kKeepPairs, true>(p, stream);
+        return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: sorted rows of a contraction that has none");
     }
 }
-template <int C8, int W, bool KEPT>
+template <int C8, int W, StreamWant WANT>
 static int launch_stream(const StreamGemm& p, hipStream_t stream)
 {
-    if (p.topk_idx == nullptr) return launch_stream_rows<C8, W, kRowsSorted, KEPT>(p, stream);
-    if (p.max_rows <= 8) return launch_stream_rows<C8, W, kRowsEight, KEPT>(p, stream);
-    return p.max_rows <= kFewAssignments ? launch_stream_rows<C8, W, kRowsFew, KEPT>(p, stream) : launch_stream_rows<C8, W, kRowsInline, KEPT>(p, stream);
+    if (p.topk_idx == nullptr) return launch_stream_rows<C8, W, kRowsSorted, WANT>(p, stream);
+    if (p.max_rows <= 8) return launch_stream_rows<C8, W, kRowsEight, WANT>(p, stream);
+    return p.max_rows <= kFewAssignments ? launch_stream_rows<C8, W, kRowsFew, WANT>(p, stream) : launch_stream_rows<C8, W, kRowsInline, WANT>(p, stream);
 }
 
 // Columns per block, by a model of the launch (blocks of 8 columns: one row of 4096 x 1024 has 128 of them for 256 workgroups
@@ -693,7 +747,7 @@ static int launch_stream(const StreamGemm& p, hipStream_t stream)
 // 40.3; of 512 x 2048 15.3 and 14.3).  Among several, blocks of 8 columns only where an expert's rows hardly exceed a tile: up to
 // kFewAssignments in all (four experts of 512 x 2048, 120 rows 20.7 us with them and 18.5) and 28 an expert (two of 768 x 3072, 60
 // rows 23.0 and 20.4; 48 rows 16.4 and 16.9).
-template <bool KEPT>
+template <StreamWant WANT>
 static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
 {
     const double A = p.max_rows, E = p.E_local;
@@ -711,10 +765,10 @@ static int launch_stream_bf16(const StreamGemm& p, hipStream_t stream)
             best = c;
         }
     }
-    if (best == 8) return launch_stream<8, 4, KEPT>(p, stream);
-    if (best == 4) return launch_stream<4, 4, KEPT>(p, stream);
-    if (best == 2) return launch_stream<2, 8, KEPT>(p, stream);
-    return launch_stream<1, 8, KEPT>(p, stream);
+    if (best == 8) return launch_stream<8, 4, WANT>(p, stream);
+    if (best == 4) return launch_stream<4, 4, WANT>(p, stream);
+    if (best == 2) return launch_stream<2, 8, WANT>(p, stream);
+    return launch_stream<1, 8, WANT>(p, stream);
 }
 
 // ---------------------------------------------------------------------------- fp32
@@ -807,7 +861,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     constexpr int TILE_ROWS = 16 * M;
     extern __shared__ float red[];  // [WI][WK][TILE_ROWS][RS]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (p.unrouted != nullptr) clear_unrouted_rows<true>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 4, WK * WI);
+    if (p.unrouted != nullptr) clear_unrouted_rows<true, KEEP == kKeepPairs>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 4, WK * WI);
     const int32_t *a_row = p.a_row, *offsets = p.offsets;
     if constexpr (INLINE) {
         InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * WK * TILE_ROWS * RS);
@@ -841,10 +895,15 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     constexpr bool ONE = TILE_ROWS * GROUPS <= WK * kWave;
     const int thread = threadIdx.x % (WK * kWave);
     int one_dst = 0;
-    float one_scale = 1.0f;
+    float one_scale = 1.0f, one_mate_scale = 0.0f;
+    bool one_mated = false;
     if (ONE && valid && p.out_row != nullptr) {
         one_dst = p.out_row[min(row_begin + thread / GROUPS, row_end - 1)];
         one_scale = p.out_scale[one_dst];
+        if constexpr (KEEP == kKeepPairs) {
+            one_mate_scale = p.out_scale[one_dst ^ 1];
+            one_mated = p.unrouted[one_dst ^ 1] >= 0;
+        }
     }
 
     float* item_red = red + static_cast<size_t>(wave / WK) * (WK * TILE_ROWS * RS);
@@ -868,6 +927,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     }
     __syncthreads();
     if constexpr (INLINE && KEEP == kKeepAct) copy_sorted_rows<WK * WI * kWave, float>(p, a_row, offsets[p.E_local], p.a_div);
+    if (INLINE && p.exchange != nullptr) clear_exchange<WK * WI * kWave, float>(p);
     if (!valid) return;
 
     // four columns of one row per thread: the wavefronts' sums in a fixed order, bias, activation, scale
@@ -892,7 +952,34 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
             if (bias != nullptr) v[j] += bias[n + j];
             if (p.epi == kEpiGeluErf) v[j] = gelu_erf_exact(v[j]);
             else if (p.epi == kEpiGeluTanh) v[j] = gelu_tanh_exact(v[j]);
-            if constexpr (KEEP != kKeepOut) v[j] *= scale;
+            if constexpr (KEEP != kKeepOut && KEEP != kKeepPairs) v[j] *= scale;
+        }
+        if constexpr (KEEP == kKeepPairs) {
+            if (p.sorted_out != nullptr)
+                *reinterpret_cast<float4*>(static_cast<float*>(p.sorted_out) + static_cast<size_t>(row_begin + r) * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
+            const bool second = (dst & 1) != 0, mated = ONE ? one_mated : p.unrouted[dst ^ 1] >= 0;
+            const float mate_scale = !mated ? 0.0f : (ONE ? one_mate_scale : p.out_scale[dst ^ 1]);
+            const float w0 = second ? mate_scale : scale, w1 = second ? scale : mate_scale;
+            dst >>= 1;
+            const size_t at = static_cast<size_t>(dst) * p.N + n;
+            unsigned long long other[2] = {0ull, 0ull};
+            if (mated) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    other[h] = meet(p.exchange + at / 2 + h, static_cast<unsigned long long>(__float_as_uint(v[2 * h + 1])) << 32 | __float_as_uint(v[2 * h]));
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (other[h] == kNoRow) continue;  // the other row's thread finds this one
+                float o[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {  // (the combine's bits)
+                    const float theirs = __uint_as_float(static_cast<uint32_t>(other[h] >> (32 * j))), ours = v[2 * h + j];
+                    o[j] = fmaf(w1, second ? ours : theirs, fmaf(w0, second ? theirs : ours, 0.0f));
+                }
+                *reinterpret_cast<float2*>(static_cast<float*>(p.out) + at + 2 * h) = make_float2(o[0], o[1]);
+            }
+            continue;
         }
         if constexpr (KEEP == kKeepOut) {
             *reinterpret_cast<float4*>(static_cast<float*>(p.sorted_out) + static_cast<size_t>(row_begin + r) * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
@@ -928,6 +1015,7 @@ static int launch_exact(const StreamGemm& p, hipStream_t stream)
         if (p.sorted_act != nullptr) return launch_exact_as<C, M, WK, WI, D, true, kKeepAct>(p, stream);
         return launch_exact_as<C, M, WK, WI, D, true, kKeepNone>(p, stream);
     }
+    if (p.exchange != nullptr) return launch_exact_as<C, M, WK, WI, D, false, kKeepPairs>(p, stream);
     if (p.sorted_out != nullptr) return launch_exact_as<C, M, WK, WI, D, false, kKeepOut>(p, stream);
     return launch_exact_as<C, M, WK, WI, D, false, kKeepNone>(p, stream);
 }
@@ -1023,7 +1111,7 @@ __global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const St
     const int act_stride = d + 4, hid_stride = f + 4;  // (padded: 16 rows lie in distinct banks)
     float* hid = pair_smem;                     // [16][f + 4]
     float* act = hid + kPairRows * hid_stride;  // [16][d + 4], later the sums of the parts: [4][16][d + 4]
-    if (q.unrouted != nullptr) clear_unrouted_rows<false>(q.unrouted, q.n_unrouted, static_cast<uint4*>(q.out), d / 4, kPairWaves);
+    if (q.unrouted != nullptr) clear_unrouted_rows<false, false>(q.unrouted, q.n_unrouted, static_cast<uint4*>(q.out), d / 4, kPairWaves);
     // every XCD takes a contiguous share of the tiles: those of an expert meet in one L2
     const ExpertTiles et = scan_row_tiles(p, p.offsets, kPairRows);
     const int xcd = static_cast<int>(blockIdx.x % kXcdCount);
@@ -1166,8 +1254,9 @@ bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt)
 int launch_stream_gemm(const StreamGemm& p, int dt, hipStream_t stream)
 {
     if (dt == EXF_BF16) {
-        if (p.sorted_act == nullptr && p.sorted_out == nullptr) return launch_stream_bf16<false>(p, stream);
-        return launch_stream_bf16<true>(p, stream);
+        if (p.epi == kEpiNone && p.exchange != nullptr) return launch_stream_bf16<kWantPairs>(p, stream);
+        if (p.sorted_act == nullptr && p.sorted_out == nullptr) return launch_stream_bf16<kWantResult>(p, stream);
+        return launch_stream_bf16<kWantSorted>(p, stream);
     }
     // tiles of 64 rows for the reuse of weights that do not lie in the L2s (3544 rows, 4 experts of 232 x 524, both contractions 61.1 us with them, 47.6)
     return p.max_rows <= 16ll * p.E_local || static_cast<int64_t>(p.K) * p.N <= (1 << 18) ? launch_exact_rows<1>(p, stream) : launch_exact_rows<4>(p, stream);

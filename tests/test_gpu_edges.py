@@ -307,6 +307,55 @@ def test_unfused_layer_is_its_calls(T, k, E, E_local, dtype, routing, d, f):
     _layer_against_calls(T, k, E, E_local, dtype, False, routing, d, f, ("x_sorted", "y_sorted"))
 
 
+# top-2 layers whose two rows of a token meet in the second contraction: up to eight rows, up to 64 and up to 1024; blocks of 8 to 64 columns and
+# tiles of one and several row groups; tokens of which one or both assignments are dropped, and with the same expert twice ("ids"); the last
+# shape of the separate calls that gets by with the reserved 16 MiB, the first that does not, and weights past the line
+@pytest.mark.parametrize("T,E,E_local,dtype,fused,routing,d,f", [
+    (1, 8, 8, "bf16", True, "gate", 64, 64), (4, 5, 5, "bf16", False, "ids", 1088, 128), (3, 64, 9, "bf16", True, "ids", 4096, 64), (5, 8, 3, "bf16", True, "gate", 192, 320),
+    (32, 2, 2, "bf16", False, "gate", 704, 192), (31, 40, 13, "bf16", True, "ids", 128, 1088), (33, 3, 3, "bf16", True, "ids", 2112, 64), (128, 2, 1, "bf16", True, "ids", 64, 64),
+    (100, 16, 16, "bf16", False, "ids", 512, 128), (512, 64, 64, "bf16", True, "gate", 128, 64), (511, 64, 40, "bf16", False, "ids", 64, 192), (60, 7, 2, "bf16", True, "dropped", 64, 64),
+    (448, 64, 64, "bf16", False, "gate", 18688, 64), (448, 64, 64, "bf16", False, "gate", 18752, 64), (2, 2, 2, "bf16", True, "gate", 16448, 16384),
+    (1, 2, 2, "f32", True, "gate", 4, 4), (27, 12, 12, "f32", True, "gate", 60, 156), (200, 9, 4, "f32", True, "ids", 44, 260), (512, 3, 3, "f32", True, "ids", 256, 1024),
+    (512, 16, 16, "f32", True, "gate", 132, 1028), (90, 7, 7, "f32", False, "ids", 36, 64)])
+def test_top2_rows_that_meet(T, E, E_local, dtype, fused, routing, d, f):
+    _say(f"top-2 layer T={T} E={E} E_local={E_local} {dtype} fused={fused} {routing} {d} x {f}")
+    _layer_against_calls(T, 2, E, E_local, dtype, fused, routing, d, f, () if fused else ("x_sorted", "y_sorted"))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [3, 20, 200])
+def test_top2_rows_of_nans_meet(T, dtype):
+    """Also where every bit of the weights is set, as in a word that no row has reached yet, and with everything replayed from a graph."""
+    from paper_2401_08383_amd.pipeline import MoELayerRun
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1650 + T)
+    dt, bits = (torch.bfloat16, torch.int16) if dtype == "bf16" else (torch.float32, torch.int32)
+    x, wg = (torch.randn(shape, device="cuda", generator=g).to(dt) for shape in ((T, 64), (4, 64)))
+    w1, w2 = (torch.randn(shape, device="cuda", generator=g).to(dt) for shape in ((4, 128, 64), (4, 64, 128)))
+    for w in (w1, w2):
+        w[1].view(bits).fill_(-1)
+    idx = torch.randint(0, 4, (T, 2), device="cuda", generator=g, dtype=torch.int32)
+    idx[0] = torch.tensor([2, 3])
+    run = MoELayerRun(x, wg, w1, w2, 2, True, topk_idx=idx)
+    bad = (idx == 1).any(dim=1)
+
+    def look():
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(run.out[bad]).all()) and bool(torch.isfinite(run.out[~bad]).all())
+        return run.out[~bad].clone()
+
+    run.step()
+    first = look()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run.step()
+    for _ in range(4):
+        run.out.fill_(-7)
+        graph.replay()
+        assert torch.equal(look(), first)
+
+
 def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f, more=()):
     from paper_2401_08383_amd.pipeline import MoELayerRun
 
