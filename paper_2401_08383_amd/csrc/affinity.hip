@@ -41,6 +41,17 @@ constexpr int kTargetWorkgroups = 256;          // about one per CU
 // Ids per load of a trace column: four, except that a column of fewer has no vector to load.
 static int trace_vec(int64_t N) { return N >= 4 ? 4 : 1; }
 
+// The (chunk, group) of a workgroup of the multi-hop counts, numbered chunk by chunk; below zero: none.  Every XCD takes a contiguous eighth of the
+// items: the groups of a chunk share its columns in one L2 (two for a chunk on the edge), and 256 items are one workgroup for every compute
+// unit.  Dealt by whole chunks, 21 chunks of twelve groups were 36 workgroups for the 32 compute units of five XCDs (8 x 300000 tokens, 64 experts:
+// 17.3 us, now 13.5; 10 x 100000 13.9 and 12.0).
+static int64_t xcd_items_grid(int C, int Q) { return (static_cast<int64_t>(C) * Q + kXcds - 1) / kXcds * kXcds; }
+__device__ __forceinline__ int xcd_item(int C, int Q)
+{
+    const int items = C * Q, item = static_cast<int>(blockIdx.x % kXcds) * ((items + kXcds - 1) / kXcds) + static_cast<int>(blockIdx.x / kXcds);
+    return item < items ? item : -1;
+}
+
 struct AffinityPlan {
     int g;           // layer pairs per workgroup
     int Q;           // pair groups
@@ -67,7 +78,12 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
     while (p.copies < 16 && hist_bytes * g * (p.copies * 2) <= kAffHistBudget) p.copies *= 2;
     p.Q = pairs > 0 ? (pairs + g - 1) / g : 1;
     p.vec = trace_vec(N);
-    int c_target = kTargetWorkgroups / p.Q;
+    // At most one workgroup per compute unit of every XCD, which takes whole chunks: 42 chunks of six groups were 36 workgroups for the 32
+    // compute units of two XCDs, which began the last four when the others ended (19 x 870535 tokens, 60 experts 32.9 us, in 40 chunks 22.0; 10 x 1M,
+    // 64 experts 28.0 and 19.3; 22 x 1M, 32 experts 32.5 and 21.2).  Dealing an eighth of all workgroups to every XCD instead fills
+    // it as well, but reads slower: 20.2 and 22.4 there, 24 x 1M, 64 experts 26.8 and 26.0.
+    int c_target = kTargetWorkgroups / kXcds / p.Q * kXcds;
+    if (c_target < 1) c_target = kTargetWorkgroups / p.Q;
     if (c_target < 1) c_target = 1;
     // at least a sweep (the second launch reads all chunks: 3 x 79098 tokens in chunks of 512 17.0 us, of 4096 9.2), past that whole wavefronts (one
     // cut by the end of its chunk takes the checked path), not sweeps: 24 x 135000 tokens were 17 chunks for 32
@@ -340,12 +356,11 @@ __global__ __launch_bounds__(kHopThreads) void multihop_partial_kernel(const int
                                                                           int64_t chunk, int C, uint32_t* __restrict__ part_counts)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];  // [copies][copy_words >= slots * words], two 16-bit counters per word
-    // every XCD takes an eighth of the workgroups, chunk by chunk: the block pairs of a chunk share its columns in one L2
-    const int64_t items = static_cast<int64_t>(C) * Q, item = (blockIdx.x % kXcds) * ((items + kXcds - 1) / kXcds) + blockIdx.x / kXcds;
-    if (item >= items) return;
-    const int c = static_cast<int>(item / Q);
+    const int item = xcd_item(C, Q);
+    if (item < 0) return;
+    const int c = item / Q;
     int I, J;
-    hop_blocks(static_cast<int>(item % Q), blocks, I, J);
+    hop_blocks(item - c * Q, blocks, I, J);
     const int i0 = I * kHopBlock, j0 = J * kHopBlock;
     const int targets = I == J ? 0 : min(kHopBlock, L - j0);  // (block I is whole where there is a later one)
     const unsigned inside_i = hop_inside_mask(I, J, blocks, L), inside_j = I == J ? 0u : hop_inside_mask(J, I, blocks, L);
@@ -524,11 +539,10 @@ __global__ __launch_bounds__(kTraceThreads) void multihop_group_kernel(const int
                                                                        uint32_t* __restrict__ part_counts)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];  // [copies][kAffMaxGroup][words], two 16-bit counters per word
-    // all groups of a token chunk on one XCD: the columns they share are served by its L2
-    const int j = static_cast<int>(blockIdx.x) / kXcds;
-    const int c = j / Q * kXcds + static_cast<int>(blockIdx.x) % kXcds;
-    if (c >= C) return;
-    int q = j % Q, l = 0, pair = 0;  // source layer and number of its first pair
+    const int item = xcd_item(C, Q);
+    if (item < 0) return;
+    const int c = item / Q;
+    int q = item - c * Q, l = 0, pair = 0;  // source layer and number of its first pair
     for (; q >= (L - 2 - l) / kAffMaxGroup + 1; ++l) {
         q -= (L - 2 - l) / kAffMaxGroup + 1;
         pair += L - 1 - l;
@@ -1126,13 +1140,13 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
     if (multihop_direct(trace, L, N, E, counts, cond_prob, s)) return check_launch("affinity_multihop");
     uint32_t* part_counts = static_cast<uint32_t*>(workspace);
     if (p.C > 0 && p.groups) {
-        const int64_t grid = static_cast<int64_t>((p.C + kXcds - 1) / kXcds * kXcds) * p.Q;
+        const int64_t grid = xcd_items_grid(p.C, p.Q);
         if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "affinity_multihop: too many workgroups");
         auto kern = p.vec == 4 ? multihop_group_kernel<4> : multihop_group_kernel<1>;
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kTraceThreads), p.lds_bytes, s, trace, L, N, E, p.Q, p.copies, p.words,
                            p.chunk, p.C, part_counts);
     } else if (p.C > 0) {
-        const int64_t grid = (static_cast<int64_t>(p.C) * p.Q + kXcds - 1) / kXcds * kXcds;
+        const int64_t grid = xcd_items_grid(p.C, p.Q);
         if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "affinity_multihop: too many workgroups");
         auto kern = p.vec == 4 ? multihop_partial_kernel<4> : multihop_partial_kernel<1>;
         static std::atomic<uint64_t> allowed4{0}, allowed1{0};
