@@ -602,9 +602,23 @@ __global__ __launch_bounds__(kTraceThreads) void multihop_group_kernel(const int
     }
 }
 
-// Half a wavefront per (pair, source expert) row, lane w of it the counters 2w and 2w+1: sums the chunks (16 independent loads
+// The second launches ask for the partials of U chunks together: all of them up to 24 (asked for 16 by 16, 17 chunks were two round trips), past that
+// 32 by 32 for as many rows as the chip has SIMDs and else 16 by 16, where the reads are bound by their number (24 x 1M tokens, 64 experts,
+// 32 chunks 26.3 us with 32 and 26.0; 24 x 300000, 32 experts 12.8 and 13.4; 3 x 500000, 24 experts, 123 chunks 12.9 and 14.3).
+template <typename Launch>
+static void with_chunks_ahead(int C, int64_t rows, Launch launch)
+{
+    if (C <= 8) launch(std::integral_constant<int, 8>());
+    else if (C <= 16) launch(std::integral_constant<int, 16>());
+    else if (C <= 24) launch(std::integral_constant<int, 24>());
+    else if (rows <= 4 * kTargetWorkgroups) launch(std::integral_constant<int, 32>());
+    else launch(std::integral_constant<int, 16>());
+}
+
+// Half a wavefront per (pair, source expert) row, lane w of it the counters 2w and 2w+1: sums the chunks (up to 32 independent loads
 // in flight), the row sum by lane exchanges, the conditional probabilities.  Bound by the read of the partials: a lane per
 // counter fetched every word twice (24 layers, 64 experts, 17 chunks: 18 us, now 12).
+template <int U>
 __global__ __launch_bounds__(256) void multihop_finalize_kernel(const uint32_t* __restrict__ part_counts, int C, int pairs, int E, int words,
                                                                 int64_t* __restrict__ counts, float* __restrict__ cond_prob)
 {
@@ -616,13 +630,13 @@ __global__ __launch_bounds__(256) void multihop_finalize_kernel(const uint32_t* 
     const uint32_t* src = part_counts + static_cast<size_t>(pair) * words + i * row_words + min(w, row_words - 1);
     const size_t step = static_cast<size_t>(pairs) * words;
     long long even = 0, odd = 0;
-    for (int c0 = 0; c0 < C; c0 += 16) {
-        uint32_t v[16];
+    for (int c0 = 0; c0 < C; c0 += U) {
+        uint32_t v[U];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = src[min(c0 + u, C - 1) * step];  // clamped, never branched around
+        for (int u = 0; u < U; ++u) v[u] = src[min(c0 + u, C - 1) * step];  // clamped, never branched around
         uint32_t lo = 0, hi = 0;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < U; ++u) {
             lo += c0 + u < C ? v[u] & 0xffffu : 0u;
             hi += c0 + u < C ? v[u] >> 16 : 0u;
         }
@@ -648,13 +662,14 @@ __global__ __launch_bounds__(256) void multihop_finalize_kernel(const uint32_t* 
 }
 
 // Workgroups of 256 threads.  The first ceil((L-1)*E / 4) give every wavefront one (pair l, source
-// expert i) row: lane p sums bin (i, p) over all chunks (16 independent loads in flight), the row sum
+// expert i) row: lane p sums bin (i, p) over all chunks (up to 32 independent loads in flight), the row sum
 // is a wavefront reduction -> counts, load of (l, i), conditional probabilities; nothing goes through
 // LDS and no workgroup barrier is needed.  The next E workgroups take one
 // expert p of the FINAL layer each: its load is the column sum of the last pair (taken from the
 // partials, so that no result of another workgroup is needed) plus the orphans.  One workgroup
 // adds up the invalid tally.  With a placement, L-1 more workgroups form the locality numerators.
 constexpr int kFinRowsPerWorkgroup = 4;
+template <int U>
 __global__ __launch_bounds__(256) void affinity_finalize_kernel(const uint32_t* __restrict__ part_counts,
                                                                 const uint32_t* __restrict__ part_orphan_next,
                                                                 const uint32_t* __restrict__ part_orphan_last,
@@ -676,23 +691,25 @@ __global__ __launch_bounds__(256) void affinity_finalize_kernel(const uint32_t* 
         const int l = row / E;
         const int i = row % E;
         long long cnt = 0;
-        if (p < E) {
-            const int bin = i * E + p;
-            const int shift = (bin & 1) * 16;
-            const uint32_t* src = part_counts + static_cast<size_t>(l) * words + (bin >> 1);
-            const size_t step = static_cast<size_t>(pairs) * words;
-            // 16 independent loads in flight (clamped, never branched around)
-            for (int c0 = 0; c0 < C; c0 += 16) {
-                uint32_t v[16];
+        const uint32_t* orphans = part_orphan_next + static_cast<size_t>(l) * E + i;
+        const uint32_t first_orphan = *(C > 0 ? orphans + static_cast<size_t>(min(p, C - 1)) * pairs * E : part_counts);  // (travels with the counts;
+        // no chunks: any word that is there)
+        const int bin = i * E + min(p, E - 1);
+        const int shift = (bin & 1) * 16;
+        const uint32_t* src = part_counts + static_cast<size_t>(l) * words + (bin >> 1);
+        const size_t step = static_cast<size_t>(pairs) * words;
+        for (int c0 = 0; c0 < C; c0 += U) {
+            uint32_t v[U];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = src[min(c0 + u, C - 1) * step];
+            for (int u = 0; u < U; ++u) v[u] = src[min(c0 + u, C - 1) * step];  // clamped, never branched around
+            uint32_t sum = 0;
 #pragma unroll
-                for (int u = 0; u < 16; ++u)
-                    if (c0 + u < C) cnt += (v[u] >> shift) & 0xffffu;
-            }
+            for (int u = 0; u < U; ++u) sum += c0 + u < C ? (v[u] >> shift) & 0xffffu : 0u;
+            cnt += sum;
         }
-        long long orphan = 0;
-        for (int c = p; c < C; c += kWave) orphan += part_orphan_next[(static_cast<size_t>(c) * pairs + l) * E + i];
+        if (p >= E) cnt = 0;
+        long long orphan = p < C ? first_orphan : 0u;
+        for (int c = p + kWave; c < C; c += kWave) orphan += orphans[static_cast<size_t>(c) * pairs * E];
         orphan = wave_sum(orphan);
         const long long row_sum = wave_sum(cnt);
         if (p < E) {
@@ -988,8 +1005,10 @@ static int run_affinity(const char* fn, const int32_t* trace, const int32_t* pla
     // locality numerators of all pairs
     const unsigned fin_grid = static_cast<unsigned>(((L - 1) * E + kFinRowsPerWorkgroup - 1) / kFinRowsPerWorkgroup + E + 1 +
                                                    (placement != nullptr ? L - 1 : 0));
-    hipLaunchKernelGGL(affinity_finalize_kernel, dim3(fin_grid), dim3(256), 0, s, part_counts, part_orphan_next, part_orphan_last,
-                       part_invalid, p.C, p.Q, L, E, p.words, counts, loads, cond_prob, n_invalid, part_local, local_per_pair);
+    with_chunks_ahead(p.C, static_cast<int64_t>(L - 1) * E, [&](auto ahead) {
+        hipLaunchKernelGGL(affinity_finalize_kernel<decltype(ahead)::value>, dim3(fin_grid), dim3(256), 0, s, part_counts, part_orphan_next, part_orphan_last,
+                           part_invalid, p.C, p.Q, L, E, p.words, counts, loads, cond_prob, n_invalid, part_local, local_per_pair);
+    });
     return check_launch(fn);
 }
 
@@ -1155,8 +1174,10 @@ extern "C" int affinity_multihop(const int32_t* trace, int L, int64_t N, int E, 
                            p.copies, p.copy_words, p.words, p.chunk, p.C, part_counts);
     }
     const int64_t fin_grid = (static_cast<int64_t>(p.pairs) * E + 256 / 32 - 1) / (256 / 32);
-    hipLaunchKernelGGL(multihop_finalize_kernel, dim3(static_cast<unsigned>(fin_grid)), dim3(256), 0, s, part_counts, p.C, p.pairs, E, p.words,
-                       counts, cond_prob);
+    with_chunks_ahead(p.C, static_cast<int64_t>(p.pairs) * E, [&](auto ahead) {
+        hipLaunchKernelGGL(multihop_finalize_kernel<decltype(ahead)::value>, dim3(static_cast<unsigned>(fin_grid)), dim3(256), 0, s, part_counts, p.C, p.pairs, E,
+                           p.words, counts, cond_prob);
+    });
     return check_launch("affinity_multihop");
 }
 

@@ -45,7 +45,9 @@ def test_short_traces(oracle, L, N, E, G):
 
 # chunks of whole wavefronts past one sweep, the last one cut; rows of 23, 31 and 32 words and an odd number of experts (words of two rows),
 # groups of three pairs and of fewer
-@pytest.mark.parametrize("L,N,E,G", [(24, 135001, 64, 8), (4, 40000, 62, 2), (23, 200003, 46, 2), (5, 300002, 64, 4), (24, 140001, 63, 7), (24, 131072, 44, 4)])
+@pytest.mark.parametrize("L,N,E,G", [(24, 135001, 64, 8), (4, 40000, 62, 2), (23, 200003, 46, 2), (5, 300002, 64, 4), (24, 140001, 63, 7), (24, 131072, 44, 4),
+                                     # partials of 7, 22 and (28 layer groups, one of them of a chunk an XCD) 8 chunks
+                                     (22, 26562, 64, 4), (6, 90001, 40, 4), (85, 70000, 16, 4)])
 def test_locality_from_the_histograms_of_a_chunk(oracle, L, N, E, G):
     _say(f"statistics L={L} N={N} E={E} G={G}")
     trace, _ = syn.planted_trace(L, N, E, 0.5, seed=2150 + N)
