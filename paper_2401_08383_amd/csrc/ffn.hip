@@ -784,9 +784,14 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     timeline_stamp(map, 0);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap)
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + 4] = 0ull;  // stays zero if this workgroup has no tile
-    if (map.unrouted != nullptr) clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
+    // Where every token is kept nobody has to look for others: their round trip in front of every tile is 39.2 us of 656 tokens, 12 experts of 960 x 1984
+    // and 38.5 without.  (The offsets of locate_tile travel along.)
+    const int ahead = offsets[min(lane_id(), E_local)];
+    if (map.unrouted != nullptr && min(offsets[E_local], max_rows) < map.n_unrouted)
+        clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
     Tile2D tile;
     if (!locate_tile(offsets, E_local, NT, N, max_rows, static_cast<int>(blockIdx.x), map, tile)) return;
+    keep_alive(ahead);
     timeline_stamp(map, 1);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap) {
         unsigned hw = 0, xcc = 0;

@@ -620,8 +620,9 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
             list = d->list;
             offsets = d->offs;
         }
-        if (SECOND && p.unrouted != nullptr) clear_unrouted_rows<false, PAIRS>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
         et = scan_row_tiles(p, offsets, TILE_ROWS);
+        if (SECOND && p.unrouted != nullptr && wave_read_lane(et.hi, p.E_local - 1) < p.max_rows)  // (else every assignment is kept)
+            clear_unrouted_rows<false, PAIRS>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 8, W);
     }
     const uint32_t n_blocks = static_cast<uint32_t>(p.N / COLS);
     // Every workgroup begins its blocks at another place of the reduction: rows a power of two bytes apart put the same
