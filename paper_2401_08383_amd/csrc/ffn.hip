@@ -41,23 +41,23 @@ constexpr int kKTile = 64;             // reduction elements of a stage: 128 byt
 // They let the contraction read the tokens where they lie (no sorted copy of the activations) and
 // let the second contraction of a top-1 layer write the gate-weighted result straight to the
 // token's own row (no sorted copy of the outputs, no separate combine pass).
+// (No padding between the members: all arguments and the size of the grid, which lies behind them, are two lines.)
 struct RowMap {
     const int32_t* a_row;     // operand row of sorted row s is a_row[s] / a_div        (null: row s)
-    int a_div;
     const int32_t* out_row;   // output row of sorted row s is out_row[s]; every output row is the
     const float* out_scale;   //   target of at most one s and is scaled by out_scale[out_row[s]] in
                               //   fp32 before the single rounding to bf16              (null: row s, no scale)
     const int32_t* unrouted;  // [n_unrouted]: output row t with unrouted[t] < 0 is set to zero
-    int n_unrouted;
     // Measurement only (exf_probe_ffn_timeline; null in every other call): workgroup b < timeline_cap
     // writes eight 64-bit words - [0] start, [1] tile located, [2] first K tile landed, [3] K loop done,
     // [4] end (all on the constant 100 MHz clock), [5] hardware id, [6] tile kind / expert / column tile /
     // rows / K tiles, [7] the experts' row ranges have arrived (between [0] and [1]).
     unsigned long long* timeline;
-    int timeline_cap;
     // With out_row and kEpiKeepSorted: sorted row s is the result in bf16, and what is scaled and rounded again is that, as the combine does it.
     bf16_t* sorted_out;
+    int a_div, n_unrouted, timeline_cap;
 };
+static_assert(sizeof(RowMap) == 64, "with the other arguments 120 bytes");
 
 // The hidden activations between the two contractions live in a layout of their own (nobody else reads them): the
 // 16-byte pieces (8 columns) of 32 consecutive rows are contiguous, and every expert starts on a 32-row boundary: sorted
@@ -786,12 +786,14 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + 4] = 0ull;  // stays zero if this workgroup has no tile
     // Where every token is kept nobody has to look for others: their round trip in front of every tile is 39.2 us of 656 tokens, 12 experts of 960 x 1984
     // and 38.5 without.  (The offsets of locate_tile travel along.)
-    const int ahead = offsets[min(lane_id(), E_local)];
-    if (map.unrouted != nullptr && min(offsets[E_local], max_rows) < map.n_unrouted)
-        clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
+    if (map.unrouted != nullptr) {
+        const int ahead = offsets[min(lane_id(), E_local)];
+        if (min(offsets[E_local], max_rows) < map.n_unrouted)
+            clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
+        keep_alive(ahead);
+    }
     Tile2D tile;
     if (!locate_tile(offsets, E_local, NT, N, max_rows, static_cast<int>(blockIdx.x), map, tile)) return;
-    keep_alive(ahead);
     timeline_stamp(map, 1);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap) {
         unsigned hw = 0, xcc = 0;
