@@ -225,16 +225,6 @@ __device__ __forceinline__ void touch_arguments()
 #endif
 }
 
-// A load whose value is not looked at (it brings a line near) is not taken out.
-__device__ __forceinline__ void keep_alive(int v)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" ::"v"(v));
-#else
-    (void)v;
-#endif
-}
-
 // Value of `v` in lane `src`, where src is the same in every lane (read on the scalar path).
 __device__ __forceinline__ int wave_read_lane(int v, int src)
 {

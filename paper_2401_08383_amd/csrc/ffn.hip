@@ -174,16 +174,25 @@ struct Tile2D {
     bool through;   // its hidden rows are written through to memory
 };
 
-__device__ __forceinline__ TilePlan plan_tiles(const int32_t* __restrict__ offsets, int E_local, int n_tiles, int max_rows, const RowMap& probe)
+struct RowRange {  // rows [lo, hi) of expert `lane`; the last expert's hi is the number of rows
+    int lo, hi;
+};
+__device__ __forceinline__ RowRange row_range(const int32_t* __restrict__ offsets, int E_local, int max_rows)
+{
+    RowRange r{0, 0};
+    const int lane = lane_id();
+    if (lane < E_local) {  // clamped so that a corrupt offsets array can never index past the buffers
+        r.lo = min(max(offsets[lane], 0), max_rows);
+        r.hi = min(max(offsets[lane + 1], r.lo), max_rows);
+    }
+    return r;
+}
+
+__device__ __forceinline__ TilePlan plan_tiles(const RowRange& range, int n_tiles, const RowMap& probe)
 {
     TilePlan p;
-    const int lane = lane_id();
-    p.lo = 0;
-    p.hi = 0;
-    if (lane < E_local) {  // clamped so that a corrupt offsets array can never index past the buffers
-        p.lo = min(max(offsets[lane], 0), max_rows);
-        p.hi = min(max(offsets[lane + 1], p.lo), max_rows);
-    }
+    p.lo = range.lo;
+    p.hi = range.hi;
     const int cnt = p.hi - p.lo;
     if (probe.timeline != nullptr) {  // measurement only: when did the row ranges arrive?
         if (__ballot(cnt >= 0) != 0ull) timeline_stamp(probe, 7);
@@ -226,11 +235,10 @@ __device__ __forceinline__ int xcd_share(int n, int xcd, int& rot, int& begin)
 // 63.7 -> 47.8 us; one of 2048 x 8192, 130 rows 75.4 -> 60.0; eight of 1024 x 4096, 2000 rows 92.3 -> 81.5; 16 of them, 3062
 // rows (the second contraction alone is cut: 256 x 64 -> 128 x 128) 101.9 -> 96.4.
 constexpr int kUnitsPerXcd = kComputeUnits / kXcdCount;
-__device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E_local, int NT, int N, int max_rows, int wg,
-                                            const RowMap& probe, Tile2D& out)
+__device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N, int wg, const RowMap& probe, Tile2D& out)
 {
     const int n_tiles = (N + NT - 1) / NT;
-    const TilePlan p = plan_tiles(offsets, E_local, n_tiles, max_rows, probe);
+    const TilePlan p = plan_tiles(range, n_tiles, probe);
     const int xcd = static_cast<int>(static_cast<unsigned>(wg) % kXcdCount);
     int pos = static_cast<int>(static_cast<unsigned>(wg) / kXcdCount);
     int rot = 0, begin = 0, begin_small = 0;
@@ -784,16 +792,14 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     timeline_stamp(map, 0);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap)
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + 4] = 0ull;  // stays zero if this workgroup has no tile
-    // Where every token is kept nobody has to look for others: their round trip in front of every tile is 39.2 us of 656 tokens, 12 experts of 960 x 1984
-    // and 38.5 without.  (The offsets of locate_tile travel along.)
-    if (map.unrouted != nullptr) {
-        const int ahead = offsets[min(lane_id(), E_local)];
-        if (min(offsets[E_local], max_rows) < map.n_unrouted)
-            clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
-        keep_alive(ahead);
-    }
+    const RowRange range = row_range(offsets, E_local, max_rows);
+    // Where every token is kept nobody has to look for others.  The last expert's end tells, and it has come with the ranges the tile is found by: asked for
+    // by itself in front of them it was a second round trip for every tile (5920 tokens of which an eighth is kept, 1024 x 4096 54.1 us, now 53.2; 3000
+    // tokens, 8 experts of 768 x 3072 60.9 and 60.5).
+    if (map.unrouted != nullptr && wave_read_lane(range.hi, E_local - 1) < map.n_unrouted)
+        clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
     Tile2D tile;
-    if (!locate_tile(offsets, E_local, NT, N, max_rows, static_cast<int>(blockIdx.x), map, tile)) return;
+    if (!locate_tile(range, NT, N, static_cast<int>(blockIdx.x), map, tile)) return;
     timeline_stamp(map, 1);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap) {
         unsigned hw = 0, xcc = 0;
