@@ -780,11 +780,17 @@ constexpr int kExactUnit = 32;  // reduction elements per step: 128 bytes of eve
 // stride RS floats).  A lane loads two 16-byte pieces of one weight row and the same pieces of one activation row per
 // unit; they are the operands of eight 16x16x4 MFMAs as they lie (the order in which the reduction index is dealt
 // to the lanes is free as long as both operands agree).  Loads run D units ahead; units past the end are clamped.
-template <int C, int M, int D, int RS>
+//   Whatever the kernel, a reduction is kExactParts sums of its own, added in order: short chains for the precision's sake, and the same bits from all of
+// them.  A wavefront that takes SUB parts adds them up as it goes (the first one of its item) or leaves each in a slot of its own.
+constexpr int kExactParts = 4;
+template <int C, int M, int D, int RS, int SUB>
 __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, const float* __restrict__ act, const int32_t* __restrict__ a_row,
-                                            int a_div, int row_begin, int row_end, int n0, int K, int N, int u_begin, int u_end,
-                                            float* __restrict__ red)
+                                            int a_div, int row_begin, int row_end, int n0, int K, int N, int part, float* __restrict__ red, int slot_floats)
 {
+    const int units = (K + kExactUnit - 1) / kExactUnit;
+    const int u_begin = part * SUB * units / kExactParts, u_end = (part + 1) * SUB * units / kExactParts;
+    const bool first_parts = SUB == kExactParts || part == 0;
+    if (!first_parts) red += (1 + (part - 1) * SUB) * slot_floats;
     const int lane = lane_id();
     const int r16 = lane & 15, g = lane >> 4;
     const float *row_w[C], *row_a[M];
@@ -819,7 +825,46 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
             }
         }
     };
-    auto compute = [&](int s) {
+    // a lane holds four consecutive columns of one row
+    auto store = [&](const f32x4_t(&sum)[C][M]) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int m = 0; m < M; ++m) *reinterpret_cast<f32x4_t*>(red + (m * 16 + r16) * RS + c * 16 + g * 4) = sum[c][m];
+    };
+    f32x4_t earlier[C][M];  // parts that are complete (a single wavefront, or the first one of an item)
+    if constexpr (SUB > 1) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int m = 0; m < M; ++m) earlier[c][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    int ends[SUB];
+#pragma unroll
+    for (int i = 0; i + 1 < SUB; ++i) ends[i] = (part * SUB + i + 1) * units / kExactParts;
+    auto behind = [&](int u) {  // all units below u are in acc: on to the next part?
+        if constexpr (SUB > 1) {
+            static_assert(SUB == 2 || SUB == kExactParts, "one slot a part");
+            bool next = false;
+#pragma unroll
+            for (int i = 0; i + 1 < SUB; ++i) next = next || u == ends[i];
+            if (!next) return;
+            if (SUB == kExactParts || first_parts) {
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int m = 0; m < M; ++m) earlier[c][m] += acc[c][m];
+            } else {
+                store(acc);
+                red += slot_floats;
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int m = 0; m < M; ++m) acc[c][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    auto compute = [&](int u, int s) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -829,7 +874,9 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
 #pragma unroll
                     for (int m = 0; m < M; ++m)
                         acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][c][h][j], a[s][m][h][j], acc[c][m], 0, 0, 0);
+        behind(u + 1);
     };
+    behind(u_begin);
     if (u_begin < u_end) {
 #pragma unroll
         for (int s = 0; s < D; ++s) load(min(u_begin + s, u_end - 1), s);
@@ -837,7 +884,7 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
         for (; u + D < u_end; u += D) {
 #pragma unroll
             for (int s = 0; s < D; ++s) {
-                compute(s);
+                compute(u + s, s);
                 __builtin_amdgcn_sched_barrier(0);
                 load(min(u + D + s, u_end - 1), s);
                 __builtin_amdgcn_sched_barrier(0);
@@ -845,27 +892,33 @@ __device__ __forceinline__ void exact_units(const float* __restrict__ wexp, cons
         }
 #pragma unroll
         for (int s = 0; s < D; ++s)
-            if (u + s < u_end) compute(s);
+            if (u + s < u_end) compute(u + s, s);
     }
-    // a lane holds four consecutive columns of one row
+    if constexpr (SUB > 1) {
+        if (SUB == kExactParts || first_parts) {
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+            for (int c = 0; c < C; ++c)
 #pragma unroll
-        for (int m = 0; m < M; ++m) *reinterpret_cast<f32x4_t*>(red + (m * 16 + r16) * RS + c * 16 + g * 4) = acc[c][m];
+                for (int m = 0; m < M; ++m) acc[c][m] = earlier[c][m] + acc[c][m];
+        }
+    }
+    store(acc);
 }
 
-// WI items per workgroup, WK wavefronts per item (they cut the reduction into parts).
+// WI items per workgroup, WK wavefronts per item (they share its parts).
+__host__ __device__ constexpr int exact_slots(int WK) { return 1 + (WK - 1) * (kExactParts / WK); }
 template <int C, int M, int WK, int WI, int D, bool INLINE, StreamKeep KEEP>
 __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGemm p)
 {
     constexpr int COLS = 16 * C, RS = COLS + 4;  // (padded: the 16 rows of a float4 column store hit distinct banks)
     constexpr int TILE_ROWS = 16 * M;
-    extern __shared__ float red[];  // [WI][WK][TILE_ROWS][RS]
+    extern __shared__ float red[];  // [WI][exact_slots(WK)][TILE_ROWS][RS]
+    constexpr int SLOTS = exact_slots(WK);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (p.unrouted != nullptr) clear_unrouted_rows<true, KEEP == kKeepPairs>(p.unrouted, p.n_unrouted, static_cast<uint4*>(p.out), p.N / 4, WK * WI);
     const int32_t *a_row = p.a_row, *offsets = p.offsets;
     if constexpr (INLINE) {
-        InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * WK * TILE_ROWS * RS);
+        InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * SLOTS * TILE_ROWS * RS);
         sort_assignments<WK * WI * kWave>(p, *d, blockIdx.x == 0);
         a_row = d->list;
         offsets = d->offs;
@@ -907,16 +960,13 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
         }
     }
 
-    float* item_red = red + static_cast<size_t>(wave / WK) * (WK * TILE_ROWS * RS);
+    float* item_red = red + static_cast<size_t>(wave / WK) * (SLOTS * TILE_ROWS * RS);
     if (valid) {
         const float* wexp = static_cast<const float*>(p.weight) + static_cast<size_t>(e) * p.N * p.K;
         const float* act = static_cast<const float*>(p.act);
-        const int units = (p.K + kExactUnit - 1) / kExactUnit;
-        const int part = wave % WK;
-        const int u_begin = part * units / WK, u_end = (part + 1) * units / WK;
-        float* mine = item_red + part * (TILE_ROWS * RS);
         const int m_used = (row_end - row_begin + 15) / 16;
-#define EXF_EXACT_UNITS(MU) exact_units<C, MU, D, RS>(wexp, act, a_row, p.a_div, row_begin, row_end, n0, p.K, p.N, u_begin, u_end, mine)
+#define EXF_EXACT_UNITS(MU) \
+    exact_units<C, MU, D, RS, kExactParts / WK>(wexp, act, a_row, p.a_div, row_begin, row_end, n0, p.K, p.N, wave % WK, item_red, TILE_ROWS* RS)
         if constexpr (M == 1) {
             EXF_EXACT_UNITS(1);
         } else {
@@ -931,14 +981,14 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     if (INLINE && p.exchange != nullptr) clear_exchange<WK * WI * kWave, float>(p);
     if (!valid) return;
 
-    // four columns of one row per thread: the wavefronts' sums in a fixed order, bias, activation, scale
+    // four columns of one row per thread: the parts' sums in a fixed order, bias, activation, scale
     const float* bias = p.bias != nullptr ? static_cast<const float*>(p.bias) + static_cast<size_t>(e) * p.N : nullptr;
     for (int i = thread; i < (row_end - row_begin) * GROUPS; i += WK * kWave) {
         const int r = i / GROUPS, q = i % GROUPS;
         const int n = n0 + q * 4;
         f32x4_t z = *reinterpret_cast<const f32x4_t*>(item_red + r * RS + q * 4);
 #pragma unroll
-        for (int wv = 1; wv < WK; ++wv) z += *reinterpret_cast<const f32x4_t*>(item_red + (wv * TILE_ROWS + r) * RS + q * 4);
+        for (int slot = 1; slot < SLOTS; ++slot) z += *reinterpret_cast<const f32x4_t*>(item_red + (slot * TILE_ROWS + r) * RS + q * 4);
         if (n >= p.N) continue;  // N % 4 == 0: the four columns are inside or outside together
         int dst = row_begin + r;
         float scale = 1.0f;
@@ -995,7 +1045,7 @@ template <int C, int M, int WK, int WI, int D, bool INLINE, StreamKeep KEEP>
 static int launch_exact_as(const StreamGemm& p, hipStream_t stream)
 {
     constexpr int TILE_ROWS = 16 * M;
-    constexpr size_t lds = static_cast<size_t>(WK * WI) * TILE_ROWS * (16 * C + 4) * sizeof(float) + (INLINE ? sizeof(InlineDispatch) : 0);
+    constexpr size_t lds = static_cast<size_t>(exact_slots(WK) * WI) * TILE_ROWS * (16 * C + 4) * sizeof(float) + (INLINE ? sizeof(InlineDispatch) : 0);
     auto kern = exact_gemm_kernel<C, M, WK, WI, D, INLINE, KEEP>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
@@ -1042,7 +1092,7 @@ static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 // in at some 40 bytes a cycle, 0.2 us for 1000 d f, so it is for layers whose tiles fill the chip (see exact_pair_fits).
 // Every sum is that of exact_gemm_kernel<1, 1, 4, 1>: the reduction in four parts, added in order.  Two launches and one, us: 3724 rows, 10 experts
 // of 120 x 444 26.0 and 17.6; 3333, 9 of 92 x 192 16.0 and 10.1; 2692, 2 of 56 x 256 14.8 and 9.1; 7688, 5 of 132 x 396 54.3 and 37.6.
-constexpr int kPairRows = 16, kPairWaves = 16, kPairParts = 4;
+constexpr int kPairRows = 16, kPairWaves = 16, kPairParts = kExactParts;
 constexpr int kPairAhead = 2;  // units of 32 asked for ahead (two workgroups share a compute unit: 64 registers)
 struct PairWeights {
     f32x4_t w[kPairAhead][2];

@@ -213,6 +213,25 @@ def test_exact_ffn_ragged(oracle, counts, d, f):
     P._ffn_case(oracle, "f32", counts, d, f, 0, True, seed=1500 + d + f)
 
 
+# Every fp32 kernel forms the same partial sums: the rows of an expert come out the same in a list of any length, alone as in the company of other experts.
+# Lists of one launch, of two in 16 and in 64 rows, reductions of one wavefront, two and four; fewer units of 32 than parts, a cut last one.
+@pytest.mark.parametrize("d,f", [(4, 64), (36, 100), (96, 1096), (132, 1028), (256, 512), (512, 512), (64, 4096)])
+def test_exact_rows_do_not_depend_on_the_list(d, f):
+    _say(f"fp32 rows alone and in company {d} x {f}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1560 + d + f)
+    counts = [4000, 0, 3, 1997, 2001]
+    A, E = sum(counts), len(counts)
+    x = torch.randn((A, d), device="cuda", generator=g)
+    w1, w2 = torch.randn((E, f, d), device="cuda", generator=g), torch.randn((E, d, f), device="cuda", generator=g)
+    begin = [sum(counts[:e]) for e in range(E + 1)]
+    y = B.moe_expert_ffn(x, torch.tensor(begin, dtype=torch.int32, device="cuda"), w1, w2)
+    for e, n in [(0, 1), (0, 17), (0, 300), (0, 1500), (0, 4000), (2, 3), (3, 1997), (4, 65)]:
+        mine = slice(begin[e], begin[e] + n)
+        alone = B.moe_expert_ffn(x[mine].contiguous(), torch.tensor([0, n], dtype=torch.int32, device="cuda"), w1[e:e + 1], w2[e:e + 1])
+        assert torch.equal(alone, y[mine]), (e, n)
+
+
 # both contractions by one workgroup a row tile: last columns and reductions of any length, tiles of one row, experts without rows, either side
 # of the line (a long list of few tiles, weights that do not fit, the last list that a first contraction sorts)
 @pytest.mark.parametrize("d,f", [(4, 4), (36, 20), (132, 260), (256, 1024), (68, 2052)])
