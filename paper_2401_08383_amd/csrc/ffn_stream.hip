@@ -20,6 +20,8 @@
 //   - row ids and gate weights travel through LDS as well, so that no load result is awaited through a register (the
 //     compiler would wait for every load in flight).
 // fp32 (the exact path, small layers): operands straight from global memory into registers, no LDS but for the sums.
+#include <cmath>
+
 #include "ffn_common.hpp"
 #include "gate_tile.hpp"
 
@@ -1075,14 +1077,56 @@ static int launch_exact(const StreamGemm& p, hipStream_t stream)
 // add up), two per 32 columns of 16 rows (7688 rows, 5 experts of 132 x 396, both contractions 54.3 us, with one per 64 columns 62.7; 3017, 6 of 96 x 284
 // 19.1 and 22.5), four for long reductions.  A smaller problem is cut into 16 x 16 tiles with four wavefronts along the reduction
 // (512 tokens x 8 experts x 64 x 256: 36 workgroups of 64 rows took 8.3 us in the second contraction, 4 now).
+constexpr int64_t kExactFewTiles = 384;
+constexpr int kExactShortReduction = 1024;
+static int64_t exact_tiles(int64_t A, int N, int E_local, int rows) { return ((A < E_local ? A : E_local) + A / rows) * ((N + 63) / 64); }
 template <int M>
 static int launch_exact_rows(const StreamGemm& p, hipStream_t stream)
 {
-    const int64_t tiles = (p.max_rows < p.E_local ? p.max_rows : p.E_local) + p.max_rows / (16 * M);
-    if (tiles * ((p.N + 63) / 64) < 384) return launch_exact<1, 1, 4, 1, 2>(p, stream);
-    if (p.K > 1024) return launch_exact<4, M, 4, 1, 2>(p, stream);
+    if (exact_tiles(p.max_rows, p.N, p.E_local, 16 * M) < kExactFewTiles) return launch_exact<1, 1, 4, 1, 2>(p, stream);
+    if (p.K > kExactShortReduction) return launch_exact<4, M, 4, 1, 2>(p, stream);
     if constexpr (M == 1) return launch_exact<2, 1, 2, 2, 2>(p, stream);
     else return launch_exact<4, M, 1, 4, 2>(p, stream);
+}
+
+// What an fp32 contraction [A,K] x [N,K] takes in launch_exact_rows<tall ? 4 : 1>, us.  Fitted to both contractions of 1540 lists (1025 to 100000 rows,
+// 1 to 64 experts, 16 x 64 to 1024 x 4096) in every combination of the kernels: within 5 % for half of them, 15 for nine tenths.  Wavefronts per SIMD (w)
+// run side by side until the operands' way from the L2 bounds them; tiles of 64 rows take their registers, one wavefront a SIMD, so that theirs come in rounds.
+static double exact_cost(int64_t A, int K, int N, int E_local, bool gelu, bool tall)
+{
+    const double experts = static_cast<double>(A < E_local ? A : E_local), written = static_cast<double>(A) * N * 4e-6;  // MB
+    const double simds = 4.0 * 256, row_tiles = A / 16.0 + experts / 2, col_tiles = (N + 63) / 64;  // (on the mean half a tile more per expert)
+    if (exact_tiles(A, N, E_local, tall ? 64 : 16) < kExactFewTiles)
+        return 2.7 + K / 4 * (0.0166 + 0.0106 * row_tiles * ((N + 15) / 16) * 4 / simds) + 1.15 * written;
+    if (tall) {
+        const bool parts = K > kExactShortReduction;
+        const double w = (A / 64.0 + experts / 2) * col_tiles * (parts ? 4 : 1) / simds, whole = floor(w);
+        const double begun = w < 2 ? 0.7 : 0.45, rounds = w <= 1 ? 1 : whole + (w > whole ? begun + (1 - begun) * (w - whole) : 0);
+        return parts ? 2.3 + rounds * (0.0203 * K + 2.3) + 1.1 * written : 3.1 + rounds * (0.0806 * K + (gelu ? 9.1 : 6.6)) + 0.41 * written;
+    }
+    if (K > kExactShortReduction) return K / 4 * (0.0298 + 0.0259 * row_tiles * col_tiles * 4 / simds) + 5.0 * written;
+    return 3.0 + K / 2 * (0.0115 + 0.0176 * row_tiles * ((N + 31) / 32) * 2 / simds) + 0.52 * written;
+}
+
+// Do the tiles of 64 rows nearly fill whole rounds of wavefronts?  Then they beat tiles of 16 by more than the model knows, but for reductions of 96 to 128 and
+// below 48: 32000 rows of 256 x 256, both contractions, 180 us in 16 rows and 144 in 64 (1.96 rounds); 8000 of 512 x 512 178 and 114 (0.99), of 16
+// experts (1.04) 178 and 206; 2000 of 64 x 4096 84.7 and 77.8 with the first in 64; first contraction of 16000 of 128 x 2048 22 more of 340.
+static bool whole_rounds(int64_t A, int K, int N, int E_local)
+{
+    if (A <= 16ll * E_local || !(K >= 240 || (K >= 48 && K <= 64)) || exact_tiles(A, N, E_local, 64) < kExactFewTiles) return false;
+    const int64_t half_tiles = (A / 32 + E_local) * ((N + 63) / 64) * (K > kExactShortReduction ? 4 : 1);
+    return 10 * half_tiles >= 9 * 2048 * ((half_tiles + 2047) / 2048);
+}
+
+// Tiles of 64 rows, else 16: for the weights' sake where these do not lie in the L2s (2^18 floats an expert; 3544 rows, 4 experts of 232 x 524, which do, both
+// contractions 61.1 us in 64 rows, 47.6 in 16), else where they fill their rounds or cost less.  Layers that were always in 16 rows and
+// now: 20000 rows, 8 experts of 512 x 512 454 and 337 us; 40000, 64 of 64 x 4096 1445 and 1186; 20000, 8 of 128 x 2048 444 and 388.
+static bool tall_exact_tiles(int64_t A, int K, int N, int E_local, bool gelu)
+{
+    if (A <= 16ll * E_local) return false;
+    if (static_cast<int64_t>(K) * N > 1 << 18) return true;
+    if (exact_tiles(A, N, E_local, 64) < kExactFewTiles) return false;
+    return whole_rounds(A, K, N, E_local) || exact_cost(A, K, N, E_local, gelu, true) < 0.95 * exact_cost(A, K, N, E_local, gelu, false);
 }
 
 // ---------------------------------------------------------------------------- fp32, both contractions at once
@@ -1255,13 +1299,32 @@ __global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const St
     }
 }
 
-// The line: 6.5 us and 0.2 for 1000 d f at one tile a compute unit, against 11 us and 1.4 for a million tiles d f in two launches; both within a
-// few microseconds of 50 layers of 600 to 8000 rows (79 tiles of 232 x 232 20.6 and 16.7, 98 of 52 x 576 16.3 and 18.5, 117 of
-// 188 x 796 39.6 and 41.5, 227 of 220 x 968 49.8 and 74.2).  Lists that a first contraction sorts have at most 80 tiles: two launches.
+// What the launch takes, us: rounds of tiles, one or (LDS) two on a compute unit.  In a tile the wavefronts wait for their operands (in units of 32
+// by 16 columns, all 16 wavefronts at once) and for the first ones of every 16 hidden columns and every quarter of 16 output columns; rows
+// of a multiple of 128 bytes begin on the same channels.  Fitted to 1000 lists as exact_cost: within 4 % for half of them, 9 for nine tenths.
+static double exact_pair_cost(int64_t A, int d, int f, int E_local)
+{
+    const int units1 = (d + 31) / 32, units2 = (f + 31) / 32, passes1 = (f + 255) / 256, passes2 = ((d + 15) / 16 * kPairParts + kPairWaves - 1) / kPairWaves;
+    const bool even1 = d % 32 == 0, even2 = f % 32 == 0;
+    const double operands = 0.455 * units1 * ((f + 15) / 16) / kPairWaves * (even1 ? 1.475 : 1.0) + 0.775 * units2 * ((d + 15) / 16) / kPairWaves * (even2 ? 1.1 : 1.0);
+    const double waits = passes1 * (0.47 + 0.093 * units1) + passes2 * (0.6 + 0.146 * ((units2 + 3) / 4)) * (even2 ? 1.1 : 1.0);
+    const double one = 2.0 + operands + waits, two = 2.0 + 1.9 * operands + 1.675 * waits;
+    const int64_t tiles = A / kPairRows + (A < E_local ? A : E_local) / 2;
+    if (pair_floats(d, f) * sizeof(float) > 80 * 1024) return 1.75 + (tiles + 255) / 256 * one;
+    const int64_t rest = tiles % 512;
+    return 1.75 + tiles / 512 * two + (rest == 0 ? 0 : (rest <= 256 ? one : two));
+}
+
+// The line: not where two launches would cost a twentieth less, nor where both contractions fill whole rounds of tiles of 64 rows.  Two launches and one, us:
+// 1500 rows, 4 experts of 256 x 256 18.0 and 19.4; 1100, 16 of 96 x 400 11.4 and 14.3; 1100, 64 of 256 x 1024 47 and 62; 1500, 4 of 64 x 1024 24.5 and
+// 19.1; 4000, 16 of 512 x 128 33.5 and 49.9; 64000 of 512 x 128 299 and 398; 32000 of 256 x 512 255 and 264; 8000 of 256 x 1024 156 and 126.  Over 1540 lists the choice
+// costs 1.5 % more than the best one (one launch wherever it fits 3.8).  Lists that a first contraction sorts are two launches: this kernel reads finished offsets.
 bool exact_pair_fits(int64_t A, int d, int f, int E_local)
 {
-    const int64_t tiles = A / kPairRows + (A < E_local ? A : E_local);
-    return A > kInlineDispatchMax && pair_floats(d, f) * sizeof(float) <= 160 * 1024 && static_cast<int64_t>(d) * f * (143 - tiles) <= 3200000;
+    if (A <= kInlineDispatchMax || pair_floats(d, f) * sizeof(float) > 160 * 1024) return false;
+    if (d >= 240 && whole_rounds(A, d, f, E_local) && whole_rounds(A, f, d, E_local)) return false;
+    const double both = exact_cost(A, d, f, E_local, true, tall_exact_tiles(A, d, f, E_local, true)) + exact_cost(A, f, d, E_local, false, tall_exact_tiles(A, f, d, E_local, false));
+    return both >= 0.95 * exact_pair_cost(A, d, f, E_local);
 }
 
 int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream)
@@ -1309,8 +1372,7 @@ int launch_stream_gemm(const StreamGemm& p, int dt, hipStream_t stream)
         if (p.sorted_act == nullptr && p.sorted_out == nullptr) return launch_stream_bf16<kWantResult>(p, stream);
         return launch_stream_bf16<kWantSorted>(p, stream);
     }
-    // tiles of 64 rows for the reuse of weights that do not lie in the L2s (3544 rows, 4 experts of 232 x 524, both contractions 61.1 us with them, 47.6)
-    return p.max_rows <= 16ll * p.E_local || static_cast<int64_t>(p.K) * p.N <= (1 << 18) ? launch_exact_rows<1>(p, stream) : launch_exact_rows<4>(p, stream);
+    return tall_exact_tiles(p.max_rows, p.K, p.N, p.E_local, p.epi != kEpiNone) ? launch_exact_rows<4>(p, stream) : launch_exact_rows<1>(p, stream);
 }
 
 }  // namespace exf
