@@ -72,7 +72,7 @@ __device__ __forceinline__ void clear_unrouted_rows(const int32_t* __restrict__ 
     }
 }
 
-enum Epilogue { kEpiNone = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2, kEpiKeepSorted = 3 };  // (the last: tiles of ffn.hip, RowMap::sorted_out)
+enum Epilogue { kEpiNone = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2, kEpiKeepSorted = 3 };  // (the last: tiles of ffn_tiles.hpp, RowMap::sorted_out)
 
 // ---------------------------------------------------------------------------- weight-streaming path
 // One contraction  out[rows of e, N] = epi(act[rows, K] * weight_e[N, K]^T + bias_e)  (see ffn_stream.hip).

@@ -16,7 +16,7 @@
 //   - the slot of a block's last unit is free until the block is stored: it carries the sums (at most eight rows have a place of
 //     their own for them).
 //   - the weights are read once: loaded with the streaming hint they leave the L2 to the activations (64 experts of
-//     4096 x 16384, 256 tokens top-2, both contractions: 3.08 ms without, 2.66 with, 2.89 as 64-row tiles of ffn.hip).
+//     4096 x 16384, 256 tokens top-2, both contractions: 3.08 ms without, 2.66 with, 2.89 as 64-row tiles of ffn_tiles.hpp).
 //   - row ids and gate weights travel through LDS as well, so that no load result is awaited through a register (the
 //     compiler would wait for every load in flight).
 // fp32 (the exact path, small layers): operands straight from global memory into registers, no LDS but for the sums.
@@ -311,7 +311,7 @@ __host__ __device__ constexpr int stream_sums_bytes(int C8) { return 8 * 8 * C8 
 // more the more of the ring they take.  Dealing ranges of equal cost instead of equal numbers of blocks keeps the tall tiles of
 // the experts that many tokens chose from being what the launch waits for, both contractions, rows falling on the experts as
 // 1/rank^1.1: 290 rows, 57 experts of 1024 x 4096 180 us before, 144 now; 400 rows, 32 of 2048 x 8192 489 and 379; 655
-// rows, 29 of 2560 x 10240 755 and 593 (64-row tiles of ffn.hip: 164, 423, 557); evenly spread rows as before or up to 6 %
+// rows, 29 of 2560 x 10240 755 and 593 (64-row tiles of ffn_tiles.hpp: 164, 423, 557); evenly spread rows as before or up to 6 %
 // less.  Coefficients of 3 and 5 instead of 4 give 601 and 586 there, but 290 instead of 284 with 5 for 128 rows, 8 of 4096 x 14336.
 __host__ __device__ constexpr uint32_t stream_cost(int C8, int AR) { return static_cast<uint32_t>((10 * C8 + 8 * AR) / C8); }
 
@@ -1351,7 +1351,7 @@ bool gate_joins_layer(int64_t T, int d, int E, int dt, bool routed)
 }
 
 // bf16: the weights are streamed where few rows use them, on the mean at most 28 an expert: 24 rows of 64 experts of 1024 x 4096 take
-// 222 us against 219 with the tiles of ffn.hip, 32 rows of 8 experts of 2048 x 8192 both 114.  With few experts the
+// 222 us against 219 with the tiles of ffn_tiles.hpp, 32 rows of 8 experts of 2048 x 8192 both 114.  With few experts the
 // tiles also wait for their K loops, a quarter of a microsecond for 64 elements of d + f, while streaming costs 35 ns per row and
 // million weights: up to 256 rows in all the lower of the two (three experts of 1024 x 4096: 21.2 us against 27.2 with 87 rows, 27.6
 // against 27.3 with 117).  Up to 128 rows of a single expert are known to fill 32, 64 or 128 of a row tile's, which is what they
