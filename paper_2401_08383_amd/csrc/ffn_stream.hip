@@ -333,7 +333,7 @@ enum StreamRows { kRowsSorted, kRowsInline, kRowsFew, kRowsEight };  // (the las
 
 // The sorted rows that are wanted besides the result: none, p.sorted_act (a contraction that sorts), p.sorted_out (one that scales).  Instances
 // of their own: what a handful of rows does not need costs them 0.6 us of 12.
-// The last: the two rows of a token meet in p.exchange (p.sorted_out as well if it is given).
+// The last: the two rows of a token meet in p.exchange (bf16: p.sorted_out as well if it is given; fp32 layers that keep their sorted rows have a combine).
 enum StreamKeep { kKeepNone, kKeepAct, kKeepOut, kKeepPairs };
 
 // Column blocks [block_begin, block_end) of one row tile (rows [row_begin, row_end), at most 8 AR).
@@ -1008,8 +1008,6 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
             if constexpr (KEEP != kKeepOut && KEEP != kKeepPairs) v[j] *= scale;
         }
         if constexpr (KEEP == kKeepPairs) {
-            if (p.sorted_out != nullptr)
-                *reinterpret_cast<float4*>(static_cast<float*>(p.sorted_out) + static_cast<size_t>(row_begin + r) * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
             const bool second = (dst & 1) != 0, mated = ONE ? one_mated : p.unrouted[dst ^ 1] >= 0;
             const float mate_scale = !mated ? 0.0f : (ONE ? one_mate_scale : p.out_scale[dst ^ 1]);
             const float w0 = second ? mate_scale : scale, w1 = second ? scale : mate_scale;
@@ -1068,7 +1066,10 @@ static int launch_exact(const StreamGemm& p, hipStream_t stream)
         if (p.sorted_act != nullptr) return launch_exact_as<C, M, WK, WI, D, true, kKeepAct>(p, stream);
         return launch_exact_as<C, M, WK, WI, D, true, kKeepNone>(p, stream);
     }
-    if (p.exchange != nullptr) return launch_exact_as<C, M, WK, WI, D, false, kKeepPairs>(p, stream);
+    if (p.exchange != nullptr) {
+        if (p.sorted_out != nullptr) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: sorted rows of a contraction that keeps none");
+        return launch_exact_as<C, M, WK, WI, D, false, kKeepPairs>(p, stream);
+    }
     if (p.sorted_out != nullptr) return launch_exact_as<C, M, WK, WI, D, false, kKeepOut>(p, stream);
     return launch_exact_as<C, M, WK, WI, D, false, kKeepNone>(p, stream);
 }
