@@ -49,10 +49,14 @@ __device__ __forceinline__ void copy_sorted_rows(const StreamGemm& p, const int*
 // floats) meet in a word of p.exchange: an atomic exchange puts a row's there and returns what was; who gets kNoRow came first and leaves,
 // who gets the other row's bytes adds both up, in the order of the combine.  Nobody waits and the data travel inside the atomics, so no
 // store has to be made visible to another XCD's L2.  The launch of the combine is gone.
+//   kNoRow is eight bytes of NaN: a row with these leaves others.  (fp32 rows do have them, where a weight has every bit set; the bf16 conversion makes
+// 0xffc0 of such a NaN, so that no bf16 row is known to.)
+constexpr unsigned long long kRowOfNans = 0x7fff7fff7fff7fffull;
+__host__ __device__ constexpr unsigned long long word_of_row(unsigned long long mine) { return mine == kNoRow ? kRowOfNans : mine; }
+static_assert(word_of_row(kNoRow) != kNoRow && word_of_row(~1ull) == ~1ull && word_of_row(0) == 0, "only the word that stands for no row is another one");
 __device__ __forceinline__ unsigned long long meet(unsigned long long* word, unsigned long long mine)
 {
-    if (mine == kNoRow) mine = 0x7fff7fff7fff7fffull;  // (NaNs as well, in either type)
-    return __hip_atomic_exchange(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_exchange(word, word_of_row(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // By the first contraction, behind everything else.
 template <int THREADS, typename ST>
