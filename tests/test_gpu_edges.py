@@ -241,6 +241,27 @@ def test_exact_ffn_in_one_launch(oracle, counts, d, f, act):
     P._ffn_case(oracle, "f32", counts, d, f, act, act == 0, seed=1540 + d + f)
 
 
+# gather, scale, scatter and clearing of that kernel against the oracle: tiles of one row, experts without rows, half of the experts elsewhere, none of the
+# tokens here, two assignments a token
+@pytest.mark.parametrize("T,E,E_local,k,d,f,skew", [
+    (3001, 9, 9, 1, 44, 212, True), (3001, 9, 4, 1, 256, 92, False), (2000, 5, 5, 2, 96, 132, False), (1100, 64, 32, 1, 28, 52, False), (1100, 16, 7, 2, 60, 100, True)])
+def test_exact_fused_layer_in_one_launch_parity(oracle, T, E, E_local, k, d, f, skew):
+    _say(f"fused fp32 layer against the oracle T={T} E={E} E_local={E_local} k={k} {d} x {f}")
+    P._fused_case(oracle, T, d, f, E, E_local, k, k - 1, E_local < E, seed=1570 + T + d, skew=skew, dtype="f32")
+
+
+def test_exact_fused_layer_in_one_launch_without_rows():
+    """Every expert lives elsewhere: nothing but zeros."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1580)
+    x = torch.randn((2000, 44), device="cuda", generator=g)
+    w1, w2 = torch.randn((3, 212, 44), device="cuda", generator=g), torch.randn((3, 44, 212), device="cuda", generator=g)
+    maps = B.moe_dispatch(x, torch.full((2000, 1), 5, dtype=torch.int32, device="cuda"), 6, E_local=3, gather=False)
+    out = torch.full_like(x, -7)
+    B.moe_expert_ffn_fused(x, maps.src_of_sorted, maps.sorted_of_src, torch.ones((2000, 1), device="cuda"), maps.expert_offsets, w1, w2, out=out)
+    assert torch.equal(out, torch.zeros_like(out))
+
+
 @pytest.mark.parametrize("T,k,E,E_local,fused,routing,d,f", [
     (3001, 1, 9, 9, True, "gate", 44, 212), (3001, 1, 9, 4, True, "ids", 256, 92), (2000, 2, 5, 5, True, "gate", 96, 132), (5000, 1, 3, 1, True, "dropped", 32, 128),
     (3001, 1, 9, 4, False, "ids", 100, 60), (1100, 2, 16, 16, False, "gate", 64, 128), (4096, 1, 16, 16, False, "gate", 256, 1024)])
@@ -343,10 +364,11 @@ def test_top2_rows_that_meet(T, E, E_local, dtype, fused, routing, d, f):
     _layer_against_calls(T, 2, E, E_local, dtype, fused, routing, d, f, () if fused else ("x_sorted", "y_sorted"))
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("T", [3, 20, 200])
-def test_top2_rows_of_nans_meet(T, dtype):
-    """Also where every bit of the weights is set, as in a word that no row has reached yet, and with everything replayed from a graph."""
+@pytest.mark.parametrize("dtype,fused", [("bf16", True), ("bf16", False), ("f32", True)])
+@pytest.mark.parametrize("T", [4, 20, 200])
+def test_top2_rows_of_nans_meet(T, dtype, fused):
+    """Also where every bit of the weights is set, as in a word that no row has reached yet, and with everything replayed from a graph.  (Separate
+    calls in fp32 have a combine.)"""
     from paper_2401_08383_amd.pipeline import MoELayerRun
 
     g = torch.Generator(device="cuda")
@@ -357,9 +379,14 @@ def test_top2_rows_of_nans_meet(T, dtype):
     for w in (w1, w2):
         w[1].view(bits).fill_(-1)
     idx = torch.randint(0, 4, (T, 2), device="cuda", generator=g, dtype=torch.int32)
-    idx[0] = torch.tensor([2, 3])
-    run = MoELayerRun(x, wg, w1, w2, 2, True, topk_idx=idx)
+    idx[:4] = torch.tensor([[2, 3], [1, 2], [3, 1], [1, 1]])  # neither row, either one, both of NaNs
+    run = MoELayerRun(x, wg, w1, w2, 2, True, topk_idx=idx, fused=fused)
     bad = (idx == 1).any(dim=1)
+    # rows with eight bytes of set bits, as the separate calls leave them: fp32 has them, the conversion to bf16 makes 0xffc0 of these NaNs
+    apart = MoELayerRun(x, wg, w1, w2, 2, True, topk_idx=idx)
+    apart.step()
+    torch.cuda.synchronize()
+    assert bool((apart.y_sorted.view(torch.int64) == -1).any()) == (dtype == "f32")
 
     def look():
         torch.cuda.synchronize()
