@@ -52,6 +52,19 @@ __device__ __forceinline__ int xcd_item(int C, int Q)
     return item < items ? item : -1;
 }
 
+// The second launches ask for the partials of so many chunks together: all of them up to 24 (asked for 16 by 16, 17 chunks were two round trips), past that
+// up to 32 for as many rows as the chip has SIMDs and else 16 by 16, where the reads are bound by their number (24 x 1M tokens, 64 experts,
+// 32 chunks 26.3 us with 32 and 26.0; 24 x 300000, 32 experts 12.8 and 13.4; 3 x 500000, 24 experts, 123 chunks 12.9 and 14.3).
+// Trips of equal length: 35 chunks in two of 24 (2 x 142392 tokens, 24 experts 9.25 us in two of 32,
+// 8.9; 16 x 265000, 64 experts, 48 chunks 17.75 and 16.6).
+static int chunks_ahead(int C, int64_t rows)
+{
+    if (C > 24 && rows > 4 * kTargetWorkgroups) return 16;
+    const int trips = C > 0 ? (C + 31) / 32 : 1;
+    return ((C + trips - 1) / trips + 7) / 8 * 8;
+}
+static int trips_of_chunks(int C, int64_t rows) { return C > 0 ? (C + chunks_ahead(C, rows) - 1) / chunks_ahead(C, rows) : 0; }
+
 struct AffinityPlan {
     int g;           // layer pairs per workgroup
     int Q;           // pair groups
@@ -78,7 +91,7 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
     while (p.copies < 16 && hist_bytes * g * (p.copies * 2) <= kAffHistBudget) p.copies *= 2;
     p.Q = pairs > 0 ? (pairs + g - 1) / g : 1;
     p.vec = trace_vec(N);
-    // At most one workgroup per compute unit of every XCD, which takes whole chunks: 42 chunks of six groups were 36 workgroups for the 32
+    // Up to 32 groups, and where the counters do not ask for shorter chunks: at most one workgroup per compute unit of every XCD, which takes whole chunks.  42 chunks of six groups were 36 workgroups for the 32
     // compute units of two XCDs, which began the last four when the others ended (19 x 870535 tokens, 60 experts 32.9 us, in 40 chunks 22.0; 10 x 1M,
     // 64 experts 28.0 and 19.3; 22 x 1M, 32 experts 32.5 and 21.2).  Dealing an eighth of all workgroups to every XCD instead fills
     // it as well, but reads slower: 20.2 and 22.4 there, 24 x 1M, 64 experts 26.8 and 26.0.
@@ -86,13 +99,19 @@ static AffinityPlan make_affinity_plan(int L, int64_t N, int E)
     if (c_target < 1) c_target = kTargetWorkgroups / p.Q;
     if (c_target < 1) c_target = 1;
     // at least a sweep (the second launch reads all chunks: 3 x 79098 tokens in chunks of 512 17.0 us, of 4096 9.2), past that whole wavefronts (one
-    // cut by the end of its chunk takes the checked path), not sweeps: 24 x 135000 tokens were 17 chunks for 32
-    // (16.3 us, now 14.4; 24 x 500000 of 52 experts 20.0 and 17.9)
+    // cut by the end of its chunk takes the checked path), not sweeps: 24 x 500000 tokens of 52 experts 20.0 us in 31 chunks, 17.9 in 32
     const int64_t sweep = static_cast<int64_t>(kTraceThreads) * p.vec;  // tokens one pass of the workgroup covers
     const int64_t unit = static_cast<int64_t>(kWave) * p.vec;
     int64_t chunk = (N + c_target - 1) / c_target;
     chunk = (chunk + unit - 1) / unit * unit;
     if (chunk < sweep) chunk = sweep;
+    // Between one sweep and two, two where so many fewer chunks save the second launch a round trip: the first one gains less by the compute units that it fills
+    // (16 x 230004 tokens, 64 experts: 11.0 us in 48 chunks and 12.6 in 29, the second 7.2 and 4.6, together 17.5 and 14.8; 3 x 1.2M 24.5 and 19.3; 10 x 400000
+    // of 16 12.0 and 11.5).  Where they save none: 24 x 147000, 16 experts, 9.6 in 32 chunks and 10.7 in 18.
+    const int64_t rows = static_cast<int64_t>(pairs) * E;
+    if (chunk > sweep && chunk < 2 * sweep &&
+        trips_of_chunks(static_cast<int>((N + 2 * sweep - 1) / (2 * sweep)), rows) < trips_of_chunks(static_cast<int>((N + chunk - 1) / chunk), rows))
+        chunk = 2 * sweep;
     if (chunk > kAffMaxChunk) chunk = kAffMaxChunk / unit * unit;
     p.chunk = chunk;
     p.C = static_cast<int>(N > 0 ? (N + chunk - 1) / chunk : 0);
@@ -602,17 +621,14 @@ __global__ __launch_bounds__(kTraceThreads) void multihop_group_kernel(const int
     }
 }
 
-// The second launches ask for the partials of U chunks together: all of them up to 24 (asked for 16 by 16, 17 chunks were two round trips), past that
-// 32 by 32 for as many rows as the chip has SIMDs and else 16 by 16, where the reads are bound by their number (24 x 1M tokens, 64 experts,
-// 32 chunks 26.3 us with 32 and 26.0; 24 x 300000, 32 experts 12.8 and 13.4; 3 x 500000, 24 experts, 123 chunks 12.9 and 14.3).
 template <typename Launch>
 static void with_chunks_ahead(int C, int64_t rows, Launch launch)
 {
-    if (C <= 8) launch(std::integral_constant<int, 8>());
-    else if (C <= 16) launch(std::integral_constant<int, 16>());
-    else if (C <= 24) launch(std::integral_constant<int, 24>());
-    else if (rows <= 4 * kTargetWorkgroups) launch(std::integral_constant<int, 32>());
-    else launch(std::integral_constant<int, 16>());
+    const int ahead = chunks_ahead(C, rows);
+    if (ahead <= 8) launch(std::integral_constant<int, 8>());
+    else if (ahead <= 16) launch(std::integral_constant<int, 16>());
+    else if (ahead <= 24) launch(std::integral_constant<int, 24>());
+    else launch(std::integral_constant<int, 32>());
 }
 
 // Half a wavefront per (pair, source expert) row, lane w of it the counters 2w and 2w+1: sums the chunks (up to 32 independent loads

@@ -47,7 +47,9 @@ def test_short_traces(oracle, L, N, E, G):
 # groups of three pairs and of fewer
 @pytest.mark.parametrize("L,N,E,G", [(24, 135001, 64, 8), (4, 40000, 62, 2), (23, 200003, 46, 2), (5, 300002, 64, 4), (24, 140001, 63, 7), (24, 131072, 44, 4),
                                      # partials of 7, 22 and (28 layer groups, one of them of a chunk an XCD) 8 chunks
-                                     (22, 26562, 64, 4), (6, 90001, 40, 4), (85, 70000, 16, 4)])
+                                     (22, 26562, 64, 4), (6, 90001, 40, 4), (85, 70000, 16, 4),
+                                     # chunks of two sweeps for a round trip fewer, and one token more than they would do for; 34, 48 and 128 partials in equal trips
+                                     (16, 239003, 64, 8), (16, 262145, 48, 8), (2, 139001, 24, 8), (7, 1000003, 8, 4)])
 def test_locality_from_the_histograms_of_a_chunk(oracle, L, N, E, G):
     _say(f"statistics L={L} N={N} E={E} G={G}")
     trace, _ = syn.planted_trace(L, N, E, 0.5, seed=2150 + N)
