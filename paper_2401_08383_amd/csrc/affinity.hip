@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
     // flush: sum the replicas (packed halves cannot carry: a bin holds at most `chunk` < 65536); with a placement, also count per pair the
     // transitions of the bins whose two experts share a device.  A power of two of lanes takes a row, each of them two of its bins (found
     // for every word by itself, with divisions, the devices were 3.6 us of the 22.7 of this launch at 24 x 1M tokens: the call 28.0 us, now
-    // 26.0; fewer words than two a thread gain nothing, 23 x 7452 of 38 experts 10.6 us and 11.2).  An odd number of experts has words of two rows.
+    // 26.0; fewer than 2.75 words a thread gain nothing, 23 x 7452 of 38 experts 10.6 us and 11.2).  An odd number of experts has words of two rows.
     const int my_pairs = l1 - l0;
     if (placement != nullptr && E % 2 == 0 && my_pairs * words > 11 * kTraceThreads / 4) {
         const int row_words = E / 2, log_lanes = row_words > 1 ? 32 - __builtin_clz(row_words - 1) : 0;
@@ -336,9 +336,10 @@ __global__ __launch_bounds__(kTraceThreads) void affinity_partial_kernel(const i
 //   - A histogram row starts at an even counter, so the word of a transition is row(a) + b/2 and its half is b%2: both
 //     are formed once per token and column, a transition costs one addition and one atomic.
 // Transitions with an invalid end are skipped; the packed per-chunk partials go to part_counts[chunk][pair][words].
-// 24 x 1M tokens, 64 experts, both launches: 99.0 us with loops over the targets and a second set of registers for the next sweep, 96.6
-// now.  Atomics are 59 us of it (7.6 cycles each; 43 without bank conflicts), the second launch 11.5, start, clearing and
-// writing of the histograms 15.
+// 24 x 1M tokens, 64 experts, both launches: 99.0 us with loops over the targets and a second set of registers for the next sweep, 95.3
+// now, 85 and 10 in the profiler.  In the first one a workgroup (one a compute unit) spends 3.5 us on clearing and its first loads, 68 on counting - 59 are the
+// LDS's for the atomics (7.6 cycles each; 43 without bank conflicts) -, 7 on writing, 79 on the mean; they end between 73 and 87.  Its wavefronts are done
+// between 30 and 68 us after the first loads: the LDS serves some before others.
 constexpr int kHopBlock = 4;       // layers per block
 constexpr int kHopThreads = 1024;
 constexpr int kHopInside = 6;      // pairs inside a block
