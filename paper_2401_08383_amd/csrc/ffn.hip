@@ -12,9 +12,30 @@
 
 namespace exf {
 
+// Launches in which some experts have a single row tile, whose weights nobody else reads, and are many enough not to stay in the
+// memory-side cache of 256 MB between two calls (both contractions of 2^26 weights): those tiles load them with the streaming hint.
+// us without and with it, the same weights from call to call / other ones each time:
+//   tokens, experts                     fits the cache?
+//   1200, 16 of 4096 x 16384            no    827 / 852 -> 730 / 752 (both begin the reduction at different places)
+//   6000, 64 of 2048 x 8192             no    835 / 866 -> 761 / 788
+//   600, 4 of 2560 x 10240              no    161 / 162 -> 144 / 160
+//   1500, 16 of 2048 x 8192             no    217 / 214 -> 206 / 197
+//   1531 top-2, 16 of 1024 x 4096       no    98.3 -> 96.6 / 102.4 -> 102.2
+//   800, 10 of 1024 x 4096              yes   51.8 / 60.4 -> 59.6 / 58.2
+//   600, 16 of 768 x 3072               yes   39.4 / 46.1 -> 43.1 / 43.5
+// Up to 1024 rows an expert on the mean: beyond, routing as uneven as Zipf's leaves no expert below 256 (16384 tokens, 32 of 2048 x 8192,
+// 512 on the mean, 1107 -> 1096 us).
+constexpr int64_t kStreamedWeights = 1ll << 26;
+constexpr int64_t kStreamedMeanRows = 1024;
+static bool weights_are_streamed(int64_t A, int K, int N, int E_local)
+{
+    return A <= kStreamedMeanRows * E_local && static_cast<int64_t>(E_local) * K * N >= kStreamedWeights;
+}
+
 static int launch_first_contraction(const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N,
                                     int E_local, int epi, void* out, hipStream_t stream, const RowMap& map)
 {
+    if (weights_are_streamed(A, K, N, E_local)) return launch_once_first(epi, act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
     if (epi == kEpiGeluErf) return launch_bf16_as<256, 8, kEpiGeluErf>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
     return launch_bf16_as<256, 8, kEpiGeluTanh>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
 }
@@ -29,6 +50,7 @@ static int launch_second_contraction(const void* act, const int32_t* offsets, co
 {
     const int64_t wide_tiles = (A / 256) * ((N + 255) / 256);
     const bool wide = wide_tiles >= static_cast<int64_t>(kWideRounds) * kComputeUnits;
+    if (weights_are_streamed(A, K, N, E_local)) return launch_once_second(wide, act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
     if (map.sorted_out == nullptr) {
         if (wide) return launch_bf16_as<256, 4, kEpiNone>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
         return launch_bf16_as<128, 4, kEpiNone>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);

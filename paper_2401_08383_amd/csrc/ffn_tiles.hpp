@@ -166,6 +166,8 @@ struct Tile2D {
     int cut;     // log2 of the pieces its columns are cut into (height and rows are those of the piece)
     int hid_shift;  // hidden row of sorted row m of this expert: m + hid_shift
     bool through;   // its hidden rows are written through to memory
+    bool once;      // nobody else reads its weights (see gemm_tile)
+    int turn;       // of kComputeUnits: where it begins the reduction
 };
 
 struct RowRange {  // rows [lo, hi) of expert `lane`; the last expert's hi is the number of rows
@@ -229,6 +231,7 @@ __device__ __forceinline__ int xcd_share(int n, int xcd, int& rot, int& begin)
 // 63.7 -> 47.8 us; one of 2048 x 8192, 130 rows 75.4 -> 60.0; eight of 1024 x 4096, 2000 rows 92.3 -> 81.5; 16 of them, 3062
 // rows (the second contraction alone is cut: 256 x 64 -> 128 x 128) 101.9 -> 96.4.
 constexpr int kUnitsPerXcd = kComputeUnits / kXcdCount;
+template <bool STREAMS>
 __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N, int wg, const RowMap& probe, Tile2D& out)
 {
     const int n_tiles = (N + NT - 1) / NT;
@@ -238,6 +241,7 @@ __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N
     int rot = 0, begin = 0, begin_small = 0;
     const int share = xcd_share(p.total_big, xcd, rot, begin), share_small = xcd_share(p.total_small, xcd, rot, begin_small);
     const int last_round = (share + share_small) % kUnitsPerXcd, whole = share + share_small - last_round;
+    int row_cut = 0;
     out.cut = last_round > kUnitsPerXcd / 2 ? 0 : (last_round > kUnitsPerXcd / 4 ? 1 : (last_round > kUnitsPerXcd / 8 ? 2 : 3));
     int piece = 0;
     if (pos < whole) {
@@ -286,6 +290,7 @@ __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N
         const TileCut t = cut_tile(NT, height, __builtin_amdgcn_readfirstlane(row_end - row_begin), out.cut);
         if (piece >= 1 << (t.cut + t.row_cut)) return false;
         out.cut = t.cut;
+        row_cut = t.row_cut;
         height = t.height;
         if (t.row_cut > 0) {
             row_begin += (piece & ((1 << t.row_cut) - 1)) * height;
@@ -308,6 +313,16 @@ __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N
     // longer launches (32768 tokens, 8 experts: 520 -> 535 us) and not where the weights of experts of one row tile bound the
     // launch (16 experts, 2500 tokens: 87.0 -> 89.7): non-temporal stores.
     out.through = __builtin_amdgcn_readfirstlane(e_rt >= 2 && p.total_big + p.total_small <= 2 * kComputeUnits ? 1 : 0) != 0;
+    // Where the reduction begins.  Rows a power of two bytes apart put the same columns of all rows on few memory channels, and compute
+    // units that walk the reduction in step all ask these, so the XCDs begin at different places.  The tiles of one XCD, which share
+    // panels in their L2, stay in step - but where much weight is streamed for experts of one or two row tiles: their activations fit the L2 as
+    // a whole, and every column tile has a place of its own (its row tiles and pieces, which share weights, stay together).  1200 tokens,
+    // 16 experts of 4096 x 16384 858 -> 747 us, 4000 1361 -> 1221; two row tiles: 4000 of 8 1064 -> 1042, 5000 of 16 of 2048 x 8192 447 -> 441;
+    // less weight: 2500 of 8 of 1024 x 4096 61.5 and 62.2.
+    out.turn = xcd * kUnitsPerXcd;
+    if (STREAMS && e_rt <= 2) out.turn += col_tile % kUnitsPerXcd;
+    out.turn = __builtin_amdgcn_readfirstlane(out.turn);
+    out.once = STREAMS && __builtin_amdgcn_readfirstlane(e_rt == 1 && row_cut == 0 && height <= kTileRows ? 1 : 0) != 0;
     out.hid_shift = __builtin_amdgcn_readfirstlane(kHiddenRowBlock * e - (e_lo & (kHiddenRowBlock - 1)));
     return true;
 }
@@ -357,7 +372,7 @@ __host__ __device__ constexpr int wave_columns(int H, int NT, int waves)
     return best;
 }
 
-template <int H, int NT, int WAVES_>
+template <int H, int NT, int WAVES_, bool ONCE>
 struct GemmTile {
     static constexpr int RB = kKTile * 2;           // bytes per tile row
     static constexpr int WAVES = WAVES_;
@@ -394,7 +409,12 @@ struct GemmTile {
     __device__ __forceinline__ int group_a(int i) const { return GA % WAVES == 0 ? i * WAVES + wave : min(i * WAVES + wave, GA - 1); }
     __device__ __forceinline__ int group_w(int i) const { return GW % WAVES == 0 ? i * WAVES + wave : min(i * WAVES + wave, GW - 1); }
     __device__ __forceinline__ void issue_a(uint32_t st, int i) { lds_dma_16B(act_b, off_a[i], smem_addr + st + group_a(i) * 1024); }
-    __device__ __forceinline__ void issue_w(uint32_t st, int i) { lds_dma_16B(wgt_b, off_w[i], smem_addr + SA * A_BYTES + st + group_w(i) * 1024); }
+    __device__ __forceinline__ void issue_w(uint32_t st, int i)
+    {
+        const uint32_t at = smem_addr + SA * A_BYTES + st + group_w(i) * 1024;
+        if constexpr (ONCE) lds_dma_16B_stream(wgt_b, off_w[i], at);
+        else lds_dma_16B(wgt_b, off_w[i], at);
+    }
 
     // On to the next K tile of the reduction; behind the last one follows the first (see gemm_tile).
     // (A loop of few MFMAs is bound by the issue of its other instructions, so the way back is kept and rings of equal depth share a
@@ -526,12 +546,15 @@ struct GemmTile {
     }
 };
 
-template <int H, int NT, int WAVES, int EPI>
+// ONCE: the weights are read by this workgroup alone and loaded with the streaming hint, which leaves the L2 to the activations.  Tiles that share
+// a panel lose by it (8 experts of 1024 x 4096, 8192 tokens 143.7 -> 159.7 us), and so do weights that lie in the memory-side cache from the call
+// before, which such loads do not keep there (see weights_are_streamed).
+template <int H, int NT, int WAVES, int EPI, bool ONCE>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const bf16_t* __restrict__ wexp, const bf16_t* __restrict__ bias_e,
-                                          int row_begin, int row_end, int hid_shift, bool through, int n0, int K, int N, bf16_t* __restrict__ out,
+                                          int row_begin, int row_end, int hid_shift, bool through, int turn, int n0, int K, int N, bf16_t* __restrict__ out,
                                           unsigned char* smem, const RowMap& map)
 {
-    typedef GemmTile<H, NT, WAVES> G;
+    typedef GemmTile<H, NT, WAVES, ONCE> G;
     constexpr int RB = G::RB, SA = G::SA, SB = G::SB, TM = G::TM, TN = G::TN, LA = G::LA, LW = G::LW;
     G g;
     const int lane = lane_id();
@@ -543,10 +566,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     constexpr bool HIDDEN_ACT = EPI == kEpiNone || EPI == kEpiKeepSorted, HIDDEN_OUT = !HIDDEN_ACT;  // the first contraction writes what the second reads
     const int r8 = lane >> 3, c8 = lane & 7;
     const int nk = K / kKTile;
-    // The XCDs begin at different places of the reduction: rows a power of two bytes apart put the same columns of all rows
-    // on few memory channels, and compute units that walk the reduction in step all ask these.  (The tiles of one XCD, which
-    // share panels in their L2, stay in step.)
-    const int k0 = static_cast<int>(static_cast<unsigned>(blockIdx.x % kXcdCount) * static_cast<unsigned>(nk) / kXcdCount);
+    const int k0 = static_cast<int>(static_cast<unsigned>(turn) * static_cast<unsigned>(nk) / kComputeUnits);
     g.nk = nk;
     g.a_left = nk - 1 - k0;
     g.w_left = nk - 1 - k0;
@@ -773,7 +793,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     else finish(std::false_type());
 }
 
-template <int NT, int WAVES, int EPI>
+template <int NT, int WAVES, int EPI, bool STREAMS>
 __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(const bf16_t* __restrict__ act,     // [A,K]
                                                                             const int32_t* __restrict__ offsets,
                                                                             const bf16_t* __restrict__ weight,  // [E_local,N,K]
@@ -793,7 +813,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     if (map.unrouted != nullptr && wave_read_lane(range.hi, E_local - 1) < map.n_unrouted)
         clear_unrouted_rows<false, false>(map.unrouted, map.n_unrouted, reinterpret_cast<uint4*>(out), N / 8, WAVES);
     Tile2D tile;
-    if (!locate_tile(range, NT, N, static_cast<int>(blockIdx.x), map, tile)) return;
+    if (!locate_tile<STREAMS>(range, NT, N, static_cast<int>(blockIdx.x), map, tile)) return;
     timeline_stamp(map, 1);
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap) {
         unsigned hw = 0, xcc = 0;
@@ -809,29 +829,37 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     }
     const bf16_t* wexp = weight + static_cast<size_t>(tile.expert) * N * K;
     const bf16_t* bias_e = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
-#define EXF_TILE(H, CUT) \
-    gemm_tile<H, (NT >> CUT), WAVES, EPI>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.through, tile.n0, K, N, out, smem, map)
-#define EXF_CASE(H, CUT)                                         \
-    case (CUT) * 16 + (H) / kQuantum:                            \
-        if constexpr (has_instance(NT, H, CUT)) EXF_TILE(H, CUT); \
+#define EXF_CASE(H, CUT, ONCE)                                                                                                                        \
+    case (CUT) * 16 + (H) / kQuantum:                                                                                                                 \
+        if constexpr (has_instance(NT, H, CUT) && (!(ONCE) || H <= kTileRows))                                                                        \
+            gemm_tile<H, (NT >> CUT), WAVES, EPI, ONCE>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.through, tile.turn,     \
+                                                        tile.n0, K, N, out, smem, map);                                                               \
         break
-#define EXF_CASES(CUT)  \
-    EXF_CASE(64, CUT);  \
-    EXF_CASE(96, CUT);  \
-    EXF_CASE(128, CUT); \
-    EXF_CASE(160, CUT); \
-    EXF_CASE(192, CUT); \
-    EXF_CASE(256, CUT); \
-    EXF_CASE(288, CUT); \
-    EXF_CASE(320, CUT)
-    switch (tile.cut * 16 + tile.height / kQuantum) {
-        EXF_CASES(0);
-        EXF_CASES(1);
-        EXF_CASES(2);
+#define EXF_CASES(CUT, ONCE)  \
+    EXF_CASE(64, CUT, ONCE);  \
+    EXF_CASE(96, CUT, ONCE);  \
+    EXF_CASE(128, CUT, ONCE); \
+    EXF_CASE(160, CUT, ONCE); \
+    EXF_CASE(192, CUT, ONCE); \
+    EXF_CASE(256, CUT, ONCE); \
+    EXF_CASE(288, CUT, ONCE); \
+    EXF_CASE(320, CUT, ONCE)
+    const int instance = tile.cut * 16 + tile.height / kQuantum;
+    if (STREAMS && tile.once) {
+        switch (instance) {
+            EXF_CASES(0, STREAMS);
+            EXF_CASES(1, STREAMS);
+            EXF_CASES(2, STREAMS);
+        }
+    } else {
+        switch (instance) {
+            EXF_CASES(0, false);
+            EXF_CASES(1, false);
+            EXF_CASES(2, false);
+        }
     }
 #undef EXF_CASES
 #undef EXF_CASE
-#undef EXF_TILE
     timeline_stamp(map, 4);
 }
 
@@ -847,7 +875,7 @@ constexpr int gemm_lds_bytes()
     return most;
 }
 
-template <int NT, int WAVES, int EPI>
+template <int NT, int WAVES, int EPI, bool STREAMS = false>
 static int launch_bf16_as(const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N, int E_local,
                           void* out, hipStream_t stream, const RowMap& map)
 {
@@ -858,7 +886,7 @@ static int launch_bf16_as(const void* act, const int32_t* offsets, const void* w
     const int64_t items = (A / kTileRows + (A < E_local ? A : E_local)) * n_tiles;
     const int64_t grid = (items / kXcdCount + 2 + kUnitsPerXcd) * kXcdCount;
     if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: too many tiles");
-    auto kern = grouped_gemm_bf16_kernel<NT, WAVES, EPI>;
+    auto kern = grouped_gemm_bf16_kernel<NT, WAVES, EPI, STREAMS>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(WAVES * kWave), lds, stream, static_cast<const bf16_t*>(act), offsets,
@@ -870,5 +898,10 @@ static int launch_bf16_as(const void* act, const int32_t* offsets, const void* w
 // The second contraction that leaves its sorted rows besides (ffn_keep.hip): `wide`, 256 columns a tile instead of 128.
 int launch_kept_contraction(bool wide, const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N,
                             int E_local, void* out, hipStream_t stream, const RowMap& map);
+// Contractions whose weights are streamed where one row tile reads them (ffn_once.hip, ffn_once_second.hip); epi: kEpiGeluErf or kEpiGeluTanh.
+int launch_once_first(int epi, const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N, int E_local,
+                      void* out, hipStream_t stream, const RowMap& map);
+int launch_once_second(bool wide, const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N, int E_local,
+                       void* out, hipStream_t stream, const RowMap& map);
 
 }  // namespace exf

@@ -7,6 +7,7 @@ import oracle as O
 import synth_inputs as syn
 import test_gpu_parity as P
 import test_placement_search as Q
+from helpers import sample_rows
 from paper_2401_08383_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -201,6 +202,23 @@ def test_grouped_ffn_cut_tiles(oracle, counts, d, f):
 def test_grouped_ffn_around_two_rounds(oracle, counts):
     """512 tiles of the first contraction and a few more: hidden rows written through, by some experts only, by none."""
     P._ffn_case(oracle, "bf16", counts, 64, 4096, 0, True, seed=1790)
+
+
+# the least weights that are streamed: whole and cut tiles of every height that one workgroup reads, experts of several tiles and of none beside
+# them, short and long reductions (16 and 128 K tiles, the column tiles of an XCD begin at different ones)
+@pytest.mark.parametrize("counts,d,f", [
+    ([1, 63, 64, 65, 96, 97, 128, 129, 160, 192, 193, 255, 256, 257, 288, 289, 700, 0] + [30] * 46, 1024, 1024),
+    ([40, 0, 64, 65, 128, 129, 192, 193, 256, 300, 513, 33, 1, 0, 70, 90], 512, 8192), ([70, 33, 250, 140], 2048, 8192)])
+def test_grouped_ffn_streamed_weights(oracle, counts, d, f):
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    P._ffn_case(oracle, "bf16", counts, d, f, 0, False, seed=1795, rows=sample_rows(offsets, 1, 1796))
+
+
+@pytest.mark.parametrize("T,k,E,E_local,routing", [(3000, 1, 64, 64, "gate"), (2500, 2, 64, 64, "ids"), (33000, 1, 64, 64, "gate")])
+def test_streamed_weights_of_a_layer(T, k, E, E_local, routing):
+    """The layer and its calls, fused and not; 256 columns a tile in the second contraction (the last)."""
+    _layer_against_calls(T, k, E, E_local, "bf16", True, routing, 1024, 1024)
+    _layer_against_calls(T, k, E, E_local, "bf16", False, routing, 1024, 1024, ("x_sorted", "y_sorted"))
 
 
 @pytest.mark.parametrize("T,d,f,E,k", [(700, 64, 192, 3, 1), (1500, 192, 320, 5, 2), (900, 320, 1088, 2, 2)])
