@@ -75,8 +75,11 @@ __device__ __forceinline__ void timeline_stamp(const RowMap& map, int slot)
 // The rows of an expert become q = rows / 256 tiles, and what is left over is spread over them in quanta of 32 rows: a tile
 // of 288 rows costs an eighth more, one more tile a whole one.  A tile takes at most `most` quanta; where the
 // remainder is larger there is one tile more, all of one height.  most = 1, or 2 where the launch then has fewer rounds of
-// tiles (see plan_tiles).  An expert of at most 128 rows has one small tile.  Heights of a tile: 64 and 128 (small), 192,
-// 256, 288, 320; of a piece of one (see locate_tile) 64, 96, 128 and 160 besides.
+// tiles (see plan_tiles).  An expert of at most 128 rows has one small tile.  Heights of a tile: 64 and 128 (small), 192, 224,
+// 256, 288, 320; of a piece of one (see locate_tile) 64, 96, 128 and 160 besides.  224 (`between`) in launches of
+// more tiles than half the compute units, where tiles are whole and the tallest one is the time: 3000 tokens, 16 experts of 1024 x 4096 85.5 us in
+// 256 rows, 82.7 in 224; 3360, 8 of 2048 x 8192 247 and 234; 12000, 60 of 2048 x 8192 999 and 979; 1531 top-2, 16 of 1024 x 4096 96.6 and 95.8.  In
+// fewer tiles, which are cut, the second one of two ends in a piece of a few rows more: 420, one of 2048 x 8192 57.7 and 59.5.
 constexpr int kTileRows = 256;
 constexpr int kQuantum = 32;
 constexpr int kSmallRows = 128;
@@ -84,7 +87,7 @@ constexpr int kSmallRows = 128;
 struct TileRows {
     int tiles, height, extra;  // row tiles, their base height, quanta spread over them
 };
-__device__ __forceinline__ TileRows cut_rows(int cnt, int most)
+__device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool between)
 {
     TileRows t;
     const int q = cnt / kTileRows, r = cnt - q * kTileRows;
@@ -96,7 +99,7 @@ __device__ __forceinline__ TileRows cut_rows(int cnt, int most)
         t.extra = 0;
         // (q is at most 7 here)
         const int even = q == 0 ? cnt : (q == 1 ? (cnt + 1) / 2 : (q == 2 ? (cnt + 2) / 3 : kTileRows));
-        t.height = even <= 64 && q == 0 ? 64 : (even <= kSmallRows && q == 0 ? kSmallRows : (even <= 192 ? 192 : kTileRows));
+        t.height = even <= 64 && q == 0 ? 64 : (even <= kSmallRows && q == 0 ? kSmallRows : (even <= 192 ? 192 : (even <= 224 && between ? 224 : kTileRows)));
     }
     return t;
 }
@@ -125,7 +128,7 @@ __host__ __device__ constexpr TileCut cut_tile(int NT, int height, int rows, int
 __host__ __device__ constexpr bool has_instance(int NT, int height, int cut)
 {
     const bool wide = NT == 256;
-    if (cut == 0) return height == 64 || (height == 96 && !wide) || height == 128 || height == 160 || height == 192 || height == 256 || height == 288 || height == 320;
+    if (cut == 0) return height == 64 || (height == 96 && !wide) || height == 128 || height == 160 || height == 192 || height == 224 || height == 256 || height == 288 || height == 320;
     if (cut == 1) return height == 64 || height == 96 || height == 128 || height == 160 || (wide && (height == 192 || height == 256 || height == 320));
     return cut == 2 && (height == 64 || (wide && height == 128));
 }
@@ -133,13 +136,14 @@ __host__ __device__ constexpr int instance_height(int NT, int height, int cut)
 {
     if (height < 64) height = 64;
     if (NT == 256 && height == 96 && cut != 1) height = 128;
+    if (height == 224 && cut == 1) height = 256;
     if (height == 288 && cut == 1) height = 320;
     return height;
 }
 // Every tile, whole or in pieces, has all its rows in pieces that the kernel has an instance for (it writes nothing otherwise).
 constexpr bool tiles_are_covered(int NT)
 {
-    const int heights[] = {64, 128, 192, 256, 288, 320};
+    const int heights[] = {64, 128, 192, 224, 256, 288, 320};
     for (int height : heights)
         for (int rows = 1; rows <= height; rows += rows % kQuantum == 1 ? kQuantum - 2 : 1)  // 1, 31, 32, 33, 63, ..
             for (int pieces = 0; pieces <= 3; ++pieces) {
@@ -195,7 +199,7 @@ __device__ __forceinline__ TilePlan plan_tiles(const RowRange& range, int n_tile
     }
     // one quantum per tile, unless two make the launch a round of tiles shorter
     const bool small = cnt <= kSmallRows;
-    const int lean = cnt > 0 ? cut_rows(cnt, 1).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2).tiles : 0;
+    const int lean = cnt > 0 ? cut_rows(cnt, 1, false).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2, false).tiles : 0;
     const int lean_incl = wave_inclusive_scan(small ? 0 : lean * n_tiles), tall_incl = wave_inclusive_scan(small ? 0 : tall * n_tiles);
     p.small_incl = wave_inclusive_scan(small ? lean * n_tiles : 0);
     const int lean_total = wave_read_lane(lean_incl, kWave - 1), tall_total = wave_read_lane(tall_incl, kWave - 1);
@@ -280,7 +284,7 @@ __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N
         col_tile = static_cast<int>(c);
         row_tile = blocked_rows + static_cast<int>(rr - c * rows_left);
     }
-    const TileRows t = cut_rows(e_hi - e_lo, p.most);
+    const TileRows t = cut_rows(e_hi - e_lo, p.most, p.total_big + p.total_small > kComputeUnits / 2);
     // quanta: every tile takes extra / tiles, the first extra % tiles one more
     const int each = t.extra >= 2 * t.tiles ? 2 : (t.extra >= t.tiles ? 1 : 0), more = t.extra - each * t.tiles;
     const int begin_row = e_lo + row_tile * t.height + (row_tile * each + min(row_tile, more)) * kQuantum;
@@ -841,6 +845,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
     EXF_CASE(128, CUT, ONCE); \
     EXF_CASE(160, CUT, ONCE); \
     EXF_CASE(192, CUT, ONCE); \
+    EXF_CASE(224, CUT, ONCE); \
     EXF_CASE(256, CUT, ONCE); \
     EXF_CASE(288, CUT, ONCE); \
     EXF_CASE(320, CUT, ONCE)
@@ -868,7 +873,7 @@ template <int NT>
 constexpr int gemm_lds_bytes()
 {
     int most = 0;
-    const int heights[] = {64, 96, 128, 160, 192, kTileRows, kTileRows + kQuantum, kTileRows + 2 * kQuantum};
+    const int heights[] = {64, 96, 128, 160, 192, 224, kTileRows, kTileRows + kQuantum, kTileRows + 2 * kQuantum};
     for (int h : heights) most = tile_ring_bytes(h, NT) > most ? tile_ring_bytes(h, NT) : most;
     for (int h : heights) most = tile_ring_bytes(h, NT / 2) > most ? tile_ring_bytes(h, NT / 2) : most;
     for (int h : heights) most = tile_ring_bytes(h, NT / 4) > most ? tile_ring_bytes(h, NT / 4) : most;

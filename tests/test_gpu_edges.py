@@ -198,6 +198,12 @@ def test_grouped_ffn_cut_tiles(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1770 + d)
 
 
+@pytest.mark.parametrize("counts,d,f", [([192, 193, 224, 225, 200] * 3, 64, 3328), ([193, 224, 223, 210] * 4, 1664, 64), ([385, 448, 447, 449, 193] * 4 + [200], 4096, 64)])
+def test_grouped_ffn_tiles_of_224_rows(oracle, counts, d, f):
+    """Whole tiles between 192 and 256 rows: in the first contraction, in the second one of 128 columns and of 256, one and two to an expert."""
+    P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1790 + f)
+
+
 @pytest.mark.parametrize("counts", [[4096, 4096], [4095, 0, 200, 4097], [4096, 4100, 300]])
 def test_grouped_ffn_around_two_rounds(oracle, counts):
     """512 tiles of the first contraction and a few more: hidden rows written through, by some experts only, by none."""
