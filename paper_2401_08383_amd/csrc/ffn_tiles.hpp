@@ -76,10 +76,14 @@ __device__ __forceinline__ void timeline_stamp(const RowMap& map, int slot)
 // of 288 rows costs an eighth more, one more tile a whole one.  A tile takes at most `most` quanta; where the
 // remainder is larger there is one tile more, all of one height.  most = 1, or 2 where the launch then has fewer rounds of
 // tiles (see plan_tiles).  An expert of at most 128 rows has one small tile.  Heights of a tile: 64 and 128 (small), 192, 224,
-// 256, 288, 320; of a piece of one (see locate_tile) 64, 96, 128 and 160 besides.  224 (`between`) in launches of
-// more tiles than half the compute units, where tiles are whole and the tallest one is the time: 3000 tokens, 16 experts of 1024 x 4096 85.5 us in
-// 256 rows, 82.7 in 224; 3360, 8 of 2048 x 8192 247 and 234; 12000, 60 of 2048 x 8192 999 and 979; 1531 top-2, 16 of 1024 x 4096 96.6 and 95.8.  In
-// fewer tiles, which are cut, the second one of two ends in a piece of a few rows more: 420, one of 2048 x 8192 57.7 and 59.5.
+// 256, 288, 320; of a piece of one (see locate_tile) 64, 96, 128 and 160 besides.  160 instead of 192 and
+// 224 instead of 256 (`by160`, `by224`) in launches of more tiles than half the compute units, whose only round's tiles are whole: the tallest one is the
+// time.  160 where no expert of a single round has more rows, or in several rounds.  Experts of up to 160 rows in 192 and in 160: 1000 tokens, 8 experts of
+// 2048 x 8192 131.9 -> 122.9 us, 1100, 8 of 1536 x 6144 97.4 -> 92.0, 2200, 16 of 2048 x 8192 236 -> 222, 8600, 60 of 2048 x 8192 867 -> 839; with a
+// taller one among them 1150, 8 of 2048 x 8192 132.5 and 134.8.  Up to 224 rows in 256 and in 224: 3000, 16 of 1024 x 4096 85.5 -> 82.7; 3360, 8 of
+// 2048 x 8192 247 -> 234; 12000, 60 of 2048 x 8192 999 -> 979; 1531 top-2, 16 of 1024 x 4096 96.6 -> 95.8.  In up to half as many tiles as compute
+// units, which are cut, the second one of two ends in a piece of a few rows more: 420, one of 2048 x 8192 57.7 and 59.5.  (The exact rule, no tile of the
+// only round taller, takes the heights of all experts in front of the look-up: 0.4 to 2 us of 44 to 100.)
 constexpr int kTileRows = 256;
 constexpr int kQuantum = 32;
 constexpr int kSmallRows = 128;
@@ -87,7 +91,7 @@ constexpr int kSmallRows = 128;
 struct TileRows {
     int tiles, height, extra;  // row tiles, their base height, quanta spread over them
 };
-__device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool between)
+__device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool by160 = true, bool by224 = true)
 {
     TileRows t;
     const int q = cnt / kTileRows, r = cnt - q * kTileRows;
@@ -99,7 +103,7 @@ __device__ __forceinline__ TileRows cut_rows(int cnt, int most, bool between)
         t.extra = 0;
         // (q is at most 7 here)
         const int even = q == 0 ? cnt : (q == 1 ? (cnt + 1) / 2 : (q == 2 ? (cnt + 2) / 3 : kTileRows));
-        t.height = even <= 64 && q == 0 ? 64 : (even <= kSmallRows && q == 0 ? kSmallRows : (even <= 192 ? 192 : (even <= 224 && between ? 224 : kTileRows)));
+        t.height = even <= 64 && q == 0 ? 64 : (even <= kSmallRows && q == 0 ? kSmallRows : (even <= 160 && by160 ? 160 : (even <= 192 ? 192 : (even <= 224 && by224 ? 224 : kTileRows))));
     }
     return t;
 }
@@ -143,7 +147,7 @@ __host__ __device__ constexpr int instance_height(int NT, int height, int cut)
 // Every tile, whole or in pieces, has all its rows in pieces that the kernel has an instance for (it writes nothing otherwise).
 constexpr bool tiles_are_covered(int NT)
 {
-    const int heights[] = {64, 128, 192, 224, 256, 288, 320};
+    const int heights[] = {64, 128, 160, 192, 224, 256, 288, 320};
     for (int height : heights)
         for (int rows = 1; rows <= height; rows += rows % kQuantum == 1 ? kQuantum - 2 : 1)  // 1, 31, 32, 33, 63, ..
             for (int pieces = 0; pieces <= 3; ++pieces) {
@@ -199,7 +203,7 @@ __device__ __forceinline__ TilePlan plan_tiles(const RowRange& range, int n_tile
     }
     // one quantum per tile, unless two make the launch a round of tiles shorter
     const bool small = cnt <= kSmallRows;
-    const int lean = cnt > 0 ? cut_rows(cnt, 1, false).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2, false).tiles : 0;
+    const int lean = cnt > 0 ? cut_rows(cnt, 1).tiles : 0, tall = cnt > 0 ? cut_rows(cnt, 2).tiles : 0;
     const int lean_incl = wave_inclusive_scan(small ? 0 : lean * n_tiles), tall_incl = wave_inclusive_scan(small ? 0 : tall * n_tiles);
     p.small_incl = wave_inclusive_scan(small ? lean * n_tiles : 0);
     const int lean_total = wave_read_lane(lean_incl, kWave - 1), tall_total = wave_read_lane(tall_incl, kWave - 1);
@@ -284,7 +288,9 @@ __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N
         col_tile = static_cast<int>(c);
         row_tile = blocked_rows + static_cast<int>(rr - c * rows_left);
     }
-    const TileRows t = cut_rows(e_hi - e_lo, p.most, p.total_big + p.total_small > kComputeUnits / 2);
+    const int tiles = p.total_big + p.total_small;
+    const bool by224 = tiles > kComputeUnits / 2, by160 = tiles > kComputeUnits || (by224 && __ballot(p.hi - p.lo > 160) == 0ull);
+    const TileRows t = cut_rows(e_hi - e_lo, p.most, by160, by224);
     // quanta: every tile takes extra / tiles, the first extra % tiles one more
     const int each = t.extra >= 2 * t.tiles ? 2 : (t.extra >= t.tiles ? 1 : 0), more = t.extra - each * t.tiles;
     const int begin_row = e_lo + row_tile * t.height + (row_tile * each + min(row_tile, more)) * kQuantum;

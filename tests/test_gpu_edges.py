@@ -198,9 +198,12 @@ def test_grouped_ffn_cut_tiles(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1770 + d)
 
 
-@pytest.mark.parametrize("counts,d,f", [([192, 193, 224, 225, 200] * 3, 64, 3328), ([193, 224, 223, 210] * 4, 1664, 64), ([385, 448, 447, 449, 193] * 4 + [200], 4096, 64)])
-def test_grouped_ffn_tiles_of_224_rows(oracle, counts, d, f):
-    """Whole tiles between 192 and 256 rows: in the first contraction, in the second one of 128 columns and of 256, one and two to an expert."""
+@pytest.mark.parametrize("counts,d,f", [([192, 193, 224, 225, 200] * 3, 64, 3328), ([193, 224, 223, 210] * 4, 1664, 64), ([385, 448, 447, 449, 193] * 4 + [200], 4096, 64),
+                                        ([129, 160, 159, 140, 100] * 3, 64, 3328), ([129, 160, 161, 130] * 5, 64, 3392), ([129, 160, 131, 150] * 4, 1664, 64),
+                                        ([161, 192, 129, 224] * 4, 64, 2624), ([289, 320, 310, 129, 160] * 4 + [2208], 4096, 64)])
+def test_grouped_ffn_tiles_between(oracle, counts, d, f):
+    """Whole tiles between 128 and 192, 192 and 256 rows: in the first contraction, in the second one of 128 columns and of 256, one and two to an
+    expert; with taller ones in the launch, of one round and of more."""
     P._ffn_case(oracle, "bf16", counts, d, f, 0, True, seed=1790 + f)
 
 
