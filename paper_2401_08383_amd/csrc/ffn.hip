@@ -40,6 +40,27 @@ static int launch_first_contraction(const void* act, const int32_t* offsets, con
     return launch_bf16_as<256, 8, kEpiGeluTanh>(act, offsets, weight, bias, A, K, N, E_local, out, stream, map);
 }
 
+// In tiles the first contraction sorts where the sorted rows are wanted besides, so that the launch that goes had rows to move, where all experts are resident (few
+// rows to move otherwise) and where their tiles are one round (every round counts again).  Separate calls, with a dispatch of its own and without, us:
+//   one round: 1531 tokens top-2, 16 experts of 1024 x 4096 96.1 -> 93.9, 2000 top-2, 8 of 576 x 2304 62.5 -> 57.2, 4000, 8 of 1024 x 4096 91.7 -> 85.1,
+//     2048 top-2, 8 of 4096 x 4096 287 -> 271, 300, 4 of 1024 x 4096 36.8 -> 35.9, 1000, 4 of 512 x 2048 31.3 -> 29.9
+//   more: 2000 top-2, 32 of 1024 x 4096 140 and 145, 4000, 4 of 4096 x 16384 920 and 927, 850 top-2, 27 of 3072 x 8512 522 and 542
+//   a share of the experts: 3900 tokens, 16 of 64 of 960 x 3840 99.8 and 105.2, 4000, 8 of 64 of 1024 x 4096 46.9 and 47.7
+//   no sorted rows (fused): 4000, 8 of 1024 x 4096 79.8 and 82.1, 300, 4 of them 34.6 and 34.8
+bool routed_tiles_fit(int64_t A, int d, int f, int E, int E_local, int dt)
+{
+    if (dt != EXF_BF16 || A <= 0 || A > kRoutedTilesMax || E_local != E || stream_path_fits(A, d, f, E_local, dt)) return false;
+    constexpr int kRows = kTileRows + kQuantum;
+    return (A + static_cast<int64_t>(E) * kRows - 1) / (static_cast<int64_t>(E) * kRows) * E * ((f + 255) / 256) <= kComputeUnits;
+}
+
+static int launch_routed_contraction(const void* act, const void* weight, int64_t A, int K, int N, int E_local, int epi, void* out, hipStream_t stream,
+                                     const TileRouting& route)
+{
+    if (weights_are_streamed(A, K, N, E_local)) return launch_routed_once_first(epi, act, weight, A, K, N, E_local, out, stream, route);
+    return launch_routed_first(epi, act, weight, A, K, N, E_local, out, stream, route);
+}
+
 // The second contraction has few output columns (N = d).  With 256x128 tiles it offers twice as many
 // tiles, which a short batch needs to fill the chip; the 256x256 tile of the first contraction moves
 // a third less operand data per flop through the L2s and is taken once it, too, gives every compute
@@ -277,7 +298,14 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
         first.E_local = second.E_local = E_local;
         rc = launch_stream_pair(first, second, dt, s);
     } else {
-        rc = launch_first_contraction(x, expert_offsets, w1, b1, A, d, f, E_local, epi, hidden, s, gather);
+        if (routing != nullptr) {
+            const TileRouting route{routing->topk_idx,      routing->expert_map,     routing->src_of_sorted, routing->sorted_of_src,
+                                    routing->expert_counts, routing->expert_offsets, static_cast<bf16_t*>(routing->x_sorted), routing->E, k};
+            if (k == 1) scatter.sorted_out = static_cast<bf16_t*>(routing->y_sorted);
+            rc = launch_routed_contraction(x, w1, A, d, f, E_local, epi, hidden, s, route);
+        } else {
+            rc = launch_first_contraction(x, expert_offsets, w1, b1, A, d, f, E_local, epi, hidden, s, gather);
+        }
         if (rc == EXF_OK) rc = launch_second_contraction(hidden, expert_offsets, w2, b2, A, f, d, E_local, second_out, s, scatter);
     }
     if (rc != EXF_OK) return rc;

@@ -114,6 +114,7 @@ struct StreamGemm {
 constexpr unsigned long long kNoRow = ~0ull;
 constexpr int kFewAssignments = 64;
 constexpr int kInlineDispatchMax = 1024;  // assignments a workgroup sorts for itself
+constexpr int kRoutedTilesMax = 4096;     // ... in a contraction in tiles
 // Is the path taken for A rows of `dt` spread over E_local experts?
 bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
@@ -148,6 +149,8 @@ inline bool routed_path_fits(int64_t A, int d, int f, int E_local, int dt)
 {
     return A > 0 && A <= kInlineDispatchMax && stream_path_fits(A, d, f, E_local, dt);
 }
+// The same in tiles (bf16, separate calls), with all E experts resident.
+bool routed_tiles_fit(int64_t A, int d, int f, int E, int E_local, int dt);
 // Is a layer on the routed path gated by its first contraction?  routed: its experts are given, the gate's ids are only stored.
 bool gate_joins_layer(int64_t T, int d, int E, int dt, bool routed);
 // The expert FFN of a top-1 layer and its combine, moe_expert_ffn and moe_combine in two launches: the same results.

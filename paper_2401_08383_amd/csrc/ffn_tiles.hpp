@@ -29,6 +29,7 @@ namespace exf {
 
 constexpr int kLdsBytes = 160 * 1024;  // LDS of a compute unit
 constexpr int kComputeUnits = 256;
+constexpr int kTallestTile = 320;      // rows
 constexpr int kKTile = 64;             // reduction elements of a stage: 128 bytes of every row
 
 // Optional row indirections of the bf16 grouped GEMM; all members null / zero = sorted rows on both sides.
@@ -70,6 +71,23 @@ __device__ __forceinline__ void timeline_stamp(const RowMap& map, int slot)
     if (map.timeline != nullptr && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < map.timeline_cap)
         map.timeline[static_cast<size_t>(blockIdx.x) * 8 + slot] = wall_clock64();
 }
+
+// A first contraction that is the dispatch as well: every workgroup counts all assignments, finds its tile by that and collects the tile's
+// rows; the tiles of the first output columns write the maps, and every tile its share of the columns of the sorted rows.
+struct TileRouting {
+    const int32_t* topk_idx;    // [A]
+    const int32_t* expert_map;  // [E] or null
+    int32_t *src_of_sorted, *sorted_of_src, *expert_counts, *expert_offsets;
+    bf16_t* sorted_act;         // [A,K]
+    int E, k;
+};
+constexpr int kRoutedRounds = kRoutedTilesMax / (8 * kWave);  // assignments of a thread
+constexpr int kRoutedCopies = 8;  // of a counter, so that few experts do not meet at one address
+struct RoutedSort {
+    uint32_t count[EXF_MAX_EXPERTS][kRoutedCopies];
+    int wave_rows[8];
+    int list[kTallestTile];  // assignments of the tile's rows
+};
 
 // ---------------------------------------------------------------------------- row tiles
 // The rows of an expert become q = rows / 256 tiles, and what is left over is spread over them in quanta of 32 rows: a tile
@@ -190,6 +208,70 @@ __device__ __forceinline__ RowRange row_range(const int32_t* __restrict__ offset
         r.hi = min(max(offsets[lane + 1], r.lo), max_rows);
     }
     return r;
+}
+
+// The same from the assignments.  e[u]: local expert of assignment (wave * rounds + u) * 64 + lane (-1: none); wavefronts have consecutive ones.
+__device__ __forceinline__ RowRange count_rows(const TileRouting& r, int E_local, int A, int rounds, int (&e)[kRoutedRounds], RoutedSort& d)
+{
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int map = r.expert_map != nullptr ? r.expert_map[min(lane, r.E - 1)] : lane;  // lane = expert
+    const int first = wave * rounds * kWave + lane;
+#pragma unroll
+    for (int u = 0; u < kRoutedRounds; ++u) e[u] = u < rounds ? r.topk_idx[min(first + u * kWave, A - 1)] : -1;
+    reinterpret_cast<uint32_t*>(d.count)[threadIdx.x] = 0u;  // (as many counters as threads)
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRoutedRounds; ++u) {
+        const bool ok = u < rounds && first + u * kWave < A && e[u] >= 0 && e[u] < r.E;
+        const int m = r.expert_map != nullptr ? __shfl(map, ok ? e[u] : 0, kWave) : e[u];
+        e[u] = ok && m >= 0 && m < E_local ? m : -1;
+        if (e[u] >= 0) atomicAdd(&d.count[e[u]][lane % kRoutedCopies], 1u);
+    }
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int c = 0; c < kRoutedCopies; ++c) total += d.count[lane][c];  // (beyond E_local: zero)
+    RowRange range;
+    range.hi = wave_inclusive_scan(static_cast<int>(total));
+    range.lo = range.hi - static_cast<int>(total);
+    if (blockIdx.x == 0) {
+        if (wave == 0 && lane < E_local) {
+            r.expert_counts[lane] = static_cast<int>(total);
+            r.expert_offsets[lane] = range.lo;
+            if (lane == E_local - 1) r.expert_offsets[E_local] = range.hi;
+        }
+#pragma unroll
+        for (int u = 0; u < kRoutedRounds; ++u)
+            if (u < rounds && first + u * kWave < A && e[u] < 0) r.sorted_of_src[first + u * kWave] = -1;
+    }
+    return range;
+}
+
+// Assignments of sorted rows [row_begin, row_end) of `expert`, whose rows begin at `lo`, into d.list (behind the last barrier).
+__device__ __forceinline__ void collect_rows(int expert, int lo, int row_begin, int row_end, int rounds, const int (&e)[kRoutedRounds], RoutedSort& d)
+{
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    unsigned long long like[kRoutedRounds];
+    int mine = 0;
+#pragma unroll
+    for (int u = 0; u < kRoutedRounds; ++u) {
+        like[u] = __ballot(e[u] == expert);
+        mine += __popcll(like[u]);
+    }
+    if (lane == 0) d.wave_rows[wave] = mine;
+    __syncthreads();
+    int at = lo - row_begin;
+#pragma unroll
+    for (int w = 0; w < 7; ++w) at += w < wave ? d.wave_rows[w] : 0;
+#pragma unroll
+    for (int u = 0; u < kRoutedRounds; ++u) {
+        const int row = at + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(like[u] >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(like[u]), 0u)));
+        if (e[u] == expert && row >= 0 && row < row_end - row_begin) d.list[row] = (wave * rounds + u) * kWave + lane;
+        at += __popcll(like[u]);
+    }
+    __syncthreads();
 }
 
 __device__ __forceinline__ TilePlan plan_tiles(const RowRange& range, int n_tiles, const RowMap& probe)
@@ -559,10 +641,11 @@ struct GemmTile {
 // ONCE: the weights are read by this workgroup alone and loaded with the streaming hint, which leaves the L2 to the activations.  Tiles that share
 // a panel lose by it (8 experts of 1024 x 4096, 8192 tokens 143.7 -> 159.7 us), and so do weights that lie in the memory-side cache from the call
 // before, which such loads do not keep there (see weights_are_streamed).
-template <int H, int NT, int WAVES, int EPI, bool ONCE>
+// ROUTED: the tile's rows are the assignments in RoutedSort::list at the begin of the LDS, which the ring overwrites once they are read.
+template <int H, int NT, int WAVES, int EPI, bool ONCE, bool ROUTED>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const bf16_t* __restrict__ wexp, const bf16_t* __restrict__ bias_e,
                                           int row_begin, int row_end, int hid_shift, bool through, int turn, int n0, int K, int N, bf16_t* __restrict__ out,
-                                          unsigned char* smem, const RowMap& map)
+                                          unsigned char* smem, const RowMap& map, const TileRouting& route)
 {
     typedef GemmTile<H, NT, WAVES, ONCE> G;
     constexpr int RB = G::RB, SA = G::SA, SB = G::SB, TM = G::TM, TN = G::TN, LA = G::LA, LW = G::LW;
@@ -599,7 +682,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     // this wavefront's rows are fetched straight into LDS (where its own loads of the last stage will land), the weights of the
     // first K tiles behind them, and the ids are read back once only the weights are outstanding: ids and weights travel
     // together.  (Through a register the id load would be awaited with vmcnt(0), i.e. together with the weights.)
-    const bool gather = map.a_row != nullptr;
+    const bool gather = !ROUTED && map.a_row != nullptr;
     constexpr int ID_LOADS = (LA + 7) / 8;
     const uint32_t ids_at = static_cast<uint32_t>((SA - 1) * G::A_BYTES + wave * 1024);
     static_assert(ID_LOADS * 256 <= 1024, "row ids fit the wavefront's first group of a stage");
@@ -610,6 +693,17 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
             const int row = g.group_a(min(i * 8 + r8, LA - 1)) * 8 + c8;
             lds_dma_4B(ids_b, static_cast<uint32_t>(min(row_begin + row, row_end - 1)) * 4u, g.smem_addr + ids_at + i * 256);
         }
+    }
+    auto chunk_of = [&](int i) { return static_cast<uint32_t>((c8 ^ (((g.group_a(i) * 8 + r8) >> 1) & 7)) * 16); };
+    if constexpr (ROUTED) {
+        const RoutedSort& d = *reinterpret_cast<const RoutedSort*>(smem);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            unsigned r = static_cast<unsigned>(d.list[min(g.group_a(i) * 8 + r8, row_end - row_begin - 1)]);
+            if (route.k > 1) r /= static_cast<unsigned>(route.k);
+            g.off_a[i] = r * row_bytes + chunk_of(i);
+        }
+        __syncthreads();  // (the list has been read: its place may be written)
     }
     const int first_a = min(nk, SA), first_w = min(nk, SB);
     auto first_weights = [&](int s) {
@@ -639,6 +733,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
             continue;
         }
         const int row = g.group_a(i) * 8 + r8;
+        if constexpr (ROUTED) continue;
         int r = min(row_begin + row, row_end - 1);  // rows past the tile end re-read the last valid row
         if (gather) {
             r = *reinterpret_cast<const int*>(smem + ids_at + i * 32 + r8 * 4);
@@ -720,6 +815,21 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     timeline_stamp(map, 3);
     EXF_PIN_ACC();
 #undef EXF_PIN_ACC
+
+    if constexpr (ROUTED) {  // the columns of the sorted rows that fall to this tile's outputs
+        const int pieces = K / 8, piece_begin = static_cast<int>(static_cast<int64_t>(n0) * pieces / N);
+        const int piece_end = static_cast<int>(static_cast<int64_t>(min(n0 + NT, N)) * pieces / N);
+        for (int piece = piece_begin + c8; piece < piece_end; piece += 8) {
+            f32x4_t v[LA];  // (16 bytes)
+#pragma unroll
+            for (int i = 0; i < LA; ++i) v[i] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const unsigned char*>(act) + (g.off_a[i] - chunk_of(i)) + piece * 16);
+#pragma unroll
+            for (int i = 0; i < LA; ++i) {
+                const int row = row_begin + (i * WAVES + wave) * 8 + r8;
+                if (row < row_end) reinterpret_cast<f32x4_t*>(route.sorted_act)[static_cast<size_t>(row) * pieces + piece] = v[i];
+            }
+        }
+    }
 
     // ---- epilogue -----------------------------------------------------------------------------
     // A lane holds, for the 16 x 16 block (b, a), row lane%16 and columns 4*(lane/16) .. +3.  For two blocks side by side the
@@ -803,6 +913,46 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     else finish(std::false_type());
 }
 
+template <int NT, int WAVES, int EPI, bool STREAMS, bool ROUTED>
+__device__ __forceinline__ void run_tile(const Tile2D& tile, const bf16_t* __restrict__ act, const bf16_t* __restrict__ weight, const bf16_t* __restrict__ bias,
+                                         int K, int N, bf16_t* __restrict__ out, unsigned char* smem, const RowMap& map, const TileRouting& route)
+{
+    const bf16_t* wexp = weight + static_cast<size_t>(tile.expert) * N * K;
+    const bf16_t* bias_e = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
+#define EXF_CASE(H, CUT, ONCE)                                                                                                                        \
+    case (CUT) * 16 + (H) / kQuantum:                                                                                                                 \
+        if constexpr (has_instance(NT, H, CUT) && (!(ONCE) || H <= kTileRows))                                                                        \
+            gemm_tile<H, (NT >> CUT), WAVES, EPI, ONCE, ROUTED>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.through, tile.turn,     \
+                                                        tile.n0, K, N, out, smem, map, route);                                                               \
+        break
+#define EXF_CASES(CUT, ONCE)  \
+    EXF_CASE(64, CUT, ONCE);  \
+    EXF_CASE(96, CUT, ONCE);  \
+    EXF_CASE(128, CUT, ONCE); \
+    EXF_CASE(160, CUT, ONCE); \
+    EXF_CASE(192, CUT, ONCE); \
+    EXF_CASE(224, CUT, ONCE); \
+    EXF_CASE(256, CUT, ONCE); \
+    EXF_CASE(288, CUT, ONCE); \
+    EXF_CASE(320, CUT, ONCE)
+    const int instance = tile.cut * 16 + tile.height / kQuantum;
+    if (STREAMS && tile.once) {
+        switch (instance) {
+            EXF_CASES(0, STREAMS);
+            EXF_CASES(1, STREAMS);
+            EXF_CASES(2, STREAMS);
+        }
+    } else {
+        switch (instance) {
+            EXF_CASES(0, false);
+            EXF_CASES(1, false);
+            EXF_CASES(2, false);
+        }
+    }
+#undef EXF_CASES
+#undef EXF_CASE
+}
+
 template <int NT, int WAVES, int EPI, bool STREAMS>
 __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(const bf16_t* __restrict__ act,     // [A,K]
                                                                             const int32_t* __restrict__ offsets,
@@ -837,41 +987,34 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
                  (static_cast<unsigned long long>(tile.expert) << 8) | (static_cast<unsigned long long>(tile.n0 / NT) << 16) |
                  (static_cast<unsigned long long>(tile.row_end - tile.row_begin) << 32) | (static_cast<unsigned long long>(K / kKTile) << 48);
     }
-    const bf16_t* wexp = weight + static_cast<size_t>(tile.expert) * N * K;
-    const bf16_t* bias_e = bias != nullptr ? bias + static_cast<size_t>(tile.expert) * N : nullptr;
-#define EXF_CASE(H, CUT, ONCE)                                                                                                                        \
-    case (CUT) * 16 + (H) / kQuantum:                                                                                                                 \
-        if constexpr (has_instance(NT, H, CUT) && (!(ONCE) || H <= kTileRows))                                                                        \
-            gemm_tile<H, (NT >> CUT), WAVES, EPI, ONCE>(act, wexp, bias_e, tile.row_begin, tile.row_end, tile.hid_shift, tile.through, tile.turn,     \
-                                                        tile.n0, K, N, out, smem, map);                                                               \
-        break
-#define EXF_CASES(CUT, ONCE)  \
-    EXF_CASE(64, CUT, ONCE);  \
-    EXF_CASE(96, CUT, ONCE);  \
-    EXF_CASE(128, CUT, ONCE); \
-    EXF_CASE(160, CUT, ONCE); \
-    EXF_CASE(192, CUT, ONCE); \
-    EXF_CASE(224, CUT, ONCE); \
-    EXF_CASE(256, CUT, ONCE); \
-    EXF_CASE(288, CUT, ONCE); \
-    EXF_CASE(320, CUT, ONCE)
-    const int instance = tile.cut * 16 + tile.height / kQuantum;
-    if (STREAMS && tile.once) {
-        switch (instance) {
-            EXF_CASES(0, STREAMS);
-            EXF_CASES(1, STREAMS);
-            EXF_CASES(2, STREAMS);
-        }
-    } else {
-        switch (instance) {
-            EXF_CASES(0, false);
-            EXF_CASES(1, false);
-            EXF_CASES(2, false);
+    run_tile<NT, WAVES, EPI, STREAMS, false>(tile, act, weight, bias, K, N, out, smem, map, TileRouting{});
+    timeline_stamp(map, 4);
+}
+
+// The first contraction of a layer whose assignments it sorts itself (at most kRoutedTilesMax).
+template <int NT, int EPI, bool STREAMS>
+__global__ __launch_bounds__(8 * kWave, 1) void routed_gemm_bf16_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ weight, int A, int K, int N,
+                                                                        int E_local, bf16_t* __restrict__ out, const TileRouting route)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    touch_arguments<3 * 8 + 4 * 4 + sizeof(TileRouting)>();
+    static_assert(sizeof(RoutedSort::count) == 8 * kWave * 4 && sizeof(RoutedSort) <= 64 * kKTile * 4, "a counter a thread; less than the smallest ring");
+    RoutedSort& d = *reinterpret_cast<RoutedSort*>(smem);
+    const int rounds = (A + 8 * kWave - 1) / (8 * kWave);
+    int e[kRoutedRounds];
+    const RowRange range = count_rows(route, E_local, A, rounds, e, d);
+    const RowMap map{};
+    Tile2D tile;
+    if (!locate_tile<STREAMS>(range, NT, N, static_cast<int>(blockIdx.x), map, tile)) return;
+    collect_rows(tile.expert, wave_read_lane(range.lo, tile.expert), tile.row_begin, tile.row_end, rounds, e, d);
+    if (tile.n0 == 0) {
+        for (int i = threadIdx.x; i < tile.row_end - tile.row_begin; i += 8 * kWave) {
+            const int a = d.list[i];
+            route.src_of_sorted[tile.row_begin + i] = a;
+            route.sorted_of_src[a] = tile.row_begin + i;
         }
     }
-#undef EXF_CASES
-#undef EXF_CASE
-    timeline_stamp(map, 4);
+    run_tile<NT, 8, EPI, STREAMS, true>(tile, act, weight, nullptr, K, N, out, smem, map, route);
 }
 
 // ---------------------------------------------------------------------------- host launchers
@@ -886,16 +1029,20 @@ constexpr int gemm_lds_bytes()
     return most;
 }
 
+// worst case: every expert has one tile more than whole ones (a cut round has at most one workgroup per compute unit); two
+// kinds of tiles are shared out over the XCDs, and the last round may be cut
+static int64_t tile_grid(int64_t A, int N, int NT, int E_local)
+{
+    const int64_t items = (A / kTileRows + (A < E_local ? A : E_local)) * ((N + NT - 1) / NT);
+    return (items / kXcdCount + 2 + kUnitsPerXcd) * kXcdCount;
+}
+
 template <int NT, int WAVES, int EPI, bool STREAMS = false>
 static int launch_bf16_as(const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N, int E_local,
                           void* out, hipStream_t stream, const RowMap& map)
 {
     constexpr size_t lds = gemm_lds_bytes<NT>();
-    // worst case: every expert has one tile more than whole ones (a cut round has at most one workgroup per compute unit); two
-    // kinds of tiles are shared out over the XCDs, and the last round may be cut
-    const int64_t n_tiles = (N + NT - 1) / NT;
-    const int64_t items = (A / kTileRows + (A < E_local ? A : E_local)) * n_tiles;
-    const int64_t grid = (items / kXcdCount + 2 + kUnitsPerXcd) * kXcdCount;
+    const int64_t grid = tile_grid(A, N, NT, E_local);
     if (grid >= (1ll << 31)) return fail(EXF_ERR_BAD_SHAPE, "moe_expert_ffn: too many tiles");
     auto kern = grouped_gemm_bf16_kernel<NT, WAVES, EPI, STREAMS>;
     static std::atomic<uint64_t> allowed{0};
@@ -903,6 +1050,19 @@ static int launch_bf16_as(const void* act, const int32_t* offsets, const void* w
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(WAVES * kWave), lds, stream, static_cast<const bf16_t*>(act), offsets,
                        static_cast<const bf16_t*>(weight), static_cast<const bf16_t*>(bias), static_cast<int>(A), K, N, E_local,
                        static_cast<bf16_t*>(out), map);
+    return EXF_OK;
+}
+
+template <int EPI, bool STREAMS>
+static int launch_routed_as(const void* act, const void* weight, int64_t A, int K, int N, int E_local, void* out, hipStream_t stream, const TileRouting& route)
+{
+    constexpr int NT = 256;
+    constexpr size_t lds = gemm_lds_bytes<NT>();
+    auto kern = routed_gemm_bf16_kernel<NT, EPI, STREAMS>;
+    static std::atomic<uint64_t> allowed{0};
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(tile_grid(A, N, NT, E_local))), dim3(8 * kWave), lds, stream, static_cast<const bf16_t*>(act),
+                       static_cast<const bf16_t*>(weight), static_cast<int>(A), K, N, E_local, static_cast<bf16_t*>(out), route);
     return EXF_OK;
 }
 
@@ -914,5 +1074,9 @@ int launch_once_first(int epi, const void* act, const int32_t* offsets, const vo
                       void* out, hipStream_t stream, const RowMap& map);
 int launch_once_second(bool wide, const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N, int E_local,
                        void* out, hipStream_t stream, const RowMap& map);
+
+// First contractions that sort the assignments (ffn_routed.hip, ffn_routed_once.hip): without and with streamed weights.
+int launch_routed_first(int epi, const void* act, const void* weight, int64_t A, int K, int N, int E_local, void* out, hipStream_t stream, const TileRouting& route);
+int launch_routed_once_first(int epi, const void* act, const void* weight, int64_t A, int K, int N, int E_local, void* out, hipStream_t stream, const TileRouting& route);
 
 }  // namespace exf

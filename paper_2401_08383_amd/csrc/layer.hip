@@ -3,7 +3,7 @@
 // the sorted copies of the rows that these write are by-products of the contractions, and the combine of a top-1 layer is the epilogue of the second one.
 // Small layers are bound by their launches (and by the host, about 4 us each): one token, 5 experts of 896 x 3584 19.0 us in five
 // launches, 10.0 in two; 38 tokens, 8 of 1152 x 4608 46.6 and 39.3; 46 tokens in fp32, 5 of 44 x 812 20.5 and 15.1; with a dispatch of its own, 2759
-// tokens, 7 of 1856 x 5184 171.0 and 166.2.
+// tokens, 7 of 1856 x 5184 171.0 and 166.2.  What sorts in tiles besides: routed_tiles_fit().
 #include "ffn_common.hpp"
 
 extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
@@ -28,8 +28,12 @@ extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
             return bad;
         if (int bad = exf::check_combine(l.y_sorted, l.sorted_of_src, l.topk_w, l.T, l.d, l.k, l.dt, l.out)) return bad;
     }
-    const bool routed = exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt);
-    const bool gated = routed && exf::gate_joins_layer(l.T, l.d, l.E, l.dt, idx != l.topk_idx);
+    const bool streamed = exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt);
+    // (In tiles it reads x while it writes the hidden activations, where separate calls read their sorted copy: these have to lie apart.)
+    const uintptr_t x = reinterpret_cast<uintptr_t>(l.x), ws = reinterpret_cast<uintptr_t>(l.ffn_workspace);
+    const bool apart = x >= ws + l.ffn_workspace_bytes || x + static_cast<uintptr_t>(l.T) * l.d * 2 <= ws;
+    const bool routed = streamed || (!fused && apart && exf::routed_tiles_fit(l.T * l.k, l.d, l.f, l.E, l.E_local, l.dt));
+    const bool gated = streamed && exf::gate_joins_layer(l.T, l.d, l.E, l.dt, idx != l.topk_idx);
     int rc = EXF_OK;
     if (!gated) rc = moe_gate_topk(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.renormalize, l.dt, nullptr, l.topk_idx, l.topk_w, stream);
     if (rc != EXF_OK) return rc;

@@ -378,6 +378,18 @@ def test_unfused_layer_is_its_calls(T, k, E, E_local, dtype, routing, d, f):
     _layer_against_calls(T, k, E, E_local, dtype, False, routing, d, f, ("x_sorted", "y_sorted"))
 
 
+# the same where a first contraction in tiles sorts: one and eight assignments a thread, the longest list and the first with a dispatch launch; tiles of
+# all kinds, whole and cut, reductions of one K tile, more columns of rows than of hidden activations (a tile copies several pieces of a row) and
+# fewer than a piece; weights that are streamed; invalid ids, also all of them; the most tiles of a round and the first that are more; a share of the experts
+@pytest.mark.parametrize("T,k,E,E_local,routing,d,f", [
+    (60, 1, 1, 1, "gate", 4096, 4160), (257, 1, 1, 1, "ids", 64, 64), (512, 1, 2, 2, "gate", 128, 576), (513, 1, 9, 9, "ids", 1088, 64), (2047, 2, 64, 64, "gate", 64, 192),
+    (2048, 2, 12, 12, "ids", 192, 1344), (4095, 1, 8, 8, "ids", 320, 1088), (4096, 1, 16, 16, "gate", 64, 4096), (4096, 1, 16, 16, "gate", 64, 4160), (4097, 1, 16, 16, "gate", 64, 320),
+    (700, 1, 5, 5, "dropped", 64, 128), (1365, 2, 13, 13, "ids", 64, 64), (1500, 1, 33, 33, "gate", 448, 64), (1200, 2, 16, 16, "gate", 2048, 2112), (1500, 1, 64, 33, "ids", 448, 64)])
+def test_layer_that_sorts_in_tiles_is_its_calls(T, k, E, E_local, routing, d, f):
+    _say(f"layer in tiles T={T} k={k} E={E} E_local={E_local} {routing} {d} x {f}")
+    _layer_against_calls(T, k, E, E_local, "bf16", False, routing, d, f, ("x_sorted", "y_sorted"))
+
+
 # top-2 layers whose two rows of a token meet in the second contraction: up to eight rows, up to 64 and up to 1024; blocks of 8 to 64 columns and
 # tiles of one and several row groups; tokens of which one or both assignments are dropped, and with the same expert twice ("ids"); the last
 # shape of the separate calls that gets by with the reserved 16 MiB, the first that does not, and weights past the line
