@@ -120,10 +120,12 @@ bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
 // fp32: are both contractions one launch, and that launch (out of the first one is not written).
 bool exact_pair_fits(int64_t A, int d, int f, int E_local);
+bool exact_pair_routed_fits(int64_t A, int d, int f, int E_local);  // (that sorts; its rows do not meet, see StreamGemm::exchange)
 int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream);
 inline int launch_stream_pair(const StreamGemm& first, const StreamGemm& second, int dt, hipStream_t stream)
 {
-    if (dt == EXF_F32 && exact_pair_fits(first.max_rows, first.K, first.N, first.E_local)) {
+    auto fits = first.topk_idx != nullptr ? exact_pair_routed_fits : exact_pair_fits;
+    if (dt == EXF_F32 && first.exchange == nullptr && fits(first.max_rows, first.K, first.N, first.E_local)) {
         // (two launches may write where the first one has read)
         const uintptr_t bytes = static_cast<uintptr_t>(first.max_rows) * first.K * 4, act = reinterpret_cast<uintptr_t>(first.act);
         auto apart = [&](const void* to) { return reinterpret_cast<uintptr_t>(to) >= act + bytes || reinterpret_cast<uintptr_t>(to) + bytes <= act; };

@@ -78,8 +78,9 @@ struct InlineDispatch {
     int offs[EXF_MAX_EXPERTS + 1];
     unsigned short seg[kInlineSegments][EXF_MAX_EXPERTS];  // count, then start inside its expert's bucket
 };
-template <int THREADS>
-__device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDispatch& d, bool publish)
+// dropped(a): assignment a is not kept (by the one thread that has it).
+template <int THREADS, typename Dropped>
+__device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDispatch& d, bool publish, Dropped dropped)
 {
     constexpr int WAVES = THREADS / kWave, R = kInlineDispatchMax / THREADS;
     const int lane = lane_id();
@@ -143,6 +144,7 @@ __device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDisp
             if (publish) p.src_of_sorted[pos] = a;
         }
         if (publish && a < A) p.sorted_of_src[a] = pos;
+        if (a < A && pos < 0) dropped(a);
     }
     __syncthreads();
 }
@@ -622,7 +624,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         const int32_t* offsets = p.offsets;
         if constexpr (ROWS == kRowsInline) {
             InlineDispatch* d = reinterpret_cast<InlineDispatch*>(smem + stream_ring_bytes(C8, W) + W * kStreamIdBytes);
-            sort_assignments<W * kWave>(p, *d, blockIdx.x == 0);
+            sort_assignments<W * kWave>(p, *d, blockIdx.x == 0, [](int) {});
             list = d->list;
             offsets = d->offs;
         }
@@ -925,7 +927,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     const int32_t *a_row = p.a_row, *offsets = p.offsets;
     if constexpr (INLINE) {
         InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * SLOTS * TILE_ROWS * RS);
-        sort_assignments<WK * WI * kWave>(p, *d, blockIdx.x == 0);
+        sort_assignments<WK * WI * kWave>(p, *d, blockIdx.x == 0, [](int) {});
         a_row = d->list;
         offsets = d->offs;
     }
@@ -1201,6 +1203,8 @@ struct PairWeights {
 };
 __host__ __device__ constexpr size_t pair_floats(int d, int f) { return static_cast<size_t>(kPairRows) * (f + 4) + static_cast<size_t>(kPairParts) * kPairRows * (d + 4); }
 
+// INLINE: of a list that is sorted on the way (p.topk_idx): gate and this are the whole layer.
+template <bool INLINE>
 __global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const StreamGemm p, const StreamGemm q)
 {
     extern __shared__ __attribute__((aligned(16))) float pair_smem[];
@@ -1211,9 +1215,21 @@ __global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const St
     const int act_stride = d + 4, hid_stride = f + 4;  // (padded: 16 rows lie in distinct banks)
     float* hid = pair_smem;                     // [16][f + 4]
     float* act = hid + kPairRows * hid_stride;  // [16][d + 4], later the sums of the parts: [4][16][d + 4]
-    if (q.unrouted != nullptr) clear_unrouted_rows<false, false>(q.unrouted, q.n_unrouted, static_cast<uint4*>(q.out), d / 4, kPairWaves);
+    const int32_t *a_row = p.a_row, *out_row = q.out_row, *offsets = p.offsets;
+    if constexpr (INLINE) {
+        InlineDispatch* sort = reinterpret_cast<InlineDispatch*>(pair_smem + pair_floats(d, f));
+        sort_assignments<kPairWaves * kWave>(p, *sort, blockIdx.x == 0, [&](int a) {
+            if (q.unrouted == nullptr || static_cast<unsigned>(a) % gridDim.x != blockIdx.x) return;
+            for (int c = 0; c < d / 4; ++c) reinterpret_cast<uint4*>(q.out)[static_cast<size_t>(a) * (d / 4) + c] = make_uint4(0u, 0u, 0u, 0u);
+        });
+        a_row = sort->list;
+        if (out_row != nullptr) out_row = sort->list;
+        offsets = sort->offs;
+    } else if (q.unrouted != nullptr) {
+        clear_unrouted_rows<false, false>(q.unrouted, q.n_unrouted, static_cast<uint4*>(q.out), d / 4, kPairWaves);
+    }
     // every XCD takes a contiguous share of the tiles: those of an expert meet in one L2
-    const ExpertTiles et = scan_row_tiles(p, p.offsets, kPairRows);
+    const ExpertTiles et = scan_row_tiles(p, offsets, kPairRows);
     const int xcd = static_cast<int>(blockIdx.x % kXcdCount);
     const int item = static_cast<int>(static_cast<int64_t>(et.total) * xcd / kXcdCount) + static_cast<int>(blockIdx.x / kXcdCount);
     if (item >= static_cast<int>(static_cast<int64_t>(et.total) * (xcd + 1) / kXcdCount)) return;
@@ -1227,17 +1243,19 @@ __global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const St
     const int units1 = (d + kExactUnit - 1) / kExactUnit, units2 = (f + kExactUnit - 1) / kExactUnit;
     const int sorted = row_begin + min(wave, rows - 1);  // (rows past the end repeat the last one)
     int from = sorted;
-    if (p.a_row != nullptr) from = p.a_div > 1 ? static_cast<int>(static_cast<unsigned>(p.a_row[sorted]) / static_cast<unsigned>(p.a_div)) : p.a_row[sorted];
+    if (a_row != nullptr) from = p.a_div > 1 ? static_cast<int>(static_cast<unsigned>(a_row[sorted]) / static_cast<unsigned>(p.a_div)) : a_row[sorted];
     int dst = sorted;
     float scale = 1.0f;
-    if (q.out_row != nullptr) {
-        dst = q.out_row[sorted];
+    if (out_row != nullptr) {
+        dst = out_row[sorted];
         scale = q.out_scale[dst];
     }
     PairWeights pw;
     pw.begin(w1, wave * 16, f, d, 0, units1);
     for (int c = lane; c < d / 4; c += kWave) {
-        reinterpret_cast<float4*>(act + wave * act_stride)[c] = reinterpret_cast<const float4*>(static_cast<const float*>(p.act) + static_cast<size_t>(from) * d)[c];
+        const float4 v = reinterpret_cast<const float4*>(static_cast<const float*>(p.act) + static_cast<size_t>(from) * d)[c];
+        reinterpret_cast<float4*>(act + wave * act_stride)[c] = v;
+        if (INLINE && p.sorted_act != nullptr && wave < rows) reinterpret_cast<float4*>(static_cast<float*>(p.sorted_act) + static_cast<size_t>(sorted) * d)[c] = v;
     }
     __syncthreads();
 
@@ -1323,24 +1341,43 @@ static double exact_pair_cost(int64_t A, int d, int f, int E_local)
 // The line: not where two launches would cost a twentieth less, nor where both contractions fill whole rounds of tiles of 64 rows.  Two launches and one, us:
 // 1500 rows, 4 experts of 256 x 256 18.0 and 19.4; 1100, 16 of 96 x 400 11.4 and 14.3; 1100, 64 of 256 x 1024 47 and 62; 1500, 4 of 64 x 1024 24.5 and
 // 19.1; 4000, 16 of 512 x 128 33.5 and 49.9; 64000 of 512 x 128 299 and 398; 32000 of 256 x 512 255 and 264; 8000 of 256 x 1024 156 and 126.  Over 1540 lists the choice
-// costs 1.5 % more than the best one (one launch wherever it fits 3.8).  Lists that a first contraction sorts are two launches: this kernel reads finished offsets.
+// costs 1.5 % more than the best one (one launch wherever it fits 3.8).  Shorter lists are sorted on the way, see below.
+static double exact_both_cost(int64_t A, int d, int f, int E_local)
+{
+    return exact_cost(A, d, f, E_local, true, tall_exact_tiles(A, d, f, E_local, true)) + exact_cost(A, f, d, E_local, false, tall_exact_tiles(A, f, d, E_local, false));
+}
 bool exact_pair_fits(int64_t A, int d, int f, int E_local)
 {
     if (A <= kInlineDispatchMax || pair_floats(d, f) * sizeof(float) > 160 * 1024) return false;
     if (d >= 240 && whole_rounds(A, d, f, E_local) && whole_rounds(A, f, d, E_local)) return false;
-    const double both = exact_cost(A, d, f, E_local, true, tall_exact_tiles(A, d, f, E_local, true)) + exact_cost(A, f, d, E_local, false, tall_exact_tiles(A, f, d, E_local, false));
-    return both >= 0.95 * exact_pair_cost(A, d, f, E_local);
+    return exact_both_cost(A, d, f, E_local) >= 0.95 * exact_pair_cost(A, d, f, E_local);
 }
 
-int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream)
+// Lists that are sorted on the way: sorting takes the same time in either, and so few tiles leave most compute units idle, so where the model has this launch
+// ahead.  Whole layers with two and one, us: 1024 tokens, 8 experts of 64 x 256 15.8 and 13.5; 512, 8 of 64 x 128 12.7 and 11.3; 512, 4 of 32 x 128
+// 12.2 and 10.6; 700, 14 of 44 x 300, separate calls 15.2 and 14.1; 900, 16 of 92 x 252 16.2 and 15.4; not 512, 8 of 64 x 256 13.3 and 13.4; 100 of
+// these 11.9 and 13.2; 512, 8 of 128 x 256 15.3 and 16.3; 512, 8 of 256 x 512 20.9 and 37.3.
+bool exact_pair_routed_fits(int64_t A, int d, int f, int E_local)
 {
+    return A <= kInlineDispatchMax && pair_floats(d, f) * sizeof(float) + sizeof(InlineDispatch) <= 160 * 1024 &&
+           exact_both_cost(A, d, f, E_local) >= exact_pair_cost(A, d, f, E_local);
+}
+
+template <bool INLINE>
+static int launch_exact_pair_as(const StreamGemm& first, const StreamGemm& second, hipStream_t stream)
+{
+    auto kern = exact_pair_kernel<INLINE>;
     static std::atomic<uint64_t> allowed{0};
-    if (int rc = allow_lds(reinterpret_cast<const void*>(exact_pair_kernel), 160 * 1024, allowed, "moe_expert_ffn")) return rc;
+    if (int rc = allow_lds(reinterpret_cast<const void*>(kern), 160 * 1024, allowed, "moe_expert_ffn")) return rc;
     const int64_t A = first.max_rows;
     const int64_t share = (A / kPairRows + (A < first.E_local ? A : first.E_local)) / kXcdCount + 1;  // tiles of an XCD at most
-    hipLaunchKernelGGL(exact_pair_kernel, dim3(static_cast<unsigned>(share * kXcdCount)), dim3(kPairWaves * kWave), pair_floats(first.K, first.N) * sizeof(float),
-                       stream, first, second);
+    const size_t lds = pair_floats(first.K, first.N) * sizeof(float) + (INLINE ? sizeof(InlineDispatch) : 0);
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(share * kXcdCount)), dim3(kPairWaves * kWave), lds, stream, first, second);
     return EXF_OK;
+}
+int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream)
+{
+    return first.topk_idx != nullptr ? launch_exact_pair_as<true>(first, second, stream) : launch_exact_pair_as<false>(first, second, stream);
 }
 
 // ---------------------------------------------------------------------------- host
