@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(PKG, "libexflow_moe.so")
-SOURCES = ["api.hip", "gate.hip", "dispatch.hip", "ffn.hip", "ffn_keep.hip", "ffn_stream.hip", "combine.hip", "layer.hip", "affinity.hip", "affinity_direct.hip", "placement.hip", "probe.hip", "ffn_once.hip", "ffn_once_second.hip", "ffn_routed.hip", "ffn_routed_once.hip"]
+SOURCES = ["api.hip", "gate.hip", "dispatch.hip", "ffn.hip", "ffn_keep.hip", "ffn_stream.hip", "combine.hip", "layer.hip", "affinity.hip", "affinity_direct.hip", "placement.hip", "probe.hip", "ffn_once.hip", "ffn_once_second.hip", "ffn_routed.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

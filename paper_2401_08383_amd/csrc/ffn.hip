@@ -41,24 +41,19 @@ static int launch_first_contraction(const void* act, const int32_t* offsets, con
 }
 
 // In tiles the first contraction sorts where the sorted rows are wanted besides, so that the launch that goes had rows to move, where all experts are resident (few
-// rows to move otherwise) and where their tiles are one round (every round counts again).  Separate calls, with a dispatch of its own and without, us:
-//   one round: 1531 tokens top-2, 16 experts of 1024 x 4096 96.1 -> 93.9, 2000 top-2, 8 of 576 x 2304 62.5 -> 57.2, 4000, 8 of 1024 x 4096 91.7 -> 85.1,
-//     2048 top-2, 8 of 4096 x 4096 287 -> 271, 300, 4 of 1024 x 4096 36.8 -> 35.9, 1000, 4 of 512 x 2048 31.3 -> 29.9
-//   more: 2000 top-2, 32 of 1024 x 4096 140 and 145, 4000, 4 of 4096 x 16384 920 and 927, 850 top-2, 27 of 3072 x 8512 522 and 542
+// rows to move otherwise), where their tiles are one round (every round counts again) and where the weights are not streamed (they are asked for later than
+// behind finished offsets).  Separate calls, other tensors each time, with a dispatch of its own and without, us:
+//   one round: 4000 tokens, 8 experts of 1024 x 4096 101.5 -> 95.7, 2000 top-2, 8 of 576 x 2304 61.6 -> 56.9, 4096, 4 of 512 x 1024 38.5 -> 36.7,
+//     300, 4 of 1024 x 4096 36.8 -> 36.0, 1000, 4 of 512 x 2048 32.4 -> 31.8, 1600, 2 of 2560 x 10240 189.5 -> 187.1, 3000, 6 of 768 x 3072 65.9 -> 64.9
+//   more (the same tensors): 2000 top-2, 32 of 1024 x 4096 140 and 145, 4000, 4 of 4096 x 16384 920 and 927, 850 top-2, 27 of 3072 x 8512 522 and 542
 //   a share of the experts: 3900 tokens, 16 of 64 of 960 x 3840 99.8 and 105.2, 4000, 8 of 64 of 1024 x 4096 46.9 and 47.7
 //   no sorted rows (fused): 4000, 8 of 1024 x 4096 79.8 and 82.1, 300, 4 of them 34.6 and 34.8
+//   streamed: 1531 top-2, 16 of 1024 x 4096 101.4 and 102.6, 600, 8 of 4096 x 8192 188.6 and 188.2 (2048 top-2, 8 of 4096 x 4096 296 and 291)
 bool routed_tiles_fit(int64_t A, int d, int f, int E, int E_local, int dt)
 {
-    if (dt != EXF_BF16 || A <= 0 || A > kRoutedTilesMax || E_local != E || stream_path_fits(A, d, f, E_local, dt)) return false;
+    if (dt != EXF_BF16 || A <= 0 || A > kRoutedTilesMax || E_local != E || stream_path_fits(A, d, f, E_local, dt) || weights_are_streamed(A, d, f, E)) return false;
     constexpr int kRows = kTileRows + kQuantum;
     return (A + static_cast<int64_t>(E) * kRows - 1) / (static_cast<int64_t>(E) * kRows) * E * ((f + 255) / 256) <= kComputeUnits;
-}
-
-static int launch_routed_contraction(const void* act, const void* weight, int64_t A, int K, int N, int E_local, int epi, void* out, hipStream_t stream,
-                                     const TileRouting& route)
-{
-    if (weights_are_streamed(A, K, N, E_local)) return launch_routed_once_first(epi, act, weight, A, K, N, E_local, out, stream, route);
-    return launch_routed_first(epi, act, weight, A, K, N, E_local, out, stream, route);
 }
 
 // The second contraction has few output columns (N = d).  With 256x128 tiles it offers twice as many
@@ -302,7 +297,7 @@ static int ffn_fused_run(const void* x, const int32_t* src_of_sorted, const int3
             const TileRouting route{routing->topk_idx,      routing->expert_map,     routing->src_of_sorted, routing->sorted_of_src,
                                     routing->expert_counts, routing->expert_offsets, static_cast<bf16_t*>(routing->x_sorted), routing->E, k};
             if (k == 1) scatter.sorted_out = static_cast<bf16_t*>(routing->y_sorted);
-            rc = launch_routed_contraction(x, w1, A, d, f, E_local, epi, hidden, s, route);
+            rc = launch_routed_first(epi, x, w1, A, d, f, E_local, hidden, s, route);
         } else {
             rc = launch_first_contraction(x, expert_offsets, w1, b1, A, d, f, E_local, epi, hidden, s, gather);
         }

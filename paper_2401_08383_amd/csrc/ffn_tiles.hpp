@@ -992,7 +992,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void grouped_gemm_bf16_kernel(con
 }
 
 // The first contraction of a layer whose assignments it sorts itself (at most kRoutedTilesMax).
-template <int NT, int EPI, bool STREAMS>
+template <int NT, int EPI>
 __global__ __launch_bounds__(8 * kWave, 1) void routed_gemm_bf16_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ weight, int A, int K, int N,
                                                                         int E_local, bf16_t* __restrict__ out, const TileRouting route)
 {
@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(8 * kWave, 1) void routed_gemm_bf16_kernel(const bf
     const RowRange range = count_rows(route, E_local, A, rounds, e, d);
     const RowMap map{};
     Tile2D tile;
-    if (!locate_tile<STREAMS>(range, NT, N, static_cast<int>(blockIdx.x), map, tile)) return;
+    if (!locate_tile<false>(range, NT, N, static_cast<int>(blockIdx.x), map, tile)) return;
     collect_rows(tile.expert, wave_read_lane(range.lo, tile.expert), tile.row_begin, tile.row_end, rounds, e, d);
     if (tile.n0 == 0) {
         for (int i = threadIdx.x; i < tile.row_end - tile.row_begin; i += 8 * kWave) {
@@ -1014,7 +1014,7 @@ __global__ __launch_bounds__(8 * kWave, 1) void routed_gemm_bf16_kernel(const bf
             route.sorted_of_src[a] = tile.row_begin + i;
         }
     }
-    run_tile<NT, 8, EPI, STREAMS, true>(tile, act, weight, nullptr, K, N, out, smem, map, route);
+    run_tile<NT, 8, EPI, false, true>(tile, act, weight, nullptr, K, N, out, smem, map, route);
 }
 
 // ---------------------------------------------------------------------------- host launchers
@@ -1053,12 +1053,12 @@ static int launch_bf16_as(const void* act, const int32_t* offsets, const void* w
     return EXF_OK;
 }
 
-template <int EPI, bool STREAMS>
+template <int EPI>
 static int launch_routed_as(const void* act, const void* weight, int64_t A, int K, int N, int E_local, void* out, hipStream_t stream, const TileRouting& route)
 {
     constexpr int NT = 256;
     constexpr size_t lds = gemm_lds_bytes<NT>();
-    auto kern = routed_gemm_bf16_kernel<NT, EPI, STREAMS>;
+    auto kern = routed_gemm_bf16_kernel<NT, EPI>;
     static std::atomic<uint64_t> allowed{0};
     if (int rc = allow_lds(reinterpret_cast<const void*>(kern), lds, allowed, "moe_expert_ffn")) return rc;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(tile_grid(A, N, NT, E_local))), dim3(8 * kWave), lds, stream, static_cast<const bf16_t*>(act),
@@ -1075,8 +1075,7 @@ int launch_once_first(int epi, const void* act, const int32_t* offsets, const vo
 int launch_once_second(bool wide, const void* act, const int32_t* offsets, const void* weight, const void* bias, int64_t A, int K, int N, int E_local,
                        void* out, hipStream_t stream, const RowMap& map);
 
-// First contractions that sort the assignments (ffn_routed.hip, ffn_routed_once.hip): without and with streamed weights.
+// First contractions that sort the assignments (ffn_routed.hip).
 int launch_routed_first(int epi, const void* act, const void* weight, int64_t A, int K, int N, int E_local, void* out, hipStream_t stream, const TileRouting& route);
-int launch_routed_once_first(int epi, const void* act, const void* weight, int64_t A, int K, int N, int E_local, void* out, hipStream_t stream, const TileRouting& route);
 
 }  // namespace exf

@@ -389,7 +389,7 @@ def test_unfused_layer_is_its_calls(T, k, E, E_local, dtype, routing, d, f):
 
 # the same where a first contraction in tiles sorts: one and eight assignments a thread, the longest list and the first with a dispatch launch; tiles of
 # all kinds, whole and cut, reductions of one K tile, more columns of rows than of hidden activations (a tile copies several pieces of a row) and
-# fewer than a piece; weights that are streamed; invalid ids, also all of them; the most tiles of a round and the first that are more; a share of the experts
+# fewer than a piece; weights that are streamed (a dispatch launch); invalid ids, also all of them; the most tiles of a round and the first that are more; a share of the experts
 @pytest.mark.parametrize("T,k,E,E_local,routing,d,f", [
     (60, 1, 1, 1, "gate", 4096, 4160), (257, 1, 1, 1, "ids", 64, 64), (512, 1, 2, 2, "gate", 128, 576), (513, 1, 9, 9, "ids", 1088, 64), (2047, 2, 64, 64, "gate", 64, 192),
     (2048, 2, 12, 12, "ids", 192, 1344), (4095, 1, 8, 8, "ids", 320, 1088), (4096, 1, 16, 16, "gate", 64, 4096), (4096, 1, 16, 16, "gate", 64, 4160), (4097, 1, 16, 16, "gate", 64, 320),
