@@ -122,15 +122,37 @@ int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
 bool exact_pair_fits(int64_t A, int d, int f, int E_local);
 bool exact_pair_routed_fits(int64_t A, int d, int f, int E_local);  // (that sorts; its rows do not meet, see StreamGemm::exchange)
 int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream);
+// Bytes [a, a + n) and [b, b + m) have none in common (a null pointer: there are none).
+inline bool lie_apart(const void* a, size_t n, const void* b, size_t m)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return a == nullptr || b == nullptr || (p <= q ? q - p >= n : p - q >= m);
+}
+// One launch writes results while other workgroups of it still read what the first contraction reads, and write what it leaves besides.  Two launches
+// may have these in one place (the result of a layer over the sorted copies of its rows, rows that are written where they were read), so one is
+// taken only where the results lie apart from all of that.  Sorted rows over the sorted copies of the same rows are no matter: the thread that
+// copies a piece of a row writes the result's as well.
+inline bool pair_lies_apart(const StreamGemm& first, const StreamGemm& second)
+{
+    const size_t A = static_cast<size_t>(first.max_rows), rows = A * first.K * 4, weights = static_cast<size_t>(first.E_local) * first.N;
+    const struct {
+        const void* at;
+        size_t bytes;
+    } early[] = {{first.act, first.a_div > 1 ? rows / first.a_div : rows}, {first.weight, weights * first.K * 4}, {first.bias, weights * 4}, {first.sorted_act, rows},
+                 {first.a_row, A * 4}, {first.topk_idx, A * 4}, {first.expert_map, static_cast<size_t>(first.E) * 4}, {first.src_of_sorted, A * 4},
+                 {first.expert_counts, static_cast<size_t>(first.E_local) * 4}};
+    auto apart = [&](const void* to, bool sorted) {
+        for (const auto& e : early)
+            if (!(sorted && to == first.sorted_act && e.at == to) && !lie_apart(to, rows, e.at, e.bytes)) return false;
+        return true;
+    };
+    return apart(second.out, second.out_row == nullptr) && apart(second.sorted_out, true);
+}
 inline int launch_stream_pair(const StreamGemm& first, const StreamGemm& second, int dt, hipStream_t stream)
 {
     auto fits = first.topk_idx != nullptr ? exact_pair_routed_fits : exact_pair_fits;
-    if (dt == EXF_F32 && first.exchange == nullptr && fits(first.max_rows, first.K, first.N, first.E_local)) {
-        // (two launches may write where the first one has read)
-        const uintptr_t bytes = static_cast<uintptr_t>(first.max_rows) * first.K * 4, act = reinterpret_cast<uintptr_t>(first.act);
-        auto apart = [&](const void* to) { return reinterpret_cast<uintptr_t>(to) >= act + bytes || reinterpret_cast<uintptr_t>(to) + bytes <= act; };
-        if (apart(second.out) && (second.sorted_out == nullptr || apart(second.sorted_out))) return launch_exact_pair(first, second, stream);
-    }
+    if (dt == EXF_F32 && first.exchange == nullptr && fits(first.max_rows, first.K, first.N, first.E_local) && pair_lies_apart(first, second))
+        return launch_exact_pair(first, second, stream);
     const int rc = launch_stream_gemm(first, dt, stream);
     return rc == EXF_OK ? launch_stream_gemm(second, dt, stream) : rc;
 }

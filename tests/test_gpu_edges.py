@@ -322,6 +322,29 @@ def test_exact_ffn_in_place():
     assert float((x - y).abs().max()) <= 1e-5 * float(y.abs().max())
 
 
+@pytest.mark.parametrize("T,k,over", [(512, 1, ["out"]), (1024, 1, ["out"]), (1024, 1, ["y_sorted"]), (700, 1, ["out", 4096]), (512, 2, ["y_sorted"]), (512, 2, ["y_sorted", 4096])])
+def test_exact_layer_over_the_sorted_copies(T, k, over):
+    """Results in the buffer of the sorted copies, which are dead by then, or reaching into it: those of the calls, which write them in launches of their own."""
+    from paper_2401_08383_amd.pipeline import MoELayerRun
+
+    _say(f"fp32 layer, T={T} k={k}, {over} over the sorted copies")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1595 + T)
+    x, wg, w1, w2 = (torch.randn(shape, device="cuda", generator=g) for shape in ((T, 64), (8, 64), (8, 256, 64), (8, 64, 256)))
+    idx = torch.randint(-1, 9, (T, k), device="cuda", generator=g, dtype=torch.int32)
+    run = MoELayerRun(x, wg, w1, w2, k, k > 1, topk_idx=idx)
+    run.step()
+    ref = run.out.clone()
+    room = torch.zeros(T * k * 64 + 4096, device="cuda")
+    run.x_sorted = room[:T * k * 64].view(T * k, 64)
+    begin = sum(over[1:])  # floats
+    setattr(run, over[0], room[begin:begin + T * k * 64].view(T * k, 64))
+    for _ in range(3):
+        room.fill_(-7)
+        run.step()
+        assert torch.equal(run.out, ref)
+
+
 # ----------------------------------------------------------------------------- dispatch: every workgroup counts the whole list
 @pytest.mark.parametrize("T,k,d,E,E_local", [
     (1, 1, 8, 1, 1), (7, 1, 72, 3, 3), (9, 2, 1032, 64, 64), (2048, 2, 64, 8, 8), (4097, 1, 136, 40, 7), (3584, 2, 16, 64, 64), (7169, 1, 16, 64, 64),
