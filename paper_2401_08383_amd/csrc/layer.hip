@@ -28,12 +28,16 @@ extern "C" int moe_layer_forward(const exf_moe_layer* layer, void* stream)
             return bad;
         if (int bad = exf::check_combine(l.y_sorted, l.sorted_of_src, l.topk_w, l.T, l.d, l.k, l.dt, l.out)) return bad;
     }
-    const bool streamed = exf::routed_path_fits(l.T * l.k, l.d, l.f, l.E_local, l.dt);
-    // (In tiles it reads x while it writes the hidden activations, where separate calls read their sorted copy: these have to lie apart.)
-    const uintptr_t x = reinterpret_cast<uintptr_t>(l.x), ws = reinterpret_cast<uintptr_t>(l.ffn_workspace);
-    const bool apart = x >= ws + l.ffn_workspace_bytes || x + static_cast<uintptr_t>(l.T) * l.d * 2 <= ws;
-    const bool routed = streamed || (!fused && apart && exf::routed_tiles_fit(l.T * l.k, l.d, l.f, l.E, l.E_local, l.dt));
-    const bool gated = streamed && exf::gate_joins_layer(l.T, l.d, l.E, l.dt, idx != l.topk_idx);
+    // A first contraction that sorts reads the ids, and x where separate calls read their sorted copy, while hidden activations are written.  Calls in sequence
+    // may have these in the workspace of a later one: there they stay calls in sequence.
+    const int64_t A = l.T * l.k;
+    const size_t elem = l.dt == EXF_BF16 ? 2 : 4;
+    const size_t hidden = fused ? moe_expert_ffn_fused_workspace_bytes(l.T, l.k, l.d, l.f, l.E_local, l.dt) : moe_expert_ffn_workspace_bytes(A, l.d, l.f, l.E_local, l.dt);
+    auto apart = [&](const void* p, size_t n) { return exf::lie_apart(p, n, l.ffn_workspace, hidden); };
+    const bool free = apart(idx, A * sizeof(int32_t)) && apart(l.expert_map, l.E * sizeof(int32_t)) && (fused || apart(l.x, l.T * l.d * elem));
+    const bool streamed = free && exf::routed_path_fits(A, l.d, l.f, l.E_local, l.dt);
+    const bool routed = streamed || (free && !fused && exf::routed_tiles_fit(A, l.d, l.f, l.E, l.E_local, l.dt));
+    const bool gated = streamed && exf::gate_joins_layer(l.T, l.d, l.E, l.dt, idx != l.topk_idx) && apart(l.w_gate, l.E * l.d * elem);
     int rc = EXF_OK;
     if (!gated) rc = moe_gate_topk(l.x, l.w_gate, l.T, l.d, l.E, l.k, l.renormalize, l.dt, nullptr, l.topk_idx, l.topk_w, stream);
     if (rc != EXF_OK) return rc;

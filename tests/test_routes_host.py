@@ -38,6 +38,53 @@ int main(int argc, char** argv)
 }
 """
 
+LAYER = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include "layer.hip"
+namespace exf {
+int fail(int code, const char*, ...) { return code; }
+int check_gate(const void*, const void*, int64_t, int, int, int, int, const int32_t*, const float*) { return 0; }
+int check_dispatch(const void*, const int32_t*, int64_t, int, int, int, int, int, const void*, const int32_t*, const int32_t*, const int32_t*, const int32_t*, const void*, size_t) { return 0; }
+int check_ffn(const void*, const int32_t*, const void*, const void*, int64_t, int, int, int, int, int, const void*, const void*, size_t) { return 0; }
+int check_ffn_fused(const void*, const int32_t*, const int32_t*, const float*, const int32_t*, const void*, const void*, int64_t, int, int, int, int, int, int, const void*, const void*, size_t) { return 0; }
+int check_combine(const void*, const int32_t*, const float*, int64_t, int, int, int, const void*) { return 0; }
+bool stream_path_fits(int64_t A, int, int, int, int) { return A <= 512; }
+bool routed_tiles_fit(int64_t A, int, int, int, int, int) { return A > 512; }
+bool gate_joins_layer(int64_t T, int, int, int, bool) { return T <= 16; }
+int ffn_combined(const void*, const int32_t*, const int32_t*, const float*, const int32_t*, const void*, const void*, int64_t, int, int, int, int, int, void*, void*, void*, void*) { puts("ffn"); return 0; }
+int ffn_fused_routed(const FfnRouting& r, const void*, const float*, const void*, const void*, int64_t, int, int, int, int, int, int, void*, void*, size_t, void*)
+{
+    puts(r.w_gate != nullptr ? "gated" : "routed");
+    return 0;
+}
+}
+extern "C" {
+size_t moe_expert_ffn_workspace_bytes(int64_t, int, int, int, int) { return 1 << 20; }
+size_t moe_expert_ffn_fused_workspace_bytes(int64_t, int, int, int, int, int) { return 1 << 20; }
+int moe_gate_topk(const void*, const void*, int64_t, int, int, int, int, int, float*, int32_t*, float*, void*) { puts("gate"); return 0; }
+int moe_dispatch(const void*, const int32_t*, const int32_t*, int64_t, int, int, int, int, int, void*, int32_t*, int32_t*, int32_t*, int32_t*, void*, size_t, void*) { puts("dispatch"); return 0; }
+int moe_expert_ffn(const void*, const int32_t*, const void*, const void*, const void*, const void*, int64_t, int, int, int, int, int, void*, void*, size_t, void*) { puts("ffn"); return 0; }
+int moe_expert_ffn_fused(const void*, const int32_t*, const int32_t*, const float*, const int32_t*, const void*, const void*, const void*, const void*, int64_t, int, int, int, int, int, int, void*, void*, size_t, void*) { puts("ffn"); return 0; }
+int moe_combine(const void*, const int32_t*, const float*, int64_t, int, int, int, void*, void*) { puts("combine"); return 0; }
+}
+int main(int argc, char** argv)
+{
+    auto at = [&](const char* name) -> char* {
+        for (int i = 1; i + 1 < argc; i += 2)
+            if (strcmp(argv[i], name) == 0) return reinterpret_cast<char*>(strtoull(argv[i + 1], nullptr, 0));
+        return nullptr;
+    };
+    auto number = [&](const char* name) { return reinterpret_cast<uintptr_t>(at(name)); };
+    exf_moe_layer l{};
+    l.T = number("T"), l.k = 1, l.d = 64, l.f = 256, l.E = 8, l.E_local = 8, l.dt = number("f32") ? EXF_F32 : EXF_BF16, l.fused = number("fused");
+    l.x = at("x"), l.w_gate = at("w_gate"), l.forced_idx = reinterpret_cast<int32_t*>(at("ids")), l.expert_map = reinterpret_cast<int32_t*>(at("map"));
+    l.topk_idx = reinterpret_cast<int32_t*>(at("topk_idx")), l.ffn_workspace = at("ws"), l.ffn_workspace_bytes = number("ws_bytes");
+    return moe_layer_forward(&l, nullptr);
+}
+"""
+
 
 def _compile(tmp, name, text):
     if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
@@ -77,3 +124,27 @@ def test_one_launch_only_where_results_lie_apart_from_what_the_first_contraction
     second contraction leaves the sorted rows, `out` here.)"""
     at = {**APART, **moved}
     assert pair(k=k, **at) == (["one"] if launches == 1 else ["two", "two"])
+
+
+@pytest.fixture(scope="module")
+def layer(tmp_path_factory):
+    return _compile(tmp_path_factory.mktemp("layer"), "layer", LAYER)
+
+
+# a workspace of a megabyte is needed and given; the rows are T * 64 of two bytes (four)
+BUFFERS = dict(x=1 * MB, w_gate=2 * MB, topk_idx=4 * MB, ws=16 * MB, ws_bytes=MB)
+SEQUENCE = ["gate", "dispatch", "ffn"]
+
+
+@pytest.mark.parametrize("T,fused,moved,calls", [
+    (8, 0, {}, ["gated"]), (8, 1, {}, ["gated"]), (100, 0, {}, ["gate", "routed"]), (1000, 0, {}, ["gate", "routed"]), (1000, 1, {}, SEQUENCE),
+    # x in the workspace, where it ends and begins, with a workspace given larger than is needed
+    (8, 0, {"x": 16 * MB}, SEQUENCE), (100, 0, {"x": 17 * MB - 16}, SEQUENCE), (100, 0, {"x": 17 * MB}, ["gate", "routed"]), (1000, 0, {"x": 16 * MB + 64}, SEQUENCE),
+    (1000, 0, {"x": 16 * MB - 128000}, ["gate", "routed"]), (1000, 0, {"x": 16 * MB - 127984}, SEQUENCE), (1000, 0, {"x": 17 * MB - 16, "ws_bytes": (1 << 64) - 1}, SEQUENCE),
+    (1000, 0, {"x": 17 * MB, "ws_bytes": 64 * MB}, ["gate", "routed"]), (400, 0, {"x": 16 * MB - 102400, "f32": 1}, ["gate", "routed"]), (400, 0, {"x": 16 * MB - 102384, "f32": 1}, SEQUENCE),
+    # the ids, the map, the gate's weights
+    (100, 1, {"ids": 16 * MB + 64}, SEQUENCE), (1000, 0, {"ids": 16 * MB + 64}, SEQUENCE), (100, 0, {"ids": 8 * MB}, ["gate", "routed"]), (100, 1, {"map": 17 * MB - 4}, SEQUENCE),
+    (1000, 0, {"map": 17 * MB - 4}, SEQUENCE), (1000, 0, {"map": 8 * MB}, ["gate", "routed"]), (8, 1, {"w_gate": 16 * MB}, ["gate", "routed"])])
+def test_a_layer_is_calls_in_sequence_where_what_they_read_lies_in_the_workspace(layer, T, fused, moved, calls):
+    """A first contraction that sorts reads x and the ids while hidden activations are written, where the calls in sequence have read them before."""
+    assert layer(T=T, fused=fused, **{**BUFFERS, **moved}) == calls
