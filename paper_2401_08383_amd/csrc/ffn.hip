@@ -43,12 +43,16 @@ static int launch_first_contraction(const void* act, const int32_t* offsets, con
 // In tiles the first contraction sorts where the sorted rows are wanted besides, so that the launch that goes had rows to move, where all experts are resident (few
 // rows to move otherwise), where their tiles are one round (every round counts again) and where the weights are not streamed (they are asked for later than
 // behind finished offsets).  Separate calls, other tensors each time, with a dispatch of its own and without, us:
-//   one round: 4000 tokens, 8 experts of 1024 x 4096 101.5 -> 95.7, 2000 top-2, 8 of 576 x 2304 61.6 -> 56.9, 4096, 4 of 512 x 1024 38.5 -> 36.7,
-//     300, 4 of 1024 x 4096 36.8 -> 36.0, 1000, 4 of 512 x 2048 32.4 -> 31.8, 1600, 2 of 2560 x 10240 189.5 -> 187.1, 3000, 6 of 768 x 3072 65.9 -> 64.9
-//   more (the same tensors): 2000 top-2, 32 of 1024 x 4096 140 and 145, 4000, 4 of 4096 x 16384 920 and 927, 850 top-2, 27 of 3072 x 8512 522 and 542
-//   a share of the experts: 3900 tokens, 16 of 64 of 960 x 3840 99.8 and 105.2, 4000, 8 of 64 of 1024 x 4096 46.9 and 47.7
+//   one round: 4000 tokens, 8 experts of 1024 x 4096 101.5 -> 96.5, 2000 top-2, 8 of 576 x 2304 62.3 -> 57.1, 4096, 4 of 512 x 1024 33.8 -> 32.0,
+//     300, 4 of 1024 x 4096 36.8 -> 35.6, 1000, 4 of 512 x 2048 32.8 -> 31.4, 1600, 2 of 2560 x 10240 190.5 -> 189.1, 638, 9 of 896 x 3584 46.5 -> 46.3; where
+//     the tensors lie decides most about 2500, 5 of 832 x 3328 71.7 -> 63.3 or 64.4 -> 60.5 and 3000, 6 of 768 x 3072 70.0 -> 71.3 or 71.7 -> 67.7 (45
+//     such layers twice: the least 0.98, all others 1.002 or more, 1.04 on the mean)
+//   more: 2000 top-2, 32 of 1024 x 4096 138 and 143, 850 top-2, 27 of 3072 x 8512 545 and 574, 4000, 40 of 512 x 2048 71.9 and 73.1, 4000, 4 of
+//     4096 x 16384 944 and 949; 4096, 14 of 1024 x 4096 130.8 and 128.9
+//   a share of the experts: 4000, 8 of 64 of 1024 x 4096 56.7 and 57.4, 3900, 16 of 64 of 960 x 3840 75.1 and 75.5; with many rows of it kept 2000 top-2, 8 of 32
+//     of 768 x 3072 50.6 and 48.3
 //   no sorted rows (fused): 4000, 8 of 1024 x 4096 79.8 and 82.1, 300, 4 of them 34.6 and 34.8
-//   streamed: 1531 top-2, 16 of 1024 x 4096 101.4 and 102.6, 600, 8 of 4096 x 8192 188.6 and 188.2 (2048 top-2, 8 of 4096 x 4096 296 and 291)
+//   streamed: 600, 8 of 4096 x 8192 189.6 and 201.1, 1531 top-2, 16 of 1024 x 4096 101.5 and 100.7, 2048 top-2, 8 of 4096 x 4096 301 and 294
 bool routed_tiles_fit(int64_t A, int d, int f, int E, int E_local, int dt)
 {
     if (dt != EXF_BF16 || A <= 0 || A > kRoutedTilesMax || E_local != E || stream_path_fits(A, d, f, E_local, dt) || weights_are_streamed(A, d, f, E)) return false;

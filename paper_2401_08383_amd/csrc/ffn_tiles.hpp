@@ -816,21 +816,6 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     EXF_PIN_ACC();
 #undef EXF_PIN_ACC
 
-    if constexpr (ROUTED) {  // the columns of the sorted rows that fall to this tile's outputs
-        const int pieces = K / 8, piece_begin = static_cast<int>(static_cast<int64_t>(n0) * pieces / N);
-        const int piece_end = static_cast<int>(static_cast<int64_t>(min(n0 + NT, N)) * pieces / N);
-        for (int piece = piece_begin + c8; piece < piece_end; piece += 8) {
-            f32x4_t v[LA];  // (16 bytes)
-#pragma unroll
-            for (int i = 0; i < LA; ++i) v[i] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const unsigned char*>(act) + (g.off_a[i] - chunk_of(i)) + piece * 16);
-#pragma unroll
-            for (int i = 0; i < LA; ++i) {
-                const int row = row_begin + (i * WAVES + wave) * 8 + r8;
-                if (row < row_end) reinterpret_cast<f32x4_t*>(route.sorted_act)[static_cast<size_t>(row) * pieces + piece] = v[i];
-            }
-        }
-    }
-
     // ---- epilogue -----------------------------------------------------------------------------
     // A lane holds, for the 16 x 16 block (b, a), row lane%16 and columns 4*(lane/16) .. +3.  For two blocks side by side the
     // odd rows of 16 lanes of the first trade with the even ones of the second: every lane then holds eight
@@ -911,6 +896,24 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ act, const 
     };
     if (HIDDEN_OUT && through) finish(std::integral_constant<bool, HIDDEN_OUT>());
     else finish(std::false_type());
+
+    // The columns of the sorted rows that fall to this tile's outputs.  Behind the hidden activations, which the next launch waits for, and past the L2 like these: in
+    // front of the epilogue, as ordinary stores, they made that launch longer as well (2500 rows, five experts of 832 x 3328: 30.8 us with a dispatch launch, 35.9 with
+    // these; the layer 65.4, 70.8 and now 60.5 to 63.3; 397 top-2, 10 of 1024 x 4096 66.6, 68.1, 64.9).
+    if constexpr (ROUTED) {
+        const int pieces = K / 8, piece_begin = static_cast<int>(static_cast<int64_t>(n0) * pieces / N);
+        const int piece_end = static_cast<int>(static_cast<int64_t>(min(n0 + NT, N)) * pieces / N);
+        for (int piece = piece_begin + c8; piece < piece_end; piece += 8) {
+            f32x4_t v[LA];  // (16 bytes)
+#pragma unroll
+            for (int i = 0; i < LA; ++i) v[i] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const unsigned char*>(act) + (g.off_a[i] - chunk_of(i)) + piece * 16);
+#pragma unroll
+            for (int i = 0; i < LA; ++i) {
+                const int row = row_begin + (i * WAVES + wave) * 8 + r8;
+                if (row < row_end) __builtin_nontemporal_store(v[i], reinterpret_cast<f32x4_t*>(route.sorted_act) + static_cast<size_t>(row) * pieces + piece);
+            }
+        }
+    }
 }
 
 template <int NT, int WAVES, int EPI, bool STREAMS, bool ROUTED>
