@@ -78,9 +78,9 @@ struct InlineDispatch {
     int offs[EXF_MAX_EXPERTS + 1];
     unsigned short seg[kInlineSegments][EXF_MAX_EXPERTS];  // count, then start inside its expert's bucket
 };
-// dropped(a): assignment a is not kept (by the one thread that has it).
-template <int THREADS, typename Dropped>
-__device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDispatch& d, bool publish, Dropped dropped)
+// each(a, dropped): of every assignment and, to fill its wavefront, of some past the end (not dropped), by all lanes of the wavefront that has it.
+template <int THREADS, typename Each>
+__device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDispatch& d, bool publish, Each each)
 {
     constexpr int WAVES = THREADS / kWave, R = kInlineDispatchMax / THREADS;
     const int lane = lane_id();
@@ -144,7 +144,7 @@ __device__ __forceinline__ void sort_assignments(const StreamGemm& p, InlineDisp
             if (publish) p.src_of_sorted[pos] = a;
         }
         if (publish && a < A) p.sorted_of_src[a] = pos;
-        if (a < A && pos < 0) dropped(a);
+        each(a, a < A && pos < 0);
     }
     __syncthreads();
 }
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const StreamGemm p)
         const int32_t* offsets = p.offsets;
         if constexpr (ROWS == kRowsInline) {
             InlineDispatch* d = reinterpret_cast<InlineDispatch*>(smem + stream_ring_bytes(C8, W) + W * kStreamIdBytes);
-            sort_assignments<W * kWave>(p, *d, blockIdx.x == 0, [](int) {});
+            sort_assignments<W * kWave>(p, *d, blockIdx.x == 0, [](int, bool) {});
             list = d->list;
             offsets = d->offs;
         }
@@ -927,7 +927,7 @@ __global__ __launch_bounds__(WK* WI * 64) void exact_gemm_kernel(const StreamGem
     const int32_t *a_row = p.a_row, *offsets = p.offsets;
     if constexpr (INLINE) {
         InlineDispatch* d = reinterpret_cast<InlineDispatch*>(red + WI * SLOTS * TILE_ROWS * RS);
-        sort_assignments<WK * WI * kWave>(p, *d, blockIdx.x == 0, [](int) {});
+        sort_assignments<WK * WI * kWave>(p, *d, blockIdx.x == 0, [](int, bool) {});
         a_row = d->list;
         offsets = d->offs;
     }
@@ -1218,9 +1218,16 @@ __global__ __launch_bounds__(kPairWaves * 64, 8) void exact_pair_kernel(const St
     const int32_t *a_row = p.a_row, *out_row = q.out_row, *offsets = p.offsets;
     if constexpr (INLINE) {
         InlineDispatch* sort = reinterpret_cast<InlineDispatch*>(pair_smem + pair_floats(d, f));
-        sort_assignments<kPairWaves * kWave>(p, *sort, blockIdx.x == 0, [&](int a) {
-            if (q.unrouted == nullptr || static_cast<unsigned>(a) % gridDim.x != blockIdx.x) return;
-            for (int c = 0; c < d / 4; ++c) reinterpret_cast<uint4*>(q.out)[static_cast<size_t>(a) * (d / 4) + c] = make_uint4(0u, 0u, 0u, 0u);
+        // Every workgroup clears its share of the rows that are dropped, a wavefront a row (by the one thread that has the
+        // assignment 1000 tokens, 2 of 16 experts of 64 x 256 took 15.9 us and take 14.7; 1024 without an expert here, 468 x 564 19.2 and 10.8).
+        sort_assignments<kPairWaves * kWave>(p, *sort, blockIdx.x == 0, [&](int a, bool dropped) {
+            if (q.unrouted == nullptr) return;
+            unsigned long long todo = __ballot(dropped && static_cast<unsigned>(a) % gridDim.x == blockIdx.x);
+            while (todo != 0) {
+                uint4* row = reinterpret_cast<uint4*>(q.out) + static_cast<size_t>(a - lane + __builtin_ctzll(todo)) * (d / 4);
+                todo &= todo - 1;
+                for (int c = lane; c < d / 4; c += kWave) row[c] = make_uint4(0u, 0u, 0u, 0u);
+            }
         });
         a_row = sort->list;
         if (out_row != nullptr) out_row = sort->list;

@@ -302,7 +302,10 @@ def test_exact_layer_in_one_launch(T, k, E, E_local, fused, routing, d, f):
 # lists that are sorted by the one launch: the longest, tiles of one row and of 16, invalid ids and tokens without an expert here, also all of them
 @pytest.mark.parametrize("T,k,E,E_local,fused,routing,d,f", [
     (1024, 1, 8, 8, True, "gate", 64, 256), (1023, 1, 64, 64, True, "ids", 4, 4), (1000, 1, 9, 4, True, "ids", 36, 20), (512, 1, 1, 1, True, "gate", 32, 128),
-    (700, 1, 14, 14, False, "ids", 44, 300), (1024, 1, 9, 9, True, "dropped", 60, 64), (512, 2, 8, 8, False, "gate", 64, 256), (500, 2, 7, 3, False, "ids", 12, 68)])
+    (700, 1, 14, 14, False, "ids", 44, 300), (1024, 1, 9, 9, True, "dropped", 60, 64), (512, 2, 8, 8, False, "gate", 64, 256), (500, 2, 7, 3, False, "ids", 12, 68),
+    # rows of several wavefronts' width that are cleared; a share of the experts
+    (900, 1, 29, 29, True, "ids", 468, 564), (1024, 1, 29, 29, False, "dropped", 468, 564), (1000, 1, 16, 2, True, "ids", 64, 256), (999, 1, 16, 1, False, "gate", 64, 256),
+    (900, 1, 58, 29, True, "ids", 468, 564)])
 def test_exact_layer_that_sorts_in_one_launch(T, k, E, E_local, fused, routing, d, f):
     _say(f"fp32 layer T={T} k={k} E={E} E_local={E_local} fused={fused} {routing} {d} x {f}")
     _layer_against_calls(T, k, E, E_local, "f32", fused, routing, d, f, () if fused else ("x_sorted", "y_sorted"))
