@@ -120,7 +120,7 @@ bool stream_path_fits(int64_t A, int d, int f, int E_local, int dt);
 int launch_stream_gemm(const StreamGemm& g, int dt, hipStream_t stream);
 // fp32: are both contractions one launch, and that launch (out of the first one is not written).
 bool exact_pair_fits(int64_t A, int d, int f, int E_local);
-bool exact_pair_routed_fits(int64_t A, int d, int f, int E_local);  // (that sorts; its rows do not meet, see StreamGemm::exchange)
+bool exact_pair_routed_fits(int64_t A, int d, int f, int E, int E_local);  // (that sorts; its rows do not meet, see StreamGemm::exchange)
 int launch_exact_pair(const StreamGemm& first, const StreamGemm& second, hipStream_t stream);
 // Bytes [a, a + n) and [b, b + m) have none in common (a null pointer: there are none).
 inline bool lie_apart(const void* a, size_t n, const void* b, size_t m)
@@ -150,9 +150,11 @@ inline bool pair_lies_apart(const StreamGemm& first, const StreamGemm& second)
 }
 inline int launch_stream_pair(const StreamGemm& first, const StreamGemm& second, int dt, hipStream_t stream)
 {
-    auto fits = first.topk_idx != nullptr ? exact_pair_routed_fits : exact_pair_fits;
-    if (dt == EXF_F32 && first.exchange == nullptr && fits(first.max_rows, first.K, first.N, first.E_local) && pair_lies_apart(first, second))
-        return launch_exact_pair(first, second, stream);
+    if (dt == EXF_F32 && first.exchange == nullptr) {
+        const bool fits = first.topk_idx != nullptr ? exact_pair_routed_fits(first.max_rows, first.K, first.N, first.E, first.E_local)
+                                                    : exact_pair_fits(first.max_rows, first.K, first.N, first.E_local);
+        if (fits && pair_lies_apart(first, second)) return launch_exact_pair(first, second, stream);
+    }
     const int rc = launch_stream_gemm(first, dt, stream);
     return rc == EXF_OK ? launch_stream_gemm(second, dt, stream) : rc;
 }

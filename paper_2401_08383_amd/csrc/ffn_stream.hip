@@ -1361,13 +1361,20 @@ bool exact_pair_fits(int64_t A, int d, int f, int E_local)
 }
 
 // Lists that are sorted on the way: sorting takes the same time in either, and so few tiles leave most compute units idle, so where the model has this launch
-// ahead.  Whole layers with two and one, us: 1024 tokens, 8 experts of 64 x 256 15.8 and 13.5; 512, 8 of 64 x 128 12.7 and 11.3; 512, 4 of 32 x 128
-// 12.2 and 10.6; 700, 14 of 44 x 300, separate calls 15.2 and 14.1; 900, 16 of 92 x 252 16.2 and 15.4; not 512, 8 of 64 x 256 13.3 and 13.4; 100 of
+// ahead.  Whole layers with two and one, us: 1024 tokens, 8 experts of 64 x 256 15.6 and 13.5; 512, 8 of 64 x 128 12.7 and 11.3; 512, 4 of 32 x 128
+// 12.2 and 10.6; 700, 14 of 44 x 300, separate calls 15.3 and 14.1; 900, 29 of 468 x 564 74.7 and 69.6; not 512, 8 of 64 x 256 13.3 and 13.4; 100 of
 // these 11.9 and 13.2; 512, 8 of 128 x 256 15.3 and 16.3; 512, 8 of 256 x 512 20.9 and 37.3.
-bool exact_pair_routed_fits(int64_t A, int d, int f, int E_local)
+// With a share of the experts nobody here knows how many rows are kept.  Fewer rows shorten two launches and not the one, whose tiles take as long each, but two
+// have the other rows cleared by a few wavefronts in front of the second one's products, which takes at least kClearing.  So the model has to have the
+// one ahead with all rows kept and, but for that, with the experts' share of them: 1000 tokens, 2 of 16 of 64 x 256 18.4 and 14.7; 512, 2 of 8 of 32 x 128 15.0 and
+// 10.7; 900, 16 of 32 of 92 x 252 19.1 and 17.7; 700, 7 of 56 of 44 x 300, separate calls 23.1 and 19.2; not 900, 29 of 58 of 468 x 564 59.7 and 75.9.
+constexpr double kClearing = 2.0;
+bool exact_pair_routed_fits(int64_t A, int d, int f, int E, int E_local)
 {
-    return A <= kInlineDispatchMax && pair_floats(d, f) * sizeof(float) + sizeof(InlineDispatch) <= 160 * 1024 &&
-           exact_both_cost(A, d, f, E_local) >= exact_pair_cost(A, d, f, E_local);
+    if (A > kInlineDispatchMax || pair_floats(d, f) * sizeof(float) + sizeof(InlineDispatch) > 160 * 1024) return false;
+    if (exact_both_cost(A, d, f, E_local) < exact_pair_cost(A, d, f, E_local)) return false;
+    const int64_t share = A * E_local >= E ? A * E_local / E : 1;
+    return share >= A || exact_both_cost(share, d, f, E_local) + kClearing >= exact_pair_cost(share, d, f, E_local);
 }
 
 template <bool INLINE>

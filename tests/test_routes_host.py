@@ -16,7 +16,7 @@ PAIR = r"""
 #include "ffn_common.hpp"
 namespace exf {
 bool exact_pair_fits(int64_t, int, int, int) { return true; }
-bool exact_pair_routed_fits(int64_t, int, int, int) { return true; }
+bool exact_pair_routed_fits(int64_t, int, int, int, int) { return true; }
 int launch_exact_pair(const StreamGemm&, const StreamGemm&, hipStream_t) { puts("one"); return 0; }
 int launch_stream_gemm(const StreamGemm&, int, hipStream_t) { puts("two"); return 0; }
 }
@@ -85,8 +85,19 @@ int main(int argc, char** argv)
 }
 """
 
+RULE = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "ffn_stream.hip"
+int main(int, char** argv)
+{
+    auto n = [&](int i) { return atoi(argv[2 * i]); };
+    return puts(exf::exact_pair_routed_fits(n(1), n(2), n(3), n(4), n(5)) ? "one" : "two") < 0;
+}
+"""
 
-def _compile(tmp, name, text):
+
+def _compile(tmp, name, text, link=()):
     if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
         pytest.skip("no hipcc")
     src, exe = str(tmp / (name + ".cpp")), str(tmp / name)
@@ -94,7 +105,7 @@ def _compile(tmp, name, text):
         f.write(text)
     csrc = os.path.join(ROOT, "paper_2401_08383_amd", "csrc")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-x", "hip", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                    "-I", os.path.join(ROOT, "include"), "-I", csrc, src, "-o", exe], check=True, capture_output=True)
+                    "-I", os.path.join(ROOT, "include"), "-I", csrc, src, "-o", exe, *link], check=True, capture_output=True)
 
     def run(**values):
         args = [w for k, v in values.items() for w in (k, str(v))]
@@ -148,3 +159,16 @@ SEQUENCE = ["gate", "dispatch", "ffn"]
 def test_a_layer_is_calls_in_sequence_where_what_they_read_lies_in_the_workspace(layer, T, fused, moved, calls):
     """A first contraction that sorts reads x and the ids while hidden activations are written, where the calls in sequence have read them before."""
     assert layer(T=T, fused=fused, **{**BUFFERS, **moved}) == calls
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    return _compile(tmp_path_factory.mktemp("rule"), "rule", RULE, ("-Wl,--unresolved-symbols=ignore-all",))
+
+
+@pytest.mark.parametrize("A,d,f,E,E_local,launches", [
+    (1024, 64, 256, 8, 8, "one"), (512, 64, 256, 8, 8, "two"), (900, 468, 564, 29, 29, "one"), (900, 468, 564, 58, 29, "two"), (1000, 64, 256, 16, 2, "one"),
+    (1000, 64, 256, 16, 1, "one"), (512, 32, 128, 8, 2, "one"), (700, 44, 300, 56, 7, "one"), (900, 92, 252, 32, 16, "one"), (1025, 64, 256, 8, 8, "two")])
+def test_one_launch_of_a_share_of_the_experts(rule, A, d, f, E, E_local, launches):
+    """Not where the rows that are dropped shorten two launches by more than clearing them costs."""
+    assert rule(A=A, d=d, f=f, E=E, E_local=E_local) == [launches]
