@@ -12,19 +12,27 @@
 
 namespace exf {
 
-// Launches in which some experts have a single row tile, whose weights nobody else reads, and are many enough not to stay in the
-// memory-side cache of 256 MB between two calls (both contractions of 2^26 weights): those tiles load them with the streaming hint.
-// us without and with it, the same weights from call to call / other ones each time:
-//   tokens, experts                     fits the cache?
-//   1200, 16 of 4096 x 16384            no    827 / 852 -> 730 / 752 (both begin the reduction at different places)
-//   6000, 64 of 2048 x 8192             no    835 / 866 -> 761 / 788
-//   600, 4 of 2560 x 10240              no    161 / 162 -> 144 / 160
-//   1500, 16 of 2048 x 8192             no    217 / 214 -> 206 / 197
-//   1531 top-2, 16 of 1024 x 4096       no    98.3 -> 96.6 / 102.4 -> 102.2
-//   800, 10 of 1024 x 4096              yes   51.8 / 60.4 -> 59.6 / 58.2
-//   600, 16 of 768 x 3072               yes   39.4 / 46.1 -> 43.1 / 43.5
-// Up to 1024 rows an expert on the mean: beyond, routing as uneven as Zipf's leaves no expert below 256 (16384 tokens, 32 of 2048 x 8192,
-// 512 on the mean, 1107 -> 1096 us).
+// Launches in which some experts have a single row tile, whose weights nobody else reads, and are too many to stay in the
+// memory-side cache of 256 MB from call to call (268 MB in both contractions): those tiles load them with the streaming hint.
+// us without and with it, the same weights from call to call / other ones each time, as in a model of several layers:
+//   tokens, experts                    weights
+//   1000, 10 of 1024 x 4096             42 M   54.2 and 61.7 / 62.5 and 60.6
+//   1500, 15 of 1024 x 4096             63 M   62.1 and 70.2 / 71.5 and 67.8
+//   6000, 60 of 512 x 2048              63 M   76.4 and 83.7 / 85.4 and 81.8
+//   6400, 64 of 512 x 2048              67 M   80.6 -> 87.3 / 87.8 -> 83.3
+//   1600, 16 of 1024 x 4096             67 M   65.4 -> 66.3 / 72.5 -> 68.6
+//   2000, 20 of 1024 x 4096             84 M   93.5 -> 96.4 / 95.0 -> 91.3
+//   2400, 24 of 1024 x 4096            101 M   109.9 -> 109.6 / 105.8 -> 101.4
+//   600, 4 of 2560 x 10240             105 M   161 -> 144 / 162 -> 160
+//   1500, 16 of 2048 x 8192            268 M   217 -> 206 / 214 -> 197
+//   6000, 64 of 2048 x 8192           1074 M   835 -> 761 / 866 -> 788
+//   1200, 16 of 4096 x 16384          1074 M   827 -> 730 / 852 -> 752 (both begin the reduction at different places)
+// Other weights each time gain from 33 M on; called again with the same ones, layers below the line lose up to 15 % by it, up to 84 M at most 8 % (the cache still has
+// some of them), beyond nothing.
+// The line in rows is where nothing is left to gain or lose, routing as uneven as Zipf's (it leaves some experts one row tile far beyond it, which are then a small
+// part of the launch).  us without and with the hint by rows an expert on the mean, 16 experts of 1024 x 4096: 256 127.3 -> 124.7, 512 182.5 -> 181.8, 1024
+// 307.1 -> 307.4, 1536 446.3 and 447.3, 2048 549.1 and 551.8; 64 of 1024 x 1024: 256 142.1 -> 139.4, 512 201.9 -> 200.0, 1024 355.9 -> 358.6, 1536 520.4
+// and 521.1, 2048 674.0 and 676.6.
 constexpr int64_t kStreamedWeights = 1ll << 26;
 constexpr int64_t kStreamedMeanRows = 1024;
 static bool weights_are_streamed(int64_t A, int K, int N, int E_local)

@@ -95,8 +95,9 @@ struct RoutedSort {
 // remainder is larger there is one tile more, all of one height.  most = 1, or 2 where the launch then has fewer rounds of
 // tiles (see plan_tiles).  An expert of at most 128 rows has one small tile.  Heights of a tile: 64 and 128 (small), 192, 224,
 // 256, 288, 320; of a piece of one (see locate_tile) 64, 96, 128 and 160 besides.  160 instead of 192 and
-// 224 instead of 256 (`by160`, `by224`) in launches of more tiles than half the compute units, whose only round's tiles are whole: the tallest one is the
-// time.  160 where no expert of a single round has more rows, or in several rounds.  Experts of up to 160 rows in 192 and in 160: 1000 tokens, 8 experts of
+// 224 instead of 256 (`by160`, `by224`) in launches of more tiles than half the compute units: the tallest whole tile of the only round is the
+// time (from 136 tiles on all are whole; of 129 to 135 the XCDs that have 17 keep them whole, the others cut theirs in two: 22 layers of 129 to 135 tiles, 150 and 210
+// rows an expert, 41 to 66 us, 2 to 6 % faster than with the line at 136).  160 where no expert of a single round has more rows, or in several rounds.  Experts of up to 160 rows in 192 and in 160: 1000 tokens, 8 experts of
 // 2048 x 8192 131.9 -> 122.9 us, 1100, 8 of 1536 x 6144 97.4 -> 92.0, 2200, 16 of 2048 x 8192 236 -> 222, 8600, 60 of 2048 x 8192 867 -> 839; with a
 // taller one among them 1150, 8 of 2048 x 8192 132.5 and 134.8.  Up to 224 rows in 256 and in 224: 3000, 16 of 1024 x 4096 85.5 -> 82.7; 3360, 8 of
 // 2048 x 8192 247 -> 234; 12000, 60 of 2048 x 8192 999 -> 979; 1531 top-2, 16 of 1024 x 4096 96.6 -> 95.8.  In up to half as many tiles as compute
@@ -410,7 +411,8 @@ __device__ __forceinline__ bool locate_tile(const RowRange& range, int NT, int N
     // panels in their L2, stay in step - but where much weight is streamed for experts of one or two row tiles: their activations fit the L2 as
     // a whole, and every column tile has a place of its own (its row tiles and pieces, which share weights, stay together).  1200 tokens,
     // 16 experts of 4096 x 16384 858 -> 747 us, 4000 1361 -> 1221; two row tiles: 4000 of 8 1064 -> 1042, 5000 of 16 of 2048 x 8192 447 -> 441;
-    // less weight: 2500 of 8 of 1024 x 4096 61.5 and 62.2.
+    // less weight: 2500 of 8 of 1024 x 4096 61.5 and 62.2.  The place decides the order of the fp32 sums and so the last bit of some results, not
+    // their error: against 64 bits 2.349e-3 of the result with and without (16384 skewed tokens, 32 of 2048 x 8192).
     out.turn = xcd * kUnitsPerXcd;
     if (STREAMS && e_rt <= 2) out.turn += col_tile % kUnitsPerXcd;
     out.turn = __builtin_amdgcn_readfirstlane(out.turn);
