@@ -223,6 +223,15 @@ def test_grouped_ffn_streamed_weights(oracle, counts, d, f):
     P._ffn_case(oracle, "bf16", counts, d, f, 0, False, seed=1795, rows=sample_rows(offsets, 1, 1796))
 
 
+@pytest.mark.parametrize("counts,d,f,act,bias", [
+    ([1, 64, 65, 128, 160, 193, 224, 256, 257, 288, 700, 0] + [30] * 52, 1024, 1024, 1, True), ([70, 33, 250, 140], 2048, 8192, 1, False), ([129, 33, 300, 192], 2048, 8192, 0, True)])
+def test_grouped_ffn_streamed_weights_of_either_activation(oracle, counts, d, f, act, bias):
+    """The tanh form, and biases with either, in the instances that stream."""
+    _say(f"streamed weights {len(counts)} experts {d} x {f} act={act} bias={bias}")
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    P._ffn_case(oracle, "bf16", counts, d, f, act, bias, seed=1797 + act, rows=sample_rows(offsets, 1, 1798))
+
+
 @pytest.mark.parametrize("T,k,E,E_local,routing", [(3000, 1, 64, 64, "gate"), (2500, 2, 64, 64, "ids"), (33000, 1, 64, 64, "gate")])
 def test_streamed_weights_of_a_layer(T, k, E, E_local, routing):
     """The layer and its calls, fused and not; 256 columns a tile in the second contraction (the last)."""
@@ -425,6 +434,16 @@ def test_layer_that_sorts_in_tiles_is_its_calls(T, k, E, E_local, routing, d, f)
     _layer_against_calls(T, k, E, E_local, "bf16", False, routing, d, f, ("x_sorted", "y_sorted"))
 
 
+# every expert resident and a map all the same: another order of them, and one that drops an expert's tokens and gives two others one expert; either activation
+@pytest.mark.parametrize("T,k,E,dtype,routing,d,f,act,mapped", [
+    (300, 1, 8, "bf16", "gate", 128, 576, 1, "permuted"), (700, 1, 9, "bf16", "ids", 64, 192, 0, "shared"), (2047, 2, 64, "bf16", "gate", 64, 192, 0, "permuted"),
+    (2048, 2, 12, "bf16", "ids", 192, 1344, 1, "shared"), (4096, 1, 3, "bf16", "gate", 320, 1088, 1, "shared"), (257, 1, 1, "bf16", "ids", 64, 64, 1, "permuted"),
+    (1024, 1, 8, "f32", "gate", 64, 256, 1, "permuted"), (1000, 1, 14, "f32", "ids", 44, 300, 0, "shared")])
+def test_layer_that_sorts_by_a_map_of_resident_experts(T, k, E, dtype, routing, d, f, act, mapped):
+    _say(f"layer with a {mapped} map T={T} k={k} E={E} {dtype} {routing} {d} x {f} act={act}")
+    _layer_against_calls(T, k, E, E, dtype, False, routing, d, f, ("x_sorted", "y_sorted"), act=act, mapped=mapped)
+
+
 # top-2 layers whose two rows of a token meet in the second contraction: up to eight rows, up to 64 and up to 1024; blocks of 8 to 64 columns and
 # tiles of one and several row groups; tokens of which one or both assignments are dropped, and with the same expert twice ("ids"); the last
 # shape of the separate calls that gets by with the reserved 16 MiB, the first that does not, and weights past the line
@@ -480,7 +499,7 @@ def test_top2_rows_of_nans_meet(T, dtype, fused):
         assert torch.equal(look(), first)
 
 
-def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f, more=()):
+def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f, more=(), act=0, mapped=None):
     from paper_2401_08383_amd.pipeline import MoELayerRun
 
     g = torch.Generator(device="cuda")
@@ -494,12 +513,16 @@ def _layer_against_calls(T, k, E, E_local, dtype, fused, routing, d, f, more=())
     if E_local < E:
         expert_map = torch.full((E,), -1, dtype=torch.int32, device="cuda")
         expert_map[torch.randperm(E, device="cuda", generator=g)[:E_local]] = torch.arange(E_local, dtype=torch.int32, device="cuda")
+    elif mapped is not None:
+        expert_map = torch.randperm(E, device="cuda", generator=g).int()
+        if mapped == "shared":
+            expert_map[0], expert_map[1] = -1, expert_map[2]
     idx = None
     if routing == "ids":
         idx = torch.randint(-1, E + 2, (T, k), device="cuda", generator=g, dtype=torch.int32)  # invalid ids among them
     elif routing == "dropped":
         idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
-    run = MoELayerRun(rnd(T, d), rnd(E, d), rnd(E_local, f, d), rnd(E_local, d, f), k, k > 1, expert_map=expert_map, topk_idx=idx, fused=fused)
+    run = MoELayerRun(rnd(T, d), rnd(E, d), rnd(E_local, f, d), rnd(E_local, d, f), k, k > 1, expert_map=expert_map, topk_idx=idx, act=act, fused=fused)
     names = ["topk_idx", "topk_w", "src_of_sorted", "sorted_of_src", "expert_counts", "expert_offsets", "out", *more]
 
     def results(how):
